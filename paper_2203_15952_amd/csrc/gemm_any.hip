@@ -1,0 +1,894 @@
+// The contractions of the quantized dense layer for any shape (arxiv 2203.15952, Sec. 1 and Sec. 2.2; the
+// straight-through backward; Sec. 4.1 for the weight-only modes): sizes that no tile of the tuned kernels in
+// gemm_fwd.hip / gemm_bwd.hip divides, and problems too small to fill the chip with their tiles.
+//
+// All kernels work straight from the caller's tensors (no re-ordered operand, no pre-pass).  A workgroup is
+// WM x WN wavefronts side by side, times WK groups of them that share one output tile and take turns along the
+// contraction.  Each group brings a slice of its tile's rows through registers into LDS, whole 64- or 128-byte
+// row pieces at a time, converts what has to be converted there once for all its wavefronts, and multiplies while
+// the next two slices' loads are in flight.  (Fragments fetched straight from memory, one row per lane, were tried
+// first: rows a power of two apart share a cache set and every access misses; dX 40 x 2048 -> 512 took 20 us
+// that way, 10 us this way.)  Small problems (WK = 8, one wavefront per group) are bound by the latency of a trip to
+// memory, so eight slices are in flight at a time; the sums are added up through LDS.
+// Measured at 4099 x 520 x 1000, int8 codes, against the one-thread-per-output kernels these replace: forward 18 us
+// (7902), dX 37 (6565), dW with its fold 50 (1096); forward 40 x 512 -> 2048 3.3 us (about 170).
+//
+// Edges: rows and columns beyond the tensors are read at clamped, valid addresses and not stored; contraction
+// positions beyond the end are zeros, the pieces that straddle it are loaded element by element.
+#include <type_traits>
+
+#include "aqt_internal.h"
+#include "epilogue.h"
+
+namespace aqt {
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+
+template <class T>
+__device__ __forceinline__ T load_at(const void *p) {   // any byte alignment
+  T v;
+  __builtin_memcpy(&v, p, sizeof(T));
+  return v;
+}
+
+__device__ __forceinline__ bool mask_bit(const uint32_t *__restrict__ mask, int64_t i) {
+  return (mask[i >> 5] >> (i & 31)) & 1u;
+}
+
+// Up to 16 bytes at p + at, at + 16 <= end; beyond `end` zeros.
+__device__ __forceinline__ v4i load16_guarded(const uint8_t *p, int64_t at, int64_t end) {
+  if (at + 16 <= end) return load_at<v4i>(p + at);
+  uint32_t d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    if (at + e < end) d[e >> 2] |= static_cast<uint32_t>(p[at + e]) << (8 * (e & 3));
+  return v4i{static_cast<int>(d[0]), static_cast<int>(d[1]), static_cast<int>(d[2]), static_cast<int>(d[3])};
+}
+
+// LDS rows are CH chunks of 16 bytes without padding; the chunk index is XORed with row bits so that the rows
+// of a fragment read spread over all banks.
+template <int CH>
+__device__ __forceinline__ int swz(int row) {
+  return CH >= 8 ? (row & 7) : CH == 4 ? ((row >> 1) & 3) : ((row >> 2) & 1);
+}
+template <int CH>
+__device__ __forceinline__ int chunk_at(int row, int chunk) { return row * (CH * 16) + ((chunk ^ swz<CH>(row)) << 4); }
+
+// Eight int4 codes in memory order (low nibble first) -> eight bytes 16 * code, in order.
+__device__ __forceinline__ v2i expand16(uint32_t w) {
+  const uint32_t even = (w << 4) & 0xF0F0F0F0u, odd = w & 0xF0F0F0F0u;
+  v2i o;
+  o.x = static_cast<int>(__builtin_amdgcn_perm(odd, even, 0x05010400u));
+  o.y = static_cast<int>(__builtin_amdgcn_perm(odd, even, 0x07030602u));
+  return o;
+}
+
+// The slice loop of a workgroup.  load(set, slice) requests a slice into register set 0 or 1, stage(set, slot)
+// moves that set to LDS, multiply(slot) consumes it.
+//   WK == 1: all wavefronts share the slices; two LDS slots, so that a slice is staged (and converted) while the one
+//            before it is multiplied, one barrier per slice, loads two slices ahead.
+//   WK > 1:  every wavefront has its own slices wk, wk + WK, ... and its own slot: its LDS operations are executed
+//            in order, so no barrier is needed and the wavefronts overlap as they come.
+template <int WK, class Load, class Stage, class Multiply>
+__device__ __forceinline__ void run_slices(uint8_t *lds, int slice_bytes, int wk, int64_t slices, Load load, Stage stage,
+                                           Multiply multiply) {
+  constexpr std::integral_constant<int, 0> set0{};
+  constexpr std::integral_constant<int, 1> set1{};
+  if (WK > 1) {
+    uint8_t *const slot = lds + wk * slice_bytes;
+    if (wk < slices) load(set0, wk);
+    if (wk + WK < slices) load(set1, wk + WK);
+    auto one = [&](auto set, int64_t s) {
+      __builtin_amdgcn_wave_barrier();
+      stage(set, slot);
+      if (s + 2 * WK < slices) load(set, s + 2 * WK);
+      __builtin_amdgcn_wave_barrier();
+      multiply(slot);
+    };
+    for (int64_t s = wk; s < slices; s += 2 * WK) {
+      one(set0, s);
+      if (s + WK < slices) one(set1, s + WK);
+    }
+    return;
+  }
+  uint8_t *const slot0 = lds, *const slot1 = lds + slice_bytes;
+  load(set0, 0);
+  if (1 < slices) load(set1, 1);
+  stage(set0, slot0);
+  if (2 < slices) load(set0, 2);
+  __syncthreads();
+  for (int64_t s = 0; s < slices; s += 2) {
+    if (s + 1 < slices) {
+      stage(set1, slot1);
+      if (s + 3 < slices) load(set1, s + 3);
+    }
+    multiply(slot0);
+    __syncthreads();
+    if (s + 1 >= slices) break;
+    if (s + 2 < slices) {
+      stage(set0, slot0);
+      if (s + 4 < slices) load(set0, s + 4);
+    }
+    multiply(slot1);
+    __syncthreads();
+  }
+}
+
+// ---- forward: int8 codes x int8 / int4 codes, int32 sums -----------------------------------
+// A wavefront owns TM x TN blocks of 32 x 32; a GLU tile pairs value (even) and gate (odd) column blocks.
+// BK: fan-in positions per slice.
+template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
+    const int8_t *__restrict__ xq, const float *__restrict__ s_x, const uint8_t *__restrict__ wq,
+    const float *__restrict__ s_w, int64_t M, int64_t K, int64_t N, const float *__restrict__ bias,
+    float *__restrict__ y, int32_t *__restrict__ acc_out, uint32_t *__restrict__ y_absmax, float *__restrict__ dact,
+    int tiles_n) {
+  static_assert(16 % WK == 0 && (EPI != AQT_EPI_GLU || TN % 2 == 0), "the epilogue is shared out by registers");
+  constexpr bool GLU = EPI == AQT_EPI_GLU;
+  constexpr int G = 64 * WM * WN;                       // threads of a group
+  constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
+  constexpr int CHA = BK / 16, CHB = PACKED ? BK / 32 : BK / 16;   // 16-byte chunks per row
+  constexpr int NA = BM * CHA / G, NB = BN * CHB / G;   // chunks per thread and slice
+  static_assert(NA * G == BM * CHA && NB * G == BN * CHB && NA > 0 && NB > 0, "whole chunks per thread");
+  constexpr int kSliceBytes = BM * CHA * 16 + BN * CHB * 16;
+  constexpr int kRedBytes = WK > 1 ? WK * TM * TN * 16 * 64 * 4 : 0;
+  constexpr int kBuffers = WK == 1 ? 2 : WK;            // two slots for a shared slice, one per private one
+  constexpr int kLds = kBuffers * kSliceBytes > kRedBytes ? kBuffers * kSliceBytes : kRedBytes;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kLds];
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wk = wave / (WM * WN), wn = wave % WN, wm = (wave / WN) % WM, gt = t - wk * G;
+  const int64_t bm = blockIdx.x / tiles_n, bn = blockIdx.x % tiles_n;
+  const int64_t oc = GLU ? N / 2 : N;
+  // first channel of the tile's column block cb
+  auto chan = [&](int cb) -> int64_t {
+    if (GLU) return bn * (BN / 2) + (cb >> 1) * 32 + ((cb & 1) ? oc : 0);
+    return bn * BN + cb * 32;
+  };
+  const int64_t row_bytes = PACKED ? (K + 1) / 2 : K;
+  const uint8_t *pa[NA], *pb[NB];
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int64_t m = bm * BM + (gt + u * G) / CHA;
+    pa[u] = reinterpret_cast<const uint8_t *>(xq) + (m < M ? m : M - 1) * K;
+  }
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int r = (gt + u * G) / CHB;
+    const int64_t n = chan(r >> 5) + (r & 31);
+    pb[u] = wq + (n < N ? n : N - 1) * row_bytes;
+  }
+  // G is a multiple of the chunks per row: a thread's chunks sit at the same place of their rows
+  const int ca = gt % CHA, cb = gt % CHB;
+  v4i ra[2][NA], rb[2][NB];
+  auto load = [&](auto set, int64_t slice) {
+    constexpr int S = decltype(set)::value;
+    const int64_t at = slice * BK + 16 * ca, bt = slice * (PACKED ? BK / 2 : BK) + 16 * cb;
+    if (at + 16 <= K) {
+#pragma unroll
+      for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4i>(pa[u] + at);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NA; ++u) ra[S][u] = load16_guarded(pa[u], at, K);
+    }
+    if (bt + 16 <= row_bytes) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) rb[S][u] = load_at<v4i>(pb[u] + bt);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) rb[S][u] = load16_guarded(pb[u], bt, row_bytes);
+    }
+  };
+  v16i acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+  const int64_t slices = cdiv(K, BK);
+  // slot: where a slice lives in LDS (its A rows, then its B rows)
+  auto stage = [&](auto set, uint8_t *slot) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int u = 0; u < NA; ++u) *reinterpret_cast<v4i *>(slot + chunk_at<CHA>((gt + u * G) / CHA, ca)) = ra[S][u];
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+      *reinterpret_cast<v4i *>(slot + BM * CHA * 16 + chunk_at<CHB>((gt + u * G) / CHB, cb)) = rb[S][u];
+  };
+  auto multiply = [&](const uint8_t *slot) {
+    const uint8_t *const sA = slot, *const sB = slot + BM * CHA * 16;
+#pragma unroll
+    for (int kk = 0; kk < BK / 32; ++kk) {
+      v4i a[TM];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        a[i] = *reinterpret_cast<const v4i *>(sA + chunk_at<CHA>((wm * TM + i) * 32 + lr, 2 * kk + lk));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        v4i b;
+        if (PACKED) {
+          const v2i w = *reinterpret_cast<const v2i *>(sB + chunk_at<CHB>((wn * TN + j) * 32 + lr, kk) + 8 * lk);
+          const v2i lo = expand16(static_cast<uint32_t>(w.x)), hi = expand16(static_cast<uint32_t>(w.y));
+          b = v4i{lo.x, lo.y, hi.x, hi.y};
+        } else {
+          b = *reinterpret_cast<const v4i *>(sB + chunk_at<CHB>((wn * TN + j) * 32 + lr, 2 * kk + lk));
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b, acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+  run_slices<WK>(lds, kSliceBytes, wk, slices, load, stage, multiply);
+
+  // The groups of a tile add their sums (integers: any order) and share the epilogue: each takes 16 / WK of the
+  // accumulator registers.
+  constexpr int RW = 16 / WK;
+  int *const red = reinterpret_cast<int *>(lds);
+  static_assert(WK == 1 || WM * WN == 1, "the sums of a split contraction are kept per wavefront");
+  if (WK > 1) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[(((wk * TM + i) * TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+  }
+  auto sum_of = [&](int i, int j, int rr) -> int {   // register wk * RW + rr
+    int v;
+    if (WK > 1) {
+      v = 0;
+#pragma unroll
+      for (int w = 0; w < WK; ++w) v += red[(((w * TM + i) * TN + j) * 16 + wk * RW + rr) * 64 + lane];
+    } else {
+      v = acc[i][j][rr];
+    }
+    return PACKED ? (v >> 4) : v;
+  };
+  const float sx = s_x[0];
+  uint32_t amax = 0u;
+  constexpr int JS = GLU ? 2 : 1;
+#pragma unroll
+  for (int j = 0; j < TN; j += JS) {
+    const int64_t n = chan(wn * TN + j) + lr;
+    const bool live = n < oc;
+    const int64_t nc = live ? n : oc - 1, ng = nc + (GLU ? oc : 0);
+    const float sc_a = sx * s_w[nc], bias_a = bias ? bias[nc] : 0.0f;
+    const float sc_b = GLU ? sx * s_w[ng] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int rr = 0; rr < RW; ++rr) {
+        const int r = wk * RW + rr;
+        const int64_t m = bm * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+        const int a0 = sum_of(i, j, rr);
+        const int a1 = GLU ? sum_of(i, j + JS - 1, rr) : 0;
+        if (!live || m >= M) continue;
+        if (acc_out) {
+          acc_out[m * N + n] = a0;
+          if (GLU) acc_out[m * N + ng] = a1;
+        }
+        const float v = dequant_f32(a0, sc_a) + bias_a;
+        float out = v;
+        if (EPI == AQT_EPI_SWISH) {
+          const float sg = sigmoid_f32(v);
+          out = v * sg;
+          if (dact) dact[m * N + n] = swish_dact_f32(v, sg);
+        } else if (GLU) {
+          const float sg = sigmoid_f32(dequant_f32(a1, sc_b) + bias_b);
+          out = v * sg;
+          if (dact) {
+            dact[m * N + n] = sg;
+            dact[m * N + ng] = glu_gate_dact_f32(v, sg);
+          }
+        }
+        y[m * oc + n] = out;
+        amax = max(amax, __float_as_uint(out) & 0x7FFFFFFFu);
+      }
+  }
+  if (y_absmax) {   // one atomic per wavefront, and only if it can raise the word (it only grows)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) amax = max(amax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(amax), off)));
+    if (lane == 0 && amax > *reinterpret_cast<volatile uint32_t *>(y_absmax)) atomicMax(y_absmax, amax);
+  }
+}
+
+// ---- float32 operand x codes ------------------------------------------------------------------
+// Codes are exact in bf16; the float operand is carried whole, as three bf16 terms of 8 significant bits each
+// (a = hi + mid + lo exactly), and three v_mfma_f32_32x32x16_bf16 passes form products that are exact in
+// float32.  Sums run in float32 over at most kChain contraction positions and are added up in float64, so a
+// result is the float64 sum to within about one float32 rounding.
+constexpr int kChain = 512;
+constexpr int kSlice = 32;    // contraction positions per slice: LDS rows of 64 bytes
+constexpr int kCh = 4;        // 16-byte chunks of such a row
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even
+  v2f f = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
+}
+__device__ __forceinline__ void split3(float a, float b, int &hi, int &mid, int &lo) {
+  const uint32_t h = pack_bf16(a, b);
+  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
+  const uint32_t m = pack_bf16(ra, rb);
+  const float qa = ra - __uint_as_float(m << 16), qb = rb - __uint_as_float(m & 0xFFFF0000u);
+  hi = static_cast<int>(h); mid = static_cast<int>(m); lo = static_cast<int>(pack_bf16(qa, qb));
+}
+// four floats -> their four bf16 pieces of each of the three images
+__device__ __forceinline__ void store_split(uint8_t *at, int image, v4f v) {
+  v2i h, m, l;
+  int x, y, z;
+  split3(v.x, v.y, x, y, z); h.x = x; m.x = y; l.x = z;
+  split3(v.z, v.w, x, y, z); h.y = x; m.y = y; l.y = z;
+  *reinterpret_cast<v2i *>(at) = h;
+  *reinterpret_cast<v2i *>(at + image) = m;
+  *reinterpret_cast<v2i *>(at + 2 * image) = l;
+}
+__device__ __forceinline__ v16f mfma_bf16(v4i a, v4i b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ v4i codes8_bf16(uint32_t x, uint32_t y) {   // eight int8 codes in order
+  float f[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f[e] = static_cast<float>(static_cast<int8_t>(x >> (8 * e)));
+    f[4 + e] = static_cast<float>(static_cast<int8_t>(y >> (8 * e)));
+  }
+  return v4i{static_cast<int>(pack_bf16(f[0], f[1])), static_cast<int>(pack_bf16(f[2], f[3])),
+             static_cast<int>(pack_bf16(f[4], f[5])), static_cast<int>(pack_bf16(f[6], f[7]))};
+}
+__device__ __forceinline__ v4i nibbles8_bf16(uint32_t w) {   // eight int4 codes, low nibble first
+  float f[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f[e] = static_cast<float>(static_cast<int>(w << (28 - 4 * e)) >> 28);
+  return v4i{static_cast<int>(pack_bf16(f[0], f[1])), static_cast<int>(pack_bf16(f[2], f[3])),
+             static_cast<int>(pack_bf16(f[4], f[5])), static_cast<int>(pack_bf16(f[6], f[7]))};
+}
+
+// out[m, r] = sum_c f[m, c] (* scale[c]) * q[r, c]: rows of both operands contraction-contiguous.
+//   MODE 0 (dX):   f = dy [M,N], scale = s_w, q = wq_kn [K,N]; out times the clip mask and the factor
+//   MODE 1 + e:    weight-only forward with epilogue e: f = x [M,K], q = the forward weight operand [N][K]
+// LONG: a group's share of the contraction exceeds kChain, so float32 sums are moved to float64 on the way.
+template <int TM, int TN, int WM, int WN, int WK, bool PACKED, int MODE, bool LONG>
+__global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
+    const float *__restrict__ f, const float *__restrict__ scale, const uint8_t *__restrict__ q, int64_t M, int64_t R,
+    int64_t C, const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x, const float *__restrict__ factor,
+    const float *__restrict__ bias, float *__restrict__ out, int tiles_r) {
+  static_assert(16 % WK == 0 && (WK == 1 || (WM * WN == 1 && TM == 1)) && (MODE != 1 + AQT_EPI_GLU || TN % 2 == 0),
+                "the epilogue is shared out by registers, a split contraction has one wavefront per group");
+  constexpr bool DX = MODE == 0, GLU = MODE == 1 + AQT_EPI_GLU;
+  constexpr int G = 64 * WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
+  // pieces of four floats, of sixteen codes, per thread and slice; a narrow tile leaves some threads without codes
+  constexpr int NA = BM * 8 / G, NB = BN * 2 >= G ? BN * 2 / G : 1;
+  static_assert(NA * G == BM * 8 && NA > 0 && (NB * G == BN * 2 || BN * 2 < G), "whole pieces per thread");
+  constexpr int kImage = BM * 64;
+  constexpr int kSliceBytes = 3 * kImage + BN * 64;
+  constexpr int kRedBytes = WK > 1 ? WK * TN * 16 * 64 * (LONG ? 8 : 4) : 0;
+  constexpr int kBuffers = WK == 1 ? 2 : WK;
+  constexpr int kLds = kBuffers * kSliceBytes > kRedBytes ? kBuffers * kSliceBytes : kRedBytes;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kLds];
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wk = wave / (WM * WN), wn = wave % WN, wm = (wave / WN) % WM, gt = t - wk * G;
+  const int64_t bm = blockIdx.x / tiles_r, br = blockIdx.x % tiles_r;
+  const int64_t oc = GLU ? R / 2 : R;
+  auto chan = [&](int cb) -> int64_t {
+    if (GLU) return br * (BN / 2) + (cb >> 1) * 32 + ((cb & 1) ? oc : 0);
+    return br * BN + cb * 32;
+  };
+  const int64_t row_bytes = PACKED ? (C + 1) / 2 : C;
+  const float *pf[NA];
+  const uint8_t *pq[NB];
+  const bool has_codes = BN * 2 >= G || gt < BN * 2;
+  const int piece = gt & 7;   // G is a multiple of 8: a thread's pieces sit at the same place of their rows
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int64_t m = bm * BM + ((gt + u * G) >> 3);
+    pf[u] = f + (m < M ? m : M - 1) * C;
+  }
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int r = has_codes ? (gt + u * G) >> 1 : 0;
+    const int64_t n = chan(r >> 5) + (r & 31);
+    pq[u] = q + (n < R ? n : R - 1) * row_bytes;
+  }
+  v4f ra[2][NA], rs[2] = {{1.0f, 1.0f, 1.0f, 1.0f}, {1.0f, 1.0f, 1.0f, 1.0f}};
+  v4i rb[2][NB];
+  auto load = [&](auto set, int64_t slice) {
+    constexpr int S = decltype(set)::value;
+    const int64_t c = slice * kSlice + 4 * piece;
+    if (c + 4 <= C) {
+#pragma unroll
+      for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4f>(pf[u] + c);
+      if (DX) rs[S] = load_at<v4f>(scale + c);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NA; ++u) {
+        ra[S][u] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (c + e < C) ra[S][u][e] = pf[u][c + e];
+      }
+      if (DX) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (c + e < C) rs[S][e] = scale[c + e];
+      }
+    }
+    if (!has_codes) return;
+    constexpr int kPiece = PACKED ? 8 : 16;   // bytes of sixteen codes
+    const int64_t at = slice * (2 * kPiece) + kPiece * (gt & 1);
+    if (at + kPiece <= row_bytes) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        if (PACKED) {
+          const v2i w = load_at<v2i>(pq[u] + at);
+          rb[S][u].x = w.x; rb[S][u].y = w.y;
+        } else {
+          rb[S][u] = load_at<v4i>(pq[u] + at);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) rb[S][u] = load16_guarded(pq[u], at, row_bytes);
+    }
+  };
+  v16f acc[TM][TN];
+  double sum[LONG ? TM : 1][LONG ? TN : 1][16];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] = 0.0f;
+        if (LONG) sum[LONG ? i : 0][LONG ? j : 0][r] = 0.0;
+      }
+  auto fold = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[LONG ? i : 0][LONG ? j : 0][r] += static_cast<double>(acc[i][j][r]);
+          acc[i][j][r] = 0.0f;
+        }
+  };
+  const int64_t slices = cdiv(C, kSlice);
+  int since = 0;
+  auto stage = [&](auto set, uint8_t *slot) {
+    constexpr int S = decltype(set)::value;
+    uint8_t *const sA = slot, *const sB = slot + 3 * kImage;
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      v4f v = ra[S][u];
+      if (DX) { v.x *= rs[S].x; v.y *= rs[S].y; v.z *= rs[S].z; v.w *= rs[S].w; }
+      store_split(sA + chunk_at<kCh>((gt + u * G) >> 3, piece >> 1) + 8 * (piece & 1), kImage, v);
+    }
+    if (has_codes) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const int r = (gt + u * G) >> 1, c0 = 2 * (gt & 1);
+        const v4i w = rb[S][u];
+        const uint32_t w0 = static_cast<uint32_t>(w.x), w1 = static_cast<uint32_t>(w.y), w2 = static_cast<uint32_t>(w.z),
+                       w3 = static_cast<uint32_t>(w.w);
+        *reinterpret_cast<v4i *>(sB + chunk_at<kCh>(r, c0)) = PACKED ? nibbles8_bf16(w0) : codes8_bf16(w0, w1);
+        *reinterpret_cast<v4i *>(sB + chunk_at<kCh>(r, c0 + 1)) = PACKED ? nibbles8_bf16(w1) : codes8_bf16(w2, w3);
+      }
+    }
+  };
+  auto multiply = [&](const uint8_t *slot) {
+    const uint8_t *const sA = slot, *const sB = slot + 3 * kImage;
+#pragma unroll
+    for (int kk = 0; kk < kSlice / 16; ++kk) {
+      v4i b[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const v4i *>(sB + chunk_at<kCh>((wn * TN + j) * 32 + lr, 2 * kk + lk));
+#pragma unroll
+      for (int img = 2; img >= 0; --img)   // smallest terms first
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const v4i a = *reinterpret_cast<const v4i *>(sA + img * kImage + chunk_at<kCh>((wm * TM + i) * 32 + lr, 2 * kk + lk));
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = mfma_bf16(a, b[j], acc[i][j]);
+        }
+    }
+    if (LONG && ++since == kChain / kSlice) {
+      fold();
+      since = 0;
+    }
+  };
+  run_slices<WK>(lds, kSliceBytes, wk, slices, load, stage, multiply);
+  if (LONG) fold();
+  constexpr int RW = 16 / WK;
+  if (WK > 1) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int at = ((wk * TN + j) * 16 + r) * 64 + lane;
+        if (LONG) reinterpret_cast<double *>(lds)[at] = sum[0][LONG ? j : 0][r];
+        else reinterpret_cast<float *>(lds)[at] = acc[0][j][r];
+      }
+    __syncthreads();
+  }
+  auto sum_of = [&](int i, int j, int rr) -> double {   // register wk * RW + rr, the groups' shares in order
+    if (WK == 1) return LONG ? sum[LONG ? i : 0][LONG ? j : 0][rr] : static_cast<double>(acc[i][j][rr]);
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < WK; ++w) {
+      const int at = ((w * TN + j) * 16 + wk * RW + rr) * 64 + lane;
+      v += LONG ? reinterpret_cast<const double *>(lds)[at] : static_cast<double>(reinterpret_cast<const float *>(lds)[at]);
+    }
+    return v;
+  };
+  if (DX) {
+    const bool keep = s_x[0] != 0.0f;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int64_t n = chan(wn * TN + j) + lr;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int rr = 0; rr < RW; ++rr) {
+          const int r = wk * RW + rr;
+          const int64_t m = bm * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+          float v = static_cast<float>(sum_of(i, j, rr));
+          if (n >= R || m >= M) continue;
+          const int64_t at = m * R + n;
+          if (factor) v = v * factor[at];
+          out[at] = (mask_x ? mask_bit(mask_x, at) : keep) ? v : 0.0f;
+        }
+    }
+    return;
+  }
+  constexpr int JS = GLU ? 2 : 1;
+#pragma unroll
+  for (int j = 0; j < TN; j += JS) {
+    const int64_t n = chan(wn * TN + j) + lr;
+    const bool live = n < oc;
+    const int64_t nc = live ? n : oc - 1, ng = nc + (GLU ? oc : 0);
+    const double sc_a = scale[nc], sc_b = GLU ? scale[ng] : 0.0f;
+    const float bias_a = bias ? bias[nc] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int rr = 0; rr < RW; ++rr) {
+        const int r = wk * RW + rr;
+        const int64_t m = bm * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+        const float v = static_cast<float>(sum_of(i, j, rr) * sc_a) + bias_a;
+        const float gt2 = GLU ? static_cast<float>(sum_of(i, j + JS - 1, rr) * sc_b) + bias_b : 0.0f;
+        if (!live || m >= M) continue;
+        float o = v;
+        if (MODE == 1 + AQT_EPI_SWISH) o = swish_f32(v);
+        else if (GLU) o = v * sigmoid_f32(gt2);
+        out[m * oc + n] = o;
+      }
+  }
+}
+
+// ---- dW: contraction over the rows of both operands ---------------------------------------------
+// partial[slab][k][n] = sum over the slab's rows of xq[m,k] dy[m,n].  A workgroup of four wavefronts owns 128
+// fan-in positions x 128 channels and one slab of rows, 32 rows per slice.  Neither operand is
+// contraction-contiguous, so a thread gathers 4 positions x 4 rows of each with row-wise loads and writes pieces
+// along the rows into LDS; tile column 4 g + b lives in LDS row 32 b + g, so that the lanes of a write spread over
+// the banks.  With a single slab the result is finished here; otherwise dw_any_fold_kernel adds the slabs in
+// order, in float64.
+constexpr int kDwThreads = 256;
+constexpr int kDwTile = 128;
+
+struct DwFinish {
+  const float *s_x, *s_w;
+  const uint32_t *mask_w;
+};
+
+__device__ __forceinline__ float dw_value(double s, int64_t at, int64_t n, const DwFinish &fin, double sx) {
+  const bool pass = fin.mask_w ? mask_bit(fin.mask_w, at) : (fin.s_w[n] != 0.0f);
+  return pass ? static_cast<float>(sx * s) : 0.0f;
+}
+
+// Off: how offsets inside a slice's 32 rows are held; with 32 bits a load is one scalar base and a fixed lane offset.
+template <class Off>
+__global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t *__restrict__ xq, const float *__restrict__ dy,
+                                                                   int64_t M, int64_t K, int64_t N, int64_t rows_per_slab,
+                                                                   float *__restrict__ out, int tiles_n, int tiles, int finish,
+                                                                   DwFinish fin) {
+  constexpr int kImage = kDwTile * 64;
+  constexpr int kSliceBytes = 4 * kImage;             // codes; dy hi, mid, lo
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSliceBytes];
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int slab = blockIdx.x / tiles, tile = blockIdx.x % tiles;
+  const int64_t k0 = (tile / tiles_n) * static_cast<int64_t>(kDwTile), n0 = (tile % tiles_n) * static_cast<int64_t>(kDwTile);
+  const int64_t m0 = slab * rows_per_slab, m1 = m0 + rows_per_slab < M ? m0 + rows_per_slab : M;
+  const int g = t & 31, mg = t >> 5;          // this thread's column group and its four rows 4 mg .. + 3 of a slice
+  const int64_t kc = k0 + 4 * g, nc = n0 + 4 * g;
+  const bool kwhole = kc + 4 <= K, nwhole = nc + 4 <= N;
+  Off xo[4], yo[4];
+  auto offsets = [&](int64_t m) {             // rows beyond the slab are read from its last one
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t left = m1 - 1 - m, r = 4 * mg + i < left ? 4 * mg + i : left;
+      xo[i] = static_cast<Off>(r * K + kc);
+      yo[i] = static_cast<Off>((r * N + nc) * 4);
+    }
+  };
+  uint32_t rc[2][4];
+  v4f rg[2][4];
+  auto load = [&](auto set, int64_t slice) {
+    constexpr int S = decltype(set)::value;
+    const int64_t m = m0 + slice * kSlice;
+    if (m + kSlice > m1) offsets(m);
+    const char *x = reinterpret_cast<const char *>(xq) + m * K, *y = reinterpret_cast<const char *>(dy + m * N);
+    if (kwhole) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rc[S][i] = load_at<uint32_t>(x + xo[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        rc[S][i] = 0u;
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (kc + e < K) rc[S][i] |= static_cast<uint32_t>(load_at<uint8_t>(x + xo[i] + e)) << (8 * e);
+      }
+    }
+    if (nwhole) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rg[S][i] = load_at<v4f>(y + yo[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (nc + e < N) rg[S][i][e] = load_at<float>(y + yo[i] + 4 * e);
+      }
+    }
+    if (m + kSlice > m1) {   // rows beyond the slab contribute nothing
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (m + 4 * mg + i >= m1) {
+          rc[S][i] = 0u;
+          rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
+  };
+  // a wavefront multiplies all four codes blocks with one block of the gradient (seven fragment reads per twelve products)
+  v16f acc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
+  auto stage = [&](auto set, uint8_t *slot) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      uint8_t *const at = slot + chunk_at<kCh>(32 * b + g, mg >> 1) + 8 * (mg & 1);
+      v2i a;
+      a.x = static_cast<int>(pack_bf16(static_cast<float>(static_cast<int8_t>(rc[S][0] >> (8 * b))),
+                                       static_cast<float>(static_cast<int8_t>(rc[S][1] >> (8 * b)))));
+      a.y = static_cast<int>(pack_bf16(static_cast<float>(static_cast<int8_t>(rc[S][2] >> (8 * b))),
+                                       static_cast<float>(static_cast<int8_t>(rc[S][3] >> (8 * b)))));
+      *reinterpret_cast<v2i *>(at) = a;
+      store_split(at + kImage, kImage, v4f{rg[S][0][b], rg[S][1][b], rg[S][2][b], rg[S][3][b]});
+    }
+  };
+  auto multiply = [&](const uint8_t *slot) {
+#pragma unroll
+    for (int kk = 0; kk < kSlice / 16; ++kk) {
+      v4i a[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const v4i *>(slot + chunk_at<kCh>(i * 32 + lr, 2 * kk + lk));
+#pragma unroll
+      for (int img = 2; img >= 0; --img) {
+        const v4i d = *reinterpret_cast<const v4i *>(slot + (1 + img) * kImage + chunk_at<kCh>(wave * 32 + lr, 2 * kk + lk));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = mfma_bf16(a[i], d, acc[i]);
+      }
+    }
+  };
+  offsets(m0);
+  run_slices<1>(lds, kSliceBytes, 0, cdiv(m1 - m0, kSlice), load, stage, multiply);
+  // Out through LDS as whole rows, 32 tile rows 4 q + p at a time: they are codes block p, and tile column 4 g + b is
+  // gradient block b = wave, column g.
+  constexpr int kRow = kDwTile + 4;
+  static_assert(32 * kRow * 4 <= 2 * kSliceBytes, "the output image must fit");
+  float *const img = reinterpret_cast<float *>(lds);
+  const double sx = finish ? fin.s_x[0] : 1.0;
+  bool nz[4];                       // channels whose scale is not zero (what a missing clip mask stands for)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) nz[e] = finish && fin.s_w[nc + e < N ? nc + e : N - 1] != 0.0f;
+  float *const o = out + (finish ? 0 : static_cast<int64_t>(slab) * K * N);
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) img[(8 * (r >> 2) + 4 * lk + (r & 3)) * kRow + 4 * lr + wave] = acc[p][r];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int q = (t >> 5) + 8 * u;
+      const int64_t k = k0 + 4 * q + p, at = k * N + nc;
+      v4f v = *reinterpret_cast<const v4f *>(img + q * kRow + 4 * g);
+      if (k >= K || nc >= N) continue;
+      if (finish) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[e] = ((fin.mask_w && nc + e < N) ? mask_bit(fin.mask_w, at + e) : nz[e]) ? static_cast<float>(sx * v[e]) : 0.0f;
+      }
+      if (nwhole) {
+        __builtin_memcpy(o + at, &v, sizeof(v));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (nc + e < N) o[at + e] = v[e];
+      }
+    }
+  }
+}
+
+// 64 elements x 4 groups of slabs per workgroup, eight loads in flight per thread; the order of the sums is fixed.
+__global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__restrict__ partial, int slabs, int64_t K,
+                                                                 int64_t N, DwFinish fin, float *__restrict__ dw) {
+  __shared__ double sm[4][64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t KN = K * N, at = static_cast<int64_t>(blockIdx.x) * 64 + lane, ac = at < KN ? at : KN - 1;
+  double s = 0.0;
+  for (int j = grp * 8; j < slabs; j += 32) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = partial[(j + u < slabs ? j + u : slabs - 1) * KN + ac];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += j + u < slabs ? static_cast<double>(v[u]) : 0.0;
+  }
+  sm[grp][lane] = s;
+  __syncthreads();
+  if (grp == 0 && at < KN)
+    dw[at] = dw_value((sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]), at, at % N, fin, fin.s_x[0]);
+}
+
+// Which workgroup arrangement.  128 x 128 tiles move the fewest bytes through LDS per product but there have to be
+// enough of them for 256 compute units; narrower ones when the columns would mostly be padding; the split
+// contraction below that.
+enum class Tile { kLarge, kRows, kNarrow, kSmall, kSmallest };   // 128 x 128, 64 x 128, 128 x 64; split contraction: 32 x 64, 32 x 32
+Tile pick_tile(int64_t M, int64_t cols, bool glu) {
+  const int64_t narrow = cdiv(M, 128) * cdiv(cols, 64), large = cdiv(M, 128) * cdiv(cols, 128), rows = cdiv(M, 64) * cdiv(cols, 128);
+  const bool odd = cdiv(cols, 64) % 2 && cols < 512;   // half of the last 128-wide tile would be padding
+  if (odd && narrow >= 128) return Tile::kNarrow;
+  if (large >= 192) return Tile::kLarge;
+  if (rows >= 160) return Tile::kRows;
+  return glu || cdiv(M, 32) * cdiv(cols, 64) >= 128 ? Tile::kSmall : Tile::kSmallest;
+}
+
+template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
+aqt_status fwd_any(const int8_t *xq, const float *s_x, const void *wq, const float *s_w, int64_t M, int64_t K, int64_t N,
+                   const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
+                   hipStream_t st) {
+  const int64_t oc = epilogue == AQT_EPI_GLU ? N / 2 : N;
+  const int64_t tn = cdiv(oc, (epilogue == AQT_EPI_GLU ? 16 : 32) * TN * WN), tm = cdiv(M, 32 * TM * WM);
+  if (tn * tm > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
+  constexpr int kGlu = TN % 2 ? AQT_EPI_NONE : AQT_EPI_GLU;   // tiles of one column block are not picked for GLU
+  auto kern = epilogue == AQT_EPI_NONE    ? dense_fwd_any_kernel<TM, TN, WM, WN, WK, BK, PACKED, AQT_EPI_NONE>
+              : epilogue == AQT_EPI_SWISH ? dense_fwd_any_kernel<TM, TN, WM, WN, WK, BK, PACKED, AQT_EPI_SWISH>
+                                          : dense_fwd_any_kernel<TM, TN, WM, WN, WK, BK, PACKED, kGlu>;
+  kern<<<static_cast<unsigned>(tn * tm), 64 * WM * WN * WK, 0, st>>>(xq, s_x, static_cast<const uint8_t *>(wq), s_w, M, K, N,
+                                                                     bias, y, acc_out, y_absmax, dact, static_cast<int>(tn));
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
+template <bool PACKED>
+aqt_status fwd_any_sized(const int8_t *xq, const float *s_x, const void *wq, const float *s_w, int64_t M, int64_t K, int64_t N,
+                         const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
+                         hipStream_t st) {
+  switch (pick_tile(M, N, epilogue == AQT_EPI_GLU)) {
+    case Tile::kLarge: return fwd_any<2, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+    case Tile::kRows: return fwd_any<1, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+    case Tile::kNarrow: return fwd_any<1, 2, 4, 1, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+    case Tile::kSmallest: return fwd_any<1, 1, 1, 1, 8, 64, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+    default: return fwd_any<1, 2, 1, 1, 8, 64, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+  }
+}
+
+template <int TM, int TN, int WM, int WN, int WK, bool PACKED>
+aqt_status f32_codes_any(int mode, const float *f, const float *scale, const void *q, int64_t M, int64_t R, int64_t C,
+                         const float *s_x, const uint32_t *mask_x, const float *factor, const float *bias, float *out,
+                         hipStream_t st) {
+  const int64_t oc = mode == 1 + AQT_EPI_GLU ? R / 2 : R;
+  const int64_t tr = cdiv(oc, (mode == 1 + AQT_EPI_GLU ? 16 : 32) * TN * WN), tm = cdiv(M, 32 * TM * WM);
+  if (tr * tm > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
+  const bool lng = C > int64_t(kChain) * WK && TM == 1;   // 128 x 128 tiles are only picked for short contractions
+#define AQT_PICK(MODE) (lng ? f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, TM == 1> \
+                            : f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, false>)
+  auto kern = mode == 1 + AQT_EPI_NONE    ? AQT_PICK(1 + AQT_EPI_NONE)
+              : mode == 1 + AQT_EPI_SWISH ? AQT_PICK(1 + AQT_EPI_SWISH)
+              : mode == 1 + AQT_EPI_GLU   ? AQT_PICK((TN % 2 ? 1 + AQT_EPI_NONE : 1 + AQT_EPI_GLU))
+                                          : AQT_PICK((PACKED ? 1 + AQT_EPI_NONE : 0));   // dX codes are never packed
+#undef AQT_PICK
+  kern<<<static_cast<unsigned>(tr * tm), 64 * WM * WN * WK, 0, st>>>(f, scale, static_cast<const uint8_t *>(q), M, R, C, s_x,
+                                                                     mask_x, factor, bias, out, static_cast<int>(tr));
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
+template <bool PACKED>
+aqt_status f32_codes_any_sized(int mode, const float *f, const float *scale, const void *q, int64_t M, int64_t R, int64_t C,
+                               const float *s_x, const uint32_t *mask_x, const float *factor, const float *bias, float *out,
+                               hipStream_t st) {
+  const Tile tile = pick_tile(M, R, mode == 1 + AQT_EPI_GLU);
+  switch (tile == Tile::kLarge && C > kChain ? Tile::kRows : tile) {   // float64 sums of a 128 x 128 tile would not fit the registers
+    case Tile::kLarge: return f32_codes_any<2, 2, 2, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+    case Tile::kRows: return f32_codes_any<1, 2, 2, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+    case Tile::kNarrow: return f32_codes_any<1, 2, 4, 1, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+    case Tile::kSmallest: return f32_codes_any<1, 1, 1, 1, 8, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+    default: return f32_codes_any<1, 2, 1, 1, 8, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+  }
+}
+
+}  // namespace
+
+aqt_status launch_dense_fwd_any(const int8_t *xq, const float *s_x, const void *wq_packed, const float *s_w, int64_t M,
+                                int64_t K, int64_t N, int bits_w, const float *bias, int epilogue, float *y,
+                                int32_t *acc_out, uint32_t *y_absmax, float *dact, hipStream_t st) {
+  return packed4(bits_w) ? fwd_any_sized<true>(xq, s_x, wq_packed, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st)
+                         : fwd_any_sized<false>(xq, s_x, wq_packed, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+}
+
+aqt_status launch_bwd_dx_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
+                             const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st) {
+  return f32_codes_any_sized<false>(0, dy, s_w, wq_kn, M, K, N, s_x, mask_x, factor, nullptr, dx, st);
+}
+
+aqt_status launch_dense_fwd_wonly_any(const float *x, const void *wq_packed, const float *s_w, int64_t M, int64_t K,
+                                      int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st) {
+  return packed4(bits_w)
+             ? f32_codes_any_sized<true>(1 + epilogue, x, s_w, wq_packed, M, N, K, nullptr, nullptr, nullptr, bias, y, st)
+             : f32_codes_any_sized<false>(1 + epilogue, x, s_w, wq_packed, M, N, K, nullptr, nullptr, nullptr, bias, y, st);
+}
+
+// Slabs of at most kChain rows, so that a float32 sum is never longer, as long as their partial results stay under
+// 64 MiB; shorter slabs while the launch does not fill the chip, of at least 64 rows each.
+int dw_any_slabs(int64_t M, int64_t K, int64_t N) {
+  const int64_t tiles = cdiv(K, kDwTile) * cdiv(N, kDwTile);
+  int64_t slabs = cdiv(M, kChain);
+  const int64_t fill = cdiv(512, tiles), most = cdiv(M, 64);
+  if (slabs < fill) slabs = fill < most ? fill : most;
+  const int64_t room = (int64_t(64) << 20) / (K * N * 4) + 1;
+  if (slabs > room) slabs = room;
+  while (slabs > 1 && slabs * tiles > 0x7FFFFFFF) slabs /= 2;
+  return static_cast<int>(slabs);
+}
+
+aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
+                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, int max_slabs, hipStream_t st) {
+  const int64_t tiles_n = cdiv(N, kDwTile), tiles = cdiv(K, kDwTile) * tiles_n;
+  int64_t slabs = dw_any_slabs(M, K, N);
+  if (slabs > max_slabs) slabs = max_slabs;
+  const int64_t rows = cdiv(cdiv(M, slabs), kSlice) * kSlice;
+  slabs = cdiv(M, rows);
+  if (tiles * slabs > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
+  const DwFinish fin{s_x, s_w, mask_w};
+  const bool one = slabs == 1;
+  auto kern = K < (1 << 24) && N < (1 << 24) ? bwd_dw_any_kernel<uint32_t> : bwd_dw_any_kernel<int64_t>;
+  kern<<<static_cast<unsigned>(tiles * slabs), kDwThreads, 0, st>>>(
+      xq, dy, M, K, N, rows, one ? dw : partial, static_cast<int>(tiles_n), static_cast<int>(tiles), one ? 1 : 0, fin);
+  AQT_HIP(hipGetLastError());
+  if (one) return AQT_OK;
+  dw_any_fold_kernel<<<static_cast<unsigned>(cdiv(K * N, 64)), kDwThreads, 0, st>>>(partial, static_cast<int>(slabs), K, N,
+                                                                                   fin, dw);
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
+}  // namespace aqt

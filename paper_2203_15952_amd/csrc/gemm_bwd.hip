@@ -62,35 +62,6 @@ __device__ __forceinline__ v16f mfma_bf16(v4i a, v4i b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
-// ---- general kernels: one thread per output, float64 accumulation ------------------
-__global__ __launch_bounds__(kThreads) void bwd_dx_general_kernel(
-    const float *__restrict__ dy, const int8_t *__restrict__ wq_kn, const float *__restrict__ s_w,
-    const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x, int64_t M, int64_t K, int64_t N,
-    float *__restrict__ dx) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (idx >= M * K) return;
-  const int64_t m = idx / K, k = idx - m * K;
-  double s = 0.0;
-  for (int64_t n = 0; n < N; ++n)
-    s += static_cast<double>(dy[m * N + n] * s_w[n]) * static_cast<double>(wq_kn[k * N + n]);
-  const bool pass = mask_x ? mask_bit(mask_x, idx) : (s_x[0] != 0.0f);
-  dx[idx] = pass ? static_cast<float>(s) : 0.0f;
-}
-
-__global__ __launch_bounds__(kThreads) void bwd_dw_general_kernel(
-    const float *__restrict__ dy, const int8_t *__restrict__ xq, const float *__restrict__ s_x,
-    const float *__restrict__ s_w, const uint32_t *__restrict__ mask_w, int64_t M, int64_t K, int64_t N,
-    float *__restrict__ dw) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (idx >= K * N) return;
-  const int64_t k = idx / N, n = idx - k * N;
-  double s = 0.0;
-  for (int64_t m = 0; m < M; ++m)
-    s += static_cast<double>(xq[m * K + k]) * static_cast<double>(dy[m * N + n]);
-  const bool pass = mask_w ? mask_bit(mask_w, idx) : (s_w[n] != 0.0f);
-  dw[idx] = pass ? static_cast<float>(static_cast<double>(s_x[0]) * s) : 0.0f;
-}
-
 // Column sums of dy in two stages: (64 columns x row slab) partials, then a fold.
 constexpr int kBiasSlabs = 64;
 
@@ -852,6 +823,7 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   if (per * (K > N ? K : N) >= (int64_t(1) << 30)) p.dw_mfma = false;   // 32-bit byte offsets inside a slab
   p.slabs = static_cast<int>(slabs);
   p.m_per_slab = static_cast<int>(per);
+  if (!p.dw_mfma) p.slabs = dw_any_slabs(M, K, N);
   size_t off = 0;
   p.off_bf = off;   off += align_up(static_cast<size_t>(K) * N * 2, 256);
   p.off_part = off; off += align_up(static_cast<size_t>(p.slabs) * K * N * 4, 256);
@@ -890,42 +862,6 @@ aqt_status launch_dw(const float *dy, const aqt_saved *sv, int64_t M, int64_t K,
                                                          tiles_c);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
-}
-
-// Weight-only forward for any shape: one thread per output, the de-quantized weight
-// rounded to float32 as a float graph would hold it, products summed in float64.
-__global__ __launch_bounds__(kThreads) void dense_fwd_wonly_general_kernel(
-    const float *__restrict__ x, const uint8_t *__restrict__ wq, const float *__restrict__ s_w, int64_t M,
-    int64_t K, int64_t N, int packed, const float *__restrict__ bias, int epilogue, float *__restrict__ y) {
-  const int64_t ncols = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (idx >= M * ncols) return;
-  const int64_t m = idx / ncols, j = idx - m * ncols;
-  const int64_t row_bytes = packed ? (K + 1) / 2 : K;
-  const int parts = (epilogue == AQT_EPI_GLU) ? 2 : 1;
-  float v[2];
-  for (int p = 0; p < parts; ++p) {
-    const int64_t n = j + p * ncols;
-    double s = 0.0;
-    for (int64_t k = 0; k < K; ++k) {
-      int c;
-      if (packed) {
-        const uint32_t b = wq[n * row_bytes + (k >> 1)];
-        c = static_cast<int>(((k & 1) ? (b >> 4) : (b & 0xFu)) << 28) >> 28;
-      } else {
-        c = static_cast<int8_t>(wq[n * row_bytes + k]);
-      }
-      s += static_cast<double>(x[m * K + k]) * static_cast<double>(s_w[n] * static_cast<float>(c));
-    }
-    float t = static_cast<float>(s);
-    if (bias) t = t + bias[n];
-    v[p] = t;
-  }
-  float out;
-  if (epilogue == AQT_EPI_NONE) out = v[0];
-  else if (epilogue == AQT_EPI_SWISH) out = swish_f32(v[0]);
-  else out = v[0] * sigmoid_f32(v[1]);
-  y[m * ncols + j] = out;
 }
 
 template <int TM, int TN, int WN = 2>
@@ -970,11 +906,7 @@ aqt_status launch_dense_fwd_wonly(const float *x, const void *wq_packed, const f
     if (wide) return launch_wonly<2, 4>(x, frag, s_w, bias, epilogue, M, K, N, y, st);
     return launch_wonly<2, 2>(x, frag, s_w, bias, epilogue, M, K, N, y, st);
   }
-  const int64_t ncols = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
-  dense_fwd_wonly_general_kernel<<<static_cast<int>(cdiv(M * ncols, kThreads)), kThreads, 0, st>>>(
-      x, static_cast<const uint8_t *>(wq_packed), s_w, M, K, N, packed ? 1 : 0, bias, epilogue, y);
-  AQT_HIP(hipGetLastError());
-  return AQT_OK;
+  return launch_dense_fwd_wonly_any(x, wq_packed, s_w, M, K, N, bits_w, bias, epilogue, y, st);
 }
 
 size_t bwd_workspace_bytes(int64_t M, int64_t K, int64_t N) { return plan_bwd(M, K, N).total; }
@@ -1004,10 +936,7 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
       else AQT_TRY((launch_dx<2, 2>(dy, wq_frag, sv, M, K, N, dx, st, fused)));
       if (dx_factor && !fused) AQT_TRY(launch_dact_mul(dx, dx_factor, M, K, K, dx, st));
     } else {
-      bwd_dx_general_kernel<<<static_cast<int>(cdiv(M * K, kThreads)), kThreads, 0, st>>>(
-          dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, M, K, N, dx);
-      AQT_HIP(hipGetLastError());
-      if (dx_factor) AQT_TRY(launch_dact_mul(dx, dx_factor, M, K, K, dx, st));
+      AQT_TRY(launch_bwd_dx_any(dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, dx_factor, M, K, N, dx, st));
     }
   }
   if (dw) {
@@ -1020,9 +949,8 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
           partial, p.slabs, K * N, N, sv->s_x, sv->s_w, sv->mask_w, dw);
       AQT_HIP(hipGetLastError());
     } else {
-      bwd_dw_general_kernel<<<static_cast<int>(cdiv(K * N, kThreads)), kThreads, 0, st>>>(
-          dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw);
-      AQT_HIP(hipGetLastError());
+      AQT_TRY(launch_bwd_dw_any(dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw,
+                                reinterpret_cast<float *>(base + p.off_part), p.slabs, st));
     }
   }
   if (dbias) {

@@ -3,8 +3,7 @@
 // for gfx950:  acc = xq . wq in int32 on the int8 matrix cores, then
 // v = float(acc) * (s_x * s_w[n]) (+ bias), then none / Swish / GLU.
 //
-// The tuned kernel is described where it is defined; shapes it does not cover take
-// a one-thread-per-output kernel with identical results.
+// The tuned kernel is described where it is defined; shapes it does not cover go to gemm_any.hip (same results).
 #include <mutex>
 #include <type_traits>
 
@@ -32,17 +31,6 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
 
-// ---- general kernel: one thread per output, any shape -----------------------------
-__device__ __forceinline__ int weight_code(const uint8_t *__restrict__ wq, int64_t row_bytes, int packed,
-                                           int64_t n, int64_t k) {
-  if (packed) {
-    const uint32_t b = wq[n * row_bytes + (k >> 1)];
-    const uint32_t nib = (k & 1) ? (b >> 4) : (b & 0xFu);
-    return static_cast<int>(nib ^ 8u) - 8;
-  }
-  return static_cast<int8_t>(wq[n * row_bytes + k]);
-}
-
 // max|y| as an unsigned maximum over bit patterns (non-negative floats order like
 // their bits; NaN and Inf come out on top, which is how the consumer learns of them).
 // The word only grows, so a stale read can only cause a redundant atomic.
@@ -52,47 +40,6 @@ __device__ __forceinline__ void note_absmax(uint32_t *y_absmax, uint32_t bits) {
 
 __global__ void zero_word_kernel(uint32_t *p) {
   if (threadIdx.x == 0) *p = 0u;
-}
-
-__global__ __launch_bounds__(kThreads) void dense_fwd_general_kernel(
-    const int8_t *__restrict__ xq, const float *__restrict__ s_x, const uint8_t *__restrict__ wq,
-    const float *__restrict__ s_w, int64_t M, int64_t K, int64_t N, int packed,
-    const float *__restrict__ bias, int epilogue, float *__restrict__ y, int32_t *__restrict__ acc_out,
-    uint32_t *__restrict__ y_absmax, float *__restrict__ dact) {
-  const int64_t ncols = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (idx >= M * ncols) return;
-  const int64_t m = idx / ncols, j = idx - m * ncols;
-  const int64_t row_bytes = packed ? (K + 1) / 2 : K;
-  const float sx = s_x[0];
-  const int parts = (epilogue == AQT_EPI_GLU) ? 2 : 1;
-  float v[2];
-  for (int p = 0; p < parts; ++p) {
-    const int64_t n = j + p * ncols;
-    int acc = 0;
-    for (int64_t k = 0; k < K; ++k) acc += static_cast<int>(xq[m * K + k]) * weight_code(wq, row_bytes, packed, n, k);
-    if (acc_out) acc_out[m * N + n] = acc;
-    float t = dequant_f32(acc, sx * s_w[n]);
-    if (bias) t = t + bias[n];
-    v[p] = t;
-  }
-  float out;
-  if (epilogue == AQT_EPI_NONE) {
-    out = v[0];
-  } else if (epilogue == AQT_EPI_SWISH) {
-    const float sg = sigmoid_f32(v[0]);
-    out = v[0] * sg;
-    if (dact) dact[m * N + j] = swish_dact_f32(v[0], sg);
-  } else {
-    const float sg = sigmoid_f32(v[1]);
-    out = v[0] * sg;
-    if (dact) {
-      dact[m * N + j] = sg;
-      dact[m * N + j + ncols] = glu_gate_dact_f32(v[0], sg);
-    }
-  }
-  y[m * ncols + j] = out;
-  if (y_absmax) note_absmax(y_absmax, __float_as_uint(out) & 0x7FFFFFFFu);
 }
 
 // ---- tuned MFMA kernel --------------------------------------------------------------
@@ -551,13 +498,8 @@ aqt_status launch_dense_fwd_q(const int8_t *xq, const float *s_x, const void *wq
     return packed ? launch_mfma_epi<2, 2, true>(epilogue, xq, s_x, wfrag, s_w, M, K, N, bias, y, acc_out, y_absmax, dact, st)
                   : launch_mfma_epi<2, 2, false>(epilogue, xq, s_x, wfrag, s_w, M, K, N, bias, y, acc_out, y_absmax, dact, st);
   }
-  if (ws_is_prepared) return AQT_ERR_UNSUPPORTED;   // the general kernel reads the canonical operand
-  const int64_t ncols = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
-  dense_fwd_general_kernel<<<static_cast<int>(cdiv(M * ncols, kThreads)), kThreads, 0, st>>>(
-      xq, s_x, static_cast<const uint8_t *>(wq_packed), s_w, M, K, N, packed ? 1 : 0, bias, epilogue, y,
-      acc_out, y_absmax, dact);
-  AQT_HIP(hipGetLastError());
-  return AQT_OK;
+  if (!wq_packed) return AQT_ERR_UNSUPPORTED;   // only the prepared operand was given
+  return launch_dense_fwd_any(xq, s_x, wq_packed, s_w, M, K, N, bits_w, bias, epilogue, y, acc_out, y_absmax, dact, st);
 }
 
 }  // namespace aqt
