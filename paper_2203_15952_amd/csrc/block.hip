@@ -39,6 +39,18 @@ __device__ __forceinline__ float ln_value(float x, float mean, float rstd, const
   return t;
 }
 
+__device__ __forceinline__ v4f ln_value4(v4f x, float mean, float rstd, bool has_g, bool has_b, v4f g, v4f b) {
+  v4f t;
+  t.x = (x.x - mean) * rstd; t.y = (x.y - mean) * rstd; t.z = (x.z - mean) * rstd; t.w = (x.w - mean) * rstd;
+  if (has_g) { t.x = t.x * g.x; t.y = t.y * g.y; t.z = t.z * g.z; t.w = t.w * g.w; }
+  if (has_b) { t.x = t.x + b.x; t.y = t.y + b.y; t.z = t.z + b.z; t.w = t.w + b.w; }
+  return t;
+}
+__device__ __forceinline__ uint32_t absmax4(v4f v) {
+  return max(max(__float_as_uint(v.x) & 0x7FFFFFFFu, __float_as_uint(v.y) & 0x7FFFFFFFu),
+             max(__float_as_uint(v.z) & 0x7FFFFFFFu, __float_as_uint(v.w) & 0x7FFFFFFFu));
+}
+
 // A row in registers: lane l keeps the float4 pieces l, l + 64, ... of its row (NV pieces, rows of up to
 // 256 NV floats whose length is a multiple of 4), so each pass reads the row from memory once.
 template <int NV>
@@ -68,6 +80,13 @@ __global__ __launch_bounds__(kThreads) void ln_stats_kernel(const float *__restr
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (zero_word && blockIdx.x == 0 && threadIdx.x == 0) *zero_word = 0u;   // for a kernel launched after this one
   uint32_t amax = 0u;
+  // gamma and beta of this lane's columns stay in registers (16-byte loads; read element by element inside the row
+  // loop they doubled the kernel's time at 12800 x 512: 23.6 us with them, 12 without)
+  v4f gm[NV > 0 ? NV : 1], bt[NV > 0 ? NV : 1];
+  if constexpr (NV > 0) {
+    if (gamma) load_row<NV>(gamma, D, lane, gm);
+    if (beta) load_row<NV>(beta, D, lane, bt);
+  }
   for (int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + wave; m < M; m += static_cast<int64_t>(gridDim.x) * 4) {
     const float *row = x + m * D;
     if constexpr (NV > 0) {
@@ -104,12 +123,7 @@ __global__ __launch_bounds__(kThreads) void ln_stats_kernel(const float *__restr
 #pragma unroll
       for (int k = 0; k < NV; ++k) {
         const int64_t c = 4 * (lane + 64 * k);
-        if (c < D) {
-          amax = max(amax, __float_as_uint(ln_value(v[k].x, mean, rstd, gamma, beta, c)) & 0x7FFFFFFFu);
-          amax = max(amax, __float_as_uint(ln_value(v[k].y, mean, rstd, gamma, beta, c + 1)) & 0x7FFFFFFFu);
-          amax = max(amax, __float_as_uint(ln_value(v[k].z, mean, rstd, gamma, beta, c + 2)) & 0x7FFFFFFFu);
-          amax = max(amax, __float_as_uint(ln_value(v[k].w, mean, rstd, gamma, beta, c + 3)) & 0x7FFFFFFFu);
-        }
+        if (c < D) amax = max(amax, absmax4(ln_value4(v[k], mean, rstd, gamma != nullptr, beta != nullptr, gm[k], bt[k])));
       }
     } else {
       if (res) {   // any row length: form the sum first, then read it back like any input row
@@ -149,9 +163,9 @@ __device__ __forceinline__ int8_t ln_code(float v, float s, float fq) {
 
 // Pass 2: fold the block maxima into the scale (Fig. 2: max / qmax), recompute the normalised
 // values from x and the stored row statistics, quantize (divide, + 0.5, floor), write codes
-// and, when asked, the float32 values themselves.  VEC: four columns per lane and access
-// (D % 4 == 0, 16-byte aligned x and y_out, 4-byte aligned q).
-template <bool VEC>
+// and, when asked, the float32 values themselves.  NV as in ln_stats_kernel (NV > 0: 16-byte aligned x and y_out,
+// 4-byte aligned q; gamma and beta in registers); NV < 0: four columns per lane and access, rows of any length.
+template <int NV>
 __global__ __launch_bounds__(kThreads) void ln_quantize_kernel(const float *__restrict__ x, int64_t M, int64_t D,
                                                                const float *__restrict__ gamma,
                                                                const float *__restrict__ beta,
@@ -174,23 +188,34 @@ __global__ __launch_bounds__(kThreads) void ln_quantize_kernel(const float *__re
     if (scale) scale[0] = s;
     if (mx >= 0x7F800000u && dev_status) *dev_status = AQT_ERR_NONFINITE;
   }
+  v4f gm[NV > 0 ? NV : 1], bt[NV > 0 ? NV : 1];
+  if constexpr (NV > 0) {
+    if (gamma) load_row<NV>(gamma, D, lane, gm);
+    if (beta) load_row<NV>(beta, D, lane, bt);
+  }
   for (int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + wave; m < M; m += static_cast<int64_t>(gridDim.x) * 4) {
     const float *row = x + m * D;
     const float mean = stats[2 * m], rstd = stats[2 * m + 1];
-    if constexpr (VEC) {
+    auto put = [&](int64_t c, v4f xv, v4f g, v4f b) {
+      const v4f y = ln_value4(xv, mean, rstd, gamma != nullptr, beta != nullptr, g, b);
+      if (y_out) *reinterpret_cast<v4f *>(y_out + m * D + c) = y;
+      if (q) {
+        const uint32_t b0 = static_cast<uint8_t>(ln_code(y.x, s, fq)), b1 = static_cast<uint8_t>(ln_code(y.y, s, fq));
+        const uint32_t b2 = static_cast<uint8_t>(ln_code(y.z, s, fq)), b3 = static_cast<uint8_t>(ln_code(y.w, s, fq));
+        *reinterpret_cast<uint32_t *>(q + m * D + c) = b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
+      }
+    };
+    if constexpr (NV > 0) {
+      v4f v[NV];
+      load_row<NV>(row, D, lane, v);
+#pragma unroll
+      for (int k = 0; k < NV; ++k)
+        if (4 * (lane + 64 * k) < D) put(4 * (lane + 64 * k), v[k], gm[k], bt[k]);
+    } else if constexpr (NV < 0) {
       for (int64_t c = 4 * lane; c < D; c += 256) {
-        const v4f xv = *reinterpret_cast<const v4f *>(row + c);
-        v4f y;
-        y.x = ln_value(xv.x, mean, rstd, gamma, beta, c);
-        y.y = ln_value(xv.y, mean, rstd, gamma, beta, c + 1);
-        y.z = ln_value(xv.z, mean, rstd, gamma, beta, c + 2);
-        y.w = ln_value(xv.w, mean, rstd, gamma, beta, c + 3);
-        if (y_out) *reinterpret_cast<v4f *>(y_out + m * D + c) = y;
-        if (q) {
-          const uint32_t b0 = static_cast<uint8_t>(ln_code(y.x, s, fq)), b1 = static_cast<uint8_t>(ln_code(y.y, s, fq));
-          const uint32_t b2 = static_cast<uint8_t>(ln_code(y.z, s, fq)), b3 = static_cast<uint8_t>(ln_code(y.w, s, fq));
-          *reinterpret_cast<uint32_t *>(q + m * D + c) = b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
-        }
+        const v4f one = {1.0f, 1.0f, 1.0f, 1.0f};
+        put(c, *reinterpret_cast<const v4f *>(row + c), gamma ? *reinterpret_cast<const v4f *>(gamma + c) : one,
+            beta ? *reinterpret_cast<const v4f *>(beta + c) : one);
       }
     } else {
       for (int64_t c = lane; c < D; c += 64) {
@@ -323,26 +348,35 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_colsum_kernel(const float *__
   part[(static_cast<int64_t>(blockIdx.y) * 2 + 1) * D + c] = ab;
 }
 
-__global__ __launch_bounds__(kThreads) void ln_bwd_fold_kernel(const float *__restrict__ part, int P, int64_t D,
-                                                               float *__restrict__ dgamma, float *__restrict__ dbeta) {
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (c >= D) return;
-  // four independent running sums per output so that loads overlap; the order of the additions is fixed
-  float ag[4] = {0.0f, 0.0f, 0.0f, 0.0f}, ab[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  int p = 0;
-  for (; p + 4 <= P; p += 4) {
+// Column sums of the partials: 64 columns per workgroup, its sixteen wavefronts share the partials (eight loads in
+// flight each) and are added up in order; blockIdx.y: the gamma or the beta sums.  (Two workgroups walking all 512
+// partials one after the other took 45 us.)
+constexpr int kFoldWaves = 16;
+__global__ __launch_bounds__(64 * kFoldWaves) void ln_bwd_fold_kernel(const float *__restrict__ part, int P, int64_t D,
+                                                                      float *__restrict__ dgamma, float *__restrict__ dbeta) {
+  float *const out = blockIdx.y ? dbeta : dgamma;
+  if (!out) return;
+  __shared__ float sm[kFoldWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + lane, cc = c < D ? c : D - 1;
+  float s = 0.0f;
+  for (int p = wave * 8; p < P; p += kFoldWaves * 8) {
+    float v[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      ag[u] += part[(static_cast<int64_t>(p + u) * 2) * D + c];
-      ab[u] += part[(static_cast<int64_t>(p + u) * 2 + 1) * D + c];
-    }
+    for (int u = 0; u < 8; ++u) v[u] = part[(static_cast<int64_t>(p + u < P ? p + u : P - 1) * 2 + blockIdx.y) * D + cc];
+    float q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = p + u < P ? v[u] : 0.0f;
+    s += ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
   }
-  for (; p < P; ++p) {
-    ag[0] += part[(static_cast<int64_t>(p) * 2) * D + c];
-    ab[0] += part[(static_cast<int64_t>(p) * 2 + 1) * D + c];
+  sm[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && c < D) {
+    float t = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kFoldWaves; ++w) t += sm[w][lane];
+    out[c] = t;
   }
-  if (dgamma) dgamma[c] = (ag[0] + ag[1]) + (ag[2] + ag[3]);
-  if (dbeta) dbeta[c] = (ab[0] + ab[1]) + (ab[2] + ab[3]);
 }
 
 // out = alpha * m
@@ -491,6 +525,7 @@ aqt_status launch_layernorm_quantize(const float *x, int64_t M, int64_t D, const
   const bool vec = (D % 4 == 0) && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                    (!y_out || reinterpret_cast<uintptr_t>(y_out) % 16 == 0) &&
                    (!q || reinterpret_cast<uintptr_t>(q) % 4 == 0) &&
+                   (!gamma || reinterpret_cast<uintptr_t>(gamma) % 16 == 0) && (!beta || reinterpret_cast<uintptr_t>(beta) % 16 == 0) &&
                    (!res || (reinterpret_cast<uintptr_t>(res) % 16 == 0 && reinterpret_cast<uintptr_t>(sum_out) % 16 == 0));
   if (vec && D <= 512) ln_stats_kernel<2><<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, eps, stats, partial, res, alpha, sum_out, zero_word);
   else if (vec && D <= 1024) ln_stats_kernel<4><<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, eps, stats, partial, res, alpha, sum_out, zero_word);
@@ -498,8 +533,8 @@ aqt_status launch_layernorm_quantize(const float *x, int64_t M, int64_t D, const
   AQT_HIP(hipGetLastError());
   if (res) x = sum_out;   // the second pass normalises the sum the first pass wrote
   const int qm = q ? qmax_of(bits) : 1;
-  if (vec) ln_quantize_kernel<true><<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, stats, partial, g, qm, q, scale, y_out, dev_status);
-  else ln_quantize_kernel<false><<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, stats, partial, g, qm, q, scale, y_out, dev_status);
+  auto kern = !vec ? ln_quantize_kernel<0> : D <= 512 ? ln_quantize_kernel<2> : D <= 1024 ? ln_quantize_kernel<4> : ln_quantize_kernel<-1>;
+  kern<<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, stats, partial, g, qm, q, scale, y_out, dev_status);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }
@@ -536,7 +571,7 @@ aqt_status launch_layernorm_bwd(const float *x, const float *stats, const float 
   }
   AQT_HIP(hipGetLastError());
   if (want_cols) {
-    ln_bwd_fold_kernel<<<static_cast<unsigned>(cdiv(D, kThreads)), kThreads, 0, st>>>(part, P, D, dgamma, dbeta);
+    ln_bwd_fold_kernel<<<dim3(static_cast<unsigned>(cdiv(D, 64)), 2), 64 * kFoldWaves, 0, st>>>(part, P, D, dgamma, dbeta);
     AQT_HIP(hipGetLastError());
   }
   return AQT_OK;
