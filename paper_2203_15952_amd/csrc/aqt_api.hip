@@ -201,7 +201,7 @@ struct WeightJobList {
 aqt_status weight_side(const aqt_dense_policy &p, const float *w, const aqt_saved &l, int64_t M, int64_t K, int64_t N,
                        int epilogue, uint32_t *wpart, void *wfrag, hipStream_t st, int32_t *dev_status,
                        WeightSide *out, WeightJobList *later = nullptr) {
-  const bool takes = p.bits_x && fwd_q_takes_fragments(M, K, N, epilogue) && reinterpret_cast<uintptr_t>(l.xq) % 16 == 0;
+  const bool takes = p.bits_x && fwd_q_uses_fragments(M, K, N, epilogue) && reinterpret_cast<uintptr_t>(l.xq) % 16 == 0;
   if (p.weights_ready) {
     const bool have = takes && l.wprep && reinterpret_cast<uintptr_t>(l.wprep) % 16 == 0;
     out->operand = have ? l.wprep : wfrag;
@@ -721,7 +721,7 @@ aqt_status aqt_dense_fwd(const float *x, const float *w, int64_t M, int64_t K, i
   AQT_TRY(launch_quantize(x, M, K, K, bits_x, AQT_AXIS_ALL, xq, s_x, saved ? saved->mask_x : nullptr,
                           f.partials, st, dev_status));
   // when the matrix-core kernel takes the shape, the weight quantizer emits its operand in fragment order itself
-  const bool frag = fwd_q_takes_fragments(M, K, N, epilogue) && reinterpret_cast<uintptr_t>(xq) % 16 == 0 &&
+  const bool frag = fwd_q_uses_fragments(M, K, N, epilogue) && reinterpret_cast<uintptr_t>(xq) % 16 == 0 &&
                     reinterpret_cast<uintptr_t>(f.wfrag) % 16 == 0;
   AQT_TRY(launch_quantize_weights(w, K, N, bits_w, wq, s_w, saved ? saved->wq_kn : nullptr,
                                   saved ? saved->mask_w : nullptr, f.wpart, st, dev_status, frag ? f.wfrag : nullptr));

@@ -99,6 +99,8 @@ aqt_status launch_dense_fwd_q(const int8_t *xq, const float *s_x, const void *wq
 // True when the matrix-core kernel takes the shape (then its weight operand may be handed over
 // already in fragment order: from the weight quantizer, or from launch_prepare_weights).
 bool fwd_q_takes_fragments(int64_t M, int64_t K, int64_t N, int epilogue);
+// True when it is also the kernel launch_dense_fwd_q picks, given the forward operand in its canonical form as well.
+bool fwd_q_uses_fragments(int64_t M, int64_t K, int64_t N, int epilogue);
 aqt_status launch_prepare_weights(const void *wq_packed, int64_t K, int64_t N, int bits_w, void *wprep,
                                   hipStream_t st);
 size_t fwd_q_workspace_bytes(int64_t K, int64_t N);

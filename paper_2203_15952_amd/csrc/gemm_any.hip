@@ -8,13 +8,14 @@
 // row pieces at a time, converts what has to be converted there once for all its wavefronts, and multiplies while
 // the next two slices' loads are in flight.  (Fragments fetched straight from memory, one row per lane, were tried
 // first: rows a power of two apart share a cache set and every access misses; dX 40 x 2048 -> 512 took 20 us
-// that way, 10 us this way.)  Small problems (WK = 8, one wavefront per group) are bound by the latency of a trip to
+// that way, 11 us this way.)  Small problems (WK = 8, one wavefront per group) are bound by the latency of a trip to
 // memory, so eight slices are in flight at a time; the sums are added up through LDS.
-// Measured at 4099 x 520 x 1000, int8 codes, against the one-thread-per-output kernels these replace: forward 18 us
-// (7902), dX 37 (6565), dW with its fold 50 (1096); forward 40 x 512 -> 2048 3.3 us (about 170).
+// Measured at 4099 x 520 x 1000, int8 codes, against the one-thread-per-output kernels these replace: forward 17 us
+// (7902), dX 37 (6565), dW with its fold 41 (1096); forward 40 x 512 -> 2048 3.5 us (about 170).
 //
-// Edges: rows and columns beyond the tensors are read at clamped, valid addresses and not stored; contraction
-// positions beyond the end are zeros, the pieces that straddle it are loaded element by element.
+// Edges: rows and columns beyond the tensors are read at clamped, valid addresses and not stored.  Contraction
+// positions beyond the end are zeros: a piece that would cross the end of its row is read so that it ends there and is
+// shifted down when it is staged (rows shorter than one piece are read element by element).
 #include <type_traits>
 
 #include "aqt_internal.h"
@@ -53,6 +54,30 @@ __device__ __forceinline__ v4i load16_guarded(const uint8_t *p, int64_t at, int6
   return v4i{static_cast<int>(d[0]), static_cast<int>(d[1]), static_cast<int>(d[2]), static_cast<int>(d[3])};
 }
 
+// 16 bytes moved down by `bytes` (0 .. 16), zeros from above.
+__device__ __forceinline__ v4i shift_down(v4i v, int bytes) {
+  if (bytes & 4) v = v4i{v.y, v.z, v.w, 0};
+  if (bytes & 8) v = v4i{v.z, v.w, 0, 0};
+  if (bytes & 16) v = v4i{0, 0, 0, 0};
+  const int b = bytes & 3;
+  v.x = static_cast<int>(__builtin_amdgcn_alignbyte(static_cast<uint32_t>(v.y), static_cast<uint32_t>(v.x), b));
+  v.y = static_cast<int>(__builtin_amdgcn_alignbyte(static_cast<uint32_t>(v.z), static_cast<uint32_t>(v.y), b));
+  v.z = static_cast<int>(__builtin_amdgcn_alignbyte(static_cast<uint32_t>(v.w), static_cast<uint32_t>(v.z), b));
+  v.w = static_cast<int>(__builtin_amdgcn_alignbyte(0u, static_cast<uint32_t>(v.w), b));
+  return v;
+}
+__device__ __forceinline__ v4f shift_down(v4f v, int elements) {   // 0 .. 4
+  if (elements & 1) v = v4f{v.y, v.z, v.w, 0.0f};
+  if (elements & 2) v = v4f{v.z, v.w, 0.0f, 0.0f};
+  if (elements & 4) v = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  return v;
+}
+// how far a piece of `size` that starts at `at` was moved up to end at `end`, at most `size`
+__device__ __forceinline__ int moved(int64_t at, int64_t end, int size) {
+  const int64_t d = at + size - end;
+  return d <= 0 ? 0 : d < size ? static_cast<int>(d) : size;
+}
+
 // LDS rows are CH chunks of 16 bytes without padding; the chunk index is XORed with row bits so that the rows
 // of a fragment read spread over all banks.
 template <int CH>
@@ -71,62 +96,77 @@ __device__ __forceinline__ v2i expand16(uint32_t w) {
   return o;
 }
 
-// The slice loop of a workgroup.  load(set, slice) requests a slice into register set 0 or 1, stage(set, slot)
-// moves that set to LDS, multiply(slot) consumes it.
+// The slice loop of a workgroup.  load(set, slice) requests a slice into register set 0 or 1, stage(set, slice, slot)
+// moves it to LDS, multiply(slot) consumes it.
 //   WK == 1: all wavefronts share the slices; two LDS slots, so that a slice is staged (and converted) while the one
 //            before it is multiplied, one barrier per slice, loads two slices ahead.
 //   WK > 1:  every wavefront has its own slices wk, wk + WK, ... and its own slot: its LDS operations are executed
 //            in order, so no barrier is needed and the wavefronts overlap as they come.
+// The loop has no branch around a load (past the end the last slice is requested again): behind a branch the compiler
+// cannot count what is in flight and waits for everything, which undoes the prefetch.
 template <int WK, class Load, class Stage, class Multiply>
 __device__ __forceinline__ void run_slices(uint8_t *lds, int slice_bytes, int wk, int64_t slices, Load load, Stage stage,
                                            Multiply multiply) {
   constexpr std::integral_constant<int, 0> set0{};
   constexpr std::integral_constant<int, 1> set1{};
+  const int64_t mine = WK > 1 ? (slices - wk + WK - 1) / WK : slices;   // this wavefront's slices
+  auto at = [&](int64_t i) { return wk + WK * (i < mine ? i : mine - 1); };
+  if (mine <= 0) return;   // WK > 1 only
   if (WK > 1) {
     uint8_t *const slot = lds + wk * slice_bytes;
-    if (wk < slices) load(set0, wk);
-    if (wk + WK < slices) load(set1, wk + WK);
-    auto one = [&](auto set, int64_t s) {
-      __builtin_amdgcn_wave_barrier();
-      stage(set, slot);
-      if (s + 2 * WK < slices) load(set, s + 2 * WK);
+    load(set0, at(0));
+    load(set1, at(1));
+    for (int64_t i = 0; i < mine; i += 2) {
+      stage(set0, at(i), slot);
+      load(set0, at(i + 2));
       __builtin_amdgcn_wave_barrier();
       multiply(slot);
-    };
-    for (int64_t s = wk; s < slices; s += 2 * WK) {
-      one(set0, s);
-      if (s + WK < slices) one(set1, s + WK);
+      if (i + 1 >= mine) break;
+      __builtin_amdgcn_wave_barrier();
+      stage(set1, at(i + 1), slot);
+      load(set1, at(i + 3));
+      __builtin_amdgcn_wave_barrier();
+      multiply(slot);
+      __builtin_amdgcn_wave_barrier();
     }
     return;
   }
   uint8_t *const slot0 = lds, *const slot1 = lds + slice_bytes;
-  load(set0, 0);
-  if (1 < slices) load(set1, 1);
-  stage(set0, slot0);
-  if (2 < slices) load(set0, 2);
+  load(set0, at(0));
+  load(set1, at(1));
+  stage(set0, at(0), slot0);
+  load(set0, at(2));
   __syncthreads();
-  for (int64_t s = 0; s < slices; s += 2) {
-    if (s + 1 < slices) {
-      stage(set1, slot1);
-      if (s + 3 < slices) load(set1, s + 3);
-    }
+  for (int64_t s = 0; s < mine; s += 2) {
+    stage(set1, at(s + 1), slot1);
+    load(set1, at(s + 3));
     multiply(slot0);
     __syncthreads();
-    if (s + 1 >= slices) break;
-    if (s + 2 < slices) {
-      stage(set0, slot0);
-      if (s + 4 < slices) load(set0, s + 4);
-    }
+    if (s + 1 >= mine) break;
+    stage(set0, at(s + 2), slot0);
+    load(set0, at(s + 4));
     multiply(slot1);
     __syncthreads();
   }
+}
+
+// One slice that is loaded whole before anything else (rows shorter than a piece); WK > 1: by one wavefront alone.
+template <int WK, class LoadNarrow, class Stage, class Multiply>
+__device__ __forceinline__ void run_narrow(uint8_t *slot, LoadNarrow load_narrow, Stage stage, Multiply multiply) {
+  constexpr std::integral_constant<int, 0> set0{};
+  load_narrow(set0);
+  stage(set0, 0, slot);
+  if (WK > 1) __builtin_amdgcn_wave_barrier();
+  else __syncthreads();
+  multiply(slot);
+  if (WK == 1) __syncthreads();
 }
 
 // ---- forward: int8 codes x int8 / int4 codes, int32 sums -----------------------------------
 // A wavefront owns TM x TN blocks of 32 x 32; a GLU tile pairs value (even) and gate (odd) column blocks.
 // BK: fan-in positions per slice.
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI>
-__global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
+__global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense_fwd_any_kernel(
     const int8_t *__restrict__ xq, const float *__restrict__ s_x, const uint8_t *__restrict__ wq,
     const float *__restrict__ s_w, int64_t M, int64_t K, int64_t N, const float *__restrict__ bias,
     float *__restrict__ y, int32_t *__restrict__ acc_out, uint32_t *__restrict__ y_absmax, float *__restrict__ dact,
@@ -169,23 +209,23 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
   // G is a multiple of the chunks per row: a thread's chunks sit at the same place of their rows
   const int ca = gt % CHA, cb = gt % CHB;
   v4i ra[2][NA], rb[2][NB];
+  constexpr int kRowSlice = PACKED ? BK / 2 : BK;   // bytes of a weight row per slice
+  const bool narrow = K < 16 || row_bytes < 16;     // uniform
   auto load = [&](auto set, int64_t slice) {
     constexpr int S = decltype(set)::value;
-    const int64_t at = slice * BK + 16 * ca, bt = slice * (PACKED ? BK / 2 : BK) + 16 * cb;
-    if (at + 16 <= K) {
+    const int64_t a0 = slice * BK + 16 * ca, b0 = slice * kRowSlice + 16 * cb;
+    const int64_t at = a0 + 16 <= K ? a0 : K - 16, bt = b0 + 16 <= row_bytes ? b0 : row_bytes - 16;
 #pragma unroll
-      for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4i>(pa[u] + at);
-    } else {
+    for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4i>(pa[u] + at);
 #pragma unroll
-      for (int u = 0; u < NA; ++u) ra[S][u] = load16_guarded(pa[u], at, K);
-    }
-    if (bt + 16 <= row_bytes) {
+    for (int u = 0; u < NB; ++u) rb[S][u] = load_at<v4i>(pb[u] + bt);
+  };
+  auto load_narrow = [&](auto set) {   // fewer than 32 positions: part of the first slice
+    constexpr int S = decltype(set)::value;
 #pragma unroll
-      for (int u = 0; u < NB; ++u) rb[S][u] = load_at<v4i>(pb[u] + bt);
-    } else {
+    for (int u = 0; u < NA; ++u) ra[S][u] = load16_guarded(pa[u], 16 * ca, K);
 #pragma unroll
-      for (int u = 0; u < NB; ++u) rb[S][u] = load16_guarded(pb[u], bt, row_bytes);
-    }
+    for (int u = 0; u < NB; ++u) rb[S][u] = load16_guarded(pb[u], 16 * cb, row_bytes);
   };
   v16i acc[TM][TN];
 #pragma unroll
@@ -194,10 +234,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-  const int64_t slices = cdiv(K, BK);
   // slot: where a slice lives in LDS (its A rows, then its B rows)
-  auto stage = [&](auto set, uint8_t *slot) {
+  auto stage = [&](auto set, int64_t slice, uint8_t *slot) {
     constexpr int S = decltype(set)::value;
+    if ((slice + 1) * BK > K && !narrow) {
+      const int da = moved(slice * BK + 16 * ca, K, 16), db = moved(slice * kRowSlice + 16 * cb, row_bytes, 16);
+#pragma unroll
+      for (int u = 0; u < NA; ++u) ra[S][u] = shift_down(ra[S][u], da);
+#pragma unroll
+      for (int u = 0; u < NB; ++u) rb[S][u] = shift_down(rb[S][u], db);
+    }
 #pragma unroll
     for (int u = 0; u < NA; ++u) *reinterpret_cast<v4i *>(slot + chunk_at<CHA>((gt + u * G) / CHA, ca)) = ra[S][u];
 #pragma unroll
@@ -227,7 +273,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
       }
     }
   };
-  run_slices<WK>(lds, kSliceBytes, wk, slices, load, stage, multiply);
+  if (!narrow) run_slices<WK>(lds, kSliceBytes, wk, cdiv(K, BK), load, stage, multiply);
+  else if (wk == 0) run_narrow<WK>(lds, load_narrow, stage, multiply);
 
   // The groups of a tile add their sums (integers: any order) and share the epilogue: each takes 16 / WK of the
   // accumulator registers.
@@ -258,6 +305,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
   const float sx = s_x[0];
   uint32_t amax = 0u;
   constexpr int JS = GLU ? 2 : 1;
+  const int64_t m_lane = bm * BM + wm * 32 * TM + 4 * lk;   // this lane's first row
 #pragma unroll
   for (int j = 0; j < TN; j += JS) {
     const int64_t n = chan(wn * TN + j) + lr;
@@ -265,34 +313,36 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void dense_fwd_any_kernel(
     const int64_t nc = live ? n : oc - 1, ng = nc + (GLU ? oc : 0);
     const float sc_a = sx * s_w[nc], bias_a = bias ? bias[nc] : 0.0f;
     const float sc_b = GLU ? sx * s_w[ng] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
+    const int rows = live ? static_cast<int>(M - m_lane < BM ? M - m_lane : BM) : 0;   // rows of this lane's column in the tensor
+    float *const yl = y + m_lane * oc + n, *const dl = dact + m_lane * N + n;
+    int32_t *const al = acc_out + m_lane * N + n;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int rr = 0; rr < RW; ++rr) {
-        const int r = wk * RW + rr;
-        const int64_t m = bm * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+        const int r = wk * RW + rr, row = i * 32 + 8 * (r >> 2) + (r & 3);   // the same in every lane
         const int a0 = sum_of(i, j, rr);
         const int a1 = GLU ? sum_of(i, j + JS - 1, rr) : 0;
-        if (!live || m >= M) continue;
+        if (row >= rows) continue;
         if (acc_out) {
-          acc_out[m * N + n] = a0;
-          if (GLU) acc_out[m * N + ng] = a1;
+          al[row * N] = a0;
+          if (GLU) al[row * N + oc] = a1;
         }
         const float v = dequant_f32(a0, sc_a) + bias_a;
         float out = v;
         if (EPI == AQT_EPI_SWISH) {
           const float sg = sigmoid_f32(v);
           out = v * sg;
-          if (dact) dact[m * N + n] = swish_dact_f32(v, sg);
+          if (dact) dl[row * N] = swish_dact_f32(v, sg);
         } else if (GLU) {
           const float sg = sigmoid_f32(dequant_f32(a1, sc_b) + bias_b);
           out = v * sg;
           if (dact) {
-            dact[m * N + n] = sg;
-            dact[m * N + ng] = glu_gate_dact_f32(v, sg);
+            dl[row * N] = sg;
+            dl[row * N + oc] = glu_gate_dact_f32(v, sg);
           }
         }
-        y[m * oc + n] = out;
+        yl[row * oc] = out;
         amax = max(amax, __float_as_uint(out) & 0x7FFFFFFFu);
       }
   }
@@ -359,7 +409,7 @@ __device__ __forceinline__ v4i nibbles8_bf16(uint32_t w) {   // eight int4 codes
 //   MODE 1 + e:    weight-only forward with epilogue e: f = x [M,K], q = the forward weight operand [N][K]
 // LONG: a group's share of the contraction exceeds kChain, so float32 sums are moved to float64 on the way.
 template <int TM, int TN, int WM, int WN, int WK, bool PACKED, int MODE, bool LONG>
-__global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
+__global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 && !LONG ? 4 : 2) void f32_codes_any_kernel(
     const float *__restrict__ f, const float *__restrict__ scale, const uint8_t *__restrict__ q, int64_t M, int64_t R,
     int64_t C, const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x, const float *__restrict__ factor,
     const float *__restrict__ bias, float *__restrict__ out, int tiles_r) {
@@ -403,44 +453,42 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
   }
   v4f ra[2][NA], rs[2] = {{1.0f, 1.0f, 1.0f, 1.0f}, {1.0f, 1.0f, 1.0f, 1.0f}};
   v4i rb[2][NB];
+  constexpr int kPiece = PACKED ? 8 : 16;   // bytes of sixteen codes
+  const bool narrow = C < 4 || row_bytes < kPiece;   // uniform
   auto load = [&](auto set, int64_t slice) {
     constexpr int S = decltype(set)::value;
-    const int64_t c = slice * kSlice + 4 * piece;
-    if (c + 4 <= C) {
+    const int64_t c0 = slice * kSlice + 4 * piece, a0 = slice * (2 * kPiece) + kPiece * (gt & 1);
+    const int64_t c = c0 + 4 <= C ? c0 : C - 4, at = a0 + kPiece <= row_bytes ? a0 : row_bytes - kPiece;
 #pragma unroll
-      for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4f>(pf[u] + c);
-      if (DX) rs[S] = load_at<v4f>(scale + c);
-    } else {
+    for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4f>(pf[u] + c);
+    if (DX) rs[S] = load_at<v4f>(scale + c);
 #pragma unroll
-      for (int u = 0; u < NA; ++u) {
-        ra[S][u] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (c + e < C) ra[S][u][e] = pf[u][c + e];
-      }
-      if (DX) {
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (c + e < C) rs[S][e] = scale[c + e];
+    for (int u = 0; u < NB; ++u) {   // a thread without codes reads what it will not use
+      if (PACKED) {
+        const v2i w = load_at<v2i>(pq[u] + at);
+        rb[S][u] = v4i{w.x, w.y, 0, 0};
+      } else {
+        rb[S][u] = load_at<v4i>(pq[u] + at);
       }
     }
-    if (!has_codes) return;
-    constexpr int kPiece = PACKED ? 8 : 16;   // bytes of sixteen codes
-    const int64_t at = slice * (2 * kPiece) + kPiece * (gt & 1);
-    if (at + kPiece <= row_bytes) {
+  };
+  auto load_narrow = [&](auto set) {   // fewer than 16 positions
+    constexpr int S = decltype(set)::value;
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        if (PACKED) {
-          const v2i w = load_at<v2i>(pq[u] + at);
-          rb[S][u].x = w.x; rb[S][u].y = w.y;
-        } else {
-          rb[S][u] = load_at<v4i>(pq[u] + at);
-        }
-      }
-    } else {
+    for (int u = 0; u < NA; ++u) {
+      ra[S][u] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int u = 0; u < NB; ++u) rb[S][u] = load16_guarded(pq[u], at, row_bytes);
+      for (int e = 0; e < 4; ++e)
+        if (4 * piece + e < C) ra[S][u][e] = pf[u][4 * piece + e];
     }
+    if (DX) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * piece + e < C) rs[S][e] = scale[4 * piece + e];
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+      rb[S][u] = load16_guarded(pq[u], kPiece * (gt & 1), (gt & 1) ? kPiece : row_bytes);   // all in the first piece
   };
   v16f acc[TM][TN];
   double sum[LONG ? TM : 1][LONG ? TN : 1][16];
@@ -464,11 +512,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
           acc[i][j][r] = 0.0f;
         }
   };
-  const int64_t slices = cdiv(C, kSlice);
   int since = 0;
-  auto stage = [&](auto set, uint8_t *slot) {
+  auto stage = [&](auto set, int64_t slice, uint8_t *slot) {
     constexpr int S = decltype(set)::value;
     uint8_t *const sA = slot, *const sB = slot + 3 * kImage;
+    if ((slice + 1) * kSlice > C && !narrow) {
+      const int df = moved(slice * kSlice + 4 * piece, C, 4), dq = moved(slice * (2 * kPiece) + kPiece * (gt & 1), row_bytes, kPiece);
+#pragma unroll
+      for (int u = 0; u < NA; ++u) ra[S][u] = shift_down(ra[S][u], df);
+      if (DX) rs[S] = shift_down(rs[S], df);
+#pragma unroll
+      for (int u = 0; u < NB; ++u) rb[S][u] = shift_down(rb[S][u], dq);
+    }
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       v4f v = ra[S][u];
@@ -508,7 +563,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
       since = 0;
     }
   };
-  run_slices<WK>(lds, kSliceBytes, wk, slices, load, stage, multiply);
+  if (!narrow) run_slices<WK>(lds, kSliceBytes, wk, cdiv(C, kSlice), load, stage, multiply);
+  else if (wk == 0) run_narrow<WK>(lds, load_narrow, stage, multiply);
   if (LONG) fold();
   constexpr int RW = 16 / WK;
   if (WK > 1) {
@@ -533,20 +589,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
     }
     return v;
   };
+  const int64_t m_lane = bm * BM + wm * 32 * TM + 4 * lk;   // this lane's first row
   if (DX) {
     const bool keep = s_x[0] != 0.0f;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int64_t n = chan(wn * TN + j) + lr;
+      const int64_t n = chan(wn * TN + j) + lr, at0 = m_lane * R + n;
+      const int rows = n < R ? static_cast<int>(M - m_lane < BM ? M - m_lane : BM) : 0;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int rr = 0; rr < RW; ++rr) {
-          const int r = wk * RW + rr;
-          const int64_t m = bm * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+          const int r = wk * RW + rr, row = i * 32 + 8 * (r >> 2) + (r & 3);   // the same in every lane
           float v = static_cast<float>(sum_of(i, j, rr));
-          if (n >= R || m >= M) continue;
-          const int64_t at = m * R + n;
+          if (row >= rows) continue;
+          const int64_t at = at0 + row * R;
           if (factor) v = v * factor[at];
           out[at] = (mask_x ? mask_bit(mask_x, at) : keep) ? v : 0.0f;
         }
@@ -561,19 +618,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, 2) void f32_codes_any_kernel(
     const int64_t nc = live ? n : oc - 1, ng = nc + (GLU ? oc : 0);
     const double sc_a = scale[nc], sc_b = GLU ? scale[ng] : 0.0f;
     const float bias_a = bias ? bias[nc] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
+    const int rows = live ? static_cast<int>(M - m_lane < BM ? M - m_lane : BM) : 0;
+    float *const ol = out + m_lane * oc + n;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int rr = 0; rr < RW; ++rr) {
-        const int r = wk * RW + rr;
-        const int64_t m = bm * BM + (wm * TM + i) * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+        const int r = wk * RW + rr, row = i * 32 + 8 * (r >> 2) + (r & 3);
         const float v = static_cast<float>(sum_of(i, j, rr) * sc_a) + bias_a;
-        const float gt2 = GLU ? static_cast<float>(sum_of(i, j + JS - 1, rr) * sc_b) + bias_b : 0.0f;
-        if (!live || m >= M) continue;
+        const float gate = GLU ? static_cast<float>(sum_of(i, j + JS - 1, rr) * sc_b) + bias_b : 0.0f;
+        if (row >= rows) continue;
         float o = v;
         if (MODE == 1 + AQT_EPI_SWISH) o = swish_f32(v);
-        else if (GLU) o = v * sigmoid_f32(gt2);
-        out[m * oc + n] = o;
+        else if (GLU) o = v * sigmoid_f32(gate);
+        ol[row * oc] = o;
       }
   }
 }
@@ -615,53 +673,45 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
   const int g = t & 31, mg = t >> 5;          // this thread's column group and its four rows 4 mg .. + 3 of a slice
   const int64_t kc = k0 + 4 * g, nc = n0 + 4 * g;
   const bool kwhole = kc + 4 <= K, nwhole = nc + 4 <= N;
-  Off xo[4], yo[4];
-  auto offsets = [&](int64_t m) {             // rows beyond the slab are read from its last one
+  const bool narrow = K < 4 || N < 4, edge = k0 + kDwTile > K || n0 + kDwTile > N;   // uniform
+  const int64_t kr = narrow || kwhole ? kc : K - 4, nr = narrow || nwhole ? nc : N - 4;
+  const int dk = moved(kc, K, 4), dn = moved(nc, N, 4);
+  const int64_t slices = cdiv(m1 - m0, kSlice);
+  const int last_rows = static_cast<int>(m1 - m0 - (slices - 1) * kSlice);
+  Off xo[4], yo[4], xl[4], yl[4];   // offsets of this thread's rows in a slice; in the last one, where rows beyond the end are its last
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t left = m1 - 1 - m, r = 4 * mg + i < left ? 4 * mg + i : left;
-      xo[i] = static_cast<Off>(r * K + kc);
-      yo[i] = static_cast<Off>((r * N + nc) * 4);
-    }
-  };
+  for (int i = 0; i < 4; ++i) {
+    const int64_t r = 4 * mg + i, l = r < last_rows ? r : last_rows - 1;
+    xo[i] = static_cast<Off>(r * K + kr);
+    yo[i] = static_cast<Off>((r * N + nr) * 4);
+    xl[i] = static_cast<Off>(l * K + kr);
+    yl[i] = static_cast<Off>((l * N + nr) * 4);
+  }
   uint32_t rc[2][4];
   v4f rg[2][4];
   auto load = [&](auto set, int64_t slice) {
     constexpr int S = decltype(set)::value;
     const int64_t m = m0 + slice * kSlice;
-    if (m + kSlice > m1) offsets(m);
+    const bool last = slice == slices - 1;
     const char *x = reinterpret_cast<const char *>(xq) + m * K, *y = reinterpret_cast<const char *>(dy + m * N);
-    if (kwhole) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rc[S][i] = load_at<uint32_t>(x + xo[i]);
-    } else {
+    for (int i = 0; i < 4; ++i) rc[S][i] = load_at<uint32_t>(x + (last ? xl[i] : xo[i]));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        rc[S][i] = 0u;
+    for (int i = 0; i < 4; ++i) rg[S][i] = load_at<v4f>(y + (last ? yl[i] : yo[i]));
+  };
+  int64_t narrow_slice = 0;
+  auto load_narrow = [&](auto set) {   // fewer than four columns of an operand: element by element
+    constexpr int S = decltype(set)::value;
 #pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (kc + e < K) rc[S][i] |= static_cast<uint32_t>(load_at<uint8_t>(x + xo[i] + e)) << (8 * e);
+    for (int i = 0; i < 4; ++i) {
+      const int64_t r = m0 + narrow_slice * kSlice + 4 * mg + i;
+      rc[S][i] = 0u;
+      rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (r < m1 && kc + e < K) rc[S][i] |= static_cast<uint32_t>(static_cast<uint8_t>(xq[r * K + kc + e])) << (8 * e);
+        if (r < m1 && nc + e < N) rg[S][i][e] = dy[r * N + nc + e];
       }
-    }
-    if (nwhole) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) rg[S][i] = load_at<v4f>(y + yo[i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (nc + e < N) rg[S][i][e] = load_at<float>(y + yo[i] + 4 * e);
-      }
-    }
-    if (m + kSlice > m1) {   // rows beyond the slab contribute nothing
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (m + 4 * mg + i >= m1) {
-          rc[S][i] = 0u;
-          rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-        }
     }
   };
   // a wavefront multiplies all four codes blocks with one block of the gradient (seven fragment reads per twelve products)
@@ -670,8 +720,23 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
-  auto stage = [&](auto set, uint8_t *slot) {
+  auto stage = [&](auto set, int64_t slice, uint8_t *slot) {
     constexpr int S = decltype(set)::value;
+    if (edge && !narrow) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        rc[S][i] = dk < 4 ? rc[S][i] >> (8 * dk) : 0u;
+        rg[S][i] = shift_down(rg[S][i], dn);
+      }
+    }
+    if (slice == slices - 1 && last_rows < kSlice) {   // rows beyond the slab contribute nothing
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * mg + i >= last_rows) {
+          rc[S][i] = 0u;
+          rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       uint8_t *const at = slot + chunk_at<kCh>(32 * b + g, mg >> 1) + 8 * (mg & 1);
@@ -698,8 +763,9 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
       }
     }
   };
-  offsets(m0);
-  run_slices<1>(lds, kSliceBytes, 0, cdiv(m1 - m0, kSlice), load, stage, multiply);
+  if (!narrow) run_slices<1>(lds, kSliceBytes, 0, slices, load, stage, multiply);
+  else
+    for (; narrow_slice < slices; ++narrow_slice) run_narrow<1>(lds, load_narrow, stage, multiply);
   // Out through LDS as whole rows, 32 tile rows 4 q + p at a time: they are codes block p, and tile column 4 g + b is
   // gradient block b = wave, column g.
   constexpr int kRow = kDwTile + 4;
@@ -760,15 +826,21 @@ __global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__
 
 // Which workgroup arrangement.  128 x 128 tiles move the fewest bytes through LDS per product but there have to be
 // enough of them for 256 compute units; narrower ones when the columns would mostly be padding; the split
-// contraction below that.
+// contraction below that.  Eight wavefronts per workgroup, so that two share a SIMD even where the launch has one
+// workgroup per compute unit (the staging of one runs under the products of the other).
+// The lines were drawn from sweeps over all five arrangements (us, forward / dX): 3200 x 512 -> 128 (50 tiles of 64 x 128)
+// 5.9 as such, 4.1 split; 800 x 256 -> 1024 (104 tiles) 5.2 / 5.7 split; 10008 x 144 -> 576 12.4 in 64 x 128, 10.7 in
+// 128 x 64; dX 3200 x 128 x 512 (50 tiles) 14.1, split 6.9; dX 3000 x 576 x 144 (235 tiles) 9.1, split 14.1.
 enum class Tile { kLarge, kRows, kNarrow, kSmall, kSmallest };   // 128 x 128, 64 x 128, 128 x 64; split contraction: 32 x 64, 32 x 32
-Tile pick_tile(int64_t M, int64_t cols, bool glu) {
+Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, bool glu, bool integer) {
   const int64_t narrow = cdiv(M, 128) * cdiv(cols, 64), large = cdiv(M, 128) * cdiv(cols, 128), rows = cdiv(M, 64) * cdiv(cols, 128);
-  const bool odd = cdiv(cols, 64) % 2 && cols < 512;   // half of the last 128-wide tile would be padding
+  const bool odd = cdiv(cols, 64) % 2 && cols < 640;   // half of the last 128-wide tile would be padding
   if (odd && narrow >= 128) return Tile::kNarrow;
   if (large >= 192) return Tile::kLarge;
-  if (rows >= 160) return Tile::kRows;
-  return glu || cdiv(M, 32) * cdiv(cols, 64) >= 128 ? Tile::kSmall : Tile::kSmallest;
+  if (rows >= (integer ? (contraction <= 256 ? 64 : 100) : 160)) return Tile::kRows;
+  if (glu) return Tile::kSmall;
+  // 32 x 64 halves the conversions of the float operand, where the columns fill it; codes need none
+  return !integer && cdiv(cols, 32) % 2 == 0 && cdiv(M, 32) * cdiv(cols, 64) >= 128 ? Tile::kSmall : Tile::kSmallest;
 }
 
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
@@ -792,9 +864,11 @@ template <bool PACKED>
 aqt_status fwd_any_sized(const int8_t *xq, const float *s_x, const void *wq, const float *s_w, int64_t M, int64_t K, int64_t N,
                          const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
                          hipStream_t st) {
-  switch (pick_tile(M, N, epilogue == AQT_EPI_GLU)) {
-    case Tile::kLarge: return fwd_any<2, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
-    case Tile::kRows: return fwd_any<1, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+  switch (pick_tile(M, N, K, epilogue == AQT_EPI_GLU, true)) {
+    case Tile::kLarge: return fwd_any<1, 2, 4, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+    case Tile::kRows:
+      if (epilogue != AQT_EPI_GLU) return fwd_any<1, 1, 2, 4, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+      return fwd_any<1, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
     case Tile::kNarrow: return fwd_any<1, 2, 4, 1, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
     case Tile::kSmallest: return fwd_any<1, 1, 1, 1, 8, 64, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
     default: return fwd_any<1, 2, 1, 1, 8, 64, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
@@ -808,8 +882,8 @@ aqt_status f32_codes_any(int mode, const float *f, const float *scale, const voi
   const int64_t oc = mode == 1 + AQT_EPI_GLU ? R / 2 : R;
   const int64_t tr = cdiv(oc, (mode == 1 + AQT_EPI_GLU ? 16 : 32) * TN * WN), tm = cdiv(M, 32 * TM * WM);
   if (tr * tm > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
-  const bool lng = C > int64_t(kChain) * WK && TM == 1;   // 128 x 128 tiles are only picked for short contractions
-#define AQT_PICK(MODE) (lng ? f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, TM == 1> \
+  const bool lng = C > int64_t(kChain) * WK;
+#define AQT_PICK(MODE) (lng ? f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, true> \
                             : f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, false>)
   auto kern = mode == 1 + AQT_EPI_NONE    ? AQT_PICK(1 + AQT_EPI_NONE)
               : mode == 1 + AQT_EPI_SWISH ? AQT_PICK(1 + AQT_EPI_SWISH)
@@ -826,11 +900,18 @@ template <bool PACKED>
 aqt_status f32_codes_any_sized(int mode, const float *f, const float *scale, const void *q, int64_t M, int64_t R, int64_t C,
                                const float *s_x, const uint32_t *mask_x, const float *factor, const float *bias, float *out,
                                hipStream_t st) {
-  const Tile tile = pick_tile(M, R, mode == 1 + AQT_EPI_GLU);
-  switch (tile == Tile::kLarge && C > kChain ? Tile::kRows : tile) {   // float64 sums of a 128 x 128 tile would not fit the registers
-    case Tile::kLarge: return f32_codes_any<2, 2, 2, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-    case Tile::kRows: return f32_codes_any<1, 2, 2, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-    case Tile::kNarrow: return f32_codes_any<1, 2, 4, 1, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+  const bool glu = mode == 1 + AQT_EPI_GLU;
+  Tile tile = pick_tile(M, R, C, glu, false);
+  // the float64 sums of long contractions need registers the larger tile does not leave
+  if (tile == Tile::kSmall && C > 8 * kChain && !glu) tile = Tile::kSmallest;
+  switch (tile) {
+    case Tile::kLarge: return f32_codes_any<1, 2, 4, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+    case Tile::kRows:
+      if (!glu) return f32_codes_any<1, 1, 2, 4, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+      return f32_codes_any<1, 2, 2, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+    case Tile::kNarrow:
+      if (!glu) return f32_codes_any<1, 1, 4, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+      return f32_codes_any<1, 2, 4, 1, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
     case Tile::kSmallest: return f32_codes_any<1, 1, 1, 1, 8, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
     default: return f32_codes_any<1, 2, 1, 1, 8, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
   }

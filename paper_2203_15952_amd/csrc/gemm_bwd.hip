@@ -807,12 +807,17 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   BwdPlan p{};
   const bool fits32 = M < (int64_t(1) << 31) / (K > N ? K : N);
   // dX: columns are K, contraction N in stages of 32; row tiles of 128 (the last one may be shifted)
-  p.dx_mfma = fits32 && (N % kSN == 0) && (K % 128 == 0) && (M >= 128);
+  // (up to 64 such tiles the split contraction of gemm_any.hip is faster, for all its three passes: with the
+  // re-ordering of the codes 20 us against 9 at 1024 x 1024 -> 256, 39 against 30 at 2048 x 2048 -> 512)
+  p.dx_mfma = fits32 && (N % kSN == 0) && (K % 128 == 0) && (M >= 128) && cdiv(M, 128) * (K / 128) > 64;
   p.dx_wide = (K % 256 == 0) && cdiv(M, 128) * (K / 256) >= 512;
   p.dx_wide8 = p.dx_wide && (K % 512 == 0) && cdiv(M, 128) * (K / 512) >= 256;
   // dW: 256 x 256 tiles (eight wavefronts, one workgroup per compute unit) when N allows, else 256 x 128
   // (two per compute unit); slabs over M so that the launch fills the chip once
-  p.dw_mfma = fits32 && (K % 256 == 0) && (N % 128 == 0);
+  // (below about 4e9 multiply-adds the smaller tiles of gemm_any.hip win although they take three passes: few large tiles
+  // mean many slabs, and their partial results cost more than the products: 12800 x 512 x 512 43 us against 36,
+  // 1024 x 256 x 1024 32 against 20; 4096 x 512 x 2048 41 against 43)
+  p.dw_mfma = fits32 && (K % 256 == 0) && (N % 128 == 0) && M >= 4000000000ll / (K * N);
   p.dw_wide8 = p.dw_mfma && (N % 256 == 0);
   const int64_t tiles = p.dw_mfma ? (K / 256) * (N / (p.dw_wide8 ? 256 : 128)) : 1;
   int64_t slabs = p.dw_mfma ? cdiv(p.dw_wide8 ? 256 : 512, tiles) : 1;
@@ -892,7 +897,8 @@ aqt_status launch_dense_fwd_wonly(const float *x, const void *wq_packed, const f
   // column tiles of 128 channels (64 value + 64 gate channels for GLU), 256 when there are enough of them
   const int64_t nn = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
   const int64_t unit = (epilogue == AQT_EPI_GLU) ? 64 : 128;
-  if (fits32 && aligned && M >= 128 && K % kSN == 0 && nn % unit == 0) {
+  // up to 64 tiles of 128 x 128: gemm_any.hip (1024 x 1024 -> 256 9 us against 19; 2048 x 2048 -> 512 29 against 36)
+  if (fits32 && aligned && M >= 128 && K % kSN == 0 && nn % unit == 0 && cdiv(M, 128) * cdiv(N, 128) > 64) {
     v4i *frag = static_cast<v4i *>(ws);
     const int64_t pieces = N * (K / 8);
     int g = static_cast<int>(cdiv(pieces, kThreads));

@@ -36,6 +36,8 @@ SHAPES = [
     (2051, 72, 46, 8, 0),         # several slabs of rows
     (20000, 144, 60, 8, 0),       # 128 x 64 tiles (odd number of 64-channel blocks); many slabs
     (9, 40, 4300, 4, 0),          # dX: a split contraction long enough for the float64 sums
+    (130, 3, 2, 8, 0), (130, 2, 3, 4, 0), (9, 15, 17, 8, 1), (9, 31, 14, 4, 2), (200, 33, 5, 4, 0),   # rows shorter than a piece
+    (300, 50, 6, 8, 2), (5000, 30, 31, 4, 1), (25000, 17, 129, 8, 0),
     (6, 4400, 33, 8, 0),          # the same for the weight-only forward
     (24700, 96, 130, 8, 0),       # 128 x 128 tiles, short contraction
 ]
