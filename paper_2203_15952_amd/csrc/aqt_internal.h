@@ -159,7 +159,19 @@ aqt_status launch_dwconv_bwd(const float *dout, const float *dmul, const float *
                              int64_t C, int kw, int pad_left, float *dx, float *dw, float *dbias, void *ws,
                              hipStream_t st);
 
-// ---- attention core of the self-attention module (attention.hip) ---------------------------
+// ---- attention core of the self-attention module (attention.hip, attention_fwd.hip, attention_bwd.hip) -------------
+struct AttnShape {
+  int64_t B, D;
+  int T;                        // frames: positions within an utterance are 32-bit (2^31 - 1 here: too long for that)
+  int heads, dh, left, right;   // left / right < 0: no limit on that side, otherwise at most T
+  int qtiles;                   // 128-frame tiles per utterance
+  float scale_log2e, scale;     // log2(e) / sqrt(dh), 1 / sqrt(dh)
+};
+// Heads of a multiple of four on 16-byte aligned tensors; dsum [B*T, heads].
+bool attention_rows_ok(const AttnShape &g, const void *a, const void *b, const void *c, const void *d);
+aqt_status launch_attention_rows(const float *qkv, const AttnShape &g, float *ctx, uint32_t *absmax, float *lse, hipStream_t st);
+aqt_status launch_attention_bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g,
+                                      float *dqkv, float *dsum, hipStream_t st);
 bool attention_shape_ok(int64_t B, int64_t T, int64_t D, int heads);
 aqt_status launch_attention(const float *qkv, int64_t B, int64_t T, int64_t D, int heads, int left, int right,
                             float *ctx, uint32_t *absmax, float *lse, hipStream_t st, bool absmax_is_zero = false);

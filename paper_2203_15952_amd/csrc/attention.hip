@@ -523,10 +523,17 @@ bool attention_shape_ok(int64_t B, int64_t T, int64_t D, int heads) {
   return cdiv(T, kQ) * heads <= (int64_t(1) << 31) / B - 1;
 }
 
+static AttnShape attn_shape(const AttnGeom &g) {
+  const int T = g.T < INT32_MAX ? static_cast<int>(g.T) : INT32_MAX;
+  return AttnShape{g.B, g.D, T, g.heads, g.dh, g.left < T ? g.left : T, g.right < T ? g.right : T, g.qtiles, g.scale_log2e, g.scale};
+}
+
 aqt_status launch_attention(const float *qkv, int64_t B, int64_t T, int64_t D, int heads, int left, int right,
                             float *ctx, uint32_t *absmax, float *lse, hipStream_t st, bool absmax_is_zero) {
   const AttnGeom g = attn_geom(B, T, D, heads, left, right);
   if (absmax && !absmax_is_zero) zero_attn_absmax_kernel<<<1, 64, 0, st>>>(absmax);
+  // heads whose rows are whole 16-byte pieces: attention_fwd.hip, attention_bwd.hip
+  if (attention_rows_ok(attn_shape(g), qkv, ctx, qkv, ctx)) return launch_attention_rows(qkv, attn_shape(g), ctx, absmax, lse, st);
   const int64_t blocks = static_cast<int64_t>(g.qtiles) * heads * B;
   attention_fwd_kernel<<<static_cast<unsigned>(blocks), kThreads, 0, st>>>(qkv, g, ctx, absmax, lse);
   AQT_HIP(hipGetLastError());
@@ -542,6 +549,8 @@ aqt_status launch_attention_bwd(const float *qkv, const float *ctx, const float 
                                 hipStream_t st) {
   const AttnGeom g = attn_geom(B, T, D, heads, left, right);
   float *dsum = static_cast<float *>(ws);
+  if (attention_rows_ok(attn_shape(g), qkv, ctx, dctx, dqkv))
+    return launch_attention_bwd_rows(qkv, ctx, dctx, lse, attn_shape(g), dqkv, dsum, st);
   int64_t rg = cdiv(B * T, 4);
   if (rg > 4096) rg = 4096;
   attention_rowdot_kernel<<<static_cast<unsigned>(rg), kThreads, 0, st>>>(dctx, ctx, g, dsum);

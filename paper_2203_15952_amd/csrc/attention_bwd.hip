@@ -1,0 +1,403 @@
+// Backward of the float attention core for heads of a multiple of four positions on 16-byte aligned tensors (the chain rule
+// and the two kernels of attention.hip) on the bf16 matrix cores, without giving up float32: every operand is carried whole
+// as three bf16 terms of 8 significant bits each (a = hi + mid + lo exactly), and a product is six
+// v_mfma_f32_32x32x16_bf16 passes, hi hi, hi mid, mid hi, mid mid, hi lo, lo hi; what is left out is below 2^-25 of a
+// product, under the rounding of the float32 sum itself (64-term dot products measured against float64: rms
+// error 1.8e-8 of the sum of magnitudes, 2.4e-8 with v_mfma_f32_32x32x2_f32).  Six bf16 passes take 6/16 of the float32
+// instruction's time, so the matrix work shrinks 2.7-fold; the splitting is vector work, done once per workgroup
+// for the staged rows, and runs under the products of the other wavefronts.
+//
+// As in attention.hip all products are formed transposed, a lane owns one query (in the key / value gradient kernel:
+// one key) from start to end, and the probabilities go from the first products' accumulators into the last products'
+// B operand without leaving the lane.  Tiles of 32 rows go through LDS row-major, one 128-byte row per image, 16-byte
+// chunks XOR-swizzled with the row.  Operands that contract along the head are read as 16-byte row pieces; operands
+// that contract along the rows are read from the same image with ds_read_b64_tr_b16 (sixteen lanes read four rows of
+// sixteen columns, each lane receives one column), whose four-row groups are exactly the rows an accumulator lane
+// holds.  Two LDS slots: a tile is staged and split while the one before it is multiplied, one barrier per tile.
+//
+// Measured in us, float32 instructions before -> here: 32 utterances of 400 frames, 8 heads of 64: 621 -> 283; 128 of
+// 512: 2808 -> 1370; 24 of 417, 4 heads of 36: 310 -> 126.  The matrix cores are 40 % busy; the rest is the vector work
+// of the splits and the exponentials.
+#include "attention_tiles.h"
+
+namespace aqt {
+namespace {
+
+constexpr int kStep = 32;            // rows per staged tile
+constexpr int kRowBytes = 128;       // an LDS row: 64 bf16
+constexpr int kImage = kStep * kRowBytes;
+constexpr int kTensor = 3 * kImage;  // hi, mid, lo
+constexpr int kSlot = 2 * kTensor;   // two tensors per tile
+constexpr int kLd = 68;              // row stride in floats of the output image
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+
+struct Split {   // one operand fragment: eight values of a lane as three bf16 terms
+  v4i hi, mid, lo;
+};
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even
+  v2f f = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
+}
+__device__ __forceinline__ void split2(float a, float b, int &hi, int &mid, int &lo) {
+  const uint32_t h = pack_bf16(a, b);
+  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
+  const uint32_t m = pack_bf16(ra, rb);
+  const float qa = ra - __uint_as_float(m << 16), qb = rb - __uint_as_float(m & 0xFFFF0000u);
+  hi = static_cast<int>(h); mid = static_cast<int>(m); lo = static_cast<int>(pack_bf16(qa, qb));
+}
+__device__ __forceinline__ Split split8(float a, float b, float c, float d, float e, float f, float g, float h) {
+  Split s;
+  int x, y, z;
+  split2(a, b, x, y, z); s.hi.x = x; s.mid.x = y; s.lo.x = z;
+  split2(c, d, x, y, z); s.hi.y = x; s.mid.y = y; s.lo.y = z;
+  split2(e, f, x, y, z); s.hi.z = x; s.mid.z = y; s.lo.z = z;
+  split2(g, h, x, y, z); s.hi.w = x; s.mid.w = y; s.lo.w = z;
+  return s;
+}
+
+__device__ __forceinline__ v16f mfma(v4i a, v4i b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ v16f mfma6(const Split &a, const Split &b, v16f c) {   // smallest terms first
+  c = mfma(a.lo, b.hi, c);
+  c = mfma(a.hi, b.lo, c);
+  c = mfma(a.mid, b.mid, c);
+  c = mfma(a.mid, b.hi, c);
+  c = mfma(a.hi, b.mid, c);
+  return mfma(a.hi, b.hi, c);
+}
+// Rows lr of an image set, head positions 16 s + 8 lk .. + 7: contraction along the head.
+__device__ __forceinline__ Split read_rows(const uint8_t *tensor, int s, int lr, int lk) {
+  const uint8_t *p = tensor + lr * kRowBytes + (((2 * s + lk) ^ (lr & 7)) << 4);
+  return Split{*reinterpret_cast<const v4i *>(p), *reinterpret_cast<const v4i *>(p + kImage),
+               *reinterpret_cast<const v4i *>(p + 2 * kImage)};
+}
+// Head columns 32 blk + lr, the eight rows 16 s + 8 (e / 4) + 4 lk + e % 4: contraction along the rows, in the order
+// in which elements 8 s .. 8 s + 7 of an accumulator lane hold them.
+__device__ __forceinline__ v4i read_tr8(const uint8_t *image, int at0, int at1) {
+  typedef __attribute__((address_space(3))) v4s *lds_v4s;
+  const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(image));
+  const v2i a = __builtin_bit_cast(v2i, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_v4s>(base + at0)));
+  const v2i b = __builtin_bit_cast(v2i, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_v4s>(base + at1)));
+  return v4i{a.x, a.y, b.x, b.y};
+}
+__device__ __forceinline__ Split read_cols(const uint8_t *tensor, int s, int blk, int lane) {
+  const int i = lane & 15, c = i & 3, chunk = 4 * blk + 2 * ((lane >> 4) & 1) + (c >> 1);
+  const int row0 = 16 * s + 4 * (lane >> 5) + (i >> 2), row1 = row0 + 8;   // the same row modulo 8
+  const int in_row = ((chunk ^ (row0 & 7)) << 4) + 8 * (c & 1);
+  const int at0 = row0 * kRowBytes + in_row, at1 = row1 * kRowBytes + in_row;
+  return Split{read_tr8(tensor, at0, at1), read_tr8(tensor + kImage, at0, at1), read_tr8(tensor + 2 * kImage, at0, at1)};
+}
+
+// A thread's share of a tile: eight head positions of one row (rows beyond the utterance are read from its last one).
+struct Raw {
+  v4f a, b;
+};
+__device__ __forceinline__ Raw load_piece(const float *__restrict__ src, int64_t ld, const AttnShape &g, int64_t b, int row0,
+                                          int64_t col0) {
+  const int piece = threadIdx.x & 7;
+  const int t = row0 + static_cast<int>(threadIdx.x >> 3), tc = t < g.T ? t : g.T - 1;
+  const float *p = src + (b * g.T + tc) * ld + col0;
+  const int d = 8 * piece, d0 = d < g.dh ? d : g.dh - 4, d1 = d + 4 < g.dh ? d + 4 : g.dh - 4;
+  return Raw{*reinterpret_cast<const v4f *>(p + d0), *reinterpret_cast<const v4f *>(p + d1)};
+}
+// ... split into the three images; zeros beyond the head and, where `rows` says so, beyond the utterance
+template <int PIECES>
+__device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnShape &g, int row0, bool rows) {
+  const int piece = threadIdx.x & 7, row = static_cast<int>(threadIdx.x >> 3);
+  const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (8 * piece >= g.dh || (rows && row0 + row >= g.T)) v.a = zero;
+  if (8 * piece + 4 >= g.dh || (rows && row0 + row >= g.T)) v.b = zero;
+  if (PIECES == 8 || piece < PIECES) {
+    const Split s = split8(v.a.x, v.a.y, v.a.z, v.a.w, v.b.x, v.b.y, v.b.z, v.b.w);
+    uint8_t *p = tensor + row * kRowBytes + ((piece ^ (row & 7)) << 4);
+    *reinterpret_cast<v4i *>(p) = s.hi;
+    *reinterpret_cast<v4i *>(p + kImage) = s.mid;
+    *reinterpret_cast<v4i *>(p + 2 * kImage) = s.lo;
+  }
+}
+
+// A lane's own row as a B operand, straight from memory: positions 16 s + 8 lk .. + 7, times `mul`.
+__device__ __forceinline__ void load_own(v4f &x, v4f &y, const float *row, int s, int lk, int dh) {
+  const int d = 16 * s + 8 * lk;
+  const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  x = d < dh ? *reinterpret_cast<const v4f *>(row + d) : zero;
+  y = d + 4 < dh ? *reinterpret_cast<const v4f *>(row + d + 4) : zero;
+}
+__device__ __forceinline__ Split split_own(v4f x, v4f y, float mul) {
+  return split8(x.x * mul, x.y * mul, x.z * mul, x.w * mul, y.x * mul, y.y * mul, y.z * mul, y.w * mul);
+}
+__device__ __forceinline__ float dot8(v4f a, v4f b, v4f c, v4f d) {
+  return ((a.x * c.x + a.y * c.y) + (a.z * c.z + a.w * c.w)) + ((b.x * d.x + b.y * d.y) + (b.z * d.z + b.w * d.w));
+}
+
+// a wavefront's transposed result (head positions x 32 rows) out through its own part of LDS as whole rows
+template <int DB>
+__device__ __forceinline__ uint32_t store_rows(float *img, const v16f (&acc)[DB], float mul, float *__restrict__ out, int64_t ld,
+                                               int rows_left, int dh, int lane) {
+  const int lr = lane & 31, lk = lane >> 5;
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const v4f v = {acc[blk][4 * r4] * mul, acc[blk][4 * r4 + 1] * mul, acc[blk][4 * r4 + 2] * mul, acc[blk][4 * r4 + 3] * mul};
+      *reinterpret_cast<v4f *>(img + lr * kLd + 32 * blk + 8 * r4 + 4 * lk) = v;
+    }
+  __builtin_amdgcn_wave_barrier();
+  // sixteen lanes per row, four rows at a time
+  uint32_t amax = 0u;
+  const int d = 4 * (lane & 15);
+#pragma unroll
+  for (int q4 = 0; q4 < 8; ++q4) {
+    const int q = 4 * q4 + (lane >> 4);
+    if (q < rows_left && d < dh) {
+      const v4f v = *reinterpret_cast<const v4f *>(img + q * kLd + d);
+      *reinterpret_cast<v4f *>(out + q * ld + d) = v;
+      amax = max(max(amax, __float_as_uint(v.x) & 0x7FFFFFFFu), max(__float_as_uint(v.y) & 0x7FFFFFFFu,
+                 max(__float_as_uint(v.z) & 0x7FFFFFFFu, __float_as_uint(v.w) & 0x7FFFFFFFu)));
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  return amax;
+}
+
+// The tile loop: rows first, first + 32, ... <= last, two tensors per tile; compute(slot, row0) between.
+template <class Load, class Stage, class Compute>
+__device__ __forceinline__ void run_tiles(uint8_t *lds, int first, int last, Load load, Stage stage, Compute compute) {
+  uint8_t *cur = lds, *nxt = lds + kSlot;
+  load(first);
+  stage(cur, first);
+  load(first + kStep);   // rows beyond the utterance are clamped: no branch around a load
+  __syncthreads();
+  for (int r0 = first; r0 <= last; r0 += kStep) {
+    if (r0 + kStep <= last) stage(nxt, r0 + kStep);
+    load(r0 + 2 * kStep);
+    compute(cur, r0);
+    __syncthreads();
+    uint8_t *const t = cur; cur = nxt; nxt = t;
+  }
+}
+
+// ---- backward: the chain rule and the two kernels of attention.hip ---------------------------------
+// dq: a lane owns a query.  Also forms D_t = dO_t . O_t of its queries (the lane reads dO_t anyway) and leaves it in
+// dsum for the dk / dv kernel.
+template <int KS>
+__global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(const float *__restrict__ qkv,
+                                                                             const float *__restrict__ ctx,
+                                                                             const float *__restrict__ dctx,
+                                                                             const float *__restrict__ lse,
+                                                                             float *__restrict__ dsum, AttnShape g,
+                                                                             float *__restrict__ dqkv) {
+  constexpr int DB = (KS + 1) / 2;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSlot];
+  const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Place pl = place_of(g);
+  const int64_t b = pl.b, hc = pl.hc;
+  const int t0 = pl.r0;
+  const int tw = t0 + wave * 32, t = tw + lr, tc = t < g.T ? t : g.T - 1;
+  const bool active = tw < g.T;
+  Split q[KS], go[KS];
+  float D = 0.0f;
+  {
+    const float *row = qkv + (b * g.T + tc) * 3 * g.D + hc, *grow = dctx + (b * g.T + tc) * g.D + hc, *orow = ctx + (b * g.T + tc) * g.D + hc;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      v4f x, y, gx, gy, ox, oy;
+      load_own(x, y, row, s, lk, g.dh);
+      load_own(gx, gy, grow, s, lk, g.dh);
+      load_own(ox, oy, orow, s, lk, g.dh);
+      q[s] = split_own(x, y, g.scale_log2e);
+      go[s] = split_own(gx, gy, 1.0f);
+      D += dot8(gx, gy, ox, oy);
+    }
+  }
+  D += __shfl_xor(D, 32, 64);
+  const float L = lse[(b * g.T + tc) * g.heads + pl.h];
+  if (lk == 0 && t < g.T) dsum[(b * g.T + t) * g.heads + pl.h] = D;
+  const int tlast = t0 + kQ - 1 < g.T ? t0 + kQ - 1 : g.T - 1;
+  const int jmin = (g.left < 0 || t0 - g.left < 0) ? 0 : t0 - g.left;
+  const int jmax = (g.right < 0 || tlast + g.right > g.T - 1) ? g.T - 1 : tlast + g.right;
+  const int wlo = g.left < 0 ? 0 : t - g.left;
+  const int whi = (g.right < 0 || t + g.right > g.T - 1) ? g.T - 1 : t + g.right;
+  const int some_lo = g.left < 0 ? 0 : tw - g.left, all_lo = g.left < 0 ? 0 : tw + 31 - g.left;
+  const int some_hi = (g.right < 0 || tw + 31 + g.right > g.T - 1) ? g.T - 1 : tw + 31 + g.right;
+  const int all_hi = (g.right < 0 || tw + g.right > g.T - 1) ? g.T - 1 : tw + g.right;
+  v16f dq[DB];
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk) dq[blk] = zero16();
+  Raw kr, vr;
+  auto load = [&](int j0) {
+    kr = load_piece(qkv, 3 * g.D, g, b, j0, g.D + hc);
+    vr = load_piece(qkv, 3 * g.D, g, b, j0, 2 * g.D + hc);
+  };
+  auto stage = [&](uint8_t *slot, int j0) {
+    stage_piece<4 * DB>(slot, kr, g, j0, true);
+    stage_piece<2 * KS>(slot + kTensor, vr, g, j0, false);
+  };
+  auto compute = [&](const uint8_t *slot, int j0) {
+    if (!active || j0 > some_hi || j0 + kStep - 1 < some_lo) return;
+    v16f s = zero16(), dp = zero16();
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      s = mfma6(read_rows(slot, k, lr, lk), q[k], s);              // S^T: keys x this lane's query
+      dp = mfma6(read_rows(slot + kTensor, k, lr, lk), go[k], dp);   // dP^T
+    }
+    const bool whole = j0 >= all_lo && j0 + kStep - 1 <= all_hi;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + 8 * (r >> 2) + 4 * lk + (r & 3);
+      const float p = __builtin_amdgcn_exp2f(s[r] - L);
+      s[r] = (whole || (j >= wlo && j <= whi)) ? p * (dp[r] - D) : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const Split d = split8(s[8 * k], s[8 * k + 1], s[8 * k + 2], s[8 * k + 3], s[8 * k + 4], s[8 * k + 5], s[8 * k + 6], s[8 * k + 7]);
+#pragma unroll
+      for (int blk = 0; blk < DB; ++blk) dq[blk] = mfma6(read_cols(slot, k, blk, lane), d, dq[blk]);   // dQ^T += K^T dS^T
+    }
+  };
+  run_tiles(lds, jmin / kStep * kStep, jmax, load, stage, compute);
+  if (active)
+    store_rows<DB>(reinterpret_cast<float *>(lds) + wave * 32 * kLd, dq, g.scale, dqkv + (b * g.T + tw) * 3 * g.D + hc, 3 * g.D,
+                   g.T - tw, g.dh, lane);
+}
+
+// dk / dv: a lane owns a key, the tiles are queries and upstream gradient rows.
+template <int KS>
+__global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(const float *__restrict__ qkv,
+                                                                              const float *__restrict__ dctx,
+                                                                              const float *__restrict__ lse,
+                                                                              const float *__restrict__ dsum, AttnShape g,
+                                                                              float *__restrict__ dqkv) {
+  constexpr int DB = (KS + 1) / 2;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSlot];
+  __shared__ float Ls[2][kStep], Ds[2][kStep];
+  const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Place pl = place_of(g);
+  const int64_t b = pl.b, hc = pl.hc;
+  const int j0t = pl.r0;
+  const int jw = j0t + wave * 32, j = jw + lr, jc = j < g.T ? j : g.T - 1;
+  const bool active = jw < g.T;
+  Split kk[KS], vv[KS];
+  {
+    const float *row = qkv + (b * g.T + jc) * 3 * g.D + g.D + hc;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      v4f x, y;
+      load_own(x, y, row, s, lk, g.dh);
+      kk[s] = split_own(x, y, g.scale_log2e);
+      load_own(x, y, row + g.D, s, lk, g.dh);
+      vv[s] = split_own(x, y, 1.0f);
+    }
+  }
+  // query frames that may look at a key of this workgroup / of this wavefront: t - left <= j <= t + right
+  const int jlast = j0t + kQ - 1 < g.T ? j0t + kQ - 1 : g.T - 1;
+  const int tmin = (g.right < 0 || j0t - g.right < 0) ? 0 : j0t - g.right;
+  const int tmax = (g.left < 0 || jlast + g.left > g.T - 1) ? g.T - 1 : jlast + g.left;
+  const int qlo = g.right < 0 ? 0 : j - g.right;
+  const int qhi = (g.left < 0 || j + g.left > g.T - 1) ? g.T - 1 : j + g.left;
+  const int some_lo = g.right < 0 ? 0 : jw - g.right, all_lo = g.right < 0 ? 0 : jw + 31 - g.right;
+  const int some_hi = (g.left < 0 || jw + 31 + g.left > g.T - 1) ? g.T - 1 : jw + 31 + g.left;
+  const int all_hi = (g.left < 0 || jw + g.left > g.T - 1) ? g.T - 1 : jw + g.left;
+  v16f dk[DB], dv[DB];
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk) {
+    dk[blk] = zero16();
+    dv[blk] = zero16();
+  }
+  Raw qr, gr;
+  float Lr, Dr;
+  const int row = static_cast<int>(threadIdx.x & 31);
+  auto load = [&](int t0) {
+    qr = load_piece(qkv, 3 * g.D, g, b, t0, hc);
+    gr = load_piece(dctx, g.D, g, b, t0, hc);
+    const int tt = t0 + row < g.T ? t0 + row : g.T - 1;
+    Lr = lse[(b * g.T + tt) * g.heads + pl.h];
+    Dr = dsum[(b * g.T + tt) * g.heads + pl.h];
+  };
+  auto stage = [&](uint8_t *slot, int t0) {
+    stage_piece<4 * DB>(slot, qr, g, t0, true);
+    stage_piece<4 * DB>(slot + kTensor, gr, g, t0, true);
+    if (threadIdx.x < kStep) {
+      const int at = slot == lds ? 0 : 1;
+      Ls[at][row] = Lr;
+      Ds[at][row] = Dr;
+    }
+  };
+  auto compute = [&](const uint8_t *slot, int t0) {
+    if (!active || t0 > some_hi || t0 + kStep - 1 < some_lo) return;
+    const int at = slot == lds ? 0 : 1;
+    v16f s = zero16(), dp = zero16();
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      s = mfma6(read_rows(slot, k, lr, lk), kk[k], s);              // S: queries x this lane's key
+      dp = mfma6(read_rows(slot + kTensor, k, lr, lk), vv[k], dp);   // dP
+    }
+    const bool whole = t0 >= all_lo && t0 + kStep - 1 <= all_hi && jw + 31 < g.T;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const v4f L4 = *reinterpret_cast<const v4f *>(&Ls[at][8 * r4 + 4 * lk]), D4 = *reinterpret_cast<const v4f *>(&Ds[at][8 * r4 + 4 * lk]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * r4 + e;
+        const int tt = t0 + 8 * r4 + 4 * lk + e;
+        const float x = __builtin_amdgcn_exp2f(s[r] - L4[e]);
+        const float p = (whole || (j < g.T && tt >= qlo && tt <= qhi)) ? x : 0.0f;
+        s[r] = p;
+        dp[r] = p * (dp[r] - D4[e]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const Split p = split8(s[8 * k], s[8 * k + 1], s[8 * k + 2], s[8 * k + 3], s[8 * k + 4], s[8 * k + 5], s[8 * k + 6], s[8 * k + 7]);
+#pragma unroll
+      for (int blk = 0; blk < DB; ++blk) dv[blk] = mfma6(read_cols(slot + kTensor, k, blk, lane), p, dv[blk]);   // dV^T += dO^T P
+      const Split d = split8(dp[8 * k], dp[8 * k + 1], dp[8 * k + 2], dp[8 * k + 3], dp[8 * k + 4], dp[8 * k + 5], dp[8 * k + 6], dp[8 * k + 7]);
+#pragma unroll
+      for (int blk = 0; blk < DB; ++blk) dk[blk] = mfma6(read_cols(slot, k, blk, lane), d, dk[blk]);             // dK^T += Q^T dS
+    }
+  };
+  run_tiles(lds, tmin / kStep * kStep, tmax, load, stage, compute);
+  if (active) {
+    float *const img = reinterpret_cast<float *>(lds) + wave * 32 * kLd;
+    float *const out = dqkv + (b * g.T + jw) * 3 * g.D + g.D + hc;
+    store_rows<DB>(img, dk, g.scale, out, 3 * g.D, g.T - jw, g.dh, lane);
+    store_rows<DB>(img, dv, 1.0f, out + g.D, 3 * g.D, g.T - jw, g.dh, lane);
+  }
+}
+
+}  // namespace
+
+bool attention_rows_ok(const AttnShape &g, const void *a, const void *b, const void *c, const void *d) {
+  auto aligned = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+  return g.T <= 1 << 30 && g.dh % 4 == 0 && g.D % 4 == 0 && aligned(a) && aligned(b) && aligned(c) && aligned(d);
+}
+
+aqt_status launch_attention_bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g,
+                                      float *dqkv, float *dsum, hipStream_t st) {
+  const unsigned blocks = static_cast<unsigned>(static_cast<int64_t>(g.qtiles) * g.heads * g.B);
+  auto dq = g.dh <= 16   ? attention_bwd_dq_rows_kernel<1>
+            : g.dh <= 32 ? attention_bwd_dq_rows_kernel<2>
+            : g.dh <= 48 ? attention_bwd_dq_rows_kernel<3>
+                         : attention_bwd_dq_rows_kernel<4>;
+  dq<<<blocks, kThreads, 0, st>>>(qkv, ctx, dctx, lse, dsum, g, dqkv);
+  AQT_HIP(hipGetLastError());
+  auto dkv = g.dh <= 16   ? attention_bwd_dkv_rows_kernel<1>
+             : g.dh <= 32 ? attention_bwd_dkv_rows_kernel<2>
+             : g.dh <= 48 ? attention_bwd_dkv_rows_kernel<3>
+                          : attention_bwd_dkv_rows_kernel<4>;
+  dkv<<<blocks, kThreads, 0, st>>>(qkv, dctx, lse, dsum, g, dqkv);
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
+}  // namespace aqt

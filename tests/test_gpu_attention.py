@@ -226,3 +226,28 @@ def test_mhsa_backward_stage_by_stage(B_, T, D, heads, left, right, policy):
     check_grad(host(o["dxn"]), g1["dx"], g1["dx_abs"], "dxn")
     check_grad(host(o["dwqkv"]), g1["dw"], g1["dw_abs"], "dwqkv")
     check_grad(host(o["dbqkv"]), g1["dbias"], np.abs(dqkv_h.astype(np.float64)).sum(0), "dbqkv")
+
+
+@pytest.mark.parametrize("T", [1, 31, 33, 128, 161])
+@pytest.mark.parametrize("dh,left,right", [(4, -1, -1), (16, 33, 0), (20, -1, 31), (32, 0, 64), (44, 32, 32), (52, -1, -1), (64, 95, 1)])
+def test_attention_tile_edges(T, dh, left, right):
+    """Every step count of the kernels for vectorised rows (head widths up to 16, 32, 48 and 64, with and without a partial
+    step) against tile remainders of the frames and window ends on and next to tile ends."""
+    from parity_util import check_grad
+    B_, heads = 2, 3
+    D, M = heads * dh, B_ * T
+    say("attention edges", T, dh, left, right)
+    rng = np.random.default_rng(660 + 100 * T + dh)
+    qkv, dctx = rng.standard_normal((M, 3 * D)).astype(F), rng.standard_normal((M, D)).astype(F)
+    qkv_d, dctx_d = dev(qkv), dev(dctx)
+    lse = torch.empty((M, heads), dtype=torch.float32, device="cuda")
+    ctx, _ = B.aqt_attention_fwd(qkv_d, B_, T, heads, left=left, right=right, lse=lse)
+    check_attention(host(ctx), qkv, B_, T, D, heads, left, right)
+    got = host(B.aqt_attention_bwd(qkv_d, ctx, dctx_d, lse, B_, T, heads, left=left, right=right)).reshape(B_, T, 3 * D)
+    ref, mag = oracle.attention_bwd(qkv.reshape(B_, T, 3 * D), dctx.reshape(B_, T, D), heads, left, right)
+    check_grad(got, ref, mag, "dqkv")
+    # a tensor that is not 16-byte aligned takes the kernels for any layout
+    odd = torch.empty(qkv.size + 1, device="cuda")[1:].view(M, 3 * D)
+    odd.copy_(qkv_d)
+    ctx_odd, _ = B.aqt_attention_fwd(odd, B_, T, heads, left=left, right=right)
+    np.testing.assert_array_equal(host(ctx_odd), host(ctx))   # the forwards share every product and sum
