@@ -118,10 +118,11 @@ aqt_status launch_dense_fwd_wonly_any(const float *x, const void *wq_packed, con
                                       int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st);
 aqt_status launch_bwd_dx_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
                              const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st);
-int dw_any_slabs(int64_t M, int64_t K, int64_t N);   // slabs of rows it would like: K x N floats each in `partial`
+int dw_any_slabs(int64_t M, int64_t K, int64_t N);   // slabs of rows it would like: K x N floats each in `partial`,
+                                                     // cdiv(K, 128) x N doubles each in `bias_part` (dbias not null)
 aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
-                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, int max_slabs,
-                             hipStream_t st);
+                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, int max_slabs, float *dbias,
+                             double *bias_part, hipStream_t st);
 
 // ---- straight-through backward (gemm_bwd.hip) -------------------------------------
 size_t bwd_workspace_bytes(int64_t M, int64_t K, int64_t N);

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "aqt_internal.h"
+#include "colsum.h"
 #include "epilogue.h"
 
 #ifdef AQT_TIMELINE
@@ -62,7 +63,7 @@ __device__ __forceinline__ v16f mfma_bf16(v4i a, v4i b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
-// Column sums of dy in two stages: (64 columns x row slab) partials, then a fold.
+// Column sums of dy without a dW to ride on: (64 columns x row slab) partials, then a fold.
 constexpr int kBiasSlabs = 64;
 
 __global__ __launch_bounds__(kThreads) void bwd_dbias_partial_kernel(const float *__restrict__ dy, int64_t M,
@@ -81,13 +82,9 @@ __global__ __launch_bounds__(kThreads) void bwd_dbias_partial_kernel(const float
   if (ty == 0 && n < N) part[static_cast<int64_t>(blockIdx.y) * N + n] = (sm[0][tx] + sm[1][tx]) + (sm[2][tx] + sm[3][tx]);
 }
 
-__global__ __launch_bounds__(kThreads) void bwd_dbias_fold_kernel(const double *__restrict__ part, int64_t N,
-                                                                  float *__restrict__ dbias) {
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (n >= N) return;
-  double s = 0.0;
-  for (int j = 0; j < kBiasSlabs; ++j) s += part[static_cast<int64_t>(j) * N + n];
-  dbias[n] = static_cast<float>(s);
+__global__ __launch_bounds__(kColsumThreads) void bwd_dbias_fold_kernel(const double *__restrict__ part, int64_t N,
+                                                                        float *__restrict__ dbias) {
+  fold_column_sums(part, kBiasSlabs, N, blockIdx.x, dbias);
 }
 
 // int8 codes [K,N] -> bf16 (exact) in MFMA-fragment order, the dX kernel's second
@@ -521,10 +518,16 @@ __global__ __launch_bounds__(128 * WN, WN == 2 ? 2 : 1) void dense_fwd_wonly_mfm
 // and the younger finishes its slab alone at about half the matrix pipe's rate (measured: 318 k
 // against 407 k cycles for the two slabs of a pair).  Eight wavefronts behind one barrier
 // cannot drift apart, so the wide form is used whenever the channel count allows it.
-template <int TR, int TC, bool RAGGED, int WNW>  // tile is (64*TR) k-rows x (32*TC*WNW) n-columns; 32 m per stage
+//
+// BIAS: the bias gradient's column sums ride along.  A thread adds its four rows of a column in float64 as it splits
+// them, into an LDS word of its own (no registers are left).  The row tiles of a column stage the same rows, so they
+// take turns: row tile br adds up the stages s with s % tiles_r == br and leaves one partial row of its columns.
+// 65536 x 512 <-> 2048 and its neighbours in an encoder layer: 163 us (N = 2048) and 70 us (N = 512) for a pass of its
+// own over dy, nothing measurable here (eight dW launches 1526 us without, 1517 with).
+template <int TR, int TC, bool RAGGED, int WNW, bool BIAS>  // tile is (64*TR) k-rows x (32*TC*WNW) n-columns; 32 m per stage
 __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kernel(
     const int8_t *__restrict__ xq, const float *__restrict__ dy, int M, int K, int N, int m_per_slab,
-    float *__restrict__ partial, int tiles_r, int tiles_c) {
+    float *__restrict__ partial, double *__restrict__ bias_part, int tiles_r, int tiles_c) {
   constexpr int NT = 128 * WNW;               // threads
   constexpr int BR = 64 * TR, BC = 32 * TC * WNW;
   constexpr int SM = 32;
@@ -536,6 +539,7 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
   // memory stages the output tile.
   constexpr int kCBytes = BR * kRowB, kDBytes = 2 * BC * kRowB;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * (kCBytes + kDBytes)];
+  __shared__ double colsum[BIAS ? 4 * NT : 1];   // [column of the thread's four][thread]
   uint8_t *const sC0 = smem, *const sC1 = smem + kCBytes;
   uint8_t *const sD0 = smem + 2 * kCBytes, *const sD1 = smem + 2 * kCBytes + kDBytes;
   static_assert(2 * (kCBytes + kDBytes) >= 64 * BC * 4, "the output staging image must fit");
@@ -629,6 +633,16 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
     *reinterpret_cast<v2i *>(sD + offd0 + b * GB * kRowB) = hi;
     *reinterpret_cast<v2i *>(sD + BC * kRowB + offd0 + b * GB * kRowB) = lo;
   };
+  // component b of the four rows staged from row mrel0 on, added up
+  auto row_sum = [&](int set, int b, int mrel0) {
+    double y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float v = b == 0 ? ry[set][i].x : (b == 1 ? ry[set][i].y : (b == 2 ? ry[set][i].z : ry[set][i].w));
+      y[i] = static_cast<double>(RAGGED && mrel0 + ms * 4 + i > m_last ? 0.0f : v);
+    }
+    return (y[0] + y[1]) + (y[2] + y[3]);
+  };
 
   v16f acc[TR][TC];
 #pragma unroll
@@ -667,7 +681,12 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
   // ---- prologue ----
   load_global(0, stage_m(0));
 #pragma unroll
-  for (int b = 0; b < 4; ++b) { store_codes(0, b, sC0); store_dy(0, b, sD0); }
+  for (int b = 0; b < 4; ++b) {
+    store_codes(0, b, sC0);
+    store_dy(0, b, sD0);
+    if (BIAS) colsum[b * NT + t] = br == 0 ? row_sum(0, b, 0) : 0.0;
+  }
+  int turn = br == 0 ? tiles_r : br;   // BIAS: the next stage whose rows this workgroup adds up
   load_global(1, stage_m(1));
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
   __builtin_amdgcn_s_barrier();
@@ -697,6 +716,8 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
       else store_dy(PAR ^ 1, p - 4, nxtD);
       AQT_SCHED_FENCE();
     }
+    const bool add = BIAS && s + 1 == turn && s + 1 < stages;   // the stage past the last one is the last one again
+    if (add) turn += tiles_r;
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));   // own LDS traffic drained
     __builtin_amdgcn_s_barrier();
     // ---- second half: step 1 ----
@@ -707,6 +728,9 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
       AQT_SCHED_FENCE();
       if (p < 2 * TC) read_b(nxtD, 0, 0, p);                       // next stage, step 0
       if ((2 * p + 2) % (2 * TC) == 0) read_a(nxtC, 0, (2 * p + 1) / (2 * TC));
+      if (BIAS && p >= 4 && add)   // the rows just staged are still in registers
+        __hip_atomic_fetch_add(&colsum[(p - 4) * NT + t], row_sum(PAR ^ 1, p - 4, stage_m(s + 1)), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
       AQT_SCHED_FENCE();
     }
   };
@@ -719,6 +743,17 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
   }
   if (s < stages) stage(std::integral_constant<int, 0>{}, s);
   AQT_TL(2);
+
+  if (BIAS) {   // the eight row groups of a column, in order
+    __syncthreads();
+    if (t < BC) {
+      const double *const p = colsum + (t & 3) * NT + (t >> 2);
+      double sum = p[0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) sum += p[i * GB];
+      bias_part[(static_cast<int64_t>(slab) * tiles_r + br) * N + c0 + t] = sum;
+    }
+  }
 
   // ---- epilogue: partial tile -> workspace.
   // Written lane by lane the tile would reach HBM as 4-byte pieces at a 16-byte stride (the
@@ -768,13 +803,24 @@ __global__ __launch_bounds__(128 * WNW, WNW == 2 ? 2 : 1) void bwd_dw_mfma_kerne
 #endif
 }
 
+// The bias gradient's partial rows, where a launch folds them beside the slabs (its first `blocks` workgroups).
+struct BiasFold {
+  const double *part;
+  float *dbias;
+  int rows, blocks;
+};
+
 // Fold the slabs in order, scale by s_x, apply the mask.
 __global__ __launch_bounds__(kThreads) void bwd_dw_fold_kernel(const float *__restrict__ partial, int slabs,
                                                                int64_t KN, int64_t N, const float *__restrict__ s_x,
                                                                const float *__restrict__ s_w,
                                                                const uint32_t *__restrict__ mask_w,
-                                                               float *__restrict__ dw) {
-  const int64_t i4 = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+                                                               float *__restrict__ dw, BiasFold bias) {
+  if (static_cast<int>(blockIdx.x) < bias.blocks) {
+    fold_column_sums(bias.part, bias.rows, N, blockIdx.x, bias.dbias);
+    return;
+  }
+  const int64_t i4 = (static_cast<int64_t>(blockIdx.x) - bias.blocks) * kThreads + threadIdx.x;
   const int64_t i = i4 * 4;
   if (i >= KN) return;
   float4 s = *reinterpret_cast<const float4 *>(partial + i);
@@ -829,10 +875,13 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   p.slabs = static_cast<int>(slabs);
   p.m_per_slab = static_cast<int>(per);
   if (!p.dw_mfma) p.slabs = dw_any_slabs(M, K, N);
+  // one row of column sums per slab and row tile (of at least 128 positions), or per row slab without a dW
+  size_t bias_rows = static_cast<size_t>(p.slabs) * cdiv(K, 128);
+  if (bias_rows < kBiasSlabs) bias_rows = kBiasSlabs;
   size_t off = 0;
   p.off_bf = off;   off += align_up(static_cast<size_t>(K) * N * 2, 256);
   p.off_part = off; off += align_up(static_cast<size_t>(p.slabs) * K * N * 4, 256);
-  p.off_bias = off; off += align_up(static_cast<size_t>(kBiasSlabs) * N * sizeof(double), 256);
+  p.off_bias = off; off += align_up(bias_rows * N * sizeof(double), 256);
   p.total = off;
   return p;
 }
@@ -858,13 +907,14 @@ aqt_status launch_dx(const float *dy, const v4i *wq_frag, const aqt_saved *sv, i
 
 template <int TR, int TC, int WNW>
 aqt_status launch_dw(const float *dy, const aqt_saved *sv, int64_t M, int64_t K, int64_t N, const BwdPlan &p,
-                     float *partial, hipStream_t st) {
+                     float *partial, double *bias_part, hipStream_t st) {
   constexpr int BR = 64 * TR, BC = 32 * TC * WNW;
-  auto kern = (M % 32 == 0) ? bwd_dw_mfma_kernel<TR, TC, false, WNW> : bwd_dw_mfma_kernel<TR, TC, true, WNW>;
+  auto kern = bias_part ? ((M % 32 == 0) ? bwd_dw_mfma_kernel<TR, TC, false, WNW, true> : bwd_dw_mfma_kernel<TR, TC, true, WNW, true>)
+                        : ((M % 32 == 0) ? bwd_dw_mfma_kernel<TR, TC, false, WNW, false> : bwd_dw_mfma_kernel<TR, TC, true, WNW, false>);
   const int tiles_r = static_cast<int>(K / BR), tiles_c = static_cast<int>(N / BC);
   kern<<<tiles_r * tiles_c * p.slabs, 128 * WNW, 0, st>>>(sv->xq, dy, static_cast<int>(M), static_cast<int>(K),
-                                                         static_cast<int>(N), p.m_per_slab, partial, tiles_r,
-                                                         tiles_c);
+                                                         static_cast<int>(N), p.m_per_slab, partial, bias_part,
+                                                         tiles_r, tiles_c);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }
@@ -945,26 +995,28 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
       AQT_TRY(launch_bwd_dx_any(dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, dx_factor, M, K, N, dx, st));
     }
   }
-  if (dw) {
+  double *bias_part = reinterpret_cast<double *>(base + p.off_bias);
+  if (dw) {   // with the bias gradient, where it is wanted as well
     if (p.dw_mfma && dy_aligned && reinterpret_cast<uintptr_t>(sv->xq) % 4 == 0 &&
         reinterpret_cast<uintptr_t>(dw) % 16 == 0) {
       float *partial = reinterpret_cast<float *>(base + p.off_part);
-      if (p.dw_wide8) AQT_TRY((launch_dw<4, 2, 4>(dy, sv, M, K, N, p, partial, st)));
-      else AQT_TRY((launch_dw<4, 2, 2>(dy, sv, M, K, N, p, partial, st)));
-      bwd_dw_fold_kernel<<<static_cast<int>(cdiv(K * N / 4, kThreads)), kThreads, 0, st>>>(
-          partial, p.slabs, K * N, N, sv->s_x, sv->s_w, sv->mask_w, dw);
+      if (p.dw_wide8) AQT_TRY((launch_dw<4, 2, 4>(dy, sv, M, K, N, p, partial, dbias ? bias_part : nullptr, st)));
+      else AQT_TRY((launch_dw<4, 2, 2>(dy, sv, M, K, N, p, partial, dbias ? bias_part : nullptr, st)));
+      const BiasFold fold{bias_part, dbias, static_cast<int>(p.slabs * (K / 256)),
+                          dbias ? static_cast<int>(cdiv(N, kColsumCols)) : 0};
+      bwd_dw_fold_kernel<<<static_cast<int>(cdiv(K * N / 4, kThreads)) + fold.blocks, kThreads, 0, st>>>(
+          partial, p.slabs, K * N, N, sv->s_x, sv->s_w, sv->mask_w, dw, fold);
       AQT_HIP(hipGetLastError());
     } else {
       AQT_TRY(launch_bwd_dw_any(dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw,
-                                reinterpret_cast<float *>(base + p.off_part), p.slabs, st));
+                                reinterpret_cast<float *>(base + p.off_part), p.slabs, dbias, bias_part, st));
     }
   }
-  if (dbias) {
-    double *part = reinterpret_cast<double *>(base + p.off_bias);
+  if (dbias && !dw) {
     dim3 grid(static_cast<unsigned>(cdiv(N, 64)), kBiasSlabs);
-    bwd_dbias_partial_kernel<<<grid, kThreads, 0, st>>>(dy, M, N, part);
+    bwd_dbias_partial_kernel<<<grid, kThreads, 0, st>>>(dy, M, N, bias_part);
     AQT_HIP(hipGetLastError());
-    bwd_dbias_fold_kernel<<<static_cast<int>(cdiv(N, kThreads)), kThreads, 0, st>>>(part, N, dbias);
+    bwd_dbias_fold_kernel<<<static_cast<int>(cdiv(N, kColsumCols)), kColsumThreads, 0, st>>>(bias_part, N, dbias);
     AQT_HIP(hipGetLastError());
   }
   return AQT_OK;

@@ -74,3 +74,30 @@ def test_weight_only_forward(M, K, N, bw, epi):
     wq, s_w, _, _ = B.aqt_quantize_weights(dev(c.w), bw)
     y = B.aqt_dense_fwd_wonly(dev(c.x), wq, s_w, N, bw, bias=dev(c.bias), epilogue=epi)
     check_float_forward(host(y), ora, epi)
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (15301, 512, 512),     # 256 x 256 dW tiles, the last stage of rows in part
+    (61100, 512, 128),     # 256 x 128 tiles; most row tiles' slabs end with a turn that is not theirs
+    (30528, 256, 512),     # whole stages, one row tile
+    (4096, 2048, 512),     # more row tiles than stages in a slab would share evenly
+    (1000, 520, 130),      # any-shape dW: partial tiles on every side
+    (33, 129, 3),          # one slab of two slices, two row tiles, fewer than four columns
+    (1, 1, 1), (64, 128, 128),
+])
+def test_bias_gradient_rides_on_dw(M, K, N):
+    """The column sums taken inside the dW kernels are float64 sums rounded once: half a float32 ulp, plus the float64
+    sums' own M * 2^-53 of the magnitudes.  Without dW they come from their own kernels."""
+    import torch
+    print("[bias gradient]", M, K, N, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + K + N)
+    x = torch.randn((M, K), device="cuda", generator=gen)
+    w = torch.randn((K, N), device="cuda", generator=gen)
+    dy = torch.randn((M, N), device="cuda", generator=gen) + 0.3
+    sv = B.Saved(M, K, N, 8)
+    B.aqt_dense_fwd(x, w, 8, 8, saved=sv)
+    ref = dy.double().sum(0)
+    bound = 2.0 ** -24 * ref.abs() * 1.0001 + M * 2.0 ** -53 * dy.double().abs().sum(0)
+    for want_dw in (True, False):
+        _, _, db = B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, want_dw=want_dw, want_dbias=True)
+        assert bool(((db.double() - ref).abs() <= bound).all()), (want_dw, float(((db.double() - ref).abs() - bound).max()))
