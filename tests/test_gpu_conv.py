@@ -158,6 +158,38 @@ def rows_of(M):
     return np.unique(np.r_[0:min(128, M), mid:min(mid + 128, M), max(0, M - 256):M])
 
 
+@pytest.mark.parametrize("C,kw,T", [(4, 8, 9), (36, 9, 64), (100, 24, 65), (68, 25, 130), (64, 32, 16), (128, 7, 200)])
+def test_depthwise_conv_read_in_pieces_or_one_by_one_same_bits(C, kw, T):
+    """Channels in fours on 16-byte aligned tensors are read 16 bytes at a time, anything else one by one; the
+    arithmetic is the same, so a tensor moved by four bytes gives the same bits.  The aligned result is held to the
+    bound of the forward test, the gradients to the usual bar."""
+    say("depthwise pieces", C, kw, T)
+    x, w, bias, a, b, dout = conv_inputs(500 + C + kw, 2, T, C, kw)
+    pl = kw // 2
+    dfac = (0.5 + np.random.default_rng(2).random((2, T, C))).astype(F)
+
+    def moved(h):
+        buf = torch.empty(h.size + 1, dtype=torch.float32, device="cuda")
+        buf[1:].copy_(dev(h).reshape(-1))
+        return buf[1:].view(h.shape)
+
+    results = []
+    for put in (dev, moved):
+        out, slope, m = B.aqt_depthwise_conv_fwd(put(x), put(w), bias=dev(bias), pad_left=pl, norm_scale=dev(a),
+                                                 norm_shift=dev(b), swish=True, want_dfac=True, want_absmax=True)
+        results.append([host(t) for t in (out, slope, m, *B.aqt_depthwise_conv_bwd(put(dout), put(x), put(w), dfac=put(dfac),
+                                                                                   pad_left=pl))])
+    for p, q in zip(*results):
+        assert np.array_equal(p, q)
+    out, slope, _, dx, dw, db = results[0]
+    check_depthwise_forward(out, slope, x, w, bias, a, b, pl, True)
+    dv = dout.astype(np.float64) * dfac.astype(np.float64)
+    g = oracle.depthwise_conv_bwd(dv, x, w, pad_left=pl)
+    check_grad(dx, g["dx"], g["dx_abs"], "dx")
+    check_grad(dw, g["dw"], g["dw_abs"], "dw")
+    check_grad(db, g["dbias"], np.abs(dv).sum((0, 1)), "dbias")
+
+
 @pytest.mark.parametrize("B_,T,D,kw,pl,policy", [
     (32, 400, 512, 32, 15, ((4, 8), (8, 8))),   # the convolution-module configuration: int4 then int8 weights
     (3, 300, 256, 15, 14, ((8, 8), (4, 8))),    # causal kernel 15; tuned kernels, ragged M
