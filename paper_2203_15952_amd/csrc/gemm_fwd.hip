@@ -396,10 +396,15 @@ __global__ __launch_bounds__(kThreads, 2) void dense_fwd_mfma_kernel(
   AQT_TL(4);
   AQT_TL_WRITE(g_timeline_fwd, bm * 65536 + bn);
 #endif
-  if (y_absmax) {   // uniform: one atomic per wavefront, and only if it can raise the word
+  // Uniform: one atomic per workgroup, and only if it can raise the word.  The workgroups of a first round all find it at
+  // zero and queue at it: 12800 x 512 -> 2048 with Swish 64 us, 82 with one atomic per wavefront.
+  if (y_absmax) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) amax = max(amax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(amax), off)));
-    if (lane == 0) note_absmax(y_absmax, amax);
+    __shared__ uint32_t wave_max[kThreads / 64];
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    if (threadIdx.x == 0) note_absmax(y_absmax, max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3])));
   }
 }
 
