@@ -110,7 +110,8 @@ aqt_status launch_dense_fwd_wonly(const float *x, const void *wq_packed, const f
                                   int64_t N, int bits_w, const float *bias, int epilogue, float *y, void *ws,
                                   hipStream_t st);
 
-// ---- the contractions for any shape, straight from the caller's tensors (gemm_any.hip) -----------
+// ---- contractions straight from the caller's tensors (gemm_any.hip): the forward for any shape; the float ones for small
+// problems on the tuned kernels' grid, which gemm_bwd.hip checks -----------
 aqt_status launch_dense_fwd_any(const int8_t *xq, const float *s_x, const void *wq_packed, const float *s_w, int64_t M,
                                 int64_t K, int64_t N, int bits_w, const float *bias, int epilogue, float *y,
                                 int32_t *acc_out, uint32_t *y_absmax, float *dact, hipStream_t st);
@@ -118,10 +119,20 @@ aqt_status launch_dense_fwd_wonly_any(const float *x, const void *wq_packed, con
                                       int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st);
 aqt_status launch_bwd_dx_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
                              const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st);
-int dw_any_slabs(int64_t M, int64_t K, int64_t N);   // slabs of rows it would like: K x N floats each in `partial`,
-                                                     // cdiv(K, 128) x N doubles each in `bias_part` (dbias not null)
+int dw_any_slabs(int64_t M, int64_t K, int64_t N);   // slabs of rows: K x N floats each in `partial`, K / 128 x N doubles
+                                                     // each in `bias_part` (dbias not null)
 aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
-                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, int max_slabs, float *dbias,
+                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, float *dbias, double *bias_part,
+                             hipStream_t st);
+
+// ---- the float ones in float64, off the tuned kernels' grid (gemm_any_f64.hip) -------------------------
+aqt_status launch_bwd_dx_f64(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
+                             const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st);
+aqt_status launch_dense_fwd_wonly_f64(const float *x, const void *wq_packed, const float *s_w, int64_t M, int64_t K,
+                                      int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st);
+int dw_f64_slabs(int64_t M, int64_t K, int64_t N);   // K x N doubles each in `partial`, cdiv(K, 64) x N each in `bias_part`
+aqt_status launch_bwd_dw_f64(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
+                             int64_t M, int64_t K, int64_t N, float *dw, double *partial, int max_slabs, float *dbias,
                              double *bias_part, hipStream_t st);
 
 // ---- straight-through backward (gemm_bwd.hip) -------------------------------------

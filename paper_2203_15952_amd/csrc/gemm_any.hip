@@ -1,83 +1,31 @@
-// The contractions of the quantized dense layer for any shape (arxiv 2203.15952, Sec. 1 and Sec. 2.2; the
-// straight-through backward; Sec. 4.1 for the weight-only modes): sizes that no tile of the tuned kernels in
-// gemm_fwd.hip / gemm_bwd.hip divides, and problems too small to fill the chip with their tiles.
+// The contractions of the quantized dense layer straight from the caller's tensors, without a re-ordered operand or a
+// pre-pass (arxiv 2203.15952, Sec. 1 and Sec. 2.2; the straight-through backward; Sec. 4.1 for the weight-only modes):
+//   the forward, integer sums, for any shape that no tile of the tuned kernel in gemm_fwd.hip divides, and for problems
+//   too small to fill the chip with its tiles;
+//   dX, dW and the weight-only forward for problems on the grid of the tuned kernels in gemm_bwd.hip (which checks
+//   it: whole column tiles, 16-byte aligned tensors) that are too small for their tiles.  Off that grid gemm_any_f64.hip.
 //
-// All kernels work straight from the caller's tensors (no re-ordered operand, no pre-pass).  A workgroup is
-// WM x WN wavefronts side by side, times WK groups of them that share one output tile and take turns along the
-// contraction.  Each group brings a slice of its tile's rows through registers into LDS, whole 64- or 128-byte
-// row pieces at a time, converts what has to be converted there once for all its wavefronts, and multiplies while
-// the next two slices' loads are in flight.  (Fragments fetched straight from memory, one row per lane, were tried
-// first: rows a power of two apart share a cache set and every access misses; dX 40 x 2048 -> 512 took 20 us
+// A workgroup is WM x WN wavefronts side by side, times WK groups of them that share one output tile and take turns
+// along the contraction.  Each group brings a slice of its tile's rows through registers into LDS, whole 64- or
+// 128-byte row pieces at a time, converts what has to be converted there once for all its wavefronts, and multiplies
+// while the next two slices' loads are in flight.  (Fragments fetched straight from memory, one row per lane, were
+// tried first: rows a power of two apart share a cache set and every access misses; dX 40 x 2048 -> 512 took 20 us
 // that way, 11 us this way.)  Small problems (WK = 8, one wavefront per group) are bound by the latency of a trip to
 // memory, so eight slices are in flight at a time; the sums are added up through LDS.
-// Measured at 4099 x 520 x 1000, int8 codes, against the one-thread-per-output kernels these replace: forward 17 us
-// (7902), dX 37 (6565), dW with its fold 41 (1096); forward 40 x 512 -> 2048 3.5 us (about 170).
-//
-// Edges: rows and columns beyond the tensors are read at clamped, valid addresses and not stored.  Contraction
-// positions beyond the end are zeros: a piece that would cross the end of its row is read so that it ends there and is
-// shifted down when it is staged (rows shorter than one piece are read element by element).
-#include <type_traits>
-
-#include "aqt_internal.h"
+// Measured against the one-thread-per-output kernels these replace: forward 4099 x 520 x 1000, int8 codes, 17 us (7902);
+// 40 x 512 -> 2048 3.5 us (about 170).
+#include "any_shape.h"
 #include "colsum.h"
 #include "epilogue.h"
 
 namespace aqt {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
-template <class T>
-__device__ __forceinline__ T load_at(const void *p) {   // any byte alignment
-  T v;
-  __builtin_memcpy(&v, p, sizeof(T));
-  return v;
-}
-
-__device__ __forceinline__ bool mask_bit(const uint32_t *__restrict__ mask, int64_t i) {
-  return (mask[i >> 5] >> (i & 31)) & 1u;
-}
-
-// Up to 16 bytes at p + at, at + 16 <= end; beyond `end` zeros.
-__device__ __forceinline__ v4i load16_guarded(const uint8_t *p, int64_t at, int64_t end) {
-  if (at + 16 <= end) return load_at<v4i>(p + at);
-  uint32_t d[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int e = 0; e < 16; ++e)
-    if (at + e < end) d[e >> 2] |= static_cast<uint32_t>(p[at + e]) << (8 * (e & 3));
-  return v4i{static_cast<int>(d[0]), static_cast<int>(d[1]), static_cast<int>(d[2]), static_cast<int>(d[3])};
-}
-
-// 16 bytes moved down by `bytes` (0 .. 16), zeros from above.
-__device__ __forceinline__ v4i shift_down(v4i v, int bytes) {
-  if (bytes & 4) v = v4i{v.y, v.z, v.w, 0};
-  if (bytes & 8) v = v4i{v.z, v.w, 0, 0};
-  if (bytes & 16) v = v4i{0, 0, 0, 0};
-  const int b = bytes & 3;
-  v.x = static_cast<int>(__builtin_amdgcn_alignbyte(static_cast<uint32_t>(v.y), static_cast<uint32_t>(v.x), b));
-  v.y = static_cast<int>(__builtin_amdgcn_alignbyte(static_cast<uint32_t>(v.z), static_cast<uint32_t>(v.y), b));
-  v.z = static_cast<int>(__builtin_amdgcn_alignbyte(static_cast<uint32_t>(v.w), static_cast<uint32_t>(v.z), b));
-  v.w = static_cast<int>(__builtin_amdgcn_alignbyte(0u, static_cast<uint32_t>(v.w), b));
-  return v;
-}
-__device__ __forceinline__ v4f shift_down(v4f v, int elements) {   // 0 .. 4
-  if (elements & 1) v = v4f{v.y, v.z, v.w, 0.0f};
-  if (elements & 2) v = v4f{v.z, v.w, 0.0f, 0.0f};
-  if (elements & 4) v = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-  return v;
-}
-// how far a piece of `size` that starts at `at` was moved up to end at `end`, at most `size`
-__device__ __forceinline__ int moved(int64_t at, int64_t end, int size) {
-  const int64_t d = at + size - end;
-  return d <= 0 ? 0 : d < size ? static_cast<int>(d) : size;
-}
 
 // LDS rows are CH chunks of 16 bytes without padding; the chunk index is XORed with row bits so that the rows
 // of a fragment read spread over all banks.
@@ -87,81 +35,6 @@ __device__ __forceinline__ int swz(int row) {
 }
 template <int CH>
 __device__ __forceinline__ int chunk_at(int row, int chunk) { return row * (CH * 16) + ((chunk ^ swz<CH>(row)) << 4); }
-
-// Eight int4 codes in memory order (low nibble first) -> eight bytes 16 * code, in order.
-__device__ __forceinline__ v2i expand16(uint32_t w) {
-  const uint32_t even = (w << 4) & 0xF0F0F0F0u, odd = w & 0xF0F0F0F0u;
-  v2i o;
-  o.x = static_cast<int>(__builtin_amdgcn_perm(odd, even, 0x05010400u));
-  o.y = static_cast<int>(__builtin_amdgcn_perm(odd, even, 0x07030602u));
-  return o;
-}
-
-// The slice loop of a workgroup.  load(set, slice) requests a slice into register set 0 or 1, stage(set, slice, slot)
-// moves it to LDS, multiply(slot) consumes it.
-//   WK == 1: all wavefronts share the slices; two LDS slots, so that a slice is staged (and converted) while the one
-//            before it is multiplied, one barrier per slice, loads two slices ahead.
-//   WK > 1:  every wavefront has its own slices wk, wk + WK, ... and its own slot: its LDS operations are executed
-//            in order, so no barrier is needed and the wavefronts overlap as they come.
-// The loop has no branch around a load (past the end the last slice is requested again): behind a branch the compiler
-// cannot count what is in flight and waits for everything, which undoes the prefetch.
-template <int WK, class Load, class Stage, class Multiply>
-__device__ __forceinline__ void run_slices(uint8_t *lds, int slice_bytes, int wk, int64_t slices, Load load, Stage stage,
-                                           Multiply multiply) {
-  constexpr std::integral_constant<int, 0> set0{};
-  constexpr std::integral_constant<int, 1> set1{};
-  const int64_t mine = WK > 1 ? (slices - wk + WK - 1) / WK : slices;   // this wavefront's slices
-  auto at = [&](int64_t i) { return wk + WK * (i < mine ? i : mine - 1); };
-  if (mine <= 0) return;   // WK > 1 only
-  if (WK > 1) {
-    uint8_t *const slot = lds + wk * slice_bytes;
-    load(set0, at(0));
-    load(set1, at(1));
-    for (int64_t i = 0; i < mine; i += 2) {
-      stage(set0, at(i), slot);
-      load(set0, at(i + 2));
-      __builtin_amdgcn_wave_barrier();
-      multiply(slot);
-      if (i + 1 >= mine) break;
-      __builtin_amdgcn_wave_barrier();
-      stage(set1, at(i + 1), slot);
-      load(set1, at(i + 3));
-      __builtin_amdgcn_wave_barrier();
-      multiply(slot);
-      __builtin_amdgcn_wave_barrier();
-    }
-    return;
-  }
-  uint8_t *const slot0 = lds, *const slot1 = lds + slice_bytes;
-  load(set0, at(0));
-  load(set1, at(1));
-  stage(set0, at(0), slot0);
-  load(set0, at(2));
-  __syncthreads();
-  for (int64_t s = 0; s < mine; s += 2) {
-    stage(set1, at(s + 1), slot1);
-    load(set1, at(s + 3));
-    multiply(slot0);
-    __syncthreads();
-    if (s + 1 >= mine) break;
-    stage(set0, at(s + 2), slot0);
-    load(set0, at(s + 4));
-    multiply(slot1);
-    __syncthreads();
-  }
-}
-
-// One slice that is loaded whole before anything else (rows shorter than a piece); WK > 1: by one wavefront alone.
-template <int WK, class LoadNarrow, class Stage, class Multiply>
-__device__ __forceinline__ void run_narrow(uint8_t *slot, LoadNarrow load_narrow, Stage stage, Multiply multiply) {
-  constexpr std::integral_constant<int, 0> set0{};
-  load_narrow(set0);
-  stage(set0, 0, slot);
-  if (WK > 1) __builtin_amdgcn_wave_barrier();
-  else __syncthreads();
-  multiply(slot);
-  if (WK == 1) __syncthreads();
-}
 
 // ---- forward: int8 codes x int8 / int4 codes, int32 sums -----------------------------------
 // A wavefront owns TM x TN blocks of 32 x 32; a GLU tile pairs value (even) and gate (odd) column blocks.
@@ -357,11 +230,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
 // ---- float32 operand x codes ------------------------------------------------------------------
 // Codes are exact in bf16; the float operand is carried whole, as three bf16 terms of 8 significant bits each
 // (a = hi + mid + lo exactly), and three v_mfma_f32_32x32x16_bf16 passes form products that are exact in
-// float32.  Sums run in float32 over at most kChain contraction positions and are added up in float64, so a
-// result is the float64 sum to within about one float32 rounding.
+// float32.  Sums run in float32 over at most kChain contraction positions and are added up in float64.  (The tuned
+// kernels that would otherwise take these shapes carry two terms and one float32 sum: error against float64 2.4e-6 of
+// the result at 1024 x 256 x 1024, here 1.1e-7 for dX, 8e-8 for dW.)  An infinity, or a finite value above bf16's
+// largest, gives NaN, as it does in the tuned kernels.
 constexpr int kChain = 512;
-constexpr int kSlice = 32;    // contraction positions per slice: LDS rows of 64 bytes
-constexpr int kCh = 4;        // 16-byte chunks of such a row
+constexpr int kCh = 4;        // 16-byte chunks of an LDS row: kSlice bf16 values
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even
   v2f f = {a, b};
@@ -408,63 +282,56 @@ __device__ __forceinline__ v4i nibbles8_bf16(uint32_t w) {   // eight int4 codes
 // out[m, r] = sum_c f[m, c] (* scale[c]) * q[r, c]: rows of both operands contraction-contiguous.
 //   MODE 0 (dX):   f = dy [M,N], scale = s_w, q = wq_kn [K,N]; out times the clip mask and the factor
 //   MODE 1 + e:    weight-only forward with epilogue e: f = x [M,K], q = the forward weight operand [N][K]
-// LONG: a group's share of the contraction exceeds kChain, so float32 sums are moved to float64 on the way.
-template <int TM, int TN, int WM, int WN, int WK, bool PACKED, int MODE, bool LONG>
-__global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 && !LONG ? 4 : 2) void f32_codes_any_kernel(
+// Eight wavefronts share a tile of 32 rows x 32 TN columns and take turns along the contraction.
+// LONG: a wavefront's share of the contraction exceeds kChain, so float32 sums are moved to float64 on the way.
+template <int TN, bool PACKED, int MODE, bool LONG>
+__global__ __launch_bounds__(512, 2) void f32_codes_any_kernel(
     const float *__restrict__ f, const float *__restrict__ scale, const uint8_t *__restrict__ q, int64_t M, int64_t R,
     int64_t C, const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x, const float *__restrict__ factor,
     const float *__restrict__ bias, float *__restrict__ out, int tiles_r) {
-  static_assert(16 % WK == 0 && (WK == 1 || (WM * WN == 1 && TM == 1)) && (MODE != 1 + AQT_EPI_GLU || TN % 2 == 0),
-                "the epilogue is shared out by registers, a split contraction has one wavefront per group");
+  static_assert(MODE != 1 + AQT_EPI_GLU || TN % 2 == 0, "a GLU tile pairs value and gate blocks");
   constexpr bool DX = MODE == 0, GLU = MODE == 1 + AQT_EPI_GLU;
-  constexpr int G = 64 * WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
-  // pieces of four floats, of sixteen codes, per thread and slice; a narrow tile leaves some threads without codes
-  constexpr int NA = BM * 8 / G, NB = BN * 2 >= G ? BN * 2 / G : 1;
-  static_assert(NA * G == BM * 8 && NA > 0 && (NB * G == BN * 2 || BN * 2 < G), "whole pieces per thread");
+  constexpr int WK = 8, G = 64, BM = 32, BN = 32 * TN;
+  constexpr int NA = BM * 8 / G, NB = BN * 2 / G;   // pieces of four floats, of sixteen codes, per thread and slice
   constexpr int kImage = BM * 64;
   constexpr int kSliceBytes = 3 * kImage + BN * 64;
-  constexpr int kRedBytes = WK > 1 ? WK * TN * 16 * 64 * (LONG ? 8 : 4) : 0;
-  constexpr int kBuffers = WK == 1 ? 2 : WK;
-  constexpr int kLds = kBuffers * kSliceBytes > kRedBytes ? kBuffers * kSliceBytes : kRedBytes;
+  constexpr int kRedBytes = WK * TN * 16 * 64 * (LONG ? 8 : 4);
+  constexpr int kLds = WK * kSliceBytes > kRedBytes ? WK * kSliceBytes : kRedBytes;
   __shared__ __attribute__((aligned(16))) uint8_t lds[kLds];
-  const int t = threadIdx.x, lane = t & 63, lr = lane & 31, lk = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int wk = wave / (WM * WN), wn = wave % WN, wm = (wave / WN) % WM, gt = t - wk * G;
+  const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
+  const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t bm = blockIdx.x / tiles_r, br = blockIdx.x % tiles_r;
   const int64_t oc = GLU ? R / 2 : R;
   auto chan = [&](int cb) -> int64_t {
     if (GLU) return br * (BN / 2) + (cb >> 1) * 32 + ((cb & 1) ? oc : 0);
     return br * BN + cb * 32;
   };
-  const int64_t row_bytes = PACKED ? (C + 1) / 2 : C;
+  const int64_t row_bytes = PACKED ? C / 2 : C;
   const float *pf[NA];
   const uint8_t *pq[NB];
-  const bool has_codes = BN * 2 >= G || gt < BN * 2;
-  const int piece = gt & 7;   // G is a multiple of 8: a thread's pieces sit at the same place of their rows
+  const int piece = lane & 7;   // a thread's pieces sit at the same place of their rows
 #pragma unroll
   for (int u = 0; u < NA; ++u) {
-    const int64_t m = bm * BM + ((gt + u * G) >> 3);
+    const int64_t m = bm * BM + ((lane + u * G) >> 3);
     pf[u] = f + (m < M ? m : M - 1) * C;
   }
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
-    const int r = has_codes ? (gt + u * G) >> 1 : 0;
+    const int r = (lane + u * G) >> 1;
     const int64_t n = chan(r >> 5) + (r & 31);
-    pq[u] = q + (n < R ? n : R - 1) * row_bytes;
+    pq[u] = q + n * row_bytes;
   }
   v4f ra[2][NA], rs[2] = {{1.0f, 1.0f, 1.0f, 1.0f}, {1.0f, 1.0f, 1.0f, 1.0f}};
   v4i rb[2][NB];
   constexpr int kPiece = PACKED ? 8 : 16;   // bytes of sixteen codes
-  const bool narrow = C < 4 || row_bytes < kPiece;   // uniform
   auto load = [&](auto set, int64_t slice) {
     constexpr int S = decltype(set)::value;
-    const int64_t c0 = slice * kSlice + 4 * piece, a0 = slice * (2 * kPiece) + kPiece * (gt & 1);
-    const int64_t c = c0 + 4 <= C ? c0 : C - 4, at = a0 + kPiece <= row_bytes ? a0 : row_bytes - kPiece;
+    const int64_t c = slice * kSlice + 4 * piece, at = slice * (2 * kPiece) + kPiece * (lane & 1);
 #pragma unroll
     for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4f>(pf[u] + c);
     if (DX) rs[S] = load_at<v4f>(scale + c);
 #pragma unroll
-    for (int u = 0; u < NB; ++u) {   // a thread without codes reads what it will not use
+    for (int u = 0; u < NB; ++u) {
       if (PACKED) {
         const v2i w = load_at<v2i>(pq[u] + at);
         rb[S][u] = v4i{w.x, w.y, 0, 0};
@@ -473,74 +340,42 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 && !LONG ? 4 : 2) v
       }
     }
   };
-  auto load_narrow = [&](auto set) {   // fewer than 16 positions
-    constexpr int S = decltype(set)::value;
+  v16f acc[TN];
+  double sum[LONG ? TN : 1][16];
 #pragma unroll
-    for (int u = 0; u < NA; ++u) {
-      ra[S][u] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (4 * piece + e < C) ra[S][u][e] = pf[u][4 * piece + e];
+    for (int r = 0; r < 16; ++r) {
+      acc[j][r] = 0.0f;
+      if (LONG) sum[LONG ? j : 0][r] = 0.0;
     }
-    if (DX) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (4 * piece + e < C) rs[S][e] = scale[4 * piece + e];
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u)
-      rb[S][u] = load16_guarded(pq[u], kPiece * (gt & 1), (gt & 1) ? kPiece : row_bytes);   // all in the first piece
-  };
-  v16f acc[TM][TN];
-  double sum[LONG ? TM : 1][LONG ? TN : 1][16];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
+  auto fold = [&]() {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        acc[i][j][r] = 0.0f;
-        if (LONG) sum[LONG ? i : 0][LONG ? j : 0][r] = 0.0;
+        sum[LONG ? j : 0][r] += static_cast<double>(acc[j][r]);
+        acc[j][r] = 0.0f;
       }
-  auto fold = [&]() {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sum[LONG ? i : 0][LONG ? j : 0][r] += static_cast<double>(acc[i][j][r]);
-          acc[i][j][r] = 0.0f;
-        }
   };
   int since = 0;
   auto stage = [&](auto set, int64_t slice, uint8_t *slot) {
     constexpr int S = decltype(set)::value;
     uint8_t *const sA = slot, *const sB = slot + 3 * kImage;
-    if ((slice + 1) * kSlice > C && !narrow) {
-      const int df = moved(slice * kSlice + 4 * piece, C, 4), dq = moved(slice * (2 * kPiece) + kPiece * (gt & 1), row_bytes, kPiece);
-#pragma unroll
-      for (int u = 0; u < NA; ++u) ra[S][u] = shift_down(ra[S][u], df);
-      if (DX) rs[S] = shift_down(rs[S], df);
-#pragma unroll
-      for (int u = 0; u < NB; ++u) rb[S][u] = shift_down(rb[S][u], dq);
-    }
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       v4f v = ra[S][u];
       if (DX) { v.x *= rs[S].x; v.y *= rs[S].y; v.z *= rs[S].z; v.w *= rs[S].w; }
-      store_split(sA + chunk_at<kCh>((gt + u * G) >> 3, piece >> 1) + 8 * (piece & 1), kImage, v);
+      store_split(sA + chunk_at<kCh>((lane + u * G) >> 3, piece >> 1) + 8 * (piece & 1), kImage, v);
     }
-    if (has_codes) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int r = (gt + u * G) >> 1, c0 = 2 * (gt & 1);
-        const v4i w = rb[S][u];
-        const uint32_t w0 = static_cast<uint32_t>(w.x), w1 = static_cast<uint32_t>(w.y), w2 = static_cast<uint32_t>(w.z),
-                       w3 = static_cast<uint32_t>(w.w);
-        *reinterpret_cast<v4i *>(sB + chunk_at<kCh>(r, c0)) = PACKED ? nibbles8_bf16(w0) : codes8_bf16(w0, w1);
-        *reinterpret_cast<v4i *>(sB + chunk_at<kCh>(r, c0 + 1)) = PACKED ? nibbles8_bf16(w1) : codes8_bf16(w2, w3);
-      }
+    for (int u = 0; u < NB; ++u) {
+      const int r = (lane + u * G) >> 1, c0 = 2 * (lane & 1);
+      const v4i w = rb[S][u];
+      const uint32_t w0 = static_cast<uint32_t>(w.x), w1 = static_cast<uint32_t>(w.y), w2 = static_cast<uint32_t>(w.z),
+                     w3 = static_cast<uint32_t>(w.w);
+      *reinterpret_cast<v4i *>(sB + chunk_at<kCh>(r, c0)) = PACKED ? nibbles8_bf16(w0) : codes8_bf16(w0, w1);
+      *reinterpret_cast<v4i *>(sB + chunk_at<kCh>(r, c0 + 1)) = PACKED ? nibbles8_bf16(w1) : codes8_bf16(w2, w3);
     }
   };
   auto multiply = [&](const uint8_t *slot) {
@@ -549,39 +384,33 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 && !LONG ? 4 : 2) v
     for (int kk = 0; kk < kSlice / 16; ++kk) {
       v4i b[TN];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const v4i *>(sB + chunk_at<kCh>((wn * TN + j) * 32 + lr, 2 * kk + lk));
+      for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const v4i *>(sB + chunk_at<kCh>(j * 32 + lr, 2 * kk + lk));
 #pragma unroll
-      for (int img = 2; img >= 0; --img)   // smallest terms first
+      for (int img = 2; img >= 0; --img) {   // smallest terms first
+        const v4i a = *reinterpret_cast<const v4i *>(sA + img * kImage + chunk_at<kCh>(lr, 2 * kk + lk));
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const v4i a = *reinterpret_cast<const v4i *>(sA + img * kImage + chunk_at<kCh>((wm * TM + i) * 32 + lr, 2 * kk + lk));
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = mfma_bf16(a, b[j], acc[i][j]);
-        }
+        for (int j = 0; j < TN; ++j) acc[j] = mfma_bf16(a, b[j], acc[j]);
+      }
     }
     if (LONG && ++since == kChain / kSlice) {
       fold();
       since = 0;
     }
   };
-  if (!narrow) run_slices<WK>(lds, kSliceBytes, wk, cdiv(C, kSlice), load, stage, multiply);
-  else if (wk == 0) run_narrow<WK>(lds, load_narrow, stage, multiply);
+  run_slices<WK>(lds, kSliceBytes, wk, C / kSlice, load, stage, multiply);
   if (LONG) fold();
   constexpr int RW = 16 / WK;
-  if (WK > 1) {
-    __syncthreads();
+  __syncthreads();
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+  for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int at = ((wk * TN + j) * 16 + r) * 64 + lane;
-        if (LONG) reinterpret_cast<double *>(lds)[at] = sum[0][LONG ? j : 0][r];
-        else reinterpret_cast<float *>(lds)[at] = acc[0][j][r];
-      }
-    __syncthreads();
-  }
-  auto sum_of = [&](int i, int j, int rr) -> double {   // register wk * RW + rr, the groups' shares in order
-    if (WK == 1) return LONG ? sum[LONG ? i : 0][LONG ? j : 0][rr] : static_cast<double>(acc[i][j][rr]);
+    for (int r = 0; r < 16; ++r) {
+      const int at = ((wk * TN + j) * 16 + r) * 64 + lane;
+      if (LONG) reinterpret_cast<double *>(lds)[at] = sum[LONG ? j : 0][r];
+      else reinterpret_cast<float *>(lds)[at] = acc[j][r];
+    }
+  __syncthreads();
+  auto sum_of = [&](int j, int rr) -> double {   // register wk * RW + rr, the wavefronts' shares in order
     double v = 0.0;
 #pragma unroll
     for (int w = 0; w < WK; ++w) {
@@ -590,19 +419,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 && !LONG ? 4 : 2) v
     }
     return v;
   };
-  const int64_t m_lane = bm * BM + wm * 32 * TM + 4 * lk;   // this lane's first row
+  const int64_t m_lane = bm * BM + 4 * lk;   // this lane's first row
   if (DX) {
     const bool keep = s_x[0] != 0.0f;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int64_t n = chan(wn * TN + j) + lr, at0 = m_lane * R + n;
-      const int rows = n < R ? static_cast<int>(M - m_lane < BM ? M - m_lane : BM) : 0;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
+      const int64_t n = chan(j) + lr, at0 = m_lane * R + n;
+      const int rows = static_cast<int>(M - m_lane < BM ? M - m_lane : BM);
 #pragma unroll
         for (int rr = 0; rr < RW; ++rr) {
-          const int r = wk * RW + rr, row = i * 32 + 8 * (r >> 2) + (r & 3);   // the same in every lane
-          float v = static_cast<float>(sum_of(i, j, rr));
+          const int r = wk * RW + rr, row = 8 * (r >> 2) + (r & 3);   // the same in every lane
+          float v = static_cast<float>(sum_of(j, rr));
           if (row >= rows) continue;
           const int64_t at = at0 + row * R;
           if (factor) v = v * factor[at];
@@ -614,20 +441,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 && !LONG ? 4 : 2) v
   constexpr int JS = GLU ? 2 : 1;
 #pragma unroll
   for (int j = 0; j < TN; j += JS) {
-    const int64_t n = chan(wn * TN + j) + lr;
-    const bool live = n < oc;
-    const int64_t nc = live ? n : oc - 1, ng = nc + (GLU ? oc : 0);
-    const double sc_a = scale[nc], sc_b = GLU ? scale[ng] : 0.0f;
-    const float bias_a = bias ? bias[nc] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
-    const int rows = live ? static_cast<int>(M - m_lane < BM ? M - m_lane : BM) : 0;
+    const int64_t n = chan(j) + lr, ng = n + (GLU ? oc : 0);
+    const double sc_a = scale[n], sc_b = GLU ? scale[ng] : 0.0f;
+    const float bias_a = bias ? bias[n] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
+    const int rows = static_cast<int>(M - m_lane < BM ? M - m_lane : BM);
     float *const ol = out + m_lane * oc + n;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
       for (int rr = 0; rr < RW; ++rr) {
-        const int r = wk * RW + rr, row = i * 32 + 8 * (r >> 2) + (r & 3);
-        const float v = static_cast<float>(sum_of(i, j, rr) * sc_a) + bias_a;
-        const float gate = GLU ? static_cast<float>(sum_of(i, j + JS - 1, rr) * sc_b) + bias_b : 0.0f;
+        const int r = wk * RW + rr, row = 8 * (r >> 2) + (r & 3);
+        const float v = static_cast<float>(sum_of(j, rr) * sc_a) + bias_a;
+        const float gate = GLU ? static_cast<float>(sum_of(j + JS - 1, rr) * sc_b) + bias_b : 0.0f;
         if (row >= rows) continue;
         float o = v;
         if (MODE == 1 + AQT_EPI_SWISH) o = swish_f32(v);
@@ -650,18 +473,6 @@ constexpr int kDwThreads = kColsumThreads;
 static_assert(kDwThreads == 256);
 constexpr int kDwTile = 128;
 
-struct DwFinish {
-  const float *s_x, *s_w;
-  const uint32_t *mask_w;
-};
-
-__device__ __forceinline__ float dw_value(double s, int64_t at, int64_t n, const DwFinish &fin, double sx) {
-  const bool pass = fin.mask_w ? mask_bit(fin.mask_w, at) : (fin.s_w[n] != 0.0f);
-  return pass ? static_cast<float>(sx * s) : 0.0f;
-}
-
-// Off: how offsets inside a slice's 32 rows are held; with 32 bits a load is one scalar base and a fixed lane offset.
-template <class Off>
 __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t *__restrict__ xq, const float *__restrict__ dy,
                                                                    int64_t M, int64_t K, int64_t N, int64_t rows_per_slab,
                                                                    float *__restrict__ out, int tiles_n, int tiles, int finish,
@@ -676,20 +487,18 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
   const int64_t m0 = slab * rows_per_slab, m1 = m0 + rows_per_slab < M ? m0 + rows_per_slab : M;
   const int g = t & 31, mg = t >> 5;          // this thread's column group and its four rows 4 mg .. + 3 of a slice
   const int64_t kc = k0 + 4 * g, nc = n0 + 4 * g;
-  const bool kwhole = kc + 4 <= K, nwhole = nc + 4 <= N;
-  const bool narrow = K < 4 || N < 4, edge = k0 + kDwTile > K || n0 + kDwTile > N;   // uniform
-  const int64_t kr = narrow || kwhole ? kc : K - 4, nr = narrow || nwhole ? nc : N - 4;
-  const int dk = moved(kc, K, 4), dn = moved(nc, N, 4);
   const int64_t slices = cdiv(m1 - m0, kSlice);
   const int last_rows = static_cast<int>(m1 - m0 - (slices - 1) * kSlice);
-  Off xo[4], yo[4], xl[4], yl[4];   // offsets of this thread's rows in a slice; in the last one, where rows beyond the end are its last
+  // byte offsets of this thread's rows in a slice (K, N below 2^24), so that a load is one scalar base and a fixed lane
+  // offset; in the last slice, rows beyond the end are its last
+  uint32_t xo[4], yo[4], xl[4], yl[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t r = 4 * mg + i, l = r < last_rows ? r : last_rows - 1;
-    xo[i] = static_cast<Off>(r * K + kr);
-    yo[i] = static_cast<Off>((r * N + nr) * 4);
-    xl[i] = static_cast<Off>(l * K + kr);
-    yl[i] = static_cast<Off>((l * N + nr) * 4);
+    xo[i] = static_cast<uint32_t>(r * K + kc);
+    yo[i] = static_cast<uint32_t>((r * N + nc) * 4);
+    xl[i] = static_cast<uint32_t>(l * K + kc);
+    yl[i] = static_cast<uint32_t>((l * N + nc) * 4);
   }
   uint32_t rc[2][4];
   v4f rg[2][4];
@@ -703,21 +512,6 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
 #pragma unroll
     for (int i = 0; i < 4; ++i) rg[S][i] = load_at<v4f>(y + (last ? yl[i] : yo[i]));
   };
-  int64_t narrow_slice = 0;
-  auto load_narrow = [&](auto set) {   // fewer than four columns of an operand: element by element
-    constexpr int S = decltype(set)::value;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t r = m0 + narrow_slice * kSlice + 4 * mg + i;
-      rc[S][i] = 0u;
-      rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (r < m1 && kc + e < K) rc[S][i] |= static_cast<uint32_t>(static_cast<uint8_t>(xq[r * K + kc + e])) << (8 * e);
-        if (r < m1 && nc + e < N) rg[S][i][e] = dy[r * N + nc + e];
-      }
-    }
-  };
   // a wavefront multiplies all four codes blocks with one block of the gradient (seven fragment reads per twelve products)
   v16f acc[4];
 #pragma unroll
@@ -729,13 +523,6 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
   int64_t staged = 0, turn = bias_part ? kt : slices;
   auto stage = [&](auto set, int64_t slice, uint8_t *slot) {
     constexpr int S = decltype(set)::value;
-    if (edge && !narrow) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        rc[S][i] = dk < 4 ? rc[S][i] >> (8 * dk) : 0u;
-        rg[S][i] = shift_down(rg[S][i], dn);
-      }
-    }
     if (slice == slices - 1 && last_rows < kSlice) {   // rows beyond the slab contribute nothing
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -778,16 +565,14 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
       }
     }
   };
-  if (!narrow) run_slices<1>(lds, kSliceBytes, 0, slices, load, stage, multiply);
-  else
-    for (; narrow_slice < slices; ++narrow_slice) run_narrow<1>(lds, load_narrow, stage, multiply);
+  run_slices<1>(lds, kSliceBytes, 0, slices, load, stage, multiply);
   if (bias_part) {   // the eight row groups of a column, in order
     double *const sums = reinterpret_cast<double *>(lds);
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < 4; ++b) sums[b * kDwThreads + t] = colsum[b];
     __syncthreads();
-    if (t < kDwTile && n0 + t < N) {
+    if (t < kDwTile) {
       const double *const p = sums + (t & 3) * kDwThreads + (t >> 2);
       double sum = p[0];
 #pragma unroll
@@ -803,7 +588,7 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
   const double sx = finish ? fin.s_x[0] : 1.0;
   bool nz[4];                       // channels whose scale is not zero (what a missing clip mask stands for)
 #pragma unroll
-  for (int e = 0; e < 4; ++e) nz[e] = finish && fin.s_w[nc + e < N ? nc + e : N - 1] != 0.0f;
+  for (int e = 0; e < 4; ++e) nz[e] = finish && fin.s_w[nc + e] != 0.0f;
   float *const o = out + (finish ? 0 : static_cast<int64_t>(slab) * K * N);
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
@@ -816,19 +601,11 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
       const int q = (t >> 5) + 8 * u;
       const int64_t k = k0 + 4 * q + p, at = k * N + nc;
       v4f v = *reinterpret_cast<const v4f *>(img + q * kRow + 4 * g);
-      if (k >= K || nc >= N) continue;
       if (finish) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          v[e] = ((fin.mask_w && nc + e < N) ? mask_bit(fin.mask_w, at + e) : nz[e]) ? static_cast<float>(sx * v[e]) : 0.0f;
+        for (int e = 0; e < 4; ++e) v[e] = (fin.mask_w ? mask_bit(fin.mask_w, at + e) : nz[e]) ? static_cast<float>(sx * v[e]) : 0.0f;
       }
-      if (nwhole) {
-        __builtin_memcpy(o + at, &v, sizeof(v));
-      } else {
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (nc + e < N) o[at + e] = v[e];
-      }
+      *reinterpret_cast<v4f *>(o + at) = v;
     }
   }
 }
@@ -860,23 +637,20 @@ __global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__
     dw[at] = dw_value((sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]), at, at % N, fin, fin.s_x[0]);
 }
 
-// Which workgroup arrangement.  128 x 128 tiles move the fewest bytes through LDS per product but there have to be
-// enough of them for 256 compute units; narrower ones when the columns would mostly be padding; the split
+// Which workgroup arrangement of the forward.  128 x 128 tiles move the fewest bytes through LDS per product but there
+// have to be enough of them for 256 compute units; narrower ones when the columns would mostly be padding; the split
 // contraction below that.  Eight wavefronts per workgroup, so that two share a SIMD even where the launch has one
 // workgroup per compute unit (the staging of one runs under the products of the other).
-// The lines were drawn from sweeps over all five arrangements (us, forward / dX): 3200 x 512 -> 128 (50 tiles of 64 x 128)
-// 5.9 as such, 4.1 split; 800 x 256 -> 1024 (104 tiles) 5.2 / 5.7 split; 10008 x 144 -> 576 12.4 in 64 x 128, 10.7 in
-// 128 x 64; dX 3200 x 128 x 512 (50 tiles) 14.1, split 6.9; dX 3000 x 576 x 144 (235 tiles) 9.1, split 14.1.
+// The lines were drawn from sweeps over all five arrangements (us): 3200 x 512 -> 128 (50 tiles of 64 x 128) 5.9 as
+// such, 4.1 split; 800 x 256 -> 1024 (104 tiles) 5.2, 5.7 split; 10008 x 144 -> 576 12.4 in 64 x 128, 10.7 in 128 x 64.
 enum class Tile { kLarge, kRows, kNarrow, kSmall, kSmallest };   // 128 x 128, 64 x 128, 128 x 64; split contraction: 32 x 64, 32 x 32
-Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, bool glu, bool integer) {
+Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, bool glu) {
   const int64_t narrow = cdiv(M, 128) * cdiv(cols, 64), large = cdiv(M, 128) * cdiv(cols, 128), rows = cdiv(M, 64) * cdiv(cols, 128);
   const bool odd = cdiv(cols, 64) % 2 && cols < 640;   // half of the last 128-wide tile would be padding
   if (odd && narrow >= 128) return Tile::kNarrow;
   if (large >= 192) return Tile::kLarge;
-  if (rows >= (integer ? (contraction <= 256 ? 64 : 100) : 160)) return Tile::kRows;
-  if (glu) return Tile::kSmall;
-  // 32 x 64 halves the conversions of the float operand, where the columns fill it; codes need none
-  return !integer && cdiv(cols, 32) % 2 == 0 && cdiv(M, 32) * cdiv(cols, 64) >= 128 ? Tile::kSmall : Tile::kSmallest;
+  if (rows >= (contraction <= 256 ? 64 : 100)) return Tile::kRows;
+  return glu ? Tile::kSmall : Tile::kSmallest;
 }
 
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
@@ -900,7 +674,7 @@ template <bool PACKED>
 aqt_status fwd_any_sized(const int8_t *xq, const float *s_x, const void *wq, const float *s_w, int64_t M, int64_t K, int64_t N,
                          const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
                          hipStream_t st) {
-  switch (pick_tile(M, N, K, epilogue == AQT_EPI_GLU, true)) {
+  switch (pick_tile(M, N, K, epilogue == AQT_EPI_GLU)) {
     case Tile::kLarge: return fwd_any<1, 2, 4, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
     case Tile::kRows:
       if (epilogue != AQT_EPI_GLU) return fwd_any<1, 1, 2, 4, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
@@ -911,46 +685,33 @@ aqt_status fwd_any_sized(const int8_t *xq, const float *s_x, const void *wq, con
   }
 }
 
-template <int TM, int TN, int WM, int WN, int WK, bool PACKED>
-aqt_status f32_codes_any(int mode, const float *f, const float *scale, const void *q, int64_t M, int64_t R, int64_t C,
-                         const float *s_x, const uint32_t *mask_x, const float *factor, const float *bias, float *out,
-                         hipStream_t st) {
-  const int64_t oc = mode == 1 + AQT_EPI_GLU ? R / 2 : R;
-  const int64_t tr = cdiv(oc, (mode == 1 + AQT_EPI_GLU ? 16 : 32) * TN * WN), tm = cdiv(M, 32 * TM * WM);
-  if (tr * tm > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
-  const bool lng = C > int64_t(kChain) * WK;
-#define AQT_PICK(MODE) (lng ? f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, true> \
-                            : f32_codes_any_kernel<TM, TN, WM, WN, WK, PACKED, MODE, false>)
-  auto kern = mode == 1 + AQT_EPI_NONE    ? AQT_PICK(1 + AQT_EPI_NONE)
-              : mode == 1 + AQT_EPI_SWISH ? AQT_PICK(1 + AQT_EPI_SWISH)
-              : mode == 1 + AQT_EPI_GLU   ? AQT_PICK((TN % 2 ? 1 + AQT_EPI_NONE : 1 + AQT_EPI_GLU))
-                                          : AQT_PICK((PACKED ? 1 + AQT_EPI_NONE : 0));   // dX codes are never packed
-#undef AQT_PICK
-  kern<<<static_cast<unsigned>(tr * tm), 64 * WM * WN * WK, 0, st>>>(f, scale, static_cast<const uint8_t *>(q), M, R, C, s_x,
-                                                                     mask_x, factor, bias, out, static_cast<int>(tr));
+template <int TN, bool PACKED, int MODE, bool LONG>
+aqt_status f32_codes_any(const CodesArgs &a, hipStream_t st) {
+  const int64_t tr = a.R / (32 * TN), tm = cdiv(a.M, 32);
+  f32_codes_any_kernel<TN, PACKED, MODE, LONG><<<static_cast<unsigned>(tr * tm), 512, 0, st>>>(
+      a.f, a.scale, static_cast<const uint8_t *>(a.q), a.M, a.R, a.C, a.s_x, a.mask_x, a.factor, a.bias, a.out, static_cast<int>(tr));
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }
 
-template <bool PACKED>
-aqt_status f32_codes_any_sized(int mode, const float *f, const float *scale, const void *q, int64_t M, int64_t R, int64_t C,
-                               const float *s_x, const uint32_t *mask_x, const float *factor, const float *bias, float *out,
-                               hipStream_t st) {
-  const bool glu = mode == 1 + AQT_EPI_GLU;
-  Tile tile = pick_tile(M, R, C, glu, false);
-  // the float64 sums of long contractions need registers the larger tile does not leave
-  if (tile == Tile::kSmall && C > 8 * kChain && !glu) tile = Tile::kSmallest;
-  switch (tile) {
-    case Tile::kLarge: return f32_codes_any<1, 2, 4, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-    case Tile::kRows:
-      if (!glu) return f32_codes_any<1, 1, 2, 4, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-      return f32_codes_any<1, 2, 2, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-    case Tile::kNarrow:
-      if (!glu) return f32_codes_any<1, 1, 4, 2, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-      return f32_codes_any<1, 2, 4, 1, 1, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-    case Tile::kSmallest: return f32_codes_any<1, 1, 1, 1, 8, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
-    default: return f32_codes_any<1, 2, 1, 1, 8, PACKED>(mode, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, st);
+// Tiles of 32 x 64 halve the conversions of the float operand where there are enough of them; the float64 sums of long
+// contractions need registers they do not leave.  (us: dX 3200 x 512 -> 128, 50 tiles of 64 x 128, 14.1 as such, 6.9 split.)
+template <bool PACKED, int MODE>
+aqt_status f32_codes_any_sized(const CodesArgs &a, hipStream_t st) {
+  const bool lng = a.C > 8 * kChain;
+  if constexpr (MODE == 1 + AQT_EPI_GLU) {
+    return lng ? f32_codes_any<2, PACKED, MODE, true>(a, st) : f32_codes_any<2, PACKED, MODE, false>(a, st);
+  } else {
+    if (lng) return f32_codes_any<1, PACKED, MODE, true>(a, st);
+    return cdiv(a.M, 32) * (a.R / 64) >= 128 ? f32_codes_any<2, PACKED, MODE, false>(a, st) : f32_codes_any<1, PACKED, MODE, false>(a, st);
   }
+}
+
+template <bool PACKED>
+aqt_status wonly_any(const CodesArgs &a, int epilogue, hipStream_t st) {
+  return epilogue == AQT_EPI_NONE    ? f32_codes_any_sized<PACKED, 1 + AQT_EPI_NONE>(a, st)
+         : epilogue == AQT_EPI_SWISH ? f32_codes_any_sized<PACKED, 1 + AQT_EPI_SWISH>(a, st)
+                                     : f32_codes_any_sized<PACKED, 1 + AQT_EPI_GLU>(a, st);
 }
 
 }  // namespace
@@ -964,42 +725,31 @@ aqt_status launch_dense_fwd_any(const int8_t *xq, const float *s_x, const void *
 
 aqt_status launch_bwd_dx_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
                              const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st) {
-  return f32_codes_any_sized<false>(0, dy, s_w, wq_kn, M, K, N, s_x, mask_x, factor, nullptr, dx, st);
+  return f32_codes_any_sized<false, 0>(CodesArgs{dy, s_w, wq_kn, M, K, N, s_x, mask_x, factor, nullptr, dx}, st);
 }
 
 aqt_status launch_dense_fwd_wonly_any(const float *x, const void *wq_packed, const float *s_w, int64_t M, int64_t K,
                                       int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st) {
-  return packed4(bits_w)
-             ? f32_codes_any_sized<true>(1 + epilogue, x, s_w, wq_packed, M, N, K, nullptr, nullptr, nullptr, bias, y, st)
-             : f32_codes_any_sized<false>(1 + epilogue, x, s_w, wq_packed, M, N, K, nullptr, nullptr, nullptr, bias, y, st);
+  const CodesArgs a{x, s_w, wq_packed, M, N, K, nullptr, nullptr, nullptr, bias, y};
+  return packed4(bits_w) ? wonly_any<true>(a, epilogue, st) : wonly_any<false>(a, epilogue, st);
 }
 
-// Slabs of at most kChain rows, so that a float32 sum is never longer, as long as their partial results stay under
-// 64 MiB; shorter slabs while the launch does not fill the chip, of at least 64 rows each.
+// Slabs of at most kChain rows, so that a float32 sum is never longer; shorter slabs while the launch does not fill the
+// chip, of at least 64 rows each.
 int dw_any_slabs(int64_t M, int64_t K, int64_t N) {
-  const int64_t tiles = cdiv(K, kDwTile) * cdiv(N, kDwTile);
-  int64_t slabs = cdiv(M, kChain);
-  const int64_t fill = cdiv(512, tiles), most = cdiv(M, 64);
-  if (slabs < fill) slabs = fill < most ? fill : most;
-  const int64_t room = (int64_t(64) << 20) / (K * N * 4) + 1;
-  if (slabs > room) slabs = room;
-  while (slabs > 1 && slabs * tiles > 0x7FFFFFFF) slabs /= 2;
-  return static_cast<int>(slabs);
+  const int64_t slabs = cdiv(M, kChain), fill = cdiv(512, (K / kDwTile) * (N / kDwTile)), most = cdiv(M, 64);
+  return static_cast<int>(slabs >= fill ? slabs : fill < most ? fill : most);
 }
 
 aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
-                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, int max_slabs, float *dbias,
-                             double *bias_part, hipStream_t st) {
-  const int64_t tiles_n = cdiv(N, kDwTile), tiles = cdiv(K, kDwTile) * tiles_n;
-  int64_t slabs = dw_any_slabs(M, K, N);
-  if (slabs > max_slabs) slabs = max_slabs;
-  const int64_t rows = cdiv(cdiv(M, slabs), kSlice) * kSlice;
-  slabs = cdiv(M, rows);
+                             int64_t M, int64_t K, int64_t N, float *dw, float *partial, float *dbias, double *bias_part,
+                             hipStream_t st) {
+  const int64_t tiles_n = N / kDwTile, tiles = (K / kDwTile) * tiles_n;
+  const int64_t rows = cdiv(cdiv(M, dw_any_slabs(M, K, N)), kSlice) * kSlice, slabs = cdiv(M, rows);
   if (tiles * slabs > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
   const DwFinish fin{s_x, s_w, mask_w};
   const bool one = slabs == 1;
-  auto kern = K < (1 << 24) && N < (1 << 24) ? bwd_dw_any_kernel<uint32_t> : bwd_dw_any_kernel<int64_t>;
-  kern<<<static_cast<unsigned>(tiles * slabs), kDwThreads, 0, st>>>(
+  bwd_dw_any_kernel<<<static_cast<unsigned>(tiles * slabs), kDwThreads, 0, st>>>(
       xq, dy, M, K, N, rows, one ? dw : partial, static_cast<int>(tiles_n), static_cast<int>(tiles), one ? 1 : 0, fin,
       dbias ? bias_part : nullptr);
   AQT_HIP(hipGetLastError());

@@ -840,7 +840,8 @@ __global__ __launch_bounds__(kThreads) void bwd_dw_fold_kernel(const float *__re
 }
 
 struct BwdPlan {
-  bool dx_mfma, dw_mfma;
+  bool dx_grid, dw_grid;   // on the tuned kernels' grid: float32 sums; off it gemm_any_f64.hip
+  bool dx_mfma, dw_mfma;   // and large enough for the tuned tiles; else gemm_any.hip
   bool dx_wide;    // 128 x 256 tiles (else 128 x 128)
   bool dx_wide8;   // 128 x 512 tiles, eight wavefronts: the gradient tile is staged once for four column wavefronts
   bool dw_wide8;   // dW on 256 x 256 tiles, eight wavefronts
@@ -853,9 +854,10 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   BwdPlan p{};
   const bool fits32 = M < (int64_t(1) << 31) / (K > N ? K : N);
   // dX: columns are K, contraction N in stages of 32; row tiles of 128 (the last one may be shifted)
+  p.dx_grid = fits32 && (N % kSN == 0) && (K % 128 == 0) && (M >= 128);
   // (up to 64 such tiles the split contraction of gemm_any.hip is faster, for all its three passes: with the
   // re-ordering of the codes 20 us against 9 at 1024 x 1024 -> 256, 39 against 30 at 2048 x 2048 -> 512)
-  p.dx_mfma = fits32 && (N % kSN == 0) && (K % 128 == 0) && (M >= 128) && cdiv(M, 128) * (K / 128) > 64;
+  p.dx_mfma = p.dx_grid && cdiv(M, 128) * (K / 128) > 64;
   p.dx_wide = (K % 256 == 0) && cdiv(M, 128) * (K / 256) >= 512;
   p.dx_wide8 = p.dx_wide && (K % 512 == 0) && cdiv(M, 128) * (K / 512) >= 256;
   // dW: 256 x 256 tiles (eight wavefronts, one workgroup per compute unit) when N allows, else 256 x 128
@@ -863,7 +865,8 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   // (below about 4e9 multiply-adds the smaller tiles of gemm_any.hip win although they take three passes: few large tiles
   // mean many slabs, and their partial results cost more than the products: 12800 x 512 x 512 43 us against 36,
   // 1024 x 256 x 1024 32 against 20; 4096 x 512 x 2048 41 against 43)
-  p.dw_mfma = fits32 && (K % 256 == 0) && (N % 128 == 0) && M >= 4000000000ll / (K * N);
+  p.dw_grid = fits32 && (K % 256 == 0) && (N % 128 == 0) && K < (1 << 24) && N < (1 << 24);
+  p.dw_mfma = p.dw_grid && M >= 4000000000ll / (K * N);
   p.dw_wide8 = p.dw_mfma && (N % 256 == 0);
   const int64_t tiles = p.dw_mfma ? (K / 256) * (N / (p.dw_wide8 ? 256 : 128)) : 1;
   int64_t slabs = p.dw_mfma ? cdiv(p.dw_wide8 ? 256 : 512, tiles) : 1;
@@ -871,16 +874,16 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   int64_t per = cdiv(M, slabs);
   per = cdiv(per, 32) * 32;            // whole stages
   slabs = cdiv(M, per);
-  if (per * (K > N ? K : N) >= (int64_t(1) << 30)) p.dw_mfma = false;   // 32-bit byte offsets inside a slab
+  if (p.dw_mfma && per * (K > N ? K : N) >= (int64_t(1) << 30)) p.dw_mfma = p.dw_grid = false;   // 32-bit byte offsets inside a slab
   p.slabs = static_cast<int>(slabs);
   p.m_per_slab = static_cast<int>(per);
-  if (!p.dw_mfma) p.slabs = dw_any_slabs(M, K, N);
-  // one row of column sums per slab and row tile (of at least 128 positions), or per row slab without a dW
-  size_t bias_rows = static_cast<size_t>(p.slabs) * cdiv(K, 128);
+  if (!p.dw_mfma) p.slabs = p.dw_grid ? dw_any_slabs(M, K, N) : dw_f64_slabs(M, K, N);
+  // one row of column sums per slab and row tile (of at least 128 positions, 64 off the grid), or per row slab without a dW
+  size_t bias_rows = static_cast<size_t>(p.slabs) * cdiv(K, p.dw_grid ? 128 : 64);
   if (bias_rows < kBiasSlabs) bias_rows = kBiasSlabs;
   size_t off = 0;
   p.off_bf = off;   off += align_up(static_cast<size_t>(K) * N * 2, 256);
-  p.off_part = off; off += align_up(static_cast<size_t>(p.slabs) * K * N * 4, 256);
+  p.off_part = off; off += align_up(static_cast<size_t>(p.slabs) * K * N * (p.dw_grid ? 4 : 8), 256);
   p.off_bias = off; off += align_up(bias_rows * N * sizeof(double), 256);
   p.total = off;
   return p;
@@ -948,7 +951,8 @@ aqt_status launch_dense_fwd_wonly(const float *x, const void *wq_packed, const f
   const int64_t nn = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
   const int64_t unit = (epilogue == AQT_EPI_GLU) ? 64 : 128;
   // up to 64 tiles of 128 x 128: gemm_any.hip (1024 x 1024 -> 256 9 us against 19; 2048 x 2048 -> 512 29 against 36)
-  if (fits32 && aligned && M >= 128 && K % kSN == 0 && nn % unit == 0 && cdiv(M, 128) * cdiv(N, 128) > 64) {
+  const bool grid = fits32 && aligned && M >= 128 && K % kSN == 0 && nn % unit == 0;
+  if (grid && cdiv(M, 128) * cdiv(N, 128) > 64) {
     v4i *frag = static_cast<v4i *>(ws);
     const int64_t pieces = N * (K / 8);
     int g = static_cast<int>(cdiv(pieces, kThreads));
@@ -962,7 +966,7 @@ aqt_status launch_dense_fwd_wonly(const float *x, const void *wq_packed, const f
     if (wide) return launch_wonly<2, 4>(x, frag, s_w, bias, epilogue, M, K, N, y, st);
     return launch_wonly<2, 2>(x, frag, s_w, bias, epilogue, M, K, N, y, st);
   }
-  return launch_dense_fwd_wonly_any(x, wq_packed, s_w, M, K, N, bits_w, bias, epilogue, y, st);
+  return (grid ? launch_dense_fwd_wonly_any : launch_dense_fwd_wonly_f64)(x, wq_packed, s_w, M, K, N, bits_w, bias, epilogue, y, st);
 }
 
 size_t bwd_workspace_bytes(int64_t M, int64_t K, int64_t N) { return plan_bwd(M, K, N).total; }
@@ -977,8 +981,9 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
   // offsets are multiples of 256); anything else takes the general kernels
   const bool dy_aligned = reinterpret_cast<uintptr_t>(dy) % 16 == 0 && reinterpret_cast<uintptr_t>(ws) % 16 == 0;
   if (dx) {
-    if (p.dx_mfma && dy_aligned && reinterpret_cast<uintptr_t>(sv->s_w) % 16 == 0 &&
-        reinterpret_cast<uintptr_t>(sv->wq_kn) % 8 == 0) {
+    const bool grid = p.dx_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->s_w) % 16 == 0 &&
+                      reinterpret_cast<uintptr_t>(sv->wq_kn) % 8 == 0;
+    if (grid && p.dx_mfma) {
       v4i *wq_frag = reinterpret_cast<v4i *>(base + p.off_bf);
       const int64_t pieces = K * (N / 8);
       int g = static_cast<int>(cdiv(pieces, kThreads));
@@ -992,14 +997,16 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
       else AQT_TRY((launch_dx<2, 2>(dy, wq_frag, sv, M, K, N, dx, st, fused)));
       if (dx_factor && !fused) AQT_TRY(launch_dact_mul(dx, dx_factor, M, K, K, dx, st));
     } else {
-      AQT_TRY(launch_bwd_dx_any(dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, dx_factor, M, K, N, dx, st));
+      auto launch = grid ? launch_bwd_dx_any : launch_bwd_dx_f64;
+      AQT_TRY(launch(dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, dx_factor, M, K, N, dx, st));
     }
   }
   double *bias_part = reinterpret_cast<double *>(base + p.off_bias);
   if (dw) {   // with the bias gradient, where it is wanted as well
-    if (p.dw_mfma && dy_aligned && reinterpret_cast<uintptr_t>(sv->xq) % 4 == 0 &&
-        reinterpret_cast<uintptr_t>(dw) % 16 == 0) {
-      float *partial = reinterpret_cast<float *>(base + p.off_part);
+    const bool grid = p.dw_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->xq) % 4 == 0 &&
+                      reinterpret_cast<uintptr_t>(dw) % 16 == 0;
+    float *partial = reinterpret_cast<float *>(base + p.off_part);
+    if (grid && p.dw_mfma) {
       if (p.dw_wide8) AQT_TRY((launch_dw<4, 2, 4>(dy, sv, M, K, N, p, partial, dbias ? bias_part : nullptr, st)));
       else AQT_TRY((launch_dw<4, 2, 2>(dy, sv, M, K, N, p, partial, dbias ? bias_part : nullptr, st)));
       const BiasFold fold{bias_part, dbias, static_cast<int>(p.slabs * (K / 256)),
@@ -1007,9 +1014,12 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
       bwd_dw_fold_kernel<<<static_cast<int>(cdiv(K * N / 4, kThreads)) + fold.blocks, kThreads, 0, st>>>(
           partial, p.slabs, K * N, N, sv->s_x, sv->s_w, sv->mask_w, dw, fold);
       AQT_HIP(hipGetLastError());
-    } else {
-      AQT_TRY(launch_bwd_dw_any(dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw,
-                                reinterpret_cast<float *>(base + p.off_part), p.slabs, dbias, bias_part, st));
+    } else if (grid) {
+      AQT_TRY(launch_bwd_dw_any(dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw, partial, dbias, bias_part, st));
+    } else {   // where only a tensor's alignment is off the grid, as many slabs of doubles as fit in place of the floats
+      const int slabs = p.dw_grid ? (p.slabs > 1 ? p.slabs / 2 : 1) : p.slabs;
+      AQT_TRY(launch_bwd_dw_f64(dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw, reinterpret_cast<double *>(partial), slabs,
+                                dbias, bias_part, st));
     }
   }
   if (dbias && !dw) {

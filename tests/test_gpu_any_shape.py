@@ -101,3 +101,80 @@ def test_bias_gradient_rides_on_dw(M, K, N):
     for want_dw in (True, False):
         _, _, db = B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, want_dw=want_dw, want_dbias=True)
         assert bool(((db.double() - ref).abs() <= bound).all()), (want_dw, float(((db.double() - ref).abs() - bound).max()))
+
+
+def rounded_once(got, ref, terms, mag):
+    """A float64 sum of `terms` products, rounded to float32 once: half a unit in the last place (2^-24 of the value; 2^-150
+    below the normal range), and what the float64 additions themselves may lose of the magnitudes."""
+    import torch
+    bound = 2.0 ** -24 * (1 + 2.0 ** -20) * ref.abs() + 2.0 ** -149 + terms * 2.0 ** -53 * mag
+    fine = torch.where(torch.isfinite(ref), (got.double() - ref).abs() <= bound, (got.double() == ref) | (got.isnan() & ref.isnan()))
+    assert bool(fine.all()), (int((~fine).sum()), fine.numel())
+
+
+def float64_products(M, K, N, moved=False, wild=False):
+    """dX, dW and the weight-only forward of one layer with their float64 values; moved: tensors that are 4-byte aligned only."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(M + 3 * K + N)
+
+    def put(t):
+        if not moved:
+            return t
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        buf[1:].copy_(t.reshape(-1))
+        return buf[1:].view(t.shape)
+
+    x, w = torch.randn((M, K), device="cuda", generator=gen), torch.randn((K, N), device="cuda", generator=gen)
+    dy, xf = torch.randn((M, N), device="cuda", generator=gen) + 0.2, torch.randn((M, K), device="cuda", generator=gen) + 0.2
+    sv = B.Saved(M, K, N, 8)
+    B.aqt_dense_fwd(x, w, 8, 8, saved=sv)
+    if wild:   # infinities, the largest finite value, products and sums that float32 cannot hold but the result can
+        for t in (dy, xf):
+            t[0, 0], t[M // 2, 1], t[M - 1, 2] = float("inf"), 3.4028234e38, float("-inf")
+            t[M // 3, 3:5] = torch.tensor([3.0e38, -3.0e38], device="cuda")
+            t[1, :] = 1e-41
+    dy, xf = put(dy), put(xf)
+    dx, dw, _ = B.aqt_dense_bwd(dy, sv, 8, 8)
+    y = B.aqt_dense_fwd_wonly(xf, sv.wq_packed, sv.s_w, N, 8)
+    dys, q, xq = (dy * sv.s_w).double(), sv.wq_kn.double(), sv.xq.double()
+    sx, sw = sv.s_x.double(), sv.s_w.double()
+    return dict(dx=(dx, dys @ q.t().contiguous(), N, dys.abs() @ q.abs().t().contiguous()),
+                dw=(dw, sx * (xq.t().contiguous() @ dy.double()), M, sx * (xq.abs().t().contiguous() @ dy.double().abs())),
+                y=(y, (xf.double() @ q) * sw, K, (xf.double().abs() @ q.abs()) * sw))
+
+
+@pytest.mark.parametrize("M,K,N,off", [
+    (4099, 520, 1000, "dx dw y"), (2051, 1002, 1000, "dx dw y"), (300, 2040, 1030, "dx dw y"), (40, 512, 2048, "dx y"),
+    (20000, 384, 1536, "dw"),          # a fan-in that the tuned dW's tiles do not divide, several slabs
+    (2000, 1100, 4300, "dx dw y"),     # many tiles, one slab
+    (33, 130, 3, "dx dw y"), (1, 1, 1, "dx dw y"), (70, 2, 65, "dx dw y"), (65, 63, 64, "dx dw y")])
+def test_off_the_grid_sums_are_float64(M, K, N, off):
+    """Shapes that the tuned kernels do not divide: the float64 sum, rounded to float32 once."""
+    print("[float64 sums]", M, K, N, flush=True)
+    for what, (got, ref, terms, mag) in float64_products(M, K, N).items():
+        if what in off.split():
+            rounded_once(got, ref, terms, mag)
+
+
+def test_off_the_grid_by_alignment():
+    """Sizes of the tuned kernels' grid on tensors that are not 16-byte aligned: float64 sums as well."""
+    for M, K, N in ((512, 256, 256), (20000, 512, 512)):
+        print("[float64 sums, 4-byte aligned]", M, K, N, flush=True)
+        for got, ref, terms, mag in float64_products(M, K, N, moved=True).values():
+            rounded_once(got, ref, terms, mag)
+
+
+@pytest.mark.parametrize("M,K,N", [(300, 131, 77), (40, 512, 128)])
+def test_off_the_grid_infinite_and_huge_values(M, K, N):
+    """Infinities, the largest finite value and intermediate results beyond float32 come out as a float64 loop has them."""
+    print("[float64 sums, wild values]", M, K, N, flush=True)
+    for what, (got, ref, terms, mag) in float64_products(M, K, N, wild=True).items():
+        if what == "dw" and K % 256 == 0:
+            continue
+        ref32 = ref.float().double()   # a float64 result beyond float32 is an infinity
+        rounded_once(got, torch_where_finite(ref32, ref), terms, mag.nan_to_num(0.0, 0.0, 0.0))
+
+
+def torch_where_finite(ref32, ref):
+    import torch
+    return torch.where(torch.isfinite(ref32), ref, ref32)
