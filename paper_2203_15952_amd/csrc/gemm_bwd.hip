@@ -878,8 +878,10 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   p.slabs = static_cast<int>(slabs);
   p.m_per_slab = static_cast<int>(per);
   if (!p.dw_mfma) p.slabs = p.dw_grid ? dw_any_slabs(M, K, N) : dw_f64_slabs(M, K, N);
-  // one row of column sums per slab and row tile (of at least 128 positions, 64 off the grid), or per row slab without a dW
+  // one row of column sums per slab and row tile (of at least 128 positions, 64 off the grid), or per row slab without a dW;
+  // a tensor's alignment alone takes a dW off the grid too, with half the slabs, but at least one
   size_t bias_rows = static_cast<size_t>(p.slabs) * cdiv(K, p.dw_grid ? 128 : 64);
+  if (bias_rows < static_cast<size_t>(cdiv(K, 64))) bias_rows = cdiv(K, 64);
   if (bias_rows < kBiasSlabs) bias_rows = kBiasSlabs;
   size_t off = 0;
   p.off_bf = off;   off += align_up(static_cast<size_t>(K) * N * 2, 256);

@@ -61,6 +61,14 @@ def test_workspace_sizes_are_shape_functions(L):
     assert B.aqt_workspace_bytes(B.AQT_OP_DENSE_FWD, 0, 512, 2048, 8, 4) == 0
 
 
+@pytest.mark.parametrize("M,K,N", [(256, 8192, 2048), (100, 16384, 1024), (70, 8192, 8192)])
+def test_backward_workspace_holds_a_single_slabs_bias_rows(L, M, K, N):
+    """One slab of rows: the float64 kernel (tensors that are not 16-byte aligned) leaves a row of N doubles per 64
+    fan-in positions behind the re-ordered codes and the partial sums."""
+    need = 2 * K * N + 4 * K * N + K // 64 * N * 8
+    assert B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, M, K, N) >= need
+
+
 def test_argument_errors_are_synchronous_and_touch_no_gpu(L):
     one = ctypes.c_void_p(256)   # never dereferenced: every call below must fail its checks first
     none = None

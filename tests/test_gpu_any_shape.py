@@ -103,6 +103,27 @@ def test_bias_gradient_rides_on_dw(M, K, N):
         assert bool(((db.double() - ref).abs() <= bound).all()), (want_dw, float(((db.double() - ref).abs() - bound).max()))
 
 
+def test_unaligned_single_slab_stays_in_its_workspace():
+    """A fan-in on the tuned grid so wide that its row tiles outnumber the rows reserved at least, on a gradient that is
+    4-byte aligned only: nothing behind the workspace is written, and the sums are right."""
+    import torch
+    M, K, N = 128, 8192, 2048
+    print("[bias gradient, unaligned, one slab]", M, K, N, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x, w = torch.randn((M, K), device="cuda", generator=gen), torch.randn((K, N), device="cuda", generator=gen)
+    dy = torch.randn(M * N + 1, device="cuda", generator=gen)[1:].view(M, N)
+    sv = B.Saved(M, K, N, 8)
+    B.aqt_dense_fwd(x, w, 8, 8, saved=sv)
+    need = B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, M, K, N)
+    ws = torch.full((need + (4 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    _, dw, db = B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, want_dbias=True, ws=ws[:need])
+    assert bool((ws[need:] == 0x5A).all())
+    ref = dy.double().sum(0)
+    assert bool(((db.double() - ref).abs() <= 2.0 ** -24 * ref.abs() * 1.0001 + M * 2.0 ** -53 * dy.double().abs().sum(0)).all())
+    xq = sv.xq.double().t().contiguous()
+    rounded_once(dw, sv.s_x.double() * (xq @ dy.double()), M, sv.s_x.double() * (xq.abs() @ dy.double().abs()))
+
+
 def rounded_once(got, ref, terms, mag):
     """A float64 sum of `terms` products, rounded to float32 once: half a unit in the last place (2^-24 of the value; 2^-150
     below the normal range), and what the float64 additions themselves may lose of the magnitudes."""
