@@ -1,23 +1,27 @@
 // Backward of the float attention core for heads of a multiple of four positions on 16-byte aligned tensors (the chain rule
-// and the two kernels of attention.hip) on the bf16 matrix cores, without giving up float32: every operand is carried whole
+// and the two kernels of attention.hip).  The scores are formed as in the forward, on the float32 matrix cores with the same
+// products in the same order, so that a probability exp2(score - lse) is the one the forward's normaliser was made of:
+// a score that differs in its last bits, even for the better, leaves rows that do not add up to one, an error that grows with
+// the scores (normal queries and keys, heads of 64, 512 frames, times eight: dv off by 3.0e-5 of its norm, 4.3e-6 so).
+// The other products run on the bf16 matrix cores without giving up float32: every operand is carried whole
 // as three bf16 terms of 8 significant bits each (a = hi + mid + lo exactly), and a product is six
-// v_mfma_f32_32x32x16_bf16 passes, hi hi, hi mid, mid hi, mid mid, hi lo, lo hi; what is left out is below 2^-25 of a
-// product, under the rounding of the float32 sum itself (64-term dot products measured against float64: rms
-// error 1.8e-8 of the sum of magnitudes, 2.4e-8 with v_mfma_f32_32x32x2_f32).  Six bf16 passes take 6/16 of the float32
-// instruction's time, so the matrix work shrinks 2.7-fold; the splitting is vector work, done once per workgroup
-// for the staged rows, and runs under the products of the other wavefronts.
+// v_mfma_f32_32x32x16_bf16 passes, hi hi, hi mid, mid hi, mid mid, hi lo, lo hi.  What is left out is at most 2^-24 (1 + 2^-10)
+// of a product, one rounding of it, and mostly far less: 64-term dot products measured against float64, rms error
+// 1.8e-8 of the sum of magnitudes, 2.4e-8 with v_mfma_f32_32x32x2_f32.  Six bf16 passes take 6/16 of the float32
+// instruction's time; the splitting is vector work, done once per workgroup for the staged rows.
 //
 // As in attention.hip all products are formed transposed, a lane owns one query (in the key / value gradient kernel:
 // one key) from start to end, and the probabilities go from the first products' accumulators into the last products'
-// B operand without leaving the lane.  Tiles of 32 rows go through LDS row-major, one 128-byte row per image, 16-byte
-// chunks XOR-swizzled with the row.  Operands that contract along the head are read as 16-byte row pieces; operands
+// B operand without leaving the lane.  Tiles of 32 rows go through LDS: split images row-major, one 128-byte row per image,
+// 16-byte chunks XOR-swizzled with the row, and the rows that scores are made of once more in float32, parity-major as in
+// attention.hip.  Operands that contract along the head are read as 16-byte row pieces; operands
 // that contract along the rows are read from the same image with ds_read_b64_tr_b16 (sixteen lanes read four rows of
 // sixteen columns, each lane receives one column), whose four-row groups are exactly the rows an accumulator lane
 // holds.  Two LDS slots: a tile is staged and split while the one before it is multiplied, one barrier per tile.
 //
-// Measured in us, float32 instructions before -> here: 32 utterances of 400 frames, 8 heads of 64: 621 -> 283; 128 of
-// 512: 2808 -> 1370; 24 of 417, 4 heads of 36: 310 -> 126.  The matrix cores are 40 % busy; the rest is the vector work
-// of the splits and the exponentials.
+// Measured in us, all products in float32 (attention.hip) -> scores in float32, the rest here: 32 utterances of 400 frames,
+// 8 heads of 64: 621 -> 311; 128 of 512: 2808 -> 1557; 24 of 417, 4 heads of 36: 310 -> 146.  (All products in bf16 passes:
+// 273, 1392 and 125, with the error above.)
 #include "attention_tiles.h"
 
 namespace aqt {
@@ -27,8 +31,8 @@ constexpr int kStep = 32;            // rows per staged tile
 constexpr int kRowBytes = 128;       // an LDS row: 64 bf16
 constexpr int kImage = kStep * kRowBytes;
 constexpr int kTensor = 3 * kImage;  // hi, mid, lo
-constexpr int kSlot = 2 * kTensor;   // two tensors per tile
-constexpr int kLd = 68;              // row stride in floats of the output image
+constexpr int kLd = 68;              // row stride in floats of the float32 rows and of the output image
+constexpr int kSlot = 2 * kTensor + kStep * kLd * 4;   // two tensors per tile, and the float32 rows of the first
 
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -109,8 +113,9 @@ __device__ __forceinline__ Raw load_piece(const float *__restrict__ src, int64_t
   return Raw{*reinterpret_cast<const v4f *>(p + d0), *reinterpret_cast<const v4f *>(p + d1)};
 }
 // ... split into the three images; zeros beyond the head and, where `rows` says so, beyond the utterance
+// (`floats`: the same rows in float32, even positions, then odd ones).
 template <int PIECES>
-__device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnShape &g, int row0, bool rows) {
+__device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnShape &g, int row0, bool rows, float *floats = nullptr) {
   const int piece = threadIdx.x & 7, row = static_cast<int>(threadIdx.x >> 3);
   const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
   if (8 * piece >= g.dh || (rows && row0 + row >= g.T)) v.a = zero;
@@ -121,18 +126,57 @@ __device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnSh
     *reinterpret_cast<v4i *>(p) = s.hi;
     *reinterpret_cast<v4i *>(p + kImage) = s.mid;
     *reinterpret_cast<v4i *>(p + 2 * kImage) = s.lo;
+    if (floats) {
+      *reinterpret_cast<v4f *>(floats + row * kLd + 4 * piece) = v4f{v.a.x, v.a.z, v.b.x, v.b.z};
+      *reinterpret_cast<v4f *>(floats + row * kLd + 32 + 4 * piece) = v4f{v.a.y, v.a.w, v.b.y, v.b.w};
+    }
   }
 }
 
-// A lane's own row as a B operand, straight from memory: positions 16 s + 8 lk .. + 7, times `mul`.
+// A lane's own row as a B operand of the scores: positions 2 i + lk.
+template <int KS>
+struct Own {
+  float v[8 * KS];
+};
+template <int KS>
+__device__ __forceinline__ Own<KS> own_floats(const float *row, int lk, int dh) {
+  Own<KS> q;
+#pragma unroll
+  for (int p = 0; p < 4 * KS; ++p) {
+    v4f x = *reinterpret_cast<const v4f *>(row + (4 * p < dh ? 4 * p : 0));
+    if (4 * p >= dh) x = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    q.v[2 * p] = lk ? x.y : x.x;
+    q.v[2 * p + 1] = lk ? x.w : x.z;
+  }
+  return q;
+}
+// ... as a split operand: positions 16 s + 8 lk .. + 7.
 __device__ __forceinline__ void load_own(v4f &x, v4f &y, const float *row, int s, int lk, int dh) {
   const int d = 16 * s + 8 * lk;
   const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
   x = d < dh ? *reinterpret_cast<const v4f *>(row + d) : zero;
   y = d + 4 < dh ? *reinterpret_cast<const v4f *>(row + d + 4) : zero;
 }
-__device__ __forceinline__ Split split_own(v4f x, v4f y, float mul) {
-  return split8(x.x * mul, x.y * mul, x.z * mul, x.w * mul, y.x * mul, y.y * mul, y.z * mul, y.w * mul);
+__device__ __forceinline__ Split split_own(v4f x, v4f y) { return split8(x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w); }
+
+// Scores (staged rows x own row, the forward's bits) and the second product of a tile, in one loop so that either's
+// chain of matrix instructions runs under the other's operand reads.
+template <int KS>
+__device__ __forceinline__ void first_products(const uint8_t *slot, const Own<KS> &own, const Split (&second)[KS], v16f &s, v16f &dp,
+                                               int lr, int lk) {
+  const float *const rows = reinterpret_cast<const float *>(slot + 2 * kTensor) + lr * kLd + lk * 32;
+  s = zero16();
+  dp = zero16();
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+#pragma unroll
+    for (int i4 = 2 * k; i4 < 2 * k + 2; ++i4) {
+      const v4f x = *reinterpret_cast<const v4f *>(rows + 4 * i4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], own.v[4 * i4 + e], s, 0, 0, 0);
+    }
+    dp = mfma6(read_rows(slot + kTensor, k, lr, lk), second[k], dp);
+  }
 }
 __device__ __forceinline__ float dot8(v4f a, v4f b, v4f c, v4f d) {
   return ((a.x * c.x + a.y * c.y) + (a.z * c.z + a.w * c.w)) + ((b.x * d.x + b.y * d.y) + (b.z * d.z + b.w * d.w));
@@ -140,7 +184,7 @@ __device__ __forceinline__ float dot8(v4f a, v4f b, v4f c, v4f d) {
 
 // a wavefront's transposed result (head positions x 32 rows) out through its own part of LDS as whole rows
 template <int DB>
-__device__ __forceinline__ uint32_t store_rows(float *img, const v16f (&acc)[DB], float mul, float *__restrict__ out, int64_t ld,
+__device__ __forceinline__ void store_rows(float *img, const v16f (&acc)[DB], float mul, float *__restrict__ out, int64_t ld,
                                                int rows_left, int dh, int lane) {
   const int lr = lane & 31, lk = lane >> 5;
 #pragma unroll
@@ -152,20 +196,13 @@ __device__ __forceinline__ uint32_t store_rows(float *img, const v16f (&acc)[DB]
     }
   __builtin_amdgcn_wave_barrier();
   // sixteen lanes per row, four rows at a time
-  uint32_t amax = 0u;
   const int d = 4 * (lane & 15);
 #pragma unroll
   for (int q4 = 0; q4 < 8; ++q4) {
     const int q = 4 * q4 + (lane >> 4);
-    if (q < rows_left && d < dh) {
-      const v4f v = *reinterpret_cast<const v4f *>(img + q * kLd + d);
-      *reinterpret_cast<v4f *>(out + q * ld + d) = v;
-      amax = max(max(amax, __float_as_uint(v.x) & 0x7FFFFFFFu), max(__float_as_uint(v.y) & 0x7FFFFFFFu,
-                 max(__float_as_uint(v.z) & 0x7FFFFFFFu, __float_as_uint(v.w) & 0x7FFFFFFFu)));
-    }
+    if (q < rows_left && d < dh) *reinterpret_cast<v4f *>(out + q * ld + d) = *reinterpret_cast<const v4f *>(img + q * kLd + d);
   }
   __builtin_amdgcn_wave_barrier();
-  return amax;
 }
 
 // The tile loop: rows first, first + 32, ... <= last, two tensors per tile; compute(slot, row0) between.
@@ -204,18 +241,18 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
   const int t0 = pl.r0;
   const int tw = t0 + wave * 32, t = tw + lr, tc = t < g.T ? t : g.T - 1;
   const bool active = tw < g.T;
-  Split q[KS], go[KS];
+  const float *const qrow = qkv + (b * g.T + tc) * 3 * g.D + hc, *const grow = dctx + (b * g.T + tc) * g.D + hc;
+  const Own<KS> q = own_floats<KS>(qrow, lk, g.dh);
+  Split go[KS];
   float D = 0.0f;
   {
-    const float *row = qkv + (b * g.T + tc) * 3 * g.D + hc, *grow = dctx + (b * g.T + tc) * g.D + hc, *orow = ctx + (b * g.T + tc) * g.D + hc;
+    const float *orow = ctx + (b * g.T + tc) * g.D + hc;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      v4f x, y, gx, gy, ox, oy;
-      load_own(x, y, row, s, lk, g.dh);
+      v4f gx, gy, ox, oy;
       load_own(gx, gy, grow, s, lk, g.dh);
       load_own(ox, oy, orow, s, lk, g.dh);
-      q[s] = split_own(x, y, g.scale_log2e);
-      go[s] = split_own(gx, gy, 1.0f);
+      go[s] = split_own(gx, gy);
       D += dot8(gx, gy, ox, oy);
     }
   }
@@ -239,22 +276,18 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
     vr = load_piece(qkv, 3 * g.D, g, b, j0, 2 * g.D + hc);
   };
   auto stage = [&](uint8_t *slot, int j0) {
-    stage_piece<4 * DB>(slot, kr, g, j0, true);
+    stage_piece<4 * DB>(slot, kr, g, j0, true, reinterpret_cast<float *>(slot + 2 * kTensor));
     stage_piece<2 * KS>(slot + kTensor, vr, g, j0, false);
   };
   auto compute = [&](const uint8_t *slot, int j0) {
     if (!active || j0 > some_hi || j0 + kStep - 1 < some_lo) return;
-    v16f s = zero16(), dp = zero16();
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      s = mfma6(read_rows(slot, k, lr, lk), q[k], s);              // S^T: keys x this lane's query
-      dp = mfma6(read_rows(slot + kTensor, k, lr, lk), go[k], dp);   // dP^T
-    }
+    v16f s, dp;
+    first_products<KS>(slot, q, go, s, dp, lr, lk);   // S^T: keys x this lane's query; dP^T
     const bool whole = j0 >= all_lo && j0 + kStep - 1 <= all_hi;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = j0 + 8 * (r >> 2) + 4 * lk + (r & 3);
-      const float p = __builtin_amdgcn_exp2f(s[r] - L);
+      const float p = __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - L);
       s[r] = (whole || (j >= wlo && j <= whi)) ? p * (dp[r] - D) : 0.0f;
     }
 #pragma unroll
@@ -265,9 +298,9 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
     }
   };
   run_tiles(lds, jmin / kStep * kStep, jmax, load, stage, compute);
-  if (active)
-    store_rows<DB>(reinterpret_cast<float *>(lds) + wave * 32 * kLd, dq, g.scale, dqkv + (b * g.T + tw) * 3 * g.D + hc, 3 * g.D,
-                   g.T - tw, g.dh, lane);
+  if (!active) return;
+  float *const out = dqkv + (b * g.T + tw) * 3 * g.D + hc;
+  store_rows<DB>(reinterpret_cast<float *>(lds) + wave * 32 * kLd, dq, g.scale, out, 3 * g.D, g.T - tw, g.dh, lane);
 }
 
 // dk / dv: a lane owns a key, the tiles are queries and upstream gradient rows.
@@ -287,17 +320,14 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
   const int j0t = pl.r0;
   const int jw = j0t + wave * 32, j = jw + lr, jc = j < g.T ? j : g.T - 1;
   const bool active = jw < g.T;
-  Split kk[KS], vv[KS];
-  {
-    const float *row = qkv + (b * g.T + jc) * 3 * g.D + g.D + hc;
+  const float *const krow = qkv + (b * g.T + jc) * 3 * g.D + g.D + hc;
+  const Own<KS> kk = own_floats<KS>(krow, lk, g.dh);
+  Split vv[KS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      v4f x, y;
-      load_own(x, y, row, s, lk, g.dh);
-      kk[s] = split_own(x, y, g.scale_log2e);
-      load_own(x, y, row + g.D, s, lk, g.dh);
-      vv[s] = split_own(x, y, 1.0f);
-    }
+  for (int s = 0; s < KS; ++s) {
+    v4f x, y;
+    load_own(x, y, krow + g.D, s, lk, g.dh);
+    vv[s] = split_own(x, y);
   }
   // query frames that may look at a key of this workgroup / of this wavefront: t - left <= j <= t + right
   const int jlast = j0t + kQ - 1 < g.T ? j0t + kQ - 1 : g.T - 1;
@@ -325,7 +355,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
     Dr = dsum[(b * g.T + tt) * g.heads + pl.h];
   };
   auto stage = [&](uint8_t *slot, int t0) {
-    stage_piece<4 * DB>(slot, qr, g, t0, true);
+    stage_piece<4 * DB>(slot, qr, g, t0, true, reinterpret_cast<float *>(slot + 2 * kTensor));
     stage_piece<4 * DB>(slot + kTensor, gr, g, t0, true);
     if (threadIdx.x < kStep) {
       const int at = slot == lds ? 0 : 1;
@@ -336,12 +366,8 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
   auto compute = [&](const uint8_t *slot, int t0) {
     if (!active || t0 > some_hi || t0 + kStep - 1 < some_lo) return;
     const int at = slot == lds ? 0 : 1;
-    v16f s = zero16(), dp = zero16();
-#pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      s = mfma6(read_rows(slot, k, lr, lk), kk[k], s);              // S: queries x this lane's key
-      dp = mfma6(read_rows(slot + kTensor, k, lr, lk), vv[k], dp);   // dP
-    }
+    v16f s, dp;
+    first_products<KS>(slot, kk, vv, s, dp, lr, lk);   // S: queries x this lane's key; dP
     const bool whole = t0 >= all_lo && t0 + kStep - 1 <= all_hi && jw + 31 < g.T;
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
@@ -350,7 +376,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
       for (int e = 0; e < 4; ++e) {
         const int r = 4 * r4 + e;
         const int tt = t0 + 8 * r4 + 4 * lk + e;
-        const float x = __builtin_amdgcn_exp2f(s[r] - L4[e]);
+        const float x = __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - L4[e]);
         const float p = (whole || (j < g.T && tt >= qlo && tt <= qhi)) ? x : 0.0f;
         s[r] = p;
         dp[r] = p * (dp[r] - D4[e]);
@@ -367,12 +393,11 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
     }
   };
   run_tiles(lds, tmin / kStep * kStep, tmax, load, stage, compute);
-  if (active) {
-    float *const img = reinterpret_cast<float *>(lds) + wave * 32 * kLd;
-    float *const out = dqkv + (b * g.T + jw) * 3 * g.D + g.D + hc;
-    store_rows<DB>(img, dk, g.scale, out, 3 * g.D, g.T - jw, g.dh, lane);
-    store_rows<DB>(img, dv, 1.0f, out + g.D, 3 * g.D, g.T - jw, g.dh, lane);
-  }
+  if (!active) return;
+  float *const out = dqkv + (b * g.T + jw) * 3 * g.D + g.D + hc;
+  float *const img = reinterpret_cast<float *>(lds) + wave * 32 * kLd;
+  store_rows<DB>(img, dk, g.scale, out, 3 * g.D, g.T - jw, g.dh, lane);
+  store_rows<DB>(img, dv, 1.0f, out + g.D, 3 * g.D, g.T - jw, g.dh, lane);
 }
 
 }  // namespace

@@ -251,3 +251,30 @@ def test_attention_tile_edges(T, dh, left, right):
     odd.copy_(qkv_d)
     ctx_odd, _ = B.aqt_attention_fwd(odd, B_, T, heads, left=left, right=right)
     np.testing.assert_array_equal(host(ctx_odd), host(ctx))   # the forwards share every product and sum
+
+
+def moved(t):
+    """The same values 4-byte aligned only: the kernels for any layout take them."""
+    out = torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape)
+    return out.copy_(t)
+
+
+@pytest.mark.parametrize("dh", [16, 36, 64])
+def test_backward_uses_the_probabilities_of_the_forward(dh):
+    """Large scores: exp2(score - lse) repeats the forward's rounding, so what the two backwards make of one lse may differ by
+    the float32 rounding of dv's sum over T products, (T + 4) u of the magnitudes each, but not by the scores' own error,
+    which is 30 times that here."""
+    T, heads = 40, 4
+    D = heads * dh
+    rng = np.random.default_rng(680 + dh)
+    qkv = rng.standard_normal((2 * T, 3 * D)).astype(F)
+    qkv[:, :2 * D] *= 8
+    qkv_d, go = dev(qkv), dev(rng.standard_normal((2 * T, D)).astype(F))
+    lse = torch.empty((2 * T, heads), device="cuda")
+    ctx, _ = B.aqt_attention_fwd(qkv_d, 2, T, heads, lse=lse)
+
+    def dv(q, g):
+        return host(B.aqt_attention_bwd(q, ctx, g, lse, 2, T, heads))[:, 2 * D:].astype(np.float64)
+
+    mag = dv(moved(qkv_d), go.abs())
+    assert np.all(np.abs(dv(qkv_d, go) - dv(moved(qkv_d), go)) <= 2 * (T + 4) * U * mag * 1.001 + TINY)
