@@ -865,27 +865,39 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N) {
   // (below about 4e9 multiply-adds the smaller tiles of gemm_any.hip win although they take three passes: few large tiles
   // mean many slabs, and their partial results cost more than the products: 12800 x 512 x 512 43 us against 36,
   // 1024 x 256 x 1024 32 against 20; 4096 x 512 x 2048 41 against 43)
-  p.dw_grid = fits32 && (K % 256 == 0) && (N % 128 == 0) && K < (1 << 24) && N < (1 << 24);
-  p.dw_mfma = p.dw_grid && M >= 4000000000ll / (K * N);
+  const bool dw_widths = (K % 256 == 0) && (N % 128 == 0) && K < (1 << 24) && N < (1 << 24);
+  const int64_t large_m = 4000000000ll / (K * N);
+  p.dw_grid = fits32 && dw_widths;
+  const bool large = dw_widths && M >= large_m;
+  p.dw_mfma = p.dw_grid && large;
   p.dw_wide8 = p.dw_mfma && (N % 256 == 0);
-  const int64_t tiles = p.dw_mfma ? (K / 256) * (N / (p.dw_wide8 ? 256 : 128)) : 1;
-  int64_t slabs = p.dw_mfma ? cdiv(p.dw_wide8 ? 256 : 512, tiles) : 1;
-  if (slabs > 64) slabs = 64;
-  int64_t per = cdiv(M, slabs);
+  const int64_t tiles = large ? (K / 256) * (N / (N % 256 == 0 ? 256 : 128)) : 1;
+  int64_t most = large ? cdiv(N % 256 == 0 ? 256 : 512, tiles) : 1;   // slabs of a tuned launch
+  if (most > 64) most = 64;
+  int64_t per = cdiv(M, most);
   per = cdiv(per, 32) * 32;            // whole stages
-  slabs = cdiv(M, per);
   if (p.dw_mfma && per * (K > N ? K : N) >= (int64_t(1) << 30)) p.dw_mfma = p.dw_grid = false;   // 32-bit byte offsets inside a slab
-  p.slabs = static_cast<int>(slabs);
+  p.slabs = static_cast<int>(cdiv(M, per));
   p.m_per_slab = static_cast<int>(per);
   if (!p.dw_mfma) p.slabs = p.dw_grid ? dw_any_slabs(M, K, N) : dw_f64_slabs(M, K, N);
+  // A workspace for so many rows serves every smaller number: room for the slabs that gemm_any.hip takes up to large_m rows
+  // (128 at 256 x 256, against 64 from there on) and for a tuned launch's slabs before they are rounded to whole stages.
+  int64_t floats = p.dw_grid ? p.slabs : 0;
+  const int64_t doubles = p.dw_grid ? 0 : p.slabs;
+  if (large) {
+    if (floats < most) floats = most;
+    if (large_m > 1 && floats < dw_any_slabs(large_m - 1, K, N)) floats = dw_any_slabs(large_m - 1, K, N);
+  }
+  const size_t slab_bytes = static_cast<size_t>(floats > 2 * doubles ? floats : 2 * doubles) * K * N * 4;
   // one row of column sums per slab and row tile (of at least 128 positions, 64 off the grid), or per row slab without a dW;
   // a tensor's alignment alone takes a dW off the grid too, with half the slabs, but at least one
-  size_t bias_rows = static_cast<size_t>(p.slabs) * cdiv(K, p.dw_grid ? 128 : 64);
+  size_t bias_rows = static_cast<size_t>(floats) * cdiv(K, 128);
+  if (bias_rows < static_cast<size_t>(doubles) * cdiv(K, 64)) bias_rows = static_cast<size_t>(doubles) * cdiv(K, 64);
   if (bias_rows < static_cast<size_t>(cdiv(K, 64))) bias_rows = cdiv(K, 64);
   if (bias_rows < kBiasSlabs) bias_rows = kBiasSlabs;
   size_t off = 0;
   p.off_bf = off;   off += align_up(static_cast<size_t>(K) * N * 2, 256);
-  p.off_part = off; off += align_up(static_cast<size_t>(p.slabs) * K * N * (p.dw_grid ? 4 : 8), 256);
+  p.off_part = off; off += align_up(slab_bytes, 256);
   p.off_bias = off; off += align_up(bias_rows * N * sizeof(double), 256);
   p.total = off;
   return p;

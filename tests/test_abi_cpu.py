@@ -69,6 +69,26 @@ def test_backward_workspace_holds_a_single_slabs_bias_rows(L, M, K, N):
     assert B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, M, K, N) >= need
 
 
+@pytest.mark.parametrize("K,N", [(256, 256), (256, 128), (512, 512), (512, 2048), (2048, 512), (256, 1 << 19), (520, 1000), (17, 129),
+                                 (8192, 8192), (65536, 65536)])
+def test_backward_workspace_serves_every_smaller_number_of_rows(L, K, N):
+    """Sized for the longest batch, a workspace is enough for the shorter ones, across every line between kernels (few and
+    many multiply-adds, 32-bit offsets) and whatever the rounding to whole stages."""
+    step = 4000000000 // (K * N)
+    rows = {1, 127, 128, (1 << 31) // max(K, N), (1 << 30) // max(K, N), 65536, 1 << 20}
+    rows |= {m + d for m in (step, 64 * ((1 << 30) // max(K, N))) for d in range(-40, 41)}
+    rows |= set(range(1, 4200, 13)) | set(range(4000, 140000, 997))
+    rows = [m for m in sorted(rows) if m > 0]
+    sizes = [B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, m, K, N) for m in rows]
+    assert min(sizes) > 0 and all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+@pytest.mark.parametrize("D,H", [(512, 2048), (144, 576), (256, 1024)])
+def test_layer_backward_workspace_serves_every_smaller_number_of_rows(L, D, H):
+    sizes = [B.aqt_workspace_bytes(B.AQT_OP_CONFORMER_LAYER_BWD, m, D, H, 8, 8) for m in sorted(set(range(8, 66000, 41)) | {4096, 4099})]
+    assert min(sizes) > 0 and all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_argument_errors_are_synchronous_and_touch_no_gpu(L):
     one = ctypes.c_void_p(256)   # never dereferenced: every call below must fail its checks first
     none = None
