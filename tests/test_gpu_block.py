@@ -115,6 +115,18 @@ def test_layernorm_quantize(M, D, affine, bits):
 # ----------------------------------------------------------------------------
 # the float32-emulated product against the native integer product (Sec. 1)
 # ----------------------------------------------------------------------------
+@pytest.mark.parametrize("M,D", [(300, 512), (70, 144), (33, 1000), (20, 2048)])
+def test_layernorm_of_affine_vectors_off_a_16_byte_boundary(M, D):
+    """Gamma and beta may lie on any float boundary: same rows, same order of every sum, same bits."""
+    say("layernorm, gamma and beta 4-byte aligned", M, D)
+    rng = np.random.default_rng(330 + D)
+    x, gamma, beta = (dev(rng.standard_normal(s).astype(F)) for s in ((M, D), (D,), (D,)))
+    q, s, y, st = B.aqt_layernorm_quantize(x, 8, gamma=gamma, beta=beta, want_y=True, want_stats=True)
+    moved = [torch.empty(D + 1, device="cuda")[1:].copy_(t) for t in (gamma, beta)]
+    for got, want in zip(B.aqt_layernorm_quantize(x, 8, gamma=moved[0], beta=moved[1], want_y=True, want_stats=True), (q, s, y, st)):
+        np.testing.assert_array_equal(host(got), host(want))
+
+
 def test_fake_float32_product_equals_int32_accumulators_until_24_bits():
     say("fake float32 product")
     rng = np.random.default_rng(60)
