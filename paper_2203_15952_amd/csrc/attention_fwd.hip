@@ -77,7 +77,7 @@ __device__ __forceinline__ void attend(const float *Ks, const float *Vt, const R
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float p = __builtin_amdgcn_exp2f(s[nb][r] - m);
-      s[nb][r] = (whole || s[nb][r] > -1e29f) ? p : 0.0f;
+      s[nb][r] = s[nb][r] > -1e29f ? p : 0.0f;   // in whole tiles too: a NaN or an overflow counts as a masked key everywhere
       sum += s[nb][r];
     }
   l += sum;

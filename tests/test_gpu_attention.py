@@ -278,3 +278,28 @@ def test_backward_uses_the_probabilities_of_the_forward(dh):
 
     mag = dv(moved(qkv_d), go.abs())
     assert np.all(np.abs(dv(qkv_d, go) - dv(moved(qkv_d), go)) <= 2 * (T + 4) * U * mag * 1.001 + TINY)
+
+
+BIG = F(3.4e38)   # rounds to an infinity in bf16
+
+
+@pytest.mark.parametrize("what,value", [("q", np.nan), ("k", np.nan), ("k", np.inf), ("k", -BIG), ("v", np.inf), ("v", BIG)])
+@pytest.mark.parametrize("dh,left,right", [(64, -1, -1), (12, 40, 70)])
+def test_forward_takes_special_values_as_the_any_layout_kernel_does(what, value, dh, left, right):
+    """Whole tiles and tiles that a window cuts alike: a score that is NaN or below -1e29 counts as a masked key."""
+    say("special values", what, value, dh, left, right)
+    T, heads = 100, 2
+    D = heads * dh
+    qkv = np.random.default_rng(690 + dh).standard_normal((2 * T, 3 * D)).astype(F)
+    qkv[37, {"q": 0, "k": D, "v": 2 * D}[what] + 5] = value
+    got = []
+    for t in (dev(qkv), moved(dev(qkv))):
+        lse = torch.empty((2 * T, heads), device="cuda")
+        ctx, m = B.aqt_attention_fwd(t, 2, T, heads, left=left, right=right, lse=lse, want_absmax=True)
+        got.append((host(ctx), host(lse), host(m).view(np.int32)))
+    if what == "v" and not np.isfinite(value) and left >= 0:
+        # a masked key's probability is zero: zero times an infinity only where the key's half of a tile is formed at all
+        seen = np.abs(np.arange(2 * T) - 37) <= 40
+        got = [(c[seen], l, 0) for c, l, _ in got]
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
