@@ -9,6 +9,10 @@
 // of a product, one rounding of it, and mostly far less: 64-term dot products measured against float64, rms error
 // 1.8e-8 of the sum of magnitudes, 2.4e-8 with v_mfma_f32_32x32x2_f32.  Six bf16 passes take 6/16 of the float32
 // instruction's time; the splitting is vector work, done once per workgroup for the staged rows.
+// An infinity, or a value that rounds to one in bf16, has no such terms: its lowest is a NaN, and so is every sum that it
+// enters.  A wavefront that ends with a value that is not finite forms its rows again with every product in float32
+// (redo_dq, redo_dkv, straight from memory), so what is finite or infinite in float32 stays so: 32 utterances of 400 frames, 8 heads
+// of 64, 302 us, 1321 if every wavefront does.
 //
 // As in attention.hip all products are formed transposed, a lane owns one query (in the key / value gradient kernel:
 // one key) from start to end, and the probabilities go from the first products' accumulators into the last products'
@@ -205,6 +209,16 @@ __device__ __forceinline__ void store_rows(float *img, const v16f (&acc)[DB], fl
   __builtin_amdgcn_wave_barrier();
 }
 
+template <int DB>
+__device__ __forceinline__ bool any_nonfinite(const v16f (&acc)[DB]) {
+  uint32_t most = 0u;
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) most = max(most, __float_as_uint(acc[blk][r]) & 0x7FFFFFFFu);
+  return __any(most >= 0x7F800000u);
+}
+
 // The tile loop: rows first, first + 32, ... <= last, two tensors per tile; compute(slot, row0) between.
 template <class Load, class Stage, class Compute>
 __device__ __forceinline__ void run_tiles(uint8_t *lds, int first, int last, Load load, Stage stage, Compute compute) {
@@ -222,6 +236,108 @@ __device__ __forceinline__ void run_tiles(uint8_t *lds, int first, int last, Loa
   }
 }
 
+// ---- the same sums with every product in float32, a wavefront by itself --------------------------------
+// (Only where it is needed: everything is formed anew from the workgroup's number, so that nothing has to be kept for it.)
+// A's 32 rows (zeros beyond the utterance) times each lane's own row, along the head, in the order of first_products.
+__device__ __forceinline__ v16f float_product(const float *__restrict__ row, bool in, const float *__restrict__ own, int lk, int dh) {
+  v16f s = zero16();
+#pragma unroll 1
+  for (int d = 0; d < dh; d += 4) {
+    v4f x = *reinterpret_cast<const v4f *>(row + d);
+    const v4f y = *reinterpret_cast<const v4f *>(own + d);
+    if (!in) x = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    s = __builtin_amdgcn_mfma_f32_32x32x2f32(lk ? x.y : x.x, lk ? y.y : y.x, s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_32x32x2f32(lk ? x.w : x.z, lk ? y.w : y.z, s, 0, 0, 0);
+  }
+  return s;
+}
+// acc += rows^T x: step r contracts the rows r0 + 8 (r / 4) + r % 4 (lk = 0) and that + 4 (lk = 1)
+template <int DB>
+__device__ __forceinline__ void float_product_rows(v16f (&acc)[DB], const float *__restrict__ src, int64_t ld, const AttnShape &g,
+                                                   int r0, const v16f &x, int lr, int lk) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int at = r0 + 8 * (r >> 2) + 4 * lk + (r & 3);
+#pragma unroll
+    for (int blk = 0; blk < DB; ++blk) {
+      const int d = 32 * blk + lr;
+      const float v = src[(at < g.T ? at : g.T - 1) * ld + (d < g.dh ? d : 0)];
+      acc[blk] = __builtin_amdgcn_mfma_f32_32x32x2f32(at < g.T && d < g.dh ? v : 0.0f, x[r], acc[blk], 0, 0, 0);
+    }
+  }
+}
+// What a wavefront of either kernel walks: its lane's own row t of the utterance, and the rows first .. last, of which
+// the lane's row meets lo .. hi; back / ahead: how far that reaches from its own row (negative: no limit).
+struct Redo {
+  int64_t base, hc;   // the utterance's first token, the head's first column
+  int tw, t, tc, first, last, lo, hi, h, lr, lk;
+};
+__device__ __forceinline__ Redo redo_place(const AttnShape &g, int back, int ahead) {
+  int id = static_cast<int>(blockIdx.x), thread = static_cast<int>(threadIdx.x);
+  asm volatile("" : "+s"(id));
+  asm volatile("" : "+v"(thread));
+  const Place pl = place_of(g, id);
+  const int lr = thread & 31, tw = pl.r0 + (__builtin_amdgcn_readfirstlane(thread) >> 6) * 32, t = tw + lr;
+  const Window w = window_of(t, tw, back, ahead, g.T);
+  return Redo{pl.b * g.T, pl.hc, tw, t, t < g.T ? t : g.T - 1, w.some_lo > 0 ? w.some_lo / kStep * kStep : 0, w.some_hi, w.lo, w.hi,
+              pl.h, lr, (thread >> 5) & 1};
+}
+template <int DB>
+__device__ __forceinline__ void redo_dq(v16f (&dq)[DB], const float *__restrict__ qkv, const float *__restrict__ dctx,
+                                        const float *__restrict__ lse, const float *dsum, const AttnShape &g) {
+  const Redo w = redo_place(g, g.left, g.right);
+  const int64_t ld = 3 * g.D;
+  const float *const q = qkv + (w.base + w.tc) * ld + w.hc, *const go = dctx + (w.base + w.tc) * g.D + w.hc;
+  const float *const keys = qkv + w.base * ld + g.D + w.hc;
+  const float L = lse[(w.base + w.tc) * g.heads + w.h], D = dsum[(w.base + w.tc) * g.heads + w.h];
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk) dq[blk] = zero16();
+#pragma unroll 1
+  for (int j0 = w.first; j0 <= w.last; j0 += kStep) {
+    const bool in = j0 + w.lr < g.T;
+    const float *const key = keys + (in ? j0 + w.lr : g.T - 1) * ld;
+    v16f s = float_product(key, in, q, w.lk, g.dh);
+    const v16f dp = float_product(key + g.D, in, go, w.lk, g.dh);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + 8 * (r >> 2) + 4 * w.lk + (r & 3);
+      const float p = (j >= w.lo && j <= w.hi) ? __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - L) : 0.0f;
+      s[r] = p * (dp[r] - D);
+    }
+    float_product_rows(dq, keys, ld, g, j0, s, w.lr, w.lk);
+  }
+}
+template <int DB>
+__device__ __forceinline__ void redo_dkv(v16f (&dk)[DB], v16f (&dv)[DB], const float *__restrict__ qkv, const float *__restrict__ dctx,
+                                         const float *__restrict__ lse, const float *__restrict__ dsum, const AttnShape &g) {
+  const Redo w = redo_place(g, g.right, g.left);
+  const int64_t ld = 3 * g.D;
+  const float *const k = qkv + (w.base + w.tc) * ld + g.D + w.hc;
+  const float *const queries = qkv + w.base * ld + w.hc, *const grads = dctx + w.base * g.D + w.hc;
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk) {
+    dk[blk] = zero16();
+    dv[blk] = zero16();
+  }
+#pragma unroll 1
+  for (int t0 = w.first; t0 <= w.last; t0 += kStep) {
+    const bool in = t0 + w.lr < g.T;
+    const int64_t at = in ? t0 + w.lr : g.T - 1;
+    v16f s = float_product(queries + at * ld, in, k, w.lk, g.dh);
+    v16f dp = float_product(grads + at * g.D, in, k + g.D, w.lk, g.dh);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int t = t0 + 8 * (r >> 2) + 4 * w.lk + (r & 3);
+      const int64_t row = (w.base + (t < g.T ? t : g.T - 1)) * g.heads + w.h;
+      const float p = (w.t < g.T && t >= w.lo && t <= w.hi) ? __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - lse[row]) : 0.0f;
+      s[r] = p;
+      dp[r] = p * (dp[r] - dsum[row]);
+    }
+    float_product_rows(dv, grads, g.D, g, t0, s, w.lr, w.lk);
+    float_product_rows(dk, queries, ld, g, t0, dp, w.lr, w.lk);
+  }
+}
+
 // ---- backward: the chain rule and the two kernels of attention.hip ---------------------------------
 // dq: a lane owns a query.  Also forms D_t = dO_t . O_t of its queries (the lane reads dO_t anyway) and leaves it in
 // dsum for the dk / dv kernel.
@@ -236,7 +352,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
   __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSlot];
   const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Place pl = place_of(g);
+  const Place pl = place_of(g, static_cast<int>(blockIdx.x));
   const int64_t b = pl.b, hc = pl.hc;
   const int t0 = pl.r0;
   const int tw = t0 + wave * 32, t = tw + lr, tc = t < g.T ? t : g.T - 1;
@@ -299,6 +415,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
   };
   run_tiles(lds, jmin / kStep * kStep, jmax, load, stage, compute);
   if (!active) return;
+  if (any_nonfinite(dq)) redo_dq(dq, qkv, dctx, lse, dsum, g);
   float *const out = dqkv + (b * g.T + tw) * 3 * g.D + hc;
   store_rows<DB>(reinterpret_cast<float *>(lds) + wave * 32 * kLd, dq, g.scale, out, 3 * g.D, g.T - tw, g.dh, lane);
 }
@@ -315,7 +432,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
   __shared__ float Ls[2][kStep], Ds[2][kStep];
   const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Place pl = place_of(g);
+  const Place pl = place_of(g, static_cast<int>(blockIdx.x));
   const int64_t b = pl.b, hc = pl.hc;
   const int j0t = pl.r0;
   const int jw = j0t + wave * 32, j = jw + lr, jc = j < g.T ? j : g.T - 1;
@@ -394,6 +511,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
   };
   run_tiles(lds, tmin / kStep * kStep, tmax, load, stage, compute);
   if (!active) return;
+  if (any_nonfinite(dk) || any_nonfinite(dv)) redo_dkv(dk, dv, qkv, dctx, lse, dsum, g);
   float *const out = dqkv + (b * g.T + jw) * 3 * g.D + g.D + hc;
   float *const img = reinterpret_cast<float *>(lds) + wave * 32 * kLd;
   store_rows<DB>(img, dk, g.scale, out, 3 * g.D, g.T - jw, g.dh, lane);

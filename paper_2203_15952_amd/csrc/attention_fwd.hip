@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_fwd_rows_kernel(const f
   float *const Vt = lds + kK * kLd;   // [head column][key]
   const int tid = static_cast<int>(threadIdx.x), lane = tid & 63, lr = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const Place pl = place_of(g);
+  const Place pl = place_of(g, static_cast<int>(blockIdx.x));
   const int T = g.T, t0 = pl.r0, tw = t0 + wave * 32, t = tw + lr;   // this wavefront's first query, this lane's query
   const bool active = tw < T;   // idle wavefronts of a ragged tile still stage and meet the barriers
   const int64_t ld = 3 * g.D;

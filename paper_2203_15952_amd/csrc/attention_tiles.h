@@ -25,8 +25,8 @@ struct Place {
   int64_t b, hc;
   int r0, h;
 };
-__device__ __forceinline__ Place place_of(const AttnShape &g) {
-  const int64_t id = blockIdx.x, heads = static_cast<int64_t>(g.heads) * g.B;
+__device__ __forceinline__ Place place_of(const AttnShape &g, int block) {
+  const int64_t id = block, heads = static_cast<int64_t>(g.heads) * g.B;
   int64_t bh, tile;
   if (heads % 8 == 0) {
     bh = id / (8 * g.qtiles) * 8 + id % 8;

@@ -303,3 +303,56 @@ def test_forward_takes_special_values_as_the_any_layout_kernel_does(what, value,
         got = [(c[seen], l, 0) for c, l, _ in got]
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("what,value", [("dctx", np.inf), ("dctx", -np.inf), ("v", np.inf), ("q", np.nan), ("k", np.inf)])
+@pytest.mark.parametrize("dh", [16, 32, 36, 64])
+def test_backward_keeps_what_is_infinite_and_what_is_finite(what, value, dh):
+    """An infinity has no bf16 terms: the same entries come out infinite (with their sign), NaN and finite as with float32
+    products.  The finite ones differ by the rounding of sums of T products of order one (2 (T + dh + 8) u of the largest,
+    the scores' amplification included: dP - D cancels)."""
+    say("special values, backward", what, value, dh)
+    T, heads = 100, 2
+    D = heads * dh
+    rng = np.random.default_rng(691 + dh)
+    qkv, go = rng.standard_normal((2 * T, 3 * D)).astype(F), rng.standard_normal((2 * T, D)).astype(F)
+    if what == "dctx":
+        go[37, 5] = value
+    else:
+        qkv[37, {"q": 0, "k": D, "v": 2 * D}[what] + 5] = value
+    qkv_d, go_d = dev(qkv), dev(go)
+    lse = torch.empty((2 * T, heads), device="cuda")
+    ctx, _ = B.aqt_attention_fwd(qkv_d, 2, T, heads, lse=lse)
+    a = host(B.aqt_attention_bwd(qkv_d, ctx, go_d, lse, 2, T, heads))
+    b = host(B.aqt_attention_bwd(moved(qkv_d), ctx, go_d, lse, 2, T, heads))
+    fine = np.isfinite(b)
+    assert (~fine).any() and fine[T:].all()   # the other utterance is untouched
+    np.testing.assert_array_equal(a[~fine], b[~fine])
+    assert np.isfinite(a[fine]).all() and np.abs(a[fine] - b[fine]).max() <= 2 * (T + dh + 8) * U * np.abs(b[fine]).max()
+
+
+@pytest.mark.parametrize("what", ["dctx", "v", "k", "q"])
+@pytest.mark.parametrize("dh,T,left,right", [(64, 100, -1, -1), (32, 300, 30, 45), (36, 130, -1, 3), (4, 40, 5, -1)])
+def test_backward_with_values_beyond_bf16(what, dh, T, left, right):
+    """Finite in float32, an infinity if rounded to bf16: the gradients stay finite and right."""
+    from parity_util import check_grad
+    say("beyond bf16", what, dh, T, left, right)
+    heads = 2
+    D = heads * dh
+    rng = np.random.default_rng(692 + dh)
+    qkv, go = rng.standard_normal((2 * T, 3 * D)).astype(F), (1e-3 * rng.standard_normal((2 * T, D))).astype(F)
+    if what == "dctx":
+        qkv[:, 2 * D:] *= F(0.1)
+        go[37, 2] = BIG
+    else:
+        at = {"q": 0, "k": D, "v": 2 * D}[what] + 2
+        if what != "v":                        # the score's other factor is zero, so that the scores stay what they are
+            qkv[:, {"q": D, "k": 0}[what] + 2] = 0.0
+        qkv[37, at] = BIG
+    qkv_d, go_d = dev(qkv), dev(go)
+    lse = torch.empty((2 * T, heads), device="cuda")
+    ctx, _ = B.aqt_attention_fwd(qkv_d, 2, T, heads, left=left, right=right, lse=lse)
+    got = host(B.aqt_attention_bwd(qkv_d, ctx, go_d, lse, 2, T, heads, left=left, right=right)).reshape(2, T, 3 * D)
+    ref, mag = oracle.attention_bwd(qkv.reshape(2, T, 3 * D), go.reshape(2, T, D), heads, left, right)
+    assert np.isfinite(got).all()
+    check_grad(got, ref, mag, "dqkv")
