@@ -1,5 +1,5 @@
-"""GPU: the contractions of gemm_any.hip (any shape, straight from the caller's tensors) at the sizes where
-they can go wrong: around the matrix-core steps and groups of the contraction, one row or channel over a
+"""GPU: the contractions straight from the caller's tensors (gemm_any.hip: the forward for any shape and small problems
+on the tuned kernels' grid; gemm_any_f64.hip: the float ones off that grid) at the sizes where they can go wrong: around the matrix-core steps and groups of the contraction, one row or channel over a
 block, odd row lengths, every workgroup arrangement, one slab and several."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def host(t):
 
 SHAPES = [
     # M, K, N, bits_w, epilogue
-    (40, 512, 2048, 4, 1),        # few rows, whole steps: four wavefronts share the contraction
+    (40, 512, 2048, 4, 1),        # few rows, whole steps: eight wavefronts share the contraction
     (1, 31, 1, 8, 0),             # less than one step, one channel
     (33, 33, 31, 4, 0),           # one beyond a step, odd packed rows
     (32, 128, 64, 8, 2),          # exactly one group and one tile; GLU halves of one block
@@ -60,9 +60,11 @@ def test_forward_and_backward(M, K, N, bw, epi):
     dx, dw, _ = B.aqt_dense_bwd(dev(c.dy), sv, 8, bw)
     check_grad(host(dx), g["dx"], g["dx_abs"], "dx")
     check_grad(host(dw), g["dw"], g["dw_abs"], "dw")
-    if max(M, N) % 128 and max(K, N) % 128:   # off every tuned tile: the float64 sum to about one rounding
-        for mine, ref, mag in ((host(dx), g["dx"], g["dx_abs"]), (host(dw), g["dw"], g["dw_abs"])):
-            assert np.all(np.abs(mine - ref) <= 2.0 ** -22 * mag + 1e-37)
+    # off the tuned kernels' grid, which each product has its own of: the float64 sum to about one rounding
+    for off, mine, ref, mag in ((M < 128 or K % 128 or N % 32, dx, g["dx"], g["dx_abs"]),
+                                (K % 256 or N % 128, dw, g["dw"], g["dw_abs"])):
+        if off:
+            assert np.all(np.abs(host(mine) - ref) <= 2.0 ** -22 * mag + 1e-37)
 
 
 @pytest.mark.parametrize("M,K,N,bw,epi", SHAPES)
@@ -81,7 +83,7 @@ def test_weight_only_forward(M, K, N, bw, epi):
     (61100, 512, 128),     # 256 x 128 tiles; most row tiles' slabs end with a turn that is not theirs
     (30528, 256, 512),     # whole stages, one row tile
     (4096, 2048, 512),     # more row tiles than stages in a slab would share evenly
-    (1000, 520, 130),      # any-shape dW: partial tiles on every side
+    (1000, 520, 130),      # float64 dW: partial tiles on every side
     (33, 129, 3),          # one slab of two slices, two row tiles, fewer than four columns
     (1, 1, 1), (64, 128, 128),
 ])
@@ -199,3 +201,23 @@ def test_off_the_grid_infinite_and_huge_values(M, K, N):
 def torch_where_finite(ref32, ref):
     import torch
     return torch.where(torch.isfinite(ref32), ref, ref32)
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (300, 256, 1024),      # dX of 6 tiles, dW in slabs of 64 rows (one in part)
+    (512, 256, 4160),      # dX: a contraction long enough to leave float32 sums on the way, 32 beyond whole steps
+    (131, 128, 4256),      # the same with row tiles in part
+    (122000, 256, 128),    # dW: as many slabs as it takes, of 512 rows
+    (260, 4160, 256),      # the weight-only forward: as long a contraction
+    (700, 1024, 256), (128, 256, 128),
+])
+def test_small_problems_on_the_tuned_grid(M, K, N):
+    """Three bf16 terms and a code's one carry a product whole; sums run in float32 over at most 512 positions (32 steps of
+    three passes, a rounding of the running sum each) and in float64 from there: (96 + 4) u of the magnitudes."""
+    print("[small, on the grid]", M, K, N, flush=True)
+    for what, (got, ref, terms, mag) in float64_products(M, K, N).items():
+        if what == "dw" and (K % 256 or M * K * N >= 4000000000):
+            continue
+        if what == "y" and (N % 128 or -(-M // 128) * -(-N // 128) > 64):
+            continue
+        assert bool(((got.double() - ref).abs() <= 100 * 2.0 ** -24 * mag + 1e-37).all()), what

@@ -95,7 +95,7 @@ def rows_of(M):
 @pytest.mark.parametrize("B_,T,D,heads,left,right,policy,outliers", [
     (32, 400, 512, 8, -1, -1, ((8, 8), (8, 8)), True),    # the self-attention configuration, int8 x int8
     (3, 70, 128, 4, 23, 0, ((4, 8), (8, 8)), False),      # causal, ragged, int4 projection weights
-    (2, 19, 24, 2, -1, 2, ((8, 4), (4, 8)), False),       # shapes the general kernels take
+    (2, 19, 24, 2, -1, 2, ((8, 4), (4, 8)), False),       # shapes off the tuned grid
 ])
 def test_mhsa_chain_stage_by_stage(B_, T, D, heads, left, right, policy, outliers):
     say("mhsa", B_, T, D, heads, left, right, policy)

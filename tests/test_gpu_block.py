@@ -34,11 +34,12 @@ def say(*a):
 # ----------------------------------------------------------------------------
 ACT_BWD_CASES = [
     # M, K, N, bits_w, epilogue          (which kernels)
-    (300, 128, 256, 4, 1),               # tuned forward / dX, general dW; ragged M
-    (512, 256, 512, 8, 2),               # tuned everywhere, GLU: dy is [M, N/2]
-    (37, 50, 24, 4, 2),                  # general kernels, GLU
+    (300, 128, 256, 4, 1),               # split contraction, dW in float64; ragged M
+    (512, 256, 512, 8, 2),               # split contraction and slabs, GLU: dy is [M, N/2]
+    (37, 50, 24, 4, 2),                  # off the tuned grid, GLU
     (5, 7, 3, 8, 1),
-    (1000, 512, 2048, 4, 1),             # the feed-forward shape, Swish
+    (1000, 512, 2048, 4, 1),             # the feed-forward shape, Swish: tuned forward
+    (2200, 512, 640, 8, 2),              # tuned forward and dX, GLU
 ]
 
 
@@ -199,7 +200,7 @@ def rows_of(M):
 @pytest.mark.parametrize("M,D,H,policy", [
     (12800, 512, 2048, ((4, 8), (4, 8))),      # the feed-forward configuration: int4 weights, int8 activations
     (1000, 256, 512, ((8, 8), (4, 4))),        # int8 x int8 first, int4 x int4 second; ragged M
-    (70, 40, 24, ((4, 8), (8, 8))),            # shapes the general kernels take
+    (70, 40, 24, ((4, 8), (8, 8))),            # shapes off the tuned grid
     (33, 27, 22, ((4, 8), (4, 8))),            # odd fan-in under packed codes, widths that are no multiple of 4
 ])
 def test_ffn_chain_stage_by_stage(M, D, H, policy):

@@ -192,8 +192,8 @@ def test_depthwise_conv_read_in_pieces_or_one_by_one_same_bits(C, kw, T):
 
 @pytest.mark.parametrize("B_,T,D,kw,pl,policy", [
     (32, 400, 512, 32, 15, ((4, 8), (8, 8))),   # the convolution-module configuration: int4 then int8 weights
-    (3, 300, 256, 15, 14, ((8, 8), (4, 8))),    # causal kernel 15; tuned kernels, ragged M
-    (2, 19, 24, 32, 15, ((4, 8), (8, 4))),      # shapes the general kernels take
+    (3, 300, 256, 15, 14, ((8, 8), (4, 8))),    # causal kernel 15; on the tuned grid, ragged M
+    (2, 19, 24, 32, 15, ((4, 8), (8, 4))),      # shapes off the tuned grid
 ])
 def test_conv_module_chain_stage_by_stage(B_, T, D, kw, pl, policy):
     say("conv module", B_, T, D, kw, pl, policy)

@@ -170,7 +170,7 @@ def test_serving_form_on_prepared_weights_equals_the_training_forward():
             y_serve = B.aqt_conformer_layer_fwd(x_d, no_w, sv, B=B_, T=T, H=H, heads=heads, kw=kw, pad_left=pl, left=23,
                                                 right=0)
             np.testing.assert_array_equal(host(y_serve), host(y_train))
-    # a module alone, general-kernel shapes (no prepared operand exists: the packed codes are used as they are)
+    # a module alone, shapes off the tuned grid (no prepared operand exists: the packed codes are used as they are)
     Ms, Ds, Hs = 70, 40, 24
     rng = np.random.default_rng(812)
     xs = dev(rng.standard_normal((Ms, Ds)).astype(F))

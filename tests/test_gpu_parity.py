@@ -157,17 +157,21 @@ def test_quantize_weights_layouts(K, N, bits_w):
 # ----------------------------------------------------------------------------
 FWD_CASES = [
     # M, K, N, bits_x, bits_w, epilogue, bias      (which kernel it lands on)
-    (256, 256, 1024, 8, 4, 0, False),    # the single-layer config: tuned kernel, 128 x 128 tiles
-    (300, 128, 256, 8, 4, 0, True),      # ragged M on the tuned kernel
+    (256, 256, 1024, 8, 4, 0, False),    # the single-layer config: 16 tiles of 128 x 128, split contraction
+    (300, 128, 256, 8, 4, 0, True),      # ragged M
     (300, 128, 256, 8, 8, 1, True),      # int8 weights, Swish
-    (200, 256, 512, 8, 4, 2, True),      # GLU on the tuned kernel
+    (200, 256, 512, 8, 4, 2, True),      # GLU
     (200, 384, 512, 8, 8, 2, False),     # odd number of fan-in stages
     (1100, 128, 128, 4, 4, 1, False),    # int4 activations, a single stage
-    (130, 192, 256, 8, 4, 0, True),      # fan-in not a multiple of the stage: general kernel
-    (37, 50, 23, 8, 4, 0, True),         # general kernel, odd K
-    (37, 51, 24, 8, 8, 2, True),         # general kernel, GLU
+    (130, 192, 256, 8, 4, 0, True),      # fan-in not a multiple of the tuned kernel's stage
+    (37, 50, 23, 8, 4, 0, True),         # odd N
+    (37, 51, 24, 8, 8, 2, True),         # odd K, GLU
     (5, 7, 3, 8, 4, 1, False),
     (1, 1, 1, 8, 8, 0, False),
+    (2100, 128, 512, 8, 4, 1, True),     # tuned kernel (more than 32 tiles of 128 x 128, 64 from K = 512 on): one stage, ragged M
+    (2176, 256, 512, 8, 8, 2, True),     # GLU on the tuned kernel, whole row tiles
+    (1500, 640, 768, 8, 4, 2, False),    # the same with five stages, ragged M
+    (4200, 256, 256, 4, 4, 0, True),
 ]
 
 
@@ -245,13 +249,13 @@ def test_dense_fwd_big_tiles_sampled():
 # ----------------------------------------------------------------------------
 # backward
 # ----------------------------------------------------------------------------
-BWD_CASES = [(256, 256, 1024, 8, 4),    # MFMA kernels, 128 x 128 tiles
-             (300, 128, 256, 8, 8),     # ragged M: clamped loads (dX), zero-filled tail (dW)
-             (37, 50, 23, 8, 4),        # general kernels
+BWD_CASES = [(256, 256, 1024, 8, 4),    # small problems on the tuned grid: split contraction, slabs of rows
+             (300, 128, 256, 8, 8),     # ragged M; dW off the grid (float64 kernel)
+             (37, 50, 23, 8, 4),        # off the grid
              (5, 7, 3, 8, 8),
              (1024, 512, 384, 8, 4),
-             (1000, 1024, 1024, 8, 4),  # dW on 256 x 256 tiles, several slabs, ragged M
-             (70, 128, 96, 8, 4)]       # dX on MFMA, dW on the general kernel
+             (1000, 1024, 1024, 8, 4),  # several slabs, ragged M
+             (70, 128, 96, 8, 4)]       # too few rows for the grid
 
 
 @pytest.mark.parametrize("M,K,N,bx,bw", BWD_CASES)
@@ -270,8 +274,8 @@ def test_dense_bwd_against_oracle(M, K, N, bx, bw):
     check_grad(host(db), g["dbias"], np.abs(c.dy.astype(np.float64)).sum(0), "dbias")
 
 
-@pytest.mark.parametrize("M,K,N", [(96, 64, 48),        # general kernels
-                                   (300, 256, 128)])     # masked variants of the tuned dX and dW kernels
+@pytest.mark.parametrize("M,K,N", [(96, 64, 48),        # off the tuned grid
+                                   (300, 256, 128)])     # a small problem on it (the tuned kernels: TUNED_BWD_CASES)
 def test_dense_bwd_masks_and_zero_groups(M, K, N):
     say("dense bwd masks", M, K, N)
     c = inputs.small_case(61, M, K, N, 8, 4)
@@ -303,6 +307,53 @@ def test_dense_bwd_masks_and_zero_groups(M, K, N):
     check_grad(host(dx2), g2["dx"], g2["dx_abs"], "dx")
     check_grad(host(dw2), g2["dw"], g2["dw_abs"], "dw")
     assert (host(dw2)[:, 5] == 0).all() and host(dw2)[:, 4].any()
+
+
+TUNED_BWD_CASES = [
+    # M, K, N                 dX from 65 tiles of 128 x 128 on; dW from 4e9 multiply-adds on
+    (15301, 512, 512),     # dX on 128 x 128 tiles, dW on 256 x 256; the last row tile and the last stage in part
+    (15360, 512, 512),     # the same with whole tiles and stages
+    (61100, 512, 128),     # dX on 128 x 512 tiles, dW on 256 x 128, in part
+    (61440, 512, 128),     # ... whole
+    (4163, 512, 64),       # dX on 128 x 128 tiles, two stages; dW off the grid
+]
+
+
+@pytest.mark.parametrize("M,K,N", TUNED_BWD_CASES)
+@pytest.mark.parametrize("masked,want_dbias", [(False, False), (True, True), (False, True)])
+def test_tuned_backward_kernels_in_full(M, K, N, masked, want_dbias):
+    """Every element of dX and dW against float64 products, with and without clip masks and the bias gradient's sums
+    (dW's kernel and its fold have a form for each)."""
+    say("tuned backward", M, K, N, masked, want_dbias)
+    gen = torch.Generator(device="cuda").manual_seed(M + K + N)
+    x, w = torch.randn((M, K), device="cuda", generator=gen), torch.randn((K, N), device="cuda", generator=gen)
+    dy = torch.randn((M, N), device="cuda", generator=gen) + 0.1
+    w[:, 5] = 0
+    sv = B.Saved(M, K, N, 8, masks=masked)
+    if masked:   # scales that are too small make both masks non-trivial
+        sv.s_x.fill_(0.02)
+        sv.s_w.fill_(0.02)
+        B.aqt_quantize_with_scale(x, 8, B.AQT_AXIS_ALL, sv.s_x, q=sv.xq, clip_mask=sv.mask_x)
+        B.aqt_quantize_with_scale(w, 8, B.AQT_AXIS_ROWS, sv.s_w, q=sv.wq_kn, clip_mask=sv.mask_w)
+        pass_x, pass_w = (dev(unpack_mask(host(m), n).reshape(shape)) for m, n, shape in
+                          ((sv.mask_x, M * K, (M, K)), (sv.mask_w, K * N, (K, N))))
+        assert 0 < float(pass_x.double().mean()) < 1 and 0 < float(pass_w.double().mean()) < 1
+    else:
+        B.aqt_dense_fwd(x, w, 8, 8, saved=sv)
+        pass_x, pass_w = 1.0, (sv.s_w != 0).double()
+        assert int((sv.s_w == 0).sum()) == 1
+    dx, dw, db = B.aqt_dense_bwd(dy, sv, 8, 8, want_dbias=want_dbias)
+    dys, q, xq, d, sx = (dy * sv.s_w).double(), sv.wq_kn.double(), sv.xq.double(), dy.double(), sv.s_x.double()
+    qt, xt = q.t().contiguous(), xq.t().contiguous()
+    for what, got, ref, mag in (("dx", dx, (dys @ qt) * pass_x, dys.abs() @ qt.abs()),
+                                ("dw", dw, sx * (xt @ d) * pass_w, sx * (xt.abs() @ d.abs()))):
+        err = (got.double() - ref).abs()
+        assert float(err.max()) <= 1e-4 * float(ref.abs().max()), what
+        assert bool((err <= 1e-4 * mag + 1e-37).all()), what
+        assert bool((got[ref == 0] == 0).all()), what
+    if want_dbias:
+        ref = d.sum(0)
+        assert bool(((db.double() - ref).abs() <= 2.0 ** -24 * ref.abs() * 1.0001 + M * 2.0 ** -53 * d.abs().sum(0)).all())
 
 
 DX_WIDE_CASES = [
@@ -358,11 +409,11 @@ def tile_rows(M, BM=128):
     return np.unique(np.r_[0:BM, mid:mid + BM, max(0, M - 2 * BM):M])
 
 
-def test_backward_is_bit_reproducible_and_stream_ordered():
+@pytest.mark.parametrize("M,K,N", [(4096, 512, 256), (16000, 512, 512)])   # small and tuned
+def test_backward_is_bit_reproducible_and_stream_ordered(M, K, N):
     # dW folds its slabs in a fixed order: two runs give identical bits; the same work
     # enqueued on a side stream (the stream argument of the C ABI) gives them too
-    say("bwd reproducible / side stream")
-    M, K, N = 4096, 512, 256
+    say("bwd reproducible / side stream", M, K, N)
     c = inputs.small_case(71, M, K, N, 8, 4)
     sv = B.Saved(M, K, N, 4)
     x_d, w_d, dy_d = dev(c.x), dev(c.w), dev(c.dy)
@@ -383,12 +434,12 @@ def test_backward_is_bit_reproducible_and_stream_ordered():
     np.testing.assert_array_equal(host(dx3), host(dx1))
 
 
-def test_twenty_runs_give_identical_bytes():
+@pytest.mark.parametrize("M,K,N", [(2048, 512, 512), (8000, 512, 1024)])   # small and tuned
+def test_twenty_runs_give_identical_bytes(M, K, N):
     # Every kernel is deterministic: integer maxima and integer sums do not depend on order, the float
     # reductions (dW slabs, column sums, row statistics) are folded in a fixed order, and the only atomics
     # are maxima and bit-wise ORs.  Twenty runs of each entry point must agree byte for byte.
-    say("determinism x20")
-    M, K, N = 2048, 512, 512
+    say("determinism x20", M, K, N)
     c = inputs.small_case(111, M, K, N, 8, 4, 1, with_bias=True)
     x_d, w_d, dy_d, b_d = dev(c.x), dev(c.w), dev(c.dy), dev(c.bias)
     first = None
@@ -447,10 +498,12 @@ def test_argument_errors_on_device_buffers():
 # ----------------------------------------------------------------------------
 ABSMAX_CASES = [
     # M, K, N, bits_w, epilogue, bias
-    (300, 128, 256, 4, 1, True),        # tuned kernel, ragged M (shifted tile recomputes rows), Swish
-    (200, 256, 512, 8, 2, True),        # tuned kernel, GLU: the maximum is over the gated outputs
-    (4100, 384, 384, 4, 0, False),      # several tiles, the output spans more than one quantizer block
-    (37, 50, 23, 4, 1, True),           # general kernel
+    (300, 128, 256, 4, 1, True),        # ragged M, Swish
+    (200, 256, 512, 8, 2, True),        # GLU: the maximum is over the gated outputs
+    (4100, 384, 384, 4, 0, False),      # tuned kernel, the output spans more than one quantizer block
+    (2100, 128, 512, 4, 1, True),       # tuned kernel, ragged M (shifted tile recomputes rows), Swish
+    (2176, 256, 512, 8, 2, True),       # tuned kernel, GLU
+    (37, 50, 23, 4, 1, True),           # odd N
     (1, 1, 1, 8, 0, False),
 ]
 
@@ -513,11 +566,15 @@ def test_quantize_with_absmax_edge_cases():
 # ----------------------------------------------------------------------------
 WONLY_CASES = [
     # M, K, N, bits_w, epilogue, bias       (which kernel it lands on)
-    (256, 256, 1024, 4, 0, False),   # tuned kernel, 128 x 128 tiles, packed int4 weights
-    (300, 96, 256, 8, 1, True),      # ragged M, int8 weights, Swish, three contraction stages
-    (200, 64, 512, 4, 2, True),      # GLU: value and gate blocks in one tile
+    (256, 256, 1024, 4, 0, False),   # small problems on the tuned grid: split contraction; packed int4 weights
+    (300, 96, 256, 8, 1, True),      # ragged M, int8 weights, Swish
+    (200, 64, 512, 4, 2, True),      # GLU
     (200, 160, 256, 8, 2, False),
-    (37, 50, 23, 4, 0, True),        # general kernel
+    (2176, 256, 512, 4, 0, False),   # tuned kernel (more than 64 tiles), 128 x 128 tiles, packed int4 weights
+    (2100, 96, 640, 8, 1, True),     # ragged M, int8 weights, Swish, three contraction stages
+    (2100, 64, 640, 4, 2, True),     # GLU: value and gate blocks in one tile
+    (4000, 160, 384, 8, 2, False),
+    (37, 50, 23, 4, 0, True),        # off the grid: float64 sums
     (37, 51, 24, 8, 2, True),
     (3, 1, 2, 4, 1, False),
 ]

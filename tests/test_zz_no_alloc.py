@@ -26,7 +26,7 @@ def host(t):
 def test_static_scratch_forward_two_calls_in_a_row():
     cases = [(1000, 512, 1024, 8, 4, B.AQT_EPI_SWISH),    # tuned kernel, 512 KiB of scratch
              (300, 128, 256, 8, 8, B.AQT_EPI_GLU),        # smaller layer right after: 32 KiB
-             (37, 50, 23, 8, 4, B.AQT_EPI_NONE)]          # a shape the general kernel takes (no scratch)
+             (37, 50, 23, 8, 4, B.AQT_EPI_NONE)]          # a shape off the tuned grid (no scratch)
     prepared = []
     for i, (M, K, N, bx, bw, epi) in enumerate(cases):
         print("static scratch case", M, K, N, bx, bw, epi, flush=True)
