@@ -30,7 +30,7 @@ inline void __syncthreads() { g_bar->arrive_and_wait(); }
 inline void __builtin_amdgcn_wave_barrier() { g_wbar[threadIdx.x >> 6]->arrive_and_wait(); }
 // wave shuffle: exchange through a table, in step with the other lanes of the wavefront
 static int g_shfl[1024];
-inline int __shfl_xor(int v, int off, int) {
+inline int __shfl_xor(int v, int off, int = 64) {
   std::barrier<> *wb = g_wbar[threadIdx.x >> 6];
   g_shfl[threadIdx.x] = v; wb->arrive_and_wait();
   int r = g_shfl[(threadIdx.x & ~63u) | ((threadIdx.x ^ (unsigned)off) & 63u)]; wb->arrive_and_wait();

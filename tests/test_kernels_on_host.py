@@ -3,6 +3,7 @@ and undefined-behaviour sanitizers: every global and LDS access of launch geomet
 is checked against exactly sized buffers, and the results against float64 loops in the drivers.  The
 kernels' source is taken as it is (HIP headers replaced by a small vocabulary header, launchers cut off)."""
 import os
+import re
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -35,6 +36,37 @@ def spliced_attention_source(driver="attention_driver.cpp"):
     return src + open(os.path.join(HERE, "host_emulation", driver)).read()
 
 
+def cut(src, start, end):
+    """src without what lies between two of its lines (start included, end not)."""
+    i = src.index(start)
+    return src[:i] + src[src.index(end, i):]
+
+
+def spliced_attention_rows_source():
+    def read(name):
+        src = open(os.path.join(CSRC, name)).read()
+        src = re.sub(r"^ *typedef \w+ v\w+ __attribute__\(\(ext_vector_type\(\d+\)\)\);\n", "", src, flags=re.M)   # structs in the shim
+        return re.sub(r"^#(include|pragma once).*\n", "", src, flags=re.M)
+
+    shape = open(os.path.join(CSRC, "aqt_internal.h")).read()
+    shape = shape[shape.index("struct AttnShape {"):]
+    shape = shape[:shape.index("};") + 2]
+    tiles = read("attention_tiles.h").replace("namespace aqt {", "namespace aqt {\n" + shape, 1)
+    fwd = read("attention_fwd.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace fwd_rows {")
+    fwd = fwd[:fwd.index("aqt_status launch_attention_rows")] + "}\n"
+    bwd = read("attention_bwd.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace bwd_rows {")
+    bwd = bwd[:bwd.index("bool attention_rows_ok")] + "}\n"
+    # instructions that the shim stands in for
+    bwd = cut(bwd, "__device__ __forceinline__ uint32_t pack_bf16", "__device__ __forceinline__ void split2")
+    bwd = cut(bwd, "__device__ __forceinline__ v16f mfma(", "__device__ __forceinline__ v16f mfma6")
+    bwd = cut(bwd, "  typedef __attribute__((address_space(3)))", "  return v4i{a.x, a.y, b.x, b.y};")
+    bwd = bwd.replace("  return v4i{a.x, a.y, b.x, b.y};", "  const v2i a = read_tr_b16(image + at0), b = read_tr_b16(image + at1);\n  return v4i{a.x, a.y, b.x, b.y};")
+    assert bwd.count('asm volatile("" : "+') == 2
+    bwd = re.sub(r' *asm volatile\("" : "\+[sv]"\(\w+\)\);\n', "", bwd)
+    driver = open(os.path.join(HERE, "host_emulation", "attention_rows_driver.cpp")).read()
+    return '#include "vectors_on_host.h"\n' + tiles + fwd + bwd + driver
+
+
 def test_conv_kernels_in_bounds_and_correct_on_host(tmp_path):
     build_and_run(tmp_path, "conv_on_host", spliced_source())
 
@@ -45,6 +77,10 @@ def test_attention_kernel_in_bounds_and_correct_on_host(tmp_path):
 
 def test_attention_backward_kernels_in_bounds_and_correct_on_host(tmp_path):
     build_and_run(tmp_path, "attention_bwd_on_host", spliced_attention_source("attention_bwd_driver.cpp"))
+
+
+def test_attention_kernels_for_vectorised_rows_in_bounds_and_correct_on_host(tmp_path):
+    build_and_run(tmp_path, "attention_rows_on_host", spliced_attention_rows_source())
 
 
 def build_and_run(tmp_path, name, source):
