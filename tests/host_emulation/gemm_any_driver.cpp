@@ -1,0 +1,184 @@
+// Driver of the host emulation of the contractions straight from the caller's tensors: the test splices any_shape.h,
+// colsum.h and epilogue.h, the kernels of gemm_any.hip (namespace any) and of gemm_any_f64.hip (namespace f64) in front of this
+// file.  Every tensor is an allocation of exactly its size; results are compared with plain loops written here.
+namespace aqt {
+static int bad = 0;
+static uint32_t seed = 17u;
+static float uniform() { seed = seed * 1664525u + 1013904223u; return (float)(seed >> 8) / 8388608.0f - 1.0f; }
+static int code(int q) { return (int)lrintf(uniform() * (float)q); }
+template <class T> struct Exact {   // n elements on the heap, nothing behind them
+  T *p;
+  explicit Exact(size_t n) : p((T *)malloc(n * sizeof(T))) { memset(p, 0x7E, n * sizeof(T)); }
+  ~Exact() { free(p); }
+  operator T *() const { return p; }
+};
+static void verdict(const char *what, double worst, double limit) {
+  printf("  %s: worst %.3g\n", what, worst); fflush(stdout);
+  if (!(worst <= limit)) { printf("  MISMATCH\n"); bad = 1; }
+}
+static double sigma(double x) { return 1.0 / (1.0 + exp(-x)); }
+// rows of codes [R][row bytes], and what they hold
+struct Codes {
+  std::vector<int> v;
+  Exact<uint8_t> bytes;
+  Codes(int64_t R, int64_t C, bool packed) : v(R * C), bytes(R * (packed ? (C + 1) / 2 : C)) {
+    const int64_t rb = packed ? (C + 1) / 2 : C;
+    for (int64_t r = 0; r < R; ++r) {
+      if (packed) memset(bytes + r * rb, 0, rb);
+      for (int64_t c = 0; c < C; ++c) {
+        const int q = code(packed ? 7 : 127);
+        v[r * C + c] = q;
+        if (packed) bytes[r * rb + c / 2] |= (uint8_t)((q & 15) << (4 * (c & 1)));
+        else bytes[r * rb + c] = (uint8_t)(int8_t)q;
+      }
+    }
+  }
+};
+
+template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> void forward(int64_t M, int64_t K, int64_t N) {
+  printf("forward tile %d %d %d %d %d packed %d epilogue %d: %ld %ld %ld\n", TM, TN, WM, WN, WK, (int)PACKED, EPI, (long)M, (long)K, (long)N);
+  constexpr bool GLU = EPI == AQT_EPI_GLU;
+  const int64_t oc = GLU ? N / 2 : N;
+  Codes x(M, K, false), w(N, K, PACKED);
+  Exact<float> sw(N), bias(N), y(M * oc), dact(M * N), sx(1);
+  Exact<int32_t> acc(M * N);
+  Exact<uint32_t> am(1);
+  am[0] = 0; sx[0] = 0.01f;
+  for (int64_t n = 0; n < N; ++n) { sw[n] = 0.02f + 0.01f * uniform(); bias[n] = uniform(); }
+  const int64_t tn = cdiv(oc, (GLU ? 16 : 32) * TN * WN), tm = cdiv(M, 32 * TM * WM);
+  run((unsigned)(tn * tm), 64 * WM * WN * WK, 0, [&] {
+    any::dense_fwd_any_kernel<TM, TN, WM, WN, WK, BK, PACKED, EPI>((const int8_t *)x.bytes.p, sx, w.bytes, sw, M, K, N, bias, y, acc, am, dact, (int)tn);
+  });
+  double worst = 0, sums = 0;
+  float mx = 0;
+  for (int64_t m = 0; m < M; ++m) for (int64_t n = 0; n < oc; ++n) {
+    double v[2];
+    for (int h = 0; h < (GLU ? 2 : 1); ++h) {
+      int s = 0;
+      for (int64_t k = 0; k < K; ++k) s += x.v[m * K + k] * w.v[(n + h * oc) * K + k];
+      if (s != acc[m * N + n + h * oc]) ++sums;
+      v[h] = (double)s * ((double)sx[0] * sw[n + h * oc]) + bias[n + h * oc];
+    }
+    const double ref = GLU ? v[0] * sigma(v[1]) : EPI == AQT_EPI_SWISH ? v[0] * sigma(v[0]) : v[0];
+    const double e = fabs((double)y[m * oc + n] - ref) / (1.0 + fabs(ref));
+    if (!(e <= worst)) worst = e;
+    mx = std::max(mx, fabsf(y[m * oc + n]));
+  }
+  verdict("integer sums that differ", sums, 0);
+  verdict("outputs", worst, 1e-5);
+  if (__float_as_uint(mx) != am[0]) { printf("  MISMATCH of the largest value\n"); bad = 1; }
+}
+
+// MODE 0: dX with a factor and a clip mask; 1 + e: weight-only forward.  kernel(f, scale, q, s_x, mask, factor, bias, out)
+template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_t R, int64_t C, double limit, Kernel kernel) {
+  constexpr bool GLU = MODE == 1 + AQT_EPI_GLU;
+  printf("float rows, mode %d packed %d: %ld %ld %ld\n", MODE, (int)PACKED, (long)M, (long)R, (long)C);
+  const int64_t oc = GLU ? R / 2 : R, ns = MODE ? R : C;
+  Codes q(R, C, PACKED);
+  Exact<float> f(M * C), scale(ns), bias(R), factor(M * R), out(M * oc), sx(1);
+  Exact<uint32_t> mask(cdiv(M * R, 32));
+  sx[0] = 1.0f;
+  for (int64_t i = 0; i < M * C; ++i) f[i] = uniform();
+  for (int64_t i = 0; i < ns; ++i) scale[i] = 0.02f + 0.01f * uniform();
+  for (int64_t i = 0; i < R; ++i) bias[i] = MODE ? uniform() : 0.0f;
+  for (int64_t i = 0; i < M * R; ++i) factor[i] = uniform();
+  for (int64_t i = 0; i < cdiv(M * R, 32); ++i) { uniform(); mask[i] = seed | (seed << 16); }
+  kernel((const float *)f, (const float *)scale, (const uint8_t *)q.bytes, (const float *)sx, (const uint32_t *)mask, (const float *)factor, (const float *)bias, (float *)out);
+  double worst = 0;
+  for (int64_t m = 0; m < M; ++m) for (int64_t r = 0; r < oc; ++r) {
+    double v[2], mag = 0;
+    for (int h = 0; h < (GLU ? 2 : 1); ++h) {
+      double s = 0;
+      for (int64_t c = 0; c < C; ++c) {
+        const double t = MODE ? (double)f[m * C + c] * q.v[(r + h * oc) * C + c] * scale[r + h * oc] : (double)(f[m * C + c] * scale[c]) * q.v[r * C + c];
+        s += t; mag += fabs(t);
+      }
+      v[h] = s + bias[r + h * oc]; mag += fabs(bias[r + h * oc]);
+    }
+    double ref = v[0];
+    if (!MODE) ref = (mask[(m * R + r) >> 5] >> ((m * R + r) & 31) & 1) ? v[0] * factor[m * R + r] : 0.0;
+    else if (GLU) ref = v[0] * sigma(v[1]);
+    else if (MODE == 1 + AQT_EPI_SWISH) ref = v[0] * sigma(v[0]);
+    const double e = fabs((double)out[m * oc + r] - ref) / (mag + 1e-30);
+    if (!(e <= worst)) worst = e;
+  }
+  verdict("error / sum |terms|", worst, limit);
+}
+template <int TN, int WN, int WK, bool PACKED, int MODE> void rows_f64(int64_t M, int64_t R, int64_t C) {
+  const int64_t tr = cdiv(MODE == 1 + AQT_EPI_GLU ? R / 2 : R, (MODE == 1 + AQT_EPI_GLU ? 8 : 16) * TN * WN), tm = cdiv(M, 32);
+  float_rows<MODE, PACKED>(M, R, C, MODE > 1 ? 3e-6 : 1.2e-7, [&](auto f, auto scale, auto q, auto sx, auto mask, auto factor, auto bias, auto out) {
+    run((unsigned)(tr * tm), 64 * WN * WK, 0, [&] {
+      f64::f32_codes_f64_kernel<TN, WN, WK, PACKED, MODE>(f, scale, q, M, R, C, sx, MODE ? nullptr : mask, MODE ? nullptr : factor, MODE ? bias : nullptr, out, (int)tr);
+    });
+  });
+}
+template <int TN, bool PACKED, int MODE, bool LONG> void rows_any(int64_t M, int64_t R, int64_t C) {
+  const int64_t tr = R / (32 * TN), tm = cdiv(M, 32);
+  float_rows<MODE, PACKED>(M, R, C, 3e-6, [&](auto f, auto scale, auto q, auto sx, auto mask, auto factor, auto bias, auto out) {
+    run((unsigned)(tr * tm), 512, 0, [&] {
+      any::f32_codes_any_kernel<TN, PACKED, MODE, LONG>(f, scale, q, M, R, C, sx, MODE ? nullptr : mask, MODE ? nullptr : factor, MODE ? bias : nullptr, out, (int)tr);
+    });
+  });
+}
+
+// dW in slabs of `rows` rows, with the bias gradient; T: what a slab's partial sums are kept in
+template <class T> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, bool masked) {
+  constexpr bool F64 = sizeof(T) == 8;
+  const int64_t tile = F64 ? 64 : 128, tiles_n = cdiv(N, tile), tiles_k = cdiv(K, tile), slabs = cdiv(M, rows);
+  printf("dW %s: %ld %ld %ld, %ld slabs, masked %d\n", F64 ? "float64" : "bf16", (long)M, (long)K, (long)N, (long)slabs, (int)masked);
+  Codes x(M, K, false);
+  Exact<float> dy(M * N), sx(1), sw(N), dw(K * N), db(N);
+  Exact<T> partial(slabs * K * N);
+  Exact<double> part(slabs * tiles_k * N);
+  Exact<uint32_t> mask(cdiv(K * N, 32));
+  sx[0] = 0.03f;
+  for (int64_t i = 0; i < M * N; ++i) dy[i] = uniform();
+  for (int64_t i = 0; i < N; ++i) sw[i] = i % 5 ? 0.5f : 0.0f;
+  for (int64_t i = 0; i < cdiv(K * N, 32); ++i) { uniform(); mask[i] = seed | (seed << 16); }
+  const bool one = slabs == 1;
+  const unsigned grid = (unsigned)(tiles_k * tiles_n * slabs), bias_blocks = (unsigned)cdiv(N, kColsumCols), dw_blocks = one ? 0 : (unsigned)cdiv(K * N, 64);
+  if constexpr (F64) {
+    const DwFinish fin{sx, sw, masked ? mask.p : nullptr};
+    run(grid, 256, 0, [&] { f64::bwd_dw_f64_kernel((const int8_t *)x.bytes.p, dy, M, K, N, rows, partial, one ? dw.p : nullptr, (int)tiles_n, (int)(tiles_k * tiles_n), fin, part); });
+    run(bias_blocks + dw_blocks, 256, 0, [&] { f64::dw_f64_fold_kernel(partial, (int)slabs, K, N, fin, dw, part, (int)(slabs * tiles_k), bias_blocks, db); });
+  } else {
+    const DwFinish fin{sx, sw, masked ? mask.p : nullptr};
+    run(grid, 256, 0, [&] { any::bwd_dw_any_kernel((const int8_t *)x.bytes.p, dy, M, K, N, rows, one ? dw.p : (float *)partial.p, (int)tiles_n, (int)(tiles_k * tiles_n), one ? 1 : 0, fin, part); });
+    run(bias_blocks + dw_blocks, 256, 0, [&] { any::dw_any_fold_kernel((const float *)partial.p, (int)slabs, K, N, fin, dw, part, (int)(slabs * tiles_k), bias_blocks, db); });
+  }
+  double worst = 0, worst_b = 0;
+  for (int64_t n = 0; n < N; ++n) {
+    double b = 0, ba = 0;
+    for (int64_t m = 0; m < M; ++m) { b += dy[m * N + n]; ba += fabs(dy[m * N + n]); }
+    worst_b = std::max(worst_b, fabs(db[n] - b) / (ba + 1e-30));
+    for (int64_t k = 0; k < K; ++k) {
+      double s = 0, mag = 0;
+      for (int64_t m = 0; m < M; ++m) { const double t = (double)sx[0] * x.v[m * K + k] * dy[m * N + n]; s += t; mag += fabs(t); }
+      const int64_t at = k * N + n;
+      if (masked ? !(mask[at >> 5] >> (at & 31) & 1) : sw[n] == 0.0f) s = 0;
+      const double e = fabs(dw[at] - s) / (mag + 1e-30);
+      if (!(e <= worst)) worst = e;
+    }
+  }
+  verdict("dW, error / sum |terms|", worst, F64 ? 6.1e-8 : 3e-6);
+  verdict("bias gradient", worst_b, 6.1e-8);
+}
+}  // namespace aqt
+int main() {
+  using namespace aqt;
+  constexpr int kNone = AQT_EPI_NONE, kSwish = AQT_EPI_SWISH, kGlu = AQT_EPI_GLU;
+  forward<1, 2, 4, 2, 1, 128, false, kGlu>(70, 150, 70); forward<1, 2, 4, 2, 1, 128, true, kSwish>(129, 131, 129);
+  forward<1, 1, 2, 4, 1, 128, true, kNone>(67, 257, 130); forward<1, 2, 2, 2, 1, 128, true, kGlu>(65, 33, 30);
+  forward<1, 2, 4, 1, 1, 128, false, kSwish>(131, 17, 65); forward<1, 1, 1, 1, 8, 64, false, kNone>(33, 517, 31);
+  forward<1, 1, 1, 1, 8, 64, true, kSwish>(1, 31, 1); forward<1, 2, 1, 1, 8, 64, true, kGlu>(40, 129, 34);
+  forward<1, 2, 1, 1, 8, 64, false, kGlu>(9, 15, 18); forward<1, 1, 1, 1, 8, 64, true, kNone>(9, 3, 5);
+  rows_f64<1, 1, 8, false, 0>(33, 17, 300); rows_f64<1, 1, 8, false, 0>(5, 15, 3); rows_f64<2, 1, 8, true, 1 + kSwish>(34, 33, 77);
+  rows_f64<1, 4, 1, false, 0>(65, 66, 37); rows_f64<1, 4, 1, true, 1 + kNone>(31, 65, 17); rows_f64<1, 4, 1, true, 1 + kNone>(3, 3, 15);
+  rows_f64<2, 2, 1, false, 1 + kGlu>(33, 70, 33); rows_f64<2, 1, 8, true, 1 + kGlu>(33, 34, 129); rows_f64<2, 2, 1, false, 1 + kGlu>(2, 2, 1);
+  rows_any<1, false, 0, false>(33, 128, 96); rows_any<2, false, 0, false>(33, 128, 32); rows_any<2, true, 1 + kGlu, false>(33, 128, 320);
+  rows_any<1, false, 0, true>(7, 32, 4640); rows_any<1, true, 1 + kSwish, true>(3, 32, 4128);
+  weights<double>(70, 66, 65, 64, false); weights<double>(130, 3, 2, 64, true); weights<double>(33, 64, 70, 64, true); weights<double>(1, 1, 1, 64, false);
+  weights<double>(200, 130, 5, 128, true);
+  weights<float>(70, 128, 128, 64, true); weights<float>(33, 256, 128, 64, false); weights<float>(1, 128, 128, 32, true);
+  printf(bad ? "MISMATCH\n" : "ok\n"); return bad;
+}

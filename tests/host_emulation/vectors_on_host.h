@@ -1,6 +1,7 @@
 // The short vectors of the kernels as plain structs, and the wavefront-wide instructions that the kernels for vectorised
 // rows use besides those of hip_on_host.h.  Lanes exchange through tables, in step with their wavefront.
 #pragma once
+#include <type_traits>
 #include "hip_on_host.h"
 #define AQT_VECTOR(name, type, n, bytes, ...)                          \
   struct alignas(bytes) name {                                         \
@@ -12,6 +13,8 @@ AQT_VECTOR(v2f, float, 2, 8, x, y)
 AQT_VECTOR(v4f, float, 4, 16, x, y, z, w)
 AQT_VECTOR(v2i, int, 2, 8, x, y)
 AQT_VECTOR(v4i, int, 4, 16, x, y, z, w)
+AQT_VECTOR(v4d, double, 4, 32, x, y, z, w)
+struct v16i { int v[16]; int &operator[](int i) { return v[i]; } const int &operator[](int i) const { return v[i]; } };
 inline std::barrier<> &wave_meets() { return *g_wbar[threadIdx.x >> 6]; }
 inline int __builtin_amdgcn_readfirstlane(int v) {
   static int table[16];
@@ -38,7 +41,7 @@ inline uint32_t bf16_bits(float f) {   // round to nearest even
 }
 inline uint32_t pack_bf16(float a, float b) { return bf16_bits(a) | bf16_bits(b) << 16; }
 // v_mfma_f32_32x32x16_bf16: lane (lr, lk) supplies A[lr][8 lk .. 8 lk + 7] and B[8 lk .. 8 lk + 7][lr]
-inline v16f mfma(v4i a, v4i b, v16f c) {
+inline v16f mfma_bf16(v4i a, v4i b, v16f c) {
   static v4i ta[1024], tb[1024];
   const unsigned base = threadIdx.x & ~63u, lane = threadIdx.x & 63u, lr = lane & 31u, lk = lane >> 5;
   ta[threadIdx.x] = a; tb[threadIdx.x] = b;
@@ -54,6 +57,44 @@ inline v16f mfma(v4i a, v4i b, v16f c) {
   }
   wave_meets().arrive_and_wait();
   return c;
+}
+inline v16f mfma(v4i a, v4i b, v16f c) { return mfma_bf16(a, b, c); }
+// v_mfma_i32_32x32x32_i8: lane (lr, lk) supplies A[lr][16 lk .. 16 lk + 15] and B[16 lk .. 16 lk + 15][lr]
+inline v16i __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i a, v4i b, v16i c, int, int, int) {
+  static v4i ta[1024], tb[1024];
+  const unsigned base = threadIdx.x & ~63u, lane = threadIdx.x & 63u, lr = lane & 31u, lk = lane >> 5;
+  ta[threadIdx.x] = a; tb[threadIdx.x] = b;
+  wave_meets().arrive_and_wait();
+  for (int r = 0; r < 16; ++r) {
+    const unsigned row = 8 * (r >> 2) + 4 * lk + (r & 3);
+    for (unsigned half = 0; half < 2; ++half) {
+      int8_t x[16], y[16];
+      memcpy(x, &ta[base + 32 * half + row], 16);
+      memcpy(y, &tb[base + 32 * half + lr], 16);
+      for (int k = 0; k < 16; ++k) c[r] += x[k] * y[k];
+    }
+  }
+  wave_meets().arrive_and_wait();
+  return c;
+}
+// v_mfma_f64_16x16x4_f64: lane (lc = lane % 16, lg = lane / 16) supplies A[lc][lg] and B[lg][lc]; element r of its
+// accumulator is row 4 r + lg, column lc
+inline v4d __builtin_amdgcn_mfma_f64_16x16x4f64(double a, double b, v4d c, int, int, int) {
+  static double ta[1024], tb[1024];
+  const unsigned base = threadIdx.x & ~63u, lane = threadIdx.x & 63u, lc = lane & 15u, lg = lane >> 4;
+  ta[threadIdx.x] = a; tb[threadIdx.x] = b;
+  wave_meets().arrive_and_wait();
+  for (unsigned r = 0; r < 4; ++r)
+    for (unsigned k = 0; k < 4; ++k) c[r] = fma(ta[base + 16 * k + 4 * r + lg], tb[base + 16 * k + lc], c[r]);
+  wave_meets().arrive_and_wait();
+  return c;
+}
+inline uint32_t __builtin_amdgcn_alignbyte(uint32_t hi, uint32_t lo, int b) { return (uint32_t)(((uint64_t)hi << 32 | lo) >> (8 * (b & 3))); }
+inline uint32_t __builtin_amdgcn_perm(uint32_t hi, uint32_t lo, uint32_t sel) {   // selector bytes 0 .. 3: lo, 4 .. 7: hi
+  const uint64_t v = (uint64_t)hi << 32 | lo;
+  uint32_t r = 0;
+  for (int e = 0; e < 4; ++e) r |= (uint32_t)(v >> (8 * (sel >> (8 * e) & 7)) & 0xFF) << (8 * e);
+  return r;
 }
 // ds_read_b64_tr_b16: sixteen lanes read eight bytes each, four rows of sixteen 16-bit columns; lane i receives column i
 inline v2i read_tr_b16(const uint8_t *at) {

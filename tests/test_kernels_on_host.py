@@ -1,7 +1,9 @@
-"""The depthwise-convolution and attention kernels run on the host, thread by thread, under the address
+"""The depthwise-convolution and attention kernels and the contractions straight from the caller's tensors
+(gemm_any.hip, gemm_any_f64.hip) run on the host, thread by thread, under the address
 and undefined-behaviour sanitizers: every global and LDS access of launch geometries like the GPU tests'
 is checked against exactly sized buffers, and the results against float64 loops in the drivers.  The
-kernels' source is taken as it is (HIP headers replaced by a small vocabulary header, launchers cut off)."""
+kernels' source is taken as it is (HIP headers replaced by a small vocabulary header, launchers cut off,
+instructions of a whole wavefront replaced by their stand-ins)."""
 import os
 import re
 import subprocess
@@ -42,12 +44,13 @@ def cut(src, start, end):
     return src[:i] + src[src.index(end, i):]
 
 
-def spliced_attention_rows_source():
-    def read(name):
-        src = open(os.path.join(CSRC, name)).read()
-        src = re.sub(r"^ *typedef \w+ v\w+ __attribute__\(\(ext_vector_type\(\d+\)\)\);\n", "", src, flags=re.M)   # structs in the shim
-        return re.sub(r"^#(include|pragma once).*\n", "", src, flags=re.M)
+def read(name):
+    src = open(os.path.join(CSRC, name)).read()
+    src = re.sub(r"^ *typedef \w+ v\w+ __attribute__\(\(ext_vector_type\(\d+\)\)\);\n", "", src, flags=re.M)   # structs in the shim
+    return re.sub(r"^#(include|pragma once).*\n", "", src, flags=re.M)
 
+
+def spliced_attention_rows_source():
     shape = open(os.path.join(CSRC, "aqt_internal.h")).read()
     shape = shape[shape.index("struct AttnShape {"):]
     shape = shape[:shape.index("};") + 2]
@@ -67,6 +70,18 @@ def spliced_attention_rows_source():
     return '#include "vectors_on_host.h"\n' + tiles + fwd + bwd + driver
 
 
+def spliced_gemm_any_source():
+    any_ = read("gemm_any.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace any {")
+    any_ = any_[:any_.index("// Which workgroup arrangement of the forward.")] + "}\n}\n"
+    any_ = cut(any_, "__device__ __forceinline__ uint32_t pack_bf16", "__device__ __forceinline__ void split3")
+    any_ = cut(any_, "__device__ __forceinline__ v16f mfma_bf16(", "__device__ __forceinline__ v4i codes8_bf16")
+    f64 = read("gemm_any_f64.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace f64 {")
+    f64 = f64[:f64.index("template <int TN, int WN, int WK, bool PACKED, int MODE>\naqt_status")] + "}\n}\n"
+    driver = open(os.path.join(HERE, "host_emulation", "gemm_any_driver.cpp")).read()
+    return ('#include "vectors_on_host.h"\n#include "aqt.h"\n' + read("any_shape.h") + read("colsum.h") + read("epilogue.h") +
+            any_ + f64 + driver)
+
+
 def test_conv_kernels_in_bounds_and_correct_on_host(tmp_path):
     build_and_run(tmp_path, "conv_on_host", spliced_source())
 
@@ -83,12 +98,17 @@ def test_attention_kernels_for_vectorised_rows_in_bounds_and_correct_on_host(tmp
     build_and_run(tmp_path, "attention_rows_on_host", spliced_attention_rows_source())
 
 
+def test_contractions_for_any_shape_in_bounds_and_correct_on_host(tmp_path):
+    build_and_run(tmp_path, "gemm_any_on_host", spliced_gemm_any_source())
+
+
 def build_and_run(tmp_path, name, source):
     cpp = tmp_path / (name + ".cpp")
     cpp.write_text(source)
     exe = tmp_path / name
     cmd = ["g++", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
-           "-static-libubsan", "-std=c++20", "-pthread", "-I", os.path.join(HERE, "host_emulation"), str(cpp), "-o", str(exe)]
+           "-static-libubsan", "-std=c++20", "-pthread", "-I", os.path.join(HERE, "host_emulation"),
+           "-I", os.path.join(ROOT, "include"), str(cpp), "-o", str(exe)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")
