@@ -27,6 +27,7 @@
 // 8 heads of 64: 621 -> 311; 128 of 512: 2808 -> 1557; 24 of 417, 4 heads of 36: 310 -> 146.  (All products in bf16 passes:
 // 273, 1392 and 125, with the error above.)
 #include "attention_tiles.h"
+#include "bf16_terms.h"
 
 namespace aqt {
 namespace {
@@ -38,48 +39,30 @@ constexpr int kTensor = 3 * kImage;  // hi, mid, lo
 constexpr int kLd = 68;              // row stride in floats of the float32 rows and of the output image
 constexpr int kSlot = 2 * kTensor + kStep * kLd * 4;   // two tensors per tile, and the float32 rows of the first
 
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
 struct Split {   // one operand fragment: eight values of a lane as three bf16 terms
   v4i hi, mid, lo;
 };
 
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even
-  v2f f = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
-}
-__device__ __forceinline__ void split2(float a, float b, int &hi, int &mid, int &lo) {
-  const uint32_t h = pack_bf16(a, b);
-  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
-  const uint32_t m = pack_bf16(ra, rb);
-  const float qa = ra - __uint_as_float(m << 16), qb = rb - __uint_as_float(m & 0xFFFF0000u);
-  hi = static_cast<int>(h); mid = static_cast<int>(m); lo = static_cast<int>(pack_bf16(qa, qb));
-}
 __device__ __forceinline__ Split split8(float a, float b, float c, float d, float e, float f, float g, float h) {
   Split s;
   int x, y, z;
-  split2(a, b, x, y, z); s.hi.x = x; s.mid.x = y; s.lo.x = z;
-  split2(c, d, x, y, z); s.hi.y = x; s.mid.y = y; s.lo.y = z;
-  split2(e, f, x, y, z); s.hi.z = x; s.mid.z = y; s.lo.z = z;
-  split2(g, h, x, y, z); s.hi.w = x; s.mid.w = y; s.lo.w = z;
+  split3_bf16(a, b, x, y, z); s.hi.x = x; s.mid.x = y; s.lo.x = z;
+  split3_bf16(c, d, x, y, z); s.hi.y = x; s.mid.y = y; s.lo.y = z;
+  split3_bf16(e, f, x, y, z); s.hi.z = x; s.mid.z = y; s.lo.z = z;
+  split3_bf16(g, h, x, y, z); s.hi.w = x; s.mid.w = y; s.lo.w = z;
   return s;
 }
 
-__device__ __forceinline__ v16f mfma(v4i a, v4i b, v16f c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
-}
 __device__ __forceinline__ v16f mfma6(const Split &a, const Split &b, v16f c) {   // smallest terms first
-  c = mfma(a.lo, b.hi, c);
-  c = mfma(a.hi, b.lo, c);
-  c = mfma(a.mid, b.mid, c);
-  c = mfma(a.mid, b.hi, c);
-  c = mfma(a.hi, b.mid, c);
-  return mfma(a.hi, b.hi, c);
+  c = mfma_bf16(a.lo, b.hi, c);
+  c = mfma_bf16(a.hi, b.lo, c);
+  c = mfma_bf16(a.mid, b.mid, c);
+  c = mfma_bf16(a.mid, b.hi, c);
+  c = mfma_bf16(a.hi, b.mid, c);
+  return mfma_bf16(a.hi, b.hi, c);
 }
 // Rows lr of an image set, head positions 16 s + 8 lk .. + 7: contraction along the head.
 __device__ __forceinline__ Split read_rows(const uint8_t *tensor, int s, int lr, int lk) {

@@ -15,6 +15,7 @@
 // Measured against the one-thread-per-output kernels these replace: forward 4099 x 520 x 1000, int8 codes, 17 us (7902);
 // 40 x 512 -> 2048 3.5 us (about 170).
 #include "any_shape.h"
+#include "bf16_terms.h"
 #include "colsum.h"
 #include "epilogue.h"
 
@@ -22,10 +23,6 @@ namespace aqt {
 namespace {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
 // LDS rows are CH chunks of 16 bytes without padding; the chunk index is XORed with row bits so that the rows
 // of a fragment read spread over all banks.
@@ -237,29 +234,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
 constexpr int kChain = 512;
 constexpr int kCh = 4;        // 16-byte chunks of an LDS row: kSlice bf16 values
 
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // round to nearest even
-  v2f f = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
-}
-__device__ __forceinline__ void split3(float a, float b, int &hi, int &mid, int &lo) {
-  const uint32_t h = pack_bf16(a, b);
-  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
-  const uint32_t m = pack_bf16(ra, rb);
-  const float qa = ra - __uint_as_float(m << 16), qb = rb - __uint_as_float(m & 0xFFFF0000u);
-  hi = static_cast<int>(h); mid = static_cast<int>(m); lo = static_cast<int>(pack_bf16(qa, qb));
-}
 // four floats -> their four bf16 pieces of each of the three images
 __device__ __forceinline__ void store_split(uint8_t *at, int image, v4f v) {
   v2i h, m, l;
   int x, y, z;
-  split3(v.x, v.y, x, y, z); h.x = x; m.x = y; l.x = z;
-  split3(v.z, v.w, x, y, z); h.y = x; m.y = y; l.y = z;
+  split3_bf16(v.x, v.y, x, y, z); h.x = x; m.x = y; l.x = z;
+  split3_bf16(v.z, v.w, x, y, z); h.y = x; m.y = y; l.y = z;
   *reinterpret_cast<v2i *>(at) = h;
   *reinterpret_cast<v2i *>(at + image) = m;
   *reinterpret_cast<v2i *>(at + 2 * image) = l;
-}
-__device__ __forceinline__ v16f mfma_bf16(v4i a, v4i b, v16f c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 __device__ __forceinline__ v4i codes8_bf16(uint32_t x, uint32_t y) {   // eight int8 codes in order
   float f[8];

@@ -14,12 +14,16 @@
 // Every product is exact in float32, so the only other error is the float32
 // accumulation itself.
 //
+// That is for the sizes of a grid of tiles (plan_bwd).  Small problems on that grid go to gemm_any.hip (three
+// terms), sizes and alignments off it to gemm_any_f64.hip (float64 sums).
+//
 // The weight-only forward (Sec. 4.1, configurations I8W / I4W: float32
 // activations, integer weights) is the same kind of contraction and runs on the
 // dX tile program:  y = act((x . wq) * s_w + bias).
 #include <type_traits>
 
 #include "aqt_internal.h"
+#include "bf16_terms.h"
 #include "colsum.h"
 #include "epilogue.h"
 
@@ -33,34 +37,12 @@ extern "C" int aqt_timeline_bwd(void *dst, size_t bytes) {
 namespace aqt {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 
 __device__ __forceinline__ bool mask_bit(const uint32_t *__restrict__ mask, int64_t i) {
   return (mask[i >> 5] >> (i & 31)) & 1u;
-}
-
-// Two floats -> packed bf16 pair (round to nearest even).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  v2f f = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, v2bf));
-}
-
-// hi/lo split of two floats: hi = bf16(a), lo = bf16(a - float(hi)).
-__device__ __forceinline__ void split_bf16(float a, float b, uint32_t &hi, uint32_t &lo) {
-  hi = pack_bf16(a, b);
-  const float ha = __uint_as_float(hi << 16), hb = __uint_as_float(hi & 0xFFFF0000u);
-  lo = pack_bf16(a - ha, b - hb);
-}
-
-__device__ __forceinline__ v16f mfma_bf16(v4i a, v4i b, v16f c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
 // Column sums of dy without a dW to ride on: (64 columns x row slab) partials, then a fold.
@@ -992,7 +974,7 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
   const BwdPlan p = plan_bwd(M, K, N);
   uint8_t *base = static_cast<uint8_t *>(ws);
   // 16-byte vector accesses on dy and on the buffers carved from the workspace (their
-  // offsets are multiples of 256); anything else takes the general kernels
+  // offsets are multiples of 256); anything else takes the float64 kernels
   const bool dy_aligned = reinterpret_cast<uintptr_t>(dy) % 16 == 0 && reinterpret_cast<uintptr_t>(ws) % 16 == 0;
   if (dx) {
     const bool grid = p.dx_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->s_w) % 16 == 0 &&

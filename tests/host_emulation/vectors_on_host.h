@@ -58,7 +58,6 @@ inline v16f mfma_bf16(v4i a, v4i b, v16f c) {
   wave_meets().arrive_and_wait();
   return c;
 }
-inline v16f mfma(v4i a, v4i b, v16f c) { return mfma_bf16(a, b, c); }
 // v_mfma_i32_32x32x32_i8: lane (lr, lk) supplies A[lr][16 lk .. 16 lk + 15] and B[16 lk .. 16 lk + 15][lr]
 inline v16i __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i a, v4i b, v16i c, int, int, int) {
   static v4i ta[1024], tb[1024];

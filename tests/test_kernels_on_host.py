@@ -50,6 +50,12 @@ def read(name):
     return re.sub(r"^#(include|pragma once).*\n", "", src, flags=re.M)
 
 
+def bf16_terms():
+    """bf16_terms.h without what the shim stands in for: the conversion and the matrix instruction."""
+    src = cut(read("bf16_terms.h"), "__device__ __forceinline__ uint32_t pack_bf16", "__device__ __forceinline__ v16f mfma_bf16")
+    return cut(src, "__device__ __forceinline__ v16f mfma_bf16", "// hi = bf16(a), lo")
+
+
 def spliced_attention_rows_source():
     shape = open(os.path.join(CSRC, "aqt_internal.h")).read()
     shape = shape[shape.index("struct AttnShape {"):]
@@ -60,26 +66,22 @@ def spliced_attention_rows_source():
     bwd = read("attention_bwd.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace bwd_rows {")
     bwd = bwd[:bwd.index("bool attention_rows_ok")] + "}\n"
     # instructions that the shim stands in for
-    bwd = cut(bwd, "__device__ __forceinline__ uint32_t pack_bf16", "__device__ __forceinline__ void split2")
-    bwd = cut(bwd, "__device__ __forceinline__ v16f mfma(", "__device__ __forceinline__ v16f mfma6")
     bwd = cut(bwd, "  typedef __attribute__((address_space(3)))", "  return v4i{a.x, a.y, b.x, b.y};")
     bwd = bwd.replace("  return v4i{a.x, a.y, b.x, b.y};", "  const v2i a = read_tr_b16(image + at0), b = read_tr_b16(image + at1);\n  return v4i{a.x, a.y, b.x, b.y};")
     assert bwd.count('asm volatile("" : "+') == 2
     bwd = re.sub(r' *asm volatile\("" : "\+[sv]"\(\w+\)\);\n', "", bwd)
     driver = open(os.path.join(HERE, "host_emulation", "attention_rows_driver.cpp")).read()
-    return '#include "vectors_on_host.h"\n' + tiles + fwd + bwd + driver
+    return '#include "vectors_on_host.h"\n' + bf16_terms() + tiles + fwd + bwd + driver
 
 
 def spliced_gemm_any_source():
     any_ = read("gemm_any.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace any {")
     any_ = any_[:any_.index("// Which workgroup arrangement of the forward.")] + "}\n}\n"
-    any_ = cut(any_, "__device__ __forceinline__ uint32_t pack_bf16", "__device__ __forceinline__ void split3")
-    any_ = cut(any_, "__device__ __forceinline__ v16f mfma_bf16(", "__device__ __forceinline__ v4i codes8_bf16")
     f64 = read("gemm_any_f64.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace f64 {")
     f64 = f64[:f64.index("template <int TN, int WN, int WK, bool PACKED, int MODE>\naqt_status")] + "}\n}\n"
     driver = open(os.path.join(HERE, "host_emulation", "gemm_any_driver.cpp")).read()
-    return ('#include "vectors_on_host.h"\n#include "aqt.h"\n' + read("any_shape.h") + read("colsum.h") + read("epilogue.h") +
-            any_ + f64 + driver)
+    return ('#include "vectors_on_host.h"\n#include "aqt.h"\n' + read("any_shape.h") + bf16_terms() + read("colsum.h") +
+            read("epilogue.h") + any_ + f64 + driver)
 
 
 def test_conv_kernels_in_bounds_and_correct_on_host(tmp_path):
