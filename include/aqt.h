@@ -18,9 +18,11 @@
  *     aqt_workspace_bytes(), 256-byte aligned.  Calls that share a workspace
  *     must be ordered on one stream.
  *   - Tensors are dense row-major.  X is [M,K], W is [K,N] (K = fan-in, N =
- *     output channels), Y is [M,N].  Any M, K, N >= 1 is accepted; shapes that
- *     do not meet a tuned kernel's divisibility take a slower general kernel
- *     with identical results.
+ *     output channels), Y is [M,N].  Any M, K, N >= 1 is accepted.  Which kernel
+ *     takes a call depends on its sizes and alignment (the tuned tiles for large
+ *     problems that they divide, others for small ones and for the rest); integer
+ *     sums and codes are the same in all of them, float contractions differ in how
+ *     many terms and sums they keep, as said at each entry point.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued and the call returns; argument errors are reported
  *     synchronously through the return value and enqueue nothing.
@@ -98,6 +100,7 @@ int aqt_last_hip_error(void);                /* hipError_t of this thread's last
 int aqt_version(void);
 
 /* Bytes of workspace an op needs for the given shape (host computation, no GPU). 0 on bad args. */
+/* The backward ops' need does not fall as M grows: sized for the longest batch, it serves shorter ones. */
 size_t aqt_workspace_bytes(int op, int64_t M, int64_t K, int64_t N, int bits_x, int bits_w);
 
 /*
@@ -240,9 +243,11 @@ aqt_status aqt_quantize_with_absmax(const float *x, int64_t rows, int64_t cols, 
  *   v[m,n] = (sum_k x[m,k] * wq[k,n]) * s_w[n] (+ bias[n]);  y = v | swish(v) | glu(v)
  *   x [M,K] float32; wq_packed, s_w as produced by aqt_quantize_weights; y float32
  *   [M,N] ([M,N/2] for GLU).
- * A float contraction: x is split into two bf16 terms (16 significant bits), the codes
+ * A float contraction: for sizes that the tuned tiles divide x is split into two bf16 terms
+ * (16 significant bits; three, all 24, for small problems), the codes
  * are exact in bf16, accumulation is float32; every output lies within 1e-4 of the
- * sum of the magnitudes of its terms from the exact value (typically 1e-6).
+ * sum of the magnitudes of its terms from the exact value (typically 1e-6).  Other sizes
+ * and tensors that are not 16-byte aligned are float64 sums, rounded once.
  * Needs aqt_workspace_bytes(AQT_OP_DENSE_FWD_WONLY, ., K, N, ., .) of workspace.
  */
 aqt_status aqt_dense_fwd_wonly(const float *x, const void *wq_packed, const float *s_w, int64_t M, int64_t K,
@@ -278,8 +283,12 @@ aqt_status aqt_dense_fwd(const float *x, const float *w, int64_t M, int64_t K, i
  * aqt_workspace_bytes(AQT_OP_DENSE_BWD_EPI, ...).  Any of dx, dw,
  * dbias may be NULL to skip it.  A NULL mask means "1 where the group's scale
  * is non-zero", which is what abs-max scaling always produces.  Results are
- * float32; the contractions run as two bf16 MFMA passes over a hi/lo split of
- * the float operand (codes are exact in bf16), accumulated in float32.
+ * float32.  For sizes that the tuned tiles divide the contractions run as two bf16 MFMA
+ * passes over a hi/lo split of the float operand (codes are exact in bf16), or as three
+ * over all 24 bits for small problems, accumulated in float32; an infinity, or a value
+ * that rounds to one in bf16, gives NaN there.  Other sizes (dx: K % 128, N % 32, M < 128;
+ * dw: K % 256, N % 128) and tensors that are not 16-byte aligned are float64 sums,
+ * rounded once.  dbias is a float64 sum.
  * Uses saved->xq, s_x, wq_kn, s_w and the masks.
  */
 aqt_status aqt_dense_bwd(const float *dy, const aqt_saved *saved, int64_t M, int64_t K, int64_t N,

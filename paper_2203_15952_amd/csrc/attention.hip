@@ -26,6 +26,9 @@
 // the keys 32 nb + 8 (r / 4) + r % 4 and that + 4, which is where the accumulator layout of
 // the first product put them.  LDS rows are 68 floats: 16-byte aligned, and rows map to
 // different banks.  The result leaves through LDS as whole rows.
+//
+// These kernels take any head width and alignment.  Heads of a multiple of four positions on 16-byte aligned tensors go
+// to attention_fwd.hip (the same bits) and attention_bwd.hip.
 #include "aqt_internal.h"
 
 namespace aqt {

@@ -24,8 +24,9 @@
 // holds.  Two LDS slots: a tile is staged and split while the one before it is multiplied, one barrier per tile.
 //
 // Measured in us, all products in float32 (attention.hip) -> scores in float32, the rest here: 32 utterances of 400 frames,
-// 8 heads of 64: 621 -> 311; 128 of 512: 2808 -> 1557; 24 of 417, 4 heads of 36: 310 -> 146.  (All products in bf16 passes:
-// 273, 1392 and 125, with the error above.)
+// 8 heads of 64: 621 -> 306; 128 of 512: 2808 -> 1500; 24 of 417, 4 heads of 36: 310 -> 146.  (All products in bf16 passes:
+// 273, 1392 and 125, with the error above.)  The matrix pipes are busy 48 and 50 % of the cycles of the two kernels inside an
+// encoder layer (profiles/encoder_layer_12800_tokens.txt).
 #include "attention_tiles.h"
 #include "bf16_terms.h"
 

@@ -8,7 +8,8 @@
 //   the window test only in tiles that a window cuts, the rescaling of the accumulator only when the maximum moved
 //     (it multiplies by one otherwise), frame indices in 32 bits;
 // Measured in us, before -> here: 32 utterances of 400 frames, 8 heads of 64: 172 -> 144; 128 of 512: 702 -> 619 (the float32
-// matrix instructions alone take 440 at the full clock); 24 of 417, 4 heads of 36: 84 -> 69.  Registers bound it to two
+// matrix instructions alone take 440 at the full clock; inside an encoder layer the matrix pipes are busy 58 % of the
+// kernel's cycles, profiles/encoder_layer_12800_tokens.txt); 24 of 417, 4 heads of 36: 84 -> 69.  Registers bound it to two
 // wavefronts per SIMD; at three (16 registers spilled) 150 and 653.  The backward's six-pass bf16 products would take
 // 88 here, but change last bits, and with them a code in every few thousand rows of the layers behind.
 #include "attention_tiles.h"
