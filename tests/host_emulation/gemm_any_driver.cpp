@@ -12,7 +12,7 @@ template <class T> struct Exact {   // n elements on the heap, nothing behind th
   ~Exact() { free(p); }
   operator T *() const { return p; }
 };
-static void verdict(const char *what, double worst, double limit) {
+static void expect(const char *what, double worst, double limit) {
   printf("  %s: worst %.3g\n", what, worst); fflush(stdout);
   if (!(worst <= limit)) { printf("  MISMATCH\n"); bad = 1; }
 }
@@ -64,8 +64,8 @@ template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> 
     if (!(e <= worst)) worst = e;
     mx = std::max(mx, fabsf(y[m * oc + n]));
   }
-  verdict("integer sums that differ", sums, 0);
-  verdict("outputs", worst, 1e-5);
+  expect("integer sums that differ", sums, 0);
+  expect("outputs", worst, 1e-5);
   if (__float_as_uint(mx) != am[0]) { printf("  MISMATCH of the largest value\n"); bad = 1; }
 }
 
@@ -102,7 +102,7 @@ template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_
     const double e = fabs((double)out[m * oc + r] - ref) / (mag + 1e-30);
     if (!(e <= worst)) worst = e;
   }
-  verdict("error / sum |terms|", worst, limit);
+  expect("error / sum |terms|", worst, limit);
 }
 template <int TN, int WN, int WK, bool PACKED, int MODE> void rows_f64(int64_t M, int64_t R, int64_t C) {
   const int64_t tr = cdiv(MODE == 1 + AQT_EPI_GLU ? R / 2 : R, (MODE == 1 + AQT_EPI_GLU ? 8 : 16) * TN * WN), tm = cdiv(M, 32);
@@ -160,8 +160,8 @@ template <class T> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, b
       if (!(e <= worst)) worst = e;
     }
   }
-  verdict("dW, error / sum |terms|", worst, F64 ? 6.1e-8 : 3e-6);
-  verdict("bias gradient", worst_b, 6.1e-8);
+  expect("dW, error / sum |terms|", worst, F64 ? 6.1e-8 : 3e-6);
+  expect("bias gradient", worst_b, 6.1e-8);
 }
 }  // namespace aqt
 int main() {
