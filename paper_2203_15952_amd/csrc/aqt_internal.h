@@ -135,6 +135,22 @@ aqt_status launch_bwd_dw_f64(const float *dy, const int8_t *xq, const float *s_x
                              int64_t M, int64_t K, int64_t N, float *dw, double *partial, int max_slabs, float *dbias,
                              double *bias_part, hipStream_t st);
 
+aqt_status launch_dw_f64_fold(const double *partial, int slabs, int64_t K, int64_t N, const float *s_x, const float *s_w,
+                              const uint32_t *mask_w, float *dw, const double *bias_part, int bias_rows, float *dbias,
+                              hipStream_t st);
+
+// ---- the same sums on the int8 matrix cores, where there is enough work (gemm_exact.hip) -------------------------
+bool f32_codes_exact_ok(int64_t M, int64_t R, int64_t C);   // M x R results, contraction C
+aqt_status launch_bwd_dx_exact(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
+                               const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st);
+aqt_status launch_dense_fwd_wonly_exact(const float *x, const void *wq_packed, const float *s_w, int64_t M, int64_t K,
+                                        int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st);
+bool dw_exact_ok(int64_t M, int64_t K, int64_t N, int slabs);
+int dw_exact_slabs(int64_t M, int64_t K, int64_t N);
+aqt_status launch_bwd_dw_exact(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
+                               int64_t M, int64_t K, int64_t N, float *dw, double *partial, int slabs, float *dbias,
+                               double *bias_part, hipStream_t st);
+
 // ---- straight-through backward (gemm_bwd.hip) -------------------------------------
 size_t bwd_workspace_bytes(int64_t M, int64_t K, int64_t N);
 // dx_factor (optional, [M,K]): dx leaves multiplied elementwise by it (the previous layer's activation derivative)

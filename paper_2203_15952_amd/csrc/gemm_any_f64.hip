@@ -1,6 +1,7 @@
 // The float contractions of the quantized dense layer off the tuned kernels' grid (sizes that no tile divides, fewer
 // than 128 rows, tensors that are not 16-byte aligned): dX, dW and the weight-only forward with every product and sum
-// in float64 on v_mfma_f64_16x16x4_f64, rounded to float32 once.
+// in float64 on v_mfma_f64_16x16x4_f64, rounded to float32 once.  Where there is enough work gemm_exact.hip forms the same
+// sums on the int8 matrix cores (its rules say where); what is left here are the small ones.
 //
 // Nothing is split and nothing overflows or is lost on the way: a float32 value times a code is exact, infinities and
 // the largest finite values behave as in a float64 loop, and a sum of any length is as good as one.  Float32 sums of 512 products on the
@@ -13,7 +14,7 @@
 // counted), with bf16 terms 47 and 47, one thread per output 6565 and 1096.  So everything else is kept small
 // rather than clever: float32 values and int8 codes go through LDS as they are and are converted when a fragment is read
 // (one instruction per value, a small part of the products' clocks), and tiles are small so that a launch fills 256
-// compute units evenly.
+// compute units evenly.  (These figures are of the larger problems that gemm_exact.hip now takes.)
 //
 // A lane of the instruction holds one element of A (row lane % 16) and of B (column lane % 16) at contraction index
 // lane / 16.  Which positions those are is free as long as both operands agree: lane group g takes positions
@@ -444,11 +445,13 @@ aqt_status wonly_f64(const CodesArgs &a, int epilogue, hipStream_t st) {
 
 aqt_status launch_bwd_dx_f64(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
                              const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st) {
+  if (f32_codes_exact_ok(M, K, N)) return launch_bwd_dx_exact(dy, wq_kn, s_w, s_x, mask_x, factor, M, K, N, dx, st);
   return f32_codes_f64_sized<false, 0>(CodesArgs{dy, s_w, wq_kn, M, K, N, s_x, mask_x, factor, nullptr, dx}, st);
 }
 
 aqt_status launch_dense_fwd_wonly_f64(const float *x, const void *wq_packed, const float *s_w, int64_t M, int64_t K,
                                       int64_t N, int bits_w, const float *bias, int epilogue, float *y, hipStream_t st) {
+  if (f32_codes_exact_ok(M, N, K)) return launch_dense_fwd_wonly_exact(x, wq_packed, s_w, M, K, N, bits_w, bias, epilogue, y, st);
   const CodesArgs a{x, s_w, wq_packed, M, N, K, nullptr, nullptr, nullptr, bias, y};
   return packed4(bits_w) ? wonly_f64<true>(a, epilogue, st) : wonly_f64<false>(a, epilogue, st);
 }
@@ -459,9 +462,25 @@ int dw_f64_slabs(int64_t M, int64_t K, int64_t N) {
   return static_cast<int>(fill < most ? fill : most);
 }
 
+// dw or dbias null: that part is not wanted.
+aqt_status launch_dw_f64_fold(const double *partial, int slabs, int64_t K, int64_t N, const float *s_x, const float *s_w,
+                              const uint32_t *mask_w, float *dw, const double *bias_part, int bias_rows, float *dbias,
+                              hipStream_t st) {
+  const unsigned bias_blocks = dbias ? static_cast<unsigned>(cdiv(N, kColsumCols)) : 0;
+  const unsigned dw_blocks = dw ? static_cast<unsigned>(cdiv(K * N, 64)) : 0;
+  if (bias_blocks + dw_blocks == 0) return AQT_OK;
+  dw_f64_fold_kernel<<<bias_blocks + dw_blocks, kDwThreads, 0, st>>>(partial, slabs, K, N, DwFinish{s_x, s_w, mask_w}, dw,
+                                                                    bias_part, bias_rows, bias_blocks, dbias);
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
 aqt_status launch_bwd_dw_f64(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
                              int64_t M, int64_t K, int64_t N, float *dw, double *partial, int max_slabs, float *dbias,
                              double *bias_part, hipStream_t st) {
+  const int digits = dw_exact_slabs(M, K, N) < max_slabs ? dw_exact_slabs(M, K, N) : max_slabs;
+  if (dw_exact_ok(M, K, N, digits))
+    return launch_bwd_dw_exact(dy, xq, s_x, s_w, mask_w, M, K, N, dw, partial, digits, dbias, bias_part, st);
   const int64_t tiles_n = cdiv(N, kDwTile), tiles = cdiv(K, kDwTile) * tiles_n;
   const int wish = dw_f64_slabs(M, K, N);
   const int64_t rows = cdiv(cdiv(M, wish < max_slabs ? wish : max_slabs), kDwSlice) * kDwSlice, slabs = cdiv(M, rows);
@@ -472,13 +491,8 @@ aqt_status launch_bwd_dw_f64(const float *dy, const int8_t *xq, const float *s_x
       xq, dy, M, K, N, rows, partial, one ? dw : nullptr, static_cast<int>(tiles_n), static_cast<int>(tiles), fin,
       dbias ? bias_part : nullptr);
   AQT_HIP(hipGetLastError());
-  const unsigned bias_blocks = dbias ? static_cast<unsigned>(cdiv(N, kColsumCols)) : 0;
-  const unsigned dw_blocks = one ? 0 : static_cast<unsigned>(cdiv(K * N, 64));
-  if (bias_blocks + dw_blocks == 0) return AQT_OK;
-  dw_f64_fold_kernel<<<bias_blocks + dw_blocks, kDwThreads, 0, st>>>(partial, static_cast<int>(slabs), K, N, fin, dw, bias_part,
-                                                                    static_cast<int>(slabs * (tiles / tiles_n)), bias_blocks, dbias);
-  AQT_HIP(hipGetLastError());
-  return AQT_OK;
+  return launch_dw_f64_fold(partial, static_cast<int>(slabs), K, N, s_x, s_w, mask_w, one ? nullptr : dw, bias_part,
+                            static_cast<int>(slabs * (tiles / tiles_n)), dbias, st);
 }
 
 }  // namespace aqt

@@ -15,7 +15,7 @@
 // accumulation itself.
 //
 // That is for the sizes of a grid of tiles (plan_bwd).  Small problems on that grid go to gemm_any.hip (three
-// terms), sizes and alignments off it to gemm_any_f64.hip (float64 sums).
+// terms), sizes and alignments off it to gemm_any_f64.hip (float64 sums; many of them exact ones, gemm_exact.hip).
 //
 // The weight-only forward (Sec. 4.1, configurations I8W / I4W: float32
 // activations, integer weights) is the same kind of contraction and runs on the

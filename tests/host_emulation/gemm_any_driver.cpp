@@ -1,6 +1,6 @@
 // Driver of the host emulation of the contractions straight from the caller's tensors: the test splices any_shape.h,
-// colsum.h and epilogue.h, the kernels of gemm_any.hip (namespace any) and of gemm_any_f64.hip (namespace f64) in front of this
-// file.  Every tensor is an allocation of exactly its size; results are compared with plain loops written here.
+// colsum.h and epilogue.h, the kernels of gemm_any.hip (namespace any), of gemm_any_f64.hip (namespace f64) and of gemm_exact.hip
+// (namespace exact) in front of this file.  Every tensor is an allocation of exactly its size; results are compared with plain loops written here.
 namespace aqt {
 static int bad = 0;
 static uint32_t seed = 17u;
@@ -61,7 +61,7 @@ template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> 
     }
     const double ref = GLU ? v[0] * sigma(v[1]) : EPI == AQT_EPI_SWISH ? v[0] * sigma(v[0]) : v[0];
     const double e = fabs((double)y[m * oc + n] - ref) / (1.0 + fabs(ref));
-    if (!(e <= worst)) worst = e;
+    if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e;
     mx = std::max(mx, fabsf(y[m * oc + n]));
   }
   expect("integer sums that differ", sums, 0);
@@ -70,7 +70,26 @@ template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> 
 }
 
 // MODE 0: dX with a factor and a clip mask; 1 + e: weight-only forward.  kernel(f, scale, q, s_x, mask, factor, bias, out)
-template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_t R, int64_t C, double limit, Kernel kernel) {
+// `wild`: rows with an infinity, and rows whose values lie further apart than the digits of gemm_exact.hip reach
+static void disturb(float *f, int64_t row, int64_t step, int64_t length, int64_t i) {   // element j of the row: f[row + j * step]
+  for (int64_t j = 0; j < length; ++j) {
+    float &v = f[row + j * step];
+    if (i % 7 == 1) v = ldexpf(v, -(int)(j % 60));
+    if (i % 7 == 2 && j % 50 == 9) v = ldexpf(v, -30);
+    if (i % 7 == 3 && j % 2) v = ldexpf(v, 100);
+    if (i % 7 == 4) v = ldexpf(v, -140);
+    if (i % 7 == 6) v = 0.0f;
+  }
+  if (i % 7 == 5) f[row + (length - 1) * step] = i % 2 ? INFINITY : -INFINITY;
+}
+// not further from the float64 loop than the last rounding and its own sums
+static double beyond_rounding(float got, double ref, double rounded, double mag, double share) {   // rounded: what float32 held on the way
+  if (!std::isfinite((float)ref)) return std::isnan(ref) ? !std::isnan(got) : got != (float)ref;
+  if (!std::isfinite(mag) || !std::isfinite(rounded)) return got != ref;   // an infinity behind a clip mask
+  const double limit = share * rounded + 1e-13 * mag + 3e-45;
+  return fabs((double)got - ref) / limit;
+}
+template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_t R, int64_t C, double limit, Kernel kernel, bool wild = false) {
   constexpr bool GLU = MODE == 1 + AQT_EPI_GLU;
   printf("float rows, mode %d packed %d: %ld %ld %ld\n", MODE, (int)PACKED, (long)M, (long)R, (long)C);
   const int64_t oc = GLU ? R / 2 : R, ns = MODE ? R : C;
@@ -79,6 +98,8 @@ template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_
   Exact<uint32_t> mask(cdiv(M * R, 32));
   sx[0] = 1.0f;
   for (int64_t i = 0; i < M * C; ++i) f[i] = uniform();
+  if (wild)
+    for (int64_t i = 0; i < M; ++i) disturb(f, i * C, 1, C, i);
   for (int64_t i = 0; i < ns; ++i) scale[i] = 0.02f + 0.01f * uniform();
   for (int64_t i = 0; i < R; ++i) bias[i] = MODE ? uniform() : 0.0f;
   for (int64_t i = 0; i < M * R; ++i) factor[i] = uniform();
@@ -86,7 +107,7 @@ template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_
   kernel((const float *)f, (const float *)scale, (const uint8_t *)q.bytes, (const float *)sx, (const uint32_t *)mask, (const float *)factor, (const float *)bias, (float *)out);
   double worst = 0;
   for (int64_t m = 0; m < M; ++m) for (int64_t r = 0; r < oc; ++r) {
-    double v[2], mag = 0;
+    double v[2], mag = 0, held = 0;
     for (int h = 0; h < (GLU ? 2 : 1); ++h) {
       double s = 0;
       for (int64_t c = 0; c < C; ++c) {
@@ -94,15 +115,16 @@ template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_
         s += t; mag += fabs(t);
       }
       v[h] = s + bias[r + h * oc]; mag += fabs(bias[r + h * oc]);
+      if (MODE) held += fabs(s) + fabs(bias[r + h * oc]);
     }
     double ref = v[0];
     if (!MODE) ref = (mask[(m * R + r) >> 5] >> ((m * R + r) & 31) & 1) ? v[0] * factor[m * R + r] : 0.0;
     else if (GLU) ref = v[0] * sigma(v[1]);
     else if (MODE == 1 + AQT_EPI_SWISH) ref = v[0] * sigma(v[0]);
-    const double e = fabs((double)out[m * oc + r] - ref) / (mag + 1e-30);
-    if (!(e <= worst)) worst = e;
+    const double e = wild ? beyond_rounding(out[m * oc + r], ref, fabs(ref) + held, mag, limit) : fabs((double)out[m * oc + r] - ref) / (mag + 1e-30);
+    if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e;
   }
-  expect("error / sum |terms|", worst, limit);
+  expect(wild ? "error / (rounding of the result)" : "error / sum |terms|", worst, wild ? 1 : limit);
 }
 template <int TN, int WN, int WK, bool PACKED, int MODE> void rows_f64(int64_t M, int64_t R, int64_t C) {
   const int64_t tr = cdiv(MODE == 1 + AQT_EPI_GLU ? R / 2 : R, (MODE == 1 + AQT_EPI_GLU ? 8 : 16) * TN * WN), tm = cdiv(M, 32);
@@ -111,6 +133,15 @@ template <int TN, int WN, int WK, bool PACKED, int MODE> void rows_f64(int64_t M
       f64::f32_codes_f64_kernel<TN, WN, WK, PACKED, MODE>(f, scale, q, M, R, C, sx, MODE ? nullptr : mask, MODE ? nullptr : factor, MODE ? bias : nullptr, out, (int)tr);
     });
   });
+}
+template <int TJ, bool PACKED, int MODE> void rows_exact(int64_t M, int64_t R, int64_t C, bool wild, int each = 1) {
+  constexpr bool GLU = MODE == 1 + AQT_EPI_GLU;
+  const int64_t tr = cdiv(GLU ? R / 2 : R, (GLU ? 8 : 16) * TJ), tm = cdiv(M, 64);
+  float_rows<MODE, PACKED>(M, R, C, MODE > 1 ? 3e-6 : 1.2e-7, [&](auto f, auto scale, auto q, auto sx, auto mask, auto factor, auto bias, auto out) {
+    run((unsigned)(cdiv(tr, each) * tm), 256, 0, [&] {
+      exact::f32_codes_exact_kernel<TJ, PACKED, MODE>(f, scale, q, M, R, (int)C, sx, MODE ? nullptr : mask, MODE ? nullptr : factor, MODE ? bias : nullptr, out, (int)tm, (int)tr, each);
+    });
+  }, wild);
 }
 template <int TN, bool PACKED, int MODE, bool LONG> void rows_any(int64_t M, int64_t R, int64_t C) {
   const int64_t tr = R / (32 * TN), tm = cdiv(M, 32);
@@ -121,11 +152,11 @@ template <int TN, bool PACKED, int MODE, bool LONG> void rows_any(int64_t M, int
   });
 }
 
-// dW in slabs of `rows` rows, with the bias gradient; T: what a slab's partial sums are kept in
-template <class T> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, bool masked) {
+// dW in slabs of `rows` rows, with the bias gradient; T: what a slab's partial sums are kept in; TJ > 0: gemm_exact.hip
+template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, bool masked, bool wild = false) {
   constexpr bool F64 = sizeof(T) == 8;
-  const int64_t tile = F64 ? 64 : 128, tiles_n = cdiv(N, tile), tiles_k = cdiv(K, tile), slabs = cdiv(M, rows);
-  printf("dW %s: %ld %ld %ld, %ld slabs, masked %d\n", F64 ? "float64" : "bf16", (long)M, (long)K, (long)N, (long)slabs, (int)masked);
+  const int64_t tile = F64 ? 64 : 128, tiles_n = cdiv(N, tile), tiles_k = cdiv(K, TJ ? 16 * TJ : tile), slabs = cdiv(M, rows);
+  printf("dW %s: %ld %ld %ld, %ld slabs, masked %d\n", TJ ? "digits" : F64 ? "float64" : "bf16", (long)M, (long)K, (long)N, (long)slabs, (int)masked);
   Codes x(M, K, false);
   Exact<float> dy(M * N), sx(1), sw(N), dw(K * N), db(N);
   Exact<T> partial(slabs * K * N);
@@ -133,12 +164,18 @@ template <class T> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, b
   Exact<uint32_t> mask(cdiv(K * N, 32));
   sx[0] = 0.03f;
   for (int64_t i = 0; i < M * N; ++i) dy[i] = uniform();
+  if (wild)
+    for (int64_t n = 0; n < N; ++n)
+      for (int64_t m0 = 0; m0 < M; m0 += rows) disturb(dy, m0 * N + n, N, std::min(rows, M - m0), n + m0 / rows);
   for (int64_t i = 0; i < N; ++i) sw[i] = i % 5 ? 0.5f : 0.0f;
   for (int64_t i = 0; i < cdiv(K * N, 32); ++i) { uniform(); mask[i] = seed | (seed << 16); }
   const bool one = slabs == 1;
   const unsigned grid = (unsigned)(tiles_k * tiles_n * slabs), bias_blocks = (unsigned)cdiv(N, kColsumCols), dw_blocks = one ? 0 : (unsigned)cdiv(K * N, 64);
   if constexpr (F64) {
     const DwFinish fin{sx, sw, masked ? mask.p : nullptr};
+    if constexpr (TJ > 0)
+      run(grid, 256, 0, [&] { exact::bwd_dw_exact_kernel<TJ>((const int8_t *)x.bytes.p, dy, M, K, N, rows, partial, one ? dw.p : nullptr, (int)tiles_k, (int)tiles_n, (int)slabs, fin, part); });
+    else
     run(grid, 256, 0, [&] { f64::bwd_dw_f64_kernel((const int8_t *)x.bytes.p, dy, M, K, N, rows, partial, one ? dw.p : nullptr, (int)tiles_n, (int)(tiles_k * tiles_n), fin, part); });
     run(bias_blocks + dw_blocks, 256, 0, [&] { f64::dw_f64_fold_kernel(partial, (int)slabs, K, N, fin, dw, part, (int)(slabs * tiles_k), bias_blocks, db); });
   } else {
@@ -150,18 +187,18 @@ template <class T> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, b
   for (int64_t n = 0; n < N; ++n) {
     double b = 0, ba = 0;
     for (int64_t m = 0; m < M; ++m) { b += dy[m * N + n]; ba += fabs(dy[m * N + n]); }
-    worst_b = std::max(worst_b, fabs(db[n] - b) / (ba + 1e-30));
+    worst_b = std::max(worst_b, wild ? beyond_rounding(db[n], b, fabs(b), ba, 6.1e-8) : fabs(db[n] - b) / (ba + 1e-30));
     for (int64_t k = 0; k < K; ++k) {
       double s = 0, mag = 0;
       for (int64_t m = 0; m < M; ++m) { const double t = (double)sx[0] * x.v[m * K + k] * dy[m * N + n]; s += t; mag += fabs(t); }
       const int64_t at = k * N + n;
       if (masked ? !(mask[at >> 5] >> (at & 31) & 1) : sw[n] == 0.0f) s = 0;
-      const double e = fabs(dw[at] - s) / (mag + 1e-30);
-      if (!(e <= worst)) worst = e;
+      const double e = wild ? beyond_rounding(dw[at], s, fabs(s), mag, 6.1e-8) : fabs(dw[at] - s) / (mag + 1e-30);
+      if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e;
     }
   }
-  expect("dW, error / sum |terms|", worst, F64 ? 6.1e-8 : 3e-6);
-  expect("bias gradient", worst_b, 6.1e-8);
+  expect(wild ? "dW, error / (rounding of the result)" : "dW, error / sum |terms|", worst, wild ? 1 : F64 ? 6.1e-8 : 3e-6);
+  expect("bias gradient", worst_b, wild ? 1 : 6.1e-8);
 }
 }  // namespace aqt
 int main() {
@@ -175,10 +212,15 @@ int main() {
   rows_f64<1, 1, 8, false, 0>(33, 17, 300); rows_f64<1, 1, 8, false, 0>(5, 15, 3); rows_f64<2, 1, 8, true, 1 + kSwish>(34, 33, 77);
   rows_f64<1, 4, 1, false, 0>(65, 66, 37); rows_f64<1, 4, 1, true, 1 + kNone>(31, 65, 17); rows_f64<1, 4, 1, true, 1 + kNone>(3, 3, 15);
   rows_f64<2, 2, 1, false, 1 + kGlu>(33, 70, 33); rows_f64<2, 1, 8, true, 1 + kGlu>(33, 34, 129); rows_f64<2, 2, 1, false, 1 + kGlu>(2, 2, 1);
+  rows_exact<4, false, 0>(65, 66, 64, false); rows_exact<5, false, 0>(33, 170, 200, true, 2); rows_exact<5, false, 0>(64, 33, 133, true);
+  rows_exact<5, true, 1 + kNone>(17, 97, 131, true, 2); rows_exact<4, true, 1 + kGlu>(70, 70, 65, true); rows_exact<4, false, 1 + kGlu>(5, 98, 190, true);
+  rows_exact<5, false, 1 + kSwish>(9, 19, 127, false); rows_exact<4, true, 1 + kNone>(64, 64, 128, true);
   rows_any<1, false, 0, false>(33, 128, 96); rows_any<2, false, 0, false>(33, 128, 32); rows_any<2, true, 1 + kGlu, false>(33, 128, 320);
   rows_any<1, false, 0, true>(7, 32, 4640); rows_any<1, true, 1 + kSwish, true>(3, 32, 4128);
   weights<double>(70, 66, 65, 64, false); weights<double>(130, 3, 2, 64, true); weights<double>(33, 64, 70, 64, true); weights<double>(1, 1, 1, 64, false);
   weights<double>(200, 130, 5, 128, true);
+  weights<double, 4>(70, 66, 65, 64, false); weights<double, 5>(200, 81, 33, 128, true, true); weights<double, 5>(64, 97, 5, 64, true, true);
+  weights<double, 4>(329, 4, 66, 192, false, true); weights<double, 5>(130, 193, 17, 192, true, true);
   weights<float>(70, 128, 128, 64, true); weights<float>(33, 256, 128, 64, false); weights<float>(1, 128, 128, 32, true);
   printf(bad ? "MISMATCH\n" : "ok\n"); return bad;
 }

@@ -34,6 +34,31 @@ inline bool __any(bool p) {
   wave_meets().arrive_and_wait();
   return any;
 }
+inline uint64_t __ballot(bool p) {
+  static uint8_t table[1024];
+  table[threadIdx.x] = p;
+  wave_meets().arrive_and_wait();
+  uint64_t r = 0;
+  for (unsigned l = 0; l < 64; ++l) r |= (uint64_t)(table[(threadIdx.x & ~63u) + l] != 0) << l;
+  wave_meets().arrive_and_wait();
+  return r;
+}
+inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
+template <class T> inline T lane_value(T v, unsigned from) {   // of another lane of the wavefront
+  static T table[1024];
+  table[threadIdx.x] = v;
+  wave_meets().arrive_and_wait();
+  v = table[(threadIdx.x & ~63u) | (from & 63u)];
+  wave_meets().arrive_and_wait();
+  return v;
+}
+inline int __shfl(int v, int lane) { return lane_value(v, (unsigned)lane); }
+inline double __shfl_xor(double v, int off) { return lane_value(v, (threadIdx.x & 63u) ^ (unsigned)off); }
+inline float load_f32(const float *base, uint32_t lane_bytes, uint32_t uniform_bytes) {
+  return *(const float *)((const char *)base + lane_bytes + uniform_bytes);
+}
+inline int anew(int v) { return v; }
+inline void __builtin_amdgcn_sched_barrier(int) {}
 inline uint32_t bf16_bits(float f) {   // round to nearest even
   const uint32_t u = __float_as_uint(f);
   if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;
@@ -73,6 +98,23 @@ inline v16i __builtin_amdgcn_mfma_i32_32x32x32_i8(v4i a, v4i b, v16i c, int, int
       for (int k = 0; k < 16; ++k) c[r] += x[k] * y[k];
     }
   }
+  wave_meets().arrive_and_wait();
+  return c;
+}
+// v_mfma_i32_16x16x64_i8: lane (lc = lane % 16, lg = lane / 16) supplies A[lc][16 lg .. 16 lg + 15] and B[16 lg .. 16 lg + 15][lc];
+// element r of its accumulator is row 4 lg + r, column lc
+inline v4i __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i a, v4i b, v4i c, int, int, int) {
+  static v4i ta[1024], tb[1024];
+  const unsigned base = threadIdx.x & ~63u, lane = threadIdx.x & 63u, lc = lane & 15u, lg = lane >> 4;
+  ta[threadIdx.x] = a; tb[threadIdx.x] = b;
+  wave_meets().arrive_and_wait();
+  for (unsigned r = 0; r < 4; ++r)
+    for (unsigned g = 0; g < 4; ++g) {
+      int8_t x[16], y[16];
+      memcpy(x, &ta[base + 16 * g + 4 * lg + r], 16);
+      memcpy(y, &tb[base + 16 * g + lc], 16);
+      for (int k = 0; k < 16; ++k) c[r] += x[k] * y[k];
+    }
   wave_meets().arrive_and_wait();
   return c;
 }

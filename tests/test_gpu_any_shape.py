@@ -1,5 +1,5 @@
 """GPU: the contractions straight from the caller's tensors (gemm_any.hip: the forward for any shape and small problems
-on the tuned kernels' grid; gemm_any_f64.hip: the float ones off that grid) at the sizes where they can go wrong: around the matrix-core steps and groups of the contraction, one row or channel over a
+on the tuned kernels' grid; gemm_any_f64.hip and gemm_exact.hip: the float ones off that grid) at the sizes where they can go wrong: around the matrix-core steps and groups of the contraction, one row or channel over a
 block, odd row lengths, every workgroup arrangement, one slab and several."""
 import numpy as np
 import pytest
@@ -135,8 +135,9 @@ def rounded_once(got, ref, terms, mag):
     assert bool(fine.all()), (int((~fine).sum()), fine.numel())
 
 
-def float64_products(M, K, N, moved=False, wild=False):
-    """dX, dW and the weight-only forward of one layer with their float64 values; moved: tensors that are 4-byte aligned only."""
+def float64_products(M, K, N, moved=False, wild=False, change=None):
+    """dX, dW and the weight-only forward of one layer with their float64 values; moved: tensors that are 4-byte aligned only;
+    change: what is done to the float operands."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(M + 3 * K + N)
 
@@ -156,6 +157,8 @@ def float64_products(M, K, N, moved=False, wild=False):
             t[0, 0], t[M // 2, 1], t[M - 1, 2] = float("inf"), 3.4028234e38, float("-inf")
             t[M // 3, 3:5] = torch.tensor([3.0e38, -3.0e38], device="cuda")
             t[1, :] = 1e-41
+    if change:
+        change(dy), change(xf)
     dy, xf = put(dy), put(xf)
     dx, dw, _ = B.aqt_dense_bwd(dy, sv, 8, 8)
     y = B.aqt_dense_fwd_wonly(xf, sv.wq_packed, sv.s_w, N, 8)
@@ -196,6 +199,33 @@ def test_off_the_grid_infinite_and_huge_values(M, K, N):
             continue
         ref32 = ref.float().double()   # a float64 result beyond float32 is an infinity
         rounded_once(got, torch_where_finite(ref32, ref), terms, mag.nan_to_num(0.0, 0.0, 0.0))
+
+
+@pytest.mark.parametrize("pattern", ["few", "many", "row", "zeros"])
+@pytest.mark.parametrize("M,K,N", [(1500, 345, 519), (7600, 67, 128), (500, 1001, 1024)])
+def test_off_the_grid_values_far_apart(M, K, N, pattern):
+    """Large enough for the digits of gemm_exact.hip, values further apart in a row or column than the digits reach: a few of
+    them, most of them, rows and columns with an infinity among ordinary ones, rows and columns of zeros."""
+    import torch
+    print("[float64 sums, values far apart]", M, K, N, pattern, flush=True)
+
+    def change(t):
+        gen = torch.Generator(device="cuda").manual_seed(t.shape[1])
+        if pattern == "few":
+            t[torch.rand(t.shape, device="cuda", generator=gen) < 2e-4] *= 2.0 ** -27
+        elif pattern == "many":
+            t *= torch.exp2(torch.randint(-60, 40, t.shape, device="cuda", generator=gen).float())
+        elif pattern == "row":
+            t[5, 7], t[M // 2 + 1, t.shape[1] - 1], t[M - 1, 3] = float("inf"), float("nan"), 3.0e38
+        else:
+            t[64:130], t[:, 10:30] = 0.0, 0.0
+            t[3, :] *= 2.0 ** -140
+
+    for what, (got, ref, terms, mag) in float64_products(M, K, N, change=change).items():
+        off = {"dx": K % 128 or N % 32, "dw": K % 256 or N % 128, "y": N % 128 or K % 32}[what]
+        if off:
+            ref32 = ref.float().double()
+            rounded_once(got, torch_where_finite(ref32, ref), terms, mag.nan_to_num(0.0, 0.0, 0.0))
 
 
 def torch_where_finite(ref32, ref):

@@ -1,5 +1,5 @@
 """The depthwise-convolution and attention kernels and the contractions straight from the caller's tensors
-(gemm_any.hip, gemm_any_f64.hip) run on the host, thread by thread, under the address
+(gemm_any.hip, gemm_any_f64.hip, gemm_exact.hip) run on the host, thread by thread, under the address
 and undefined-behaviour sanitizers: every global and LDS access of launch geometries like the GPU tests'
 is checked against exactly sized buffers, and the results against float64 loops in the drivers.  The
 kernels' source is taken as it is (HIP headers replaced by a small vocabulary header, launchers cut off,
@@ -79,9 +79,12 @@ def spliced_gemm_any_source():
     any_ = any_[:any_.index("// Which workgroup arrangement of the forward.")] + "}\n}\n"
     f64 = read("gemm_any_f64.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace f64 {")
     f64 = f64[:f64.index("template <int TN, int WN, int WK, bool PACKED, int MODE>\naqt_status")] + "}\n}\n"
+    exact = read("gemm_exact.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace exact {")
+    exact = exact[:exact.index("// Tiles of at most six blocks of sixteen")] + "}\n}\n"
+    exact = cut(exact, "__device__ __forceinline__ float load_f32", "__device__ __forceinline__ double power_of_two")   # the shim has its own
     driver = open(os.path.join(HERE, "host_emulation", "gemm_any_driver.cpp")).read()
     return ('#include "vectors_on_host.h"\n#include "aqt.h"\n' + read("any_shape.h") + bf16_terms() + read("colsum.h") +
-            read("epilogue.h") + any_ + f64 + driver)
+            read("epilogue.h") + any_ + f64 + exact + driver)
 
 
 def test_conv_kernels_in_bounds_and_correct_on_host(tmp_path):
