@@ -24,9 +24,13 @@
 // holds.  Two LDS slots: a tile is staged and split while the one before it is multiplied, one barrier per tile.
 //
 // Measured in us, all products in float32 (attention.hip) -> scores in float32, the rest here: 32 utterances of 400 frames,
-// 8 heads of 64: 621 -> 306; 128 of 512: 2808 -> 1500; 24 of 417, 4 heads of 36: 310 -> 146.  (All products in bf16 passes:
-// 273, 1392 and 125, with the error above.)  The matrix pipes are busy 48 and 50 % of the cycles of the two kernels inside an
-// encoder layer (profiles/encoder_layer_12800_tokens.txt).
+// 8 heads of 64: 621 -> 295; 128 of 512: 2808 -> 1455; 24 of 417, 4 heads of 36: 310 -> 136.  What every tile pays counts:
+// window tests and zeros beyond the head or the utterance stand under branches of their own, and the constant part of an LDS
+// address goes into the instruction (310 -> 295, 1510 -> 1453, 146 -> 136, the same bits).  Before that, all products in bf16
+// passes took 273, 1392 and 125 against 306, 1500 and 146, with the error above.  The matrix pipes were then busy 48 and 50 % of the
+// cycles of the two kernels inside an encoder layer (profiles/encoder_layer_12800_tokens.txt).
+#include <type_traits>
+
 #include "attention_tiles.h"
 #include "bf16_terms.h"
 
@@ -73,19 +77,20 @@ __device__ __forceinline__ Split read_rows(const uint8_t *tensor, int s, int lr,
 }
 // Head columns 32 blk + lr, the eight rows 16 s + 8 (e / 4) + 4 lk + e % 4: contraction along the rows, in the order
 // in which elements 8 s .. 8 s + 7 of an accumulator lane hold them.
-__device__ __forceinline__ v4i read_tr8(const uint8_t *image, int at0, int at1) {
+template <int AT>
+__device__ __forceinline__ v4i read_tr8(uint32_t at) {   // LDS addresses at + AT and eight rows on: the constant goes into the instruction
   typedef __attribute__((address_space(3))) v4s *lds_v4s;
-  const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(image));
-  const v2i a = __builtin_bit_cast(v2i, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_v4s>(base + at0)));
-  const v2i b = __builtin_bit_cast(v2i, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_v4s>(base + at1)));
+  const v2i a = __builtin_bit_cast(v2i, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_v4s>(at + AT)));
+  const v2i b = __builtin_bit_cast(v2i, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_v4s>(at + AT + 8 * kRowBytes)));
   return v4i{a.x, a.y, b.x, b.y};
 }
-__device__ __forceinline__ Split read_cols(const uint8_t *tensor, int s, int blk, int lane) {
+template <int S>
+__device__ __forceinline__ Split read_cols(const uint8_t *tensor, int blk, int lane) {
   const int i = lane & 15, c = i & 3, chunk = 4 * blk + 2 * ((lane >> 4) & 1) + (c >> 1);
-  const int row0 = 16 * s + 4 * (lane >> 5) + (i >> 2), row1 = row0 + 8;   // the same row modulo 8
-  const int in_row = ((chunk ^ (row0 & 7)) << 4) + 8 * (c & 1);
-  const int at0 = row0 * kRowBytes + in_row, at1 = row1 * kRowBytes + in_row;
-  return Split{read_tr8(tensor, at0, at1), read_tr8(tensor + kImage, at0, at1), read_tr8(tensor + 2 * kImage, at0, at1)};
+  const int row = 4 * (lane >> 5) + (i >> 2);   // the first of eight, the same modulo 8 in every group of sixteen
+  const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(tensor)) + row * kRowBytes + ((chunk ^ (row & 7)) << 4) + 8 * (c & 1);
+  constexpr int kAt = 16 * S * kRowBytes;
+  return Split{read_tr8<kAt>(at), read_tr8<kAt + kImage>(at), read_tr8<kAt + 2 * kImage>(at)};
 }
 
 // A thread's share of a tile: eight head positions of one row (rows beyond the utterance are read from its last one).
@@ -106,8 +111,11 @@ template <int PIECES>
 __device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnShape &g, int row0, bool rows, float *floats = nullptr) {
   const int piece = threadIdx.x & 7, row = static_cast<int>(threadIdx.x >> 3);
   const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (8 * piece >= g.dh || (rows && row0 + row >= g.T)) v.a = zero;
-  if (8 * piece + 4 >= g.dh || (rows && row0 + row >= g.T)) v.b = zero;
+  if (8 * PIECES > g.dh) {   // uniform, as the next: most tiles pay for neither
+    if (8 * piece >= g.dh) v.a = zero;
+    if (8 * piece + 4 >= g.dh) v.b = zero;
+  }
+  if (rows && row0 + kStep > g.T && row0 + row >= g.T) v.a = v.b = zero;
   if (PIECES == 8 || piece < PIECES) {
     const Split s = split8(v.a.x, v.a.y, v.a.z, v.a.w, v.b.x, v.b.y, v.b.z, v.b.w);
     uint8_t *p = tensor + row * kRowBytes + ((piece ^ (row & 7)) << 4);
@@ -383,19 +391,23 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
     if (!active || j0 > some_hi || j0 + kStep - 1 < some_lo) return;
     v16f s, dp;
     first_products<KS>(slot, q, go, s, dp, lr, lk);   // S^T: keys x this lane's query; dP^T
-    const bool whole = j0 >= all_lo && j0 + kStep - 1 <= all_hi;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = j0 + 8 * (r >> 2) + 4 * lk + (r & 3);
-      const float p = __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - L);
-      s[r] = (whole || (j >= wlo && j <= whi)) ? p * (dp[r] - D) : 0.0f;
+    for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - L) * (dp[r] - D);
+    if (j0 < all_lo || j0 + kStep - 1 > all_hi) {   // cut by a window: a loop of its own, or every tile pays for the test
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int j = j0 + 8 * (r >> 2) + 4 * lk + (r & 3);
+        s[r] = j >= wlo && j <= whi ? s[r] : 0.0f;
+      }
     }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    auto add_half = [&](auto half) {
+      constexpr int k = decltype(half)::value;
       const Split d = split8(s[8 * k], s[8 * k + 1], s[8 * k + 2], s[8 * k + 3], s[8 * k + 4], s[8 * k + 5], s[8 * k + 6], s[8 * k + 7]);
 #pragma unroll
-      for (int blk = 0; blk < DB; ++blk) dq[blk] = mfma6(read_cols(slot, k, blk, lane), d, dq[blk]);   // dQ^T += K^T dS^T
-    }
+      for (int blk = 0; blk < DB; ++blk) dq[blk] = mfma6(read_cols<k>(slot, blk, lane), d, dq[blk]);   // dQ^T += K^T dS^T
+    };
+    add_half(std::integral_constant<int, 0>{});
+    add_half(std::integral_constant<int, 1>{});
   };
   run_tiles(lds, jmin / kStep * kStep, jmax, load, stage, compute);
   if (!active) return;
@@ -469,29 +481,37 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
     const int at = slot == lds ? 0 : 1;
     v16f s, dp;
     first_products<KS>(slot, kk, vv, s, dp, lr, lk);   // S: queries x this lane's key; dP
-    const bool whole = t0 >= all_lo && t0 + kStep - 1 <= all_hi && jw + 31 < g.T;
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
-      const v4f L4 = *reinterpret_cast<const v4f *>(&Ls[at][8 * r4 + 4 * lk]), D4 = *reinterpret_cast<const v4f *>(&Ds[at][8 * r4 + 4 * lk]);
+      const v4f L4 = *reinterpret_cast<const v4f *>(&Ls[at][8 * r4 + 4 * lk]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 4 * r4 + e;
-        const int tt = t0 + 8 * r4 + 4 * lk + e;
-        const float x = __builtin_amdgcn_exp2f(s[r] * g.scale_log2e - L4[e]);
-        const float p = (whole || (j < g.T && tt >= qlo && tt <= qhi)) ? x : 0.0f;
-        s[r] = p;
-        dp[r] = p * (dp[r] - D4[e]);
+      for (int e = 0; e < 4; ++e)
+        s[4 * r4 + e] = __builtin_amdgcn_exp2f(s[4 * r4 + e] * g.scale_log2e - L4[e]);
+    }
+    if (t0 < all_lo || t0 + kStep - 1 > all_hi || jw + 31 >= g.T) {   // cut by a window or the end of the utterance
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int tt = t0 + 8 * (r >> 2) + 4 * lk + (r & 3);
+        s[r] = j < g.T && tt >= qlo && tt <= qhi ? s[r] : 0.0f;
       }
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const v4f D4 = *reinterpret_cast<const v4f *>(&Ds[at][8 * r4 + 4 * lk]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dp[4 * r4 + e] = s[4 * r4 + e] * (dp[4 * r4 + e] - D4[e]);
+    }
+    auto add_half = [&](auto half) {
+      constexpr int k = decltype(half)::value;
       const Split p = split8(s[8 * k], s[8 * k + 1], s[8 * k + 2], s[8 * k + 3], s[8 * k + 4], s[8 * k + 5], s[8 * k + 6], s[8 * k + 7]);
 #pragma unroll
-      for (int blk = 0; blk < DB; ++blk) dv[blk] = mfma6(read_cols(slot + kTensor, k, blk, lane), p, dv[blk]);   // dV^T += dO^T P
+      for (int blk = 0; blk < DB; ++blk) dv[blk] = mfma6(read_cols<k>(slot + kTensor, blk, lane), p, dv[blk]);   // dV^T += dO^T P
       const Split d = split8(dp[8 * k], dp[8 * k + 1], dp[8 * k + 2], dp[8 * k + 3], dp[8 * k + 4], dp[8 * k + 5], dp[8 * k + 6], dp[8 * k + 7]);
 #pragma unroll
-      for (int blk = 0; blk < DB; ++blk) dk[blk] = mfma6(read_cols(slot, k, blk, lane), d, dk[blk]);             // dK^T += Q^T dS
-    }
+      for (int blk = 0; blk < DB; ++blk) dk[blk] = mfma6(read_cols<k>(slot, blk, lane), d, dk[blk]);             // dK^T += Q^T dS
+    };
+    add_half(std::integral_constant<int, 0>{});
+    add_half(std::integral_constant<int, 1>{});
   };
   run_tiles(lds, tmin / kStep * kStep, tmax, load, stage, compute);
   if (!active) return;

@@ -67,7 +67,9 @@ def spliced_attention_rows_source():
     bwd = bwd[:bwd.index("bool attention_rows_ok")] + "}\n"
     # instructions that the shim stands in for
     bwd = cut(bwd, "  typedef __attribute__((address_space(3)))", "  return v4i{a.x, a.y, b.x, b.y};")
-    bwd = bwd.replace("  return v4i{a.x, a.y, b.x, b.y};", "  const v2i a = read_tr_b16(image + at0), b = read_tr_b16(image + at1);\n  return v4i{a.x, a.y, b.x, b.y};")
+    bwd = bwd.replace("  return v4i{a.x, a.y, b.x, b.y};", "  const v2i a = read_tr_b16(at + AT), b = read_tr_b16(at + AT + 8 * kRowBytes);\n  return v4i{a.x, a.y, b.x, b.y};")
+    bwd = bwd.replace("v4i read_tr8(uint32_t at)", "v4i read_tr8(const uint8_t *at)")
+    bwd = bwd.replace("const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(tensor))", "const uint8_t *const at = tensor")
     assert bwd.count('asm volatile("" : "+') == 2
     bwd = re.sub(r' *asm volatile\("" : "\+[sv]"\(\w+\)\);\n', "", bwd)
     driver = open(os.path.join(HERE, "host_emulation", "attention_rows_driver.cpp")).read()
