@@ -113,6 +113,25 @@ def test_layernorm_quantize(M, D, affine, bits):
     np.testing.assert_array_equal(host(y3), y_h)
 
 
+@pytest.mark.parametrize("M,D", [(1, 4), (5, 512), (9, 516), (70, 1024), (3, 1028), (7, 143)])
+def test_layernorm_of_values_only_reports_what_is_not_finite(M, D):
+    """Without codes the rows are the same bits as with them, and a value that is not finite is still reported."""
+    say("layernorm, values only", M, D)
+    rng = np.random.default_rng(D)
+    x = dev((rng.standard_normal((M, D)) * 3 + 1).astype(np.float32))
+    gamma, beta = (dev(rng.standard_normal(D).astype(np.float32)) for _ in range(2))
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    _, _, want, st_want = B.aqt_layernorm_quantize(x, 8, gamma=gamma, beta=beta, want_y=True, want_stats=True)
+    _, _, y, st = B.aqt_layernorm_quantize(x, 8, gamma=gamma, beta=beta, quantize=False, want_y=True, want_stats=True, dev_status=status)
+    np.testing.assert_array_equal(host(y), host(want))
+    np.testing.assert_array_equal(host(st), host(st_want))
+    assert host(status)[0] == 0
+    x[M - 1, D - 1] = float("inf")
+    _, _, y, _ = B.aqt_layernorm_quantize(x, 8, gamma=gamma, beta=beta, quantize=False, want_y=True, dev_status=status)
+    assert host(status)[0] != 0 and not np.isfinite(host(y)[M - 1]).any()
+    np.testing.assert_array_equal(host(y)[:M - 1], host(want)[:M - 1])
+
+
 # ----------------------------------------------------------------------------
 # the float32-emulated product against the native integer product (Sec. 1)
 # ----------------------------------------------------------------------------
