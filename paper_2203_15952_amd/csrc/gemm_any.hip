@@ -217,10 +217,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
         amax = max(amax, __float_as_uint(out) & 0x7FFFFFFFu);
       }
   }
-  if (y_absmax) {   // one atomic per wavefront, and only if it can raise the word (it only grows)
+  // Uniform: one atomic per workgroup, and only if it can raise the word (it only grows).  The workgroups of a first round all
+  // find it at zero and queue at it: 40 x 512 -> 2048 with Swish 8.5 us with one per wavefront, 5.3; 1302 x 144 -> 576 12.3, 9.3.
+  if (y_absmax) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) amax = max(amax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(amax), off)));
-    if (lane == 0 && amax > *reinterpret_cast<volatile uint32_t *>(y_absmax)) atomicMax(y_absmax, amax);
+    constexpr int kWaves = WM * WN * WK;
+    __shared__ uint32_t wave_max[kWaves];
+    if (lane == 0) wave_max[wave] = amax;
+    __syncthreads();
+    if (t == 0) {
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) amax = max(amax, wave_max[w]);
+      if (amax > *reinterpret_cast<volatile uint32_t *>(y_absmax)) atomicMax(y_absmax, amax);
+    }
   }
 }
 
