@@ -630,20 +630,23 @@ __global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__
     dw[at] = dw_value((sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]), at, at % N, fin, fin.s_x[0]);
 }
 
-// Which workgroup arrangement of the forward.  128 x 128 tiles move the fewest bytes through LDS per product but there
-// have to be enough of them for 256 compute units; narrower ones when the columns would mostly be padding; the split
-// contraction below that.  Eight wavefronts per workgroup, so that two share a SIMD even where the launch has one
-// workgroup per compute unit (the staging of one runs under the products of the other).
-// The lines were drawn from sweeps over all five arrangements (us): 3200 x 512 -> 128 (50 tiles of 64 x 128) 5.9 as
-// such, 4.1 split; 800 x 256 -> 1024 (104 tiles) 5.2, 5.7 split; 10008 x 144 -> 576 12.4 in 64 x 128, 10.7 in 128 x 64.
-enum class Tile { kLarge, kRows, kNarrow, kSmall, kSmallest };   // 128 x 128, 64 x 128, 128 x 64; split contraction: 32 x 64, 32 x 32
+// Which workgroup arrangement of the forward.  The lines were drawn from sweeps over all of them (us):
+//   the split contraction (32 columns to a tile, all eight wavefronts on it) while that makes fewer than 800 workgroups: 2604 x 144 -> 144
+//   (410) 3.9 against 5.3 in 64 x 128 tiles, 700 x 520 -> 1000 (704) 6.3 and 7.0, 1280 x 2048 -> 512 (640) 9.2 and 12.2;
+//   1302 x 520 -> 1000 (1312) 9.5 and 7.7;
+//   128 x 64, four wavefronts, where 64 x 128 would compute mostly padding and no longer has all its tiles on the chip
+//   at once (10008 x 144 -> 144 6.8 and 7.3, 10008 x 144 -> 576 11.0 and 12.8; 7000 x 144 -> 144 6.5 and 5.9,
+//   5000 x 144 -> 576 8.9 and 7.9; with a fan-in of 2040, 16000 -> 520, 61 and 55), and for long contractions, where fewer bytes through
+//   LDS per product count (50000 x 4100 -> 1000 467 and 526, 5000 x 1000 -> 1000 21.8 and 22.4; 16000 x 520 -> 520 27 and 25);
+//   64 x 128, eight wavefronts, otherwise.  (128 x 128 tiles, eight wavefronts, are behind both everywhere: 5000 x 520 -> 1000 21.6 against 16.7,
+//   16000 x 1000 -> 1000 67 against 50 and 52, 50000 x 4100 -> 1000 646 against 467 and 526.)
+enum class Tile { kRows, kNarrow, kSmall, kSmallest };   // 64 x 128, 128 x 64; split contraction: 32 x 64 (the GLU's pairs), 32 x 32
 Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, bool glu) {
-  const int64_t narrow = cdiv(M, 128) * cdiv(cols, 64), large = cdiv(M, 128) * cdiv(cols, 128), rows = cdiv(M, 64) * cdiv(cols, 128);
-  const bool odd = cdiv(cols, 64) % 2 && cols < 640;   // half of the last 128-wide tile would be padding
-  if (odd && narrow >= 128) return Tile::kNarrow;
-  if (large >= 192) return Tile::kLarge;
-  if (rows >= (contraction <= 256 ? 64 : 100)) return Tile::kRows;
-  return glu ? Tile::kSmall : Tile::kSmallest;
+  if (cdiv(M, 32) * cdiv(cols, 32) < 800) return glu ? Tile::kSmall : Tile::kSmallest;
+  const int64_t rows = cdiv(M, 64) * cdiv(cols, 128);
+  if (cols >= 640) return contraction >= 1000 && rows > 512 ? Tile::kNarrow : Tile::kRows;
+  const bool odd = cdiv(cols, 64) % 2;   // half of the last 128-wide tile would be padding
+  return odd && (cols <= 192 ? rows > 256 : contraction <= 256 && rows > 512) ? Tile::kNarrow : Tile::kRows;
 }
 
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
@@ -668,7 +671,6 @@ aqt_status fwd_any_sized(const int8_t *xq, const float *s_x, const void *wq, con
                          const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
                          hipStream_t st) {
   switch (pick_tile(M, N, K, epilogue == AQT_EPI_GLU)) {
-    case Tile::kLarge: return fwd_any<1, 2, 4, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
     case Tile::kRows:
       if (epilogue != AQT_EPI_GLU) return fwd_any<1, 1, 2, 4, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
       return fwd_any<1, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);

@@ -467,14 +467,17 @@ bool fwd_q_takes_fragments(int64_t M, int64_t K, int64_t N, int epilogue) {
 // are then faster even without counting the re-ordering of the weights (us: 2000 x 256 -> 256, 32 tiles, 3.9 against
 // 4.7; 512 x 512 -> 512 4.4 against 5.7; 1024 x 1024 -> 256 4.7 against 7.3; 400 x 2048 -> 512 4.5 against 11.9; not
 // with a short main loop, 800 x 256 -> 1024, 56 tiles, 5.2 against 4.9, nor from 64 tiles on, 4096 x 512 -> 512, 128 tiles,
-// 6.8 against 6.4).
-static bool fwd_q_small(int64_t M, int64_t K, int64_t N) {
+// 6.8 against 6.4).  A tile's wavefronts work through 64 elements each in the epilogue: with Swish 5 us if one
+// workgroup has a compute unit to itself, whatever the size, while eight wavefronts on half the tile take 1.5 (2048 x 256 -> 1024,
+// 128 tiles, 7.6 against 10.3; 1280 x 512 -> 1536, 120 tiles, 8.5 and 10.9; 1280 x 512 -> 2048, 160 tiles, 11.0 both; 2560 x 512 ->
+// 2048, 320 tiles, 16.3 and 13.2).
+static bool fwd_q_small(int64_t M, int64_t K, int64_t N, int epilogue) {
   const int64_t tiles = cdiv(M, 128) * cdiv(N, 128);
-  return tiles <= 32 || (tiles <= 64 && K >= 512);
+  return tiles <= (epilogue == AQT_EPI_SWISH ? 128 : K >= 512 ? 64 : 32);
 }
 
 bool fwd_q_uses_fragments(int64_t M, int64_t K, int64_t N, int epilogue) {
-  return fwd_q_takes_fragments(M, K, N, epilogue) && !fwd_q_small(M, K, N);
+  return fwd_q_takes_fragments(M, K, N, epilogue) && !fwd_q_small(M, K, N, epilogue);
 }
 
 aqt_status launch_prepare_weights(const void *wq_packed, int64_t K, int64_t N, int bits_w, void *wprep,
@@ -501,7 +504,7 @@ aqt_status launch_dense_fwd_q(const int8_t *xq, const float *s_x, const void *wq
   const bool aligned = (reinterpret_cast<uintptr_t>(xq) % 16 == 0) && ws &&
                        (reinterpret_cast<uintptr_t>(ws) % 16 == 0) &&
                        (ws_is_prepared || reinterpret_cast<uintptr_t>(wq_packed) % 16 == 0);
-  if (aligned && fwd_q_takes_fragments(M, K, N, epilogue) && (!wq_packed || !fwd_q_small(M, K, N))) {
+  if (aligned && fwd_q_takes_fragments(M, K, N, epilogue) && (!wq_packed || !fwd_q_small(M, K, N, epilogue))) {
     const int64_t nn = (epilogue == AQT_EPI_GLU) ? N / 2 : N;
     const int64_t unit_wide = (epilogue == AQT_EPI_GLU) ? 128 : 256;
     v4i *wfrag = static_cast<v4i *>(ws);

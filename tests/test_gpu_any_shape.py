@@ -251,3 +251,29 @@ def test_small_problems_on_the_tuned_grid(M, K, N):
         if what == "y" and (N % 128 or -(-M // 128) * -(-N // 128) > 64):
             continue
         assert bool(((got.double() - ref).abs() <= 100 * 2.0 ** -24 * mag + 1e-37).all()), what
+
+
+@pytest.mark.parametrize("M,K,N,bw,epi", [
+    (800, 40, 1024, 8, 0), (799, 40, 992, 4, 0),                           # 800 and 775 split tiles
+    (8192, 33, 130, 8, 1), (8193, 33, 130, 4, 0),                          # 256 and 258 tiles of 64 x 128, under 192 channels
+    (10881, 250, 322, 8, 1), (10945, 257, 322, 4, 0),                      # 513 and 516 of them under 640; 256 positions, and more
+    (6600, 999, 642, 8, 0), (6592, 1001, 642, 4, 1), (6593, 1002, 1300, 8, 2),   # 640 channels and more: around 1000 positions
+    (2048, 128, 1024, 4, 1), (2049, 128, 1024, 8, 1)])                     # Swish on the tuned grid: 128 and 136 tiles
+def test_forward_around_the_lines_between_arrangements(M, K, N, bw, epi):
+    """Whatever tile a size takes: the integer sums are exact, the result is their de-quantization, the maximum is the result's."""
+    import torch
+    print("[arrangements]", M, K, N, bw, epi, flush=True)
+    rng = np.random.default_rng(M + K + N)
+    x, w = rng.standard_normal((M, K)).astype(np.float32), (rng.standard_normal((K, N)) * K ** -0.5).astype(np.float32)
+    sv = B.Saved(M, K, N, bw)
+    y = B.aqt_dense_fwd(dev(x), dev(w), 8, bw, epilogue=epi, saved=sv)
+    y2, m = B.aqt_dense_fwd_q_absmax(sv.xq, sv.s_x, sv.wq_packed, sv.s_w, N, 8, bw, epilogue=epi)
+    _, acc = B.aqt_dense_fwd_q(sv.xq, sv.s_x, sv.wq_packed, sv.s_w, N, 8, bw, epilogue=epi, want_acc=True)
+    exact = torch.matmul(sv.xq.double(), sv.wq_kn.double().contiguous())   # whole numbers below 2^53
+    assert torch.equal(acc.double(), exact)
+    v = acc.float() * (sv.s_x * sv.s_w)
+    h = N // 2
+    want = v if epi == 0 else v * torch.sigmoid(v) if epi == 1 else v[:, :h] * torch.sigmoid(v[:, h:])
+    # exp and the logistic function built on it: a few roundings each way
+    assert torch.all((y - want).abs() <= 2e-6 * want.abs() + 1e-30)
+    assert torch.equal(y2, y) and m[0] == y.abs().max()
