@@ -277,23 +277,25 @@ __device__ __forceinline__ v4i nibbles8_bf16(uint32_t w) {   // eight int4 codes
 //   MODE 1 + e:    weight-only forward with epilogue e: f = x [M,K], q = the forward weight operand [N][K]
 // Eight wavefronts share a tile of 32 rows x 32 TN columns and take turns along the contraction.
 // LONG: a wavefront's share of the contraction exceeds kChain, so float32 sums are moved to float64 on the way.
+template <int TN, bool LONG>
+constexpr int codes_lds_bytes() {
+  constexpr int slices = 8 * (3 * 32 + 32 * TN) * 64, sums = 8 * TN * 16 * 64 * (LONG ? 8 : 4);
+  return slices > sums ? slices : sums;
+}
 template <int TN, bool PACKED, int MODE, bool LONG>
-__global__ __launch_bounds__(512, 2) void f32_codes_any_kernel(
-    const float *__restrict__ f, const float *__restrict__ scale, const uint8_t *__restrict__ q, int64_t M, int64_t R,
-    int64_t C, const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x, const float *__restrict__ factor,
-    const float *__restrict__ bias, float *__restrict__ out, int tiles_r) {
+__device__ __forceinline__ void f32_codes_tile(
+    uint8_t *lds, unsigned block, const float *__restrict__ f, const float *__restrict__ scale, const uint8_t *__restrict__ q,
+    int64_t M, int64_t R, int64_t C, const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x,
+    const float *__restrict__ factor, const float *__restrict__ bias, float *__restrict__ out, int tiles_r) {
   static_assert(MODE != 1 + AQT_EPI_GLU || TN % 2 == 0, "a GLU tile pairs value and gate blocks");
   constexpr bool DX = MODE == 0, GLU = MODE == 1 + AQT_EPI_GLU;
   constexpr int WK = 8, G = 64, BM = 32, BN = 32 * TN;
   constexpr int NA = BM * 8 / G, NB = BN * 2 / G;   // pieces of four floats, of sixteen codes, per thread and slice
   constexpr int kImage = BM * 64;
   constexpr int kSliceBytes = 3 * kImage + BN * 64;
-  constexpr int kRedBytes = WK * TN * 16 * 64 * (LONG ? 8 : 4);
-  constexpr int kLds = WK * kSliceBytes > kRedBytes ? WK * kSliceBytes : kRedBytes;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kLds];
   const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
   const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t bm = blockIdx.x / tiles_r, br = blockIdx.x % tiles_r;
+  const int64_t bm = block / tiles_r, br = block % tiles_r;
   const int64_t oc = GLU ? R / 2 : R;
   auto chan = [&](int cb) -> int64_t {
     if (GLU) return br * (BN / 2) + (cb >> 1) * 32 + ((cb & 1) ? oc : 0);
@@ -453,6 +455,15 @@ __global__ __launch_bounds__(512, 2) void f32_codes_any_kernel(
   }
 }
 
+template <int TN, bool PACKED, int MODE, bool LONG>
+__global__ __launch_bounds__(512, 2) void f32_codes_any_kernel(
+    const float *__restrict__ f, const float *__restrict__ scale, const uint8_t *__restrict__ q, int64_t M, int64_t R,
+    int64_t C, const float *__restrict__ s_x, const uint32_t *__restrict__ mask_x, const float *__restrict__ factor,
+    const float *__restrict__ bias, float *__restrict__ out, int tiles_r) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[codes_lds_bytes<TN, LONG>()];
+  f32_codes_tile<TN, PACKED, MODE, LONG>(lds, blockIdx.x, f, scale, q, M, R, C, s_x, mask_x, factor, bias, out, tiles_r);
+}
+
 // ---- dW: contraction over the rows of both operands ---------------------------------------------
 // partial[slab][k][n] = sum over the slab's rows of xq[m,k] dy[m,n].  A workgroup of four wavefronts owns 128
 // fan-in positions x 128 channels and one slab of rows, 32 rows per slice.  Neither operand is
@@ -603,6 +614,134 @@ __global__ __launch_bounds__(kDwThreads, 2) void bwd_dw_any_kernel(const int8_t 
   }
 }
 
+// The same for few rows: eight wavefronts share a tile of 32 fan-in positions x 32 channels and take turns along the rows, 32 at
+// a time, each with a slot of its own, so that there are tiles enough without slabs, no partial result goes through memory and nothing
+// is left to fold.  Sums of 64 rows in float32, then float64.  The tiles of the first 32 positions add up the bias gradient.
+// Bound by the latency of its few trips to memory and the conversions: 1024 x 256 x 1024 10.2 us, 20.9 with slabs of 64 rows and a
+// fold; error of the result against float64 8.2e-8 of its norm either way (1300 x 512 x 512 8.0e-8 and 8.2e-8).  At most 128 registers
+// for two workgroups per compute unit: 56 spilled, 15.3 us.
+constexpr int kDwSplitTile = 32;
+constexpr int kDwSplitImage = kDwSplitTile * 64, kDwSplitSlice = 4 * kDwSplitImage;   // codes; dy hi, mid, lo
+constexpr int kDwSplitLds = 8 * kDwSplitSlice;
+static_assert(kDwSplitLds >= 8 * 16 * 64 * 8, "the wavefronts' sums must fit");
+
+__device__ __forceinline__ void dw_split_tile(uint8_t *lds, unsigned block, const int8_t *__restrict__ xq, const float *__restrict__ dy,
+                                              int64_t M, int64_t K, int64_t N, DwFinish fin, float *__restrict__ dw,
+                                              float *__restrict__ dbias) {
+  constexpr int WK = 8;
+  const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
+  const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned tiles_n = static_cast<unsigned>(N / kDwSplitTile), kt = block / tiles_n;
+  const int64_t k0 = static_cast<int64_t>(kt) * kDwSplitTile, n0 = static_cast<int64_t>(block % tiles_n) * kDwSplitTile;
+  const int g = lane & 7, mg = lane >> 3;   // this thread's four columns 4 g .. and four rows 4 mg .. of a slice
+  const int64_t slices = cdiv(M, kSlice);
+  uint32_t rc[2][4];
+  v4f rg[2][4];
+  auto load = [&](auto set, int64_t slice) {
+    constexpr int S = decltype(set)::value;
+    const int64_t m = slice * kSlice + 4 * mg;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t r = m + i < M ? m + i : M - 1;
+      rc[S][i] = load_at<uint32_t>(xq + r * K + k0 + 4 * g);
+      rg[S][i] = load_at<v4f>(dy + r * N + n0 + 4 * g);
+    }
+  };
+  v16f acc;
+  double sum[16], colsum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    acc[r] = 0.0f;
+    sum[r] = 0.0;
+  }
+  auto fold = [&]() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sum[r] += static_cast<double>(acc[r]);
+      acc[r] = 0.0f;
+    }
+  };
+  const bool bias = dbias && kt == 0;
+  auto stage = [&](auto set, int64_t slice, uint8_t *slot) {
+    constexpr int S = decltype(set)::value;
+    if ((slice + 1) * kSlice > M) {   // rows beyond the end contribute nothing
+      const int64_t m = slice * kSlice + 4 * mg;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (m + i >= M) {
+          rc[S][i] = 0u;
+          rg[S][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
+    if (bias) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        colsum[b] += (static_cast<double>(rg[S][0][b]) + static_cast<double>(rg[S][1][b])) +
+                     (static_cast<double>(rg[S][2][b]) + static_cast<double>(rg[S][3][b]));
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {   // tile column 4 g + b lives in LDS row 8 b + g
+      uint8_t *const at = slot + chunk_at<kCh>(8 * b + g, mg >> 1) + 8 * (mg & 1);
+      v2i a;
+      a.x = static_cast<int>(pack_bf16(static_cast<float>(static_cast<int8_t>(rc[S][0] >> (8 * b))),
+                                       static_cast<float>(static_cast<int8_t>(rc[S][1] >> (8 * b)))));
+      a.y = static_cast<int>(pack_bf16(static_cast<float>(static_cast<int8_t>(rc[S][2] >> (8 * b))),
+                                       static_cast<float>(static_cast<int8_t>(rc[S][3] >> (8 * b)))));
+      *reinterpret_cast<v2i *>(at) = a;
+      store_split(at + kDwSplitImage, kDwSplitImage, v4f{rg[S][0][b], rg[S][1][b], rg[S][2][b], rg[S][3][b]});
+    }
+  };
+  int since = 0;
+  auto multiply = [&](const uint8_t *slot) {
+#pragma unroll
+    for (int kk = 0; kk < kSlice / 16; ++kk) {
+      const int at = chunk_at<kCh>(lr, 2 * kk + lk);
+      const v4i a = *reinterpret_cast<const v4i *>(slot + at);
+#pragma unroll
+      for (int img = 3; img >= 1; --img)   // smallest terms first
+        acc = mfma_bf16(a, *reinterpret_cast<const v4i *>(slot + img * kDwSplitImage + at), acc);
+    }
+    if (++since == 2) {
+      fold();
+      since = 0;
+    }
+  };
+  run_slices<WK>(lds, kDwSplitSlice, wk, slices, load, stage, multiply);
+  fold();
+  double *const red = reinterpret_cast<double *>(lds);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[(wk * 16 + r) * 64 + lane] = sum[r];
+  __syncthreads();
+  const double sx = fin.s_x[0];
+#pragma unroll
+  for (int rr = 0; rr < 2; ++rr) {   // the wavefronts' shares in order
+    const int r = 2 * wk + rr, row = 8 * (r >> 2) + 4 * lk + (r & 3);
+    double v = red[r * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < WK; ++w) v += red[(w * 16 + r) * 64 + lane];
+    const int64_t k = k0 + 4 * (row & 7) + (row >> 3), n = n0 + 4 * (lr & 7) + (lr >> 3), at = k * N + n;
+    dw[at] = dw_value(v, at, n, fin, sx);
+  }
+  if (bias) {   // uniform: the row groups of every wavefront, in order
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 4; ++b) red[(wk * 8 + mg) * 32 + 4 * g + b] = colsum[b];
+    __syncthreads();
+    if (threadIdx.x < kDwSplitTile) {
+      double v = red[threadIdx.x];
+      for (int i = 1; i < 8 * WK; ++i) v += red[i * 32 + threadIdx.x];
+      dbias[n0 + threadIdx.x] = static_cast<float>(v);
+    }
+  }
+}
+__global__ __launch_bounds__(512, 2) void bwd_dw_split_kernel(const int8_t *__restrict__ xq, const float *__restrict__ dy, int64_t M,
+                                                              int64_t K, int64_t N, DwFinish fin, float *__restrict__ dw,
+                                                              float *__restrict__ dbias) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kDwSplitLds];
+  dw_split_tile(lds, blockIdx.x, xq, dy, M, K, N, fin, dw, dbias);
+}
+
 // 64 elements x 4 groups of slabs per workgroup, eight loads in flight per thread; the order of the sums is fixed.
 // The first bias_blocks workgroups fold the column sums instead.
 __global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__restrict__ partial, int slabs, int64_t K,
@@ -736,13 +875,24 @@ int dw_any_slabs(int64_t M, int64_t K, int64_t N) {
   return static_cast<int>(slabs >= fill ? slabs : fill < most ? fill : most);
 }
 
+// The split kernel while its tiles, with their four times as many conversions and reads, cost less than partial results through memory
+// and a fold (us with the bias gradient, slabs and split: 1024 x 256 x 1024 20.9 and 10.2, 2048 x 256 x 256 14.8 and 13.7,
+// 2560 x 512 x 512 24.4 and 16.8, 16 x 512 x 2048 12.8 and 12.6; behind it in rows 4096 x 256 x 256 20.6 and 22.5, in products
+// 1300 x 512 x 2048 31.8 and 33.7, 300 x 1024 x 4096 54.8 and 58.3).
+static bool dw_any_splits(int64_t M, int64_t K, int64_t N) { return M <= 3072 && M * K * N <= 1000000000; }
+
 aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
                              int64_t M, int64_t K, int64_t N, float *dw, float *partial, float *dbias, double *bias_part,
                              hipStream_t st) {
+  const DwFinish fin{s_x, s_w, mask_w};
+  if (dw_any_splits(M, K, N)) {
+    bwd_dw_split_kernel<<<static_cast<unsigned>((K / kDwSplitTile) * (N / kDwSplitTile)), 512, 0, st>>>(xq, dy, M, K, N, fin, dw, dbias);
+    AQT_HIP(hipGetLastError());
+    return AQT_OK;
+  }
   const int64_t tiles_n = N / kDwTile, tiles = (K / kDwTile) * tiles_n;
   const int64_t rows = cdiv(cdiv(M, dw_any_slabs(M, K, N)), kSlice) * kSlice, slabs = cdiv(M, rows);
   if (tiles * slabs > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
-  const DwFinish fin{s_x, s_w, mask_w};
   const bool one = slabs == 1;
   bwd_dw_any_kernel<<<static_cast<unsigned>(tiles * slabs), kDwThreads, 0, st>>>(
       xq, dy, M, K, N, rows, one ? dw : partial, static_cast<int>(tiles_n), static_cast<int>(tiles), one ? 1 : 0, fin,

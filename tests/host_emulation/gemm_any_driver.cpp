@@ -152,10 +152,10 @@ template <int TN, bool PACKED, int MODE, bool LONG> void rows_any(int64_t M, int
   });
 }
 
-// dW in slabs of `rows` rows, with the bias gradient; T: what a slab's partial sums are kept in; TJ > 0: gemm_exact.hip
+// dW in slabs of `rows` rows, with the bias gradient (rows 0: no slabs, the split kernel); T: what a slab's partial sums are kept in; TJ > 0: gemm_exact.hip
 template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, bool masked, bool wild = false) {
   constexpr bool F64 = sizeof(T) == 8;
-  const int64_t tile = F64 ? 64 : 128, tiles_n = cdiv(N, tile), tiles_k = cdiv(K, TJ ? 16 * TJ : tile), slabs = cdiv(M, rows);
+  const int64_t tile = F64 ? 64 : 128, tiles_n = cdiv(N, tile), tiles_k = cdiv(K, TJ ? 16 * TJ : tile), slabs = rows ? cdiv(M, rows) : 1;
   printf("dW %s: %ld %ld %ld, %ld slabs, masked %d\n", TJ ? "digits" : F64 ? "float64" : "bf16", (long)M, (long)K, (long)N, (long)slabs, (int)masked);
   Codes x(M, K, false);
   Exact<float> dy(M * N), sx(1), sw(N), dw(K * N), db(N);
@@ -180,8 +180,12 @@ template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int
     run(bias_blocks + dw_blocks, 256, 0, [&] { f64::dw_f64_fold_kernel(partial, (int)slabs, K, N, fin, dw, part, (int)(slabs * tiles_k), bias_blocks, db); });
   } else {
     const DwFinish fin{sx, sw, masked ? mask.p : nullptr};
+    if (!rows) {
+      run((unsigned)(K / 32 * (N / 32)), 512, 0, [&] { any::bwd_dw_split_kernel((const int8_t *)x.bytes.p, dy, M, K, N, fin, dw, db); });
+    } else {
     run(grid, 256, 0, [&] { any::bwd_dw_any_kernel((const int8_t *)x.bytes.p, dy, M, K, N, rows, one ? dw.p : (float *)partial.p, (int)tiles_n, (int)(tiles_k * tiles_n), one ? 1 : 0, fin, part); });
     run(bias_blocks + dw_blocks, 256, 0, [&] { any::dw_any_fold_kernel((const float *)partial.p, (int)slabs, K, N, fin, dw, part, (int)(slabs * tiles_k), bias_blocks, db); });
+    }
   }
   double worst = 0, worst_b = 0;
   for (int64_t n = 0; n < N; ++n) {
@@ -221,6 +225,7 @@ int main() {
   weights<double>(200, 130, 5, 128, true);
   weights<double, 4>(70, 66, 65, 64, false); weights<double, 5>(200, 81, 33, 128, true, true); weights<double, 5>(64, 97, 5, 64, true, true);
   weights<double, 4>(329, 4, 66, 192, false, true); weights<double, 5>(130, 193, 17, 192, true, true);
+  weights<float>(70, 64, 96, 0, true); weights<float>(33, 32, 64, 0, false); weights<float>(1, 32, 32, 0, true); weights<float>(600, 32, 32, 0, false);
   weights<float>(70, 128, 128, 64, true); weights<float>(33, 256, 128, 64, false); weights<float>(1, 128, 128, 32, true);
   printf(bad ? "MISMATCH\n" : "ok\n"); return bad;
 }

@@ -277,3 +277,24 @@ def test_forward_around_the_lines_between_arrangements(M, K, N, bw, epi):
     # exp and the logistic function built on it: a few roundings each way
     assert torch.all((y - want).abs() <= 2e-6 * want.abs() + 1e-30)
     assert torch.equal(y2, y) and m[0] == y.abs().max()
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 256, 128), (31, 256, 128), (33, 512, 128), (255, 256, 384), (257, 256, 256), (513, 256, 128),
+                                   (3072, 256, 256), (3073, 256, 256), (1907, 512, 1024), (1908, 512, 1024)])
+def test_weight_gradient_of_few_rows(M, K, N):
+    """One workgroup per tile up to 3072 rows and 10^9 products, slabs beyond: sums of at most 512 rows in float32 (as above), then float64."""
+    import torch
+    print("[dW, few rows]", M, K, N, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    x, w = torch.randn(M, K, device="cuda", generator=gen), torch.randn(K, N, device="cuda", generator=gen)
+    dy = torch.randn(M, N, device="cuda", generator=gen)
+    sv = B.Saved(M, K, N, 8)
+    B.aqt_dense_fwd(x, w, 8, 8, saved=sv)
+    _, dw, db = B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, want_dbias=True)
+    codes = (sv.xq.double().t().contiguous(), dy.double())
+    ref, mag = sv.s_x.double() * (codes[0] @ codes[1]), sv.s_x.double() * (codes[0].abs() @ codes[1].abs())
+    assert bool(((dw.double() - ref).abs() <= 100 * 2.0 ** -24 * mag + 1e-37).all())
+    rb = dy.double().sum(0)
+    assert bool(((db.double() - rb).abs() <= 2.0 ** -24 * rb.abs() + 1e-12 * dy.double().abs().sum(0)).all())
+    again = B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, want_dbias=True)
+    assert torch.equal(again[1], dw) and torch.equal(again[2], db)
