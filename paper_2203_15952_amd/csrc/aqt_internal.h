@@ -121,6 +121,10 @@ aqt_status launch_bwd_dx_any(const float *dy, const int8_t *wq_kn, const float *
                              const float *factor, int64_t M, int64_t K, int64_t N, float *dx, hipStream_t st);
 int dw_any_slabs(int64_t M, int64_t K, int64_t N);   // slabs of rows: K x N floats each in `partial`, K / 128 x N doubles
                                                      // each in `bias_part` (dbias not null)
+bool bwd_small_ok(int64_t M, int64_t K, int64_t N);
+aqt_status launch_bwd_small_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
+                                const float *factor, const int8_t *xq, const uint32_t *mask_w, int64_t M, int64_t K, int64_t N,
+                                float *dx, float *dw, float *dbias, hipStream_t st);
 aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
                              int64_t M, int64_t K, int64_t N, float *dw, float *partial, float *dbias, double *bias_part,
                              hipStream_t st);

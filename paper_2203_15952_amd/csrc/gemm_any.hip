@@ -742,6 +742,23 @@ __global__ __launch_bounds__(512, 2) void bwd_dw_split_kernel(const int8_t *__re
   dw_split_tile(lds, blockIdx.x, xq, dy, M, K, N, fin, dw, dbias);
 }
 
+// Both gradients of a small problem in one launch: the first dw_blocks workgroups take the tiles of dW, the others those of dX, each with the
+// sums of its own kernel.  Two launches -> one: 128 x 256 x 256 9.1 -> 5.6 us, 1024 x 256 x 256 14.2 -> 10.0, 1024 x 256 x 1024
+// 18.8 -> 16.9, 2048 x 256 x 1024 25.7 -> 23.9, 2560 x 512 x 512 30.0 -> 30.3.
+template <int TN>
+__global__ __launch_bounds__(512, 2) void bwd_small_kernel(CodesArgs a, int tiles_r, const int8_t *__restrict__ xq, int64_t K, int64_t N,
+                                                           DwFinish fin, float *__restrict__ dw, float *__restrict__ dbias,
+                                                           unsigned dw_blocks) {
+  constexpr int kDx = codes_lds_bytes<TN, false>();
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kDx > kDwSplitLds ? kDx : kDwSplitLds];
+  if (blockIdx.x < dw_blocks) {
+    dw_split_tile(lds, blockIdx.x, xq, a.f, a.M, K, N, fin, dw, dbias);
+  } else {
+    f32_codes_tile<TN, false, 0, false>(lds, blockIdx.x - dw_blocks, a.f, a.scale, static_cast<const uint8_t *>(a.q), a.M, a.R, a.C, a.s_x,
+                                        a.mask_x, a.factor, nullptr, a.out, tiles_r);
+  }
+}
+
 // 64 elements x 4 groups of slabs per workgroup, eight loads in flight per thread; the order of the sums is fixed.
 // The first bias_blocks workgroups fold the column sums instead.
 __global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__restrict__ partial, int slabs, int64_t K,
@@ -830,6 +847,7 @@ aqt_status f32_codes_any(const CodesArgs &a, hipStream_t st) {
 
 // Tiles of 32 x 64 halve the conversions of the float operand where there are enough of them; the float64 sums of long
 // contractions need registers they do not leave.  (us: dX 3200 x 512 -> 128, 50 tiles of 64 x 128, 14.1 as such, 6.9 split.)
+static bool codes_any_wide(int64_t M, int64_t R) { return cdiv(M, 32) * (R / 64) >= 128; }
 template <bool PACKED, int MODE>
 aqt_status f32_codes_any_sized(const CodesArgs &a, hipStream_t st) {
   const bool lng = a.C > 8 * kChain;
@@ -837,7 +855,7 @@ aqt_status f32_codes_any_sized(const CodesArgs &a, hipStream_t st) {
     return lng ? f32_codes_any<2, PACKED, MODE, true>(a, st) : f32_codes_any<2, PACKED, MODE, false>(a, st);
   } else {
     if (lng) return f32_codes_any<1, PACKED, MODE, true>(a, st);
-    return cdiv(a.M, 32) * (a.R / 64) >= 128 ? f32_codes_any<2, PACKED, MODE, false>(a, st) : f32_codes_any<1, PACKED, MODE, false>(a, st);
+    return codes_any_wide(a.M, a.R) ? f32_codes_any<2, PACKED, MODE, false>(a, st) : f32_codes_any<1, PACKED, MODE, false>(a, st);
   }
 }
 
@@ -903,6 +921,23 @@ aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x
   if (bias_blocks + dw_blocks == 0) return AQT_OK;
   dw_any_fold_kernel<<<bias_blocks + dw_blocks, kDwThreads, 0, st>>>(partial, static_cast<int>(slabs), K, N, fin, dw, bias_part,
                                                                     static_cast<int>(slabs * (tiles / tiles_n)), bias_blocks, dbias);
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
+// dX and dW (and the bias gradient) in one launch: where dW takes the split kernel and dX no float64 sums.
+bool bwd_small_ok(int64_t M, int64_t K, int64_t N) { return N <= 8 * kChain && dw_any_splits(M, K, N); }
+aqt_status launch_bwd_small_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
+                                const float *factor, const int8_t *xq, const uint32_t *mask_w, int64_t M, int64_t K, int64_t N,
+                                float *dx, float *dw, float *dbias, hipStream_t st) {
+  const CodesArgs a{dy, s_w, wq_kn, M, K, N, s_x, mask_x, factor, nullptr, dx};
+  const DwFinish fin{s_x, s_w, mask_w};
+  const int64_t tm = cdiv(M, 32);
+  const bool wide = codes_any_wide(M, K);
+  const int64_t tr = K / (wide ? 64 : 32);
+  const unsigned dwb = static_cast<unsigned>((K / kDwSplitTile) * (N / kDwSplitTile)), blocks = dwb + static_cast<unsigned>(tr * tm);
+  auto kern = wide ? bwd_small_kernel<2> : bwd_small_kernel<1>;
+  kern<<<blocks, 512, 0, st>>>(a, static_cast<int>(tr), xq, K, N, fin, dw, dbias, dwb);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }

@@ -976,10 +976,14 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
   // 16-byte vector accesses on dy and on the buffers carved from the workspace (their
   // offsets are multiples of 256); anything else takes the float64 kernels
   const bool dy_aligned = reinterpret_cast<uintptr_t>(dy) % 16 == 0 && reinterpret_cast<uintptr_t>(ws) % 16 == 0;
+  const bool dx_grid = dx && p.dx_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->s_w) % 16 == 0 &&
+                       reinterpret_cast<uintptr_t>(sv->wq_kn) % 8 == 0;
+  const bool dw_grid = dw && p.dw_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->xq) % 4 == 0 &&
+                       reinterpret_cast<uintptr_t>(dw) % 16 == 0;
+  if (dx_grid && !p.dx_mfma && dw_grid && !p.dw_mfma && bwd_small_ok(M, K, N))
+    return launch_bwd_small_any(dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, dx_factor, sv->xq, sv->mask_w, M, K, N, dx, dw, dbias, st);
   if (dx) {
-    const bool grid = p.dx_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->s_w) % 16 == 0 &&
-                      reinterpret_cast<uintptr_t>(sv->wq_kn) % 8 == 0;
-    if (grid && p.dx_mfma) {
+    if (dx_grid && p.dx_mfma) {
       v4i *wq_frag = reinterpret_cast<v4i *>(base + p.off_bf);
       const int64_t pieces = K * (N / 8);
       int g = static_cast<int>(cdiv(pieces, kThreads));
@@ -993,16 +997,14 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
       else AQT_TRY((launch_dx<2, 2>(dy, wq_frag, sv, M, K, N, dx, st, fused)));
       if (dx_factor && !fused) AQT_TRY(launch_dact_mul(dx, dx_factor, M, K, K, dx, st));
     } else {
-      auto launch = grid ? launch_bwd_dx_any : launch_bwd_dx_f64;
+      auto launch = dx_grid ? launch_bwd_dx_any : launch_bwd_dx_f64;
       AQT_TRY(launch(dy, sv->wq_kn, sv->s_w, sv->s_x, sv->mask_x, dx_factor, M, K, N, dx, st));
     }
   }
   double *bias_part = reinterpret_cast<double *>(base + p.off_bias);
   if (dw) {   // with the bias gradient, where it is wanted as well
-    const bool grid = p.dw_grid && dy_aligned && reinterpret_cast<uintptr_t>(sv->xq) % 4 == 0 &&
-                      reinterpret_cast<uintptr_t>(dw) % 16 == 0;
     float *partial = reinterpret_cast<float *>(base + p.off_part);
-    if (grid && p.dw_mfma) {
+    if (dw_grid && p.dw_mfma) {
       if (p.dw_wide8) AQT_TRY((launch_dw<4, 2, 4>(dy, sv, M, K, N, p, partial, dbias ? bias_part : nullptr, st)));
       else AQT_TRY((launch_dw<4, 2, 2>(dy, sv, M, K, N, p, partial, dbias ? bias_part : nullptr, st)));
       const BiasFold fold{bias_part, dbias, static_cast<int>(p.slabs * (K / 256)),
@@ -1010,7 +1012,7 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
       bwd_dw_fold_kernel<<<static_cast<int>(cdiv(K * N / 4, kThreads)) + fold.blocks, kThreads, 0, st>>>(
           partial, p.slabs, K * N, N, sv->s_x, sv->s_w, sv->mask_w, dw, fold);
       AQT_HIP(hipGetLastError());
-    } else if (grid) {
+    } else if (dw_grid) {
       AQT_TRY(launch_bwd_dw_any(dy, sv->xq, sv->s_x, sv->s_w, sv->mask_w, M, K, N, dw, partial, dbias, bias_part, st));
     } else {   // where only a tensor's alignment is off the grid, as many slabs of doubles as fit in place of the floats
       const int slabs = p.dw_grid ? (p.slabs > 1 ? p.slabs / 2 : 1) : p.slabs;

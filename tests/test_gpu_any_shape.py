@@ -279,7 +279,7 @@ def test_forward_around_the_lines_between_arrangements(M, K, N, bw, epi):
     assert torch.equal(y2, y) and m[0] == y.abs().max()
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 256, 128), (31, 256, 128), (33, 512, 128), (255, 256, 384), (257, 256, 256), (513, 256, 128),
+@pytest.mark.parametrize("M,K,N", [(1, 256, 128), (31, 256, 128), (33, 512, 128), (255, 256, 384), (257, 256, 256), (513, 256, 128), (128, 256, 4096), (130, 256, 4224),
                                    (3072, 256, 256), (3073, 256, 256), (1907, 512, 1024), (1908, 512, 1024)])
 def test_weight_gradient_of_few_rows(M, K, N):
     """One workgroup per tile up to 3072 rows and 10^9 products, slabs beyond: sums of at most 512 rows in float32 (as above), then float64."""
@@ -298,3 +298,7 @@ def test_weight_gradient_of_few_rows(M, K, N):
     assert bool(((db.double() - rb).abs() <= 2.0 ** -24 * rb.abs() + 1e-12 * dy.double().abs().sum(0)).all())
     again = B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, want_dbias=True)
     assert torch.equal(again[1], dw) and torch.equal(again[2], db)
+    # both gradients in one launch: the same sums as in launches of their own
+    dx, _, _ = B.aqt_dense_bwd(dy, sv, 8, 8, want_dw=False)
+    both = B.aqt_dense_bwd(dy, sv, 8, 8, want_dbias=True)
+    assert torch.equal(both[0], dx) and torch.equal(both[1], dw) and torch.equal(both[2], db)
