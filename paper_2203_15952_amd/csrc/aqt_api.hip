@@ -1022,7 +1022,7 @@ aqt_status aqt_conformer_layer_bwd(const float *dy, const float *x, const aqt_co
     return AQT_ERR_INVALID_ARG;
   if (!conv_shape_ok(g.B, g.T, g.D, g.kw, g.pad_left) || !attention_shape_ok(g.B, g.T, g.D, g.heads))
     return AQT_ERR_UNSUPPORTED;
-  const int64_t M = g.B * g.T, n = M * g.D;
+  const int64_t M = g.B * g.T;
   LayerBwdWorkspace f = carve_layer_bwd(ws, M, g.D, g.H, g.heads, g.kw);
   if (!ws || ws_bytes < f.total) return AQT_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1037,9 +1037,8 @@ aqt_status aqt_conformer_layer_bwd(const float *dy, const float *x, const aqt_co
   AQT_TRY(ffn_bwd_check(f.dm, &saved->ffn1, M, g.D, g.H, pf1, f.dm, grads->ffn1_w1, grads->ffn1_w2, ws, f.module));
   // final normalisation: gradient of the residual stream r4
   AQT_TRY(launch_layernorm_bwd(saved->r4, saved->out_row_stats, w->out_ln_g, dy, nullptr, M, g.D, f.da, grads->out_ln_g,
-                               grads->out_ln_b, f.ln, st));
+                               grads->out_ln_b, f.ln, st, f.dm));
   // second feed-forward module entered the stream with weight 1/2: r4 = r3 + ffn(r3) / 2
-  AQT_TRY(launch_scale(f.da, 0.5f, f.dm, n, st));
   AQT_TRY(aqt_ffn_bwd(f.dm, &saved->ffn2, M, g.D, g.H, pf2, f.dm, grads->ffn2_w1, grads->ffn2_b1, grads->ffn2_w2,
                       grads->ffn2_b2, ws, f.module, stream));
   AQT_TRY(launch_layernorm_bwd(saved->r3, saved->ffn2.row_stats, w->ffn2_ln_g, f.dm, f.da, M, g.D, f.db,
@@ -1054,9 +1053,8 @@ aqt_status aqt_conformer_layer_bwd(const float *dy, const float *x, const aqt_co
   AQT_TRY(aqt_mhsa_bwd(f.da, &saved->att, g.B, g.T, g.D, g.heads, g.left_context, g.right_context, pa, f.dm,
                        grads->att_wqkv, grads->att_bqkv, grads->att_wo, grads->att_bo, ws, f.module, stream));
   AQT_TRY(launch_layernorm_bwd(saved->r1, saved->att.row_stats, w->att_ln_g, f.dm, f.da, M, g.D, f.db,
-                               grads->att_ln_g, grads->att_ln_b, f.ln, st));
+                               grads->att_ln_g, grads->att_ln_b, f.ln, st, f.dm));
   // first feed-forward module: r1 = x + ffn(x) / 2
-  AQT_TRY(launch_scale(f.db, 0.5f, f.dm, n, st));
   AQT_TRY(aqt_ffn_bwd(f.dm, &saved->ffn1, M, g.D, g.H, pf1, f.dm, grads->ffn1_w1, grads->ffn1_b1, grads->ffn1_w2,
                       grads->ffn1_b2, ws, f.module, stream));
   return launch_layernorm_bwd(x, saved->ffn1.row_stats, w->ffn1_ln_g, f.dm, f.db, M, g.D, dx, grads->ffn1_ln_g,

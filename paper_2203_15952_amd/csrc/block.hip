@@ -260,12 +260,14 @@ __global__ __launch_bounds__(kThreads) void ln_quantize_kernel(const float *__re
 // column sums for its own columns over the rows its workgroup walks, the four wavefronts are added in LDS
 // in a fixed order and the workgroup leaves one partial per column; ln_bwd_fold_kernel adds the partials
 // in order.  NV as in ln_stats_kernel (NV = 0: any row, one column per lane and step).
+// NV > 0 with half: dx / 2 as well, what a module that entered the stream with weight 1/2 is given; half may be dy, whose row
+// the wavefront has read by then.  (As a pass of its own 65536 x 512 took 57 us, here it adds 6.)
 template <int NV>
 __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(const float *__restrict__ x, const float *__restrict__ stats,
                                                           const float *__restrict__ gamma,
-                                                          const float *__restrict__ dy, const float *__restrict__ add,
+                                                          const float *dy, const float *__restrict__ add,
                                                           int64_t M, int64_t D, float *__restrict__ dx,
-                                                          float *__restrict__ part) {
+                                                          float *__restrict__ part, float *half) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float invD = 1.0f / static_cast<float>(D);
   if constexpr (NV > 0) {
@@ -310,6 +312,7 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(const float *__restric
             o.x += a.x; o.y += a.y; o.z += a.z; o.w += a.w;
           }
           *reinterpret_cast<v4f *>(dx + m * D + c) = o;
+          if (half) *reinterpret_cast<v4f *>(half + m * D + c) = v4f{0.5f * o.x, 0.5f * o.y, 0.5f * o.z, 0.5f * o.w};
         }
       }
     }
@@ -575,19 +578,19 @@ size_t layernorm_bwd_ws_bytes(int64_t D) {
 
 aqt_status launch_layernorm_bwd(const float *x, const float *stats, const float *gamma, const float *dy,
                                 const float *add, int64_t M, int64_t D, float *dx, float *dgamma, float *dbeta,
-                                void *ws, hipStream_t st) {
+                                void *ws, hipStream_t st, float *half) {
   const bool want_cols = dgamma || dbeta;
   float *part = want_cols ? static_cast<float *>(ws) : nullptr;
   const bool vec = (D % 4 == 0) && D <= 1024 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(dy) % 16 == 0 && reinterpret_cast<uintptr_t>(dx) % 16 == 0 &&
-                   (!add || reinterpret_cast<uintptr_t>(add) % 16 == 0) &&
+                   (!add || reinterpret_cast<uintptr_t>(add) % 16 == 0) && (!half || reinterpret_cast<uintptr_t>(half) % 16 == 0) &&
                    (!gamma || reinterpret_cast<uintptr_t>(gamma) % 16 == 0);
   const int g = grid_cap(M, 4, kLnBwdBlocks);
   int P = g;
-  if (vec && D <= 512) ln_bwd_kernel<2><<<g, kThreads, 0, st>>>(x, stats, gamma, dy, add, M, D, dx, part);
-  else if (vec) ln_bwd_kernel<4><<<g, kThreads, 0, st>>>(x, stats, gamma, dy, add, M, D, dx, part);
+  if (vec && D <= 512) ln_bwd_kernel<2><<<g, kThreads, 0, st>>>(x, stats, gamma, dy, add, M, D, dx, part, half);
+  else if (vec) ln_bwd_kernel<4><<<g, kThreads, 0, st>>>(x, stats, gamma, dy, add, M, D, dx, part, half);
   else {
-    ln_bwd_kernel<0><<<g, kThreads, 0, st>>>(x, stats, gamma, dy, add, M, D, dx, nullptr);
+    ln_bwd_kernel<0><<<g, kThreads, 0, st>>>(x, stats, gamma, dy, add, M, D, dx, nullptr, nullptr);
     if (want_cols) {
       AQT_HIP(hipGetLastError());
       P = static_cast<int>(cdiv(M, 256) < kLnBwdBlocks ? cdiv(M, 256) : kLnBwdBlocks);
@@ -602,7 +605,7 @@ aqt_status launch_layernorm_bwd(const float *x, const float *stats, const float 
     ln_bwd_fold_kernel<<<dim3(static_cast<unsigned>(cdiv(D, 64)), 2), 64 * kFoldWaves, 0, st>>>(part, P, D, dgamma, dbeta);
     AQT_HIP(hipGetLastError());
   }
-  return AQT_OK;
+  return half && !vec ? launch_scale(dx, 0.5f, half, M * D, st) : AQT_OK;   // after the column sums: half may be dy
 }
 
 aqt_status launch_scale(const float *m, float alpha, float *out, int64_t n, hipStream_t st) {
