@@ -873,13 +873,12 @@ aqt_status aqt_conv_module_bwd(const float *dy, const aqt_conv_saved *saved, con
   hipStream_t st = static_cast<hipStream_t>(stream);
   // second pointwise convolution: gradient with respect to s, dw2, db2
   AQT_TRY(launch_dense_bwd(dy, &l2, M, D, D, f.ds, dw2, db2, ws, f.core, st));
-  // through Swish and normalisation (dfac), then the depthwise convolution
+  // through Swish and normalisation (dfac), the depthwise convolution and the GLU
   const bool more = dxn || dw1 || db1;
   AQT_TRY(launch_dwconv_bwd(f.ds, saved->dfac, saved->g, w_dw, B, T, D, kw, pad_left, more ? f.dg : nullptr, dw_dw,
-                            db_dw, f.taps, st));
+                            db_dw, f.taps, st, more ? l1.dact : nullptr, f.dv));
   if (!more) return AQT_OK;
-  // through the GLU, then the first pointwise convolution
-  AQT_TRY(launch_dact_mul(f.dg, l1.dact, M, 2 * D, D, f.dv, st));
+  // the first pointwise convolution
   return launch_dense_bwd(f.dv, &l1, M, D, 2 * D, dxn, dw1, db1, ws, f.core, st);
 }
 

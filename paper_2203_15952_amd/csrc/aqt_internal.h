@@ -189,7 +189,7 @@ aqt_status launch_dwconv_fwd(const float *x, const float *w, const float *bias, 
                              uint32_t *absmax, hipStream_t st, bool absmax_is_zero = false);
 aqt_status launch_dwconv_bwd(const float *dout, const float *dmul, const float *x, const float *w, int64_t B, int64_t T,
                              int64_t C, int kw, int pad_left, float *dx, float *dw, float *dbias, void *ws,
-                             hipStream_t st);
+                             hipStream_t st, const float *gate = nullptr, float *dv = nullptr);   // with gate: dv [B T, 2 C] is wanted, dx scratch
 
 // ---- attention core of the self-attention module (attention.hip, attention_fwd.hip, attention_bwd.hip) -------------
 struct AttnShape {

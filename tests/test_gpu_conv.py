@@ -273,6 +273,25 @@ def test_conv_module_chain_stage_by_stage(B_, T, D, kw, pl, policy):
     check_grad(host(o["db1"]), g1["dbias"], np.abs(g1["dv"]).sum(0), "db1")
 
 
+@pytest.mark.parametrize("B_,T,D,kw,pl", [(1, 1, 4, 1, 0), (2, 7, 64, 3, 1), (1, 9, 66, 5, 4), (3, 64, 64, 15, 7), (2, 65, 70, 32, 15),
+                                          (2, 129, 130, 32, 31), (1, 40, 24, 33, 16)])   # 33 taps: the untiled kernel
+def test_conv_module_backward_through_the_gate(B_, T, D, kw, pl):
+    """The depthwise gradient times the gate's factors in one kernel: the bits of the calls made one by one."""
+    say("conv module backward, gate", B_, T, D, kw)
+    M, policy = B_ * T, ((8, 8), (8, 8))
+    i = module_inputs(900 + M, B_, T, D, kw)
+    d = {k: dev(v) for k, v in i.items()}
+    sv = B.ConvSaved(B_, T, D, policy)
+    B.aqt_conv_module_fwd(d["x"], d["w1"], d["b1"], d["w_dw"], d["b_dw"], d["w2"], d["b2"], sv, pad_left=pl, gamma=d["gamma"],
+                          beta=d["beta"], eps=1e-6, norm_scale=d["na"], norm_shift=d["nb"])
+    o = B.aqt_conv_module_bwd(d["dy"], sv, d["w_dw"], pad_left=pl)
+    ds, _, _ = B.aqt_dense_bwd(d["dy"], sv.pw2, 8, 8, want_dw=False)
+    dg, dw_dw, db_dw = B.aqt_depthwise_conv_bwd(ds.view(B_, T, D), sv.g.view(B_, T, D), d["w_dw"], dfac=sv.dfac.view(B_, T, D), pad_left=pl)
+    dxn, dw1, db1 = B.aqt_dense_bwd(dg.view(M, D), sv.pw1, 8, 8, epilogue=B.AQT_EPI_GLU, want_dbias=True)
+    for name, want in (("dxn", dxn), ("dw1", dw1), ("db1", db1), ("dw_dw", dw_dw), ("db_dw", db_dw)):
+        np.testing.assert_array_equal(host(o[name]), host(want), err_msg=name)
+
+
 def test_conv_module_rejects_float_activations():
     sv = B.ConvSaved(1, 64, 128, ((4, 0), (8, 8)))
     z = torch.zeros((64, 128), device="cuda")

@@ -265,6 +265,29 @@ def torch_float_layer(x, w, B_, T, D, heads, kw, pl, left, right):
     return Fn.layer_norm(r4, (D,), w["out_ln_g"], w["out_ln_b"], eps=1e-6)
 
 
+@pytest.mark.parametrize("D,heads", [(18, 2), (20, 1), (516, 12), (1032, 24)])
+def test_conformer_layer_backward_halves_the_stream_gradient(D, heads):
+    """Rows of every kernel of the normalisation's backward: the halves handed to the feed-forward modules are exact."""
+    B_, T, H, kw, pl = 1, 5, 24, 3, 1
+    say("encoder layer bwd, halves", D)
+    wd = {k: dev(v) for k, v in layer_weights(840, D, H, kw).items()}
+    rng = np.random.default_rng(841)
+    x_d, dy_d = (dev(rng.standard_normal((B_ * T, D)).astype(F)) for _ in range(2))
+    _, sv = run_layer(x_d, wd, B.aqt_policy_preset(B.AQT_POLICY_ALL, 1, 0, 8, 8)[0], B_, T, D, H, heads, kw, pl, -1, -1)
+    dx, grads = B.aqt_conformer_layer_bwd(dy_d, x_d, wd, sv, B=B_, T=T, H=H, heads=heads, kw=kw, pad_left=pl, left=-1, right=-1)
+    dr4, _, _ = B.aqt_layernorm_bwd(sv.r[3], sv.out_row_stats, dy_d, gamma=wd["out_ln_g"])
+    dxn, dw1, _, _, _ = B.aqt_ffn_bwd(B.aqt_residual_add(dr4, dr4, -0.5), sv.ffn2)
+    dr3, _, _ = B.aqt_layernorm_bwd(sv.r[2], sv.ffn2.row_stats, dxn, gamma=wd["ffn2_ln_g"], add=dr4)
+    dr2, _, _ = B.aqt_layernorm_bwd(sv.r[1], sv.conv.row_stats, B.aqt_conv_module_bwd(dr3, sv.conv, wd["conv_wdw"], pad_left=pl)["dxn"],
+                                    gamma=wd["conv_ln_g"], add=dr3)
+    dr1, g_a, b_a = B.aqt_layernorm_bwd(sv.r[0], sv.att.row_stats, B.aqt_mhsa_bwd(dr2, sv.att, heads, left=-1, right=-1)["dxn"],
+                                        gamma=wd["att_ln_g"], add=dr2)
+    dxn1, dw1a, _, _, _ = B.aqt_ffn_bwd(B.aqt_residual_add(dr1, dr1, -0.5), sv.ffn1)
+    want, _, _ = B.aqt_layernorm_bwd(x_d, sv.ffn1.row_stats, dxn1, gamma=wd["ffn1_ln_g"], add=dr1)
+    for got, ref in ((dx, want), (grads["ffn2_w1"], dw1), (grads["ffn1_w1"], dw1a), (grads["att_ln_g"], g_a), (grads["att_ln_b"], b_a)):
+        np.testing.assert_array_equal(host(got), host(ref))
+
+
 def test_conformer_layer_backward_equals_its_modules_and_tracks_the_float_gradient():
     B_, T, D, H, heads, kw, pl, left, right = 4, 150, 256, 1024, 4, 15, 14, 23, 0
     M = B_ * T
