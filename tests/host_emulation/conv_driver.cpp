@@ -48,7 +48,7 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
   int kwp = (kw + 3) & ~3;
   if (kw <= kTapsMax) run(g.cgroups * P, 256, (size_t)(2 * kTile + 2 * kwp + 6) * 256, [&] { dwconv_dw_kernel(dout, dfac, x, g, P, part); });
   else run(cdiv((int64_t)(kw + 1) * C, 256), 256, 0, [&] { dwconv_dw_any_kernel(dout, dfac, x, g, part); });
-  run(cdiv((int64_t)(kw + 1) * C, 256), 256, 0, [&] { dwconv_dw_fold_kernel(part, P, kw, C, dw, db); });
+  run(cdiv((int64_t)(kw + 1) * C, 64), 256, 0, [&] { dwconv_dw_fold_kernel(part, P, kw, C, dw, db); });
   std::vector<double> rw((kw + 1) * C), mw((kw + 1) * C);
   for (int j = 0; j <= kw; ++j) for (int64_t c = 0; c < C; ++c) {
     double a = 0, m = 0;
