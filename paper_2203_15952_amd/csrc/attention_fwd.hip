@@ -216,13 +216,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_fwd_rows_kernel(const f
   if (absmax) {   // uniform: the word only grows, so a stale read can only cost a redundant atomic
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) amax = max(amax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(amax), off)));
-    __syncthreads();   // the output images have been read: four words of them hold the wavefronts' maxima
-    if (lane == 0) lds[wave] = __uint_as_float(amax);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int i = 1; i < 4; ++i) amax = max(amax, __float_as_uint(lds[i]));
-      if (amax > *reinterpret_cast<volatile uint32_t *>(absmax)) atomicMax(absmax, amax);
-    }
+    if (lane == 0 && amax > *reinterpret_cast<volatile uint32_t *>(absmax)) atomicMax(absmax, amax);
   }
 }
 
