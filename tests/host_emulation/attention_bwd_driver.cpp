@@ -39,7 +39,7 @@ static void one(int64_t B, int64_t T, int64_t D, int heads, int left, int right)
     }
   }
   double worst = 0;
-  for (size_t i = 0; i < 3 * n; ++i) { double e = fabs((double)dqkv[i] - ref[i]) / (mag[i] + 1e-30); if (!(e <= worst)) worst = e; }
+  for (size_t i = 0; i < 3 * n; ++i) { at_least(worst, fabs((double)dqkv[i] - ref[i]) / (mag[i] + 1e-30)); }
   printf("  worst err / sum|terms| = %.3g\n", worst);
   if (!(worst < 1e-4)) { printf("  MISMATCH\n"); bad = 1; }
   free(qkv); free(ctx); free(dctx); free(lse); free(dsum); free(dqkv);

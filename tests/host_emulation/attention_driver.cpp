@@ -23,7 +23,7 @@ static void one(int64_t B, int64_t T, int64_t D, int heads, int left, int right)
       double a = 0, ab = 0;
       for (int64_t j = j0; j <= j1; ++j) { double v = qkv[(b * T + j) * 3 * D + 2 * D + h * dh + d]; a += p[j] * v; ab += p[j] * fabs(v); }
       double e = fabs((double)ctx[(b * T + t) * D + h * dh + d] - a / sum) / (ab / sum + 1e-30);
-      if (e > worst) worst = e;
+      at_least(worst, e);
     }
   }
   for (size_t i = 0; i < n; ++i) mx = std::max(mx, fabsf(ctx[i]));

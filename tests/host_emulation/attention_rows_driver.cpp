@@ -60,8 +60,8 @@ static void one(int64_t B, int T, int64_t D, int heads, int left, int right, boo
   }
   double worst = 0, worst_fwd = 0;
   float mx = 0;
-  for (size_t i = 0; i < 3 * n; ++i) { double e = fabs((double)dqkv[i] - ref[i]) / (mag[i] + 1e-30); if (!(e <= worst)) worst = e; }
-  for (size_t i = 0; i < n; ++i) { double e = fabs((double)ctx[i] - out[i]) / (omag[i] + 1e-30); if (!(e <= worst_fwd)) worst_fwd = e; mx = std::max(mx, fabsf(ctx[i])); }
+  for (size_t i = 0; i < 3 * n; ++i) { at_least(worst, fabs((double)dqkv[i] - ref[i]) / (mag[i] + 1e-30)); }
+  for (size_t i = 0; i < n; ++i) { at_least(worst_fwd, fabs((double)ctx[i] - out[i]) / (omag[i] + 1e-30)); mx = std::max(mx, fabsf(ctx[i])); }
   printf("  worst err / sum|terms| = %.3g forward, %.3g backward\n", worst_fwd, worst);
   if (!(worst < 1e-5) || !(worst_fwd < 1e-5) || __float_as_uint(mx) != am) { printf("  MISMATCH\n"); bad = 1; }
   free(qkv); free(ctx); free(dctx); free(lse); free(dsum); free(dqkv);

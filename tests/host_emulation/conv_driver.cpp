@@ -7,7 +7,7 @@ static float *mk(size_t n, float v, unsigned seed) { float *p = (float *)malloc(
 static int bad = 0;
 static void cmp(const char *what, const float *got, const double *ref, const double *mag, size_t n) {
   double worst = 0;
-  for (size_t i = 0; i < n; ++i) { double e = fabs((double)got[i] - ref[i]) / (mag[i] + 1e-30); if (e > worst) worst = e; }
+  for (size_t i = 0; i < n; ++i) { at_least(worst, fabs((double)got[i] - ref[i]) / (mag[i] + 1e-30)); }
   printf("  %-6s worst err / sum|terms| = %.3g\n", what, worst);
   if (!(worst < 1e-4)) bad = 1;
 }

@@ -61,7 +61,7 @@ template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> 
     }
     const double ref = GLU ? v[0] * sigma(v[1]) : EPI == AQT_EPI_SWISH ? v[0] * sigma(v[0]) : v[0];
     const double e = fabs((double)y[m * oc + n] - ref) / (1.0 + fabs(ref));
-    if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e;
+    at_least(worst, e);
     mx = std::max(mx, fabsf(y[m * oc + n]));
   }
   expect("integer sums that differ", sums, 0);
@@ -82,10 +82,11 @@ static void disturb(float *f, int64_t row, int64_t step, int64_t length, int64_t
   }
   if (i % 7 == 5) f[row + (length - 1) * step] = i % 2 ? INFINITY : -INFINITY;
 }
-// not further from the float64 loop than the last rounding and its own sums
+// Not further from the float64 loop than the last rounding and its own sums: at most 1.
 static double beyond_rounding(float got, double ref, double rounded, double mag, double share) {   // rounded: what float32 held on the way
-  if (!std::isfinite((float)ref)) return std::isnan(ref) ? !std::isnan(got) : got != (float)ref;
-  if (!std::isfinite(mag) || !std::isfinite(rounded)) return got != ref;   // an infinity behind a clip mask
+  const double wrong = INFINITY;
+  if (!std::isfinite((float)ref)) return (std::isnan(ref) ? std::isnan(got) : got == (float)ref) ? 0.0 : wrong;
+  if (!std::isfinite(mag) || !std::isfinite(rounded)) return got == ref ? 0.0 : wrong;   // an infinity behind a clip mask
   const double limit = share * rounded + 1e-13 * mag + 3e-45;
   return fabs((double)got - ref) / limit;
 }
@@ -122,7 +123,7 @@ template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_
     else if (GLU) ref = v[0] * sigma(v[1]);
     else if (MODE == 1 + AQT_EPI_SWISH) ref = v[0] * sigma(v[0]);
     const double e = wild ? beyond_rounding(out[m * oc + r], ref, fabs(ref) + held, mag, limit) : fabs((double)out[m * oc + r] - ref) / (mag + 1e-30);
-    if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e;
+    at_least(worst, e);
   }
   expect(wild ? "error / (rounding of the result)" : "error / sum |terms|", worst, wild ? 1 : limit);
 }
@@ -191,14 +192,14 @@ template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int
   for (int64_t n = 0; n < N; ++n) {
     double b = 0, ba = 0;
     for (int64_t m = 0; m < M; ++m) { b += dy[m * N + n]; ba += fabs(dy[m * N + n]); }
-    worst_b = std::max(worst_b, wild ? beyond_rounding(db[n], b, fabs(b), ba, 6.1e-8) : fabs(db[n] - b) / (ba + 1e-30));
+    at_least(worst_b, wild ? beyond_rounding(db[n], b, fabs(b), ba, 6.1e-8) : fabs(db[n] - b) / (ba + 1e-30));
     for (int64_t k = 0; k < K; ++k) {
       double s = 0, mag = 0;
       for (int64_t m = 0; m < M; ++m) { const double t = (double)sx[0] * x.v[m * K + k] * dy[m * N + n]; s += t; mag += fabs(t); }
       const int64_t at = k * N + n;
       if (masked ? !(mask[at >> 5] >> (at & 31) & 1) : sw[n] == 0.0f) s = 0;
       const double e = wild ? beyond_rounding(dw[at], s, fabs(s), mag, 6.1e-8) : fabs(dw[at] - s) / (mag + 1e-30);
-      if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e;
+      at_least(worst, e);
     }
   }
   expect(wild ? "dW, error / (rounding of the result)" : "dW, error / sum |terms|", worst, wild ? 1 : F64 ? 6.1e-8 : 3e-6);

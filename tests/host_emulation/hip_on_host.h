@@ -60,6 +60,8 @@ inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f;
 static std::mutex g_mu;
 inline uint32_t atomicMax(uint32_t *p, uint32_t v) { std::lock_guard<std::mutex> l(g_mu); uint32_t o = *p; if (v > o) *p = v; return o; }
 using std::max; using std::min;
+// the largest error so far; a NaN is as wrong as can be
+inline void at_least(double &worst, double e) { if (!(e <= worst)) worst = std::isnan(e) ? INFINITY : e; }
 inline float __builtin_amdgcn_rcpf(float d) { return 1.0f / d; }
 namespace aqt {
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
