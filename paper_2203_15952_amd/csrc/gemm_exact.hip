@@ -6,12 +6,13 @@
 // largest.  Such an integer is six balanced base-256 digits, i.e. six int8 operands, and v_mfma_i32_16x16x64_i8 adds
 // digit x code products without rounding.  One float64 fused multiply-add makes the integer (the sum with 1.5 * 2^52
 // leaves it in the low mantissa bits) and adds 0x80 to every digit, so the digits are the bytes with their top bit flipped.
-// What a row has below that range, and rows that hold an infinity or a NaN, are multiplied in float64 (v_mfma_f64_16x16x4_f64)
-// and added on: only sixteen positions at a time that hold such a value, by the wavefront that finds one when it looks for
-// the largest and smallest of its rows.  In a normally distributed gradient that is one value in a million.
+// In a normally distributed gradient one value in a million lies below that range; in that of a softmax most do (logits of standard
+// deviation 3: a row spans thirty binades).  What the digits leave of a few such values is kept in a list as they are converted, and
+// multiplied in float64, four at a time.  Where more are left than the list holds the workgroup goes through its rows again for the next plane of
+// six digits, 47 binades further down, and so on; two planes do for a softmax, six for any two float32 values.
 //
-// The few such values are kept in a list as they are converted (what the digits leave of them, and where); more than fit, or
-// a row that is not finite, and the rows are gone through again.
+// An infinity or a NaN is multiplied in float64 (v_mfma_f64_16x16x4_f64), the sixty-four positions that hold it: they decide
+// their row's results, whatever the rest of it adds up to.
 //
 // Six int8 passes are 1/10 of the matrix time of the float64 instruction, so the conversion of the float operand weighs as
 // much as the products: about nine vector instructions a value, for 16 TJ products.  Hence a wavefront converts its own
@@ -19,8 +20,10 @@
 // results: 24 TJ accumulator registers, at TJ = 5 two wavefronts per SIMD.  The codes of a step are shared by the four
 // wavefronts of a workgroup through LDS.  The order of the contraction inside a step of 64 is free: lane group g of four takes
 // positions 16 i + 4 g .. + 3 (i = 0 .. 3), so that a load instruction reads whole 64-byte pieces of a row.
-// At 4099 x 520 x 1000 dX takes 50 and dW 42 us, there 110 and 116 (us of a step with both layers, all kernels: 531 -> 285); error
-// against float64 2.5e-8 of the result for each, as there.  A wavefront's 82 k cycles (dX) are 20 k of vector and 8 k of matrix
+// At 4099 x 520 x 1000 dX takes 46 and dW 50 us, there 114 and 118; with the gradient of a softmax over the 1000 channels 74 and 81.
+// (The lower planes have code of their own: in the first one's loop their conversion spilled, and cost dW 6 us with ordinary values.
+// The float64 products of every step with such a value, which stood in their place, took 269 and 226.)  Error
+// against float64 2.5e-8 of the result for each, as there.  A wavefront's 82 k cycles (dX, one plane) are 20 k of vector and 8 k of matrix
 // instructions, 30 k waiting for the other wavefront's, 24 k waiting for loads, a third of that in the search for the extremes.
 // Loads two steps ahead instead of one, for either operand, changed nothing; 96 columns a tile spill.
 #include "any_shape.h"
@@ -38,7 +41,8 @@ constexpr int kThreads = 256;    // four wavefronts of sixteen rows (dX, weight-
 constexpr int kOwn = 64;         // rows or channels of a workgroup
 constexpr int kStep = 64;        // contraction positions per step
 constexpr int kDigits = 6;
-constexpr int kRange = 22;       // binades below the largest that are exact
+constexpr int kRange = 22;       // binades below the largest that are exact in the first plane of digits
+constexpr int kPlane = 47;       // binades from a plane to the next: a remainder of at most half a unit stays below 2^46
 constexpr int64_t kLongest = 65536;   // 128 * 128 * 65536 < 2^31
 constexpr double kMagic = 6755399441055744.0 + 141289400074368.0;   // 1.5 * 2^52 + 0x808080808080
 
@@ -56,6 +60,8 @@ __device__ __forceinline__ int anew(int v) {   // the same value, as far as the 
 __device__ __forceinline__ double power_of_two(int e) {   // normal range
   return __builtin_bit_cast(double, static_cast<uint64_t>(1023 + e) << 52);
 }
+
+__device__ __forceinline__ bool is_finite(float v) { return (__float_as_uint(v) & 0x7FFFFFFFu) < 0x7F800000u; }
 
 // The largest and the smallest non-zero magnitude of a row, as bit patterns.
 struct Extremes {
@@ -85,9 +91,10 @@ struct Extremes {
   }
   __device__ __forceinline__ bool finite() const { return top < 0x7F800000u; }
   __device__ __forceinline__ int exponent() const { return max(static_cast<int>(top >> 23), 1); }   // biased; subnormals like 1
-  // every non-zero magnitude below this pattern may leave something (all of them in a row that is not finite)
-  __device__ __forceinline__ uint32_t doubtful() const {
-    return !finite() ? 0xFFFFFFFFu : exponent() > kRange ? static_cast<uint32_t>(exponent() - kRange) << 23 : 1u;
+  // every non-zero magnitude below this pattern may leave something behind planes 0 .. plane (rows that are not finite: none)
+  __device__ __forceinline__ uint32_t doubtful(int plane) const {
+    const int reach = kRange + kPlane * plane;
+    return finite() && exponent() > reach ? static_cast<uint32_t>(exponent() - reach) << 23 : 1u;
   }
   __device__ __forceinline__ bool exact() const {
     const int least = low == 0xFFFFFFFFu ? exponent() : max(static_cast<int>(low >> 23), 1);
@@ -98,15 +105,20 @@ struct Extremes {
 __device__ __forceinline__ double scale_of(int exponent) { return power_of_two(172 - exponent); }
 __device__ __forceinline__ double unscale_of(int exponent) { return power_of_two(exponent - 172); }
 
-// What the digits of a finite row leave of a value, exactly.
-__device__ __forceinline__ double below_digits(float x, int exponent) {
-  const double scale = scale_of(exponent), y = static_cast<double>(x) * scale;
-  return (y - (__builtin_fma(static_cast<double>(x), scale, kMagic) - kMagic)) * unscale_of(exponent);
+// The unit of a plane's last digit is 2^(-47 plane) of the first one's.
+__device__ __forceinline__ double unit_of(int plane) { return power_of_two(-kPlane * plane); }
+// What a plane leaves of a value given in units of its last digit, in units of the next one's.  Exact.
+__device__ __forceinline__ double next_plane(double y) { return (y - ((y + kMagic) - kMagic)) * power_of_two(kPlane); }
+// What all planes down to this one leave of a finite row's value, exactly.
+__device__ __forceinline__ double below_digits(float x, int exponent, int plane) {
+  double y = static_cast<double>(x) * scale_of(exponent);
+  for (int k = 0; k <= plane; ++k) y = next_plane(y);
+  return y * (unscale_of(exponent) * unit_of(plane + 1));
 }
 
 // The few values of a wavefront's rows that reach below the digits, found while they are converted: what the digits leave of
-// them, in a fixed order.  More than fit (or a row that is not finite): the rows are gone through again (for_all).
-constexpr int kFew = 24;
+// them, in a fixed order.  More than fit: another plane of digits.
+constexpr int kFew = 16;
 struct Left {
   double value;
   int row, at;   // the lane's row or channel of sixteen, the position
@@ -114,22 +126,45 @@ struct Left {
 struct LeftList {
   Left *entry;   // kFew of this wavefront
   int n = 0;     // uniform
-  __device__ __forceinline__ void note(float x, uint32_t doubtful, int exponent, int row, int at) {
-    const bool is = (__float_as_uint(x) & 0x7FFFFFFFu) - 1u < doubtful - 1u;
-    const uint64_t lanes = __ballot(is);
-    if (lanes == 0) return;
-    const int slot = n + static_cast<int>(__popcll(lanes & ((1ull << (threadIdx.x & 63)) - 1ull)));
-    if (is && slot < kFew) entry[slot] = Left{below_digits(x, exponent), row, at};
-    n += static_cast<int>(__popcll(lanes));
+  __device__ __forceinline__ bool fits() const { return n <= kFew; }
+  // four values of the lane's row, at positions at .. at + 3
+  __device__ __forceinline__ void note(v4f x, uint32_t doubtful, int exponent, int plane, int row, int at) {
+    uint32_t rank[4];   // of a zero: the largest
+#pragma unroll
+    for (int e = 0; e < 4; ++e) rank[e] = (__float_as_uint(x[e]) & 0x7FFFFFFFu) - 1u;
+    if (!__any(min(min(rank[0], rank[1]), min(rank[2], rank[3])) < doubtful - 1u)) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool is = rank[e] < doubtful - 1u;
+      const uint64_t lanes = __ballot(is);
+      const int slot = n + static_cast<int>(__popcll(lanes & ((1ull << (threadIdx.x & 63)) - 1ull)));
+      if (is && slot < kFew) entry[slot] = Left{below_digits(x[e], exponent, plane), row, at + e};
+      n += static_cast<int>(__popcll(lanes));
+    }
   }
+  // entry k, for a lane that stands for `row`; nothing where it is another row's or behind the end
+  __device__ __forceinline__ double value(int k, int row) const {
+    return k < n && entry[k].row == row ? entry[k].value : 0.0;
+  }
+  __device__ __forceinline__ int at(int k) const { return entry[k < n ? k : n - 1].at; }
 };
 
 // Dword i of the six digit operands from the values of positions 4 i .. 4 i + 3 of the lane.
-__device__ __forceinline__ void digits4(v4f x, double scale, int i, v4i (&d)[kDigits]) {
+template <bool FIRST>
+__device__ __forceinline__ void digits4(v4f x, double scale, int plane, int i, v4i (&d)[kDigits]) {
   uint32_t lo[4], hi[4];
+  double y[4];
+  if (!FIRST) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = static_cast<double>(x[e]) * scale;
+    for (int k = 0; k < plane; ++k) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = next_plane(y[e]);
+    }
+  }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, __builtin_fma(static_cast<double>(x[e]), scale, kMagic));
+    const uint64_t u = __builtin_bit_cast(uint64_t, FIRST ? __builtin_fma(static_cast<double>(x[e]), scale, kMagic) : y[e] + kMagic);
     lo[e] = static_cast<uint32_t>(u);
     hi[e] = static_cast<uint32_t>(u >> 32);
   }
@@ -164,6 +199,19 @@ __device__ __forceinline__ void multiply(const uint8_t *codes, const v4i (&d)[kD
 #pragma unroll
     for (int p = 0; p < kDigits; ++p) acc[p][j] = OWN_IS_A ? mfma_i8(d[p], q, acc[p][j]) : mfma_i8(q, d[p], acc[p][j]);
   }
+}
+
+// Whether a condition holds in one of the workgroup's four wavefronts: set by each, asked behind a barrier, set again behind another.
+__device__ __forceinline__ void set_flag(int *flag, int wave, bool mine) {
+  if ((threadIdx.x & 63) == 0) flag[wave] = mine;
+}
+__device__ __forceinline__ bool in_some_wave(const int *flag) {
+  return __builtin_amdgcn_readfirstlane(flag[0] | flag[1] | flag[2] | flag[3]) != 0;
+}
+__device__ __forceinline__ bool in_some_wave(int *flag, int wave, bool mine) {
+  set_flag(flag, wave, mine);
+  __syncthreads();
+  return in_some_wave(flag);
 }
 
 // Workgroup -> (strip, tile of the strip).  A strip's tiles read the same float rows; workgroup ids eight apart run on one
@@ -285,14 +333,20 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
   const int exponent = x.exponent();
   const double up = x.finite() ? scale_of(exponent) : 0.0;   // a row with an infinity: its digits are not used
   const bool finite = !__any(!x.finite()), wide = __any(!x.exact());   // uniform
-  const uint32_t doubtful = x.doubtful();
   __shared__ Left few[kThreads / 64][kFew];
+  __shared__ double above[4 * TJ][kThreads];   // the sums of the planes above
+  __shared__ int flag[2][kThreads / 64];
+  set_flag(flag[0], wave, wide);
   const bool keep = DX ? s_x[0] != 0.0f : true;
 
   for (; br < br_end; ++br) {
+  // ---- the digits of one plane (the first in code of its own, which most rows are done with) ----
+  v4i acc[kDigits][TJ];
+  LeftList list{few[wave]};
+  auto go_through = [&](auto first, int plane) {
+  constexpr bool FIRST = decltype(first)::value;
   // the thread's place anew, unknown to the compiler: what follows from it would otherwise stay in registers over the loop
   const int tt = anew(t), lc = tt & 15, lg = tt >> 4 & 3;
-  LeftList list{few[wave]};
   const uint8_t *pq[NQ];
 #pragma unroll
   for (int u = 0; u < NQ; ++u) {
@@ -300,9 +354,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
     const int64_t n = chan(row >> 4) + (row & 15);
     pq[u] = q + (n < R ? n : R - 1) * row_bytes;
   }
-
-  // ---- the digits ----
-  v4i acc[kDigits][TJ];
+  list.n = 0;
+  const uint32_t doubtful = x.doubtful(plane);
   const int zero = anew(0);
 #pragma unroll
   for (int p = 0; p < kDigits; ++p)
@@ -375,11 +428,8 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const v4f v = scaled(raw[i], i, P);
-      digits4(v, up, i, d);
-      if (wide && finite) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) list.note(v[e], doubtful, exponent, lc, kStep * s + 16 * i + 4 * lg + e);
-      }
+      digits4<FIRST>(v, up, plane, i, d);
+      if (wide && list.fits()) list.note(v, doubtful, exponent, plane, lc, kStep * s + 16 * i + 4 * lg);
       load_f(i, clamped(s + 1));
     }
     AQT_SCHED_FENCE();
@@ -391,35 +441,50 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
     if (s + 1 < steps) step(std::integral_constant<int, 1>{}, s + 1);
   }
 
-  // ---- sums: digits, then in float64 what they left ----
-  const int el = anew(lane), ec = el & 15, eg = el >> 4;
+  };
+
+  // ---- sums: the planes, then what they left ----
   v4d sum[TJ];
+  auto take_sums = [&](int plane) {
+    const int eg = anew(lane) >> 4;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double down = (PACKED ? 0.0625 : 1.0) * unscale_of(__shfl(exponent, 4 * eg + r));
-    const bool fine = __shfl(static_cast<int>(x.finite()), 4 * eg + r) != 0;
+    for (int r = 0; r < 4; ++r) {
+      const double down = (PACKED ? 0.0625 : 1.0) * unscale_of(__shfl(exponent, 4 * eg + r)) * unit_of(plane);
+      const bool fine = __shfl(static_cast<int>(x.finite()), 4 * eg + r) != 0;
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) sum[j][r] = fine ? digits_sum<TJ>(acc, j, r) * down : 0.0;
+      for (int j = 0; j < TJ; ++j) sum[j][r] = fine ? digits_sum<TJ>(acc, j, r) * down : 0.0;
+    }
+  };
+  go_through(std::true_type{}, 0);
+  take_sums(0);
+  if (in_some_wave(flag[0])) {   // behind the sixth plane nothing is left of any value
+    for (int plane = 1; in_some_wave(flag[1], wave, !list.fits()); ++plane) {
+#pragma unroll
+      for (int i = 0; i < 4 * TJ; ++i) above[i][t] = sum[i >> 2][i & 3];
+      go_through(std::false_type{}, plane);
+      take_sums(plane);
+#pragma unroll
+      for (int i = 0; i < 4 * TJ; ++i) sum[i >> 2][i & 3] = above[i][t] + sum[i >> 2][i & 3];
+    }
   }
+  const int el = anew(lane), ec = el & 15, eg = el >> 4;
   auto code_at = [&](int64_t n, int c) -> int {
     const uint8_t *const qr = q + (n < R ? n : R - 1) * row_bytes;
     if (PACKED) return static_cast<int>(static_cast<uint32_t>(qr[c >> 1]) << ((c & 1) ? 24 : 28)) >> 28;
     return static_cast<int8_t>(qr[c]);
   };
-  if (finite && list.n <= kFew) {
-    __builtin_amdgcn_wave_barrier();
-    for (int k = 0; k < list.n; ++k) {
-      const Left l = list.entry[k];
+  __builtin_amdgcn_wave_barrier();
+  for (int k = 0; k < list.n; k += 4) {   // four entries in turn as the positions of a product
+    const double left = list.value(k + eg, f64_row(ec));
+    const int at = list.at(k + eg);
+    double code[TJ];
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) {
-        const double term = l.value * static_cast<double>(code_at(chan(j) + ec, l.at));
+    for (int j = 0; j < TJ; ++j) code[j] = static_cast<double>(code_at(chan(j) + ec, at));
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (4 * eg + r == l.row) sum[j][r] += term;
-      }
-    }
-  } else {
-    const int row = f64_row(ec), ex = __shfl(exponent, row);
+    for (int j = 0; j < TJ; ++j) sum[j] = mfma_f64(left, code[j], sum[j]);
+  }
+  if (!finite) {
+    const int row = f64_row(ec);
     const bool fine = __shfl(static_cast<int>(x.finite()), row) != 0;
     const uint32_t fr = row_at(16 * wave + row);
     int last = -1;   // a step that is seen again is not added again
@@ -428,7 +493,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) some = some || (__float_as_uint(seen[i][e]) & 0x7FFFFFFFu) - 1u < doubtful - 1u;
+        for (int e = 0; e < 4; ++e) some = some || !is_finite(seen[i][e]);
       if (s == last || !__any(some)) return;
       last = s;
       for (int c0 = kStep * s; c0 < kStep * (s + 1) && c0 < C; c0 += 16) {
@@ -446,7 +511,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
           for (int e = 0; e < 4; ++e) code[j][e] = static_cast<double>(code_at(chan(j) + ec, c + e < C ? c + e : C - 1));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const double left = fine ? below_digits(v[e], ex) : static_cast<double>(v[e]);
+          const double left = fine ? 0.0 : static_cast<double>(v[e]);
 #pragma unroll
           for (int j = 0; j < TJ; ++j) sum[j] = mfma_f64(left, c + e < C ? code[j][e] : 0.0, sum[j]);
         }
@@ -514,23 +579,15 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
     return load_f32(py + static_cast<int64_t>(row) * N, own, more * row_bytes);
   };
   const int8_t *const px = xq + m0 * K;
-  const int g = t % G, mg = t / G;          // this thread's positions 4 g .. + 3 and rows 8 mg .. + 7 of a step
-  const bool has = t < 8 * G;
-  int slot_of[4];                           // of positions 4 g + k, first four rows; the other four: 16 bytes to or fro
-#pragma unroll
-  for (int k = 0; k < 4; ++k) slot_of[k] = has ? code_slot(k * G + g, 2 * (mg & 1), mg >> 1) : BQ * kStep + (t - 8 * G) * 32 + 4 * k;
-  const int64_t kc = k0 + 4 * g;
-  // a piece that would cross the end of its row is read so that it ends there (what lies behind the end altogether is not used)
-  const int shift = 8 * (moved(kc, K, 4) & 3);
-  const uint32_t at_q = static_cast<uint32_t>((has ? 8 * mg : 0) * K + (kc + 4 <= K ? kc : K - 4));
   const int whole = rows / kStep;
 
   auto guarded = [&](int s, int i) {
     v4f v;
+    const int g4 = anew(4 * lg);   // or sixteen addresses stay in registers from plane to plane
 #pragma unroll
     for (int e = 0; e < 4; ++e) {   // clamped: no branch around a load
-      const int row = kStep * s + 16 * i + 4 * lg + e;
-      v[e] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(py + static_cast<int64_t>(min(row, rows - 1) - 4 * lg) * N) + own);
+      const int row = kStep * s + 16 * i + g4 + e;
+      v[e] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(py + static_cast<int64_t>(min(row, rows - 1) - g4) * N) + own);
       if (row >= rows) v[e] = 0.0f;
     }
     return v;
@@ -566,11 +623,28 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
   const int exponent = x.exponent();
   const double up = x.finite() ? scale_of(exponent) : 0.0;
   const bool finite = !__any(!x.finite()), wide = __any(!x.exact());   // uniform
-  const uint32_t doubtful = x.doubtful();
   __shared__ Left few[kThreads / 64][kFew];
-  LeftList list{few[wave]};
+  __shared__ double above[4 * TJ][kThreads];   // the sums of the planes above
+  __shared__ int flag[2][kThreads / 64];
+  set_flag(flag[0], wave, wide);
 
+  // the digits of one plane (the first in code of its own, which most rows are done with)
   v4i acc[kDigits][TJ];
+  LeftList list{few[wave]};
+  double colsum = 0.0;          // of this lane's channel, over the steps that are this tile's turn
+  auto go_through = [&](auto first, int plane) {
+  constexpr bool FIRST = decltype(first)::value;
+  const int tt = anew(t), g = tt % G, mg = tt / G;        // this thread's positions 4 g .. + 3 and rows 8 mg .. + 7 of a step
+  const bool has = tt < 8 * G;
+  int slot_of[4];                           // of positions 4 g + k, first four rows; the other four: 16 bytes to or fro
+#pragma unroll
+  for (int k = 0; k < 4; ++k) slot_of[k] = has ? code_slot(k * G + g, 2 * (mg & 1), mg >> 1) : BQ * kStep + (tt - 8 * G) * 32 + 4 * k;
+  const int64_t kc = k0 + 4 * g;
+  // a piece that would cross the end of its row is read so that it ends there (what lies behind the end altogether is not used)
+  const int shift = 8 * (moved(kc, K, 4) & 3);
+  const uint32_t at_q = static_cast<uint32_t>((has ? 8 * mg : 0) * K + (kc + 4 <= K ? kc : K - 4));
+  list.n = 0;
+  const uint32_t doubtful = x.doubtful(plane);
 #pragma unroll
   for (int p = 0; p < kDigits; ++p)
 #pragma unroll
@@ -600,9 +674,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
         *reinterpret_cast<uint32_t *>(sQ[slot] + (slot_of[k] ^ 16 * h)) = along[k];
     }
   };
-  double colsum = 0.0;          // of this lane's channel, over the steps that are this tile's turn
   auto add_up = [&](int s, const v4f (&v)[4]) {
-    if (!bias_part || s % tiles_k != kt) return;   // uniform
+    if (!FIRST || !bias_part || s % tiles_k != kt) return;   // uniform
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       colsum += (static_cast<double>(v[i][0]) + static_cast<double>(v[i][1])) +
@@ -629,11 +702,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
       add_up(s, raw);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        digits4(raw[i], up, i, d);
-        if (wide && finite) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) list.note(raw[i][e], doubtful, exponent, lc, kStep * s + 16 * i + 4 * lg + e);
-        }
+        digits4<FIRST>(raw[i], up, plane, i, d);
+        if (wide && list.fits()) list.note(raw[i], doubtful, exponent, plane, lc, kStep * s + 16 * i + 4 * lg);
         load_f(i, clamped(s + 1));
       }
       AQT_SCHED_FENCE();
@@ -646,22 +716,43 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
     }
   }
   if (whole * kStep < rows) {
+    const int first = anew(kStep * whole + (has ? 8 * mg : 0));
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      rq[i] = load_at<uint32_t>(px + static_cast<int64_t>(min(kStep * whole + (has ? 8 * mg : 0) + i, rows - 1)) * K + (kc + 4 <= K ? kc : K - 4));
+      rq[i] = load_at<uint32_t>(px + static_cast<int64_t>(min(first + i, rows - 1)) * K + (kc + 4 <= K ? kc : K - 4));
     store_q(0);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       raw[i] = guarded(whole, i);
-      digits4(raw[i], up, i, d);
-      if (wide && finite) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) list.note(raw[i][e], doubtful, exponent, lc, kStep * whole + 16 * i + 4 * lg + e);
-      }
+      digits4<FIRST>(raw[i], up, plane, i, d);
+      if (wide && list.fits()) list.note(raw[i], doubtful, exponent, plane, lc, kStep * whole + 16 * i + 4 * lg);
     }
     add_up(whole, raw);
     multiply<TJ, false>(sQ[0], d, acc, lc, lg);
+  }
+  };
+
+  // ---- sums: the planes, then what they left ----
+  v4d sum[TJ];
+  auto take_sums = [&](int plane) {
+    const double down = unscale_of(exponent) * unit_of(plane);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[j][r] = x.finite() ? digits_sum<TJ>(acc, j, r) * down : 0.0;
+  };
+  go_through(std::true_type{}, 0);
+  take_sums(0);
+  if (in_some_wave(flag[0])) {   // behind the sixth plane nothing is left of any value
+    for (int plane = 1; in_some_wave(flag[1], wave, !list.fits()); ++plane) {
+#pragma unroll
+      for (int i = 0; i < 4 * TJ; ++i) above[i][t] = sum[i >> 2][i & 3];
+      go_through(std::false_type{}, plane);
+      take_sums(plane);
+#pragma unroll
+      for (int i = 0; i < 4 * TJ; ++i) sum[i >> 2][i & 3] = above[i][t] + sum[i >> 2][i & 3];
+    }
   }
   if (bias_part) {
 #pragma unroll
@@ -671,52 +762,47 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
 
   // tile row 16 j + x holds the position of LDS row 16 j + x
   auto position = [&](int row) { return k0 + 4 * (row % G) + row / G; };
-  const double down = unscale_of(exponent);
-  v4d sum[TJ];
+  const int el = anew(lane), ec = el & 15, eg = el >> 4;   // the thread's place anew, as in the kernel above
+  __builtin_amdgcn_wave_barrier();
+  for (int k = 0; k < list.n; k += 4) {   // four entries in turn as the positions of a product
+    const double left = list.value(k + eg, ec);
+    const int8_t *const row = px + static_cast<int64_t>(list.at(k + eg)) * K;
+    double code[TJ];
 #pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sum[j][r] = x.finite() ? digits_sum<TJ>(acc, j, r) * down : 0.0;
-  if (finite && list.n <= kFew) {
-    __builtin_amdgcn_wave_barrier();
-    for (int k = 0; k < list.n; ++k) {
-      const Left l = list.entry[k];
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t at = position(16 * j + 4 * lg + r);
-          const double code = static_cast<double>(px[static_cast<int64_t>(l.at) * K + (at < K ? at : K - 1)]);
-          if (lc == l.row) sum[j][r] += l.value * code;
-        }
+    for (int j = 0; j < TJ; ++j) {
+      const int64_t at = position(16 * j + f64_row(ec));
+      code[j] = static_cast<double>(row[at < K ? at : K - 1]);
     }
-  } else {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) sum[j] = mfma_f64(code[j], left, sum[j]);
+  }
+  if (!finite) {
     int last = -1;
     for_all([&](int s, const v4f (&seen)[4]) {
       bool some = false;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) some = some || (__float_as_uint(seen[i][e]) & 0x7FFFFFFFu) - 1u < doubtful - 1u;
+        for (int e = 0; e < 4; ++e) some = some || !is_finite(seen[i][e]);
       if (s == last || !__any(some)) return;
       last = s;
+#pragma unroll 1
+      for (int i = 0; i < 4; ++i) {
+        const v4f v = guarded(s, i);   // zeros behind the slab
+        double left[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int e = 0; e < 4; ++e) left[e] = x.finite() ? 0.0 : static_cast<double>(v[e]);
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
-          const int64_t k = position(16 * j + f64_row(lc));
-          double code[4];
+          const int64_t k = position(16 * j + f64_row(ec));
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int row = kStep * s + 16 * i + 4 * lg + e;
-            code[e] = static_cast<double>(px[static_cast<int64_t>(row < rows ? row : rows - 1) * K + (k < K ? k : K - 1)]);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {   // a row behind the slab holds a zero
-            const double left = x.finite() ? below_digits(seen[i][e], exponent) : static_cast<double>(seen[i][e]);
-            sum[j] = mfma_f64(code[e], left, sum[j]);
+            const int row = kStep * s + 16 * i + 4 * eg + e;
+            const double code = static_cast<double>(px[static_cast<int64_t>(row < rows ? row : rows - 1) * K + (k < K ? k : K - 1)]);
+            sum[j] = mfma_f64(code, left[e], sum[j]);
           }
         }
+      }
     });
   }
   const double sx = dw ? static_cast<double>(fin.s_x[0]) : 1.0;
@@ -724,7 +810,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
   for (int j = 0; j < TJ; ++j)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t k = position(16 * j + 4 * lg + r), at = k * N + n;
+      const int64_t k = position(16 * j + 4 * eg + r), at = k * N + n;
       if (k >= K || !live) continue;
       if (dw) dw[at] = dw_value(sum[j][r], at, n, fin, sx);
       else partial[static_cast<int64_t>(slab) * K * N + at] = sum[j][r];
@@ -767,13 +853,19 @@ aqt_status f32_codes_sized(const CodesArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// Fewer results than this leave compute units idle while a workgroup goes through the contraction (1.4 us per 64 positions,
-// the search for the extremes included), which gemm_any_f64.hip splits instead.  Measured in us, there / here: dX 1300 x 288 of 1152
-// positions 29 / 34, 2600 x 144 of 576 19 / 21, 800 x 400 of 400 16 / 17, 1300 x 400 of 400 22 / 17, 1300 x 400 of 1200 45 / 34, 2600 x 288 of 1152
-// 43 / 40, 2600 x 288 of 288 16 / 18, 5200 x 144 of 576 29 / 22; weight-only 200 x 1000 of 520 10 / 16, 520 x 1000 of 520 26 / 16, 300 x 1030 of 2040
-// 44 / 50.
+// Fewer results than this leave compute units idle while a workgroup goes through the contraction, which gemm_any_f64.hip splits
+// instead; below 128 positions the search for the extremes and the sums outweigh the steps.  Measured in us, there / here / here with a
+// softmax's gradient (logits of standard deviation 3), which takes two planes; there the values do not matter:
+//   dX M x K of N positions: 4099 x 520 of 1000 114 / 46 / 74, 4099 x 1000 of 520 103 / 54 / 90, 9000 x 520 of 2040 392 / 144 / 256,
+//   5000 x 520 of 520 73 / 45 / 76, 10008 x 144 of 576 53 / 34 / 51, 10008 x 144 of 432 44 / 25 / 41, 3000 x 700 of 300 40 / 25 / 36;
+//   where a second plane costs more than the first one gains: 10008 x 144 of 144 20 / 16 / 27, 10008 x 576 of 144 48 / 38 / 74,
+//   1300 x 400 of 400 24 / 18 / 32, 5200 x 144 of 576 32 / 25 / 39;
+//   given up on one side of the line: 1300 x 400 of 1200 47 / 42 / 68, 4000 x 1001 of 100 31 / 27 / 43, 16000 x 72 of 72 15 / 13 / 20; on the
+//   other: 2600 x 288 of 288 18 / 18 / 29, 2600 x 288 of 1152 45 / 39 / 64; right of it 520 x 520 of 1000 27 / 30 / 58, 300 x 1030 of 2040
+//   48 / 53 / 104, 30000 x 96 of 96 24 / 26 / 41;
+//   weight-only 4099 x 1000 of 520 106 / 48 / 86, 520 x 1000 of 520 28 / 18 / 34, 4000 x 1001 of 100 30 / 25 / 40, 300 x 1030 of 2040 48 / 43 / 90.
 bool f32_codes_exact_ok(int64_t M, int64_t R, int64_t C) {
-  return C >= kStep && C <= kLongest && M * R >= (C > 1024 ? C * 488 : 500000);
+  return C >= 128 && C <= kLongest && M * R >= (C > 1024 ? C * 488 : 500000);
 }
 
 aqt_status launch_bwd_dx_exact(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,
@@ -793,9 +885,14 @@ aqt_status launch_dense_fwd_wonly_exact(const float *x, const void *wq_packed, c
   return packed4(bits_w) ? wonly<true>(a, epilogue, st) : wonly<false>(a, epilogue, st);
 }
 
-// (us, there / here: 100 x 520 x 1000 13 / 12, 520 x 520 x 1000 33 / 23, 10008 x 144 x 144 28 / 17)
+// Rows enough for two steps, and so many products (of whole tiles) that one launch more or less of a step does not decide.  us, as above,
+// M x K x N: 10008 x 144 x 144 30 / 22 / 31, 2600 x 288 x 288 27 / 22 / 30, 800 x 400 x 400 24 / 17 / 25, 200 x 520 x 1000 25 / 20 / 28,
+// 16000 x 72 x 72 26 / 18 / 26, 130 x 2000 x 2000 42 / 32 / 55, 4099 x 520 x 1000 118 / 50 / 81; below the line 128 x 520 x 1000 14 / 13 / 20,
+// 64 x 2000 x 2000 23 / 24 / 34, 1024 x 144 x 576 17 / 15 / 23, 6000 x 100 x 100 16 / 15 / 23, 600 x 72 x 72 13 / 13 / 20.
 bool dw_exact_ok(int64_t M, int64_t K, int64_t N, int slabs) {
-  return M >= kStep && K >= 4 && K < (1 << 24) && N < (1 << 24) &&   // 32-bit byte offsets inside a step
+  const Tiling g = tiling(cdiv(K, 16), 4, 1);
+  return M >= 2 * kStep && K >= 4 && K < (1 << 24) && N < (1 << 24) &&   // 32-bit byte offsets inside a step
+         M * (static_cast<int64_t>(g.tiles) * 16 * g.blocks) * (cdiv(N, kOwn) * kOwn) >= 100000000 &&
          cdiv(cdiv(M, slabs), kStep) * kStep <= kLongest;
 }
 

@@ -70,17 +70,20 @@ template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> 
 }
 
 // MODE 0: dX with a factor and a clip mask; 1 + e: weight-only forward.  kernel(f, scale, q, s_x, mask, factor, bias, out)
-// `wild`: rows with an infinity, and rows whose values lie further apart than the digits of gemm_exact.hip reach
-static void disturb(float *f, int64_t row, int64_t step, int64_t length, int64_t i) {   // element j of the row: f[row + j * step]
+// `wild`: rows whose values lie further apart than the digits of gemm_exact.hip reach, and among them rows with an infinity
+// (kInfinite) or that take all planes of digits (kFar)
+enum Wild { kTame, kInfinite, kFar };
+static void disturb(float *f, int64_t row, int64_t step, int64_t length, int64_t i, Wild wild) {   // element j of the row: f[row + j * step]
   for (int64_t j = 0; j < length; ++j) {
     float &v = f[row + j * step];
     if (i % 7 == 1) v = ldexpf(v, -(int)(j % 60));
     if (i % 7 == 2 && j % 50 == 9) v = ldexpf(v, -30);
     if (i % 7 == 3 && j % 2) v = ldexpf(v, 100);
     if (i % 7 == 4) v = ldexpf(v, -140);
+    if (i % 7 == 5 && wild == kFar) v = ldexpf(v, 100 - (int)(j * 37 % 240));
     if (i % 7 == 6) v = 0.0f;
   }
-  if (i % 7 == 5) f[row + (length - 1) * step] = i % 2 ? INFINITY : -INFINITY;
+  if (i % 7 == 5 && wild == kInfinite) f[row + (length - 1) * step] = i % 2 ? INFINITY : -INFINITY;
 }
 // Not further from the float64 loop than the last rounding and its own sums: at most 1.
 static double beyond_rounding(float got, double ref, double rounded, double mag, double share) {   // rounded: what float32 held on the way
@@ -90,7 +93,7 @@ static double beyond_rounding(float got, double ref, double rounded, double mag,
   const double limit = share * rounded + 1e-13 * mag + 3e-45;
   return fabs((double)got - ref) / limit;
 }
-template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_t R, int64_t C, double limit, Kernel kernel, bool wild = false) {
+template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_t R, int64_t C, double limit, Kernel kernel, Wild wild = kTame) {
   constexpr bool GLU = MODE == 1 + AQT_EPI_GLU;
   printf("float rows, mode %d packed %d: %ld %ld %ld\n", MODE, (int)PACKED, (long)M, (long)R, (long)C);
   const int64_t oc = GLU ? R / 2 : R, ns = MODE ? R : C;
@@ -100,7 +103,7 @@ template <int MODE, bool PACKED, class Kernel> void float_rows(int64_t M, int64_
   sx[0] = 1.0f;
   for (int64_t i = 0; i < M * C; ++i) f[i] = uniform();
   if (wild)
-    for (int64_t i = 0; i < M; ++i) disturb(f, i * C, 1, C, i);
+    for (int64_t i = 0; i < M; ++i) disturb(f, i * C, 1, C, i, wild);
   for (int64_t i = 0; i < ns; ++i) scale[i] = 0.02f + 0.01f * uniform();
   for (int64_t i = 0; i < R; ++i) bias[i] = MODE ? uniform() : 0.0f;
   for (int64_t i = 0; i < M * R; ++i) factor[i] = uniform();
@@ -135,14 +138,20 @@ template <int TN, int WN, int WK, bool PACKED, int MODE> void rows_f64(int64_t M
     });
   });
 }
-template <int TJ, bool PACKED, int MODE> void rows_exact(int64_t M, int64_t R, int64_t C, bool wild, int each = 1) {
+// finite values never take the float64 instructions, an infinity those of its 64 positions only
+static void expect_few_f64(Wild wild, int64_t strips, int64_t tiles, int blocks) {
+  expect("float64 instructions", (double)g_f64_products, wild == kInfinite ? (double)(strips * 4 * tiles * 16 * blocks) : 0.0);
+}
+template <int TJ, bool PACKED, int MODE> void rows_exact(int64_t M, int64_t R, int64_t C, Wild wild, int each = 1) {
   constexpr bool GLU = MODE == 1 + AQT_EPI_GLU;
   const int64_t tr = cdiv(GLU ? R / 2 : R, (GLU ? 8 : 16) * TJ), tm = cdiv(M, 64);
+  g_f64_products = 0;
   float_rows<MODE, PACKED>(M, R, C, MODE > 1 ? 3e-6 : 1.2e-7, [&](auto f, auto scale, auto q, auto sx, auto mask, auto factor, auto bias, auto out) {
     run((unsigned)(cdiv(tr, each) * tm), 256, 0, [&] {
       exact::f32_codes_exact_kernel<TJ, PACKED, MODE>(f, scale, q, M, R, (int)C, sx, MODE ? nullptr : mask, MODE ? nullptr : factor, MODE ? bias : nullptr, out, (int)tm, (int)tr, each);
     });
   }, wild);
+  expect_few_f64(wild, tm, tr, TJ);
 }
 template <int TN, bool PACKED, int MODE, bool LONG> void rows_any(int64_t M, int64_t R, int64_t C) {
   const int64_t tr = R / (32 * TN), tm = cdiv(M, 32);
@@ -154,7 +163,7 @@ template <int TN, bool PACKED, int MODE, bool LONG> void rows_any(int64_t M, int
 }
 
 // dW in slabs of `rows` rows, with the bias gradient (rows 0: no slabs, the split kernel); T: what a slab's partial sums are kept in; TJ > 0: gemm_exact.hip
-template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, bool masked, bool wild = false) {
+template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int64_t rows, bool masked, Wild wild = kTame) {
   constexpr bool F64 = sizeof(T) == 8;
   const int64_t tile = F64 ? 64 : 128, tiles_n = cdiv(N, tile), tiles_k = cdiv(K, TJ ? 16 * TJ : tile), slabs = rows ? cdiv(M, rows) : 1;
   printf("dW %s: %ld %ld %ld, %ld slabs, masked %d\n", TJ ? "digits" : F64 ? "float64" : "bf16", (long)M, (long)K, (long)N, (long)slabs, (int)masked);
@@ -167,13 +176,14 @@ template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int
   for (int64_t i = 0; i < M * N; ++i) dy[i] = uniform();
   if (wild)
     for (int64_t n = 0; n < N; ++n)
-      for (int64_t m0 = 0; m0 < M; m0 += rows) disturb(dy, m0 * N + n, N, std::min(rows, M - m0), n + m0 / rows);
+      for (int64_t m0 = 0; m0 < M; m0 += rows) disturb(dy, m0 * N + n, N, std::min(rows, M - m0), n + m0 / rows, wild);
   for (int64_t i = 0; i < N; ++i) sw[i] = i % 5 ? 0.5f : 0.0f;
   for (int64_t i = 0; i < cdiv(K * N, 32); ++i) { uniform(); mask[i] = seed | (seed << 16); }
   const bool one = slabs == 1;
   const unsigned grid = (unsigned)(tiles_k * tiles_n * slabs), bias_blocks = (unsigned)cdiv(N, kColsumCols), dw_blocks = one ? 0 : (unsigned)cdiv(K * N, 64);
   if constexpr (F64) {
     const DwFinish fin{sx, sw, masked ? mask.p : nullptr};
+    g_f64_products = 0;
     if constexpr (TJ > 0)
       run(grid, 256, 0, [&] { exact::bwd_dw_exact_kernel<TJ>((const int8_t *)x.bytes.p, dy, M, K, N, rows, partial, one ? dw.p : nullptr, (int)tiles_k, (int)tiles_n, (int)slabs, fin, part); });
     else
@@ -188,6 +198,7 @@ template <class T, int TJ = 0> void weights(int64_t M, int64_t K, int64_t N, int
     run(bias_blocks + dw_blocks, 256, 0, [&] { any::dw_any_fold_kernel((const float *)partial.p, (int)slabs, K, N, fin, dw, part, (int)(slabs * tiles_k), bias_blocks, db); });
     }
   }
+  if (TJ) expect_few_f64(wild, tiles_n * slabs, tiles_k, TJ);
   double worst = 0, worst_b = 0;
   for (int64_t n = 0; n < N; ++n) {
     double b = 0, ba = 0;
@@ -217,15 +228,15 @@ int main() {
   rows_f64<1, 1, 8, false, 0>(33, 17, 300); rows_f64<1, 1, 8, false, 0>(5, 15, 3); rows_f64<2, 1, 8, true, 1 + kSwish>(34, 33, 77);
   rows_f64<1, 4, 1, false, 0>(65, 66, 37); rows_f64<1, 4, 1, true, 1 + kNone>(31, 65, 17); rows_f64<1, 4, 1, true, 1 + kNone>(3, 3, 15);
   rows_f64<2, 2, 1, false, 1 + kGlu>(33, 70, 33); rows_f64<2, 1, 8, true, 1 + kGlu>(33, 34, 129); rows_f64<2, 2, 1, false, 1 + kGlu>(2, 2, 1);
-  rows_exact<4, false, 0>(65, 66, 64, false); rows_exact<5, false, 0>(33, 170, 200, true, 2); rows_exact<5, false, 0>(64, 33, 133, true);
-  rows_exact<5, true, 1 + kNone>(17, 97, 131, true, 2); rows_exact<4, true, 1 + kGlu>(70, 70, 65, true); rows_exact<4, false, 1 + kGlu>(5, 98, 190, true);
-  rows_exact<5, false, 1 + kSwish>(9, 19, 127, false); rows_exact<4, true, 1 + kNone>(64, 64, 128, true);
+  rows_exact<4, false, 0>(65, 66, 64, kTame); rows_exact<5, false, 0>(33, 170, 200, kInfinite, 2); rows_exact<5, false, 0>(64, 33, 133, kFar);
+  rows_exact<5, true, 1 + kNone>(17, 97, 131, kFar, 2); rows_exact<4, true, 1 + kGlu>(70, 70, 65, kInfinite); rows_exact<4, false, 1 + kGlu>(5, 98, 190, kFar);
+  rows_exact<5, false, 1 + kSwish>(9, 19, 127, kTame); rows_exact<4, true, 1 + kNone>(64, 64, 128, kInfinite);
   rows_any<1, false, 0, false>(33, 128, 96); rows_any<2, false, 0, false>(33, 128, 32); rows_any<2, true, 1 + kGlu, false>(33, 128, 320);
   rows_any<1, false, 0, true>(7, 32, 4640); rows_any<1, true, 1 + kSwish, true>(3, 32, 4128);
   weights<double>(70, 66, 65, 64, false); weights<double>(130, 3, 2, 64, true); weights<double>(33, 64, 70, 64, true); weights<double>(1, 1, 1, 64, false);
   weights<double>(200, 130, 5, 128, true);
-  weights<double, 4>(70, 66, 65, 64, false); weights<double, 5>(200, 81, 33, 128, true, true); weights<double, 5>(64, 97, 5, 64, true, true);
-  weights<double, 4>(329, 4, 66, 192, false, true); weights<double, 5>(130, 193, 17, 192, true, true);
+  weights<double, 4>(70, 66, 65, 64, false); weights<double, 5>(200, 81, 33, 128, true, kInfinite); weights<double, 5>(64, 97, 5, 64, true, kFar);
+  weights<double, 4>(329, 4, 66, 192, false, kFar); weights<double, 5>(130, 193, 17, 192, true, kInfinite);
   weights<float>(70, 64, 96, 0, true); weights<float>(33, 32, 64, 0, false); weights<float>(1, 32, 32, 0, true); weights<float>(600, 32, 32, 0, false);
   weights<float>(70, 128, 128, 64, true); weights<float>(33, 256, 128, 64, false); weights<float>(1, 128, 128, 32, true);
   printf(bad ? "MISMATCH\n" : "ok\n"); return bad;

@@ -27,6 +27,15 @@ static std::barrier<> *g_wbar[16];   // one per wavefront of the running block
 static float *g_lds;            // dynamic shared memory of the running block
 #define AQT_EXTERN_LDS(name) float *name = g_lds
 inline void __syncthreads() { g_bar->arrive_and_wait(); }
+inline int __syncthreads_or(int p) {
+  static uint8_t table[1024];
+  table[threadIdx.x] = p != 0;
+  __syncthreads();
+  int any = 0;
+  for (unsigned t = 0; t < blockDim.x; ++t) any |= table[t];
+  __syncthreads();
+  return any;
+}
 inline void __builtin_amdgcn_wave_barrier() { g_wbar[threadIdx.x >> 6]->arrive_and_wait(); }
 // wave shuffle: exchange through a table, in step with the other lanes of the wavefront
 static int g_shfl[1024];

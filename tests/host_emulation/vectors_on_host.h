@@ -1,6 +1,7 @@
 // The short vectors of the kernels as plain structs, and the wavefront-wide instructions that the kernels for vectorised
 // rows use besides those of hip_on_host.h.  Lanes exchange through tables, in step with their wavefront.
 #pragma once
+#include <atomic>
 #include <type_traits>
 #include "hip_on_host.h"
 #define AQT_VECTOR(name, type, n, bytes, ...)                          \
@@ -120,8 +121,10 @@ inline v4i __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i a, v4i b, v4i c, int, int, 
 }
 // v_mfma_f64_16x16x4_f64: lane (lc = lane % 16, lg = lane / 16) supplies A[lc][lg] and B[lg][lc]; element r of its
 // accumulator is row 4 r + lg, column lc
+static std::atomic<long> g_f64_products{0};
 inline v4d __builtin_amdgcn_mfma_f64_16x16x4f64(double a, double b, v4d c, int, int, int) {
   static double ta[1024], tb[1024];
+  if ((threadIdx.x & 63u) == 0) ++g_f64_products;
   const unsigned base = threadIdx.x & ~63u, lane = threadIdx.x & 63u, lc = lane & 15u, lg = lane >> 4;
   ta[threadIdx.x] = a; tb[threadIdx.x] = b;
   wave_meets().arrive_and_wait();

@@ -201,11 +201,11 @@ def test_off_the_grid_infinite_and_huge_values(M, K, N):
         rounded_once(got, torch_where_finite(ref32, ref), terms, mag.nan_to_num(0.0, 0.0, 0.0))
 
 
-@pytest.mark.parametrize("pattern", ["few", "many", "row", "zeros"])
+@pytest.mark.parametrize("pattern", ["few", "many", "planes", "softmax", "row", "zeros"])
 @pytest.mark.parametrize("M,K,N", [(1500, 345, 519), (7600, 67, 128), (500, 1001, 1024)])
 def test_off_the_grid_values_far_apart(M, K, N, pattern):
     """Large enough for the digits of gemm_exact.hip, values further apart in a row or column than the digits reach: a few of
-    them, most of them, rows and columns with an infinity among ordinary ones, rows and columns of zeros."""
+    them, most of them, over all of float32's range, as in a softmax's gradient, rows and columns with an infinity among ordinary ones, rows and columns of zeros."""
     import torch
     print("[float64 sums, values far apart]", M, K, N, pattern, flush=True)
 
@@ -215,6 +215,10 @@ def test_off_the_grid_values_far_apart(M, K, N, pattern):
             t[torch.rand(t.shape, device="cuda", generator=gen) < 2e-4] *= 2.0 ** -27
         elif pattern == "many":
             t *= torch.exp2(torch.randint(-60, 40, t.shape, device="cuda", generator=gen).float())
+        elif pattern == "planes":
+            t *= torch.exp2(torch.randint(-140, 90, t.shape, device="cuda", generator=gen).float())
+        elif pattern == "softmax":
+            t.copy_(torch.softmax(30 * t / t.std(), 1))
         elif pattern == "row":
             t[5, 7], t[M // 2 + 1, t.shape[1] - 1], t[M - 1, 3] = float("inf"), float("nan"), 3.0e38
         else:
