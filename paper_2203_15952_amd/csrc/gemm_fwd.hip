@@ -468,9 +468,11 @@ bool fwd_q_takes_fragments(int64_t M, int64_t K, int64_t N, int epilogue) {
 // 4.7; 512 x 512 -> 512 4.4 against 5.7; 1024 x 1024 -> 256 4.7 against 7.3; 400 x 2048 -> 512 4.5 against 11.9; not
 // with a short main loop, 800 x 256 -> 1024, 56 tiles, 5.2 against 4.9, nor from 64 tiles on, 4096 x 512 -> 512, 128 tiles,
 // 6.8 against 6.4).  A tile's wavefronts work through 64 elements each in the epilogue: with Swish 5 us if one
-// workgroup has a compute unit to itself, whatever the size, while eight wavefronts on half the tile take 1.5 (2048 x 256 -> 1024,
-// 128 tiles, 7.6 against 10.3; 1280 x 512 -> 1536, 120 tiles, 8.5 and 10.9; 1280 x 512 -> 2048, 160 tiles, 11.0 both; 2560 x 512 ->
-// 2048, 320 tiles, 16.3 and 13.2).
+// workgroup has a compute unit to itself, whatever the size, while eight wavefronts on half the tile take 1.5.  That outweighs the
+// fan-in up to 128 tiles, where every workgroup still has a unit to itself (int4 weights, operand in matrix-core order already; 64, 128 and 160 tiles,
+// 1024 x K -> 1024, 2048 x K -> 1024, 2560 x K -> 1024): K = 128 7.0, 7.7, 9.5 against 10.3, 10.8, 11.3; 256 7.5, 8.2, 10.4 against 10.8, 11.5,
+// 12.1; 512 8.7, 9.6, 12.1 against 12.0, 12.5, 12.9; 1024 11.1, 11.9, 15.7 against 13.7, 14.1, 14.3; 2048 15.7, 17.0, 23.1 against 17.5, 17.6, 17.7;
+// with int8 weights the difference is larger (2048 x 2048 -> 1024 16.4 and 18.6).  2560 x 512 -> 2048, 320 tiles, 16.3 and 13.2.
 static bool fwd_q_small(int64_t M, int64_t K, int64_t N, int epilogue) {
   const int64_t tiles = cdiv(M, 128) * cdiv(N, 128);
   return tiles <= (epilogue == AQT_EPI_SWISH ? 128 : K >= 512 ? 64 : 32);
