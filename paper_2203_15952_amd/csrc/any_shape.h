@@ -1,5 +1,5 @@
 // Reading tensors of any shape and alignment into LDS, slice by slice of the contraction: what the kernels of
-// gemm_any.hip and gemm_any_f64.hip share.
+// gemm_any.hip, gemm_any_f64.hip and (its pieces, not its loop) gemm_exact.hip share.
 //
 // Edges: rows and columns beyond the tensors are read at clamped, valid addresses and not stored.  Contraction
 // positions beyond the end are zeros: a piece that would cross the end of its row is read so that it ends there and is

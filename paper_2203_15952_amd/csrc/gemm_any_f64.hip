@@ -1,7 +1,7 @@
 // The float contractions of the quantized dense layer off the tuned kernels' grid (sizes that no tile divides, fewer
 // than 128 rows, tensors that are not 16-byte aligned): dX, dW and the weight-only forward with every product and sum
 // in float64 on v_mfma_f64_16x16x4_f64, rounded to float32 once.  Where there is enough work gemm_exact.hip forms the same
-// sums on the int8 matrix cores (its rules say where); what is left here are the small ones.
+// sums on the int8 matrix cores (its rules say where); what is left here are small problems and short contractions.
 //
 // Nothing is split and nothing overflows or is lost on the way: a float32 value times a code is exact, infinities and
 // the largest finite values behave as in a float64 loop, and a sum of any length is as good as one.  Float32 sums of 512 products on the
@@ -9,12 +9,13 @@
 // 1.7e-7 (dW) and 2.1e-7 (weight-only) of the result at 4099 x 520 x 1000; here it is 3.6e-8, 2.5e-8 and 2.5e-8, the last rounding
 // (in dX also the float32 product dy * s_w).
 //
-// What bounds them is the instruction itself: independent ones on registers reach 46 TFLOP/s on the whole chip (two or
-// more wavefronts per SIMD; 35 with one).  At 4099 x 520 x 1000 dX takes 104 and dW 112 us (41 and 38 TFLOP/s, padding not
-// counted), with bf16 terms 47 and 47, one thread per output 6565 and 1096.  So everything else is kept small
-// rather than clever: float32 values and int8 codes go through LDS as they are and are converted when a fragment is read
-// (one instruction per value, a small part of the products' clocks), and tiles are small so that a launch fills 256
-// compute units evenly.  (These figures are of the larger problems that gemm_exact.hip now takes.)
+// The instruction itself allows 46 TFLOP/s on the whole chip (independent ones on registers, two or more wavefronts per SIMD; 35 with
+// one), and 4099 x 520 x 1000, which gemm_exact.hip takes now, reached 41 in dX and 38 in dW.  What is left here is bound by how
+// few wavefronts it makes: dX 1300 x 400 of 1200 positions 47 us (27 TFLOP/s, padding not counted), 300 x 1030 of 2040 48 (26), 520 x 520
+// of 1000 27 (20), 2600 x 144 of 576 20 (22), 800 x 400 of 400 18 (14); dW 64 x 520 x 1000 11 (6), 1024 x 144 x 576 17 (10).  So everything
+// else is kept small rather than clever: float32 values and int8 codes go through LDS as they are and are converted when a
+// fragment is read (one instruction per value, a small part of the products' clocks), and tiles are small so that a launch
+// fills 256 compute units evenly.
 //
 // A lane of the instruction holds one element of A (row lane % 16) and of B (column lane % 16) at contraction index
 // lane / 16.  Which positions those are is free as long as both operands agree: lane group g takes positions

@@ -817,7 +817,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
     }
 }
 
-// Tiles of at most six blocks of sixteen, as even as they come.
+// Tiles of at most five blocks of sixteen (four where a value block needs its gate block beside it), as even as they come; least: 4.
 struct Tiling {
   int tiles, blocks;
 };

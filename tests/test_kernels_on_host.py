@@ -82,7 +82,7 @@ def spliced_gemm_any_source():
     f64 = read("gemm_any_f64.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace f64 {")
     f64 = f64[:f64.index("template <int TN, int WN, int WK, bool PACKED, int MODE>\naqt_status")] + "}\n}\n"
     exact = read("gemm_exact.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace exact {")
-    exact = exact[:exact.index("// Tiles of at most six blocks of sixteen")] + "}\n}\n"
+    exact = exact[:exact.index("// Tiles of at most five blocks of sixteen")] + "}\n}\n"
     exact = cut(exact, "__device__ __forceinline__ float load_f32", "__device__ __forceinline__ double power_of_two")   # the shim has its own
     driver = open(os.path.join(HERE, "host_emulation", "gemm_any_driver.cpp")).read()
     return ('#include "vectors_on_host.h"\n#include "aqt.h"\n' + read("any_shape.h") + bf16_terms() + read("colsum.h") +
