@@ -3,7 +3,7 @@
 // headers), every GPU thread of a block runs as an OS thread with real barriers, LDS is a heap block
 // of exactly the launched size, and the build carries the address and undefined-behaviour sanitizers.
 // Results are compared with plain float64 loops written here.
-static float *mk(size_t n, float v, unsigned seed) { float *p = (float *)malloc(n * 4 + 4); uint32_t s = seed; for (size_t i = 0; i < n; ++i) { s = s * 1664525u + 1013904223u; p[i] = v * ((float)(s >> 8) / 8388608.0f - 1.0f); } return p; }
+static float *mk(size_t n, float v, unsigned seed) { float *p = (float *)malloc(n * 4); uint32_t s = seed; for (size_t i = 0; i < n; ++i) { s = s * 1664525u + 1013904223u; p[i] = v * ((float)(s >> 8) / 8388608.0f - 1.0f); } return p; }
 static int bad = 0;
 static void cmp(const char *what, const float *got, const double *ref, const double *mag, size_t n) {
   double worst = 0;
@@ -21,7 +21,7 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
   unsigned blocks = g.cgroups * g.tgroups * B;
   std::vector<double> ref(n), mag(n);
   // forward, no activation
-  if (kw <= kTapsMax) run(blocks, 256, (size_t)(kTile + 2 * kw - 1) * 256, [&] { dwconv_kernel(x, nullptr, w, bias, nullptr, nullptr, 0, 0, g, pad, out, nullptr, &am); });
+  if (kw <= kTapsMax) run(blocks, 256, (size_t)(kTile + 2 * kw - 1) * 256, [&] { dwconv_kernel<false>(x, nullptr, w, bias, nullptr, nullptr, 0, 0, g, pad, out, nullptr, &am); });
   else run(8, 256, 0, [&] { dwconv_any_kernel(x, nullptr, w, bias, nullptr, nullptr, 0, 0, g, pad, out, nullptr, &am); });
   float mx = 0;
   for (int64_t b = 0; b < B; ++b) for (int64_t t = 0; t < T; ++t) for (int64_t c = 0; c < C; ++c) {
@@ -33,7 +33,7 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
   for (size_t i = 0; i < n; ++i) mx = std::max(mx, fabsf(out[i]));
   if (__float_as_uint(mx) != am) { printf("  absmax mismatch\n"); bad = 1; }
   // dx
-  if (kw <= kTapsMax) run(blocks, 256, (size_t)(kTile + 2 * kw - 1) * 256, [&] { dwconv_kernel(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, g, kw - 1 - pad, dx, nullptr, nullptr); });
+  if (kw <= kTapsMax) run(blocks, 256, (size_t)(kTile + 2 * kw - 1) * 256, [&] { dwconv_kernel<false>(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, g, kw - 1 - pad, dx, nullptr, nullptr); });
   else run(8, 256, 0, [&] { dwconv_any_kernel(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, g, kw - 1 - pad, dx, nullptr, nullptr); });
   for (int64_t b = 0; b < B; ++b) for (int64_t u = 0; u < T; ++u) for (int64_t c = 0; c < C; ++c) {
     double a = 0, m = 0;
@@ -41,6 +41,19 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
     ref[(b * T + u) * C + c] = a; mag[(b * T + u) * C + c] = m;
   }
   cmp("dx", dx, ref.data(), mag.data(), n);
+  // the same through the gate: both products, [B T, 2 C]
+  if (kw <= kTapsMax) {
+    float *gate = mk(2 * n, 1.0f, 6), *dv = mk(2 * n, 0, 0);
+    run(blocks, 256, (size_t)(kTile + 2 * kw - 1) * 256, [&] { dwconv_kernel<true>(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, g, kw - 1 - pad, dv, nullptr, nullptr, gate); });
+    size_t differ = 0;
+    for (size_t f = 0; f < (size_t)(B * T); ++f) for (int h = 0; h < 2; ++h) for (int64_t c = 0; c < C; ++c) {
+      const size_t at = (2 * f + h) * C + c;
+      if (!(dv[at] == dx[f * C + c] * gate[at])) ++differ;
+    }
+    printf("  gate   values that differ from dx times the gate: %zu\n", differ);
+    if (differ) bad = 1;
+    free(gate); free(dv);
+  }
   // dw, dbias
   int P = dw_partials(g);
   size_t pb = (size_t)P * (kw + 1) * C;
