@@ -87,7 +87,8 @@ struct ConvBwdWorkspace {
   size_t total;
 };
 
-ConvBwdWorkspace carve_conv_bwd(void *ws, int64_t B, int64_t T, int64_t D, int kw) {
+// dg, the gradient in front of the gate: only where the depthwise kernel does not take the gate, or for `any_taps`.
+ConvBwdWorkspace carve_conv_bwd(void *ws, int64_t B, int64_t T, int64_t D, int kw, bool any_taps = false) {
   ConvBwdWorkspace f;
   const int64_t M = B * T;
   const size_t a = bwd_workspace_bytes(M, D, 2 * D), b = bwd_workspace_bytes(M, D, D);
@@ -100,7 +101,7 @@ ConvBwdWorkspace carve_conv_bwd(void *ws, int64_t B, int64_t T, int64_t D, int k
   };
   const size_t md = static_cast<size_t>(M) * D * sizeof(float);
   f.ds = reinterpret_cast<float *>(take(md));
-  f.dg = reinterpret_cast<float *>(take(md));
+  f.dg = any_taps || !dwconv_takes_gate(M, D, kw) ? reinterpret_cast<float *>(take(md)) : nullptr;
   f.dv = reinterpret_cast<float *>(take(2 * md));
   f.taps = take(dwconv_bwd_ws_bytes(D, kw));
   f.total = off;
@@ -172,7 +173,8 @@ bool conv_shape_ok(int64_t B, int64_t T, int64_t C, int kw, int pad_left) {
          B <= (int64_t(1) << 40) / T;
 }
 
-size_t conv_bwd_total(int64_t M, int64_t D, int kw) { return carve_conv_bwd(nullptr, 1, M, D, kw).total; }
+// (what the layer reserves for 32 taps also serves a few more)
+size_t conv_bwd_total(int64_t M, int64_t D, int kw) { return carve_conv_bwd(nullptr, 1, M, D, kw, true).total; }
 
 bool policy_ok(const aqt_dense_policy &p) {
   return bits_ok(p.bits_w) && (p.bits_x == 0 || bits_ok(p.bits_x)) && (p.weights_ready == 0 || p.weights_ready == 1);

@@ -184,12 +184,13 @@ aqt_status launch_fake_matmul_f32(const int8_t *xq, const int8_t *wq_kn, int64_t
 
 // ---- depthwise convolution of the convolution module (conv.hip) ---------------------------
 size_t dwconv_bwd_ws_bytes(int64_t C, int kw);
+bool dwconv_takes_gate(int64_t M, int64_t C, int kw);   // M = B * T frames: the backward multiplies by the gate itself
 aqt_status launch_dwconv_fwd(const float *x, const float *w, const float *bias, const float *na, const float *nb,
                              int swish, int64_t B, int64_t T, int64_t C, int kw, int pad_left, float *out, float *dfac,
                              uint32_t *absmax, hipStream_t st, bool absmax_is_zero = false);
 aqt_status launch_dwconv_bwd(const float *dout, const float *dmul, const float *x, const float *w, int64_t B, int64_t T,
                              int64_t C, int kw, int pad_left, float *dx, float *dw, float *dbias, void *ws,
-                             hipStream_t st, const float *gate = nullptr, float *dv = nullptr);   // with gate: dv [B T, 2 C] is wanted, dx scratch
+                             hipStream_t st, const float *gate = nullptr, float *dv = nullptr);   // with gate: dv [B T, 2 C] is wanted, dx scratch (not used where dwconv_takes_gate)
 
 // ---- attention core of the self-attention module (attention.hip, attention_fwd.hip, attention_bwd.hip) -------------
 struct AttnShape {

@@ -475,7 +475,7 @@ int dw_partials(const ConvGeom &g) {
   return static_cast<int>(P);
 }
 
-bool corr_staged(const ConvGeom &g) {   // else the kernel for any number of taps, which takes no gate
+bool corr_staged(const ConvGeom &g) {   // else the kernel for any number of taps
   return g.kw <= kTapsMax && static_cast<int64_t>(g.cgroups) * g.tgroups * g.B < (int64_t(1) << 31);
 }
 aqt_status launch_corr(bool rev, const float *xin, const float *xmul, const float *w, const float *bias,
@@ -501,6 +501,9 @@ aqt_status launch_corr(bool rev, const float *xin, const float *xmul, const floa
 
 }  // namespace
 
+// However the frames are divided into utterances (no more tiles than frames), the staged kernel takes them.
+bool dwconv_takes_gate(int64_t M, int64_t C, int kw) { return kw <= kTapsMax && M < (int64_t(1) << 31) / cdiv(C, 64); }
+
 // Shape-only bound (the partial count never exceeds what an unlimited number of tiles gives).
 size_t dwconv_bwd_ws_bytes(int64_t C, int kw) {
   ConvGeom g = geom(int64_t(1) << 20, kTile, C, kw, 0);
@@ -518,7 +521,7 @@ aqt_status launch_dwconv_bwd(const float *dout, const float *dmul, const float *
                              int64_t C, int kw, int pad_left, float *dx, float *dw, float *dbias, void *ws,
                              hipStream_t st, const float *gate, float *dv) {
   const ConvGeom g = geom(B, T, C, kw, pad_left);
-  if (gate && corr_staged(g)) {
+  if (gate && dwconv_takes_gate(B * T, C, kw)) {
     AQT_TRY(launch_corr(true, dout, dmul, w, nullptr, nullptr, nullptr, 0, g, dv, nullptr, nullptr, st, false, gate));
   } else if (gate) {
     AQT_TRY(launch_corr(true, dout, dmul, w, nullptr, nullptr, nullptr, 0, g, dx, nullptr, nullptr, st));

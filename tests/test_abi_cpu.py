@@ -210,6 +210,9 @@ def test_module_and_layer_argument_errors_are_synchronous(L):
                                  one, big, none) == B.AQT_ERR_INVALID_ARG
     assert L.aqt_conv_module_bwd(one, ctypes.byref(cs), one, 2, 8, 4, 3, 1, i8, one, one, none, one, none, one, none,
                                  one, 64, none) == B.AQT_ERR_WORKSPACE
+    # its backward: the gradient in front of the gate is a tensor of its own only where the kernel does not take the gate (over 32 taps)
+    short, more = (B.aqt_workspace_bytes(B.AQT_OP_CONV_MODULE_BWD, 65536, 512, kw) for kw in (32, 33))
+    assert short < more
     # self-attention module
     ms = _filled(B.aqt_mhsa_saved)
     assert L.aqt_mhsa_fwd(one, none, none, 1e-6, one, none, one, none, 2, 8, 30, 4, -1, -1, i8, one, ctypes.byref(ms),
