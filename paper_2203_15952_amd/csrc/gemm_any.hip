@@ -786,23 +786,35 @@ __global__ __launch_bounds__(kDwThreads) void dw_any_fold_kernel(const float *__
     dw[at] = dw_value((sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]), at, at % N, fin, fin.s_x[0]);
 }
 
-// Which workgroup arrangement of the forward.  The lines were drawn from sweeps over all of them (us):
+// Which workgroup arrangement of the forward.  The lines were drawn from sweeps over all of them, every epilogue and both widths of
+// the weights (us):
 //   the split contraction (32 columns to a tile, all eight wavefronts on it) while that makes fewer than 800 workgroups: 2604 x 144 -> 144
 //   (410) 3.9 against 5.3 in 64 x 128 tiles, 700 x 520 -> 1000 (704) 6.3 and 7.0, 1280 x 2048 -> 512 (640) 9.2 and 12.2;
 //   1302 x 520 -> 1000 (1312) 9.5 and 7.7;
-//   128 x 64, four wavefronts, where 64 x 128 would compute mostly padding and no longer has all its tiles on the chip
-//   at once (10008 x 144 -> 144 6.8 and 7.3, 10008 x 144 -> 576 11.0 and 12.8; 7000 x 144 -> 144 6.5 and 5.9,
-//   5000 x 144 -> 576 8.9 and 7.9; with a fan-in of 2040, 16000 -> 520, 61 and 55), and for long contractions, where fewer bytes through
-//   LDS per product count (50000 x 4100 -> 1000 467 and 526, 5000 x 1000 -> 1000 21.8 and 22.4; 16000 x 520 -> 520 27 and 25);
-//   64 x 128, eight wavefronts, otherwise.  (128 x 128 tiles, eight wavefronts, are behind both everywhere: 5000 x 520 -> 1000 21.6 against 16.7,
-//   16000 x 1000 -> 1000 67 against 50 and 52, 50000 x 4100 -> 1000 646 against 467 and 526.)
-enum class Tile { kRows, kNarrow, kSmall, kSmallest };   // 64 x 128, 128 x 64; split contraction: 32 x 64 (the GLU's pairs), 32 x 32
-Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, bool glu) {
-  if (cdiv(M, 32) * cdiv(cols, 32) < 800) return glu ? Tile::kSmall : Tile::kSmallest;
-  const int64_t rows = cdiv(M, 64) * cdiv(cols, 128);
-  if (cols >= 640) return contraction >= 1000 && rows > 512 ? Tile::kNarrow : Tile::kRows;
-  const bool odd = cdiv(cols, 64) % 2;   // half of the last 128-wide tile would be padding
-  return odd && (cols <= 192 ? rows > 256 : contraction <= 256 && rows > 512) ? Tile::kNarrow : Tile::kRows;
+//   from there 64 x 128 tiles, eight wavefronts, but
+//   128 x 128 with int4 weights and long contractions, where the expansion of the codes is shared by twice the rows, if their
+//   rounds over the compute units are as full as those of 64 x 128: 10008 x 2040 -> 2040 90 against 97, 6500 x 2040 -> 1000 39 and 43, 13000 x
+//   4100 -> 400 64 and 73, 30000 x 2040 -> 200 41 and 44; not 1000 positions (0.96 - 1.02), nor with int8 weights (646 against 467
+//   at 50000 x 4100 -> 1000), nor where a round is left half empty, 4099 x 2040 -> 1100 37 and 33;
+//   128 x 64, four wavefronts, where it saves such rounds because 64 x 128 would compute padding: 6500 x 2040 -> 288 int8 18.5 against 24.4,
+//   17000 x 288 -> 288 15.1 and 17.1, 10008 x 144 -> 576 with Swish 16.9 and 18.6, 13000 x 144 -> 288 int4 11.2 and 12.5; with as many rounds it
+//   is behind by 8 to 20 %, 10008 x 520 -> 288 14.3 and 13.2, with Swish 17.9 and 15.0; a tile's few wavefronts work longest with Swish (4099 x 520 -> 400, one
+//   round against a little more than one, 13.8 and 11.8; 4099 x 4100 -> 400 33.9 and 38.3; without it 4351 x 1000 -> 400 13.7 and 16.3); and for long contractions with int8 weights, where
+//   fewer bytes through LDS per product count (50000 x 4100 -> 1000 467 and 526, 17000 x 2040 -> 1100 0.90 of the time, 5000 x 1000 -> 1000 0.97;
+//   with int4 weights 1.05 to 1.20 times the time).
+enum class Tile { kRows, kLarge, kNarrow, kSmall, kSmallest };   // 64 x 128, 128 x 128, 128 x 64; split contraction: 32 x 64 (the GLU's pairs), 32 x 32
+Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, int epilogue, bool packed) {
+  if (cdiv(M, 32) * cdiv(cols, 32) < 800) return epilogue == AQT_EPI_GLU ? Tile::kSmall : Tile::kSmallest;
+  constexpr int64_t kUnits = 256;
+  const int64_t rows = cdiv(M, 64) * cdiv(cols, 128), large = cdiv(M, 128) * cdiv(cols, 128), narrow = cdiv(M, 128) * cdiv(cols, 64);
+  const int64_t rounds = cdiv(rows, kUnits), narrow_rounds = cdiv(narrow, kUnits);
+  if (packed && contraction >= 1500 && large > kUnits && 2 * cdiv(large, kUnits) <= rounds) return Tile::kLarge;
+  if (cols >= 640) return !packed && contraction >= 1000 && rows > 512 ? Tile::kNarrow : Tile::kRows;
+  const bool swish = epilogue == AQT_EPI_SWISH, light = packed && epilogue == AQT_EPI_NONE;
+  if (narrow_rounds == 1) return contraction >= (rows < 272 ? 1500 : swish ? 1000 : 0) && rounds > 1 ? Tile::kNarrow : Tile::kRows;
+  if (light ? 3 * narrow_rounds <= 2 * rounds : 4 * narrow_rounds <= 3 * rounds) return Tile::kNarrow;
+  // half of the last 128-wide tile would be padding, and a short contraction hides no wavefront's epilogue
+  return cdiv(cols, 64) % 2 && contraction <= 256 && rows > 512 && !light ? Tile::kNarrow : Tile::kRows;
 }
 
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
@@ -826,7 +838,10 @@ template <bool PACKED>
 aqt_status fwd_any_sized(const int8_t *xq, const float *s_x, const void *wq, const float *s_w, int64_t M, int64_t K, int64_t N,
                          const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
                          hipStream_t st) {
-  switch (pick_tile(M, N, K, epilogue == AQT_EPI_GLU)) {
+  switch (pick_tile(M, N, K, epilogue, PACKED)) {
+    case Tile::kLarge:
+      if constexpr (PACKED) return fwd_any<1, 2, 4, 2, 1, 128, true>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+      else return AQT_ERR_UNSUPPORTED;   // not picked
     case Tile::kRows:
       if (epilogue != AQT_EPI_GLU) return fwd_any<1, 1, 2, 4, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
       return fwd_any<1, 2, 2, 2, 1, 128, PACKED>(xq, s_x, wq, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);

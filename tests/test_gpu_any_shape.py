@@ -259,9 +259,12 @@ def test_small_problems_on_the_tuned_grid(M, K, N):
 
 @pytest.mark.parametrize("M,K,N,bw,epi", [
     (800, 40, 1024, 8, 0), (799, 40, 992, 4, 0),                           # 800 and 775 split tiles
-    (8192, 33, 130, 8, 1), (8193, 33, 130, 4, 0),                          # 256 and 258 tiles of 64 x 128, under 192 channels
-    (10881, 250, 322, 8, 1), (10945, 257, 322, 4, 0),                      # 513 and 516 of them under 640; 256 positions, and more
+    (8192, 33, 130, 8, 1), (9217, 33, 130, 4, 0), (9217, 1000, 130, 8, 1),  # 256 and 290 tiles of 64 x 128, one round of 128 x 64
+    (4099, 1499, 322, 8, 0), (4099, 1500, 322, 4, 2),                      # 195 of them; 1500 positions
+    (10881, 250, 322, 8, 1), (10945, 257, 322, 4, 0), (21889, 250, 322, 8, 2),   # two rounds against three, six against five
     (6600, 999, 642, 8, 0), (6592, 1001, 642, 4, 1), (6593, 1002, 1300, 8, 2),   # 640 channels and more: around 1000 positions
+    (2550, 1500, 2570, 4, 0), (2550, 1501, 2570, 4, 1), (2550, 1511, 2570, 4, 2), (2550, 1499, 2570, 4, 0),   # 128 x 128 with int4 weights
+    (3000, 1500, 2040, 4, 1),                                              # not with half a round of them
     (2048, 128, 1024, 4, 1), (2049, 128, 1024, 8, 1)])                     # Swish on the tuned grid: 128 and 136 tiles
 def test_forward_around_the_lines_between_arrangements(M, K, N, bw, epi):
     """Whatever tile a size takes: the integer sums are exact, the result is their de-quantization, the maximum is the result's."""
