@@ -909,10 +909,20 @@ int dw_any_slabs(int64_t M, int64_t K, int64_t N) {
 }
 
 // The split kernel while its tiles, with their four times as many conversions and reads, cost less than partial results through memory
-// and a fold (us with the bias gradient, slabs and split: 1024 x 256 x 1024 20.9 and 10.2, 2048 x 256 x 256 14.8 and 13.7,
-// 2560 x 512 x 512 24.4 and 16.8, 16 x 512 x 2048 12.8 and 12.6; behind it in rows 4096 x 256 x 256 20.6 and 22.5, in products
-// 1300 x 512 x 2048 31.8 and 33.7, 300 x 1024 x 4096 54.8 and 58.3).
-static bool dw_any_splits(int64_t M, int64_t K, int64_t N) { return M <= 3072 && M * K * N <= 1000000000; }
+// and a fold, and while there are tiles enough.  us with the bias gradient, slabs and split: 1024 x 256 x 1024 20.9 and 10.2, 2000 x 256 x 256
+// 15.2 and 14.9, 2500 x 512 x 512 24.7 and 18.0, 100 x 2048 x 2048 54 and 46, 16 x 512 x 2048 13.5 and 13.2; behind it
+//   in rows, 2000 x 256 x 128 12.8 and 14.6, 3000 x 256 x 128 14.3 and 19.0, 3000 x 256 x 256 18.3 and 19.3, 4000 x 512 x 256 23.9 and 24.3 (in one
+//   launch with dX later: 2000 x 256 x 128 17.3 and 15.4, 3000 x 256 x 128 22.0 and 20.3, 4000 x 256 x 256 27.4 and 24.9; the line is one for both,
+//   so that dW has the same bits with dX and without);
+//   in products, the fewer the more tiles: 2500 x 512 x 1024 27.5 and 30.9, 1400 x 1024 x 1024 31.4 and 35.8, 768 x 1024 x 2048 41 and 47,
+//   200 x 2048 x 2048 with dX 62 and 69;
+//   where a slab of rows is all there are and the other kernel finishes by itself: 64 x 1024 x 2048 15 and 24, 64 x 2048 x 2048 16 and 44,
+//   100 x 4096 x 2048 23 and 88 (up to 1024 tiles 64 x 1024 x 1024 14.3 and 13.4, 32 x 512 x 512 13.1 and 6.1).
+static bool dw_any_splits(int64_t M, int64_t K, int64_t N) {
+  const int64_t tiles = (K / kDwSplitTile) * (N / kDwSplitTile);
+  if (tiles > 1024 && dw_any_slabs(M, K, N) == 1) return false;
+  return M <= (tiles < 64 ? 2048 : 3072) && M * K * N <= 1000000000 - 100000 * tiles;
+}
 
 aqt_status launch_bwd_dw_any(const float *dy, const int8_t *xq, const float *s_x, const float *s_w, const uint32_t *mask_w,
                              int64_t M, int64_t K, int64_t N, float *dw, float *partial, float *dbias, double *bias_part,

@@ -287,9 +287,11 @@ def test_forward_around_the_lines_between_arrangements(M, K, N, bw, epi):
 
 
 @pytest.mark.parametrize("M,K,N", [(1, 256, 128), (31, 256, 128), (33, 512, 128), (255, 256, 384), (257, 256, 256), (513, 256, 128), (128, 256, 4096), (130, 256, 4224),
-                                   (3072, 256, 256), (3073, 256, 256), (1907, 512, 1024), (1908, 512, 1024)])
+                                   (3072, 256, 256), (3073, 256, 256), (1907, 512, 1024), (1908, 512, 1024),
+                                   (2048, 256, 128), (2049, 256, 128), (1809, 512, 1024), (1811, 512, 1024),   # rows of few tiles; products
+                                   (64, 1024, 2048), (65, 1024, 2048), (64, 1024, 1024), (17, 2048, 2048), (300, 4096, 2048)])   # single slabs
 def test_weight_gradient_of_few_rows(M, K, N):
-    """One workgroup per tile up to 3072 rows and 10^9 products, slabs beyond: sums of at most 512 rows in float32 (as above), then float64."""
+    """One workgroup per tile up to 3072 rows and 10^9 products, slabs beyond (and where one slab is all): sums of at most 512 rows in float32 (as above), then float64."""
     import torch
     print("[dW, few rows]", M, K, N, flush=True)
     gen = torch.Generator(device="cuda").manual_seed(M + N)
@@ -309,3 +311,49 @@ def test_weight_gradient_of_few_rows(M, K, N):
     dx, _, _ = B.aqt_dense_bwd(dy, sv, 8, 8, want_dw=False)
     both = B.aqt_dense_bwd(dy, sv, 8, 8, want_dbias=True)
     assert torch.equal(both[0], dx) and torch.equal(both[1], dw) and torch.equal(both[2], db)
+
+
+def fastest(call, calls=20, rounds=8):
+    """us of one of `calls` calls in a row, the fastest of some rounds"""
+    import torch
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(rounds):
+        a.record()
+        for _ in range(calls):
+            call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+def test_weight_gradient_of_few_rows_is_not_slower_than_of_many():
+    """A wide layer, where one slab of rows is all there are: the split kernel takes 86 us for 64 rows, the other one 20."""
+    import torch
+    K, N, us = 4096, 2048, []
+    for M in (64, 1024):
+        print("[dW time]", M, K, N, flush=True)
+        sv = B.Saved(M, K, N, 8)
+        B.aqt_dense_fwd(torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda"), 8, 8, saved=sv)
+        dy, dw = torch.randn(M, N, device="cuda"), torch.empty(K, N, device="cuda")
+        ws = B.workspace(B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, M, K, N))
+        us.append(fastest(lambda: B.aqt_dense_bwd(dy, sv, 8, 8, want_dx=False, dw=dw, ws=ws)))
+    assert us[0] <= us[1], us
+
+
+def test_gradients_of_a_softmax_cost_at_most_a_second_plane():
+    """Off the grid, logits of standard deviation 3 over 1000 channels: most values lie below the first six digits of their row's
+    largest.  Two planes take 1.6 times the time of one; what they stand in for took five times."""
+    import torch
+    M, K, N = 4099, 520, 1000
+    print("[digits, time of a softmax's gradient]", M, K, N, flush=True)
+    sv = B.Saved(M, K, N, 8)
+    B.aqt_dense_fwd(torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda"), 8, 8, saved=sv)
+    plain = torch.randn(M, N, device="cuda")
+    peaked = torch.softmax(3 * torch.randn(M, N, device="cuda"), 1)
+    peaked[torch.arange(M), torch.randint(0, N, (M,))] -= 1
+    dx, dw = torch.empty(M, K, device="cuda"), torch.empty(K, N, device="cuda")
+    ws = B.workspace(B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, M, K, N))
+    t = [fastest(lambda: B.aqt_dense_bwd(dy, sv, 8, 8, dx=dx, dw=dw, ws=ws)) for dy in (plain, peaked)]
+    assert t[1] <= 2.5 * t[0], t
