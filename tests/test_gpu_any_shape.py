@@ -31,15 +31,15 @@ SHAPES = [
     (31, 255, 65, 8, 1),          # whole steps that make no group, then a partial one
     (3, 517, 130, 4, 1),
     (700, 144, 2000, 8, 1),       # 64 x 128 tiles
-    (1543, 100, 2052, 4, 0),      # 128 x 128 tiles, packed, partial last step
-    (1537, 97, 2054, 8, 2),       # the same with GLU and odd rows
+    (1543, 100, 2052, 4, 0),      # the same, packed, partial last step
+    (1537, 97, 2054, 8, 2),       # with GLU and odd rows
     (2051, 72, 46, 8, 0),         # several slabs of rows
     (20000, 144, 60, 8, 0),       # 128 x 64 tiles (odd number of 64-channel blocks); many slabs
     (9, 40, 4300, 4, 0),          # dX: a split contraction long enough for the float64 sums
     (130, 3, 2, 8, 0), (130, 2, 3, 4, 0), (9, 15, 17, 8, 1), (9, 31, 14, 4, 2), (200, 33, 5, 4, 0),   # rows shorter than a piece
     (300, 50, 6, 8, 2), (5000, 30, 31, 4, 1), (25000, 17, 129, 8, 0),
     (6, 4400, 33, 8, 0),          # the same for the weight-only forward
-    (24700, 96, 130, 8, 0),       # 128 x 128 tiles, short contraction
+    (24700, 96, 130, 8, 0),       # 128 x 64 tiles, short contraction
 ]
 
 
@@ -173,7 +173,10 @@ def float64_products(M, K, N, moved=False, wild=False, change=None):
     (4099, 520, 1000, "dx dw y"), (2051, 1002, 1000, "dx dw y"), (300, 2040, 1030, "dx dw y"), (40, 512, 2048, "dx y"),
     (20000, 384, 1536, "dw"),          # a fan-in that the tuned dW's tiles do not divide, several slabs
     (2000, 1100, 4300, "dx dw y"),     # many tiles, one slab
-    (33, 130, 3, "dx dw y"), (1, 1, 1, "dx dw y"), (70, 2, 65, "dx dw y"), (65, 63, 64, "dx dw y")])
+    (33, 130, 3, "dx dw y"), (1, 1, 1, "dx dw y"), (70, 2, 65, "dx dw y"), (65, 63, 64, "dx dw y"),
+    (127, 1000, 1100, "dx dw y"), (128, 1000, 1100, "dx dw y"),          # digits: dW from two steps of rows on,
+    (24500, 3, 60, "dx dw y"), (24500, 4, 60, "dx dw y"),                # and four fan-in positions
+    (5000, 130, 127, "dx dw y"), (5000, 130, 128, "dx dw"), (5000, 127, 130, "dx dw y")])   # dX and weight-only from 128 positions on
 def test_off_the_grid_sums_are_float64(M, K, N, off):
     """Shapes that the tuned kernels do not divide: the float64 sum, rounded to float32 once."""
     print("[float64 sums]", M, K, N, flush=True)
