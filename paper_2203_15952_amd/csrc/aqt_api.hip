@@ -195,14 +195,13 @@ struct WeightSide {
   void *operand;   // what launch_dense_fwd_q gets as its workspace
   bool prepared;   // whether it already holds the matrix-core operand
 };
-// With a job list the quantizer launch is left to the caller (launch_quantize_weights_group over the list).
+// The matrices to be quantized; the launch is the caller's (launch_quantize_weights_group over the list).
 struct WeightJobList {
   WeightJob job[kWeightJobsMax];
   int n = 0;
 };
 aqt_status weight_side(const aqt_dense_policy &p, const float *w, const aqt_saved &l, int64_t M, int64_t K, int64_t N,
-                       int epilogue, uint32_t *wpart, void *wfrag, hipStream_t st, int32_t *dev_status,
-                       WeightSide *out, WeightJobList *later = nullptr) {
+                       int epilogue, uint32_t *wpart, void *wfrag, WeightSide *out, WeightJobList *later) {
   const bool takes = p.bits_x && fwd_q_uses_fragments(M, K, N, epilogue) && reinterpret_cast<uintptr_t>(l.xq) % 16 == 0;
   if (p.weights_ready) {
     const bool have = takes && l.wprep && reinterpret_cast<uintptr_t>(l.wprep) % 16 == 0;
@@ -213,14 +212,10 @@ aqt_status weight_side(const aqt_dense_policy &p, const float *w, const aqt_save
   if (!w) return AQT_ERR_INVALID_ARG;
   out->operand = wfrag;
   out->prepared = takes;
-  if (later) {
-    if (later->n >= kWeightJobsMax) return AQT_ERR_INVALID_ARG;
-    later->job[later->n++] = WeightJob{w, K, N, p.bits_w, l.wq_packed, l.s_w, l.wq_kn, l.mask_w, wpart,
-                                       takes ? wfrag : nullptr};
-    return AQT_OK;
-  }
-  return launch_quantize_weights(w, K, N, p.bits_w, l.wq_packed, l.s_w, l.wq_kn, l.mask_w, wpart, st, dev_status,
-                                 takes ? wfrag : nullptr);
+  if (later->n >= kWeightJobsMax) return AQT_ERR_INVALID_ARG;
+  later->job[later->n++] = WeightJob{w, K, N, p.bits_w, l.wq_packed, l.s_w, l.wq_kn, l.mask_w, wpart,
+                                     takes ? wfrag : nullptr};
+  return AQT_OK;
 }
 
 // The weight-side buffers of an encoder layer's eight dense layers, behind the modules' shared workspace: the layer
@@ -300,8 +295,8 @@ static aqt_status ffn_fwd_impl(const float *x, const float *ln_gamma, const floa
     s2 = sides[1];
   } else {   // both matrices through the weight quantizer in one launch pair
     WeightJobList jobs;
-    AQT_TRY(weight_side(p1, w1, l1, M, D, H, AQT_EPI_SWISH, f.wpart1, f.wfrag1, st, dev_status, &s1, &jobs));
-    AQT_TRY(weight_side(p2, w2, l2, M, H, D, AQT_EPI_NONE, f.wpart2, f.wfrag2, st, dev_status, &s2, &jobs));
+    AQT_TRY(weight_side(p1, w1, l1, M, D, H, AQT_EPI_SWISH, f.wpart1, f.wfrag1, &s1, &jobs));
+    AQT_TRY(weight_side(p2, w2, l2, M, H, D, AQT_EPI_NONE, f.wpart2, f.wfrag2, &s2, &jobs));
     AQT_TRY(launch_quantize_weights_group(jobs.job, jobs.n, st, dev_status));
   }
   const bool want_absmax = p2.bits_x != 0;
@@ -374,8 +369,8 @@ static aqt_status conv_module_fwd_impl(const float *x, const float *ln_gamma, co
     s2 = sides[1];
   } else {
     WeightJobList jobs;
-    AQT_TRY(weight_side(p1, w1, l1, M, D, 2 * D, AQT_EPI_GLU, f.wpart1, f.wfrag1, st, dev_status, &s1, &jobs));
-    AQT_TRY(weight_side(p2, w2, l2, M, D, D, AQT_EPI_NONE, f.wpart2, f.wfrag2, st, dev_status, &s2, &jobs));
+    AQT_TRY(weight_side(p1, w1, l1, M, D, 2 * D, AQT_EPI_GLU, f.wpart1, f.wfrag1, &s1, &jobs));
+    AQT_TRY(weight_side(p2, w2, l2, M, D, D, AQT_EPI_NONE, f.wpart2, f.wfrag2, &s2, &jobs));
     AQT_TRY(launch_quantize_weights_group(jobs.job, jobs.n, st, dev_status));
   }
   uint32_t *smax = reinterpret_cast<uint32_t *>(f.h_absmax);   // cleared by the normalisation's first pass
@@ -430,8 +425,8 @@ static aqt_status mhsa_fwd_impl(const float *x, const float *ln_gamma, const flo
     s2 = sides[1];
   } else {
     WeightJobList jobs;
-    AQT_TRY(weight_side(p1, wqkv, l1, M, D, 3 * D, AQT_EPI_NONE, f.wpart1, f.wfrag1, st, dev_status, &s1, &jobs));
-    AQT_TRY(weight_side(p2, wo, l2, M, D, D, AQT_EPI_NONE, f.wpart2, f.wfrag2, st, dev_status, &s2, &jobs));
+    AQT_TRY(weight_side(p1, wqkv, l1, M, D, 3 * D, AQT_EPI_NONE, f.wpart1, f.wfrag1, &s1, &jobs));
+    AQT_TRY(weight_side(p2, wo, l2, M, D, D, AQT_EPI_NONE, f.wpart2, f.wfrag2, &s2, &jobs));
     AQT_TRY(launch_quantize_weights_group(jobs.job, jobs.n, st, dev_status));
   }
   uint32_t *cmax = reinterpret_cast<uint32_t *>(f.h_absmax);   // cleared by the normalisation's first pass
@@ -598,8 +593,8 @@ aqt_status aqt_quantize_weights(const float *w, int64_t K, int64_t N, int bits_w
   if (!w || !wq_packed || !s_w || !shape_ok(K, N)) return AQT_ERR_INVALID_ARG;
   if (!bits_ok(bits_w)) return AQT_ERR_UNSUPPORTED;
   if (!ws || ws_bytes < weight_ws_bytes(N)) return AQT_ERR_WORKSPACE;
-  return launch_quantize_weights(w, K, N, bits_w, wq_packed, s_w, wq_kn, clip_mask_w,
-                                 static_cast<uint32_t *>(ws), static_cast<hipStream_t>(stream), dev_status);
+  const WeightJob job = {w, K, N, bits_w, wq_packed, s_w, wq_kn, clip_mask_w, static_cast<uint32_t *>(ws), nullptr};
+  return launch_quantize_weights_group(&job, 1, static_cast<hipStream_t>(stream), dev_status);
 }
 
 aqt_status aqt_unpack_weights(const void *wq_packed, int64_t K, int64_t N, int bits_w, int8_t *codes_kn,
@@ -720,13 +715,12 @@ aqt_status aqt_dense_fwd(const float *x, const float *w, int64_t M, int64_t K, i
   float *s_x = (saved && saved->s_x) ? saved->s_x : f.s_x;
   void *wq = (saved && saved->wq_packed) ? saved->wq_packed : f.wq;
   float *s_w = (saved && saved->s_w) ? saved->s_w : f.s_w;
-  AQT_TRY(launch_quantize(x, M, K, K, bits_x, AQT_AXIS_ALL, xq, s_x, saved ? saved->mask_x : nullptr,
-                          f.partials, st, dev_status));
   // when the matrix-core kernel takes the shape, the weight quantizer emits its operand in fragment order itself
   const bool frag = fwd_q_uses_fragments(M, K, N, epilogue) && reinterpret_cast<uintptr_t>(xq) % 16 == 0 &&
                     reinterpret_cast<uintptr_t>(f.wfrag) % 16 == 0;
-  AQT_TRY(launch_quantize_weights(w, K, N, bits_w, wq, s_w, saved ? saved->wq_kn : nullptr,
-                                  saved ? saved->mask_w : nullptr, f.wpart, st, dev_status, frag ? f.wfrag : nullptr));
+  const WeightJob job = {w, K, N, bits_w, wq, s_w, saved ? saved->wq_kn : nullptr, saved ? saved->mask_w : nullptr, f.wpart,
+                         frag ? f.wfrag : nullptr};
+  AQT_TRY(launch_quantize_dense(x, M, K, bits_x, xq, s_x, saved ? saved->mask_x : nullptr, f.partials, job, st, dev_status));
   return launch_dense_fwd_q(xq, s_x, wq, s_w, M, K, N, bits_w, bias, epilogue, y, nullptr, nullptr, f.wfrag, st,
                             saved ? saved->dact : nullptr, frag);
 }
@@ -942,22 +936,14 @@ aqt_status aqt_conformer_layer_fwd(const float *x, const aqt_conformer_layer_wei
   WeightJobList jobs;
   WeightSide sd[8];
   const int64_t D = g.D, H = g.H;
-  AQT_TRY(weight_side(pf1[0], w->ffn1_w1, saved->ffn1.l1, M, D, H, AQT_EPI_SWISH, lw.wpart[0], lw.wfrag[0], st,
-                      dev_status, &sd[0], &jobs));
-  AQT_TRY(weight_side(pf1[1], w->ffn1_w2, saved->ffn1.l2, M, H, D, AQT_EPI_NONE, lw.wpart[1], lw.wfrag[1], st,
-                      dev_status, &sd[1], &jobs));
-  AQT_TRY(weight_side(pa[0], w->att_wqkv, saved->att.qkv, M, D, 3 * D, AQT_EPI_NONE, lw.wpart[2], lw.wfrag[2], st,
-                      dev_status, &sd[2], &jobs));
-  AQT_TRY(weight_side(pa[1], w->att_wo, saved->att.out, M, D, D, AQT_EPI_NONE, lw.wpart[3], lw.wfrag[3], st,
-                      dev_status, &sd[3], &jobs));
-  AQT_TRY(weight_side(pc[0], w->conv_w1, saved->conv.pw1, M, D, 2 * D, AQT_EPI_GLU, lw.wpart[4], lw.wfrag[4], st,
-                      dev_status, &sd[4], &jobs));
-  AQT_TRY(weight_side(pc[1], w->conv_w2, saved->conv.pw2, M, D, D, AQT_EPI_NONE, lw.wpart[5], lw.wfrag[5], st,
-                      dev_status, &sd[5], &jobs));
-  AQT_TRY(weight_side(pf2[0], w->ffn2_w1, saved->ffn2.l1, M, D, H, AQT_EPI_SWISH, lw.wpart[6], lw.wfrag[6], st,
-                      dev_status, &sd[6], &jobs));
-  AQT_TRY(weight_side(pf2[1], w->ffn2_w2, saved->ffn2.l2, M, H, D, AQT_EPI_NONE, lw.wpart[7], lw.wfrag[7], st,
-                      dev_status, &sd[7], &jobs));
+  AQT_TRY(weight_side(pf1[0], w->ffn1_w1, saved->ffn1.l1, M, D, H, AQT_EPI_SWISH, lw.wpart[0], lw.wfrag[0], &sd[0], &jobs));
+  AQT_TRY(weight_side(pf1[1], w->ffn1_w2, saved->ffn1.l2, M, H, D, AQT_EPI_NONE, lw.wpart[1], lw.wfrag[1], &sd[1], &jobs));
+  AQT_TRY(weight_side(pa[0], w->att_wqkv, saved->att.qkv, M, D, 3 * D, AQT_EPI_NONE, lw.wpart[2], lw.wfrag[2], &sd[2], &jobs));
+  AQT_TRY(weight_side(pa[1], w->att_wo, saved->att.out, M, D, D, AQT_EPI_NONE, lw.wpart[3], lw.wfrag[3], &sd[3], &jobs));
+  AQT_TRY(weight_side(pc[0], w->conv_w1, saved->conv.pw1, M, D, 2 * D, AQT_EPI_GLU, lw.wpart[4], lw.wfrag[4], &sd[4], &jobs));
+  AQT_TRY(weight_side(pc[1], w->conv_w2, saved->conv.pw2, M, D, D, AQT_EPI_NONE, lw.wpart[5], lw.wfrag[5], &sd[5], &jobs));
+  AQT_TRY(weight_side(pf2[0], w->ffn2_w1, saved->ffn2.l1, M, D, H, AQT_EPI_SWISH, lw.wpart[6], lw.wfrag[6], &sd[6], &jobs));
+  AQT_TRY(weight_side(pf2[1], w->ffn2_w2, saved->ffn2.l2, M, H, D, AQT_EPI_NONE, lw.wpart[7], lw.wfrag[7], &sd[7], &jobs));
   AQT_TRY(launch_quantize_weights_group(jobs.job, jobs.n, st, dev_status));
   // half-step feed-forward module.  From here on the residual connection in front of a module is formed by that
   // module's normalisation pass: r = r_prev + alpha * (previous module's output), left in saved->r*.

@@ -69,10 +69,7 @@ aqt_status launch_quantize_with_absmax(const float *x, int64_t rows, int64_t col
 aqt_status launch_quantize_with_scale(const float *x, int64_t rows, int64_t cols, int64_t ldx, int bits,
                                       int axis, const float *scale, int8_t *q, uint32_t *mask,
                                       hipStream_t st);
-aqt_status launch_quantize_weights(const float *w, int64_t K, int64_t N, int bits_w, void *wq_packed,
-                                   float *s_w, int8_t *wq_kn, uint32_t *mask_w, uint32_t *part,
-                                   hipStream_t st, int32_t *dev_status, void *wfrag = nullptr);
-// Several matrices through the weight quantizer in one launch pair (same arithmetic per matrix).
+// Up to eight matrices through the weight quantizer in one launch pair.
 struct WeightJob {
   const float *w;
   int64_t K, N;
@@ -86,6 +83,9 @@ struct WeightJob {
 };
 constexpr int kWeightJobsMax = 8;
 aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream_t st, int32_t *dev_status);
+// The activations (per tensor) and the weights of one dense layer; one launch pair where the activations are aligned and want no mask.
+aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int bits_x, int8_t *q, float *scale, uint32_t *mask,
+                                 float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status);
 inline size_t weight_ws_bytes(int64_t N) { return align_up(static_cast<size_t>(kWeightSlabs) * N * 4, 256); }
 aqt_status launch_unpack_weights(const void *wq_packed, int64_t K, int64_t N, int bits_w,
                                  int8_t *codes_kn, hipStream_t st);

@@ -73,13 +73,13 @@ __device__ __forceinline__ uint32_t absmax4(float4 a) {
 // ---- per-tensor, contiguous: pass 1 -------------------------------------------
 // Each block owns one contiguous run of the tensor (per4 float4 per block).
 template <bool STREAM>
-__global__ __launch_bounds__(kThreads) void absmax_flat_kernel(const float *__restrict__ x, int64_t n,
-                                                               int64_t per4, uint32_t *__restrict__ partial) {
+__device__ __forceinline__ void absmax_flat_body(const float *__restrict__ x, int64_t n, int64_t per4,
+                                                 uint32_t *__restrict__ partial, unsigned block) {
   auto ld = [](const float4 *p) { return STREAM ? load_stream(p) : *p; };
   __shared__ uint32_t sm[4];
   const int64_t n4 = n >> 2;
   const float4 *x4 = reinterpret_cast<const float4 *>(x);
-  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * per4;
+  const int64_t i0 = static_cast<int64_t>(block) * per4;
   const int64_t i1 = min(n4, i0 + per4);
   uint32_t m = 0;
   int64_t i = i0 + threadIdx.x;
@@ -89,10 +89,16 @@ __global__ __launch_bounds__(kThreads) void absmax_flat_kernel(const float *__re
     m = max(m, max(max(absmax4(a), absmax4(b)), max(absmax4(c), absmax4(d))));
   }
   for (; i < i1; i += kThreads) m = max(m, absmax4(ld(x4 + i)));
-  if (blockIdx.x == 0)
+  if (block == 0)
     for (int64_t j = (n4 << 2) + threadIdx.x; j < n; j += kThreads) m = max(m, abs_bits(x[j]));
   m = block_max(m, sm);
-  if (threadIdx.x == 0) partial[blockIdx.x] = m;
+  if (threadIdx.x == 0) partial[block] = m;
+}
+
+template <bool STREAM>
+__global__ __launch_bounds__(kThreads) void absmax_flat_kernel(const float *__restrict__ x, int64_t n,
+                                                               int64_t per4, uint32_t *__restrict__ partial) {
+  absmax_flat_body<STREAM>(x, n, per4, partial, blockIdx.x);
 }
 
 __device__ __forceinline__ uint32_t pack4(float4 v, float s, float fq) {
@@ -106,23 +112,23 @@ __device__ __forceinline__ uint32_t pack4(float4 v, float s, float fq) {
 // ---- per-tensor, contiguous: pass 2 -------------------------------------------
 // Same block -> run mapping as pass 1, but blocks are visited in reverse so that
 // the part of the tensor pass 1 touched last is read first.
-__global__ __launch_bounds__(kThreads) void quantize_flat_kernel(
+__device__ __forceinline__ void quantize_flat_body(
     const float *__restrict__ x, int64_t n, int64_t per4, const uint32_t *__restrict__ partial, int nparts,
-    int qmax, int8_t *__restrict__ q, float *__restrict__ scale, int32_t *dev_status) {
+    int qmax, int8_t *__restrict__ q, float *__restrict__ scale, int32_t *dev_status, unsigned block, unsigned blocks) {
   __shared__ uint32_t sm[4];
   uint32_t m = 0;
   for (int i = threadIdx.x; i < nparts; i += kThreads) m = max(m, partial[i]);
   m = block_max(m, sm);
   const float fq = static_cast<float>(qmax);
   const float s = __uint_as_float(m) / fq;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (block == 0 && threadIdx.x == 0) {
     scale[0] = s;
     if (m >= 0x7F800000u && dev_status) *dev_status = AQT_ERR_NONFINITE;
   }
   const int64_t n4 = n >> 2;
   const float4 *x4 = reinterpret_cast<const float4 *>(x);
   uint32_t *q4 = reinterpret_cast<uint32_t *>(q);
-  const int64_t blk = static_cast<int64_t>(gridDim.x) - 1 - blockIdx.x;
+  const int64_t blk = static_cast<int64_t>(blocks) - 1 - block;
   const int64_t i0 = blk * per4;
   const int64_t i1 = min(n4, i0 + per4);
   int64_t i = i0 + threadIdx.x;
@@ -135,8 +141,14 @@ __global__ __launch_bounds__(kThreads) void quantize_flat_kernel(
     store_stream(q4 + i + 3 * kThreads, pack4(d, s, fq));
   }
   for (; i < i1; i += kThreads) store_stream(q4 + i, pack4(load_stream(x4 + i), s, fq));
-  if (blockIdx.x == 0)
+  if (block == 0)
     for (int64_t j = (n4 << 2) + threadIdx.x; j < n; j += kThreads) q[j] = static_cast<int8_t>(quant_code(x[j], s, fq));
+}
+
+__global__ __launch_bounds__(kThreads) void quantize_flat_kernel(
+    const float *__restrict__ x, int64_t n, int64_t per4, const uint32_t *__restrict__ partial, int nparts,
+    int qmax, int8_t *__restrict__ q, float *__restrict__ scale, int32_t *dev_status) {
+  quantize_flat_body(x, n, per4, partial, nparts, qmax, q, scale, dev_status, blockIdx.x, gridDim.x);
 }
 
 // ---- general shapes: abs-max per tensor / column / row ---------------------------
@@ -281,71 +293,127 @@ __device__ __forceinline__ void wabsmax_partial_body(const float *__restrict__ w
   const int64_t n = static_cast<int64_t>(bx) * 64 + tx;
   uint32_t m = 0;
   if (n < N)
-    for (int64_t k = k0 + ty; k < k1; k += 4) m = max(m, abs_bits(w[k * N + n]));
+    for (int64_t k = k0 + ty; k < k1; k += 32) {   // eight loads in flight, the slab's last row again behind its end
+      uint32_t v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = abs_bits(w[min(k + 4 * i, k1 - 1) * N + n]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m = max(m, v[i]);
+    }
   sm[ty][tx] = m;
   __syncthreads();
   if (ty == 0 && n < N)
     part[static_cast<int64_t>(by) * N + n] = max(max(sm[0][tx], sm[1][tx]), max(sm[2][tx], sm[3][tx]));
 }
 
-__global__ __launch_bounds__(kThreads) void wabsmax_partial_kernel(const float *__restrict__ w, int64_t K,
-                                                                   int64_t N, int64_t rows_per_slab, int vec4,
-                                                                   uint32_t *__restrict__ part) {
-  wabsmax_partial_body(w, K, N, rows_per_slab, vec4, part, blockIdx.x, blockIdx.y);
-}
-
+// Bound by latency: a tile is 8 KB, so what counts is how many trips to memory follow one another.  All of a thread's loads are
+// requested before the first is used (the fold of the slab maxima alone was sixteen trips in a row: 10.2 us at 520 x 1000, see
+// quantize_dense_kernel for what is left), the [K,N] codes leave four at a time and the operand's rows as whole words where the
+// widths allow it.
 __device__ __forceinline__ void quantize_weights_body(
     const float *__restrict__ w, int64_t K, int64_t N, int qmax, int packed, const uint32_t *__restrict__ part,
     int slabs, uint8_t *__restrict__ wq_packed, float *__restrict__ s_w, int8_t *__restrict__ wq_kn,
-    uint32_t *__restrict__ mask_w, int32_t *dev_status, uint4 *__restrict__ wfrag, unsigned bx, unsigned by) {
-  __shared__ int8_t tile[kWCols][kWChunk + 4];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    uint32_t *__restrict__ mask_w, int32_t *dev_status, uint4 *__restrict__ wfrag, int vec4, unsigned bx, unsigned by) {
+  __shared__ __attribute__((aligned(16))) int8_t tile[kWCols][kWChunk + 4];
+  __shared__ __attribute__((aligned(16))) uint32_t top[kThreads / 64][kWCols];   // the channels' maxima, a quarter of the slabs each
   const int64_t n0 = static_cast<int64_t>(bx) * kWCols;
   const int64_t k0 = static_cast<int64_t>(by) * kWChunk;
-  const int64_t n = n0 + tx;
-  const bool live = n < N;
-  uint32_t m = 0;
-  if (live)
-    for (int j = 0; j < slabs; ++j) m = max(m, part[static_cast<int64_t>(j) * N + n]);
   const float fq = static_cast<float>(qmax);
-  const float s = __uint_as_float(m) / fq;
-  if (by == 0 && ty == 0 && live) {
-    s_w[n] = s;
-    if (m >= 0x7F800000u && dev_status) *dev_status = AQT_ERR_NONFINITE;
-  }
-  const int64_t row_bytes = packed ? (K + 1) / 2 : K;
+  // this thread's values: four channels of rows ty, ty + 32, or one channel of rows ty + 8 j (the last row or channel again beyond the end)
+  const int vx = threadIdx.x & 7, vy = threadIdx.x >> 3, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  float v[8];
+  if (vec4) {
 #pragma unroll
-  for (int j = 0; j < kWChunk / 8; ++j) {
-    const int kk = ty + 8 * j;
-    const int64_t k = k0 + kk;
-    int code = 0;
-    if (live && k < K) {
-      bool pass;
-      code = quant_code(w[k * N + n], s, fq, pass);
-      if (wq_kn) wq_kn[k * N + n] = static_cast<int8_t>(code);
-      // Mask words straddle threads here; bits are set with an atomic OR on a
-      // buffer the launcher has zeroed.
-      if (mask_w && pass) atomicOr(&mask_w[(k * N + n) >> 5], 1u << ((k * N + n) & 31));
+    for (int j = 0; j < 2; ++j) {
+      const float4 a = *reinterpret_cast<const float4 *>(w + min(k0 + vy + 32 * j, K - 1) * N + min(n0 + 4 * vx, N - 4));
+      v[4 * j] = a.x; v[4 * j + 1] = a.y; v[4 * j + 2] = a.z; v[4 * j + 3] = a.w;
     }
-    tile[tx][kk] = static_cast<int8_t>(code);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = w[min(k0 + ty + 8 * j, K - 1) * N + min(n0 + tx, N - 1)];
+  }
+  {
+    uint32_t m[kWeightSlabs / 8];
+#pragma unroll
+    for (int i = 0; i < kWeightSlabs / 8; ++i) m[i] = part[static_cast<int64_t>(min(ty + 8 * i, slabs - 1)) * N + min(n0 + tx, N - 1)];
+    static_assert(kWeightSlabs == 16, "two slabs a thread");
+    uint32_t most = max(m[0], m[1]);
+    most = max(most, static_cast<uint32_t>(__shfl_xor(static_cast<int>(most), 32, 64)));
+    if ((threadIdx.x & 32) == 0) top[threadIdx.x >> 6][tx] = most;
   }
   __syncthreads();
-  // 32 rows x (64 | 32) output bytes; thread t handles bytes t, t+256, ...
-  const int bytes_per_row = packed ? kWChunk / 2 : kWChunk;
-  for (int b = threadIdx.x; b < kWCols * bytes_per_row; b += kThreads) {
-    const int rn = b / bytes_per_row, jb = b - rn * bytes_per_row;
-    const int64_t nn = n0 + rn;
-    if (nn >= N) continue;
-    if (packed) {
-      const int64_t kb = (k0 >> 1) + jb;
-      if (kb < row_bytes) {
-        const uint32_t lo = static_cast<uint32_t>(tile[rn][2 * jb]) & 0xFu;
-        const uint32_t hi = static_cast<uint32_t>(tile[rn][2 * jb + 1]) & 0xFu;  // 0 beyond K
-        wq_packed[nn * row_bytes + kb] = static_cast<uint8_t>(lo | (hi << 4));
+  auto scale_of = [&](int c) {
+    const uint32_t m = max(max(top[0][c], top[1][c]), max(top[2][c], top[3][c]));
+    return __uint_as_float(m) / fq;
+  };
+  if (by == 0 && threadIdx.x < kWCols && n0 + threadIdx.x < N) {
+    const float s = scale_of(threadIdx.x);
+    s_w[n0 + threadIdx.x] = s;
+    if (!(fabsf(s) < INFINITY) && dev_status) *dev_status = AQT_ERR_NONFINITE;
+  }
+  // Mask words straddle threads; bits are set with an atomic OR on a buffer the launcher has zeroed.
+  auto mark = [&](int64_t at) { atomicOr(&mask_w[at >> 5], 1u << (at & 31)); };
+  if (vec4) {
+    float s[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s[c] = scale_of(4 * vx + c);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int kk = vy + 32 * j;
+      const int64_t k = k0 + kk, n = n0 + 4 * vx;
+      const bool live = k < K && n < N;   // four channels at once: N is a multiple of four
+      uint32_t codes = 0u;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        bool pass;
+        const int code = live ? quant_code(v[4 * j + c], s[c], fq, pass) : 0;
+        if (live && mask_w && pass) mark(k * N + n + c);
+        tile[4 * vx + c][kk] = static_cast<int8_t>(code);
+        codes |= (static_cast<uint32_t>(code) & 0xFFu) << (8 * c);
       }
-    } else {
-      const int64_t k = k0 + jb;
-      if (k < K) wq_packed[nn * row_bytes + k] = static_cast<uint8_t>(tile[rn][jb]);
+      if (live && wq_kn) *reinterpret_cast<uint32_t *>(wq_kn + k * N + n) = codes;
+    }
+  } else {
+    const float s = scale_of(tx);
+    const int64_t n = n0 + tx;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int kk = ty + 8 * j;
+      const int64_t k = k0 + kk;
+      int code = 0;
+      if (n < N && k < K) {
+        bool pass;
+        code = quant_code(v[j], s, fq, pass);
+        if (wq_kn) wq_kn[k * N + n] = static_cast<int8_t>(code);
+        if (mask_w && pass) mark(k * N + n);
+      }
+      tile[tx][kk] = static_cast<int8_t>(code);
+    }
+  }
+  __syncthreads();
+  // 32 rows x (64 | 32) output bytes
+  const int64_t row_bytes = packed ? (K + 1) / 2 : K;
+  const int bytes_per_row = packed ? kWChunk / 2 : kWChunk;
+  const int64_t b0 = packed ? k0 >> 1 : k0;
+  auto byte_of = [&](int rn, int jb) -> uint32_t {
+    if (!packed) return static_cast<uint8_t>(tile[rn][jb]);
+    return (static_cast<uint32_t>(tile[rn][2 * jb]) & 0xFu) | ((static_cast<uint32_t>(tile[rn][2 * jb + 1]) & 0xFu) << 4);   // 0 beyond K
+  };
+  if (row_bytes % 4 == 0 && reinterpret_cast<uintptr_t>(wq_packed) % 4 == 0) {
+    const int words = bytes_per_row / 4;   // 8 or 16 a row
+    for (int i = threadIdx.x; i < kWCols * words; i += kThreads) {
+      const int rn = packed ? i >> 3 : i >> 4, jw = i & (words - 1);
+      if (n0 + rn >= N || b0 + 4 * jw >= row_bytes) continue;
+      uint32_t t = 0u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) t |= byte_of(rn, 4 * jw + b) << (8 * b);
+      *reinterpret_cast<uint32_t *>(wq_packed + (n0 + rn) * row_bytes + b0 + 4 * jw) = t;
+    }
+  } else {
+    for (int i = threadIdx.x; i < kWCols * bytes_per_row; i += kThreads) {
+      const int rn = packed ? i >> 5 : i >> 6, jb = i & (bytes_per_row - 1);
+      if (n0 + rn >= N || b0 + jb >= row_bytes) continue;
+      wq_packed[(n0 + rn) * row_bytes + b0 + jb] = static_cast<uint8_t>(byte_of(rn, jb));
     }
   }
   // The same tile once more in the order the forward contraction's matrix-core fragments
@@ -390,21 +458,12 @@ __device__ __forceinline__ void quantize_weights_body(
   }
 }
 
-__global__ __launch_bounds__(kThreads) void quantize_weights_kernel(
-    const float *__restrict__ w, int64_t K, int64_t N, int qmax, int packed, const uint32_t *__restrict__ part,
-    int slabs, uint8_t *__restrict__ wq_packed, float *__restrict__ s_w, int8_t *__restrict__ wq_kn,
-    uint32_t *__restrict__ mask_w, int32_t *dev_status, uint4 *__restrict__ wfrag) {
-  quantize_weights_body(w, K, N, qmax, packed, part, slabs, wq_packed, s_w, wq_kn, mask_w, dev_status, wfrag,
-                        blockIdx.x, blockIdx.y);
-}
-
-// Several weight matrices in one launch pair: a one-dimensional grid holds every matrix's own blocks one matrix
-// after the other (first1 / first2: where each matrix's blocks start).  The arithmetic per matrix is that of the
-// single-matrix kernels above.
+// One weight matrix as the kernels take it.
 struct WeightJobDev {
   const float *w;
   int64_t K, N, rows_per_slab;
-  int qmax, packed, slabs, vec4;
+  int qmax, packed, slabs;
+  int vec4_max, vec4;         // four channels at a time: in the abs-max pass, in the quantizer
   unsigned gx1, gx2;          // this matrix's own grid width: abs-max column blocks, quantizer column blocks
   uint32_t *part;
   uint8_t *wq_packed;
@@ -413,6 +472,16 @@ struct WeightJobDev {
   uint32_t *mask_w;
   uint4 *wfrag;
 };
+__device__ __forceinline__ void wabsmax_partial(const WeightJobDev &j, unsigned block) {
+  wabsmax_partial_body(j.w, j.K, j.N, j.rows_per_slab, j.vec4_max, j.part, block % j.gx1, block / j.gx1);
+}
+__device__ __forceinline__ void quantize_weights(const WeightJobDev &j, int32_t *dev_status, unsigned block) {
+  quantize_weights_body(j.w, j.K, j.N, j.qmax, j.packed, j.part, j.slabs, j.wq_packed, j.s_w, j.wq_kn, j.mask_w,
+                        dev_status, j.wfrag, j.vec4, block % j.gx2, block / j.gx2);
+}
+
+// Several weight matrices in one launch pair: a one-dimensional grid holds every matrix's own blocks one matrix
+// after the other (first1 / first2: where each matrix's blocks start).
 struct WeightJobsDev {
   WeightJobDev job[kWeightJobsMax];
   unsigned first1[kWeightJobsMax + 1], first2[kWeightJobsMax + 1];   // block offsets; entries from n on: the grid size
@@ -430,17 +499,37 @@ __device__ __forceinline__ int job_of_block(const unsigned *first, int n, unsign
 __global__ __launch_bounds__(kThreads) void wabsmax_partial_group_kernel(const WeightJobsDev jobs) {
   const int ji = job_of_block(jobs.first1, jobs.n, blockIdx.x);
   const WeightJobDev &j = jobs.job[ji];
-  const unsigned local = blockIdx.x - jobs.first1[ji];
-  wabsmax_partial_body(j.w, j.K, j.N, j.rows_per_slab, j.vec4, j.part, local % j.gx1, local / j.gx1);
+  wabsmax_partial(j, blockIdx.x - jobs.first1[ji]);
 }
 
 __global__ __launch_bounds__(kThreads) void quantize_weights_group_kernel(const WeightJobsDev jobs,
                                                                           int32_t *dev_status) {
   const int ji = job_of_block(jobs.first2, jobs.n, blockIdx.x);
   const WeightJobDev &j = jobs.job[ji];
-  const unsigned local = blockIdx.x - jobs.first2[ji];
-  quantize_weights_body(j.w, j.K, j.N, j.qmax, j.packed, j.part, j.slabs, j.wq_packed, j.s_w, j.wq_kn, j.mask_w,
-                        dev_status, j.wfrag, local % j.gx2, local / j.gx2);
+  quantize_weights(j, dev_status, blockIdx.x - jobs.first2[ji]);
+}
+
+// The activations and the weights of one dense layer in one launch pair: neither needs the other's abs-max, and at the sizes of a
+// single layer a launch in a chain takes 4 us whatever it does.  The weights' blocks come first: theirs is the longer
+// chain of trips to memory.  256 x 256 -> 1024, the whole forward: 25 us with a pair each (the weights' second kernel 8), 16 here;
+// the two layers of 4099 tokens, 520 x 1000, forward and backward: 268 -> 244.
+struct FlatJobDev {
+  const float *x;
+  int64_t n, per4;
+  uint32_t *partial;
+  int blocks, qmax;
+  int8_t *q;
+  float *scale;
+};
+template <bool STREAM>
+__global__ __launch_bounds__(kThreads) void absmax_dense_kernel(const FlatJobDev f, const WeightJobDev j, unsigned weight_blocks) {
+  if (blockIdx.x < weight_blocks) wabsmax_partial(j, blockIdx.x);
+  else absmax_flat_body<STREAM>(f.x, f.n, f.per4, f.partial, blockIdx.x - weight_blocks);
+}
+__global__ __launch_bounds__(kThreads) void quantize_dense_kernel(const FlatJobDev f, const WeightJobDev j, unsigned weight_blocks,
+                                                                  int32_t *dev_status) {
+  if (blockIdx.x < weight_blocks) quantize_weights(j, dev_status, blockIdx.x);
+  else quantize_flat_body(f.x, f.n, f.per4, f.partial, f.blocks, f.qmax, f.q, f.scale, dev_status, blockIdx.x - weight_blocks, f.blocks);
 }
 
 __global__ __launch_bounds__(kThreads) void zero_words_kernel(uint32_t *p, int64_t n) {
@@ -472,6 +561,50 @@ int grid_for(int64_t work_items, int per_block, int cap) {
   return static_cast<int>(g);
 }
 
+// up to 4096 blocks = 16 per CU, each on its own contiguous run of the tensor; every thread keeps four 16-byte loads in flight.
+int flat_blocks(int64_t n, int64_t *per4) {
+  const int g = grid_for(n / 4, kThreads * 4, kMaxPartials);
+  *per4 = cdiv(cdiv(n / 4, g), kThreads) * kThreads;
+  const int64_t used = *per4 > 0 ? cdiv(n / 4, *per4) : 1;
+  return static_cast<int>(used < 1 ? 1 : used);
+}
+// Below 192 MB pass 1 reads with ordinary loads, above with non-temporal ones: measured, ordinary loads make the pair of passes
+// 2-5 % faster at 26, 105 and 134 MB (whether that is the second pass hitting a cache is not something the available counters can show).
+bool streams(int64_t n) { return n * 4 > (int64_t(192) << 20); }
+
+// A matrix in the kernels' form, its clip mask cleared; blocks1, blocks2: its blocks in either launch.
+aqt_status weight_job(const WeightJob &a, hipStream_t st, WeightJobDev *out, int64_t *blocks1, int64_t *blocks2) {
+  if (!a.w || !a.wq_packed || !a.s_w || !a.part || a.K < 1 || a.N < 1) return AQT_ERR_INVALID_ARG;
+  if (a.wfrag && (a.N % kWCols != 0 || a.K % kWChunk != 0 || reinterpret_cast<uintptr_t>(a.wfrag) % 16 != 0))
+    return AQT_ERR_INVALID_ARG;
+  if (cdiv(a.N, kWCols) * cdiv(a.K, kWChunk) > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
+  if (a.mask_w) {
+    const int64_t words = cdiv(a.K * a.N, 32);
+    zero_words_kernel<<<grid_for(words, kThreads, 1024), kThreads, 0, st>>>(a.mask_w, words);
+    AQT_HIP(hipGetLastError());
+  }
+  int64_t slabs = cdiv(a.K, 32);
+  if (slabs > kWeightSlabs) slabs = kWeightSlabs;
+  const int64_t rows_per_slab = cdiv(a.K, slabs);
+  slabs = cdiv(a.K, rows_per_slab);
+  WeightJobDev &j = *out;
+  j.w = a.w; j.K = a.K; j.N = a.N; j.rows_per_slab = rows_per_slab;
+  j.qmax = qmax_of(a.bits_w); j.packed = packed4(a.bits_w) ? 1 : 0; j.slabs = static_cast<int>(slabs);
+  j.vec4_max = (a.N % 4 == 0) && (reinterpret_cast<uintptr_t>(a.w) % 16 == 0);
+  j.vec4 = j.vec4_max && reinterpret_cast<uintptr_t>(a.wq_kn) % 4 == 0;
+  j.gx1 = static_cast<unsigned>(cdiv(a.N, 64));
+  j.gx2 = static_cast<unsigned>(cdiv(a.N, kWCols));
+  j.part = a.part; j.wq_packed = static_cast<uint8_t *>(a.wq_packed); j.s_w = a.s_w; j.wq_kn = a.wq_kn;
+  j.mask_w = a.mask_w; j.wfrag = static_cast<uint4 *>(a.wfrag);
+  *blocks1 = static_cast<int64_t>(j.gx1) * slabs;
+  *blocks2 = static_cast<int64_t>(j.gx2) * cdiv(a.K, kWChunk);
+  return AQT_OK;
+}
+
+bool flat_ok(const float *x, int64_t cols, int64_t ldx, const int8_t *q) {
+  return ldx == cols && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(q) % 4 == 0;
+}
+
 }  // namespace
 
 aqt_status launch_quantize(const float *x, int64_t rows, int64_t cols, int64_t ldx, int bits, int axis,
@@ -481,19 +614,11 @@ aqt_status launch_quantize(const float *x, int64_t rows, int64_t cols, int64_t l
   const int64_t n = rows * cols;
   uint32_t *part = reinterpret_cast<uint32_t *>(partials);
   if (axis == AQT_AXIS_ALL) {
-    const bool flat = (ldx == cols) && (reinterpret_cast<uintptr_t>(x) % 16 == 0) &&
-                      (reinterpret_cast<uintptr_t>(q) % 4 == 0);
+    const bool flat = flat_ok(x, cols, ldx, q);
     if (flat && !mask) {
-      // up to 4096 blocks = 16 per CU, each on its own contiguous run of the tensor;
-      // every thread keeps four 16-byte loads in flight.
-      int g = grid_for(n / 4, kThreads * 4, kMaxPartials);
-      const int64_t per4 = cdiv(cdiv(n / 4, g), kThreads) * kThreads;
-      g = static_cast<int>(per4 > 0 ? cdiv(n / 4, per4) : 1);
-      if (g < 1) g = 1;
-      // Below 192 MB pass 1 reads with ordinary loads, above with non-temporal ones: measured,
-      // ordinary loads make the pair of passes 2-5 % faster at 26, 105 and 134 MB (whether that
-      // is the second pass hitting a cache is not something the available counters can show).
-      if (n * 4 <= (int64_t(192) << 20)) absmax_flat_kernel<false><<<g, kThreads, 0, st>>>(x, n, per4, part);
+      int64_t per4;
+      const int g = flat_blocks(n, &per4);
+      if (!streams(n)) absmax_flat_kernel<false><<<g, kThreads, 0, st>>>(x, n, per4, part);
       else absmax_flat_kernel<true><<<g, kThreads, 0, st>>>(x, n, per4, part);
       AQT_HIP(hipGetLastError());
       quantize_flat_kernel<<<g, kThreads, 0, st>>>(x, n, per4, part, g, qmax, q, scale, dev_status);
@@ -529,13 +654,9 @@ aqt_status launch_quantize_with_absmax(const float *x, int64_t rows, int64_t col
                                        hipStream_t st, int32_t *dev_status) {
   const int qmax = qmax_of(bits);
   const int64_t n = rows * cols;
-  const bool flat = (ldx == cols) && (reinterpret_cast<uintptr_t>(x) % 16 == 0) &&
-                    (reinterpret_cast<uintptr_t>(q) % 4 == 0);
-  if (flat && !mask) {
-    int g = grid_for(n / 4, kThreads * 4, kMaxPartials);
-    const int64_t per4 = cdiv(cdiv(n / 4, g), kThreads) * kThreads;
-    g = static_cast<int>(per4 > 0 ? cdiv(n / 4, per4) : 1);
-    if (g < 1) g = 1;
+  if (flat_ok(x, cols, ldx, q) && !mask) {
+    int64_t per4;
+    const int g = flat_blocks(n, &per4);
     quantize_flat_kernel<<<g, kThreads, 0, st>>>(x, n, per4, absmax_bits, 1, qmax, q, scale, dev_status);
     AQT_HIP(hipGetLastError());
     return AQT_OK;
@@ -555,28 +676,22 @@ aqt_status launch_quantize_with_scale(const float *x, int64_t rows, int64_t cols
   return AQT_OK;
 }
 
-aqt_status launch_quantize_weights(const float *w, int64_t K, int64_t N, int bits_w, void *wq_packed,
-                                   float *s_w, int8_t *wq_kn, uint32_t *mask_w, uint32_t *part, hipStream_t st,
-                                   int32_t *dev_status, void *wfrag) {
-  if (wfrag && (N % kWCols != 0 || K % kWChunk != 0 || reinterpret_cast<uintptr_t>(wfrag) % 16 != 0))
-    return AQT_ERR_INVALID_ARG;
-  if (mask_w) {
-    const int64_t words = cdiv(K * N, 32);
-    zero_words_kernel<<<grid_for(words, kThreads, 1024), kThreads, 0, st>>>(mask_w, words);
-    AQT_HIP(hipGetLastError());
+aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int bits_x, int8_t *q, float *scale, uint32_t *mask,
+                                 float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status) {
+  if (mask || !flat_ok(x, cols, cols, q)) {
+    AQT_TRY(launch_quantize(x, rows, cols, cols, bits_x, AQT_AXIS_ALL, q, scale, mask, partials, st, dev_status));
+    return launch_quantize_weights_group(&w, 1, st, dev_status);
   }
-  int64_t slabs = cdiv(K, 32);
-  if (slabs > kWeightSlabs) slabs = kWeightSlabs;
-  const int64_t rows_per_slab = cdiv(K, slabs);
-  slabs = cdiv(K, rows_per_slab);
-  dim3 g1(static_cast<unsigned>(cdiv(N, 64)), static_cast<unsigned>(slabs));
-  const int vec4 = (N % 4 == 0) && (reinterpret_cast<uintptr_t>(w) % 16 == 0);
-  wabsmax_partial_kernel<<<g1, kThreads, 0, st>>>(w, K, N, rows_per_slab, vec4, part);
+  FlatJobDev f{x, rows * cols, 0, reinterpret_cast<uint32_t *>(partials), 0, qmax_of(bits_x), q, scale};
+  f.blocks = flat_blocks(f.n, &f.per4);
+  WeightJobDev j;
+  int64_t b1, b2;
+  AQT_TRY(weight_job(w, st, &j, &b1, &b2));
+  if (b1 + f.blocks > 0x7FFFFFFF || b2 + f.blocks > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
+  auto pass1 = streams(f.n) ? absmax_dense_kernel<true> : absmax_dense_kernel<false>;
+  pass1<<<static_cast<unsigned>(b1 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b1));
   AQT_HIP(hipGetLastError());
-  dim3 g2(static_cast<unsigned>(cdiv(N, kWCols)), static_cast<unsigned>(cdiv(K, kWChunk)));
-  quantize_weights_kernel<<<g2, kThreads, 0, st>>>(w, K, N, qmax_of(bits_w), packed4(bits_w) ? 1 : 0, part,
-                                                   static_cast<int>(slabs), static_cast<uint8_t *>(wq_packed),
-                                                   s_w, wq_kn, mask_w, dev_status, static_cast<uint4 *>(wfrag));
+  quantize_dense_kernel<<<static_cast<unsigned>(b2 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b2), dev_status);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }
@@ -584,38 +699,16 @@ aqt_status launch_quantize_weights(const float *w, int64_t K, int64_t N, int bit
 aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream_t st, int32_t *dev_status) {
   if (n < 0 || n > kWeightJobsMax) return AQT_ERR_INVALID_ARG;
   if (n == 0) return AQT_OK;
-  if (n == 1)
-    return launch_quantize_weights(jobs[0].w, jobs[0].K, jobs[0].N, jobs[0].bits_w, jobs[0].wq_packed, jobs[0].s_w,
-                                   jobs[0].wq_kn, jobs[0].mask_w, jobs[0].part, st, dev_status, jobs[0].wfrag);
   WeightJobsDev d;
-  uint64_t b1 = 0, b2 = 0;     // blocks so far in the two grids
+  int64_t b1 = 0, b2 = 0;     // blocks so far in the two grids
   for (int i = 0; i < n; ++i) {
-    const WeightJob &a = jobs[i];
-    if (!a.w || !a.wq_packed || !a.s_w || !a.part || a.K < 1 || a.N < 1) return AQT_ERR_INVALID_ARG;
-    if (a.wfrag && (a.N % kWCols != 0 || a.K % kWChunk != 0 || reinterpret_cast<uintptr_t>(a.wfrag) % 16 != 0))
-      return AQT_ERR_INVALID_ARG;
-    if (cdiv(a.N, kWCols) * cdiv(a.K, kWChunk) > 0x0FFFFFFF) return AQT_ERR_UNSUPPORTED;   // 8 of them stay under 2^31
-    if (a.mask_w) {
-      const int64_t words = cdiv(a.K * a.N, 32);
-      zero_words_kernel<<<grid_for(words, kThreads, 1024), kThreads, 0, st>>>(a.mask_w, words);
-      AQT_HIP(hipGetLastError());
-    }
-    int64_t slabs = cdiv(a.K, 32);
-    if (slabs > kWeightSlabs) slabs = kWeightSlabs;
-    const int64_t rows_per_slab = cdiv(a.K, slabs);
-    slabs = cdiv(a.K, rows_per_slab);
-    WeightJobDev &j = d.job[i];
-    j.w = a.w; j.K = a.K; j.N = a.N; j.rows_per_slab = rows_per_slab;
-    j.qmax = qmax_of(a.bits_w); j.packed = packed4(a.bits_w) ? 1 : 0; j.slabs = static_cast<int>(slabs);
-    j.vec4 = (a.N % 4 == 0) && (reinterpret_cast<uintptr_t>(a.w) % 16 == 0);
-    j.gx1 = static_cast<unsigned>(cdiv(a.N, 64));
-    j.gx2 = static_cast<unsigned>(cdiv(a.N, kWCols));
+    int64_t a1, a2;
+    AQT_TRY(weight_job(jobs[i], st, &d.job[i], &a1, &a2));
     d.first1[i] = static_cast<unsigned>(b1);
     d.first2[i] = static_cast<unsigned>(b2);
-    b1 += static_cast<uint64_t>(j.gx1) * static_cast<uint64_t>(slabs);
-    b2 += static_cast<uint64_t>(j.gx2) * static_cast<uint64_t>(cdiv(a.K, kWChunk));
-    j.part = a.part; j.wq_packed = static_cast<uint8_t *>(a.wq_packed); j.s_w = a.s_w; j.wq_kn = a.wq_kn;
-    j.mask_w = a.mask_w; j.wfrag = static_cast<uint4 *>(a.wfrag);
+    b1 += a1;
+    b2 += a2;
+    if (b1 > 0x7FFFFFFF || b2 > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
   }
   for (int i = n; i < kWeightJobsMax; ++i) d.job[i] = d.job[0];   // never selected: job_of_block stops at n
   for (int i = n; i <= kWeightJobsMax; ++i) {
@@ -623,7 +716,6 @@ aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream
     d.first2[i] = static_cast<unsigned>(b2);
   }
   d.n = n;
-  if (b1 > 0x7FFFFFFFu || b2 > 0x7FFFFFFFu) return AQT_ERR_UNSUPPORTED;
   wabsmax_partial_group_kernel<<<static_cast<unsigned>(b1), kThreads, 0, st>>>(d);
   AQT_HIP(hipGetLastError());
   quantize_weights_group_kernel<<<static_cast<unsigned>(b2), kThreads, 0, st>>>(d, dev_status);

@@ -360,3 +360,31 @@ def test_gradients_of_a_softmax_cost_at_most_a_second_plane():
     ws = B.workspace(B.aqt_workspace_bytes(B.AQT_OP_DENSE_BWD, M, K, N))
     t = [fastest(lambda: B.aqt_dense_bwd(dy, sv, 8, 8, dx=dx, dw=dw, ws=ws)) for dy in (plain, peaked)]
     assert t[1] <= 2.5 * t[0], t
+
+
+@pytest.mark.parametrize("M,K,N,bw", [(1, 1, 1, 8), (5, 64, 32, 4), (33, 70, 36, 8), (130, 2, 4, 4), (3, 517, 130, 4), (7, 1030, 8, 4),
+                                      (9, 63, 31, 8), (2100, 65, 68, 8)])
+@pytest.mark.parametrize("off", [0, 1])   # elements by which the weights and their [K,N] codes are off their alignment
+def test_layer_quantizers_in_one_launch_pair(M, K, N, bw, off):
+    import torch
+    print("[layer quantizers]", M, K, N, bw, off, flush=True)
+    c = inputs.small_case(23 + M + K + N, M, K, N, 8, bw, 0, with_bias=False, with_dy=False)
+    if N > 2:
+        c.w[:, 2] = 0
+    q_ref, s_ref = oracle.quantize(c.w, bw, 0)
+    x_ref, sx_ref = oracle.quantize(c.x, 8, -1)
+    w = torch.empty(K * N + off, device="cuda")[off:].view(K, N)
+    w.copy_(dev(c.w))
+    sv = B.Saved(M, K, N, bw)
+    sv.wq_kn = torch.empty(K * N + off, dtype=torch.int8, device="cuda")[off:].view(K, N)
+    B.aqt_dense_fwd(dev(c.x), w, 8, bw, saved=sv.refresh())
+    np.testing.assert_array_equal(host(sv.xq), x_ref)
+    np.testing.assert_array_equal(host(sv.s_x), sx_ref)
+    np.testing.assert_array_equal(host(sv.s_w), s_ref)
+    np.testing.assert_array_equal(host(sv.wq_kn), q_ref)
+    rows = oracle.pack_int4(q_ref) if bw <= 4 else q_ref.T.view(np.uint8)
+    np.testing.assert_array_equal(host(sv.wq_packed).reshape(N, -1), rows)
+    c.w[K // 2, N - 1] = np.inf   # one of the matrix's last channels, in neither first slab nor first tile
+    status = B.new_status()
+    B.aqt_dense_fwd(dev(c.x), dev(c.w), 8, bw, dev_status=status)
+    assert int(status.item()) == B.AQT_ERR_NONFINITE
