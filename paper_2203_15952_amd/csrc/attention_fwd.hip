@@ -10,8 +10,11 @@
 // Measured in us, before -> here: 32 utterances of 400 frames, 8 heads of 64: 172 -> 144; 128 of 512: 702 -> 619 (the float32
 // matrix instructions alone take 440 at the full clock; inside an encoder layer the matrix pipes are busy 58 % of the
 // kernel's cycles, profiles/encoder_layer_12800_tokens.txt); 24 of 417, 4 heads of 36: 84 -> 69.  Registers bound it to two
-// wavefronts per SIMD; at three (16 registers spilled) 150 and 653.  The backward's six-pass bf16 products would take
-// 88 here, but change last bits, and with them a code in every few thousand rows of the layers behind.
+// wavefronts per SIMD; at three (16 registers spilled) 150 and 653.  The backward's six-pass bf16 products, built in full
+// (three wavefronts per SIMD), take 90 and 401 and are closer to float64 (3.8e-7 of the result's norm against 4.7e-7), but they
+// change last bits, and with them a code in every few thousand rows of the layers behind: an int8 layer of 32 x 400
+// frames then differs by 1.2e-2 of its gradients' norm.
+// Small batches: attention_few.hip, the same bits.
 #include "attention_tiles.h"
 
 namespace aqt {
@@ -223,6 +226,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_fwd_rows_kernel(const f
 }  // namespace
 
 aqt_status launch_attention_rows(const float *qkv, const AttnShape &g, float *ctx, uint32_t *absmax, float *lse, hipStream_t st) {
+  if (attention_few_ok(g)) return launch_attention_few(qkv, g, ctx, absmax, lse, st);
   const unsigned blocks = static_cast<unsigned>(static_cast<int64_t>(g.qtiles) * g.heads * g.B);
   auto kern = g.dh <= 16   ? attention_fwd_rows_kernel<1>
               : g.dh <= 32 ? attention_fwd_rows_kernel<2>

@@ -356,3 +356,25 @@ def test_backward_with_values_beyond_bf16(what, dh, T, left, right):
     ref, mag = oracle.attention_bwd(qkv.reshape(2, T, 3 * D), go.reshape(2, T, D), heads, left, right)
     assert np.isfinite(got).all()
     check_grad(got, ref, mag, "dqkv")
+
+
+@pytest.mark.parametrize("T,left,right", [(1, -1, -1), (16, 3, 0), (40, 23, 0), (65, -1, 2), (217, 40, 33), (230, -1, -1)])
+@pytest.mark.parametrize("dh", [4, 20, 36, 64])
+def test_few_utterances_have_the_bits_of_many(T, left, right, dh):
+    """A small batch takes tiles of 16 queries, a large one of 128: every sum in the same order."""
+    say("few and many", T, left, right, dh)
+    heads = 2
+    D, many = heads * dh, 300
+    assert -(-T // 16) * heads * 2 <= 512 < -(-T // 16) * heads * many
+    qkv = np.random.default_rng(695 + T + dh).standard_normal((2 * T, 3 * D)).astype(F)
+    qkv[: T // 2] *= 6
+    few_d = dev(qkv)
+    many_d = few_d.view(1, 2 * T, 3 * D).expand(many // 2, -1, -1).contiguous().view(many * T, 3 * D)
+    got = []
+    for x, B_ in ((few_d, 2), (many_d, many)):
+        lse = torch.empty((B_ * T, heads), device="cuda")
+        ctx, m = B.aqt_attention_fwd(x, B_, T, heads, left=left, right=right, lse=lse, want_absmax=True)
+        got.append((host(ctx[-2 * T:]), host(lse[-2 * T:]), host(m)))
+    check_attention(got[0][0], qkv, 2, T, D, heads, left, right)
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
