@@ -8,6 +8,7 @@
 //     matrix cores, as a comparator for the native integer product,
 //   * per-layer precision policies and the feed-forward module as one call.
 #include "aqt_internal.h"
+#include "quant_code.h"
 
 namespace aqt {
 namespace {
@@ -182,13 +183,6 @@ __global__ __launch_bounds__(kThreads) void ln_stats_kernel(const float *__restr
   if (threadIdx.x == 0) partial[blockIdx.x] = max(max(sm[0], sm[1]), max(sm[2], sm[3]));
 }
 
-__device__ __forceinline__ int8_t ln_code(float v, float s, float fq) {
-  const float t = (s == 0.0f) ? 0.0f : v / s;
-  float r = floorf(t + 0.5f);
-  r = fminf(fmaxf(r, -fq), fq);
-  return static_cast<int8_t>(static_cast<int>(r));
-}
-
 // Pass 2: fold the block maxima into the scale (Fig. 2: max / qmax), recompute the normalised
 // values from x and the stored row statistics, quantize (divide, + 0.5, floor), write codes
 // and, when asked, the float32 values themselves.  NV as in ln_stats_kernel (NV > 0: 16-byte aligned x and y_out,
@@ -204,53 +198,65 @@ __global__ __launch_bounds__(kThreads) void ln_quantize_kernel(const float *__re
                                                                int32_t *dev_status) {
   __shared__ uint32_t sm[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  uint32_t mx = 0u;
-  for (int i = threadIdx.x; i < nparts; i += kThreads) mx = max(mx, partial[i]);
-  mx = wave_max_u(mx);
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 4;
+  int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + wave;
+  // the first row, its statistics, gamma and beta are on their way while the maxima are folded
+  v4f v[NV > 0 ? NV : 1], gm[NV > 0 ? NV : 1], bt[NV > 0 ? NV : 1];
+  float mean = 0.0f, rstd = 0.0f;
+  auto load = [&](int64_t row) {
+    if constexpr (NV > 0) load_row<NV>(x + row * D, D, lane, v);
+    mean = stats[2 * row];
+    rstd = stats[2 * row + 1];
+  };
+  if (m < M) load(m);
+  if constexpr (NV > 0) {
+    if (gamma) load_affine_row<NV>(gamma, D, lane, gm);
+    if (beta) load_affine_row<NV>(beta, D, lane, bt);
+  }
+  uint32_t mx = wave_max_u(words_max<kThreads>(partial, nparts));
   if (lane == 0) sm[wave] = mx;
   __syncthreads();
   mx = max(max(sm[0], sm[1]), max(sm[2], sm[3]));
   const float fq = static_cast<float>(qmax);
   const float s = __uint_as_float(mx) / fq;
+  const Quantizer qz = quantizer(s, fq);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (scale) scale[0] = s;
     if (mx >= 0x7F800000u && dev_status) *dev_status = AQT_ERR_NONFINITE;
   }
-  v4f gm[NV > 0 ? NV : 1], bt[NV > 0 ? NV : 1];
-  if constexpr (NV > 0) {
-    if (gamma) load_affine_row<NV>(gamma, D, lane, gm);
-    if (beta) load_affine_row<NV>(beta, D, lane, bt);
-  }
-  for (int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + wave; m < M; m += static_cast<int64_t>(gridDim.x) * 4) {
+  while (m < M) {
     const float *row = x + m * D;
-    const float mean = stats[2 * m], rstd = stats[2 * m + 1];
+    const float mu = mean, rs = rstd;
     auto put = [&](int64_t c, v4f xv, v4f g, v4f b) {
-      const v4f y = ln_value4(xv, mean, rstd, gamma != nullptr, beta != nullptr, g, b);
+      const v4f y = ln_value4(xv, mu, rs, gamma != nullptr, beta != nullptr, g, b);
       if (y_out) *reinterpret_cast<v4f *>(y_out + m * D + c) = y;
-      if (q) {
-        const uint32_t b0 = static_cast<uint8_t>(ln_code(y.x, s, fq)), b1 = static_cast<uint8_t>(ln_code(y.y, s, fq));
-        const uint32_t b2 = static_cast<uint8_t>(ln_code(y.z, s, fq)), b3 = static_cast<uint8_t>(ln_code(y.w, s, fq));
-        *reinterpret_cast<uint32_t *>(q + m * D + c) = b0 | (b1 << 8) | (b2 << 16) | (b3 << 24);
-      }
+      if (q) *reinterpret_cast<uint32_t *>(q + m * D + c) = quant4(y.x, y.y, y.z, y.w, qz);
     };
+    const int64_t next = m + stride;
     if constexpr (NV > 0) {
-      v4f v[NV];
-      load_row<NV>(row, D, lane, v);
+      v4f now[NV];
+#pragma unroll
+      for (int k = 0; k < NV; ++k) now[k] = v[k];
+      if (next < M) load(next);
 #pragma unroll
       for (int k = 0; k < NV; ++k)
-        if (4 * (lane + 64 * k) < D) put(4 * (lane + 64 * k), v[k], gm[k], bt[k]);
-    } else if constexpr (NV < 0) {
-      for (int64_t c = 4 * lane; c < D; c += 256) {
-        const v4f one = {1.0f, 1.0f, 1.0f, 1.0f};
-        put(c, *reinterpret_cast<const v4f *>(row + c), gamma ? load_affine(gamma, c) : one, beta ? load_affine(beta, c) : one);
-      }
+        if (4 * (lane + 64 * k) < D) put(4 * (lane + 64 * k), now[k], gm[k], bt[k]);
     } else {
-      for (int64_t c = lane; c < D; c += 64) {
-        const float v = ln_value(row[c], mean, rstd, gamma, beta, c);
-        if (y_out) y_out[m * D + c] = v;
-        if (q) q[m * D + c] = ln_code(v, s, fq);
+      if constexpr (NV < 0) {
+        for (int64_t c = 4 * lane; c < D; c += 256) {
+          const v4f one = {1.0f, 1.0f, 1.0f, 1.0f};
+          put(c, *reinterpret_cast<const v4f *>(row + c), gamma ? load_affine(gamma, c) : one, beta ? load_affine(beta, c) : one);
+        }
+      } else {
+        for (int64_t c = lane; c < D; c += 64) {
+          const float y = ln_value(row[c], mu, rs, gamma, beta, c);
+          if (y_out) y_out[m * D + c] = y;
+          if (q) q[m * D + c] = static_cast<int8_t>(static_cast<int>(quant_floor(y, s, fq)));
+        }
       }
+      if (next < M) load(next);
     }
+    m = next;
   }
 }
 
@@ -551,7 +557,8 @@ aqt_status launch_layernorm_quantize(const float *x, int64_t M, int64_t D, const
   float *stats = row_stats ? row_stats
                            : reinterpret_cast<float *>(static_cast<uint8_t *>(ws) +
                                                        align_up(kMaxPartials * sizeof(uint32_t), 256));
-  const int g = grid_cap(M, 4, 2048);
+  int g = grid_cap(M, 4, 2048);
+  g = static_cast<int>(cdiv(M, 4 * cdiv(M, 4 * static_cast<int64_t>(g))));   // as many rows for every wavefront
   const bool vec = (D % 4 == 0) && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                    (!y_out || reinterpret_cast<uintptr_t>(y_out) % 16 == 0) &&
                    (!q || reinterpret_cast<uintptr_t>(q) % 4 == 0) &&

@@ -8,6 +8,7 @@
 // walks the tensor backwards, so what the first pass touched last is read first)
 // and writes one byte per element.
 #include "aqt_internal.h"
+#include "quant_code.h"
 
 namespace aqt {
 namespace {
@@ -101,46 +102,56 @@ __global__ __launch_bounds__(kThreads) void absmax_flat_kernel(const float *__re
   absmax_flat_body<STREAM>(x, n, per4, partial, blockIdx.x);
 }
 
-__device__ __forceinline__ uint32_t pack4(float4 v, float s, float fq) {
-  uint32_t c0 = static_cast<uint32_t>(quant_code(v.x, s, fq)) & 0xFFu;
-  uint32_t c1 = static_cast<uint32_t>(quant_code(v.y, s, fq)) & 0xFFu;
-  uint32_t c2 = static_cast<uint32_t>(quant_code(v.z, s, fq)) & 0xFFu;
-  uint32_t c3 = static_cast<uint32_t>(quant_code(v.w, s, fq)) & 0xFFu;
-  return c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
-}
+__device__ __forceinline__ uint32_t pack4(float4 v, const Quantizer &k) { return quant4(v.x, v.y, v.z, v.w, k); }
 
 // ---- per-tensor, contiguous: pass 2 -------------------------------------------
 // Same block -> run mapping as pass 1, but blocks are visited in reverse so that
-// the part of the tensor pass 1 touched last is read first.
+// the part of the tensor pass 1 touched last is read first.  A block's first loads are requested before the maxima are
+// folded, and each group of four before the group in front of it is packed.
 __device__ __forceinline__ void quantize_flat_body(
     const float *__restrict__ x, int64_t n, int64_t per4, const uint32_t *__restrict__ partial, int nparts,
     int qmax, int8_t *__restrict__ q, float *__restrict__ scale, int32_t *dev_status, unsigned block, unsigned blocks) {
   __shared__ uint32_t sm[4];
-  uint32_t m = 0;
-  for (int i = threadIdx.x; i < nparts; i += kThreads) m = max(m, partial[i]);
-  m = block_max(m, sm);
+  const int64_t n4 = n >> 2;
+  const float4 *x4 = reinterpret_cast<const float4 *>(x);
+  uint32_t *q4 = reinterpret_cast<uint32_t *>(q);
+  const int64_t blk = static_cast<int64_t>(blocks) - 1 - block;
+  int64_t i0 = blk * per4;   // uniform
+  const int64_t i1 = min(n4, i0 + per4);
+  struct Four {
+    float4 v[4];
+  };
+  auto load = [&](int64_t at) {
+    Four f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f.v[u] = load_stream(x4 + at + u * kThreads + threadIdx.x);
+    return f;
+  };
+  const bool whole = i0 + 4 * kThreads <= i1;
+  Four now;
+  if (whole) now = load(i0);
+  const uint32_t m = block_max(words_max<kThreads>(partial, nparts), sm);
   const float fq = static_cast<float>(qmax);
   const float s = __uint_as_float(m) / fq;
   if (block == 0 && threadIdx.x == 0) {
     scale[0] = s;
     if (m >= 0x7F800000u && dev_status) *dev_status = AQT_ERR_NONFINITE;
   }
-  const int64_t n4 = n >> 2;
-  const float4 *x4 = reinterpret_cast<const float4 *>(x);
-  uint32_t *q4 = reinterpret_cast<uint32_t *>(q);
-  const int64_t blk = static_cast<int64_t>(blocks) - 1 - block;
-  const int64_t i0 = blk * per4;
-  const int64_t i1 = min(n4, i0 + per4);
-  int64_t i = i0 + threadIdx.x;
-  for (; i + 3 * kThreads < i1; i += 4 * kThreads) {
-    const float4 a = load_stream(x4 + i), b = load_stream(x4 + i + kThreads);
-    const float4 c = load_stream(x4 + i + 2 * kThreads), d = load_stream(x4 + i + 3 * kThreads);
-    store_stream(q4 + i, pack4(a, s, fq));
-    store_stream(q4 + i + kThreads, pack4(b, s, fq));
-    store_stream(q4 + i + 2 * kThreads, pack4(c, s, fq));
-    store_stream(q4 + i + 3 * kThreads, pack4(d, s, fq));
+  const Quantizer k = quantizer(s, fq);
+  auto store = [&](int64_t at, const Four &f) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) store_stream(q4 + at + u * kThreads + threadIdx.x, pack4(f.v[u], k));
+  };
+  if (whole) {
+    for (; i0 + 8 * kThreads <= i1; i0 += 4 * kThreads) {
+      const Four next = load(i0 + 4 * kThreads);
+      store(i0, now);
+      now = next;
+    }
+    store(i0, now);
+    i0 += 4 * kThreads;
   }
-  for (; i < i1; i += kThreads) store_stream(q4 + i, pack4(load_stream(x4 + i), s, fq));
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) store_stream(q4 + i, pack4(load_stream(x4 + i), k));
   if (block == 0)
     for (int64_t j = (n4 << 2) + threadIdx.x; j < n; j += kThreads) q[j] = static_cast<int8_t>(quant_code(x[j], s, fq));
 }
@@ -564,7 +575,8 @@ int grid_for(int64_t work_items, int per_block, int cap) {
 // up to 4096 blocks = 16 per CU, each on its own contiguous run of the tensor; every thread keeps four 16-byte loads in flight.
 int flat_blocks(int64_t n, int64_t *per4) {
   const int g = grid_for(n / 4, kThreads * 4, kMaxPartials);
-  *per4 = cdiv(cdiv(n / 4, g), kThreads) * kThreads;
+  const int64_t even = cdiv(n / 4, g), unit = even > 4 * kThreads ? 4 * kThreads : kThreads;   // whole groups of four loads
+  *per4 = cdiv(even, unit) * unit;
   const int64_t used = *per4 > 0 ? cdiv(n / 4, *per4) : 1;
   return static_cast<int>(used < 1 ? 1 : used);
 }

@@ -580,6 +580,35 @@ WONLY_CASES = [
 ]
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("top", [1.0, 3.7e-3, 2.0 ** -59, 2.0 ** -62, 2.0 ** 66, 1e-42, 3.0e38])
+def test_codes_next_to_every_rounding_line(bits, top):
+    """Values on and up to four units in the last place to either side of every line between two codes, with scales inside
+    and outside of the range where the quantizer multiplies by a reciprocal, and a largest value below the tensor's."""
+    say("rounding lines", bits, top)
+    qmax = 2 ** (bits - 1) - 1
+    s = np.float32(top) / np.float32(qmax)
+    lines = ((np.arange(-qmax - 1, qmax + 1) + 0.5) * np.float64(s)).astype(np.float32)
+    x = np.concatenate([lines, np.float32([top, -top, 0.0, -0.0])])
+    for way in (np.float32(np.inf), np.float32(-np.inf)):
+        v = lines
+        for _ in range(4):
+            v = np.nextafter(v, way)
+            x = np.concatenate([x, v])
+    x = np.clip(x, -np.float32(top), np.float32(top))
+    x = np.resize(x, (9, 1100)).astype(np.float32)      # several groups of loads in a block, and a remainder
+    q_ref, s_ref = oracle.quantize(x, bits, oracle.AXIS_ALL)
+    q, sc, _ = B.aqt_quantize(dev(x), bits, B.AQT_AXIS_ALL)
+    np.testing.assert_array_equal(host(sc), s_ref)
+    np.testing.assert_array_equal(host(q), q_ref)
+    m = np.float32([top])
+    q1, s1, _ = B.aqt_quantize_with_absmax(dev(x), bits, dev(m))
+    np.testing.assert_array_equal(host(q1), q_ref)
+    small = np.float32([np.float32(top) * np.float32(0.37)])
+    q2, s2, _ = B.aqt_quantize_with_absmax(dev(x), bits, dev(small))
+    np.testing.assert_array_equal(host(q2), oracle.quantize_with_scale(x, bits, oracle.AXIS_ALL, host(s2))[0])
+
+
 @pytest.mark.parametrize("M,K,N,bw,epi,with_bias", WONLY_CASES)
 def test_dense_fwd_weight_only_against_oracle(M, K, N, bw, epi, with_bias):
     say("dense fwd weight-only", M, K, N, bw, epi, with_bias)
