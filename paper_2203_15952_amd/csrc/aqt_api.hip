@@ -140,7 +140,8 @@ MhsaBwdWorkspace carve_mhsa_bwd(void *ws, int64_t M, int64_t D, int heads) {
 struct LayerBwdWorkspace {
   size_t module;
   float *da, *db, *dm;
-  void *ln;
+  void *ln[kLnFoldsMax];   // the partial sums of each normalisation, which one launch folds at the end
+  size_t one_ln;           // bytes with the first of them only: enough to fold each before the next
   size_t total;
 };
 
@@ -163,7 +164,10 @@ LayerBwdWorkspace carve_layer_bwd(void *ws, int64_t M, int64_t D, int64_t H, int
   f.da = reinterpret_cast<float *>(take(md));
   f.db = reinterpret_cast<float *>(take(md));
   f.dm = reinterpret_cast<float *>(take(md));
-  f.ln = take(layernorm_bwd_ws_bytes(D));
+  for (int i = 0; i < kLnFoldsMax; ++i) {
+    f.ln[i] = take(layernorm_bwd_ws_bytes(D));
+    if (i == 0) f.one_ln = off;
+  }
   f.total = off;
   return f;
 }
@@ -1011,8 +1015,15 @@ aqt_status aqt_conformer_layer_bwd(const float *dy, const float *x, const aqt_co
     return AQT_ERR_UNSUPPORTED;
   const int64_t M = g.B * g.T;
   LayerBwdWorkspace f = carve_layer_bwd(ws, M, g.D, g.H, g.heads, g.kw);
-  if (!ws || ws_bytes < f.total) return AQT_ERR_WORKSPACE;
+  if (!ws || ws_bytes < f.one_ln) return AQT_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  LnFold folds[kLnFoldsMax] = {};
+  const bool defer = ws_bytes >= f.total;
+  auto ln_bwd = [&](int i, const float *in, const float *stats, const float *gamma, const float *d, const float *add, float *out,
+                    float *dgamma, float *dbeta, float *half) {
+    return launch_layernorm_bwd(in, stats, gamma, d, add, M, g.D, out, dgamma, dbeta, f.ln[defer ? i : 0], st, half,
+                                defer ? &folds[i] : nullptr);
+  };
   const aqt_dense_policy pf1[2] = {policy->ffn1_in, policy->ffn1_out}, pa[2] = {policy->attn_qkv, policy->attn_out};
   const aqt_dense_policy pc[2] = {policy->conv_pw1, policy->conv_pw2}, pf2[2] = {policy->ffn2_in, policy->ffn2_out};
   // the modules' own checks, before the first launch (f.dm, f.da, f.db stand for the gradients they will be given)
@@ -1023,29 +1034,25 @@ aqt_status aqt_conformer_layer_bwd(const float *dy, const float *x, const aqt_co
                          f.module));
   AQT_TRY(ffn_bwd_check(f.dm, &saved->ffn1, M, g.D, g.H, pf1, f.dm, grads->ffn1_w1, grads->ffn1_w2, ws, f.module));
   // final normalisation: gradient of the residual stream r4
-  AQT_TRY(launch_layernorm_bwd(saved->r4, saved->out_row_stats, w->out_ln_g, dy, nullptr, M, g.D, f.da, grads->out_ln_g,
-                               grads->out_ln_b, f.ln, st, f.dm));
+  AQT_TRY(ln_bwd(0, saved->r4, saved->out_row_stats, w->out_ln_g, dy, nullptr, f.da, grads->out_ln_g, grads->out_ln_b, f.dm));
   // second feed-forward module entered the stream with weight 1/2: r4 = r3 + ffn(r3) / 2
   AQT_TRY(aqt_ffn_bwd(f.dm, &saved->ffn2, M, g.D, g.H, pf2, f.dm, grads->ffn2_w1, grads->ffn2_b1, grads->ffn2_w2,
                       grads->ffn2_b2, ws, f.module, stream));
-  AQT_TRY(launch_layernorm_bwd(saved->r3, saved->ffn2.row_stats, w->ffn2_ln_g, f.dm, f.da, M, g.D, f.db,
-                               grads->ffn2_ln_g, grads->ffn2_ln_b, f.ln, st));
+  AQT_TRY(ln_bwd(1, saved->r3, saved->ffn2.row_stats, w->ffn2_ln_g, f.dm, f.da, f.db, grads->ffn2_ln_g, grads->ffn2_ln_b, nullptr));
   // convolution module: r3 = r2 + conv(r2)
   AQT_TRY(aqt_conv_module_bwd(f.db, &saved->conv, w->conv_wdw, g.B, g.T, g.D, g.kw, g.pad_left, pc, f.dm,
                               grads->conv_w1, grads->conv_b1, grads->conv_wdw, grads->conv_bdw, grads->conv_w2,
                               grads->conv_b2, ws, f.module, stream));
-  AQT_TRY(launch_layernorm_bwd(saved->r2, saved->conv.row_stats, w->conv_ln_g, f.dm, f.db, M, g.D, f.da,
-                               grads->conv_ln_g, grads->conv_ln_b, f.ln, st));
+  AQT_TRY(ln_bwd(2, saved->r2, saved->conv.row_stats, w->conv_ln_g, f.dm, f.db, f.da, grads->conv_ln_g, grads->conv_ln_b, nullptr));
   // self-attention module: r2 = r1 + mhsa(r1)
   AQT_TRY(aqt_mhsa_bwd(f.da, &saved->att, g.B, g.T, g.D, g.heads, g.left_context, g.right_context, pa, f.dm,
                        grads->att_wqkv, grads->att_bqkv, grads->att_wo, grads->att_bo, ws, f.module, stream));
-  AQT_TRY(launch_layernorm_bwd(saved->r1, saved->att.row_stats, w->att_ln_g, f.dm, f.da, M, g.D, f.db,
-                               grads->att_ln_g, grads->att_ln_b, f.ln, st, f.dm));
+  AQT_TRY(ln_bwd(3, saved->r1, saved->att.row_stats, w->att_ln_g, f.dm, f.da, f.db, grads->att_ln_g, grads->att_ln_b, f.dm));
   // first feed-forward module: r1 = x + ffn(x) / 2
   AQT_TRY(aqt_ffn_bwd(f.dm, &saved->ffn1, M, g.D, g.H, pf1, f.dm, grads->ffn1_w1, grads->ffn1_b1, grads->ffn1_w2,
                       grads->ffn1_b2, ws, f.module, stream));
-  return launch_layernorm_bwd(x, saved->ffn1.row_stats, w->ffn1_ln_g, f.dm, f.db, M, g.D, dx, grads->ffn1_ln_g,
-                              grads->ffn1_ln_b, f.ln, st);
+  AQT_TRY(ln_bwd(4, x, saved->ffn1.row_stats, w->ffn1_ln_g, f.dm, f.db, dx, grads->ffn1_ln_g, grads->ffn1_ln_b, nullptr));
+  return launch_ln_folds(folds, defer ? kLnFoldsMax : 0, g.D, st);
 }
 
 }  // extern "C"

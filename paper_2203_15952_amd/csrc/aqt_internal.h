@@ -172,9 +172,18 @@ aqt_status launch_layernorm_quantize(const float *x, int64_t M, int64_t D, const
                                      void *ws, hipStream_t st, int32_t *dev_status, const float *res = nullptr,
                                      float alpha = 0.0f, float *sum_out = nullptr, uint32_t *zero_word = nullptr);
 size_t layernorm_bwd_ws_bytes(int64_t D);
+// The column sums of a normalisation's backward, left to be folded (its workspace has to last until then).
+struct LnFold {
+  const float *part;
+  float *dgamma, *dbeta;   // nullable
+  int parts;
+};
+constexpr int kLnFoldsMax = 5;
+aqt_status launch_ln_folds(const LnFold *jobs, int n, int64_t D, hipStream_t st);
+// later (optional): the fold is not launched, but described there
 aqt_status launch_layernorm_bwd(const float *x, const float *stats, const float *gamma, const float *dy,
                                 const float *add, int64_t M, int64_t D, float *dx, float *dgamma, float *dbeta,
-                                void *ws, hipStream_t st, float *half = nullptr);
+                                void *ws, hipStream_t st, float *half = nullptr, LnFold *later = nullptr);
 aqt_status launch_scale(const float *m, float alpha, float *out, int64_t n, hipStream_t st);
 aqt_status launch_dact_mul(const float *dout, const float *dact, int64_t M, int64_t N, int64_t oc, float *dv,
                            hipStream_t st);

@@ -385,13 +385,20 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_colsum_kernel(const float *__
 }
 
 // Column sums of the partials: 64 columns per workgroup, its sixteen wavefronts share the partials (eight loads in
-// flight each) and are added up in order; blockIdx.y: the gamma or the beta sums.  (Two workgroups walking all 512
-// partials one after the other took 45 us.)
+// flight each) and are added up in order; blockIdx.y: the gamma or the beta sums, blockIdx.z: which normalisation's.  (Two
+// workgroups walking all 512 partials one after the other took 45 us.)  An encoder layer folds its five in one launch at the end:
+// nothing else waits for them, and a launch takes 4 - 5 us of its own (1024 tokens of width 256, layer forward and backward 336 ->
+// 323 us).
 constexpr int kFoldWaves = 16;
-__global__ __launch_bounds__(64 * kFoldWaves) void ln_bwd_fold_kernel(const float *__restrict__ part, int P, int64_t D,
-                                                                      float *__restrict__ dgamma, float *__restrict__ dbeta) {
-  float *const out = blockIdx.y ? dbeta : dgamma;
+struct LnFoldsDev {
+  LnFold job[kLnFoldsMax];
+};
+__global__ __launch_bounds__(64 * kFoldWaves) void ln_bwd_fold_kernel(const LnFoldsDev jobs, int64_t D) {
+  const LnFold &f = jobs.job[blockIdx.z];
+  float *const out = blockIdx.y ? f.dbeta : f.dgamma;
   if (!out) return;
+  const float *const part = f.part;
+  const int P = f.parts;
   __shared__ float sm[kFoldWaves][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + lane, cc = c < D ? c : D - 1;
@@ -583,9 +590,20 @@ size_t layernorm_bwd_ws_bytes(int64_t D) {
   return align_up(static_cast<size_t>(kLnBwdBlocks) * 2 * D * sizeof(float), 256);
 }
 
+aqt_status launch_ln_folds(const LnFold *jobs, int n, int64_t D, hipStream_t st) {
+  LnFoldsDev f{};
+  int used = 0;
+  for (int i = 0; i < n; ++i)
+    if (jobs[i].dgamma || jobs[i].dbeta) f.job[used++] = jobs[i];
+  if (!used) return AQT_OK;
+  ln_bwd_fold_kernel<<<dim3(static_cast<unsigned>(cdiv(D, 64)), 2, static_cast<unsigned>(used)), 64 * kFoldWaves, 0, st>>>(f, D);
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
 aqt_status launch_layernorm_bwd(const float *x, const float *stats, const float *gamma, const float *dy,
                                 const float *add, int64_t M, int64_t D, float *dx, float *dgamma, float *dbeta,
-                                void *ws, hipStream_t st, float *half) {
+                                void *ws, hipStream_t st, float *half, LnFold *later) {
   const bool want_cols = dgamma || dbeta;
   float *part = want_cols ? static_cast<float *>(ws) : nullptr;
   const bool vec = (D % 4 == 0) && D <= 1024 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
@@ -608,10 +626,9 @@ aqt_status launch_layernorm_bwd(const float *x, const float *stats, const float 
     }
   }
   AQT_HIP(hipGetLastError());
-  if (want_cols) {
-    ln_bwd_fold_kernel<<<dim3(static_cast<unsigned>(cdiv(D, 64)), 2), 64 * kFoldWaves, 0, st>>>(part, P, D, dgamma, dbeta);
-    AQT_HIP(hipGetLastError());
-  }
+  const LnFold fold{part, dgamma, dbeta, P};
+  if (later) *later = fold;
+  else if (want_cols) AQT_TRY(launch_ln_folds(&fold, 1, D, st));
   return half && !vec ? launch_scale(dx, 0.5f, half, M * D, st) : AQT_OK;   // after the column sums: half may be dy
 }
 

@@ -288,6 +288,27 @@ def test_conformer_layer_backward_halves_the_stream_gradient(D, heads):
         np.testing.assert_array_equal(host(got), host(ref))
 
 
+def test_conformer_layer_backward_in_a_workspace_that_folds_each_normalisation():
+    """Room for the column sums of one normalisation only: each is folded before the next, the same bits; less is refused."""
+    B_, T, D, H, heads, kw, pl = 2, 33, 64, 256, 4, 5, 2
+    M = B_ * T
+    say("encoder layer bwd, small workspace")
+    wd = {k: dev(v) for k, v in layer_weights(842, D, H, kw).items()}
+    rng = np.random.default_rng(843)
+    x_d, dy_d = (dev(rng.standard_normal((M, D)).astype(F)) for _ in range(2))
+    _, sv = run_layer(x_d, wd, B.aqt_policy_preset(B.AQT_POLICY_ALL, 1, 0, 8, 8)[0], B_, T, D, H, heads, kw, pl, -1, -1)
+    need = B.aqt_workspace_bytes(B.AQT_OP_CONFORMER_LAYER_BWD, M, D, H)
+    spare = B.aqt_workspace_bytes(B.AQT_OP_CONFORMER_LAYER_BWD, M, D, H) - 4 * B.aqt_workspace_bytes(B.AQT_OP_LAYERNORM_BWD, M, D, 1)
+    shape = dict(B=B_, T=T, H=H, heads=heads, kw=kw, pad_left=pl, left=-1, right=-1)
+    got = [B.aqt_conformer_layer_bwd(dy_d, x_d, wd, sv, ws=B.workspace(n), **shape) for n in (need, spare)]
+    np.testing.assert_array_equal(host(got[0][0]), host(got[1][0]))
+    for k in got[0][1]:
+        if got[0][1][k] is not None:
+            np.testing.assert_array_equal(host(got[0][1][k]), host(got[1][1][k]), err_msg=k)
+    with pytest.raises(B.AqtError):
+        B.aqt_conformer_layer_bwd(dy_d, x_d, wd, sv, ws=B.workspace(need // 8), **shape)
+
+
 def test_conformer_layer_backward_equals_its_modules_and_tracks_the_float_gradient():
     B_, T, D, H, heads, kw, pl, left, right = 4, 150, 256, 1024, 4, 15, 14, 23, 0
     M = B_ * T
