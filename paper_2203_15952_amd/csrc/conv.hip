@@ -134,8 +134,9 @@ __device__ __forceinline__ void put_frames(float *__restrict__ xs, const Frames<
 // GATE, with gate [B T, 2 C] (and neither na, nb, swish, dfac nor absmax) out is [B T, 2 C]: the sum times the frame's two halves of the gate,
 // the gradient through the gated unit in front of the layer (65536 x 512,
 // 32 taps: 79 us and 126 for a pass of its own, 147 in one).
-// Dynamic LDS: (kTile + 2 kw - 1) * 256 bytes.
-template <bool GATE = false>
+// GROUPS: groups of eight frames a wavefront takes in turn, 32 GROUPS frames to a workgroup.
+// Dynamic LDS: (32 GROUPS + 2 kw - 1) * 256 bytes.
+template <bool GATE = false, int GROUPS = kTile / 32>
 __global__ __launch_bounds__(kThreads) void dwconv_kernel(const float *__restrict__ xin, const float *__restrict__ xmul,
                                                           const float *__restrict__ w, const float *__restrict__ bias,
                                                           const float *__restrict__ na, const float *__restrict__ nb,
@@ -143,8 +144,9 @@ __global__ __launch_bounds__(kThreads) void dwconv_kernel(const float *__restric
                                                           float *__restrict__ out, float *__restrict__ dfac,
                                                           uint32_t *__restrict__ absmax,
                                                           const float *__restrict__ gate = nullptr) {
+  constexpr int kFrames = 32 * GROUPS;
   extern __shared__ float lds[];
-  const int rows = kTile + g.kw - 1;
+  const int rows = kFrames + g.kw - 1;
   float *xs = lds;               // [rows][64]
   float *ws = lds + rows * 64;   // [kw][64]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -154,11 +156,12 @@ __global__ __launch_bounds__(kThreads) void dwconv_kernel(const float *__restric
   const int tg = static_cast<int>(id % g.tgroups);
   const int64_t b = id / g.tgroups;
   const int64_t c = static_cast<int64_t>(cg) * 64 + lane;
-  const int64_t t0 = static_cast<int64_t>(tg) * kTile;
+  const int64_t t0 = static_cast<int64_t>(tg) * kFrames;
   if (quads_ok(g, xin, xmul, w)) {
     const int64_t c0 = static_cast<int64_t>(cg) * 64, cq = c0 + 4 * (threadIdx.x & 15), cc = cq < g.C ? cq : g.C - 4;
-    static_assert(kTile + kTapsMax - 1 <= 6 * 16 && kTapsMax <= 2 * 16);
-    Frames<6> f;
+    constexpr int kPieces = (kFrames + kTapsMax + 14) / 16;
+    static_assert(kTapsMax <= 2 * 16);
+    Frames<kPieces> f;
     load_frames(f, rows, xin, xmul, g, b, t0, pl, c0);
     v4f taps[2];
 #pragma unroll
@@ -182,8 +185,8 @@ __global__ __launch_bounds__(kThreads) void dwconv_kernel(const float *__restric
   if (c < g.C) {
     const float b0 = bias ? bias[c] : 0.0f;
     const float a = na ? na[c] : 1.0f, sh = nb ? nb[c] : 0.0f;
-    for (int grp = 0; grp < 2; ++grp) {
-      const int tl = wave * 16 + grp * 8;
+    for (int grp = 0; grp < GROUPS; ++grp) {
+      const int tl = (wave * GROUPS + grp) * 8;
       if (t0 + tl >= g.T) break;
       const float *const xr = xs + tl * 64 + lane, *const wr = ws + lane;
       const int64_t first = (b * g.T + t0 + tl) * g.C + c, at2 = 2 * first - c;   // at2: in frames of 2 C
@@ -484,10 +487,16 @@ aqt_status launch_corr(bool rev, const float *xin, const float *xmul, const floa
   const int pl = rev ? g.kw - 1 - g.pad_left : g.pad_left;
   if (absmax && !absmax_is_zero) zero_absmax_kernel<<<1, 64, 0, st>>>(absmax);
   if (corr_staged(g)) {
-    const size_t lds = static_cast<size_t>(kTile + 2 * g.kw - 1) * 64 * sizeof(float);
-    const int64_t blocks = static_cast<int64_t>(g.cgroups) * g.tgroups * g.B;
-    auto kern = gate ? dwconv_kernel<true> : dwconv_kernel<false>;
-    kern<<<static_cast<unsigned>(blocks), kThreads, lds, st>>>(xin, xmul, w, bias, na, nb, swish, rev ? 1 : 0, g, pl, out, dfac,
+    int64_t blocks = static_cast<int64_t>(g.cgroups) * g.tgroups * g.B;
+    // Fewer workgroups than compute units: tiles of half the frames, so that a wavefront is done after one group.
+    const bool half = blocks < 256;
+    ConvGeom gt = g;
+    if (half) gt.tgroups = static_cast<int>(cdiv(g.T, kTile / 2));
+    blocks = static_cast<int64_t>(gt.cgroups) * gt.tgroups * gt.B;
+    const size_t lds = static_cast<size_t>((half ? kTile / 2 : kTile) + 2 * g.kw - 1) * 64 * sizeof(float);
+    auto kern = half ? (gate ? dwconv_kernel<true, kTile / 64> : dwconv_kernel<false, kTile / 64>)
+                     : (gate ? dwconv_kernel<true> : dwconv_kernel<false>);
+    kern<<<static_cast<unsigned>(blocks), kThreads, lds, st>>>(xin, xmul, w, bias, na, nb, swish, rev ? 1 : 0, gt, pl, out, dfac,
                                                                absmax, gate);
   } else {
     int64_t grid = cdiv(g.B * g.T * g.C, kThreads);

@@ -299,3 +299,25 @@ def test_conv_module_rejects_float_activations():
     with pytest.raises(B.AqtError) as e:
         B.aqt_conv_module_fwd(z, w1, None, wd, None, w2, None, sv, pad_left=14)
     assert e.value.status == B.AQT_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("T,kw,pad_left", [(1, 1, 0), (8, 15, 14), (31, 32, 15), (33, 32, 31), (64, 3, 1), (97, 15, 7)])
+def test_few_utterances_have_the_bits_of_many(T, kw, pad_left):
+    """A small batch takes tiles of 32 frames, a large one of 64: the taps of an output in the same order, forward and backward."""
+    C, many = 72, 600
+    assert -(-C // 64) * -(-T // 64) * 2 < 256 <= -(-C // 64) * -(-T // 64) * many
+    rng = np.random.default_rng(870 + T)
+    x, dout = (rng.standard_normal((2 * T, C)).astype(np.float32) for _ in range(2))
+    w, b = rng.standard_normal((kw, C)).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+
+    def batch(a, B_):
+        return torch.from_numpy(a).cuda().view(1, 2, T, C).expand(B_ // 2, -1, -1, -1).contiguous().view(B_, T, C)
+
+    wd, bd = torch.from_numpy(w).cuda(), torch.from_numpy(b).cuda()
+    got = []
+    for B_ in (2, many):
+        y, _, _ = B.aqt_depthwise_conv_fwd(batch(x, B_), wd, bias=bd, pad_left=pad_left)
+        dx, _, _ = B.aqt_depthwise_conv_bwd(batch(dout, B_), batch(x, B_), wd, pad_left=pad_left)
+        got.append([t[-2:].cpu().numpy() for t in (y, dx)])
+    for a, c in zip(*got):
+        np.testing.assert_array_equal(a, c)
