@@ -250,6 +250,19 @@ LayerFwdWorkspace carve_layer_fwd(void *ws, int64_t M, int64_t D, int64_t H) {
   return f;
 }
 
+// The second dense layer of a module: one-pass quantizer, product.  A small problem's product makes the codes itself (it
+// reads the weights in their canonical form either way).
+aqt_status quantized_layer(const float *x, const uint32_t *absmax, const aqt_saved &l, const aqt_dense_policy &p, int64_t M, int64_t K,
+                           int64_t N, const float *bias, float *y, const WeightSide &side, hipStream_t st, int32_t *dev_status) {
+  if (dense_fwd_rows_ok(M, K, N) && !fwd_q_uses_fragments(M, K, N, AQT_EPI_NONE) && !l.mask_x &&
+      reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(l.xq) % 4 == 0)
+    return launch_dense_fwd_rows(RowSource{x, absmax, qmax_of(p.bits_x), l.xq, l.s_x, dev_status}, l.wq_packed, l.s_w, M, K, N, p.bits_w,
+                                 bias, y, st);
+  AQT_TRY(launch_quantize_with_absmax(x, M, K, K, p.bits_x, absmax, l.xq, l.s_x, l.mask_x, st, dev_status));
+  return launch_dense_fwd_q(l.xq, l.s_x, l.wq_packed, l.s_w, M, K, N, p.bits_w, bias, AQT_EPI_NONE, y, nullptr, nullptr,
+                            side.operand, st, nullptr, side.prepared);
+}
+
 // The int32 accumulator must hold K * qmax_x * qmax_w; packed (<= 4 bit) weights enter the
 // matrix cores as 16 * code, so their sums carry a factor 16 until the final shift.
 bool acc_fits(int64_t K, int bits_x, int bits_w) {
@@ -321,13 +334,10 @@ static aqt_status ffn_fwd_impl(const float *x, const float *ln_gamma, const floa
   }
   // second quantizer (one pass when the producer emitted max|h|), second contraction
   if (p2.bits_x) {
-    if (p1.bits_x) {
-      AQT_TRY(launch_quantize_with_absmax(saved->h, M, H, H, p2.bits_x, reinterpret_cast<const uint32_t *>(f.h_absmax),
-                                          l2.xq, l2.s_x, l2.mask_x, st, dev_status));
-    } else {
-      AQT_TRY(launch_quantize(saved->h, M, H, H, p2.bits_x, AQT_AXIS_ALL, l2.xq, l2.s_x, l2.mask_x,
-                              static_cast<float *>(f.ln), st, dev_status));
-    }
+    if (p1.bits_x)
+      return quantized_layer(saved->h, reinterpret_cast<const uint32_t *>(f.h_absmax), l2, p2, M, H, D, b2, y, s2, st, dev_status);
+    AQT_TRY(launch_quantize(saved->h, M, H, H, p2.bits_x, AQT_AXIS_ALL, l2.xq, l2.s_x, l2.mask_x,
+                            static_cast<float *>(f.ln), st, dev_status));
     return launch_dense_fwd_q(l2.xq, l2.s_x, l2.wq_packed, l2.s_w, M, H, D, p2.bits_w, b2, AQT_EPI_NONE, y, nullptr,
                               nullptr, s2.operand, st, nullptr, s2.prepared);
   }
@@ -387,10 +397,7 @@ static aqt_status conv_module_fwd_impl(const float *x, const float *ln_gamma, co
   AQT_TRY(launch_dwconv_fwd(saved->g, w_dw, b_dw, norm_scale, norm_shift, 1, B, T, D, kw, pad_left, saved->s,
                             saved->dfac, smax, st, true));
   // second pointwise convolution
-  AQT_TRY(launch_quantize_with_absmax(saved->s, M, D, D, p2.bits_x, reinterpret_cast<const uint32_t *>(f.h_absmax),
-                                      l2.xq, l2.s_x, l2.mask_x, st, dev_status));
-  return launch_dense_fwd_q(l2.xq, l2.s_x, l2.wq_packed, l2.s_w, M, D, D, p2.bits_w, b2, AQT_EPI_NONE, y, nullptr,
-                            nullptr, s2.operand, st, nullptr, s2.prepared);
+  return quantized_layer(saved->s, smax, l2, p2, M, D, D, b2, y, s2, st, dev_status);
 }
 
 static aqt_status mhsa_fwd_check(const float *x, float ln_eps, const float *wqkv, const float *wo, int64_t B,
@@ -443,10 +450,7 @@ static aqt_status mhsa_fwd_impl(const float *x, const float *ln_gamma, const flo
   AQT_TRY(launch_attention(saved->qkv_f, B, T, D, heads, left_context, right_context, saved->ctx, cmax, saved->lse,
                            st, true));
   // output projection
-  AQT_TRY(launch_quantize_with_absmax(saved->ctx, M, D, D, p2.bits_x, reinterpret_cast<const uint32_t *>(f.h_absmax),
-                                      l2.xq, l2.s_x, l2.mask_x, st, dev_status));
-  return launch_dense_fwd_q(l2.xq, l2.s_x, l2.wq_packed, l2.s_w, M, D, D, p2.bits_w, bo, AQT_EPI_NONE, y, nullptr,
-                            nullptr, s2.operand, st, nullptr, s2.prepared);
+  return quantized_layer(saved->ctx, cmax, l2, p2, M, D, D, bo, y, s2, st, dev_status);
 }
 
 // Argument checks of the three module backward calls, each in one function so that the layer backward can run all

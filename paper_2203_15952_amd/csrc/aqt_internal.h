@@ -162,6 +162,20 @@ aqt_status launch_dense_bwd(const float *dy, const aqt_saved *sv, int64_t M, int
                             float *dx, float *dw, float *dbias, void *ws, size_t ws_bytes,
                             hipStream_t st, const float *dx_factor = nullptr);
 
+// Float32 rows [M,K] whose codes are still to be made, by the product that takes them: launch_quantize_with_absmax inside
+// gemm_any.hip's forward.  x is 16-byte and q 4-byte aligned.
+struct RowSource {
+  const float *x;
+  const uint32_t *absmax;
+  int qmax;
+  int8_t *q;
+  float *scale;
+  int32_t *dev_status;
+};
+bool dense_fwd_rows_ok(int64_t M, int64_t K, int64_t N);
+aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, const float *s_w, int64_t M, int64_t K, int64_t N,
+                                 int bits_w, const float *bias, float *y, hipStream_t st);
+
 // ---- block pieces (block.hip) -----------------------------------------------------------
 size_t layernorm_ws_bytes(int64_t M);
 // res / alpha / sum_out (optional): normalise x + alpha * res instead of x and leave that sum in sum_out.

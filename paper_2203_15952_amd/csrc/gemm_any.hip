@@ -18,6 +18,7 @@
 #include "bf16_terms.h"
 #include "colsum.h"
 #include "epilogue.h"
+#include "quant_code.h"
 
 namespace aqt {
 namespace {
@@ -36,12 +37,17 @@ __device__ __forceinline__ int chunk_at(int row, int chunk) { return row * (CH *
 // ---- forward: int8 codes x int8 / int4 codes, int32 sums -----------------------------------
 // A wavefront owns TM x TN blocks of 32 x 32; a GLU tile pairs value (even) and gate (odd) column blocks.
 // BK: fan-in positions per slice.
-template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI>
-__global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense_fwd_any_kernel(
+// FILL: where a tile's codes come from when they are not in xq: fill(lds, slice bytes, tile row, first column tile) makes them from
+// float32 rows, at most one slice to each of the WK wavefronts, at the place of each slice's A rows, and returns the scale.
+struct FromCodes {
+  static constexpr bool kFills = false;
+};
+template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI, class FILL>
+__device__ __forceinline__ void dense_fwd_any_body(
     const int8_t *__restrict__ xq, const float *__restrict__ s_x, const uint8_t *__restrict__ wq,
     const float *__restrict__ s_w, int64_t M, int64_t K, int64_t N, const float *__restrict__ bias,
     float *__restrict__ y, int32_t *__restrict__ acc_out, uint32_t *__restrict__ y_absmax, float *__restrict__ dact,
-    int tiles_n) {
+    int tiles_n, const FILL &fill) {
   static_assert(16 % WK == 0 && (EPI != AQT_EPI_GLU || TN % 2 == 0), "the epilogue is shared out by registers");
   constexpr bool GLU = EPI == AQT_EPI_GLU;
   constexpr int G = 64 * WM * WN;                       // threads of a group
@@ -69,7 +75,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
 #pragma unroll
   for (int u = 0; u < NA; ++u) {
     const int64_t m = bm * BM + (gt + u * G) / CHA;
-    pa[u] = reinterpret_cast<const uint8_t *>(xq) + (m < M ? m : M - 1) * K;
+    pa[u] = FILL::kFills ? nullptr : reinterpret_cast<const uint8_t *>(xq) + (m < M ? m : M - 1) * K;
   }
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
@@ -86,8 +92,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
     constexpr int S = decltype(set)::value;
     const int64_t a0 = slice * BK + 16 * ca, b0 = slice * kRowSlice + 16 * cb;
     const int64_t at = a0 + 16 <= K ? a0 : K - 16, bt = b0 + 16 <= row_bytes ? b0 : row_bytes - 16;
+    if constexpr (!FILL::kFills) {
 #pragma unroll
-    for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4i>(pa[u] + at);
+      for (int u = 0; u < NA; ++u) ra[S][u] = load_at<v4i>(pa[u] + at);
+    }
 #pragma unroll
     for (int u = 0; u < NB; ++u) rb[S][u] = load_at<v4i>(pb[u] + bt);
   };
@@ -110,13 +118,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
     constexpr int S = decltype(set)::value;
     if ((slice + 1) * BK > K && !narrow) {
       const int da = moved(slice * BK + 16 * ca, K, 16), db = moved(slice * kRowSlice + 16 * cb, row_bytes, 16);
+      if constexpr (!FILL::kFills) {
 #pragma unroll
-      for (int u = 0; u < NA; ++u) ra[S][u] = shift_down(ra[S][u], da);
+        for (int u = 0; u < NA; ++u) ra[S][u] = shift_down(ra[S][u], da);
+      }
 #pragma unroll
       for (int u = 0; u < NB; ++u) rb[S][u] = shift_down(rb[S][u], db);
     }
+    if constexpr (!FILL::kFills) {
 #pragma unroll
-    for (int u = 0; u < NA; ++u) *reinterpret_cast<v4i *>(slot + chunk_at<CHA>((gt + u * G) / CHA, ca)) = ra[S][u];
+      for (int u = 0; u < NA; ++u) *reinterpret_cast<v4i *>(slot + chunk_at<CHA>((gt + u * G) / CHA, ca)) = ra[S][u];
+    }
 #pragma unroll
     for (int u = 0; u < NB; ++u)
       *reinterpret_cast<v4i *>(slot + BM * CHA * 16 + chunk_at<CHB>((gt + u * G) / CHB, cb)) = rb[S][u];
@@ -144,8 +156,24 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
       }
     }
   };
-  if (!narrow) run_slices<WK>(lds, kSliceBytes, wk, cdiv(K, BK), load, stage, multiply);
-  else if (wk == 0) run_narrow<WK>(lds, load_narrow, stage, multiply);
+  float sx;
+  if constexpr (FILL::kFills) {
+    static_assert(WM * WN * TM == 1 && BK == 64, "32 rows, one slice to a wavefront");
+    constexpr std::integral_constant<int, 0> set0{};
+    const bool mine = wk < cdiv(K, BK);   // uniform
+    if (mine) load(set0, wk);
+    sx = fill(lds, kSliceBytes, bm, bn == 0);
+    __syncthreads();
+    if (mine) {
+      stage(set0, wk, lds + wk * kSliceBytes);
+      __builtin_amdgcn_wave_barrier();
+      multiply(lds + wk * kSliceBytes);
+    }
+  } else {
+    if (!narrow) run_slices<WK>(lds, kSliceBytes, wk, cdiv(K, BK), load, stage, multiply);
+    else if (wk == 0) run_narrow<WK>(lds, load_narrow, stage, multiply);
+    sx = s_x[0];
+  }
 
   // The groups of a tile add their sums (integers: any order) and share the epilogue: each takes 16 / WK of the
   // accumulator registers.
@@ -173,7 +201,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
     }
     return PACKED ? (v >> 4) : v;
   };
-  const float sx = s_x[0];
   uint32_t amax = 0u;
   constexpr int JS = GLU ? 2 : 1;
   const int64_t m_lane = bm * BM + wm * 32 * TM + 4 * lk;   // this lane's first row
@@ -232,6 +259,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense
       if (amax > *reinterpret_cast<volatile uint32_t *>(y_absmax)) atomicMax(y_absmax, amax);
     }
   }
+}
+
+template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI>
+__global__ __launch_bounds__(64 * WM * WN * WK, WM * WN == 8 ? 4 : 2) void dense_fwd_any_kernel(
+    const int8_t *__restrict__ xq, const float *__restrict__ s_x, const uint8_t *__restrict__ wq,
+    const float *__restrict__ s_w, int64_t M, int64_t K, int64_t N, const float *__restrict__ bias,
+    float *__restrict__ y, int32_t *__restrict__ acc_out, uint32_t *__restrict__ y_absmax, float *__restrict__ dact,
+    int tiles_n) {
+  dense_fwd_any_body<TM, TN, WM, WN, WK, BK, PACKED, EPI>(xq, s_x, wq, s_w, M, K, N, bias, y, acc_out, y_absmax, dact, tiles_n,
+                                                          FromCodes{});
 }
 
 // ---- float32 operand x codes ------------------------------------------------------------------
@@ -817,6 +854,56 @@ Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, int epilogue, bool 
   return cdiv(cols, 64) % 2 && contraction <= 256 && rows > 512 && !light ? Tile::kNarrow : Tile::kRows;
 }
 
+// ---- forward from float32 rows: the one-pass quantizer in the product's launch ----
+// A launch in a chain takes 4 us whatever it does, and the quantizer of a small tensor is one.  Where its producer has left the largest
+// |value|, every workgroup of the product makes the codes of its 32 rows itself, in the quantizer's own arithmetic, under
+// the trip of its weights from memory, and those of the first column tile write them out.  40 x 512 -> 512 the quantizer 3.6 and the
+// product 4.0 us -> 5.8 in one, 1302 x 144 -> 144 4.2 and 4.1 -> 5.2, 1024 x 256 -> 256 3.9 and 4.0 -> 5.9, and a launch's
+// gap less.  With the normalisation in front of the quantizer as well it took 10 - 16 us against 4 and 5 (gamma and beta spill).
+struct FillRows {
+  static constexpr bool kFills = true;
+  RowSource s;
+  int64_t M;
+  int K;
+  __device__ __forceinline__ float operator()(uint8_t *lds, int slice_bytes, int64_t bm, bool first) const {
+    constexpr int kSlices = 8;
+    const int t = threadIdx.x, row = t >> 4, c = t & 15;   // sixteen threads a row, four positions of every slice each
+    const bool live = bm * 32 + row < M;
+    const int64_t m = live ? bm * 32 + row : M - 1;
+    const float *const x = s.x + m * K;
+    v4f v[kSlices];
+#pragma unroll
+    for (int k = 0; k < kSlices; ++k) {   // clamped: no branch around a load
+      const int at = 64 * k + 4 * c;
+      v[k] = *reinterpret_cast<const v4f *>(x + (at < K ? at : 0));
+    }
+    const uint32_t mx = s.absmax[0];
+    const float fq = static_cast<float>(s.qmax), scale = __uint_as_float(mx) / fq;
+    const Quantizer qz = quantizer(scale, fq);
+    if (blockIdx.x == 0 && t == 0) {
+      s.scale[0] = scale;
+      if (mx >= 0x7F800000u && s.dev_status) *s.dev_status = AQT_ERR_NONFINITE;
+    }
+#pragma unroll
+    for (int k = 0; k < kSlices; ++k) {
+      const int at = 64 * k + 4 * c;
+      if (64 * k < K) {   // uniform
+        const uint32_t code = at < K ? quant4(v[k].x, v[k].y, v[k].z, v[k].w, qz) : 0u;
+        *reinterpret_cast<uint32_t *>(lds + k * slice_bytes + chunk_at<4>(row, c >> 2) + 4 * (c & 3)) = code;
+        if (first && live && at < K) *reinterpret_cast<uint32_t *>(s.q + m * K + at) = code;
+      }
+    }
+    return scale;
+  }
+};
+template <bool PACKED>
+__global__ __launch_bounds__(512, 4) void dense_fwd_rows_kernel(const RowSource src, const uint8_t *__restrict__ wq,
+                                                                const float *__restrict__ s_w, int64_t M, int64_t K, int64_t N,
+                                                                const float *__restrict__ bias, float *__restrict__ y, int tiles_n) {
+  dense_fwd_any_body<1, 1, 1, 1, 8, 64, PACKED, AQT_EPI_NONE>(nullptr, nullptr, wq, s_w, M, K, N, bias, y, nullptr, nullptr, nullptr,
+                                                              tiles_n, FillRows{src, M, static_cast<int>(K)});
+}
+
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
 aqt_status fwd_any(const int8_t *xq, const float *s_x, const void *wq, const float *s_w, int64_t M, int64_t K, int64_t N,
                    const float *bias, int epilogue, float *y, int32_t *acc_out, uint32_t *y_absmax, float *dact,
@@ -888,6 +975,20 @@ aqt_status launch_dense_fwd_any(const int8_t *xq, const float *s_x, const void *
                                 int32_t *acc_out, uint32_t *y_absmax, float *dact, hipStream_t st) {
   return packed4(bits_w) ? fwd_any_sized<true>(xq, s_x, wq_packed, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st)
                          : fwd_any_sized<false>(xq, s_x, wq_packed, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
+}
+
+// Rows of whole 16-byte pieces that the eight wavefronts hold as one slice each, and where the split contraction is picked anyhow.
+bool dense_fwd_rows_ok(int64_t M, int64_t K, int64_t N) {
+  return K >= 64 && K <= 512 && K % 4 == 0 && pick_tile(M, N, K, AQT_EPI_NONE, false) == Tile::kSmallest;
+}
+aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, const float *s_w, int64_t M, int64_t K, int64_t N,
+                                 int bits_w, const float *bias, float *y, hipStream_t st) {
+  const int64_t tn = cdiv(N, 32), tm = cdiv(M, 32);
+  auto kern = packed4(bits_w) ? dense_fwd_rows_kernel<true> : dense_fwd_rows_kernel<false>;
+  kern<<<static_cast<unsigned>(tn * tm), 512, 0, st>>>(src, static_cast<const uint8_t *>(wq_packed), s_w, M, K, N, bias, y,
+                                                       static_cast<int>(tn));
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
 }
 
 aqt_status launch_bwd_dx_any(const float *dy, const int8_t *wq_kn, const float *s_w, const float *s_x, const uint32_t *mask_x,

@@ -378,3 +378,27 @@ def test_few_utterances_have_the_bits_of_many(T, left, right, dh):
     check_attention(got[0][0], qkv, 2, T, D, heads, left, right)
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("T", [1, 33, 95])
+@pytest.mark.parametrize("D,bw", [(64, 8), (68, 4), (132, 8), (508, 4), (512, 8), (512, 4), (516, 8), (60, 4)])
+def test_small_output_projections_quantize_inside_the_product(T, D, bw):
+    """Row lengths on and next to the ends of the range whose product makes the codes itself, and of its slices: the module's
+    codes, scale and result are those of the quantizer and the product called one by one, and an infinity is reported."""
+    say("quantizer inside the product", T, D, bw)
+    rng = np.random.default_rng(760 + T + D)
+    heads, policy = D // 4 if D % 16 else 16, ((8, 8), (bw, 8))
+    x, wqkv, wo, bo = (rng.standard_normal(s).astype(F) for s in ((T, D), (D, 3 * D), (D, D), (D,)))
+    sv = B.MhsaSaved(1, T, D, policy)
+    y = B.aqt_mhsa_fwd(dev(x), dev(wqkv), None, dev(wo), dev(bo), sv, heads)
+    m = dev(np.float32([np.abs(host(sv.ctx)).max()]))
+    q, s, _ = B.aqt_quantize_with_absmax(sv.ctx, 8, m)
+    wp, s_w, _, _ = B.aqt_quantize_weights(dev(wo), bw)
+    want, _ = B.aqt_dense_fwd_q(q, s, wp, s_w, D, 8, bw, bias=dev(bo))
+    np.testing.assert_array_equal(host(sv.out.xq), host(q))
+    np.testing.assert_array_equal(host(sv.out.s_x), host(s))
+    np.testing.assert_array_equal(host(y), host(want))
+    status = B.new_status()
+    x[T // 2, 1] = np.inf
+    B.aqt_mhsa_fwd(dev(x), dev(wqkv), None, dev(wo), dev(bo), sv, heads, dev_status=status)
+    assert host(status)[0] == B.AQT_ERR_NONFINITE
