@@ -728,7 +728,11 @@ aqt_status aqt_dense_fwd(const float *x, const float *w, int64_t M, int64_t K, i
                     reinterpret_cast<uintptr_t>(f.wfrag) % 16 == 0;
   const WeightJob job = {w, K, N, bits_w, wq, s_w, saved ? saved->wq_kn : nullptr, saved ? saved->mask_w : nullptr, f.wpart,
                          frag ? f.wfrag : nullptr};
-  AQT_TRY(launch_quantize_dense(x, M, K, bits_x, xq, s_x, saved ? saved->mask_x : nullptr, f.partials, job, st, dev_status));
+  DenseSource src{};
+  const bool raw = dense_fwd_raw_ok(M, K, N, epilogue) && !fwd_q_uses_fragments(M, K, N, epilogue);
+  AQT_TRY(launch_quantize_dense(x, M, K, bits_x, xq, s_x, saved ? saved->mask_x : nullptr, f.partials, job, st, dev_status,
+                                raw ? &src : nullptr));
+  if (src.xq) return launch_dense_fwd_raw(src, M, K, N, bias, epilogue, y, saved ? saved->dact : nullptr, st);
   return launch_dense_fwd_q(xq, s_x, wq, s_w, M, K, N, bits_w, bias, epilogue, y, nullptr, nullptr, f.wfrag, st,
                             saved ? saved->dact : nullptr, frag);
 }

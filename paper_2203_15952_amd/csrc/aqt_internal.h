@@ -83,9 +83,11 @@ struct WeightJob {
 };
 constexpr int kWeightJobsMax = 8;
 aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream_t st, int32_t *dev_status);
+struct DenseSource;
 // The activations (per tensor) and the weights of one dense layer; one launch pair where the activations are aligned and want no mask.
 aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int bits_x, int8_t *q, float *scale, uint32_t *mask,
-                                 float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status);
+                                 float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status,
+                                 DenseSource *later = nullptr);   // later: the second launch is described there (xq set) where a product can take it
 inline size_t weight_ws_bytes(int64_t N) { return align_up(static_cast<size_t>(kWeightSlabs) * N * 4, 256); }
 aqt_status launch_unpack_weights(const void *wq_packed, int64_t K, int64_t N, int bits_w,
                                  int8_t *codes_kn, hipStream_t st);
@@ -175,6 +177,26 @@ struct RowSource {
 bool dense_fwd_rows_ok(int64_t M, int64_t K, int64_t N);
 aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, const float *s_w, int64_t M, int64_t K, int64_t N,
                                  int bits_w, const float *bias, float *y, hipStream_t st);
+
+// A dense layer's float32 tensors and where its codes go, behind the pass that takes the maxima (launch_absmax_dense): the second
+// launch of launch_quantize_dense and the product in one.  x, w 16-byte, the codes 4-byte aligned, no clip masks.
+struct DenseSource {
+  const float *x;
+  const uint32_t *partial;   // nparts maxima of |x|
+  int nparts, qmax_x;
+  int8_t *xq;
+  float *s_x;
+  const float *w;
+  const uint32_t *part;      // slabs x N maxima of |w|
+  int slabs, qmax_w, packed;
+  uint8_t *wq_packed;
+  float *s_w;
+  int8_t *wq_kn;             // nullable
+  int32_t *dev_status;
+};
+bool dense_fwd_raw_ok(int64_t M, int64_t K, int64_t N, int epilogue);
+aqt_status launch_dense_fwd_raw(const DenseSource &src, int64_t M, int64_t K, int64_t N, const float *bias, int epilogue, float *y,
+                                float *dact, hipStream_t st);
 
 // ---- block pieces (block.hip) -----------------------------------------------------------
 size_t layernorm_ws_bytes(int64_t M);

@@ -37,10 +37,11 @@ __device__ __forceinline__ int chunk_at(int row, int chunk) { return row * (CH *
 // ---- forward: int8 codes x int8 / int4 codes, int32 sums -----------------------------------
 // A wavefront owns TM x TN blocks of 32 x 32; a GLU tile pairs value (even) and gate (odd) column blocks.
 // BK: fan-in positions per slice.
-// FILL: where a tile's codes come from when they are not in xq: fill(lds, slice bytes, tile row, first column tile) makes them from
-// float32 rows, at most one slice to each of the WK wavefronts, at the place of each slice's A rows, and returns the scale.
+// FILL: where a tile's codes come from when they are not in xq: fill(lds, slice bytes, tile row, tile column, scales) makes them from
+// float32 rows, at most one slice to each of the WK wavefronts, at the place of each slice's A rows, and returns the scale; with
+// kWeights those of the tile's B rows too, as bytes, and their scales.
 struct FromCodes {
-  static constexpr bool kFills = false;
+  static constexpr bool kFills = false, kWeights = false;
 };
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI, class FILL>
 __device__ __forceinline__ void dense_fwd_any_body(
@@ -81,7 +82,7 @@ __device__ __forceinline__ void dense_fwd_any_body(
   for (int u = 0; u < NB; ++u) {
     const int r = (gt + u * G) / CHB;
     const int64_t n = chan(r >> 5) + (r & 31);
-    pb[u] = wq + (n < N ? n : N - 1) * row_bytes;
+    pb[u] = FILL::kWeights ? nullptr : wq + (n < N ? n : N - 1) * row_bytes;
   }
   // G is a multiple of the chunks per row: a thread's chunks sit at the same place of their rows
   const int ca = gt % CHA, cb = gt % CHB;
@@ -157,16 +158,20 @@ __device__ __forceinline__ void dense_fwd_any_body(
     }
   };
   float sx;
+  __shared__ float scales[FILL::kWeights ? BN : 1];
+  static_assert(!FILL::kWeights || (TN == 1 && WN == 1 && !PACKED), "one block of byte rows");
   if constexpr (FILL::kFills) {
     static_assert(WM * WN * TM == 1 && BK == 64, "32 rows, one slice to a wavefront");
     constexpr std::integral_constant<int, 0> set0{};
     const bool mine = wk < cdiv(K, BK);   // uniform
-    if (mine) load(set0, wk);
-    sx = fill(lds, kSliceBytes, bm, bn == 0);
+    if (!FILL::kWeights && mine) load(set0, wk);
+    sx = fill(lds, kSliceBytes, bm, bn, scales);
     __syncthreads();
     if (mine) {
-      stage(set0, wk, lds + wk * kSliceBytes);
-      __builtin_amdgcn_wave_barrier();
+      if constexpr (!FILL::kWeights) {
+        stage(set0, wk, lds + wk * kSliceBytes);
+        __builtin_amdgcn_wave_barrier();
+      }
       multiply(lds + wk * kSliceBytes);
     }
   } else {
@@ -209,7 +214,7 @@ __device__ __forceinline__ void dense_fwd_any_body(
     const int64_t n = chan(wn * TN + j) + lr;
     const bool live = n < oc;
     const int64_t nc = live ? n : oc - 1, ng = nc + (GLU ? oc : 0);
-    const float sc_a = sx * s_w[nc], bias_a = bias ? bias[nc] : 0.0f;
+    const float sc_a = sx * (FILL::kWeights ? scales[nc - bn * BN] : s_w[nc]), bias_a = bias ? bias[nc] : 0.0f;
     const float sc_b = GLU ? sx * s_w[ng] : 0.0f, bias_b = (GLU && bias) ? bias[ng] : 0.0f;
     const int rows = live ? static_cast<int>(M - m_lane < BM ? M - m_lane : BM) : 0;   // rows of this lane's column in the tensor
     float *const yl = y + m_lane * oc + n, *const dl = dact + m_lane * N + n;
@@ -861,12 +866,13 @@ Tile pick_tile(int64_t M, int64_t cols, int64_t contraction, int epilogue, bool 
 // product 4.0 us -> 5.8 in one, 1302 x 144 -> 144 4.2 and 4.1 -> 5.2, 1024 x 256 -> 256 3.9 and 4.0 -> 5.9, and a launch's
 // gap less.  With the normalisation in front of the quantizer as well it took 10 - 16 us against 4 and 5 (gamma and beta spill).
 struct FillRows {
-  static constexpr bool kFills = true;
+  static constexpr bool kFills = true, kWeights = false;
   RowSource s;
   int64_t M;
   int K;
-  __device__ __forceinline__ float operator()(uint8_t *lds, int slice_bytes, int64_t bm, bool first) const {
+  __device__ __forceinline__ float operator()(uint8_t *lds, int slice_bytes, int64_t bm, int64_t bn, float *) const {
     constexpr int kSlices = 8;
+    const bool first = bn == 0;
     const int t = threadIdx.x, row = t >> 4, c = t & 15;   // sixteen threads a row, four positions of every slice each
     const bool live = bm * 32 + row < M;
     const int64_t m = live ? bm * 32 + row : M - 1;
@@ -902,6 +908,110 @@ __global__ __launch_bounds__(512, 4) void dense_fwd_rows_kernel(const RowSource 
                                                                 const float *__restrict__ bias, float *__restrict__ y, int tiles_n) {
   dense_fwd_any_body<1, 1, 1, 1, 8, 64, PACKED, AQT_EPI_NONE>(nullptr, nullptr, wq, s_w, M, K, N, bias, y, nullptr, nullptr, nullptr,
                                                               tiles_n, FillRows{src, M, static_cast<int>(K)});
+}
+
+// ---- forward of a small dense layer from its float32 tensors, behind the pass that takes the maxima ----
+// Both quantizers in the product's launch: a workgroup makes the codes of its 32 rows and of its 32 channels (four positions x four
+// channels a thread); the first column tile writes the activations' codes, the first
+// row tile everything the weights leave behind.
+struct FillDense {
+  static constexpr bool kFills = true, kWeights = true;
+  DenseSource s;
+  int64_t M, N;
+  int K;
+  __device__ __forceinline__ float operator()(uint8_t *lds, int slice_bytes, int64_t bm, int64_t bn, float *scales) const {
+    constexpr int T = 512, kSlices = 4;
+    __shared__ uint32_t most[T / 64];
+    __shared__ __attribute__((aligned(16))) uint32_t top[kWeightSlabs][32];
+    const int t = threadIdx.x, row = t >> 4, c = t & 15, nb = t & 7, kq = t >> 3;
+    const bool live = bm * 32 + row < M, channels = bn * 32 + 4 * nb < N;   // four channels at once: N is a multiple of four
+    const int64_t m = live ? bm * 32 + row : M - 1, n = bn * 32 + 4 * nb, nc = channels ? n : N - 4;
+    const float *const x = s.x + m * K;
+    v4f v[kSlices], wv[4];
+#pragma unroll
+    for (int k = 0; k < kSlices; ++k) {   // clamped: no branch around a load
+      const int at = 64 * k + 4 * c;
+      v[k] = *reinterpret_cast<const v4f *>(x + (at < K ? at : 0));
+    }
+    const int kw = 4 * kq;   // this thread's positions of its channels
+#pragma unroll
+    for (int i = 0; i < 4; ++i) wv[i] = *reinterpret_cast<const v4f *>(s.w + static_cast<int64_t>(kw + i < K ? kw + i : K - 1) * N + nc);
+    uint32_t mx = words_max<T>(s.partial, s.nparts);
+    if (t < 8 * kWeightSlabs) {
+      const int slab = t >> 3;
+      *reinterpret_cast<v4i *>(&top[slab][4 * nb]) =
+          *reinterpret_cast<const v4i *>(s.part + static_cast<int64_t>(slab < s.slabs ? slab : s.slabs - 1) * N + nc);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), off)));
+    if ((t & 63) == 0) most[t >> 6] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) mx = max(mx, most[w]);
+    const float fq = static_cast<float>(s.qmax_x), scale = __uint_as_float(mx) / fq, fw = static_cast<float>(s.qmax_w);
+    const Quantizer qz = quantizer(scale, fq);
+    if (blockIdx.x == 0 && t == 0) {
+      s.s_x[0] = scale;
+      if (mx >= 0x7F800000u && s.dev_status) *s.dev_status = AQT_ERR_NONFINITE;
+    }
+    uint32_t wm[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int slab = 0; slab < kWeightSlabs; ++slab) {
+      const v4i a = *reinterpret_cast<const v4i *>(&top[slab][4 * nb]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wm[e] = max(wm[e], static_cast<uint32_t>(a[e]));
+    }
+#pragma unroll
+    for (int k = 0; k < kSlices; ++k) {
+      const int at = 64 * k + 4 * c;
+      if (64 * k < K) {   // uniform
+        const uint32_t code = at < K ? quant4(v[k].x, v[k].y, v[k].z, v[k].w, qz) : 0u;
+        *reinterpret_cast<uint32_t *>(lds + k * slice_bytes + chunk_at<4>(row, c >> 2) + 4 * (c & 3)) = code;
+        if (bn == 0 && live && at < K) *reinterpret_cast<uint32_t *>(s.xq + m * K + at) = code;
+      }
+    }
+    uint32_t codes[4];   // channel 4 nb + e
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float ws = __uint_as_float(wm[e]) / fw;
+      if (kq == 0) scales[4 * nb + e] = ws;
+      if (bm == 0 && kq == 0 && channels) {
+        s.s_w[n + e] = ws;
+        if (!(fabsf(ws) < INFINITY) && s.dev_status) *s.dev_status = AQT_ERR_NONFINITE;
+      }
+      const Quantizer qw = quantizer(ws, fw);
+codes[e] = quant4(wv[0][e], wv[1][e], wv[2][e], wv[3][e], qw);
+      if (kw < K) *reinterpret_cast<uint32_t *>(lds + (kw >> 6) * slice_bytes + 32 * 64 + chunk_at<4>(4 * nb + e, (kw & 63) >> 4) + (kw & 15)) = codes[e];
+    }
+    if (bm == 0 && channels && kw < K) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t w = codes[e];
+        if (s.packed) {
+          const uint32_t b = (w & 0xFu) | ((w >> 4) & 0xF0u) | ((w >> 8) & 0xF00u) | ((w >> 12) & 0xF000u);
+          *reinterpret_cast<uint16_t *>(s.wq_packed + (n + e) * (K / 2) + kw / 2) = static_cast<uint16_t>(b);
+        } else {
+          *reinterpret_cast<uint32_t *>(s.wq_packed + (n + e) * K + kw) = w;
+        }
+      }
+      if (s.wq_kn) {   // four channels of a position
+        auto pair = [](uint32_t a, uint32_t b, uint32_t sel) { return __builtin_amdgcn_perm(b, a, sel); };
+        const uint32_t a = pair(codes[0], codes[1], 0x05010400u), b = pair(codes[2], codes[3], 0x05010400u);
+        const uint32_t d = pair(codes[0], codes[1], 0x07030602u), f = pair(codes[2], codes[3], 0x07030602u);
+        const uint32_t at[4] = {pair(a, b, 0x05040100u), pair(a, b, 0x07060302u), pair(d, f, 0x05040100u), pair(d, f, 0x07060302u)};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<uint32_t *>(s.wq_kn + static_cast<int64_t>(kw + i) * N + n) = at[i];
+      }
+    }
+    return scale;
+  }
+};
+template <int EPI>
+__global__ __launch_bounds__(512, 4) void dense_fwd_raw_kernel(const DenseSource src, int64_t M, int64_t K, int64_t N,
+                                                               const float *__restrict__ bias, float *__restrict__ y,
+                                                               float *__restrict__ dact, int tiles_n) {
+  dense_fwd_any_body<1, 1, 1, 1, 8, 64, false, EPI>(nullptr, nullptr, nullptr, nullptr, M, K, N, bias, y, nullptr, nullptr, dact, tiles_n,
+                                                    FillDense{src, M, N, static_cast<int>(K)});
 }
 
 template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>
@@ -987,6 +1097,22 @@ aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, co
   auto kern = packed4(bits_w) ? dense_fwd_rows_kernel<true> : dense_fwd_rows_kernel<false>;
   kern<<<static_cast<unsigned>(tn * tm), 512, 0, st>>>(src, static_cast<const uint8_t *>(wq_packed), s_w, M, K, N, bias, y,
                                                        static_cast<int>(tn));
+  AQT_HIP(hipGetLastError());
+  return AQT_OK;
+}
+
+// Where each workgroup still has half a compute unit to itself: the product with both quantizers in it takes as long as the two launches
+// (256 x 256 -> 1024 10.0 us of chained launches for the layer -> 9.9, 24 x 128 -> 2048 9.5 -> 8.6, 32 x 64 -> 64 8.8 -> 7.6), and the call of three launches,
+// which the host bounds, becomes one of two: 15.4 -> 12.2 us at 256 x 256 -> 1024 from Python.  Beyond, the repeated conversions cost more:
+// 700 x 252 -> 1000 (704 workgroups) 13.2 -> 16.5, and fan-ins of up to 512 spill (256 x 512 -> 1024 10.6 -> 18.7).
+bool dense_fwd_raw_ok(int64_t M, int64_t K, int64_t N, int epilogue) {
+  return epilogue != AQT_EPI_GLU && N % 4 == 0 && K <= 256 && cdiv(M, 32) * cdiv(N, 32) <= 256 && dense_fwd_rows_ok(M, K, N);
+}
+aqt_status launch_dense_fwd_raw(const DenseSource &src, int64_t M, int64_t K, int64_t N, const float *bias, int epilogue, float *y,
+                                float *dact, hipStream_t st) {
+  const int64_t tn = cdiv(N, 32), tm = cdiv(M, 32);
+  auto kern = epilogue == AQT_EPI_SWISH ? dense_fwd_raw_kernel<AQT_EPI_SWISH> : dense_fwd_raw_kernel<AQT_EPI_NONE>;
+  kern<<<static_cast<unsigned>(tn * tm), 512, 0, st>>>(src, M, K, N, bias, y, dact, static_cast<int>(tn));
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }

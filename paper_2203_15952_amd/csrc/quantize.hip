@@ -689,7 +689,7 @@ aqt_status launch_quantize_with_scale(const float *x, int64_t rows, int64_t cols
 }
 
 aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int bits_x, int8_t *q, float *scale, uint32_t *mask,
-                                 float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status) {
+                                 float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status, DenseSource *later) {
   if (mask || !flat_ok(x, cols, cols, q)) {
     AQT_TRY(launch_quantize(x, rows, cols, cols, bits_x, AQT_AXIS_ALL, q, scale, mask, partials, st, dev_status));
     return launch_quantize_weights_group(&w, 1, st, dev_status);
@@ -703,6 +703,12 @@ aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int
   auto pass1 = streams(f.n) ? absmax_dense_kernel<true> : absmax_dense_kernel<false>;
   pass1<<<static_cast<unsigned>(b1 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b1));
   AQT_HIP(hipGetLastError());
+  auto words = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 4 == 0; };
+  if (later && j.vec4 && !w.mask_w && !w.wfrag && words(w.wq_packed) && reinterpret_cast<uintptr_t>(j.part) % 16 == 0) {
+    *later = DenseSource{x, f.partial, f.blocks, f.qmax, q, scale, j.w, j.part, j.slabs, j.qmax, j.packed, j.wq_packed, j.s_w, j.wq_kn,
+                         dev_status};
+    return AQT_OK;
+  }
   quantize_dense_kernel<<<static_cast<unsigned>(b2 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b2), dev_status);
   AQT_HIP(hipGetLastError());
   return AQT_OK;

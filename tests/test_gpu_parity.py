@@ -196,6 +196,34 @@ def test_dense_fwd_against_oracle(M, K, N, bx, bw, epi, with_bias):
     np.testing.assert_array_equal(host(y2), host(y))
 
 
+@pytest.mark.parametrize("M,K,N", [(1, 64, 4), (33, 64, 36), (31, 68, 2044), (256, 256, 1024), (97, 252, 100), (64, 132, 60),
+                                   (32, 256, 64), (45, 260, 64), (40, 60, 64)])   # the last two: fan-ins next to the range
+@pytest.mark.parametrize("bw,epi", [(8, 0), (4, 1), (3, 0)])
+def test_small_dense_layers_quantize_inside_the_product(M, K, N, bw, epi):
+    """Everything that the two quantizers and the product leave behind, in one launch behind the maxima: as called one by one."""
+    say("dense in two launches", M, K, N, bw, epi)
+    rng = np.random.default_rng(41 + M + K + N)
+    x, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((K, N)).astype(np.float32)
+    w[:, N // 2] = 0.0
+    x_d, w_d, bias = dev(x), dev(w), dev(rng.standard_normal(N).astype(np.float32))
+    xq, s_x, _ = B.aqt_quantize(x_d, 8, B.AQT_AXIS_ALL)
+    wq, s_w, wq_kn, _ = B.aqt_quantize_weights(w_d, bw)
+    want, _ = B.aqt_dense_fwd_q(xq, s_x, wq, s_w, N, 8, bw, bias=bias, epilogue=epi)
+    sv, status = B.Saved(M, K, N, bw), B.new_status()
+    for t in (sv.xq, sv.wq_packed, sv.wq_kn):
+        t.fill_(85)
+    y = B.aqt_dense_fwd(x_d, w_d, 8, bw, bias=bias, epilogue=epi, saved=sv, dev_status=status)
+    for got, ref in ((sv.xq, xq), (sv.s_x, s_x), (sv.wq_packed, wq), (sv.s_w, s_w), (sv.wq_kn, wq_kn), (y, want)):
+        np.testing.assert_array_equal(host(got).reshape(-1), host(ref).reshape(-1))
+    assert host(status)[0] == 0
+    for t in (x, w):   # a value that is not finite is reported, whichever tensor holds it
+        keep, t[-1, -1] = t[-1, -1], np.nan
+        status = B.new_status()
+        B.aqt_dense_fwd(dev(x), dev(w), 8, bw, bias=bias, epilogue=epi, dev_status=status)
+        assert host(status)[0] == B.AQT_ERR_NONFINITE
+        t[-1, -1] = keep
+
+
 @pytest.mark.parametrize("M,K,N,bw,epi", [(300, 128, 256, 4, 1), (200, 256, 512, 8, 2), (16500, 1152, 1024, 4, 0),
                                           (12800, 512, 2048, 4, 1)])
 def test_prepared_weights_serving_path(M, K, N, bw, epi):
