@@ -26,7 +26,8 @@
 // Measured in us, all products in float32 (attention.hip) -> scores in float32, the rest here: 32 utterances of 400 frames,
 // 8 heads of 64: 621 -> 295; 128 of 512: 2808 -> 1455; 24 of 417, 4 heads of 36: 310 -> 136.  What every tile pays counts:
 // window tests and zeros beyond the head or the utterance stand under branches of their own, and the constant part of an LDS
-// address goes into the instruction (310 -> 295, 1510 -> 1453, 146 -> 136, the same bits).  Before that, all products in bf16
+// address goes into the instruction (310 -> 295, 1510 -> 1453, 146 -> 136, the same bits).  Small batches, whose workgroups of 128
+// rows leave the chip idle: FEW, 32 rows to a workgroup and the tiles shared out among its wavefronts (launch_attention_bwd_rows).  Before that, all products in bf16
 // passes took 273, 1392 and 125 against 306, 1500 and 146, with the error above.  The matrix pipes are busy 52 % of the
 // cycles of both kernels inside an encoder layer (profiles/encoder_layer_12800_tokens.txt).
 #include <type_traits>
@@ -98,9 +99,9 @@ struct Raw {
   v4f a, b;
 };
 __device__ __forceinline__ Raw load_piece(const float *__restrict__ src, int64_t ld, const AttnShape &g, int64_t b, int row0,
-                                          int64_t col0) {
-  const int piece = threadIdx.x & 7;
-  const int t = row0 + static_cast<int>(threadIdx.x >> 3), tc = t < g.T ? t : g.T - 1;
+                                          int64_t col0, int thread) {
+  const int piece = thread & 7;
+  const int t = row0 + (thread >> 3), tc = t < g.T ? t : g.T - 1;
   const float *p = src + (b * g.T + tc) * ld + col0;
   const int d = 8 * piece, d0 = d < g.dh ? d : g.dh - 4, d1 = d + 4 < g.dh ? d + 4 : g.dh - 4;
   return Raw{*reinterpret_cast<const v4f *>(p + d0), *reinterpret_cast<const v4f *>(p + d1)};
@@ -108,8 +109,9 @@ __device__ __forceinline__ Raw load_piece(const float *__restrict__ src, int64_t
 // ... split into the three images; zeros beyond the head and, where `rows` says so, beyond the utterance
 // (`floats`: the same rows in float32, even positions, then odd ones).
 template <int PIECES>
-__device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnShape &g, int row0, bool rows, float *floats = nullptr) {
-  const int piece = threadIdx.x & 7, row = static_cast<int>(threadIdx.x >> 3);
+__device__ __forceinline__ void stage_piece(uint8_t *tensor, Raw v, const AttnShape &g, int row0, bool rows, int thread,
+                                            float *floats = nullptr) {
+  const int piece = thread & 7, row = thread >> 3;
   const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
   if (8 * PIECES > g.dh) {   // uniform, as the next: most tiles pay for neither
     if (8 * piece >= g.dh) v.a = zero;
@@ -228,6 +230,54 @@ __device__ __forceinline__ void run_tiles(uint8_t *lds, int first, int last, Loa
   }
 }
 
+// FEW: a workgroup owns 32 rows, and its wavefronts take the tiles in turn, each with a slot of its own, loaded and split by
+// itself: no barrier on the way.  bring(slot, row0) requests and stages a tile.
+template <class Bring, class Compute>
+__device__ __forceinline__ void run_tiles_apart(uint8_t *slot, int wave, int first, int last, Bring bring, Compute compute) {
+  for (int r0 = first + wave * kStep; r0 <= last; r0 += 4 * kStep) {
+    bring(slot, r0);
+    __builtin_amdgcn_wave_barrier();
+    compute(slot, r0);
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+// The four wavefronts' shares of 32 rows, in order, into v (row tid / 8, positions 8 (tid % 8) .. + 7); lds: 4 x 32 x kLd floats.
+// True in every thread if one of the sums is not finite.
+template <int DB>
+__device__ __forceinline__ bool add_shares(float *lds, const v16f (&acc)[DB], int wave, int lane, v4f (&v)[2]) {
+  const int lr = lane & 31, lk = lane >> 5, row = static_cast<int>(threadIdx.x >> 3), at = 8 * static_cast<int>(threadIdx.x & 7);
+  __syncthreads();   // the tiles, or the shares before these, are no longer read
+  float *const img = lds + wave * 32 * kLd;
+#pragma unroll
+  for (int blk = 0; blk < DB; ++blk)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+      *reinterpret_cast<v4f *>(img + lr * kLd + 32 * blk + 8 * r4 + 4 * lk) =
+          v4f{acc[blk][4 * r4], acc[blk][4 * r4 + 1], acc[blk][4 * r4 + 2], acc[blk][4 * r4 + 3]};
+  __syncthreads();
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    v[c] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    if (at >= 32 * DB) continue;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const v4f x = *reinterpret_cast<const v4f *>(lds + (w * 32 + row) * kLd + at + 4 * c);
+      v[c].x += x.x; v[c].y += x.y; v[c].z += x.z; v[c].w += x.w;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad = bad || (__float_as_uint(v[c][e]) & 0x7FFFFFFFu) >= 0x7F800000u;
+  }
+  return __syncthreads_or(bad) != 0;
+}
+__device__ __forceinline__ void store_shares(const v4f (&v)[2], float mul, float *__restrict__ out, int64_t ld, int rows_left, int dh) {
+  const int row = static_cast<int>(threadIdx.x >> 3), at = 8 * static_cast<int>(threadIdx.x & 7);
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+    if (row < rows_left && at + 4 * c < dh)
+      *reinterpret_cast<v4f *>(out + row * ld + at + 4 * c) = v4f{v[c].x * mul, v[c].y * mul, v[c].z * mul, v[c].w * mul};
+}
+
 // ---- the same sums with every product in float32, a wavefront by itself --------------------------------
 // (Only where it is needed: everything is formed anew from the workgroup's number, so that nothing has to be kept for it.)
 // A's 32 rows (zeros beyond the utterance) times each lane's own row, along the head, in the order of first_products.
@@ -264,20 +314,21 @@ struct Redo {
   int64_t base, hc;   // the utterance's first token, the head's first column
   int tw, t, tc, first, last, lo, hi, h, lr, lk;
 };
+template <int ROWS>
 __device__ __forceinline__ Redo redo_place(const AttnShape &g, int back, int ahead) {
   int id = static_cast<int>(blockIdx.x), thread = static_cast<int>(threadIdx.x);
   asm volatile("" : "+s"(id));
   asm volatile("" : "+v"(thread));
-  const Place pl = place_of(g, id);
+  const Place pl = place_of<ROWS>(g, id);
   const int lr = thread & 31, tw = pl.r0 + (__builtin_amdgcn_readfirstlane(thread) >> 6) * 32, t = tw + lr;
   const Window w = window_of(t, tw, back, ahead, g.T);
   return Redo{pl.b * g.T, pl.hc, tw, t, t < g.T ? t : g.T - 1, w.some_lo > 0 ? w.some_lo / kStep * kStep : 0, w.some_hi, w.lo, w.hi,
               pl.h, lr, (thread >> 5) & 1};
 }
-template <int DB>
+template <int DB, int ROWS>
 __device__ __forceinline__ void redo_dq(v16f (&dq)[DB], const float *__restrict__ qkv, const float *__restrict__ dctx,
                                         const float *__restrict__ lse, const float *dsum, const AttnShape &g) {
-  const Redo w = redo_place(g, g.left, g.right);
+  const Redo w = redo_place<ROWS>(g, g.left, g.right);
   const int64_t ld = 3 * g.D;
   const float *const q = qkv + (w.base + w.tc) * ld + w.hc, *const go = dctx + (w.base + w.tc) * g.D + w.hc;
   const float *const keys = qkv + w.base * ld + g.D + w.hc;
@@ -299,10 +350,10 @@ __device__ __forceinline__ void redo_dq(v16f (&dq)[DB], const float *__restrict_
     float_product_rows(dq, keys, ld, g, j0, s, w.lr, w.lk);
   }
 }
-template <int DB>
+template <int DB, int ROWS>
 __device__ __forceinline__ void redo_dkv(v16f (&dk)[DB], v16f (&dv)[DB], const float *__restrict__ qkv, const float *__restrict__ dctx,
                                          const float *__restrict__ lse, const float *__restrict__ dsum, const AttnShape &g) {
-  const Redo w = redo_place(g, g.right, g.left);
+  const Redo w = redo_place<ROWS>(g, g.right, g.left);
   const int64_t ld = 3 * g.D;
   const float *const k = qkv + (w.base + w.tc) * ld + g.D + w.hc;
   const float *const queries = qkv + w.base * ld + w.hc, *const grads = dctx + w.base * g.D + w.hc;
@@ -333,21 +384,21 @@ __device__ __forceinline__ void redo_dkv(v16f (&dk)[DB], v16f (&dv)[DB], const f
 // ---- backward: the chain rule and the two kernels of attention.hip ---------------------------------
 // dq: a lane owns a query.  Also forms D_t = dO_t . O_t of its queries (the lane reads dO_t anyway) and leaves it in
 // dsum for the dk / dv kernel.
-template <int KS>
-__global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(const float *__restrict__ qkv,
+template <int KS, bool FEW = false>
+__global__ __launch_bounds__(kThreads, FEW ? 1 : 2) void attention_bwd_dq_rows_kernel(const float *__restrict__ qkv,
                                                                              const float *__restrict__ ctx,
                                                                              const float *__restrict__ dctx,
                                                                              const float *__restrict__ lse,
                                                                              float *__restrict__ dsum, AttnShape g,
                                                                              float *__restrict__ dqkv) {
-  constexpr int DB = (KS + 1) / 2;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSlot];
+  constexpr int DB = (KS + 1) / 2, kRows = FEW ? 32 : kQ;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[(FEW ? 4 : 2) * kSlot];
   const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Place pl = place_of(g, static_cast<int>(blockIdx.x));
+  const Place pl = place_of<kRows>(g, static_cast<int>(blockIdx.x));
   const int64_t b = pl.b, hc = pl.hc;
   const int t0 = pl.r0;
-  const int tw = t0 + wave * 32, t = tw + lr, tc = t < g.T ? t : g.T - 1;
+  const int tw = FEW ? t0 : t0 + wave * 32, t = tw + lr, tc = t < g.T ? t : g.T - 1;
   const bool active = tw < g.T;
   const float *const qrow = qkv + (b * g.T + tc) * 3 * g.D + hc, *const grow = dctx + (b * g.T + tc) * g.D + hc;
   const Own<KS> q = own_floats<KS>(qrow, lk, g.dh);
@@ -366,8 +417,8 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
   }
   D += __shfl_xor(D, 32, 64);
   const float L = lse[(b * g.T + tc) * g.heads + pl.h];
-  if (lk == 0 && t < g.T) dsum[(b * g.T + t) * g.heads + pl.h] = D;
-  const int tlast = t0 + kQ - 1 < g.T ? t0 + kQ - 1 : g.T - 1;
+  if ((!FEW || wave == 0) && lk == 0 && t < g.T) dsum[(b * g.T + t) * g.heads + pl.h] = D;
+  const int tlast = t0 + kRows - 1 < g.T ? t0 + kRows - 1 : g.T - 1;
   const int jmin = (g.left < 0 || t0 - g.left < 0) ? 0 : t0 - g.left;
   const int jmax = (g.right < 0 || tlast + g.right > g.T - 1) ? g.T - 1 : tlast + g.right;
   const int wlo = g.left < 0 ? 0 : t - g.left;
@@ -378,14 +429,22 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
   v16f dq[DB];
 #pragma unroll
   for (int blk = 0; blk < DB; ++blk) dq[blk] = zero16();
-  Raw kr, vr;
+  constexpr int P = FEW ? 4 : 1;   // pieces of a thread
+  Raw kr[P], vr[P];
+  auto thread = [&](int i) { return FEW ? lane + 64 * i : static_cast<int>(threadIdx.x); };
   auto load = [&](int j0) {
-    kr = load_piece(qkv, 3 * g.D, g, b, j0, g.D + hc);
-    vr = load_piece(qkv, 3 * g.D, g, b, j0, 2 * g.D + hc);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      kr[i] = load_piece(qkv, 3 * g.D, g, b, j0, g.D + hc, thread(i));
+      vr[i] = load_piece(qkv, 3 * g.D, g, b, j0, 2 * g.D + hc, thread(i));
+    }
   };
   auto stage = [&](uint8_t *slot, int j0) {
-    stage_piece<4 * DB>(slot, kr, g, j0, true, reinterpret_cast<float *>(slot + 2 * kTensor));
-    stage_piece<2 * KS>(slot + kTensor, vr, g, j0, false);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      stage_piece<4 * DB>(slot, kr[i], g, j0, true, thread(i), reinterpret_cast<float *>(slot + 2 * kTensor));
+      stage_piece<2 * KS>(slot + kTensor, vr[i], g, j0, false, thread(i));
+    }
   };
   auto compute = [&](const uint8_t *slot, int j0) {
     if (!active || j0 > some_hi || j0 + kStep - 1 < some_lo) return;
@@ -409,29 +468,40 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dq_rows_kernel(cons
     add_half(std::integral_constant<int, 0>{});
     add_half(std::integral_constant<int, 1>{});
   };
-  run_tiles(lds, jmin / kStep * kStep, jmax, load, stage, compute);
-  if (!active) return;
-  if (any_nonfinite(dq)) redo_dq(dq, qkv, dctx, lse, dsum, g);
   float *const out = dqkv + (b * g.T + tw) * 3 * g.D + hc;
+  if constexpr (FEW) {
+    run_tiles_apart(lds + wave * kSlot, wave, jmin / kStep * kStep, jmax, [&](uint8_t *slot, int j0) { load(j0); stage(slot, j0); }, compute);
+    v4f v[2];
+    if (!add_shares<DB>(reinterpret_cast<float *>(lds), dq, wave, lane, v)) {
+      store_shares(v, g.scale, out, 3 * g.D, g.T - tw, g.dh);
+      return;
+    }
+    if (wave != 0) return;
+    redo_dq<DB, kRows>(dq, qkv, dctx, lse, dsum, g);
+  } else {
+    run_tiles(lds, jmin / kStep * kStep, jmax, load, stage, compute);
+    if (!active) return;
+    if (any_nonfinite(dq)) redo_dq<DB, kRows>(dq, qkv, dctx, lse, dsum, g);
+  }
   store_rows<DB>(reinterpret_cast<float *>(lds) + wave * 32 * kLd, dq, g.scale, out, 3 * g.D, g.T - tw, g.dh, lane);
 }
 
 // dk / dv: a lane owns a key, the tiles are queries and upstream gradient rows.
-template <int KS>
-__global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(const float *__restrict__ qkv,
+template <int KS, bool FEW = false>
+__global__ __launch_bounds__(kThreads, FEW ? 1 : 2) void attention_bwd_dkv_rows_kernel(const float *__restrict__ qkv,
                                                                               const float *__restrict__ dctx,
                                                                               const float *__restrict__ lse,
                                                                               const float *__restrict__ dsum, AttnShape g,
                                                                               float *__restrict__ dqkv) {
-  constexpr int DB = (KS + 1) / 2;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSlot];
-  __shared__ float Ls[2][kStep], Ds[2][kStep];
+  constexpr int DB = (KS + 1) / 2, kRows = FEW ? 32 : kQ;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[(FEW ? 4 : 2) * kSlot];
+  __shared__ __attribute__((aligned(16))) float Ls[FEW ? 4 : 2][kStep], Ds[FEW ? 4 : 2][kStep];
   const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Place pl = place_of(g, static_cast<int>(blockIdx.x));
+  const Place pl = place_of<kRows>(g, static_cast<int>(blockIdx.x));
   const int64_t b = pl.b, hc = pl.hc;
   const int j0t = pl.r0;
-  const int jw = j0t + wave * 32, j = jw + lr, jc = j < g.T ? j : g.T - 1;
+  const int jw = FEW ? j0t : j0t + wave * 32, j = jw + lr, jc = j < g.T ? j : g.T - 1;
   const bool active = jw < g.T;
   const float *const krow = qkv + (b * g.T + jc) * 3 * g.D + g.D + hc;
   const Own<KS> kk = own_floats<KS>(krow, lk, g.dh);
@@ -443,7 +513,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
     vv[s] = split_own(x, y);
   }
   // query frames that may look at a key of this workgroup / of this wavefront: t - left <= j <= t + right
-  const int jlast = j0t + kQ - 1 < g.T ? j0t + kQ - 1 : g.T - 1;
+  const int jlast = j0t + kRows - 1 < g.T ? j0t + kRows - 1 : g.T - 1;
   const int tmin = (g.right < 0 || j0t - g.right < 0) ? 0 : j0t - g.right;
   const int tmax = (g.left < 0 || jlast + g.left > g.T - 1) ? g.T - 1 : jlast + g.left;
   const int qlo = g.right < 0 ? 0 : j - g.right;
@@ -457,28 +527,37 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
     dk[blk] = zero16();
     dv[blk] = zero16();
   }
-  Raw qr, gr;
+  constexpr int P = FEW ? 4 : 1;   // pieces of a thread
+  Raw qr[P], gr[P];
   float Lr, Dr;
   const int row = static_cast<int>(threadIdx.x & 31);
+  auto thread = [&](int i) { return FEW ? lane + 64 * i : static_cast<int>(threadIdx.x); };
   auto load = [&](int t0) {
-    qr = load_piece(qkv, 3 * g.D, g, b, t0, hc);
-    gr = load_piece(dctx, g.D, g, b, t0, hc);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      qr[i] = load_piece(qkv, 3 * g.D, g, b, t0, hc, thread(i));
+      gr[i] = load_piece(dctx, g.D, g, b, t0, hc, thread(i));
+    }
     const int tt = t0 + row < g.T ? t0 + row : g.T - 1;
     Lr = lse[(b * g.T + tt) * g.heads + pl.h];
     Dr = dsum[(b * g.T + tt) * g.heads + pl.h];
   };
+  auto slot_no = [&](const uint8_t *slot) { return FEW ? wave : slot == lds ? 0 : 1; };
   auto stage = [&](uint8_t *slot, int t0) {
-    stage_piece<4 * DB>(slot, qr, g, t0, true, reinterpret_cast<float *>(slot + 2 * kTensor));
-    stage_piece<4 * DB>(slot + kTensor, gr, g, t0, true);
-    if (threadIdx.x < kStep) {
-      const int at = slot == lds ? 0 : 1;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      stage_piece<4 * DB>(slot, qr[i], g, t0, true, thread(i), reinterpret_cast<float *>(slot + 2 * kTensor));
+      stage_piece<4 * DB>(slot + kTensor, gr[i], g, t0, true, thread(i));
+    }
+    if ((FEW ? lane : static_cast<int>(threadIdx.x)) < kStep) {
+      const int at = slot_no(slot);
       Ls[at][row] = Lr;
       Ds[at][row] = Dr;
     }
   };
   auto compute = [&](const uint8_t *slot, int t0) {
     if (!active || t0 > some_hi || t0 + kStep - 1 < some_lo) return;
-    const int at = slot == lds ? 0 : 1;
+    const int at = slot_no(slot);
     v16f s, dp;
     first_products<KS>(slot, kk, vv, s, dp, lr, lk);   // S: queries x this lane's key; dP
 #pragma unroll
@@ -513,10 +592,24 @@ __global__ __launch_bounds__(kThreads, 2) void attention_bwd_dkv_rows_kernel(con
     add_half(std::integral_constant<int, 0>{});
     add_half(std::integral_constant<int, 1>{});
   };
-  run_tiles(lds, tmin / kStep * kStep, tmax, load, stage, compute);
-  if (!active) return;
-  if (any_nonfinite(dk) || any_nonfinite(dv)) redo_dkv(dk, dv, qkv, dctx, lse, dsum, g);
   float *const out = dqkv + (b * g.T + jw) * 3 * g.D + g.D + hc;
+  if constexpr (FEW) {
+    run_tiles_apart(lds + wave * kSlot, wave, tmin / kStep * kStep, tmax, [&](uint8_t *slot, int t0) { load(t0); stage(slot, t0); }, compute);
+    v4f k[2], v[2];
+    const bool bad_k = add_shares<DB>(reinterpret_cast<float *>(lds), dk, wave, lane, k);
+    const bool bad_v = add_shares<DB>(reinterpret_cast<float *>(lds), dv, wave, lane, v);
+    if (!bad_k && !bad_v) {
+      store_shares(k, g.scale, out, 3 * g.D, g.T - jw, g.dh);
+      store_shares(v, 1.0f, out + g.D, 3 * g.D, g.T - jw, g.dh);
+      return;
+    }
+    if (wave != 0) return;
+    redo_dkv<DB, kRows>(dk, dv, qkv, dctx, lse, dsum, g);
+  } else {
+    run_tiles(lds, tmin / kStep * kStep, tmax, load, stage, compute);
+    if (!active) return;
+    if (any_nonfinite(dk) || any_nonfinite(dv)) redo_dkv<DB, kRows>(dk, dv, qkv, dctx, lse, dsum, g);
+  }
   float *const img = reinterpret_cast<float *>(lds) + wave * 32 * kLd;
   store_rows<DB>(img, dk, g.scale, out, 3 * g.D, g.T - jw, g.dh, lane);
   store_rows<DB>(img, dv, 1.0f, out + g.D, 3 * g.D, g.T - jw, g.dh, lane);
@@ -529,22 +622,36 @@ bool attention_rows_ok(const AttnShape &g, const void *a, const void *b, const v
   return g.T <= 1 << 30 && g.dh % 4 == 0 && g.D % 4 == 0 && aligned(a) && aligned(b) && aligned(c) && aligned(d);
 }
 
-aqt_status launch_attention_bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g,
-                                      float *dqkv, float *dsum, hipStream_t st) {
+template <bool FEW>
+static aqt_status bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g, float *dqkv,
+                           float *dsum, hipStream_t st) {
   const unsigned blocks = static_cast<unsigned>(static_cast<int64_t>(g.qtiles) * g.heads * g.B);
-  auto dq = g.dh <= 16   ? attention_bwd_dq_rows_kernel<1>
-            : g.dh <= 32 ? attention_bwd_dq_rows_kernel<2>
-            : g.dh <= 48 ? attention_bwd_dq_rows_kernel<3>
-                         : attention_bwd_dq_rows_kernel<4>;
+  auto dq = g.dh <= 16   ? attention_bwd_dq_rows_kernel<1, FEW>
+            : g.dh <= 32 ? attention_bwd_dq_rows_kernel<2, FEW>
+            : g.dh <= 48 ? attention_bwd_dq_rows_kernel<3, FEW>
+                         : attention_bwd_dq_rows_kernel<4, FEW>;
   dq<<<blocks, kThreads, 0, st>>>(qkv, ctx, dctx, lse, dsum, g, dqkv);
   AQT_HIP(hipGetLastError());
-  auto dkv = g.dh <= 16   ? attention_bwd_dkv_rows_kernel<1>
-             : g.dh <= 32 ? attention_bwd_dkv_rows_kernel<2>
-             : g.dh <= 48 ? attention_bwd_dkv_rows_kernel<3>
-                          : attention_bwd_dkv_rows_kernel<4>;
+  auto dkv = g.dh <= 16   ? attention_bwd_dkv_rows_kernel<1, FEW>
+             : g.dh <= 32 ? attention_bwd_dkv_rows_kernel<2, FEW>
+             : g.dh <= 48 ? attention_bwd_dkv_rows_kernel<3, FEW>
+                          : attention_bwd_dkv_rows_kernel<4, FEW>;
   dkv<<<blocks, kThreads, 0, st>>>(qkv, dctx, lse, dsum, g, dqkv);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
+}
+
+// FEW while its workgroups (133 KB of LDS, one to a compute unit) run at once, or in two rounds where every row meets many tiles.  In us,
+// 128 rows to a workgroup -> FEW: 8 x 128 frames, 4 heads of 64, causal (128 workgroups) 41 -> 24; 6 x 217, 4 of 36 (168) 50 -> 28; 2 x 1000, 4 of
+// 64 (256) 218 -> 87; two rounds: 4 x 1000, 4 of 64 (512) 221 -> 161, 8 x 417 (448) 103 -> 94, but 16 x 217, 4 of 36 (448) 51 -> 52, 32 x 128 (512)
+// 41 -> 45; four rounds 8 x 1000 223 -> 315.  Errors against float64 are no larger (four partial sums: dq at 2 x 1000 6.7e-7 -> 5.2e-7).
+aqt_status launch_attention_bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g,
+                                      float *dqkv, float *dsum, hipStream_t st) {
+  AttnShape few = g;
+  few.qtiles = static_cast<int>(cdiv(g.T, 32));
+  const int64_t met = g.left < 0 || g.right < 0 ? g.T : static_cast<int64_t>(g.left) + g.right + 1;   // frames that a row meets, at most T
+  if (static_cast<int64_t>(few.qtiles) * g.heads <= (met > 400 && g.T > 400 ? 512 : 256) / g.B) return bwd_rows<true>(qkv, ctx, dctx, lse, few, dqkv, dsum, st);
+  return bwd_rows<false>(qkv, ctx, dctx, lse, g, dqkv, dsum, st);
 }
 
 }  // namespace aqt

@@ -25,6 +25,7 @@ struct Place {
   int64_t b, hc;
   int r0, h;
 };
+template <int ROWS = kQ>   // rows a workgroup owns; g.qtiles of them make an utterance
 __device__ __forceinline__ Place place_of(const AttnShape &g, int block) {
   const int64_t id = block, heads = static_cast<int64_t>(g.heads) * g.B;
   int64_t bh, tile;
@@ -36,7 +37,7 @@ __device__ __forceinline__ Place place_of(const AttnShape &g, int block) {
     tile = id % g.qtiles;
   }
   const int h = static_cast<int>(bh % g.heads);
-  return Place{bh / g.heads, static_cast<int64_t>(h) * g.dh, static_cast<int>(tile) * kQ, h};
+  return Place{bh / g.heads, static_cast<int64_t>(h) * g.dh, static_cast<int>(tile) * ROWS, h};
 }
 
 // The frames that this wavefront's 32 rows (from tw), and this lane's row t, may look at or be seen from:

@@ -402,3 +402,22 @@ def test_small_output_projections_quantize_inside_the_product(T, D, bw):
     x[T // 2, 1] = np.inf
     B.aqt_mhsa_fwd(dev(x), dev(wqkv), None, dev(wo), dev(bo), sv, heads, dev_status=status)
     assert host(status)[0] == B.AQT_ERR_NONFINITE
+
+
+@pytest.mark.parametrize("T,left,right", [(1, -1, -1), (32, 5, 3), (33, -1, -1), (129, 23, 0), (300, -1, 40), (420, -1, -1)])
+@pytest.mark.parametrize("dh", [8, 20, 36, 64])
+def test_backward_of_few_and_of_many_utterances(T, left, right, dh):
+    """A small batch gives 32 rows to a workgroup, whose wavefronts share the tiles, a large one 128: both against the oracle."""
+    from parity_util import check_grad
+    say("backward, few and many", T, left, right, dh)
+    heads = 2
+    D, many = heads * dh, 260
+    rng = np.random.default_rng(696 + T + dh)
+    qkv, dctx = rng.standard_normal((T, 3 * D)).astype(F), rng.standard_normal((T, D)).astype(F)
+    ref, mag = oracle.attention_bwd(qkv.reshape(1, T, 3 * D), dctx.reshape(1, T, D), heads, left, right)
+    for B_ in (1, many):
+        q, g = (dev(a).view(1, T, -1).expand(B_, -1, -1).contiguous().view(B_ * T, -1) for a in (qkv, dctx))
+        lse = torch.empty((B_ * T, heads), device="cuda")
+        ctx, _ = B.aqt_attention_fwd(q, B_, T, heads, left=left, right=right, lse=lse)
+        got = host(B.aqt_attention_bwd(q, ctx, g, lse, B_, T, heads, left=left, right=right))
+        check_grad(got[-T:].reshape(1, T, 3 * D), ref, mag, "dqkv")
