@@ -167,10 +167,17 @@ __global__ __launch_bounds__(kThreads) void attention_fwd_few_kernel(const float
 #pragma unroll
     for (int r = 0; r < 4; ++r) amax = max(amax, __float_as_uint(x[r]) & 0x7FFFFFFFu);
   }
-  if (absmax) {   // uniform: the word only grows, so a stale read can only cost a redundant atomic
+  if (absmax) {   // uniform; one atomic per workgroup, and only if it can raise the word (it only grows)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) amax = max(amax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(amax), off)));
-    if (lane == 0 && amax > *reinterpret_cast<volatile uint32_t *>(absmax)) atomicMax(absmax, amax);
+    __syncthreads();   // the maxima of the scores are no longer read
+    if (lane == 0) most[wave][0] = __uint_as_float(amax);
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+      for (int w = 1; w < 4; ++w) amax = max(amax, __float_as_uint(most[w][0]));
+      if (amax > *reinterpret_cast<volatile uint32_t *>(absmax)) atomicMax(absmax, amax);
+    }
   }
 }
 
