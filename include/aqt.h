@@ -263,6 +263,7 @@ aqt_status aqt_dense_fwd_wonly(const float *x, const void *wq_packed, const floa
  *   saved  nullable; when given, its non-null buffers receive xq, s_x, mask_x,
  *          wq_packed, wq_kn, s_w, mask_w for aqt_dense_bwd.  When NULL the codes
  *          live in the workspace only.
+ * As in that sequence, y and saved->dact may share memory with x or w (y == x, say).
  */
 aqt_status aqt_dense_fwd(const float *x, const float *w, int64_t M, int64_t K, int64_t N, int bits_x,
                          int bits_w, const float *bias, int epilogue, float *y, const aqt_saved *saved,

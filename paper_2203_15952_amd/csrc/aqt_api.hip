@@ -251,10 +251,11 @@ LayerFwdWorkspace carve_layer_fwd(void *ws, int64_t M, int64_t D, int64_t H) {
 }
 
 // The second dense layer of a module: one-pass quantizer, product.  A small problem's product makes the codes itself (it
-// reads the weights in their canonical form either way).
+// reads the weights in their canonical form either way), unless y lies over x: every column tile then reads x while others write y.
 aqt_status quantized_layer(const float *x, const uint32_t *absmax, const aqt_saved &l, const aqt_dense_policy &p, int64_t M, int64_t K,
                            int64_t N, const float *bias, float *y, const WeightSide &side, hipStream_t st, int32_t *dev_status) {
   if (dense_fwd_rows_ok(M, K, N) && !fwd_q_uses_fragments(M, K, N, AQT_EPI_NONE) && !l.mask_x &&
+      !overlap(y, M * N * sizeof(float), x, M * K * sizeof(float)) &&
       reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(l.xq) % 4 == 0)
     return launch_dense_fwd_rows(RowSource{x, absmax, qmax_of(p.bits_x), l.xq, l.s_x, dev_status}, l.wq_packed, l.s_w, M, K, N, p.bits_w,
                                  bias, y, st);
@@ -728,8 +729,14 @@ aqt_status aqt_dense_fwd(const float *x, const float *w, int64_t M, int64_t K, i
                     reinterpret_cast<uintptr_t>(f.wfrag) % 16 == 0;
   const WeightJob job = {w, K, N, bits_w, wq, s_w, saved ? saved->wq_kn : nullptr, saved ? saved->mask_w : nullptr, f.wpart,
                          frag ? f.wfrag : nullptr};
+  // The product takes x and w themselves only where what it writes lies over neither of them nor the maxima: as a launch behind the
+  // quantizers it may be given y == x.
+  auto written = [&](const void *p, size_t n) {
+    return overlap(y, M * N * sizeof(float), p, n) || (saved && overlap(saved->dact, M * N * sizeof(float), p, n));
+  };
   DenseSource src{};
-  const bool raw = dense_fwd_raw_ok(M, K, N, epilogue) && !fwd_q_uses_fragments(M, K, N, epilogue);
+  const bool raw = dense_fwd_raw_ok(M, K, N, epilogue) && !fwd_q_uses_fragments(M, K, N, epilogue) &&
+                   !written(x, M * K * sizeof(float)) && !written(w, K * N * sizeof(float)) && !written(ws, f.total);
   AQT_TRY(launch_quantize_dense(x, M, K, bits_x, xq, s_x, saved ? saved->mask_x : nullptr, f.partials, job, st, dev_status,
                                 raw ? &src : nullptr));
   if (src.xq) return launch_dense_fwd_raw(src, M, K, N, bias, epilogue, y, saved ? saved->dact : nullptr, st);

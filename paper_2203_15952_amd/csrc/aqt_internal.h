@@ -53,6 +53,12 @@ extern thread_local int g_last_hip_error;
 constexpr int kMaxPartials = 4096;  // per-block abs-max slots at the head of a quantize workspace
 constexpr int kWeightSlabs = 16;    // fan-in slabs whose per-channel maxima the weight quantizer folds
 
+// Whether the n bytes at a and the m bytes at b have one in common (a null pointer has none).
+inline bool overlap(const void *a, size_t n, const void *b, size_t m) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+  return a && b && p < q + m && q < p + n;
+}
+
 inline int qmax_of(int bits) { return (1 << (bits - 1)) - 1; }
 inline bool bits_ok(int bits) { return bits >= 2 && bits <= 8; }
 inline bool packed4(int bits_w) { return bits_w <= 4; }
@@ -84,7 +90,8 @@ struct WeightJob {
 constexpr int kWeightJobsMax = 8;
 aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream_t st, int32_t *dev_status);
 struct DenseSource;
-// The activations (per tensor) and the weights of one dense layer; one launch pair where the activations are aligned and want no mask.
+// The activations (per tensor) and the weights of one dense layer; one launch pair where the activations are aligned, want no mask
+// and share no memory with what the weights leave behind (in two pairs x has been read by then).
 aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int bits_x, int8_t *q, float *scale, uint32_t *mask,
                                  float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status,
                                  DenseSource *later = nullptr);   // later: the second launch is described there (xq set) where a product can take it

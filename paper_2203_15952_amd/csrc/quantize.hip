@@ -690,7 +690,10 @@ aqt_status launch_quantize_with_scale(const float *x, int64_t rows, int64_t cols
 
 aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int bits_x, int8_t *q, float *scale, uint32_t *mask,
                                  float *partials, const WeightJob &w, hipStream_t st, int32_t *dev_status, DenseSource *later) {
-  if (mask || !flat_ok(x, cols, cols, q)) {
+  const size_t bytes = static_cast<size_t>(rows) * cols * sizeof(float), wn = static_cast<size_t>(w.K) * w.N;
+  const bool reused = overlap(w.wq_packed, packed4(w.bits_w) ? (w.K + 1) / 2 * w.N : wn, x, bytes) || overlap(w.wq_kn, wn, x, bytes) ||
+                      overlap(w.s_w, w.N * sizeof(float), x, bytes) || overlap(w.mask_w, cdiv(w.K * w.N, 32) * 4, x, bytes);
+  if (mask || reused || !flat_ok(x, cols, cols, q)) {
     AQT_TRY(launch_quantize(x, rows, cols, cols, bits_x, AQT_AXIS_ALL, q, scale, mask, partials, st, dev_status));
     return launch_quantize_weights_group(&w, 1, st, dev_status);
   }

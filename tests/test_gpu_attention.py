@@ -404,6 +404,34 @@ def test_small_output_projections_quantize_inside_the_product(T, D, bw):
     assert host(status)[0] == B.AQT_ERR_NONFINITE
 
 
+@pytest.mark.parametrize("T,D", [(95, 64), (300, 144), (40, 512)])
+def test_modules_may_leave_their_result_over_the_second_layers_input(T, D):
+    """A program that only serves needs neither ctx, s nor h behind the call: y over them is what it is elsewhere."""
+    say("module results over their scratch", T, D)
+    rng = np.random.default_rng(790 + T + D)
+    heads, H = D // 16, 2 * D
+    p = ((8, 8), (8, 8))
+    x, wq, wo, w1, wd, w2, f1, f2 = (dev(rng.standard_normal(s).astype(F)) for s in (
+        (T, D), (D, 3 * D), (D, D), (D, 2 * D), (5, D), (D, D), (D, H), (H, D)))
+
+    def mhsa(over):
+        sv = B.MhsaSaved(1, T, D, p)
+        return B.aqt_mhsa_fwd(x, wq, None, wo, None, sv, heads, y=sv.ctx if over else None)
+
+    def conv(over):
+        sv = B.ConvSaved(1, T, D, p)
+        return B.aqt_conv_module_fwd(x, w1, None, wd, None, w2, None, sv, pad_left=2, y=sv.s if over else None)
+
+    def ffn(over):
+        sv = B.FfnSaved(T, D, H, p)
+        return B.aqt_ffn_fwd(x, f1, None, f2, None, sv, y=sv.h.view(-1)[: T * D].view(T, D) if over else None)
+
+    for call in (mhsa, conv, ffn):
+        want = host(call(False))
+        for _ in range(3):
+            np.testing.assert_array_equal(host(call(True)), want, err_msg=call.__name__)
+
+
 @pytest.mark.parametrize("T,left,right", [(1, -1, -1), (32, 5, 3), (33, -1, -1), (129, 23, 0), (300, -1, 40), (420, -1, -1)])
 @pytest.mark.parametrize("dh", [8, 20, 36, 64])
 def test_backward_of_few_and_of_many_utterances(T, left, right, dh):

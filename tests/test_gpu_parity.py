@@ -224,6 +224,38 @@ def test_small_dense_layers_quantize_inside_the_product(M, K, N, bw, epi):
         t[-1, -1] = keep
 
 
+@pytest.mark.parametrize("M,K,bw,epi", [(256, 256, 4, 0), (40, 64, 8, 1), (1000, 100, 8, 0), (300, 260, 4, 0), (512, 128, 4, 1)])
+@pytest.mark.parametrize("where", ["x", "w", "dact", "codes"])
+def test_dense_fwd_into_its_own_inputs(M, K, bw, epi, where):
+    """What the product writes may lie over x or w, and the weights' codes over x: as the three calls in sequence."""
+    say("dense in place", M, K, bw, epi, where)
+    N, rng = K, np.random.default_rng(43 + M + K)
+    x, w, bias = (dev(rng.standard_normal(s).astype(np.float32)) for s in ((M, K), (K, N), N))
+    B.aqt_dense_fwd(x, w, 8, bw, bias=bias, epilogue=epi, saved=(ref := B.Saved(M, K, N, bw, dact=True)),
+                    y=(want := torch.empty((M, N), device="cuda")))
+    for _ in range(3):
+        both = torch.empty(max(M, K), K, device="cuda")   # y over w needs M rows behind it
+        sv = B.Saved(M, K, N, bw, dact=True)
+        xi, wi, y = x, w, torch.empty((M, N), device="cuda")
+        if where == "w":
+            both[:K] = w
+            wi, y = both[:K], both[:M]
+        else:
+            both[:M] = x
+            xi = both[:M]
+            if where == "x":
+                y = xi
+            elif where == "dact":
+                sv.dact = xi
+            else:
+                sv.wq_kn = both.view(torch.int8).view(-1)[: K * N].view(K, N)
+        B.aqt_dense_fwd(xi, wi, 8, bw, bias=bias, epilogue=epi, y=y, saved=sv.refresh())
+        np.testing.assert_array_equal(host(y), host(want))
+        names = ["xq", "s_x", "wq_packed", "s_w", "wq_kn"] + (["dact"] if epi else [])
+        for name in names:
+            np.testing.assert_array_equal(host(getattr(sv, name)), host(getattr(ref, name)), err_msg=name)
+
+
 @pytest.mark.parametrize("M,K,N,bw,epi", [(300, 128, 256, 4, 1), (200, 256, 512, 8, 2), (16500, 1152, 1024, 4, 0),
                                           (12800, 512, 2048, 4, 1)])
 def test_prepared_weights_serving_path(M, K, N, bw, epi):
