@@ -499,7 +499,15 @@ struct WeightJobsDev {
   int n;
 };
 
-// Which matrix a block belongs to (first[] ascends, first[0] = 0, blockIdx.x < first[n]).
+// A launch holds fewer than 2^32 threads in one dimension, which a matrix of 2^35 elements exceeds: beyond kGridX blocks the grid
+// has rows of kGridX, and the blocks past the last leave at once.
+constexpr unsigned kGridX = 1u << 22;
+dim3 rows_of_blocks(int64_t blocks) {
+  return blocks <= kGridX ? dim3(static_cast<unsigned>(blocks)) : dim3(kGridX, static_cast<unsigned>(cdiv(blocks, kGridX)));
+}
+__device__ __forceinline__ unsigned block_number() { return blockIdx.y * kGridX + blockIdx.x; }
+
+// Which matrix a block belongs to (first[] ascends, first[0] = 0, b < first[n]).
 __device__ __forceinline__ int job_of_block(const unsigned *first, int n, unsigned b) {
   int j = 0;
 #pragma unroll
@@ -508,16 +516,20 @@ __device__ __forceinline__ int job_of_block(const unsigned *first, int n, unsign
 }
 
 __global__ __launch_bounds__(kThreads) void wabsmax_partial_group_kernel(const WeightJobsDev jobs) {
-  const int ji = job_of_block(jobs.first1, jobs.n, blockIdx.x);
+  const unsigned block = block_number();
+  if (block >= jobs.first1[kWeightJobsMax]) return;
+  const int ji = job_of_block(jobs.first1, jobs.n, block);
   const WeightJobDev &j = jobs.job[ji];
-  wabsmax_partial(j, blockIdx.x - jobs.first1[ji]);
+  wabsmax_partial(j, block - jobs.first1[ji]);
 }
 
 __global__ __launch_bounds__(kThreads) void quantize_weights_group_kernel(const WeightJobsDev jobs,
                                                                           int32_t *dev_status) {
-  const int ji = job_of_block(jobs.first2, jobs.n, blockIdx.x);
+  const unsigned block = block_number();
+  if (block >= jobs.first2[kWeightJobsMax]) return;
+  const int ji = job_of_block(jobs.first2, jobs.n, block);
   const WeightJobDev &j = jobs.job[ji];
-  quantize_weights(j, dev_status, blockIdx.x - jobs.first2[ji]);
+  quantize_weights(j, dev_status, block - jobs.first2[ji]);
 }
 
 // The activations and the weights of one dense layer in one launch pair: neither needs the other's abs-max, and at the sizes of a
@@ -534,13 +546,16 @@ struct FlatJobDev {
 };
 template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void absmax_dense_kernel(const FlatJobDev f, const WeightJobDev j, unsigned weight_blocks) {
-  if (blockIdx.x < weight_blocks) wabsmax_partial(j, blockIdx.x);
-  else absmax_flat_body<STREAM>(f.x, f.n, f.per4, f.partial, blockIdx.x - weight_blocks);
+  const unsigned block = block_number();
+  if (block < weight_blocks) wabsmax_partial(j, block);
+  else if (block - weight_blocks < static_cast<unsigned>(f.blocks)) absmax_flat_body<STREAM>(f.x, f.n, f.per4, f.partial, block - weight_blocks);
 }
 __global__ __launch_bounds__(kThreads) void quantize_dense_kernel(const FlatJobDev f, const WeightJobDev j, unsigned weight_blocks,
                                                                   int32_t *dev_status) {
-  if (blockIdx.x < weight_blocks) quantize_weights(j, dev_status, blockIdx.x);
-  else quantize_flat_body(f.x, f.n, f.per4, f.partial, f.blocks, f.qmax, f.q, f.scale, dev_status, blockIdx.x - weight_blocks, f.blocks);
+  const unsigned block = block_number();
+  if (block < weight_blocks) quantize_weights(j, dev_status, block);
+  else if (block - weight_blocks < static_cast<unsigned>(f.blocks))
+    quantize_flat_body(f.x, f.n, f.per4, f.partial, f.blocks, f.qmax, f.q, f.scale, dev_status, block - weight_blocks, f.blocks);
 }
 
 __global__ __launch_bounds__(kThreads) void zero_words_kernel(uint32_t *p, int64_t n) {
@@ -704,7 +719,7 @@ aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int
   AQT_TRY(weight_job(w, st, &j, &b1, &b2));
   if (b1 + f.blocks > 0x7FFFFFFF || b2 + f.blocks > 0x7FFFFFFF) return AQT_ERR_UNSUPPORTED;
   auto pass1 = streams(f.n) ? absmax_dense_kernel<true> : absmax_dense_kernel<false>;
-  pass1<<<static_cast<unsigned>(b1 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b1));
+  pass1<<<rows_of_blocks(b1 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b1));
   AQT_HIP(hipGetLastError());
   auto words = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 4 == 0; };
   if (later && j.vec4 && !w.mask_w && !w.wfrag && words(w.wq_packed) && reinterpret_cast<uintptr_t>(j.part) % 16 == 0) {
@@ -712,7 +727,7 @@ aqt_status launch_quantize_dense(const float *x, int64_t rows, int64_t cols, int
                          dev_status};
     return AQT_OK;
   }
-  quantize_dense_kernel<<<static_cast<unsigned>(b2 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b2), dev_status);
+  quantize_dense_kernel<<<rows_of_blocks(b2 + f.blocks), kThreads, 0, st>>>(f, j, static_cast<unsigned>(b2), dev_status);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }
@@ -737,9 +752,9 @@ aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream
     d.first2[i] = static_cast<unsigned>(b2);
   }
   d.n = n;
-  wabsmax_partial_group_kernel<<<static_cast<unsigned>(b1), kThreads, 0, st>>>(d);
+  wabsmax_partial_group_kernel<<<rows_of_blocks(b1), kThreads, 0, st>>>(d);
   AQT_HIP(hipGetLastError());
-  quantize_weights_group_kernel<<<static_cast<unsigned>(b2), kThreads, 0, st>>>(d, dev_status);
+  quantize_weights_group_kernel<<<rows_of_blocks(b2), kThreads, 0, st>>>(d, dev_status);
   AQT_HIP(hipGetLastError());
   return AQT_OK;
 }

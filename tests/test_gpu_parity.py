@@ -224,6 +224,43 @@ def test_small_dense_layers_quantize_inside_the_product(M, K, N, bw, epi):
         t[-1, -1] = keep
 
 
+def test_weights_of_more_than_two_to_the_35_elements():
+    """More blocks than one grid dimension can hold: 2048 x (2^24 + 64), 137 GB, copies of one matrix side by side."""
+    K, block, copies, rest = 2048, 1 << 16, 1 << 8, 64
+    N = block * copies + rest
+    if torch.cuda.mem_get_info()[0] < 230 << 30:
+        pytest.skip("needs 230 GB of device memory")
+    say("weights", K, N)
+    gen = torch.Generator(device="cuda").manual_seed(44)
+    one = torch.randn((K, block), device="cuda", generator=gen)
+    w = torch.empty((K, N), device="cuda")
+    w[:, : block * copies].unflatten(1, (copies, block)).copy_(one[:, None, :])
+    w[:, block * copies:] = one[:, :rest]
+    ref, s_ref, _, _ = B.aqt_quantize_weights(one, 4, want_kn=False)
+    x = torch.randn((1, K), device="cuda", generator=gen)
+    sv = B.Saved(1, K, block, 4)
+    y_ref = B.aqt_dense_fwd(x, one, 8, 4, saved=sv)
+
+    def check(wq, s_w, y=None):
+        wq = wq.view(N, K // 2)
+        for i in range(copies + 1):
+            n = block if i < copies else rest
+            at = slice(i * block, i * block + n)
+            assert torch.equal(wq[at], ref.view(block, K // 2)[:n]) and torch.equal(s_w[at], s_ref[:n]), i
+            assert y is None or torch.equal(y[0, at], y_ref[0, :n]), i
+
+    wq, s_w, _, _ = B.aqt_quantize_weights(w, 4, want_kn=False)
+    check(wq, s_w)
+    wq.zero_()
+    s_w.zero_()
+    sv.wq_packed, sv.s_w, sv.wq_kn, sv.N = wq, s_w, None, N
+    y = torch.empty((1, N), device="cuda")
+    B.aqt_dense_fwd(x, w, 8, 4, y=y, saved=sv.refresh())
+    check(wq, s_w, y)
+    del w, wq
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("M,K,bw,epi", [(256, 256, 4, 0), (40, 64, 8, 1), (1000, 100, 8, 0), (300, 260, 4, 0), (512, 128, 4, 1)])
 @pytest.mark.parametrize("where", ["x", "w", "dact", "codes"])
 def test_dense_fwd_into_its_own_inputs(M, K, bw, epi, where):
