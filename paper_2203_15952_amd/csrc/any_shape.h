@@ -99,7 +99,8 @@ __device__ __forceinline__ float dw_value(double s, int64_t at, int64_t n, const
 //   WK == 1: all wavefronts share the slices; two LDS slots, so that a slice is staged (and converted) while the one
 //            before it is multiplied, one barrier per slice, loads two slices ahead.
 //   WK > 1:  every wavefront has its own slices wk, wk + WK, ... and its own slot: its LDS operations are executed
-//            in order, so no barrier is needed and the wavefronts overlap as they come.
+//            in order, so no barrier is needed and the wavefronts overlap as they come.  The next slice is requested behind
+//            wave_lds_order: in front of it the backward of 1024 x 256 layers took 1 % longer (16.8 us against 16.6).
 // The loop has no branch around a load (past the end the last slice is requested again): behind a branch the compiler
 // cannot count what is in flight and waits for everything, which undoes the prefetch.
 template <int WK, class Load, class Stage, class Multiply>
@@ -116,16 +117,16 @@ __device__ __forceinline__ void run_slices(uint8_t *lds, int slice_bytes, int wk
     load(set1, at(1));
     for (int64_t i = 0; i < mine; i += 2) {
       stage(set0, at(i), slot);
+      wave_lds_order();
       load(set0, at(i + 2));
-      __builtin_amdgcn_wave_barrier();
       multiply(slot);
       if (i + 1 >= mine) break;
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_order();
       stage(set1, at(i + 1), slot);
+      wave_lds_order();
       load(set1, at(i + 3));
-      __builtin_amdgcn_wave_barrier();
       multiply(slot);
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_order();
     }
     return;
   }
@@ -154,7 +155,7 @@ __device__ __forceinline__ void run_narrow(uint8_t *slot, LoadNarrow load_narrow
   constexpr std::integral_constant<int, 0> set0{};
   load_narrow(set0);
   stage(set0, 0, slot);
-  if (WK > 1) __builtin_amdgcn_wave_barrier();
+  if (WK > 1) wave_lds_order();
   else __syncthreads();
   multiply(slot);
   if (WK == 1) __syncthreads();

@@ -53,6 +53,17 @@ extern thread_local int g_last_hip_error;
 constexpr int kMaxPartials = 4096;  // per-block abs-max slots at the head of a quantize workspace
 constexpr int kWeightSlabs = 16;    // fan-in slabs whose per-channel maxima the weight quantizer folds
 
+#ifdef __HIPCC__
+// What lanes of this wavefront wrote to LDS in front of it, its other lanes may read behind it, and the other way round.  The hardware
+// executes a wavefront's LDS operations in order; the fences keep the compiler from exchanging them (the barrier by itself only
+// binds its scheduling) and cost no instruction.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+#endif
+
 // Whether the n bytes at a and the m bytes at b have one in common (a null pointer has none).
 inline bool overlap(const void *a, size_t n, const void *b, size_t m) {
   const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_fwd_kernel(const float 
         v.z = o[blk][4 * r4 + 2] * inv; v.w = o[blk][4 * r4 + 3] * inv;
         *reinterpret_cast<v4f *>(ot + lr * kLd + 32 * blk + 8 * r4 + 4 * lk) = v;
       }
-    __builtin_amdgcn_wave_barrier();   // the wavefront's own LDS writes above, its own reads below
+    wave_lds_order();   // the wavefront's own LDS writes above, its own reads below
     for (int q = 0; q < 32; ++q) {
       if (tw + q < g.T && lane < g.dh) {
         const float v = ot[q * kLd + lane];
@@ -338,10 +338,10 @@ __device__ __forceinline__ void store_rows(float *ot, const v16f (&acc)[2], floa
       v.z = acc[blk][4 * r4 + 2] * mul; v.w = acc[blk][4 * r4 + 3] * mul;
       *reinterpret_cast<v4f *>(ot + lr * kLd + 32 * blk + 8 * r4 + 4 * lk) = v;
     }
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   for (int q = 0; q < 32; ++q)
     if (row0 + q < rows && lane < dh) out[(row0 + q) * ld_out + lane] = ot[q * kLd + lane];
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
 }
 
 __global__ __launch_bounds__(kThreads) void attention_bwd_dq_kernel(const float *__restrict__ qkv,

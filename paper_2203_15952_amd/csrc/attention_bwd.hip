@@ -192,7 +192,7 @@ __device__ __forceinline__ void store_rows(float *img, const v16f (&acc)[DB], fl
       const v4f v = {acc[blk][4 * r4] * mul, acc[blk][4 * r4 + 1] * mul, acc[blk][4 * r4 + 2] * mul, acc[blk][4 * r4 + 3] * mul};
       *reinterpret_cast<v4f *>(img + lr * kLd + 32 * blk + 8 * r4 + 4 * lk) = v;
     }
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   // sixteen lanes per row, four rows at a time
   const int d = 4 * (lane & 15);
 #pragma unroll
@@ -200,7 +200,7 @@ __device__ __forceinline__ void store_rows(float *img, const v16f (&acc)[DB], fl
     const int q = 4 * q4 + (lane >> 4);
     if (q < rows_left && d < dh) *reinterpret_cast<v4f *>(out + q * ld + d) = *reinterpret_cast<const v4f *>(img + q * kLd + d);
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
 }
 
 template <int DB>
@@ -236,9 +236,9 @@ template <class Bring, class Compute>
 __device__ __forceinline__ void run_tiles_apart(uint8_t *slot, int wave, int first, int last, Bring bring, Compute compute) {
   for (int r0 = first + wave * kStep; r0 <= last; r0 += 4 * kStep) {
     bring(slot, r0);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     compute(slot, r0);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
   }
 }
 // The four wavefronts' shares of 32 rows, in order, into v (row tid / 8, positions 8 (tid % 8) .. + 7); lds: 4 x 32 x kLd floats.

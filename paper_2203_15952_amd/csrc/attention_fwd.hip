@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_fwd_rows_kernel(const f
       for (int r4 = 0; r4 < 4; ++r4)
         *reinterpret_cast<v4f *>(img + lr * kLd + 32 * blk + 8 * r4 + 4 * lk) =
             v4f{o[blk][4 * r4] * inv, o[blk][4 * r4 + 1] * inv, o[blk][4 * r4 + 2] * inv, o[blk][4 * r4 + 3] * inv};
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     const int d = 4 * (lane & 15);   // sixteen lanes per row, four rows at a time
     float *const out = ctx + (pl.b * T + tw) * g.D + pl.hc;
 #pragma unroll

@@ -170,7 +170,7 @@ __device__ __forceinline__ void dense_fwd_any_body(
     if (mine) {
       if constexpr (!FILL::kWeights) {
         stage(set0, wk, lds + wk * kSliceBytes);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
       }
       multiply(lds + wk * kSliceBytes);
     }

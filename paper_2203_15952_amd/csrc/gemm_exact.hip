@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kThreads, 2) void f32_codes_exact_kernel(
     if (PACKED) return static_cast<int>(static_cast<uint32_t>(qr[c >> 1]) << ((c & 1) ? 24 : 28)) >> 28;
     return static_cast<int8_t>(qr[c]);
   };
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   for (int k = 0; k < list.n; k += 4) {   // four entries in turn as the positions of a product
     const double left = list.value(k + eg, f64_row(ec));
     const int at = list.at(k + eg);
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dw_exact_kernel(const int8_t 
   // tile row 16 j + x holds the position of LDS row 16 j + x
   auto position = [&](int row) { return k0 + 4 * (row % G) + row / G; };
   const int el = anew(lane), ec = el & 15, eg = el >> 4;   // the thread's place anew, as in the kernel above
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   for (int k = 0; k < list.n; k += 4) {   // four entries in turn as the positions of a product
     const double left = list.value(k + eg, ec);
     const int8_t *const row = px + static_cast<int64_t>(list.at(k + eg)) * K;

@@ -36,7 +36,7 @@ inline int __syncthreads_or(int p) {
   __syncthreads();
   return any;
 }
-inline void __builtin_amdgcn_wave_barrier() { g_wbar[threadIdx.x >> 6]->arrive_and_wait(); }
+inline void wave_lds_order() { g_wbar[threadIdx.x >> 6]->arrive_and_wait(); }
 // wave shuffle: exchange through a table, in step with the other lanes of the wavefront
 static int g_shfl[1024];
 inline int __shfl_xor(int v, int off, int = 64) {

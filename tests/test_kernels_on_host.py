@@ -89,6 +89,14 @@ def spliced_gemm_any_source():
             read("epilogue.h") + any_ + f64 + exact + driver)
 
 
+def test_lanes_hand_over_lds_behind_fences():
+    """A scheduling barrier alone states no order of memory: every hand-over inside a wavefront goes through wave_lds_order."""
+    sources = {f: open(os.path.join(CSRC, f)).read() for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".h"))}
+    assert [f for f, src in sources.items() if "__builtin_amdgcn_wave_barrier" in src] == ["aqt_internal.h"]
+    assert re.search(r'fence\(__ATOMIC_RELEASE, "wavefront"\);\s+__builtin_amdgcn_wave_barrier\(\);\s+__builtin_amdgcn_fence\('
+                     r'__ATOMIC_ACQUIRE, "wavefront"\);', sources["aqt_internal.h"])
+
+
 def test_conv_kernels_in_bounds_and_correct_on_host(tmp_path):
     build_and_run(tmp_path, "conv_on_host", spliced_source())
 
