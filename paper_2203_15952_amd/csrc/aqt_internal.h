@@ -268,6 +268,7 @@ bool attention_rows_ok(const AttnShape &g, const void *a, const void *b, const v
 bool attention_few_ok(const AttnShape &g);   // ... and so few tiles of 128 queries that attention_few.hip's of 16 are faster
 aqt_status launch_attention_few(const float *qkv, const AttnShape &g, float *ctx, uint32_t *absmax, float *lse, hipStream_t st);
 aqt_status launch_attention_rows(const float *qkv, const AttnShape &g, float *ctx, uint32_t *absmax, float *lse, hipStream_t st);
+bool attention_bwd_few_ok(const AttnShape &g);   // ... whether its form for few workgroups is the faster
 aqt_status launch_attention_bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g,
                                       float *dqkv, float *dsum, hipStream_t st);
 bool attention_shape_ok(int64_t B, int64_t T, int64_t D, int heads);

@@ -641,16 +641,36 @@ static aqt_status bwd_rows(const float *qkv, const float *ctx, const float *dctx
   return AQT_OK;
 }
 
-// FEW while its workgroups (133 KB of LDS, one to a compute unit) run at once, or in two rounds where every row meets many tiles.  In us,
-// 128 rows to a workgroup -> FEW: 8 x 128 frames, 4 heads of 64, causal (128 workgroups) 41 -> 24; 6 x 217, 4 of 36 (168) 50 -> 28; 2 x 1000, 4 of
-// 64 (256) 218 -> 87; two rounds: 4 x 1000, 4 of 64 (512) 221 -> 161, 8 x 417 (448) 103 -> 94, but 16 x 217, 4 of 36 (448) 51 -> 52, 32 x 128 (512)
-// 41 -> 45; four rounds 8 x 1000 223 -> 315.  Errors against float64 are no larger (four partial sums: dq at 2 x 1000 6.7e-7 -> 5.2e-7).
+// FEW: its workgroups take 133 KB of LDS, one to a compute unit.  Times in us or as shares of what 128 rows to a workgroup take.
+// All at once (256 workgroups): ahead as soon as there is a second tile to share.  8 x 128 frames, 4 heads of 64, causal (128) 41 -> 24; 6 x
+//   217, 4 of 36 (168) 50 -> 28; 2 x 1000, 4 of 64 (256) 218 -> 87; 50 x 33, 2 of 4 to 64 (200) 0.90 - 1.01; but 62 x 16, 4 of 64 18.3 -> 22.2
+//   and 100 x 32, 2 of 24 13.7 -> 16.8.
+// In two rounds (512): ahead where rows meet more than 400 frames and the tiles fill the steps of the four wavefronts well, the narrower the
+//   head the later.  480 workgroups, no limits: heads of 64, 401 frames (13 tiles, 4 steps) 0.97, 417 0.92, 1000 0.73; of 48, 401
+//   1.02, 417 0.96; of 24 and 32, 401 1.07 - 1.11, 440 1.04, 480 0.97, 512 0.91 - 0.95; of 4 and 16, 401 1.14, 480 1.03 - 1.05, 512
+//   0.98, 800 (25 tiles, 7 steps) 1.00 - 1.03, 1000 0.90.  A limit makes the rows of a workgroup uneven, which costs 128 of them more: causal
+//   heads of 4, 401 1.05, 480 0.89, of 36, 401 0.91; 200 frames each way, 7 x 1000, 2 of 24 0.82, but 17 x 420, 2 of 4 1.07, of 24 1.02.
+//   Below 400 frames it is ahead at times (9 x 352 81 against 85, 8 x 370 79 and 93, 8 x 288 76 and 71).
+// Four rounds: 8 x 1000 223 -> 315.
+// Errors against float64 are no larger (four partial sums: dq at 2 x 1000 6.7e-7 -> 5.2e-7).
+bool attention_bwd_few_ok(const AttnShape &g) {
+  const int64_t tiles = cdiv(g.T, 32), groups = tiles * g.heads, T = g.T;
+  if (T <= 32 || groups > 512 / g.B) return false;
+  if (groups <= 256 / g.B) return true;
+  const int64_t met = g.left < 0 || g.right < 0 ? T : static_cast<int64_t>(g.left) + g.right + 1;   // frames that a row meets, at most T
+  if (met <= 400 || T <= 400) return false;
+  if ((g.left < 0 || g.left >= T - 1) && (g.right < 0 || g.right >= T - 1))
+    return 10 * tiles > 33 * cdiv(tiles, 4) + (g.dh <= 16 ? 21 : g.dh <= 32 ? 14 : g.dh <= 48 ? 0 : -4);
+  return tiles > 14 || g.dh > (g.left < 0 || g.right < 0 ? 16 : 32);
+}
+
 aqt_status launch_attention_bwd_rows(const float *qkv, const float *ctx, const float *dctx, const float *lse, const AttnShape &g,
                                       float *dqkv, float *dsum, hipStream_t st) {
-  AttnShape few = g;
-  few.qtiles = static_cast<int>(cdiv(g.T, 32));
-  const int64_t met = g.left < 0 || g.right < 0 ? g.T : static_cast<int64_t>(g.left) + g.right + 1;   // frames that a row meets, at most T
-  if (static_cast<int64_t>(few.qtiles) * g.heads <= (met > 400 && g.T > 400 ? 512 : 256) / g.B) return bwd_rows<true>(qkv, ctx, dctx, lse, few, dqkv, dsum, st);
+  if (attention_bwd_few_ok(g)) {
+    AttnShape few = g;
+    few.qtiles = static_cast<int>(cdiv(g.T, 32));
+    return bwd_rows<true>(qkv, ctx, dctx, lse, few, dqkv, dsum, st);
+  }
   return bwd_rows<false>(qkv, ctx, dctx, lse, g, dqkv, dsum, st);
 }
 

@@ -1,0 +1,15 @@
+// Driver of the dispatch rules on the host: the test splices the rules' source in front of this file.  One question a line on the
+// standard input, one answer (0 or 1) a line.
+int main() {
+  using namespace aqt;
+  char what[64];
+  while (scanf("%63s", what) == 1) {
+    long v[6] = {};
+    if (!strcmp(what, "attention_bwd_few")) {   // utterances, frames, heads, head width, left, right
+      for (long &x : v)
+        if (scanf("%ld", &x) != 1) return 1;
+      printf("%d\n", attention_bwd_few_ok(AttnShape{v[0], v[2] * v[3], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], 0, 0.0f, 0.0f}));
+    }
+  }
+  return 0;
+}

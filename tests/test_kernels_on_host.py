@@ -129,3 +129,42 @@ def build_and_run(tmp_path, name, source):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")
     r = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=600)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), (r.stdout[-2000:], r.stderr[-3000:])
+
+
+def rule(name, signature):
+    """One function of a dispatch, from its signature to the brace that closes it."""
+    src = open(os.path.join(CSRC, name)).read()
+    i = src.index(signature)
+    return src[i:src.index("\n}\n", i) + 3]
+
+
+def ask_rules(tmp_path, questions):
+    internal = open(os.path.join(CSRC, "aqt_internal.h")).read()
+    shape = internal[internal.index("struct AttnShape {"):]
+    shape = shape[:shape.index("};") + 2]
+    rules = [rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
+    source = ('#include <stdint.h>\n#include <stdio.h>\n#include <string.h>\nnamespace aqt {\n'
+              'inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }\n' + shape + "\n" + "\n".join(rules) + "\n}\n" +
+              open(os.path.join(HERE, "host_emulation", "rules_driver.cpp")).read())
+    cpp, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    cpp.write_text(source)
+    r = subprocess.run(["g++", "-O1", "-std=c++17", str(cpp), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    r = subprocess.run([str(exe)], input="\n".join(" ".join(str(v) for v in q) for q in questions), capture_output=True, text=True, timeout=60)
+    return [int(v) for v in r.stdout.split()]
+
+
+# utterances, frames, heads, head width, left, right -> whether 32 rows to a workgroup were measured to be the faster
+BWD_FEW = [((25, 16, 4, 4, -1, -1), 0), ((62, 16, 4, 64, -1, -1), 0), ((100, 32, 2, 24, -1, -1), 0), ((1, 1, 1, 4, -1, -1), 0),
+           ((50, 33, 2, 36, -1, -1), 1), ((8, 128, 4, 64, 23, 0), 1), ((2, 1000, 4, 64, -1, -1), 1), ((16, 128, 4, 64, -1, -1), 1),
+           ((19, 128, 4, 64, -1, -1), 0), ((8, 288, 4, 64, -1, -1), 0), ((18, 401, 2, 4, -1, -1), 0), ((18, 401, 2, 24, -1, -1), 0),
+           ((18, 401, 2, 64, -1, -1), 1), ((17, 417, 2, 32, -1, -1), 0), ((17, 417, 2, 48, -1, -1), 1), ((15, 512, 2, 24, -1, -1), 1),
+           ((16, 480, 2, 16, -1, -1), 0), ((7, 1000, 2, 4, -1, -1), 1), ((16, 480, 2, 4, -1, 0), 1), ((18, 401, 2, 4, -1, 0), 0),
+           ((7, 1000, 2, 24, 200, 200), 1), ((17, 420, 2, 4, 200, 200), 0), ((17, 420, 2, 4, 420, 420), 0), ((8, 1000, 4, 64, -1, -1), 0)]
+
+
+def test_dispatch_rules_follow_the_measurements(tmp_path):
+    cases = [(("attention_bwd_few",) + q, want) for q, want in BWD_FEW]
+    got = ask_rules(tmp_path, [q for q, _ in cases])
+    assert len(got) == len(cases)
+    assert [(q, w) for (q, w), g in zip(cases, got) if g != w] == []
