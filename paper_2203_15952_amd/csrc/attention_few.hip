@@ -186,7 +186,20 @@ __global__ __launch_bounds__(kThreads) void attention_fwd_few_kernel(const float
 // As long as all of its workgroups run at once, two to a compute unit (80 KB of LDS each).  In us, tiles of 128 -> here: 6 x 217
 // frames, 4 heads of 36 (336 workgroups) 20.9 -> 12; 8 x 128, 4 heads of 64 (256) 15.4 -> 9.3, what a launch from Python takes;
 // 8 x 128, 8 heads (512) 15.6 -> 14.8; 2 x 1000, 4 heads (504) 85 -> 53; 8 x 217, 8 heads (896) 24 -> 34.
-bool attention_few_ok(const AttnShape &g) { return cdiv(g.T, kQf) * g.heads <= 512 / g.B; }
+// Where two share a compute unit and an utterance is one step of keys, it is behind in two places.  Up to 32 frames one wavefront of the other
+// kernel does an utterance: 25 x 32 ... 63 x 32 frames, 4 heads of 24 7.1 -> 8.4, of 64 8.7 -> 10.4, of 4 6.7 -> 7.0, and 13 to 16 frames
+// where a head fills its steps of 16 positions, of 24 8.0 -> 8.3, of 48 9.4 -> 9.7 (of 36 0.97 - 1.00 of the time, of 64 0.96).  64 frames that all see
+// each other are a tile without masks there: heads of 24 8.4 -> 9.1, of 32 8.4 -> 8.8, of 44 10.2 -> 10.6, of 48 10.4 -> 10.7 (of 36 0.97, of 64 0.97, of 16 0.93).
+// Between them, 33 to 63 frames, 0.87 to 1.04 of the time, most of it below 1; one to a compute unit it is ahead everywhere (31 x
+// 17, 4 heads of 4 6.6 -> 6.0).
+bool attention_few_ok(const AttnShape &g) {
+  const int64_t groups = cdiv(g.T, kQf) * g.heads;
+  if (groups > 512 / g.B) return false;
+  if (groups <= 256 / g.B) return true;
+  const bool fills = g.dh > 16 && (g.dh <= 32 || (g.dh > 40 && g.dh <= 48));
+  const bool whole = g.T == 64 && (g.left < 0 || g.left >= 63) && (g.right < 0 || g.right >= 63);
+  return g.T <= (fills ? 12 : 16) || (g.T > 32 && !(whole && fills));
+}
 
 aqt_status launch_attention_few(const float *qkv, const AttnShape &g, float *ctx, uint32_t *absmax, float *lse, hipStream_t st) {
   const int tiles = static_cast<int>(cdiv(g.T, kQf));

@@ -5,10 +5,11 @@ int main() {
   char what[64];
   while (scanf("%63s", what) == 1) {
     long v[6] = {};
-    if (!strcmp(what, "attention_bwd_few")) {   // utterances, frames, heads, head width, left, right
+    if (!strncmp(what, "attention", 9)) {   // utterances, frames, heads, head width, left, right
       for (long &x : v)
         if (scanf("%ld", &x) != 1) return 1;
-      printf("%d\n", attention_bwd_few_ok(AttnShape{v[0], v[2] * v[3], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], 0, 0.0f, 0.0f}));
+      const AttnShape g{v[0], v[2] * v[3], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], 0, 0.0f, 0.0f};
+      printf("%d\n", !strcmp(what, "attention_few") ? attention_few_ok(g) : attention_bwd_few_ok(g));
     }
   }
   return 0;

@@ -142,7 +142,7 @@ def ask_rules(tmp_path, questions):
     internal = open(os.path.join(CSRC, "aqt_internal.h")).read()
     shape = internal[internal.index("struct AttnShape {"):]
     shape = shape[:shape.index("};") + 2]
-    rules = [rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
+    rules = ["constexpr int kQf = 16;", rule("attention_few.hip", "bool attention_few_ok("), rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
     source = ('#include <stdint.h>\n#include <stdio.h>\n#include <string.h>\nnamespace aqt {\n'
               'inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }\n' + shape + "\n" + "\n".join(rules) + "\n}\n" +
               open(os.path.join(HERE, "host_emulation", "rules_driver.cpp")).read())
@@ -163,8 +163,16 @@ BWD_FEW = [((25, 16, 4, 4, -1, -1), 0), ((62, 16, 4, 64, -1, -1), 0), ((100, 32,
            ((7, 1000, 2, 24, 200, 200), 1), ((17, 420, 2, 4, 200, 200), 0), ((17, 420, 2, 4, 420, 420), 0), ((8, 1000, 4, 64, -1, -1), 0)]
 
 
+# ... -> whether tiles of 16 queries were
+FWD_FEW = [((6, 217, 4, 36, -1, -1), 1), ((8, 128, 8, 64, -1, -1), 1), ((8, 217, 8, 64, -1, -1), 0), ((31, 32, 4, 24, -1, -1), 1),
+           ((50, 32, 4, 24, -1, -1), 0), ((37, 17, 4, 64, -1, -1), 0), ((50, 32, 4, 4, 23, 0), 0), ((33, 48, 4, 24, -1, -1), 1),
+           ((25, 64, 4, 48, -1, -1), 0), ((25, 64, 4, 48, 23, 0), 1), ((25, 64, 4, 24, 63, 64), 0), ((25, 64, 4, 64, -1, -1), 1),
+           ((25, 64, 4, 16, -1, -1), 1), ((100, 16, 4, 36, -1, -1), 1), ((100, 16, 4, 48, -1, -1), 0), ((100, 8, 4, 48, -1, -1), 1),
+           ((1, 40, 8, 64, 23, 0), 1), ((25, 65, 4, 24, -1, -1), 1)]
+
+
 def test_dispatch_rules_follow_the_measurements(tmp_path):
-    cases = [(("attention_bwd_few",) + q, want) for q, want in BWD_FEW]
+    cases = [(("attention_bwd_few",) + q, want) for q, want in BWD_FEW] + [(("attention_few",) + q, want) for q, want in FWD_FEW]
     got = ask_rules(tmp_path, [q for q, _ in cases])
     assert len(got) == len(cases)
     assert [(q, w) for (q, w), g in zip(cases, got) if g != w] == []
