@@ -980,7 +980,7 @@ struct FillDense {
         if (!(fabsf(ws) < INFINITY) && s.dev_status) *s.dev_status = AQT_ERR_NONFINITE;
       }
       const Quantizer qw = quantizer(ws, fw);
-codes[e] = quant4(wv[0][e], wv[1][e], wv[2][e], wv[3][e], qw);
+      codes[e] = quant4(wv[0][e], wv[1][e], wv[2][e], wv[3][e], qw);
       if (kw < K) *reinterpret_cast<uint32_t *>(lds + (kw >> 6) * slice_bytes + 32 * 64 + chunk_at<4>(4 * nb + e, (kw & 63) >> 4) + (kw & 15)) = codes[e];
     }
     if (bm == 0 && channels && kw < K) {
@@ -1087,9 +1087,17 @@ aqt_status launch_dense_fwd_any(const int8_t *xq, const float *s_x, const void *
                          : fwd_any_sized<false>(xq, s_x, wq_packed, s_w, M, K, N, bias, epilogue, y, acc_out, y_absmax, dact, st);
 }
 
-// Rows of whole 16-byte pieces that the eight wavefronts hold as one slice each, and where the split contraction is picked anyhow.
+// Rows of whole 16-byte pieces that the eight wavefronts hold as one slice each, and where the split contraction is picked anyhow.  Above six
+// slices the conversions pay while every workgroup has a compute unit to itself, and two to a unit where many column tiles find the
+// rows in their cache.  A module, quantizer and product apart -> in one launch, us: convolution, 5000 x 144 (785 workgroups) 36.5 -> 34.3, 2600 x 256
+// (656) 31.9 -> 31.6, 2600 x 320 (820) 37.6 -> 37.3, 600 x 400 (247) 26.0 -> 24.7, 200 x 512 (112) 23.5 -> 22.3, 800 x 448 (350) 30.0 -> 29.5,
+// 1200 x 400 (494) 34.3 -> 33.9, but 600 x 512 (304) 29.2 -> 29.8, 1302 x 512 (656) 35.6 -> 37.2, 1580 x 400 (650) 36.6 -> 37.6; feed-forward,
+// fan-in 384 -> 96, 6000 rows (564) 34.3 -> 33.6, 512 -> 128, 1302 (164) 25.0 -> 23.9, but 2600 (328) 26.6 -> 28.5, 480 -> 120, 4000 (500)
+// 29.5 -> 32.6, 400 -> 100, 4000 (500) 28.9 -> 30.7.
 bool dense_fwd_rows_ok(int64_t M, int64_t K, int64_t N) {
-  return K >= 64 && K <= 512 && K % 4 == 0 && pick_tile(M, N, K, AQT_EPI_NONE, false) == Tile::kSmallest;
+  const int64_t tiles = cdiv(M, 32) * cdiv(N, 32);
+  return K >= 64 && K <= 512 && K % 4 == 0 && pick_tile(M, N, K, AQT_EPI_NONE, false) == Tile::kSmallest &&
+         (K <= 384 || tiles <= 256 || (K <= 480 && tiles <= 512 && 2 * N >= K));
 }
 aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, const float *s_w, int64_t M, int64_t K, int64_t N,
                                  int bits_w, const float *bias, float *y, hipStream_t st) {
@@ -1101,10 +1109,11 @@ aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, co
   return AQT_OK;
 }
 
-// Where each workgroup still has half a compute unit to itself: the product with both quantizers in it takes as long as the two launches
-// (256 x 256 -> 1024 10.0 us of chained launches for the layer -> 9.9, 24 x 128 -> 2048 9.5 -> 8.6, 32 x 64 -> 64 8.8 -> 7.6), and the call of three launches,
-// which the host bounds, becomes one of two: 15.4 -> 12.2 us at 256 x 256 -> 1024 from Python.  Beyond, the repeated conversions cost more:
-// 700 x 252 -> 1000 (704 workgroups) 13.2 -> 16.5, and fan-ins of up to 512 spill (256 x 512 -> 1024 10.6 -> 18.7).
+// While every workgroup has a compute unit to itself.  The two launches apart -> in one (chained launches of a whole layer, us), at 256
+// workgroups: 256 x 64 -> 1024 10.2 -> 8.9, 256 x 128 10.5 -> 9.5, 256 x 256 10.7 -> 10.3, 2048 x 256 -> 128 10.9 -> 10.1; at 32: 40 x 256 -> 512 10.1 -> 9.5;
+// the call of three launches, which the host bounds, becomes one of two: 15.4 -> 12.2 us at 256 x 256 -> 1024 from Python.  Two to a compute
+// unit: at 512, fan-ins of 64 10.8 -> 10.8 and 128 11.0 -> 11.1, but 192 11.1 -> 11.7 and 256 11.4 -> 12.0; at 259, 64 10.8 -> 10.2, 128
+// 10.9 -> 10.9, 256 11.5 -> 11.9; 700 x 252 -> 1000 (704) 13.2 -> 16.5.  Fan-ins of up to 512 spill (256 x 512 -> 1024 10.6 -> 18.7).
 bool dense_fwd_raw_ok(int64_t M, int64_t K, int64_t N, int epilogue) {
   return epilogue != AQT_EPI_GLU && N % 4 == 0 && K <= 256 && cdiv(M, 32) * cdiv(N, 32) <= 256 && dense_fwd_rows_ok(M, K, N);
 }

@@ -10,6 +10,10 @@ int main() {
         if (scanf("%ld", &x) != 1) return 1;
       const AttnShape g{v[0], v[2] * v[3], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], 0, 0.0f, 0.0f};
       printf("%d\n", !strcmp(what, "attention_few") ? attention_few_ok(g) : attention_bwd_few_ok(g));
+    } else {   // rows, fan-in, columns
+      for (int i = 0; i < 3; ++i)
+        if (scanf("%ld", v + i) != 1) return 1;
+      printf("%d\n", dense_fwd_rows_ok(v[0], v[1], v[2]));
     }
   }
   return 0;

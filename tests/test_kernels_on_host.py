@@ -142,13 +142,14 @@ def ask_rules(tmp_path, questions):
     internal = open(os.path.join(CSRC, "aqt_internal.h")).read()
     shape = internal[internal.index("struct AttnShape {"):]
     shape = shape[:shape.index("};") + 2]
-    rules = ["constexpr int kQf = 16;", rule("attention_few.hip", "bool attention_few_ok("), rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
-    source = ('#include <stdint.h>\n#include <stdio.h>\n#include <string.h>\nnamespace aqt {\n'
+    enum = re.search(r"^enum class Tile .*$", open(os.path.join(CSRC, "gemm_any.hip")).read(), flags=re.M).group(0)
+    rules = [enum, rule("gemm_any.hip", "Tile pick_tile("), rule("gemm_any.hip", "bool dense_fwd_rows_ok("), "constexpr int kQf = 16;", rule("attention_few.hip", "bool attention_few_ok("), rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
+    source = ('#include <stdint.h>\n#include <stdio.h>\n#include <string.h>\n#include "aqt.h"\nnamespace aqt {\n'
               'inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }\n' + shape + "\n" + "\n".join(rules) + "\n}\n" +
               open(os.path.join(HERE, "host_emulation", "rules_driver.cpp")).read())
     cpp, exe = tmp_path / "rules.cpp", tmp_path / "rules"
     cpp.write_text(source)
-    r = subprocess.run(["g++", "-O1", "-std=c++17", str(cpp), "-o", str(exe)], capture_output=True, text=True)
+    r = subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), str(cpp), "-o", str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     r = subprocess.run([str(exe)], input="\n".join(" ".join(str(v) for v in q) for q in questions), capture_output=True, text=True, timeout=60)
     return [int(v) for v in r.stdout.split()]
@@ -171,8 +172,15 @@ FWD_FEW = [((6, 217, 4, 36, -1, -1), 1), ((8, 128, 8, 64, -1, -1), 1), ((8, 217,
            ((1, 40, 8, 64, 23, 0), 1), ((25, 65, 4, 24, -1, -1), 1)]
 
 
+# rows, fan-in, columns -> whether the product that makes its own codes was the faster
+OWN_CODES = [((5000, 144, 144), 1), ((2600, 256, 256), 1), ((2000, 320, 320), 1), ((6000, 384, 96), 1), ((600, 400, 400), 1),
+             ((1302, 512, 128), 1), ((40, 512, 512), 1), ((2600, 512, 128), 0), ((4000, 480, 120), 0), ((4000, 400, 100), 0),
+             ((1302, 512, 512), 0), ((600, 512, 512), 0), ((800, 448, 448), 1), ((1200, 400, 400), 1), ((1580, 400, 400), 0), ((40, 516, 64), 0), ((40, 60, 64), 0), ((3000, 128, 512), 0)]
+
+
 def test_dispatch_rules_follow_the_measurements(tmp_path):
     cases = [(("attention_bwd_few",) + q, want) for q, want in BWD_FEW] + [(("attention_few",) + q, want) for q, want in FWD_FEW]
+    cases += [(("own_codes",) + q, want) for q, want in OWN_CODES]
     got = ask_rules(tmp_path, [q for q, _ in cases])
     assert len(got) == len(cases)
     assert [(q, w) for (q, w), g in zip(cases, got) if g != w] == []
