@@ -550,6 +550,16 @@ int grid_cap(int64_t items, int per_block, int cap) {
   return static_cast<int>(g);
 }
 
+// Workgroups of both passes, a row to a wavefront.  As many rows for every wavefront, if fewer wavefronts, where a row is held in registers and
+// the next requested ahead (8193 x 512 15.4 -> 13.1 us for both passes, 24577 x 512 29.7 -> 25.9).  Rows that are walked several times want
+// every wavefront that fits if they are long (10008 x 2048 97.6, with even shares 107.7; 17000 x 1001 101 and 104) or hardly any is left for the
+// last round (24577 x 257 40.1 and 42.3); between, even shares again: 10008 x 1028 50.7 and 46.4, 17000 x 257 29.8 and 26.9.
+int layernorm_blocks(int64_t M, int64_t D, bool vec) {
+  const int64_t g = grid_cap(M, 4, 2048);
+  const bool held = vec && D <= 1024;
+  return static_cast<int>(held || (D <= (vec ? 1280 : 512) && M % 8192 > 512) ? cdiv(M, 4 * cdiv(M, 4 * g)) : g);
+}
+
 }  // namespace
 
 size_t layernorm_ws_bytes(int64_t M) {
@@ -564,12 +574,11 @@ aqt_status launch_layernorm_quantize(const float *x, int64_t M, int64_t D, const
   float *stats = row_stats ? row_stats
                            : reinterpret_cast<float *>(static_cast<uint8_t *>(ws) +
                                                        align_up(kMaxPartials * sizeof(uint32_t), 256));
-  int g = grid_cap(M, 4, 2048);
-  g = static_cast<int>(cdiv(M, 4 * cdiv(M, 4 * static_cast<int64_t>(g))));   // as many rows for every wavefront
   const bool vec = (D % 4 == 0) && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                    (!y_out || reinterpret_cast<uintptr_t>(y_out) % 16 == 0) &&
                    (!q || reinterpret_cast<uintptr_t>(q) % 4 == 0) &&
                    (!res || (reinterpret_cast<uintptr_t>(res) % 16 == 0 && reinterpret_cast<uintptr_t>(sum_out) % 16 == 0));
+  const int g = layernorm_blocks(M, D, vec);
   float *const y_once = vec && D <= 1024 && !q ? y_out : nullptr;
   if (vec && D <= 512) ln_stats_kernel<2><<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, eps, stats, partial, res, alpha, sum_out, zero_word, y_once, dev_status);
   else if (vec && D <= 1024) ln_stats_kernel<4><<<g, kThreads, 0, st>>>(x, M, D, gamma, beta, eps, stats, partial, res, alpha, sum_out, zero_word, y_once, dev_status);

@@ -143,7 +143,8 @@ def ask_rules(tmp_path, questions):
     shape = internal[internal.index("struct AttnShape {"):]
     shape = shape[:shape.index("};") + 2]
     enum = re.search(r"^enum class Tile .*$", open(os.path.join(CSRC, "gemm_any.hip")).read(), flags=re.M).group(0)
-    rules = [enum, rule("gemm_any.hip", "Tile pick_tile("), rule("gemm_any.hip", "bool dense_fwd_rows_ok("), "constexpr int kQf = 16;", rule("attention_few.hip", "bool attention_few_ok("), rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
+    rules = [enum, rule("gemm_any.hip", "Tile pick_tile("), rule("gemm_any.hip", "bool dense_fwd_rows_ok("), rule("block.hip", "int grid_cap("),
+             rule("block.hip", "int layernorm_blocks("), "constexpr int kQf = 16;", rule("attention_few.hip", "bool attention_few_ok("), rule("attention_bwd.hip", "bool attention_bwd_few_ok(")]
     source = ('#include <stdint.h>\n#include <stdio.h>\n#include <string.h>\n#include "aqt.h"\nnamespace aqt {\n'
               'inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }\n' + shape + "\n" + "\n".join(rules) + "\n}\n" +
               open(os.path.join(HERE, "host_emulation", "rules_driver.cpp")).read())
@@ -178,9 +179,14 @@ OWN_CODES = [((5000, 144, 144), 1), ((2600, 256, 256), 1), ((2000, 320, 320), 1)
              ((1302, 512, 512), 0), ((600, 512, 512), 0), ((800, 448, 448), 1), ((1200, 400, 400), 1), ((1580, 400, 400), 0), ((40, 516, 64), 0), ((40, 60, 64), 0), ((3000, 128, 512), 0)]
 
 
+# rows, width, whether in pieces of 16 bytes -> workgroups of the normalisation's two passes, 2048 (8192 wavefronts) where even shares were slower
+LN_BLOCKS = [((1, 512, 1), 1), ((8193, 512, 1), 1025), ((24577, 512, 1), 1537), ((10008, 1028, 1), 1251), ((10008, 2048, 1), 2048),
+             ((24577, 1501, 0), 2048), ((24577, 257, 0), 2048), ((17000, 257, 0), 1417), ((9000, 1500, 1), 2048), ((40, 2048, 1), 10)]
+
+
 def test_dispatch_rules_follow_the_measurements(tmp_path):
     cases = [(("attention_bwd_few",) + q, want) for q, want in BWD_FEW] + [(("attention_few",) + q, want) for q, want in FWD_FEW]
-    cases += [(("own_codes",) + q, want) for q, want in OWN_CODES]
+    cases += [(("own_codes",) + q, want) for q, want in OWN_CODES] + [(("layernorm_blocks",) + q, want) for q, want in LN_BLOCKS]
     got = ask_rules(tmp_path, [q for q, _ in cases])
     assert len(got) == len(cases)
     assert [(q, w) for (q, w), g in zip(cases, got) if g != w] == []
