@@ -7,6 +7,8 @@
 // per-tensor path reads the tensor twice (reduce, then quantize; the second pass
 // walks the tensor backwards, so what the first pass touched last is read first)
 // and writes one byte per element.
+#include <type_traits>
+
 #include "aqt_internal.h"
 #include "quant_code.h"
 
@@ -303,7 +305,9 @@ __device__ __forceinline__ void wabsmax_partial_body(const float *__restrict__ w
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int64_t n = static_cast<int64_t>(bx) * 64 + tx;
   uint32_t m = 0;
-  if (n < N)
+  if (k1 - k0 <= 4) {
+    if (n < N && k0 + ty < k1) m = abs_bits(w[(k0 + ty) * N + n]);
+  } else if (n < N)
     for (int64_t k = k0 + ty; k < k1; k += 32) {   // eight loads in flight, the slab's last row again behind its end
       uint32_t v[8];
 #pragma unroll
@@ -320,7 +324,8 @@ __device__ __forceinline__ void wabsmax_partial_body(const float *__restrict__ w
 // Bound by latency: a tile is 8 KB, so what counts is how many trips to memory follow one another.  All of a thread's loads are
 // requested before the first is used (the fold of the slab maxima alone was sixteen trips in a row: 10.2 us at 520 x 1000, see
 // quantize_dense_kernel for what is left), the [K,N] codes leave four at a time and the operand's rows as whole words where the
-// widths allow it.
+// widths allow it.  A tile of up to 16 rows (a short fan-in, the end of a long one) has a channel to a thread, so that all of them divide, and
+// nothing requests or packs rows that are not there: both launches at 8 x 8192 7.1 -> 6.2 us, 1 x 65536 11.1 -> 8.4, 65 x 65536 24.0 -> 21.9.
 __device__ __forceinline__ void quantize_weights_body(
     const float *__restrict__ w, int64_t K, int64_t N, int qmax, int packed, const uint32_t *__restrict__ part,
     int slabs, uint8_t *__restrict__ wq_packed, float *__restrict__ s_w, int8_t *__restrict__ wq_kn,
@@ -332,16 +337,23 @@ __device__ __forceinline__ void quantize_weights_body(
   const float fq = static_cast<float>(qmax);
   // this thread's values: four channels of rows ty, ty + 32, or one channel of rows ty + 8 j (the last row or channel again beyond the end)
   const int vx = threadIdx.x & 7, vy = threadIdx.x >> 3, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int rows = static_cast<int>(min(K - k0, static_cast<int64_t>(kWChunk)));   // uniform, as the next
+  const bool quads = vec4 && rows > 16;
   float v[8];
-  if (vec4) {
+  if (quads) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      if (32 * j >= rows) continue;
       const float4 a = *reinterpret_cast<const float4 *>(w + min(k0 + vy + 32 * j, K - 1) * N + min(n0 + 4 * vx, N - 4));
       v[4 * j] = a.x; v[4 * j + 1] = a.y; v[4 * j + 2] = a.z; v[4 * j + 3] = a.w;
     }
   } else {
+    auto load = [&](auto count) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = w[min(k0 + ty + 8 * j, K - 1) * N + min(n0 + tx, N - 1)];
+      for (int j = 0; j < decltype(count)::value; ++j) v[j] = w[min(k0 + ty + 8 * j, K - 1) * N + min(n0 + tx, N - 1)];
+    };
+    if (rows > 16) load(std::integral_constant<int, 8>{});
+    else load(std::integral_constant<int, 2>{});
   }
   {
     uint32_t m[kWeightSlabs / 8];
@@ -364,12 +376,13 @@ __device__ __forceinline__ void quantize_weights_body(
   }
   // Mask words straddle threads; bits are set with an atomic OR on a buffer the launcher has zeroed.
   auto mark = [&](int64_t at) { atomicOr(&mask_w[at >> 5], 1u << (at & 31)); };
-  if (vec4) {
+  if (quads) {
     float s[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) s[c] = scale_of(4 * vx + c);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      if (32 * j >= rows) continue;
       const int kk = vy + 32 * j;
       const int64_t k = k0 + kk, n = n0 + 4 * vx;
       const bool live = k < K && n < N;   // four channels at once: N is a multiple of four
@@ -387,19 +400,23 @@ __device__ __forceinline__ void quantize_weights_body(
   } else {
     const float s = scale_of(tx);
     const int64_t n = n0 + tx;
+    auto make = [&](auto count) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int kk = ty + 8 * j;
-      const int64_t k = k0 + kk;
-      int code = 0;
-      if (n < N && k < K) {
-        bool pass;
-        code = quant_code(v[j], s, fq, pass);
-        if (wq_kn) wq_kn[k * N + n] = static_cast<int8_t>(code);
-        if (mask_w && pass) mark(k * N + n);
+      for (int j = 0; j < decltype(count)::value; ++j) {
+        const int kk = ty + 8 * j;
+        const int64_t k = k0 + kk;
+        int code = 0;
+        if (n < N && k < K) {
+          bool pass;
+          code = quant_code(v[j], s, fq, pass);
+          if (wq_kn) wq_kn[k * N + n] = static_cast<int8_t>(code);
+          if (mask_w && pass) mark(k * N + n);
+        }
+        tile[tx][kk] = static_cast<int8_t>(code);
       }
-      tile[tx][kk] = static_cast<int8_t>(code);
-    }
+    };
+    if (rows > 16) make(std::integral_constant<int, 8>{});
+    else make(std::integral_constant<int, 2>{});
   }
   __syncthreads();
   // 32 rows x (64 | 32) output bytes
@@ -420,6 +437,10 @@ __device__ __forceinline__ void quantize_weights_body(
       for (int b = 0; b < 4; ++b) t |= byte_of(rn, 4 * jw + b) << (8 * b);
       *reinterpret_cast<uint32_t *>(wq_packed + (n0 + rn) * row_bytes + b0 + 4 * jw) = t;
     }
+  } else if (row_bytes - b0 <= 16) {
+    const int rn = vy;
+    for (int jb = vx; jb < row_bytes - b0; jb += 8)
+      if (n0 + rn < N) wq_packed[(n0 + rn) * row_bytes + b0 + jb] = static_cast<uint8_t>(byte_of(rn, jb));
   } else {
     for (int i = threadIdx.x; i < kWCols * bytes_per_row; i += kThreads) {
       const int rn = packed ? i >> 5 : i >> 6, jb = i & (bytes_per_row - 1);
@@ -530,6 +551,16 @@ __global__ __launch_bounds__(kThreads) void quantize_weights_group_kernel(const 
   const int ji = job_of_block(jobs.first2, jobs.n, block);
   const WeightJobDev &j = jobs.job[ji];
   quantize_weights(j, dev_status, block - jobs.first2[ji]);
+}
+
+// One matrix: its description is an argument by itself, not one trip behind the list's block numbers (both launches, 64 x 1000 7.4 -> 7.0 us).
+__global__ __launch_bounds__(kThreads) void wabsmax_partial_kernel(const WeightJobDev j, unsigned blocks) {
+  const unsigned block = block_number();
+  if (block < blocks) wabsmax_partial(j, block);
+}
+__global__ __launch_bounds__(kThreads) void quantize_weights_kernel(const WeightJobDev j, unsigned blocks, int32_t *dev_status) {
+  const unsigned block = block_number();
+  if (block < blocks) quantize_weights(j, dev_status, block);
 }
 
 // The activations and the weights of one dense layer in one launch pair: neither needs the other's abs-max, and at the sizes of a
@@ -752,6 +783,13 @@ aqt_status launch_quantize_weights_group(const WeightJob *jobs, int n, hipStream
     d.first2[i] = static_cast<unsigned>(b2);
   }
   d.n = n;
+  if (n == 1) {
+    wabsmax_partial_kernel<<<rows_of_blocks(b1), kThreads, 0, st>>>(d.job[0], static_cast<unsigned>(b1));
+    AQT_HIP(hipGetLastError());
+    quantize_weights_kernel<<<rows_of_blocks(b2), kThreads, 0, st>>>(d.job[0], static_cast<unsigned>(b2), dev_status);
+    AQT_HIP(hipGetLastError());
+    return AQT_OK;
+  }
   wabsmax_partial_group_kernel<<<rows_of_blocks(b1), kThreads, 0, st>>>(d);
   AQT_HIP(hipGetLastError());
   quantize_weights_group_kernel<<<rows_of_blocks(b2), kThreads, 0, st>>>(d, dev_status);

@@ -363,7 +363,7 @@ def test_gradients_of_a_softmax_cost_at_most_a_second_plane():
 
 
 @pytest.mark.parametrize("M,K,N,bw", [(1, 1, 1, 8), (5, 64, 32, 4), (33, 70, 36, 8), (130, 2, 4, 4), (3, 517, 130, 4), (7, 1030, 8, 4),
-                                      (9, 63, 31, 8), (2100, 65, 68, 8)])
+                                      (9, 63, 31, 8), (2100, 65, 68, 8), (3, 8, 36, 4), (2, 16, 40, 8), (2, 17, 33, 4), (4, 80, 64, 4), (4, 81, 31, 8)])
 @pytest.mark.parametrize("off", [0, 1])   # elements by which the weights and their [K,N] codes are off their alignment
 def test_layer_quantizers_in_one_launch_pair(M, K, N, bw, off):
     import torch

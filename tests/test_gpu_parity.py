@@ -132,7 +132,7 @@ def test_quantize_with_scale_saturates_and_masks():
         np.testing.assert_array_equal(unpack_mask(host(mask), x.size), m_ref.reshape(-1))
 
 
-@pytest.mark.parametrize("K,N", [(512, 2048), (256, 1024), (67, 45), (1, 1), (5, 33), (130, 31)])
+@pytest.mark.parametrize("K,N", [(512, 2048), (256, 1024), (67, 45), (1, 1), (5, 33), (130, 31), (8, 64), (16, 36), (17, 33), (81, 64)])
 @pytest.mark.parametrize("bits_w", [4, 8])
 def test_quantize_weights_layouts(K, N, bits_w):
     say("quantize weights", K, N, bits_w)
