@@ -4,7 +4,8 @@
 // reciprocal's half ulp, one rounding) and so is the defined expression (two roundings): both have the same floor unless u lies
 // within 2^-13 of a whole number, and the four values of a lane of which one does are divided (one quad in a thousand).  Beyond 128 both clamp.
 // With the loads that a block waits for first requested together: 65536 x 2048, both passes 205.5 -> 194.5 us; one pass of 12800 x
-// 2048 26 -> 23, the normalisation's quantizer of 12800 x 512 13 -> 10.5, of 65536 x 512 39 -> 32.
+// 2048 26 -> 23, the normalisation's quantizer of 12800 x 512 13 -> 10.5, of 65536 x 512 39 -> 32.  The flat quantizer asks once for four quads: a
+// branch at each had cost tensors of one block more than the divides (4096 elements, both passes 4.55 -> 4.77 us; so 4.3).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -48,18 +49,23 @@ __device__ __forceinline__ uint32_t pack_codes(float a, float b, float c, float 
   const uint32_t z = static_cast<uint32_t>(static_cast<int>(c)) & 0xFFu, w = static_cast<uint32_t>(static_cast<int>(d));
   return x | (y << 8) | (z << 16) | (w << 24);
 }
-// Four codes, the first in the lowest byte.
-__device__ __forceinline__ uint32_t quant4(float x, float y, float z, float w, const Quantizer &k) {
-  if (k.near_one) {
-    const float a = fmaf(x, k.r, 0.5f), b = fmaf(y, k.r, 0.5f), c = fmaf(z, k.r, 0.5f), d = fmaf(w, k.r, 0.5f);
-    const float ea = fabsf(__builtin_amdgcn_fractf(a) - 0.5f), eb = fabsf(__builtin_amdgcn_fractf(b) - 0.5f);
-    const float ec = fabsf(__builtin_amdgcn_fractf(c) - 0.5f), ed = fabsf(__builtin_amdgcn_fractf(d) - 0.5f);
-    if (!(fmaxf(fmaxf(ea, eb), fmaxf(ec, ed)) > 0.5f - 0x1p-13f)) {
-      auto clamp = [&](float u) { return fminf(fmaxf(floorf(u), -k.fq), k.fq); };
-      return pack_codes(clamp(a), clamp(b), clamp(c), clamp(d));
-    }
-  }
+// Four codes by the reciprocal, the first in the lowest byte; false: one of the values lies too near a whole number.
+__device__ __forceinline__ bool quant4_certain(float x, float y, float z, float w, const Quantizer &k, uint32_t &codes) {
+  const float a = fmaf(x, k.r, 0.5f), b = fmaf(y, k.r, 0.5f), c = fmaf(z, k.r, 0.5f), d = fmaf(w, k.r, 0.5f);
+  const float ea = fabsf(__builtin_amdgcn_fractf(a) - 0.5f), eb = fabsf(__builtin_amdgcn_fractf(b) - 0.5f);
+  const float ec = fabsf(__builtin_amdgcn_fractf(c) - 0.5f), ed = fabsf(__builtin_amdgcn_fractf(d) - 0.5f);
+  auto clamp = [&](float u) { return fminf(fmaxf(floorf(u), -k.fq), k.fq); };
+  codes = pack_codes(clamp(a), clamp(b), clamp(c), clamp(d));
+  return !(fmaxf(fmaxf(ea, eb), fmaxf(ec, ed)) > 0.5f - 0x1p-13f);
+}
+__device__ __forceinline__ uint32_t quant4_divided(float x, float y, float z, float w, const Quantizer &k) {
   return pack_codes(quant_floor(x, k.s, k.fq), quant_floor(y, k.s, k.fq), quant_floor(z, k.s, k.fq), quant_floor(w, k.s, k.fq));
+}
+// Four codes.
+__device__ __forceinline__ uint32_t quant4(float x, float y, float z, float w, const Quantizer &k) {
+  uint32_t codes;
+  if (k.near_one && quant4_certain(x, y, z, w, k, codes)) return codes;
+  return quant4_divided(x, y, z, w, k);
 }
 
 }  // namespace

@@ -141,8 +141,22 @@ __device__ __forceinline__ void quantize_flat_body(
   }
   const Quantizer k = quantizer(s, fq);
   auto store = [&](int64_t at, const Four &f) {
+    uint32_t codes[4];
+    bool sure[4];
+    if (k.near_one) {   // one branch for all sixteen: a wavefront whose values are all certain does not wait at each quad
 #pragma unroll
-    for (int u = 0; u < 4; ++u) store_stream(q4 + at + u * kThreads + threadIdx.x, pack4(f.v[u], k));
+      for (int u = 0; u < 4; ++u) sure[u] = quant4_certain(f.v[u].x, f.v[u].y, f.v[u].z, f.v[u].w, k, codes[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sure[u] = false;
+    }
+    if (!(sure[0] && sure[1] && sure[2] && sure[3])) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (!sure[u]) codes[u] = quant4_divided(f.v[u].x, f.v[u].y, f.v[u].z, f.v[u].w, k);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) store_stream(q4 + at + u * kThreads + threadIdx.x, codes[u]);
   };
   if (whole) {
     for (; i0 + 8 * kThreads <= i1; i0 += 4 * kThreads) {
