@@ -228,28 +228,32 @@ def test_mhsa_backward_stage_by_stage(B_, T, D, heads, left, right, policy):
     check_grad(host(o["dbqkv"]), g1["dbias"], np.abs(dqkv_h.astype(np.float64)).sum(0), "dbqkv")
 
 
+# Copies of two utterances: a small batch takes the kernels of attention_few.hip and the backward's 32 rows to a workgroup, with this many
+# copies (more than 512 workgroups from 16 queries and from 32 rows) 128 rows belong to one.
+MANY = 90
+
+
+@pytest.mark.parametrize("copies", [1, MANY])
 @pytest.mark.parametrize("T", [1, 31, 33, 128, 161])
 @pytest.mark.parametrize("dh,left,right", [(4, -1, -1), (16, 33, 0), (20, -1, 31), (32, 0, 64), (44, 32, 32), (52, -1, -1), (64, 95, 1)])
-def test_attention_tile_edges(T, dh, left, right):
+def test_attention_tile_edges(T, dh, left, right, copies):
     """Every step count of the kernels for vectorised rows (head widths up to 16, 32, 48 and 64, with and without a partial
     step) against tile remainders of the frames and window ends on and next to tile ends."""
     from parity_util import check_grad
-    B_, heads = 2, 3
-    D, M = heads * dh, B_ * T
-    say("attention edges", T, dh, left, right)
+    heads, D = 3, 3 * dh
+    say("attention edges", T, dh, left, right, copies)
     rng = np.random.default_rng(660 + 100 * T + dh)
-    qkv, dctx = rng.standard_normal((M, 3 * D)).astype(F), rng.standard_normal((M, D)).astype(F)
-    qkv_d, dctx_d = dev(qkv), dev(dctx)
+    qkv, dctx = rng.standard_normal((2 * T, 3 * D)).astype(F), rng.standard_normal((2 * T, D)).astype(F)
+    B_, qkv_d, dctx_d = 2 * copies, dev(qkv).repeat(copies, 1), dev(dctx).repeat(copies, 1)
+    M, pair = B_ * T, slice(-2 * T, None)   # the batch's last two utterances
     lse = torch.empty((M, heads), dtype=torch.float32, device="cuda")
     ctx, _ = B.aqt_attention_fwd(qkv_d, B_, T, heads, left=left, right=right, lse=lse)
-    check_attention(host(ctx), qkv, B_, T, D, heads, left, right)
-    got = host(B.aqt_attention_bwd(qkv_d, ctx, dctx_d, lse, B_, T, heads, left=left, right=right)).reshape(B_, T, 3 * D)
-    ref, mag = oracle.attention_bwd(qkv.reshape(B_, T, 3 * D), dctx.reshape(B_, T, D), heads, left, right)
+    check_attention(host(ctx[pair]), qkv, 2, T, D, heads, left, right)
+    got = host(B.aqt_attention_bwd(qkv_d, ctx, dctx_d, lse, B_, T, heads, left=left, right=right)[pair]).reshape(2, T, 3 * D)
+    ref, mag = oracle.attention_bwd(qkv.reshape(2, T, 3 * D), dctx.reshape(2, T, D), heads, left, right)
     check_grad(got, ref, mag, "dqkv")
     # a tensor that is not 16-byte aligned takes the kernels for any layout
-    odd = torch.empty(qkv.size + 1, device="cuda")[1:].view(M, 3 * D)
-    odd.copy_(qkv_d)
-    ctx_odd, _ = B.aqt_attention_fwd(odd, B_, T, heads, left=left, right=right)
+    ctx_odd, _ = B.aqt_attention_fwd(moved(qkv_d), B_, T, heads, left=left, right=right)
     np.testing.assert_array_equal(host(ctx_odd), host(ctx))   # the forwards share every product and sum
 
 
@@ -283,20 +287,22 @@ def test_backward_uses_the_probabilities_of_the_forward(dh):
 BIG = F(3.4e38)   # rounds to an infinity in bf16
 
 
+@pytest.mark.parametrize("copies", [1, MANY])
 @pytest.mark.parametrize("what,value", [("q", np.nan), ("k", np.nan), ("k", np.inf), ("k", -BIG), ("v", np.inf), ("v", BIG)])
 @pytest.mark.parametrize("dh,left,right", [(64, -1, -1), (12, 40, 70)])
-def test_forward_takes_special_values_as_the_any_layout_kernel_does(what, value, dh, left, right):
+def test_forward_takes_special_values_as_the_any_layout_kernel_does(what, value, dh, left, right, copies):
     """Whole tiles and tiles that a window cuts alike: a score that is NaN or below -1e29 counts as a masked key."""
-    say("special values", what, value, dh, left, right)
+    say("special values", what, value, dh, left, right, copies)
     T, heads = 100, 2
     D = heads * dh
     qkv = np.random.default_rng(690 + dh).standard_normal((2 * T, 3 * D)).astype(F)
     qkv[37, {"q": 0, "k": D, "v": 2 * D}[what] + 5] = value
     got = []
-    for t in (dev(qkv), moved(dev(qkv))):
-        lse = torch.empty((2 * T, heads), device="cuda")
-        ctx, m = B.aqt_attention_fwd(t, 2, T, heads, left=left, right=right, lse=lse, want_absmax=True)
-        got.append((host(ctx), host(lse), host(m).view(np.int32)))
+    batch, pair = dev(qkv).repeat(copies, 1), slice(-2 * T, None)
+    for t in (batch, moved(batch)):
+        lse = torch.empty((2 * T * copies, heads), device="cuda")
+        ctx, m = B.aqt_attention_fwd(t, 2 * copies, T, heads, left=left, right=right, lse=lse, want_absmax=True)
+        got.append((host(ctx[pair]), host(lse[pair]), host(m).view(np.int32)))
     if what == "v" and not np.isfinite(value) and left >= 0:
         # a masked key's probability is zero: zero times an infinity only where the key's half of a tile is formed at all
         seen = np.abs(np.arange(2 * T) - 37) <= 40
@@ -307,11 +313,12 @@ def test_forward_takes_special_values_as_the_any_layout_kernel_does(what, value,
 
 @pytest.mark.parametrize("what,value", [("dctx", np.inf), ("dctx", -np.inf), ("v", np.inf), ("q", np.nan), ("k", np.inf)])
 @pytest.mark.parametrize("dh", [16, 32, 36, 64])
-def test_backward_keeps_what_is_infinite_and_what_is_finite(what, value, dh):
+@pytest.mark.parametrize("copies", [1, MANY])
+def test_backward_keeps_what_is_infinite_and_what_is_finite(what, value, dh, copies):
     """An infinity has no bf16 terms: the same entries come out infinite (with their sign), NaN and finite as with float32
     products.  The finite ones differ by the rounding of sums of T products of order one (2 (T + dh + 8) u of the largest,
     the scores' amplification included: dP - D cancels)."""
-    say("special values, backward", what, value, dh)
+    say("special values, backward", what, value, dh, copies)
     T, heads = 100, 2
     D = heads * dh
     rng = np.random.default_rng(691 + dh)
@@ -320,11 +327,11 @@ def test_backward_keeps_what_is_infinite_and_what_is_finite(what, value, dh):
         go[37, 5] = value
     else:
         qkv[37, {"q": 0, "k": D, "v": 2 * D}[what] + 5] = value
-    qkv_d, go_d = dev(qkv), dev(go)
-    lse = torch.empty((2 * T, heads), device="cuda")
-    ctx, _ = B.aqt_attention_fwd(qkv_d, 2, T, heads, lse=lse)
-    a = host(B.aqt_attention_bwd(qkv_d, ctx, go_d, lse, 2, T, heads))
-    b = host(B.aqt_attention_bwd(moved(qkv_d), ctx, go_d, lse, 2, T, heads))
+    qkv_d, go_d, n = dev(qkv).repeat(copies, 1), dev(go).repeat(copies, 1), 2 * copies
+    lse = torch.empty((n * T, heads), device="cuda")
+    ctx, _ = B.aqt_attention_fwd(qkv_d, n, T, heads, lse=lse)
+    a = host(B.aqt_attention_bwd(qkv_d, ctx, go_d, lse, n, T, heads)[-2 * T:])
+    b = host(B.aqt_attention_bwd(moved(qkv_d), ctx, go_d, lse, n, T, heads)[-2 * T:])
     fine = np.isfinite(b)
     assert (~fine).any() and fine[T:].all()   # the other utterance is untouched
     np.testing.assert_array_equal(a[~fine], b[~fine])
@@ -333,10 +340,11 @@ def test_backward_keeps_what_is_infinite_and_what_is_finite(what, value, dh):
 
 @pytest.mark.parametrize("what", ["dctx", "v", "k", "q"])
 @pytest.mark.parametrize("dh,T,left,right", [(64, 100, -1, -1), (32, 300, 30, 45), (36, 130, -1, 3), (4, 40, 5, -1)])
-def test_backward_with_values_beyond_bf16(what, dh, T, left, right):
+@pytest.mark.parametrize("copies", [1, MANY])
+def test_backward_with_values_beyond_bf16(what, dh, T, left, right, copies):
     """Finite in float32, an infinity if rounded to bf16: the gradients stay finite and right."""
     from parity_util import check_grad
-    say("beyond bf16", what, dh, T, left, right)
+    say("beyond bf16", what, dh, T, left, right, copies)
     heads = 2
     D = heads * dh
     rng = np.random.default_rng(692 + dh)
@@ -349,10 +357,10 @@ def test_backward_with_values_beyond_bf16(what, dh, T, left, right):
         if what != "v":                        # the score's other factor is zero, so that the scores stay what they are
             qkv[:, {"q": D, "k": 0}[what] + 2] = 0.0
         qkv[37, at] = BIG
-    qkv_d, go_d = dev(qkv), dev(go)
-    lse = torch.empty((2 * T, heads), device="cuda")
-    ctx, _ = B.aqt_attention_fwd(qkv_d, 2, T, heads, left=left, right=right, lse=lse)
-    got = host(B.aqt_attention_bwd(qkv_d, ctx, go_d, lse, 2, T, heads, left=left, right=right)).reshape(2, T, 3 * D)
+    qkv_d, go_d, n = dev(qkv).repeat(copies, 1), dev(go).repeat(copies, 1), 2 * copies
+    lse = torch.empty((n * T, heads), device="cuda")
+    ctx, _ = B.aqt_attention_fwd(qkv_d, n, T, heads, left=left, right=right, lse=lse)
+    got = host(B.aqt_attention_bwd(qkv_d, ctx, go_d, lse, n, T, heads, left=left, right=right)[-2 * T:]).reshape(2, T, 3 * D)
     ref, mag = oracle.attention_bwd(qkv.reshape(2, T, 3 * D), go.reshape(2, T, D), heads, left, right)
     assert np.isfinite(got).all()
     check_grad(got, ref, mag, "dqkv")
@@ -432,10 +440,10 @@ def test_modules_may_leave_their_result_over_the_second_layers_input(T, D):
             np.testing.assert_array_equal(host(call(True)), want, err_msg=call.__name__)
 
 
-@pytest.mark.parametrize("T,left,right", [(1, -1, -1), (32, 5, 3), (33, -1, -1), (129, 23, 0), (300, -1, 40), (420, -1, -1)])
+@pytest.mark.parametrize("T,left,right", [(1, -1, -1), (32, 5, 3), (33, -1, -1), (64, -1, -1), (129, 23, 0), (300, -1, 40), (420, -1, -1)])
 @pytest.mark.parametrize("dh", [8, 20, 36, 64])
 def test_backward_of_few_and_of_many_utterances(T, left, right, dh):
-    """A small batch gives 32 rows to a workgroup, whose wavefronts share the tiles, a large one 128: both against the oracle."""
+    """From 33 frames on a small batch gives 32 rows to a workgroup, whose wavefronts share the tiles, a large one 128: both against the oracle."""
     from parity_util import check_grad
     say("backward, few and many", T, left, right, dh)
     heads = 2
