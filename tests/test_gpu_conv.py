@@ -274,7 +274,8 @@ def test_conv_module_chain_stage_by_stage(B_, T, D, kw, pl, policy):
 
 
 @pytest.mark.parametrize("B_,T,D,kw,pl", [(1, 1, 4, 1, 0), (2, 7, 64, 3, 1), (1, 9, 66, 5, 4), (3, 64, 64, 15, 7), (2, 65, 70, 32, 15),
-                                          (2, 129, 130, 32, 31), (1, 40, 24, 33, 16)])   # 33 taps: the untiled kernel
+                                          (2, 129, 130, 32, 31), (1, 40, 24, 33, 16),    # 33 taps: the untiled kernel
+                                          (300, 33, 66, 5, 2), (140, 65, 72, 32, 15)])   # tiles of 64 frames
 def test_conv_module_backward_through_the_gate(B_, T, D, kw, pl):
     """The depthwise gradient times the gate's factors in one kernel: the bits of the calls made one by one."""
     say("conv module backward, gate", B_, T, D, kw)
@@ -302,22 +303,26 @@ def test_conv_module_rejects_float_activations():
 
 
 @pytest.mark.parametrize("T,kw,pad_left", [(1, 1, 0), (8, 15, 14), (31, 32, 15), (33, 32, 31), (64, 3, 1), (97, 15, 7)])
-def test_few_utterances_have_the_bits_of_many(T, kw, pad_left):
-    """A small batch takes tiles of 32 frames, a large one of 64: the taps of an output in the same order, forward and backward."""
-    C, many = 72, 600
+@pytest.mark.parametrize("C", [72, 70])   # in pieces of 16 bytes, and not
+def test_few_utterances_have_the_bits_of_many(T, kw, pad_left, C):
+    """A small batch takes tiles of 32 frames, a large one of 64: the taps of an output in the same order, forward (by itself, and with scale,
+    Swish, its slope and the largest value behind it) and backward."""
+    many = 600
     assert -(-C // 64) * -(-T // 64) * 2 < 256 <= -(-C // 64) * -(-T // 64) * many
-    rng = np.random.default_rng(870 + T)
-    x, dout = (rng.standard_normal((2 * T, C)).astype(np.float32) for _ in range(2))
-    w, b = rng.standard_normal((kw, C)).astype(np.float32), rng.standard_normal(C).astype(np.float32)
+    x, w, bias, a, b, dout = conv_inputs(870 + T, 2, T, C, kw)
 
-    def batch(a, B_):
-        return torch.from_numpy(a).cuda().view(1, 2, T, C).expand(B_ // 2, -1, -1, -1).contiguous().view(B_, T, C)
+    def batch(t, B_):
+        return dev(t).repeat(B_ // 2, 1, 1)
 
-    wd, bd = torch.from_numpy(w).cuda(), torch.from_numpy(b).cuda()
+    wd, biasd, ad, bd = dev(w), dev(bias), dev(a), dev(b)
     got = []
     for B_ in (2, many):
-        y, _, _ = B.aqt_depthwise_conv_fwd(batch(x, B_), wd, bias=bd, pad_left=pad_left)
+        y, _, _ = B.aqt_depthwise_conv_fwd(batch(x, B_), wd, bias=biasd, pad_left=pad_left)
+        z, dfac, top = B.aqt_depthwise_conv_fwd(batch(x, B_), wd, bias=biasd, pad_left=pad_left, norm_scale=ad, norm_shift=bd, swish=True,
+                                                want_dfac=True, want_absmax=True)
         dx, _, _ = B.aqt_depthwise_conv_bwd(batch(dout, B_), batch(x, B_), wd, pad_left=pad_left)
-        got.append([t[-2:].cpu().numpy() for t in (y, dx)])
-    for a, c in zip(*got):
-        np.testing.assert_array_equal(a, c)
+        du, _, _ = B.aqt_depthwise_conv_bwd(batch(dout, B_), batch(x, B_), wd, dfac=dfac, pad_left=pad_left)
+        got.append([host(t[-2:]) for t in (y, z, dfac, dx, du)] + [host(top)])
+    assert got[0][5][0] == np.abs(got[0][1]).max()
+    for p, q in zip(*got):
+        np.testing.assert_array_equal(p, q)
