@@ -1,7 +1,7 @@
 // Driver of the host emulation of the attention kernels for vectorised rows: the test splices attention_tiles.h, the
-// kernels of attention_fwd.hip (namespace fwd_rows) and of attention_bwd.hip (namespace bwd_rows) in front of this file.
-// Forward, then both backward kernels, on tensors of exactly the sizes that the kernels may touch; results are
-// compared with plain float64 loops written here.
+// kernels of attention_fwd.hip (namespace fwd_rows), attention_few.hip (few) and attention_bwd.hip (bwd_rows) in front of this file.
+// Forward, then both backward kernels, in tiles of 128 rows and in the forms for small batches (16 queries, 32 rows), on tensors
+// of exactly the sizes that the kernels may touch; results are compared with plain float64 loops written here.
 namespace aqt {
 static int bad = 0;
 template <int KS> void launch(unsigned blocks, const float *qkv, float *ctx, uint32_t *am, float *lse, const float *dctx, float *dsum,
@@ -9,6 +9,15 @@ template <int KS> void launch(unsigned blocks, const float *qkv, float *ctx, uin
   run(blocks, 256, 0, [&] { fwd_rows::attention_fwd_rows_kernel<KS>(qkv, g, ctx, am, lse); });
   run(blocks, 256, 0, [&] { bwd_rows::attention_bwd_dq_rows_kernel<KS>(qkv, ctx, dctx, lse, dsum, g, dqkv); });
   run(blocks, 256, 0, [&] { bwd_rows::attention_bwd_dkv_rows_kernel<KS>(qkv, dctx, lse, dsum, g, dqkv); });
+}
+template <int KS> void launch_few(const float *qkv, float *ctx, uint32_t *am, float *lse, const float *dctx, float *dsum, float *dqkv,
+                                  AttnShape g) {
+  const int tiles = (g.T + few::kQf - 1) / few::kQf;
+  run((unsigned)(tiles * g.heads * g.B), 256, 0, [&] { few::attention_fwd_few_kernel<KS>(qkv, g, tiles, ctx, am, lse); });
+  g.qtiles = (g.T + 31) / 32;
+  const unsigned blocks = (unsigned)(g.qtiles * g.heads * g.B);
+  run(blocks, 256, 0, [&] { bwd_rows::attention_bwd_dq_rows_kernel<KS, true>(qkv, ctx, dctx, lse, dsum, g, dqkv); });
+  run(blocks, 256, 0, [&] { bwd_rows::attention_bwd_dkv_rows_kernel<KS, true>(qkv, dctx, lse, dsum, g, dqkv); });
 }
 // big: one value of dctx that is finite in float32 and an infinity in bf16, so that its rows are formed a second time
 static void one(int64_t B, int T, int64_t D, int heads, int left, int right, bool big = false) {
@@ -28,6 +37,12 @@ static void one(int64_t B, int T, int64_t D, int heads, int left, int right, boo
   const unsigned blocks = (unsigned)(g.qtiles * heads * B);
   auto f = dh <= 16 ? launch<1> : dh <= 32 ? launch<2> : dh <= 48 ? launch<3> : launch<4>;
   f(blocks, qkv, ctx, &am, lse, dctx, dsum, dqkv, g);
+  float *ctx2 = (float *)malloc(n * 4), *lse2 = (float *)malloc(rows * 4), *dqkv2 = (float *)malloc(3 * n * 4), *dsum2 = (float *)malloc(rows * 4);
+  uint32_t am2 = 0;
+  for (size_t i = 0; i < 3 * n; ++i) dqkv2[i] = NAN;
+  auto f2 = dh <= 16 ? launch_few<1> : dh <= 32 ? launch_few<2> : dh <= 48 ? launch_few<3> : launch_few<4>;
+  f2(qkv, ctx2, &am2, lse2, dctx, dsum2, dqkv2, g);
+  if (memcmp(ctx, ctx2, n * 4) || memcmp(lse, lse2, rows * 4) || am != am2) { printf("  MISMATCH of the forward's bits\n"); bad = 1; }
   const double scale = 1.0 / sqrt((double)dh);
   std::vector<double> out(n, 0.0), omag(n, 0.0), ref(3 * n, 0.0), mag(3 * n, 0.0), p(T), dp(T);
   for (int64_t b = 0; b < B; ++b) for (int h = 0; h < heads; ++h) for (int64_t t = 0; t < T; ++t) {
@@ -60,11 +75,15 @@ static void one(int64_t B, int T, int64_t D, int heads, int left, int right, boo
   }
   double worst = 0, worst_fwd = 0;
   float mx = 0;
-  for (size_t i = 0; i < 3 * n; ++i) { at_least(worst, fabs((double)dqkv[i] - ref[i]) / (mag[i] + 1e-30)); }
+  for (size_t i = 0; i < 3 * n; ++i) {
+    at_least(worst, fabs((double)dqkv[i] - ref[i]) / (mag[i] + 1e-30));
+    at_least(worst, fabs((double)dqkv2[i] - ref[i]) / (mag[i] + 1e-30));
+  }
   for (size_t i = 0; i < n; ++i) { at_least(worst_fwd, fabs((double)ctx[i] - out[i]) / (omag[i] + 1e-30)); mx = std::max(mx, fabsf(ctx[i])); }
   printf("  worst err / sum|terms| = %.3g forward, %.3g backward\n", worst_fwd, worst);
   if (!(worst < 1e-5) || !(worst_fwd < 1e-5) || __float_as_uint(mx) != am) { printf("  MISMATCH\n"); bad = 1; }
   free(qkv); free(ctx); free(dctx); free(lse); free(dsum); free(dqkv);
+  free(ctx2); free(lse2); free(dqkv2); free(dsum2);
 }
 }  // namespace aqt
 int main() {

@@ -32,6 +32,21 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
   cmp("fwd", out, ref.data(), mag.data(), n);
   for (size_t i = 0; i < n; ++i) mx = std::max(mx, fabsf(out[i]));
   if (__float_as_uint(mx) != am) { printf("  absmax mismatch\n"); bad = 1; }
+  // tiles of half the frames: the same bits
+  ConvGeom half = g;
+  half.tgroups = (int)cdiv(T, kTile / 2);
+  const unsigned half_blocks = half.cgroups * half.tgroups * B;
+  const size_t half_lds = (size_t)(kTile / 2 + 2 * kw - 1) * 256;
+  auto same = [&](const char *what, const float *a, const float *b, size_t m) {
+    if (memcmp(a, b, m * 4)) { printf("  MISMATCH of the half tiles' bits, %s\n", what); bad = 1; }
+  };
+  float *out2 = mk(2 * n, 0, 0);
+  if (kw <= kTapsMax) {
+    uint32_t am2 = 0;
+    run(half_blocks, 256, half_lds, [&] { dwconv_kernel<false, 1>(x, nullptr, w, bias, nullptr, nullptr, 0, 0, half, pad, out2, nullptr, &am2); });
+    same("fwd", out, out2, n);
+    if (am2 != am) { printf("  absmax mismatch of the half tiles\n"); bad = 1; }
+  }
   // dx
   if (kw <= kTapsMax) run(blocks, 256, (size_t)(kTile + 2 * kw - 1) * 256, [&] { dwconv_kernel<false>(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, g, kw - 1 - pad, dx, nullptr, nullptr); });
   else run(8, 256, 0, [&] { dwconv_any_kernel(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, g, kw - 1 - pad, dx, nullptr, nullptr); });
@@ -50,6 +65,10 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
       const size_t at = (2 * f + h) * C + c;
       if (!(dv[at] == dx[f * C + c] * gate[at])) ++differ;
     }
+    run(half_blocks, 256, half_lds, [&] { dwconv_kernel<false, 1>(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, half, kw - 1 - pad, out2, nullptr, nullptr); });
+    same("dx", dx, out2, n);
+    run(half_blocks, 256, half_lds, [&] { dwconv_kernel<true, 1>(dout, dfac, w, nullptr, nullptr, nullptr, 0, 1, half, kw - 1 - pad, out2, nullptr, nullptr, gate); });
+    same("gate", dv, out2, 2 * n);
     printf("  gate   values that differ from dx times the gate: %zu\n", differ);
     if (differ) bad = 1;
     free(gate); free(dv);
@@ -75,7 +94,7 @@ static void one(int64_t B, int64_t T, int64_t C, int kw, int pad) {
   }
   cmp("dw", dw, rw.data(), mw.data(), (size_t)kw * C);
   cmp("dbias", db, rw.data() + (size_t)kw * C, mw.data() + (size_t)kw * C, C);
-  free(x); free(dout); free(dfac); free(w); free(bias); free(out); free(dx); free(dw); free(db); free(part);
+  free(x); free(dout); free(dfac); free(w); free(bias); free(out); free(dx); free(dw); free(db); free(part); free(out2);
 }
 }  // namespace
 }  // namespace aqt

@@ -69,6 +69,101 @@ template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED, int EPI> 
   if (__float_as_uint(mx) != am[0]) { printf("  MISMATCH of the largest value\n"); bad = 1; }
 }
 
+// ---- the small products that make the codes themselves ----
+static float scale_of(float most, int qmax) { return most / (float)qmax; }
+static int code_of(float v, float s, int qmax) {
+  const float t = s == 0.0f ? 0.0f : v / s, r = floorf(t + 0.5f);
+  return (int)fminf(fmaxf(r, -(float)qmax), (float)qmax);
+}
+// values next to the lines between two codes among them, so that some are divided
+static void fill(float *p, size_t n, float top, int qmax) {
+  for (size_t i = 0; i < n; ++i) p[i] = i % 9 == 4 ? ((float)(int)(i % 11) - 5.0f - 0.5f) * (top / (float)qmax) : top * uniform();
+}
+template <bool PACKED> void from_rows(int64_t M, int64_t K, int64_t N, int bits_x) {
+  printf("codes made by the product: %ld %ld %ld packed %d, %d bits\n", (long)M, (long)K, (long)N, (int)PACKED, bits_x);
+  const int q = (1 << (bits_x - 1)) - 1;
+  Codes w(N, K, PACKED);
+  Exact<float> x(M * K), sw(N), bias(N), y(M * N), sx(1);
+  Exact<int8_t> xq(M * K);
+  Exact<uint32_t> most(1);
+  Exact<int32_t> status(1);
+  fill(x, M * K, 3.0f, q);
+  uint32_t top = 0;
+  for (int64_t i = 0; i < M * K; ++i) top = std::max(top, __float_as_uint(x[i]) & 0x7FFFFFFFu);
+  most[0] = top; status[0] = 0;
+  for (int64_t n = 0; n < N; ++n) { sw[n] = 0.02f + 0.01f * uniform(); bias[n] = uniform(); }
+  const int64_t tn = cdiv(N, 32), tm = cdiv(M, 32);
+  run((unsigned)(tn * tm), 512, 0, [&] { any::dense_fwd_rows_kernel<PACKED>(RowSource{x, most, q, xq, sx, status}, w.bytes, sw, M, K, N, bias, y, (int)tn); });
+  const float s = scale_of(__uint_as_float(top), q);
+  double wrong = sx[0] != s || status[0] != 0, worst = 0;
+  for (int64_t m = 0; m < M; ++m) {
+    for (int64_t k = 0; k < K; ++k) wrong += xq[m * K + k] != code_of(x[m * K + k], s, q);
+    for (int64_t n = 0; n < N; ++n) {
+      int64_t sum = 0;
+      for (int64_t k = 0; k < K; ++k) sum += xq[m * K + k] * w.v[n * K + k];
+      const double ref = (double)sum * ((double)s * sw[n]) + bias[n];
+      at_least(worst, fabs((double)y[m * N + n] - ref) / (1.0 + fabs(ref)));
+    }
+  }
+  expect("codes and scale that differ", wrong, 0);
+  expect("outputs", worst, 1e-5);
+}
+template <int EPI> void from_dense(int64_t M, int64_t K, int64_t N, int bits_w, bool kn) {
+  printf("both quantizers in the product: %ld %ld %ld, %d bits, epilogue %d\n", (long)M, (long)K, (long)N, bits_w, EPI);
+  const int qx = 127, qw = (1 << (bits_w - 1)) - 1, packed = bits_w <= 4, parts = 3;
+  Exact<float> x(M * K), w(K * N), sw(N), bias(N), y(M * N), dact(M * N), sx(1);
+  Exact<int8_t> xq(M * K), wkn(K * N);
+  Exact<uint8_t> wq(N * (packed ? K / 2 : K));
+  Exact<int32_t> status(1);
+  fill(x, M * K, 2.0f, qx);
+  for (int64_t k = 0; k < K; ++k) for (int64_t n = 0; n < N; ++n) w[k * N + n] = n % 7 == 3 ? 0.0f : uniform() * (float)(1 + n % 5);
+  for (int64_t n = 0; n < N; ++n) bias[n] = uniform();
+  status[0] = 0;
+  Exact<uint32_t> partial(parts);
+  uint32_t top = 0;
+  for (int i = 0; i < parts; ++i) partial[i] = 0;
+  for (int64_t i = 0; i < M * K; ++i) { const uint32_t u = __float_as_uint(x[i]) & 0x7FFFFFFFu; partial[i % parts] = std::max(partial[i % parts], u); top = std::max(top, u); }
+  int64_t slabs = std::min<int64_t>(cdiv(K, 32), kWeightSlabs);
+  const int64_t rows = cdiv(K, slabs);
+  slabs = cdiv(K, rows);
+  uint32_t *part = (uint32_t *)aligned_alloc(16, align_up(slabs * N * 4, 16));
+  for (int64_t i = 0; i < slabs * N; ++i) part[i] = 0;
+  for (int64_t k = 0; k < K; ++k) for (int64_t n = 0; n < N; ++n) {
+    uint32_t &u = part[k / rows * N + n];
+    u = std::max(u, __float_as_uint(w[k * N + n]) & 0x7FFFFFFFu);
+  }
+  const int64_t tn = cdiv(N, 32), tm = cdiv(M, 32);
+  const DenseSource src{x, partial, parts, qx, xq, sx, w, part, (int)slabs, qw, packed, wq, sw, kn ? wkn.p : nullptr, status};
+  run((unsigned)(tn * tm), 512, 0, [&] { any::dense_fwd_raw_kernel<EPI>(src, M, K, N, bias, y, dact, (int)tn); });
+  const float s = scale_of(__uint_as_float(top), qx);
+  double wrong = sx[0] != s || status[0] != 0, worst = 0, worst_d = 0;
+  std::vector<int> cx(M * K), cw(K * N);
+  for (int64_t i = 0; i < M * K; ++i) { cx[i] = code_of(x[i], s, qx); wrong += xq[i] != cx[i]; }
+  for (int64_t n = 0; n < N; ++n) {
+    uint32_t u = 0;
+    for (int64_t j = 0; j < slabs; ++j) u = std::max(u, part[j * N + n]);
+    const float t = scale_of(__uint_as_float(u), qw);
+    wrong += sw[n] != t;
+    for (int64_t k = 0; k < K; ++k) {
+      const int c = cw[k * N + n] = code_of(w[k * N + n], t, qw);
+      const int got = packed ? (int)(int8_t)(uint8_t)(wq[n * (K / 2) + k / 2] << (k & 1 ? 0 : 4)) >> 4 : (int8_t)wq[n * K + k];
+      wrong += got != c || (kn && wkn[k * N + n] != c);
+    }
+  }
+  for (int64_t m = 0; m < M; ++m) for (int64_t n = 0; n < N; ++n) {
+    int64_t sum = 0;
+    for (int64_t k = 0; k < K; ++k) sum += cx[m * K + k] * cw[k * N + n];
+    const double v = (double)sum * ((double)s * sw[n]) + bias[n], g = sigma(v);
+    const double ref = EPI == AQT_EPI_SWISH ? v * g : v;
+    at_least(worst, fabs((double)y[m * N + n] - ref) / (1.0 + fabs(ref)));
+    if (EPI == AQT_EPI_SWISH) at_least(worst_d, fabs((double)dact[m * N + n] - g * (1 + v * (1 - g))));
+  }
+  expect("codes and scales that differ", wrong, 0);
+  expect("outputs", worst, 1e-5);
+  expect("slopes", worst_d, 1e-5);
+  ::free(part);
+}
+
 // MODE 0: dX with a factor and a clip mask; 1 + e: weight-only forward.  kernel(f, scale, q, s_x, mask, factor, bias, out)
 // `wild`: rows whose values lie further apart than the digits of gemm_exact.hip reach, and among them rows with an infinity
 // (kInfinite) or that take all planes of digits (kFar)
@@ -225,6 +320,9 @@ int main() {
   forward<1, 2, 4, 1, 1, 128, false, kSwish>(131, 17, 65); forward<1, 1, 1, 1, 8, 64, false, kNone>(33, 517, 31);
   forward<1, 1, 1, 1, 8, 64, true, kSwish>(1, 31, 1); forward<1, 2, 1, 1, 8, 64, true, kGlu>(40, 129, 34);
   forward<1, 2, 1, 1, 8, 64, false, kGlu>(9, 15, 18); forward<1, 1, 1, 1, 8, 64, true, kNone>(9, 3, 5);
+  from_rows<false>(33, 64, 36, 8); from_rows<true>(1, 68, 4, 8); from_rows<true>(40, 512, 33, 4); from_rows<false>(31, 508, 31, 8); from_rows<false>(65, 132, 70, 8);
+  from_dense<kNone>(33, 64, 36, 8, true); from_dense<kSwish>(31, 68, 60, 4, true); from_dense<kNone>(1, 256, 4, 3, false); from_dense<kSwish>(70, 252, 100, 8, false);
+  from_dense<kNone>(40, 132, 32, 4, true);
   rows_f64<1, 1, 8, false, 0>(33, 17, 300); rows_f64<1, 1, 8, false, 0>(5, 15, 3); rows_f64<2, 1, 8, true, 1 + kSwish>(34, 33, 77);
   rows_f64<1, 4, 1, false, 0>(65, 66, 37); rows_f64<1, 4, 1, true, 1 + kNone>(31, 65, 17); rows_f64<1, 4, 1, true, 1 + kNone>(3, 3, 15);
   rows_f64<2, 2, 1, false, 1 + kGlu>(33, 70, 33); rows_f64<2, 1, 8, true, 1 + kGlu>(33, 34, 129); rows_f64<2, 2, 1, false, 1 + kGlu>(2, 2, 1);

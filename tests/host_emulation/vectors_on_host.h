@@ -133,6 +133,17 @@ inline v4d __builtin_amdgcn_mfma_f64_16x16x4f64(double a, double b, v4d c, int, 
   wave_meets().arrive_and_wait();
   return c;
 }
+// v_mfma_f32_16x16x4_f32: lanes and accumulator rows as v_mfma_i32_16x16x64_i8; the four products one after the other
+inline v4f __builtin_amdgcn_mfma_f32_16x16x4f32(float a, float b, v4f c, int, int, int) {
+  const unsigned base = threadIdx.x & ~63u, lane = threadIdx.x & 63u, lc = lane & 15u, lg = lane >> 4;
+  g_mfa[threadIdx.x] = a; g_mfb[threadIdx.x] = b;
+  wave_meets().arrive_and_wait();
+  for (unsigned r = 0; r < 4; ++r)
+    for (unsigned k = 0; k < 4; ++k) c[r] = fmaf(g_mfa[base + 16 * k + 4 * lg + r], g_mfb[base + 16 * k + lc], c[r]);
+  wave_meets().arrive_and_wait();
+  return c;
+}
+inline float __builtin_amdgcn_fractf(float x) { return fminf(x - floorf(x), 0x1.fffffep-1f); }
 inline uint32_t __builtin_amdgcn_alignbyte(uint32_t hi, uint32_t lo, int b) { return (uint32_t)(((uint64_t)hi << 32 | lo) >> (8 * (b & 3))); }
 inline uint32_t __builtin_amdgcn_perm(uint32_t hi, uint32_t lo, uint32_t sel) {   // selector bytes 0 .. 3: lo, 4 .. 7: hi
   const uint64_t v = (uint64_t)hi << 32 | lo;

@@ -63,6 +63,8 @@ def spliced_attention_rows_source():
     tiles = read("attention_tiles.h").replace("namespace aqt {", "namespace aqt {\n" + shape, 1)
     fwd = read("attention_fwd.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace fwd_rows {")
     fwd = fwd[:fwd.index("aqt_status launch_attention_rows")] + "}\n"
+    few = read("attention_few.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace few {")
+    few = few[:few.index("}  // namespace\n\n// As long as all of its workgroups")] + "}\n}\n"
     bwd = read("attention_bwd.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace bwd_rows {")
     bwd = bwd[:bwd.index("bool attention_rows_ok")] + "}\n"
     # instructions that the shim stands in for
@@ -73,12 +75,17 @@ def spliced_attention_rows_source():
     assert bwd.count('asm volatile("" : "+') == 2
     bwd = re.sub(r' *asm volatile\("" : "\+[sv]"\(\w+\)\);\n', "", bwd)
     driver = open(os.path.join(HERE, "host_emulation", "attention_rows_driver.cpp")).read()
-    return '#include "vectors_on_host.h"\n' + bf16_terms() + tiles + fwd + bwd + driver
+    return '#include "vectors_on_host.h"\n' + bf16_terms() + tiles + fwd + few + bwd + driver
 
 
 def spliced_gemm_any_source():
     any_ = read("gemm_any.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace any {")
-    any_ = any_[:any_.index("// Which workgroup arrangement of the forward.")] + "}\n}\n"
+    fill = any_[any_.index("// ---- forward from float32 rows"):any_.index("template <int TM, int TN, int WM, int WN, int WK, int BK, bool PACKED>\naqt_status")]
+    any_ = any_[:any_.index("// Which workgroup arrangement of the forward.")] + fill + "}\n}\n"
+    internal = open(os.path.join(CSRC, "aqt_internal.h")).read()
+    sources = "".join(internal[i:internal.index("};", i) + 2] + "\n" for i in (internal.index("struct RowSource {"), internal.index("struct DenseSource {\n")))
+    slabs = re.search(r"^constexpr int kWeightSlabs = .*$", internal, flags=re.M).group(0)
+    quant = read("quant_code.h") + "namespace aqt {\n" + slabs + "\n" + sources + "}\n"
     f64 = read("gemm_any_f64.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace f64 {")
     f64 = f64[:f64.index("template <int TN, int WN, int WK, bool PACKED, int MODE>\naqt_status")] + "}\n}\n"
     exact = read("gemm_exact.hip").replace("namespace aqt {\nnamespace {", "namespace aqt {\nnamespace exact {")
@@ -86,7 +93,7 @@ def spliced_gemm_any_source():
     exact = cut(exact, "__device__ __forceinline__ float load_f32", "__device__ __forceinline__ double power_of_two")   # the shim has its own
     driver = open(os.path.join(HERE, "host_emulation", "gemm_any_driver.cpp")).read()
     return ('#include "vectors_on_host.h"\n#include "aqt.h"\n' + read("any_shape.h") + bf16_terms() + read("colsum.h") +
-            read("epilogue.h") + any_ + f64 + exact + driver)
+            read("epilogue.h") + quant + any_ + f64 + exact + driver)
 
 
 def test_lanes_hand_over_lds_behind_fences():
