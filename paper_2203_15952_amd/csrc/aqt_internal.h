@@ -196,7 +196,7 @@ bool dense_fwd_rows_ok(int64_t M, int64_t K, int64_t N);
 aqt_status launch_dense_fwd_rows(const RowSource &src, const void *wq_packed, const float *s_w, int64_t M, int64_t K, int64_t N,
                                  int bits_w, const float *bias, float *y, hipStream_t st);
 
-// A dense layer's float32 tensors and where its codes go, behind the pass that takes the maxima (launch_absmax_dense): the second
+// A dense layer's float32 tensors and where its codes go, behind the pass that takes the maxima (absmax_dense_kernel): the second
 // launch of launch_quantize_dense and the product in one.  x, w 16-byte, the codes 4-byte aligned, no clip masks.
 struct DenseSource {
   const float *x;
@@ -260,7 +260,7 @@ struct AttnShape {
   int64_t B, D;
   int T;                        // frames: positions within an utterance are 32-bit (2^31 - 1 here: too long for that)
   int heads, dh, left, right;   // left / right < 0: no limit on that side, otherwise at most T
-  int qtiles;                   // 128-frame tiles per utterance
+  int qtiles;                   // tiles per utterance: of 128 frames, or of the 32 that a workgroup of the backward for small batches owns
   float scale_log2e, scale;     // log2(e) / sqrt(dh), 1 / sqrt(dh)
 };
 // Heads of a multiple of four on 16-byte aligned tensors; dsum [B*T, heads].

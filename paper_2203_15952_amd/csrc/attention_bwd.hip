@@ -26,10 +26,11 @@
 // Measured in us, all products in float32 (attention.hip) -> scores in float32, the rest here: 32 utterances of 400 frames,
 // 8 heads of 64: 621 -> 295; 128 of 512: 2808 -> 1455; 24 of 417, 4 heads of 36: 310 -> 136.  What every tile pays counts:
 // window tests and zeros beyond the head or the utterance stand under branches of their own, and the constant part of an LDS
-// address goes into the instruction (310 -> 295, 1510 -> 1453, 146 -> 136, the same bits).  Small batches, whose workgroups of 128
-// rows leave the chip idle: FEW, 32 rows to a workgroup and the tiles shared out among its wavefronts (launch_attention_bwd_rows).  Before that, all products in bf16
+// address goes into the instruction (310 -> 295, 1510 -> 1453, 146 -> 136, the same bits).  Before that, all products in bf16
 // passes took 273, 1392 and 125 against 306, 1500 and 146, with the error above.  The matrix pipes are busy 52 % of the
 // cycles of both kernels inside an encoder layer (profiles/encoder_layer_12800_tokens.txt).
+// Small batches, whose workgroups of 128 rows leave the chip idle: FEW, 32 rows to a workgroup and the tiles shared out among
+// its wavefronts (attention_bwd_few_ok).
 #include <type_traits>
 
 #include "attention_tiles.h"

@@ -6,7 +6,8 @@
 // The same bits as attention_fwd.hip: v_mfma_f32_16x16x4_f32 adds its four products one after the other, as two
 // v_mfma_f32_32x32x2_f32 do (both equal a chain of fmaf, measured on 2^18 dot products of 64), and the order of every sum
 // is kept: scores along the head; the result over keys k, k + 4, k + 1, k + 5, ..; the normaliser as two shares, keys with bit 2
-// clear and set.
+// clear and set.  (Finite values; a key that a window hides has the probability zero, and where zero times an infinite value is formed at
+// all follows the tiles: here those of 16 queries, there of 32.)
 #include "attention_tiles.h"
 
 namespace aqt {

@@ -635,7 +635,8 @@ int grid_for(int64_t work_items, int per_block, int cap) {
 // up to 4096 blocks = 16 per CU, each on its own contiguous run of the tensor; every thread keeps four 16-byte loads in flight.
 int flat_blocks(int64_t n, int64_t *per4) {
   const int g = grid_for(n / 4, kThreads * 4, kMaxPartials);
-  const int64_t even = cdiv(n / 4, g), unit = even > 4 * kThreads ? 4 * kThreads : kThreads;   // whole groups of four loads
+  // Whole groups of four loads, which may halve the blocks: 1024 and 1025 pieces a block (4096 and 2050 blocks), both passes 29.1 and 28.5 us.
+  const int64_t even = cdiv(n / 4, g), unit = even > 4 * kThreads ? 4 * kThreads : kThreads;
   *per4 = cdiv(even, unit) * unit;
   const int64_t used = *per4 > 0 ? cdiv(n / 4, *per4) : 1;
   return static_cast<int>(used < 1 ? 1 : used);
