@@ -61,10 +61,17 @@ __device__ __forceinline__ bool quant4_certain(float x, float y, float z, float 
 __device__ __forceinline__ uint32_t quant4_divided(float x, float y, float z, float w, const Quantizer &k) {
   return pack_codes(quant_floor(x, k.s, k.fq), quant_floor(y, k.s, k.fq), quant_floor(z, k.s, k.fq), quant_floor(w, k.s, k.fq));
 }
-// Four codes.
+// Four codes (apart from quant4_certain: codes packed in front of the branch cost the product that quantizes both its operands 9.5 -> 10.0 us).
 __device__ __forceinline__ uint32_t quant4(float x, float y, float z, float w, const Quantizer &k) {
-  uint32_t codes;
-  if (k.near_one && quant4_certain(x, y, z, w, k, codes)) return codes;
+  if (k.near_one) {
+    const float a = fmaf(x, k.r, 0.5f), b = fmaf(y, k.r, 0.5f), c = fmaf(z, k.r, 0.5f), d = fmaf(w, k.r, 0.5f);
+    const float ea = fabsf(__builtin_amdgcn_fractf(a) - 0.5f), eb = fabsf(__builtin_amdgcn_fractf(b) - 0.5f);
+    const float ec = fabsf(__builtin_amdgcn_fractf(c) - 0.5f), ed = fabsf(__builtin_amdgcn_fractf(d) - 0.5f);
+    if (!(fmaxf(fmaxf(ea, eb), fmaxf(ec, ed)) > 0.5f - 0x1p-13f)) {
+      auto clamp = [&](float u) { return fminf(fmaxf(floorf(u), -k.fq), k.fq); };
+      return pack_codes(clamp(a), clamp(b), clamp(c), clamp(d));
+    }
+  }
   return quant4_divided(x, y, z, w, k);
 }
 

@@ -340,6 +340,8 @@ __device__ __forceinline__ void wabsmax_partial_body(const float *__restrict__ w
 // quantize_dense_kernel for what is left), the [K,N] codes leave four at a time and the operand's rows as whole words where the
 // widths allow it.  A tile of up to 16 rows (a short fan-in, the end of a long one) has a channel to a thread, so that all of them divide, and
 // nothing requests or packs rows that are not there: both launches at 8 x 8192 7.1 -> 6.2 us, 1 x 65536 11.1 -> 8.4, 65 x 65536 24.0 -> 21.9.
+// TRIPS (8, 4 or 2, for tiles of up to 64, 32 and 16 rows): rows of a tile that a thread with one channel takes, eight apart.
+template <int TRIPS>
 __device__ __forceinline__ void quantize_weights_body(
     const float *__restrict__ w, int64_t K, int64_t N, int qmax, int packed, const uint32_t *__restrict__ part,
     int slabs, uint8_t *__restrict__ wq_packed, float *__restrict__ s_w, int8_t *__restrict__ wq_kn,
@@ -351,23 +353,17 @@ __device__ __forceinline__ void quantize_weights_body(
   const float fq = static_cast<float>(qmax);
   // this thread's values: four channels of rows ty, ty + 32, or one channel of rows ty + 8 j (the last row or channel again beyond the end)
   const int vx = threadIdx.x & 7, vy = threadIdx.x >> 3, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int rows = static_cast<int>(min(K - k0, static_cast<int64_t>(kWChunk)));   // uniform, as the next
-  const bool quads = vec4 && rows > 16;
+  const bool quads = TRIPS > 2 && vec4;
   float v[8];
   if (quads) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (32 * j >= rows) continue;
+    for (int j = 0; j < TRIPS / 4; ++j) {
       const float4 a = *reinterpret_cast<const float4 *>(w + min(k0 + vy + 32 * j, K - 1) * N + min(n0 + 4 * vx, N - 4));
       v[4 * j] = a.x; v[4 * j + 1] = a.y; v[4 * j + 2] = a.z; v[4 * j + 3] = a.w;
     }
   } else {
-    auto load = [&](auto count) {
 #pragma unroll
-      for (int j = 0; j < decltype(count)::value; ++j) v[j] = w[min(k0 + ty + 8 * j, K - 1) * N + min(n0 + tx, N - 1)];
-    };
-    if (rows > 16) load(std::integral_constant<int, 8>{});
-    else load(std::integral_constant<int, 2>{});
+    for (int j = 0; j < TRIPS; ++j) v[j] = w[min(k0 + ty + 8 * j, K - 1) * N + min(n0 + tx, N - 1)];
   }
   {
     uint32_t m[kWeightSlabs / 8];
@@ -395,8 +391,7 @@ __device__ __forceinline__ void quantize_weights_body(
 #pragma unroll
     for (int c = 0; c < 4; ++c) s[c] = scale_of(4 * vx + c);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (32 * j >= rows) continue;
+    for (int j = 0; j < TRIPS / 4; ++j) {
       const int kk = vy + 32 * j;
       const int64_t k = k0 + kk, n = n0 + 4 * vx;
       const bool live = k < K && n < N;   // four channels at once: N is a multiple of four
@@ -414,23 +409,19 @@ __device__ __forceinline__ void quantize_weights_body(
   } else {
     const float s = scale_of(tx);
     const int64_t n = n0 + tx;
-    auto make = [&](auto count) {
 #pragma unroll
-      for (int j = 0; j < decltype(count)::value; ++j) {
-        const int kk = ty + 8 * j;
-        const int64_t k = k0 + kk;
-        int code = 0;
-        if (n < N && k < K) {
-          bool pass;
-          code = quant_code(v[j], s, fq, pass);
-          if (wq_kn) wq_kn[k * N + n] = static_cast<int8_t>(code);
-          if (mask_w && pass) mark(k * N + n);
-        }
-        tile[tx][kk] = static_cast<int8_t>(code);
+    for (int j = 0; j < TRIPS; ++j) {
+      const int kk = ty + 8 * j;
+      const int64_t k = k0 + kk;
+      int code = 0;
+      if (n < N && k < K) {
+        bool pass;
+        code = quant_code(v[j], s, fq, pass);
+        if (wq_kn) wq_kn[k * N + n] = static_cast<int8_t>(code);
+        if (mask_w && pass) mark(k * N + n);
       }
-    };
-    if (rows > 16) make(std::integral_constant<int, 8>{});
-    else make(std::integral_constant<int, 2>{});
+      tile[tx][kk] = static_cast<int8_t>(code);
+    }
   }
   __syncthreads();
   // 32 rows x (64 | 32) output bytes
@@ -451,7 +442,7 @@ __device__ __forceinline__ void quantize_weights_body(
       for (int b = 0; b < 4; ++b) t |= byte_of(rn, 4 * jw + b) << (8 * b);
       *reinterpret_cast<uint32_t *>(wq_packed + (n0 + rn) * row_bytes + b0 + 4 * jw) = t;
     }
-  } else if (row_bytes - b0 <= 16) {
+  } else if (TRIPS == 2) {
     const int rn = vy;
     for (int jb = vx; jb < row_bytes - b0; jb += 8)
       if (n0 + rn < N) wq_packed[(n0 + rn) * row_bytes + b0 + jb] = static_cast<uint8_t>(byte_of(rn, jb));
@@ -467,7 +458,7 @@ __device__ __forceinline__ void quantize_weights_body(
   // forward needs no re-ordering pass of its own.  Only requested for whole tiles
   // (N % 32 == 0, K % 64 == 0).  This block's tile is exactly one packed fragment (32
   // channels x two 32-deep steps) or two int8 fragments.
-  if (wfrag) {
+  if (TRIPS == 8 && wfrag) {
     const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
     if (packed) {
       if (threadIdx.x < 64) {
@@ -521,9 +512,19 @@ struct WeightJobDev {
 __device__ __forceinline__ void wabsmax_partial(const WeightJobDev &j, unsigned block) {
   wabsmax_partial_body(j.w, j.K, j.N, j.rows_per_slab, j.vec4_max, j.part, block % j.gx1, block / j.gx1);
 }
+// SHORT: tiles of few rows have forms of their own (launches that hold nothing but weights; beside a layer's activations the choice costs each
+// block more than it saves: 2000 x 300 -> 31, the whole layer, 9.9 us without it, 10.1 with).
+template <bool SHORT>
 __device__ __forceinline__ void quantize_weights(const WeightJobDev &j, int32_t *dev_status, unsigned block) {
-  quantize_weights_body(j.w, j.K, j.N, j.qmax, j.packed, j.part, j.slabs, j.wq_packed, j.s_w, j.wq_kn, j.mask_w,
-                        dev_status, j.wfrag, j.vec4, block % j.gx2, block / j.gx2);
+  const unsigned bx = block % j.gx2, by = block / j.gx2;
+  auto tile = [&](auto trips) {
+    quantize_weights_body<decltype(trips)::value>(j.w, j.K, j.N, j.qmax, j.packed, j.part, j.slabs, j.wq_packed, j.s_w, j.wq_kn, j.mask_w,
+                                                  dev_status, j.wfrag, j.vec4, bx, by);
+  };
+  const int64_t rows = SHORT ? j.K - static_cast<int64_t>(by) * kWChunk : kWChunk;   // uniform
+  if (rows > 32) tile(std::integral_constant<int, 8>{});
+  else if (rows > 16) tile(std::integral_constant<int, 4>{});
+  else tile(std::integral_constant<int, 2>{});
 }
 
 // Several weight matrices in one launch pair: a one-dimensional grid holds every matrix's own blocks one matrix
@@ -564,7 +565,7 @@ __global__ __launch_bounds__(kThreads) void quantize_weights_group_kernel(const 
   if (block >= jobs.first2[kWeightJobsMax]) return;
   const int ji = job_of_block(jobs.first2, jobs.n, block);
   const WeightJobDev &j = jobs.job[ji];
-  quantize_weights(j, dev_status, block - jobs.first2[ji]);
+  quantize_weights<true>(j, dev_status, block - jobs.first2[ji]);
 }
 
 // One matrix: its description is an argument by itself, not one trip behind the list's block numbers (both launches, 64 x 1000 7.4 -> 7.0 us).
@@ -574,7 +575,7 @@ __global__ __launch_bounds__(kThreads) void wabsmax_partial_kernel(const WeightJ
 }
 __global__ __launch_bounds__(kThreads) void quantize_weights_kernel(const WeightJobDev j, unsigned blocks, int32_t *dev_status) {
   const unsigned block = block_number();
-  if (block < blocks) quantize_weights(j, dev_status, block);
+  if (block < blocks) quantize_weights<true>(j, dev_status, block);
 }
 
 // The activations and the weights of one dense layer in one launch pair: neither needs the other's abs-max, and at the sizes of a
@@ -598,7 +599,7 @@ __global__ __launch_bounds__(kThreads) void absmax_dense_kernel(const FlatJobDev
 __global__ __launch_bounds__(kThreads) void quantize_dense_kernel(const FlatJobDev f, const WeightJobDev j, unsigned weight_blocks,
                                                                   int32_t *dev_status) {
   const unsigned block = block_number();
-  if (block < weight_blocks) quantize_weights(j, dev_status, block);
+  if (block < weight_blocks) quantize_weights<false>(j, dev_status, block);
   else if (block - weight_blocks < static_cast<unsigned>(f.blocks))
     quantize_flat_body(f.x, f.n, f.per4, f.partial, f.blocks, f.qmax, f.q, f.scale, dev_status, block - weight_blocks, f.blocks);
 }
